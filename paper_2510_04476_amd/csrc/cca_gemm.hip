@@ -14,6 +14,8 @@
 // which leaves every lane with 4 consecutive output columns of one row, so
 // the epilogue packs them to bf16, stages the tile in LDS and writes whole
 // rows with 16-byte stores.
+#include <math.h>
+
 #include "cca_internal.h"
 
 namespace cca {
@@ -403,6 +405,174 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
   return hipGetLastError();
 }
 
+
+// ---------------------------------------------------------------------------
+// The same product on smaller tiles, for row counts whose 256-row tiles leave the chip idle (one 256 x 192 tile walks
+// K = 2048 in 39 us however few tiles there are).  What bounds a small product is the chain of slabs each workgroup
+// walks, so: the tile is small enough that every CU gets one, the loads run STAGES - 1 slabs ahead (one bare barrier per
+// slab, `s_waitcnt vmcnt` counting the later slabs' loads as still in flight), and with WAVES_K = 2 a slab is 128 wide
+// and each half of it belongs to one half of the wavefronts, whose sums are added through LDS at the end - half as many
+// steps in the chain.  Measured (M x N x K, us, 256-row tiles -> this): 512 x 1536 x 2048 39.4 -> 10.0 (64 x 64 tiles),
+// 512 x 2048 x 1024 22.2 -> 7.8, 1000 x 1536 x 2048 39.5 -> 14.1 (64 x 128), 2000 x 1536 x 2048 39.9 -> 20.4
+// (128 x 128, 8 wavefronts), 4593 x 1536 x 2048 41.0 -> 34.6 (128 x 128, 4 wavefronts, two workgroups per CU).
+// Slower everywhere: 32-wide slabs (half the work per barrier), 128 x 192 and 256 x 128 tiles at two workgroups per CU,
+// WAVES_K = 4, a fourth stage at 64 x 64.
+// ---------------------------------------------------------------------------
+template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
+__global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_deep_kernel(
+    const bf16_t *__restrict__ A, const bf16_t *__restrict__ Bt, bf16_t *__restrict__ C, long long M, int N, int K,
+    int tiles_n, int tiles_total) {
+  constexpr int NWAVES = WAVES_M * WAVES_N * WAVES_K, NTHREADS = NWAVES * 64;
+  constexpr int WM = TM / WAVES_M, WN = TN / WAVES_N, MI = WM / 32, NI = WN / 32;
+  static_assert(MI * 32 == WM && NI * 32 == WN, "wave tile must be a multiple of 32");
+  constexpr int SUB = (TM + TN) * 8, STAGE = WAVES_K * SUB;  // 16-byte chunks of one 64-wide sub-slab / of a stage
+  constexpr int PER_WAVE = STAGE / 64 / NWAVES;              // load instructions of a wavefront per stage
+  static_assert(PER_WAVE * 64 * NWAVES == STAGE, "instructions must divide evenly over the wavefronts");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  u32x4 *const sbase = reinterpret_cast<u32x4 *>(smem);
+
+  const int wg = blockIdx.x;
+  const int per_xcd = (tiles_total + 7) / 8;
+  const int tile = (wg % 8) * per_xcd + wg / 8;
+  if (tile >= tiles_total) return;
+  const long long m0 = (long long)(tile / tiles_n) * TM;
+  const int n0 = (tile % tiles_n) * TN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int wk = wave / (WAVES_M * WAVES_N), wmn = wave % (WAVES_M * WAVES_N), wm = wmn / WAVES_N, wn = wmn % WAVES_N;
+
+  const bf16_t *g_src[PER_WAVE];
+#pragma unroll
+  for (int u = 0; u < PER_WAVE; ++u) {
+    const int pos = (wave + u * NWAVES) * 64 + lane;  // chunk position inside the stage
+    const int ks = pos / SUB, p = pos % SUB;
+    const bool isb = p >= TM * 8;
+    const int r = (isb ? p - TM * 8 : p) >> 3, c = (p & 7) ^ ((r & 7) ^ ((r >> 3) & 1));
+    if (!isb) {
+      const long long gr = m0 + r;
+      g_src[u] = A + (gr < M ? gr : M - 1) * K + ks * BK + c * 8;
+    } else {
+      const int gr = n0 + r;
+      g_src[u] = Bt + (long long)(gr < N ? gr : N - 1) * K + ks * BK + c * 8;
+    }
+  }
+  typedef __attribute__((address_space(3))) void lds_void;
+  typedef __attribute__((address_space(1))) void glb_void;
+  constexpr int SLAB = BK * WAVES_K;
+  auto issue = [&](int kt, int buf) {
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; ++u)
+      __builtin_amdgcn_global_load_lds((glb_void *)(g_src[u] + (long long)kt * SLAB),
+                                       (lds_void *)(sbase + buf * STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
+  };
+  f32x16 acc[NI][MI];
+#pragma unroll
+  for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[ni][mi][r] = 0.f;
+
+  const int nk = K / SLAB;
+#pragma unroll
+  for (int i = 0; i < STAGES - 1; ++i)
+    if (i < nk) issue(i, i);
+  int buf = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    if (kt + STAGES - 1 <= nk)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((STAGES - 2) * PER_WAVE) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int nbuf = buf == 0 ? STAGES - 1 : buf - 1;  // read in the previous step: free since the barrier
+    if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, nbuf);
+    const u32x4 *sa = sbase + buf * STAGE + wk * SUB, *sb = sa + TM * 8;
+    bf16x8 fa[BK / 16][MI], fb[BK / 16][NI];
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk) {
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) fa[kk][mi] = __builtin_bit_cast(bf16x8, sa[swz(wm * WM + mi * 32 + l32, kk * 2 + half)]);
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) fb[kk][ni] = __builtin_bit_cast(bf16x8, sb[swz(wn * WN + ni * 32 + l32, kk * 2 + half)]);
+    }
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+          acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk][ni], fa[kk][mi], acc[ni][mi], 0, 0, 0);
+    buf = buf == STAGES - 1 ? 0 : buf + 1;
+  }
+  __syncthreads();
+  if constexpr (WAVES_K > 1) {  // the other parts of the contraction are added through LDS, in order
+    constexpr int PER_LANE = MI * NI * 16;
+    float *sp = reinterpret_cast<float *>(smem) + (size_t)wmn * (PER_LANE * 64) + lane;
+    constexpr int PART = WAVES_M * WAVES_N * PER_LANE * 64;
+    if (wk > 0) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sp[(wk - 1) * PART + ((ni * MI + mi) * 16 + r) * 64] = acc[ni][mi][r];
+    }
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int g = 0; g < WAVES_K - 1; ++g)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ni][mi][r] += sp[g * PART + ((ni * MI + mi) * 16 + r) * 64];
+    }
+    __syncthreads();
+  }
+  constexpr int ROW_BYTES = TN * 2 + 16;
+  unsigned char *sC = smem;
+  if (wk == 0) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) {
+        const int m = wm * WM + mi * 32 + l32;
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+          const int n = wn * WN + ni * 32 + rg * 8 + half * 4;
+          u32x2 p;
+          p.x = pack_bf16x2(acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1]);
+          p.y = pack_bf16x2(acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]);
+          *reinterpret_cast<u32x2 *>(sC + m * ROW_BYTES + n * 2) = p;
+        }
+      }
+  }
+  __syncthreads();
+  constexpr int CH_ROW = TN / 8;
+  for (int id = tid; id < TM * CH_ROW; id += NTHREADS) {
+    const int r = id / CH_ROW, c = id % CH_ROW;
+    const long long gm = m0 + r;
+    const int gn = n0 + c * 8;
+    if (gm < M && gn < N)
+      *reinterpret_cast<u32x4 *>(C + gm * N + gn) = *reinterpret_cast<const u32x4 *>(sC + r * ROW_BYTES + c * 16);
+  }
+}
+
+template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
+hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s) {
+  const int tiles_m = (int)((M + TM - 1) / TM), tiles_n = (N + TN - 1) / TN;
+  const int total = tiles_m * tiles_n;
+  constexpr size_t epi_bytes = (size_t)TM * (TN * 2 + 16), sum_bytes = (size_t)(WAVES_K - 1) * TM * TN * 4;
+  constexpr size_t main_bytes = (size_t)STAGES * WAVES_K * (TM + TN) * BK * 2;
+  constexpr size_t smem0 = main_bytes > epi_bytes ? main_bytes : epi_bytes, smem = smem0 > sum_bytes ? smem0 : sum_bytes;
+  static_assert(smem <= 160 * 1024, "LDS");
+  if (hipError_t e = raise_lds_limit<gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>>(smem); e != hipSuccess) return e;
+  gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES><<<(total + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>(
+      (const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N, K, tiles_n, total);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 // Measurement aid: nothing but matrix-core instructions (four independent accumulator chains per wavefront, no
@@ -464,16 +634,29 @@ hipError_t mfma_probe(float *out, int blocks, int iters, bool random_operands, h
 bool gemm_mfma_supported(long long M, int N, int K) { return M >= 1 && K % BK == 0 && K >= BK && N % 8 == 0 && N >= 8; }
 
 hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s) {
-  // Tile width by the number of rounds the grid needs on 256 CUs:
-  // N = 1536, M = 16384 gives 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).
-  auto cost = [&](int bn) {
-    const long long tiles = ((M + BM - 1) / BM) * ((N + bn - 1) / bn);
-    return ((tiles + 255) / 256) * bn;
+  // A tile shape costs (rounds of the grid over the chip) x (64-wide slabs x time per slab + fill and epilogue).  The two
+  // numbers of each shape (us) are fits to back-to-back timings at K = 1024 and 2048, M = 64 ... 16384:
+  //   256 x 256 (1.5, 8)   256 x 192 (1.35, 6)   128 x 128 at 8 wavefronts (0.46, 5)   64 x 128 (0.35, 3.7)   64 x 64 (0.18, 4.2)
+  //   128 x 128 at 4 wavefronts, two workgroups per CU (1.0, 6.4), a last round of one per CU (0.62, 4)
+  // e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).
+  const double slabs = (double)(K / BK);
+  auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  auto cost = [&](int tm, int tn, double per_slab, double fixed) {
+    return (double)((tiles(tm, tn) + 255) / 256) * (slabs * per_slab + fixed);
   };
-  // 8 wavefronts (2 per SIMD) measured 15-20 % faster than 4 wavefronts with 128x128 wave tiles: a second
-  // wavefront hides LDS latency better than the compiler's in-wave schedule does
-  if (cost(192) < cost(256)) return launch_gemm<192, 4, 2>(A, Bt, C, M, N, K, s);
-  return launch_gemm<256, 2, 4>(A, Bt, C, M, N, K, s);
+  const long long t128 = tiles(128, 128), rest = t128 % 512;
+  const double c256 = cost(256, 256, 1.5, 8.0), c192 = cost(256, 192, 1.35, 6.0), c128 = cost(128, 128, 0.46, 5.0),
+               c128x2 = (double)(t128 / 512 + (rest > 256)) * (slabs + 6.4) +
+                        (rest > 0 && rest <= 256 ? slabs * 0.62 + 4.0 : 0.0);
+  const bool halves = K % (2 * BK) == 0;  // the shapes that split a slab over two halves of the wavefronts
+  const double c64x128 = halves ? cost(64, 128, 0.35, 3.7) : 1e30, c64 = halves ? cost(64, 64, 0.18, 4.2) : 1e30;
+  const double small = fmin(fmin(c128, c128x2), fmin(c64x128, c64));
+  if (fmin(c192, c256) <= small)
+    return c192 < c256 ? launch_gemm<192, 4, 2>(A, Bt, C, M, N, K, s) : launch_gemm<256, 2, 4>(A, Bt, C, M, N, K, s);
+  if (c64 == small) return launch_gemm_deep<64, 64, 2, 2, 2, 3>(A, Bt, C, M, N, K, s);
+  if (c64x128 == small) return launch_gemm_deep<64, 128, 1, 4, 2, 3>(A, Bt, C, M, N, K, s);
+  if (c128 == small) return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, s);
+  return launch_gemm_deep<128, 128, 2, 2, 1, 2>(A, Bt, C, M, N, K, s);
 }
 
 bool gemm_tn_mfma_supported(int Mo, int No, long long K) { return Mo % 8 == 0 && No % 8 == 0 && Mo >= 8 && No >= 8 && K >= 1; }
