@@ -16,6 +16,8 @@
 // rows with 16-byte stores.
 #include <math.h>
 
+#include <type_traits>
+
 #include "cca_internal.h"
 
 namespace cca {
@@ -39,6 +41,70 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   bf16x2 v = {(__bf16)lo, (__bf16)hi};
   return __builtin_bit_cast(uint32_t, v);
+}
+
+// The workgroups of a small tile may split the contraction over WAVES_K groups of wavefronts: the sums of groups 1, 2, ...
+// are added to group 0's through LDS, in order.  The tiles are no longer read when this is called.
+template <int WAVES_MN, int WAVES_K, int NI, int MI>
+__device__ __forceinline__ void add_wave_parts(f32x16 (&acc)[NI][MI], unsigned char *smem, int wk, int wmn, int lane) {
+  if constexpr (WAVES_K > 1) {
+    constexpr int PER_LANE = MI * NI * 16, PART = WAVES_MN * PER_LANE * 64;
+    float *sp = reinterpret_cast<float *>(smem) + (size_t)wmn * (PER_LANE * 64) + lane;
+    if (wk > 0) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sp[(wk - 1) * PART + ((ni * MI + mi) * 16 + r) * 64] = acc[ni][mi][r];
+    }
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int g = 0; g < WAVES_K - 1; ++g)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ni][mi][r] += sp[g * PART + ((ni * MI + mi) * 16 + r) * 64];
+    }
+    __syncthreads();
+  }
+}
+
+// acc[ni][mi][r] = C[m][n] with m = wm*32*MI + mi*32 + l32 and n = wn*32*NI + ni*32 + 8*(r/4) + 4*half + r%4 of the tile
+// at (m0, n0): packed to bf16, staged in LDS and written as whole rows.  `owner`: this wavefront holds sums to store.
+template <int TM, int TN, int NTHREADS, int NI, int MI>
+__device__ __forceinline__ void store_tile_bf16(const f32x16 (&acc)[NI][MI], unsigned char *smem, bool owner, int wm, int wn,
+                                                int tid, bf16_t *__restrict__ C, long long m0, long long M, int n0, int N) {
+  constexpr int ROW_BYTES = TN * 2 + 16;  // padded row: 8-byte column writes of 32 rows hit distinct banks
+  const int l32 = tid & 31, half = (tid >> 5) & 1;
+  if (owner) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) {
+        const int m = (wm * MI + mi) * 32 + l32;
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+          const int n = (wn * NI + ni) * 32 + rg * 8 + half * 4;
+          u32x2 p;
+          p.x = pack_bf16x2(acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1]);
+          p.y = pack_bf16x2(acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]);
+          *reinterpret_cast<u32x2 *>(smem + m * ROW_BYTES + n * 2) = p;
+        }
+      }
+  }
+  __syncthreads();
+  constexpr int CH_ROW = TN / 8;  // 16-byte chunks per tile row
+  for (int id = tid; id < TM * CH_ROW; id += NTHREADS) {
+    const int r = id / CH_ROW, c = id % CH_ROW;
+    const long long gm = m0 + r;
+    const int gn = n0 + c * 8;
+    if (gm < M && gn < N)
+      *reinterpret_cast<u32x4 *>(C + gm * N + gn) = *reinterpret_cast<const u32x4 *>(smem + r * ROW_BYTES + c * 16);
+  }
 }
 
 template <int BN, int WAVES_M, int WAVES_N>
@@ -160,33 +226,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   }
-  // Epilogue.  acc[ni][mi][r] = C[m][n] with m = wm*WM + mi*32 + l32 and
-  // n = wn*WN + ni*32 + 8*(r/4) + 4*half + r%4.
-  constexpr int ROW_BYTES = BN * 2 + 16;  // padded row: 8-byte column writes of 32 rows hit distinct banks
-  unsigned char *sC = smem;
-#pragma unroll
-  for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-      const int m = wm * WM + mi * 32 + l32;
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int n = wn * WN + ni * 32 + rg * 8 + half * 4;
-        u32x2 p;
-        p.x = pack_bf16x2(acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1]);
-        p.y = pack_bf16x2(acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]);
-        *reinterpret_cast<u32x2 *>(sC + m * ROW_BYTES + n * 2) = p;
-      }
-    }
-  __syncthreads();
-  constexpr int CH_ROW = BN / 8;  // 16-byte chunks per tile row
-  for (int id = tid; id < BM * CH_ROW; id += NTHREADS) {
-    const int r = id / CH_ROW, c = id % CH_ROW;
-    const long long gm = m0 + r;
-    const int gn = n0 + c * 8;
-    if (gm < M && gn < N)
-      *reinterpret_cast<u32x4 *>(C + gm * N + gn) = *reinterpret_cast<const u32x4 *>(sC + r * ROW_BYTES + c * 16);
-  }
+  store_tile_bf16<BM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N);
 }
 
 // Up to two independent transposes in one launch (both projection weights of a forward pass): workgroups
@@ -358,6 +398,161 @@ __global__ __launch_bounds__(512) void gemm_bf16_tn_kernel(const bf16_t *__restr
     }
 }
 
+// The weight-gradient product on smaller tiles, for token counts whose 256 x 256 tiles would have to be split many ways
+// over K to fill the chip (2 x 512 tokens, 2048 x 1536: 50 MB of partial sums written and read back for 6 MB of result).
+// One workgroup walks all of K, so the result is rounded and stored directly: no partial sums, no second kernel.  Tiles
+// travel global -> LDS directly, STAGES - 1 slabs ahead; LDS rows are unpadded (a direct load fills 1 KB at a time), so
+// the 64-byte column group a transposing read touches in 4 consecutive rows is XOR-swizzled into 4 different bank groups
+// instead.  With WAVES_K = 2 each half of the wavefronts takes 32 of a slab's 64 tokens.
+template <int W>
+__device__ __forceinline__ int swz_tn(int r, int c) {  // 16-byte chunk c of token row r in a [tokens][W] tile
+  return r * (W / 8) + (c ^ (W == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2));
+}
+
+template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
+__device__ __forceinline__ void gemm_bf16_tn_deep_body(
+    const bf16_t *__restrict__ A, long long lda, const bf16_t *__restrict__ Bm, long long ldb, bf16_t *__restrict__ C,
+    int Mo, int No, long long K, int tiles_n, int tiles_total, unsigned char *smem) {
+  static_assert((TM == 64 || TM == 128) && (TN == 64 || TN == 128), "swz_tn");
+  constexpr int NWAVES = WAVES_M * WAVES_N * WAVES_K, NTHREADS = NWAVES * 64;
+  constexpr int MI = TM / WAVES_M / 32, NI = TN / WAVES_N / 32;
+  constexpr int A_CH = BK * TM / 8, STAGE = BK * (TM + TN) / 8;  // 16-byte chunks of the A part / of a stage
+  constexpr int PER_WAVE = STAGE / 64 / NWAVES;
+  static_assert(PER_WAVE * 64 * NWAVES == STAGE && A_CH % 64 == 0, "instructions must divide evenly over the wavefronts");
+  u32x4 *const sbase = reinterpret_cast<u32x4 *>(smem);
+
+  const int wg = blockIdx.x;
+  const int per_xcd = (tiles_total + 7) / 8;
+  const int tile = (wg % 8) * per_xcd + wg / 8;
+  if (tile >= tiles_total) return;
+  const int m0 = (tile / tiles_n) * TM, n0 = (tile % tiles_n) * TN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+  const int wk = wave / (WAVES_M * WAVES_N), wmn = wave % (WAVES_M * WAVES_N), wm = wmn / WAVES_N, wn = wmn % WAVES_N;
+
+  // Load instruction wave + u * NWAVES fills 64 chunks of the stage; columns past the matrix edge are read from column 0
+  // (they only feed outputs that are never stored), rows past K from the last row (zeroed in LDS before they are used).
+  const bf16_t *g_col[PER_WAVE];
+  long long g_ld[PER_WAVE];
+  int g_row[PER_WAVE];
+#pragma unroll
+  for (int u = 0; u < PER_WAVE; ++u) {
+    const int pos = (wave + u * NWAVES) * 64 + lane;
+    if (pos < A_CH) {
+      const int r = pos / (TM / 8), c = (pos % (TM / 8)) ^ (TM == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2);
+      g_row[u] = r;
+      g_ld[u] = lda;
+      g_col[u] = A + (m0 + c * 8 < Mo ? m0 + c * 8 : 0);
+    } else {
+      const int p = pos - A_CH, r = p / (TN / 8), c = (p % (TN / 8)) ^ (TN == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2);
+      g_row[u] = r;
+      g_ld[u] = ldb;
+      g_col[u] = Bm + (n0 + c * 8 < No ? n0 + c * 8 : 0);
+    }
+  }
+  typedef __attribute__((address_space(3))) void lds_void;
+  typedef __attribute__((address_space(1))) void glb_void;
+  auto issue = [&](long long kt, int buf) {
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; ++u) {
+      const long long row = kt * BK + g_row[u];
+      __builtin_amdgcn_global_load_lds((glb_void *)(g_col[u] + (row < K ? row : K - 1) * g_ld[u]),
+                                       (lds_void *)(sbase + buf * STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
+    }
+  };
+  f32x16 acc[NI][MI];
+#pragma unroll
+  for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[ni][mi][r] = 0.f;
+
+  // a lane's place in a transposing read: row 4*half + (lane & 15)/4 of each group of 8, 8 bytes of a 64-byte column group
+  const int tr = 4 * half + ((lane & 15) >> 2), tc = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1), tb = (lane & 1) * 8;
+  const int nk = (int)((K + BK - 1) / BK), nfull = (int)(K / BK);
+#pragma unroll
+  for (int i = 0; i < STAGES - 1; ++i)
+    if (i < nk) issue(i, i);
+  int buf = 0;
+  auto multiply = [&]() __attribute__((always_inline)) {  // the slab in stage `buf`
+    const unsigned char *pa = smem + (size_t)buf * STAGE * 16, *pb = pa + A_CH * 16;
+    constexpr int STEPS = BK / 16 / WAVES_K;
+    bf16x8 fa[STEPS][MI], fb[STEPS][NI];
+#pragma unroll
+    for (int k2 = 0; k2 < STEPS; ++k2) {
+      const int r0 = (wk * STEPS + k2) * 16 + tr;
+      auto frag = [&](const unsigned char *base, auto width, int c0) {
+        constexpr int W = decltype(width)::value;
+        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(base + swz_tn<W>(r0, c0 / 8 + tc) * 16 + tb));
+        const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(base + swz_tn<W>(r0 + 8, c0 / 8 + tc) * 16 + tb));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) fa[k2][mi] = frag(pa, std::integral_constant<int, TM>{}, (wm * MI + mi) * 32);
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) fb[k2][ni] = frag(pb, std::integral_constant<int, TN>{}, (wn * NI + ni) * 32);
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < STEPS; ++k2)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+          acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[k2][ni], fa[k2][mi], acc[ni][mi], 0, 0, 0);
+  };
+  for (int kt = 0; kt < nfull; ++kt) {
+    if (kt + STAGES - 1 <= nk)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((STAGES - 2) * PER_WAVE) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, buf == 0 ? STAGES - 1 : buf - 1);
+    multiply();
+    buf = buf == STAGES - 1 ? 0 : buf + 1;
+  }
+  if (nfull < nk) {  // a short last slab: its missing tokens are zeroed
+    const int live = (int)(K - (long long)nfull * BK);
+    const u32x4 zero = {0, 0, 0, 0};
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    for (int id = tid; id < STAGE; id += NTHREADS) {
+      const int r = id < A_CH ? id / (TM / 8) : (id - A_CH) / (TN / 8);
+      if (r >= live) sbase[buf * STAGE + id] = zero;
+    }
+    __syncthreads();
+    multiply();
+  }
+  __syncthreads();
+  add_wave_parts<WAVES_M * WAVES_N, WAVES_K>(acc, smem, wk, wmn, lane);
+  store_tile_bf16<TM, TN, NTHREADS>(acc, smem, wk == 0, wm, wn, tid, C, (long long)m0, (long long)Mo, n0, No);
+}
+
+// (a body inlined with restrict arguments: without them the compiler makes every transposing LDS read wait for the loads
+// into LDS in flight)
+template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
+__global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_tn_deep_kernel(
+    const bf16_t *__restrict__ A, long long lda, const bf16_t *__restrict__ Bm, long long ldb, bf16_t *__restrict__ C,
+    int Mo, int No, long long K, int tiles_n, int tiles_total) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  gemm_bf16_tn_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, lda, Bm, ldb, C, Mo, No, K, tiles_n, tiles_total, smem);
+}
+
+template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
+hipError_t launch_tn_deep(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No, long long K,
+                          hipStream_t s) {
+  const int tiles_m = (Mo + TM - 1) / TM, tiles_n = (No + TN - 1) / TN, total = tiles_m * tiles_n;
+  constexpr size_t epi_bytes = (size_t)TM * (TN * 2 + 16), sum_bytes = (size_t)(WAVES_K - 1) * TM * TN * 4;
+  constexpr size_t main_bytes = (size_t)STAGES * BK * (TM + TN) * 2;
+  constexpr size_t smem0 = main_bytes > epi_bytes ? main_bytes : epi_bytes, smem = smem0 > sum_bytes ? smem0 : sum_bytes;
+  static_assert(smem <= 160 * 1024, "LDS");
+  constexpr auto kernel = gemm_bf16_tn_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>;
+  if (hipError_t e = raise_lds_limit<kernel>(smem); e != hipSuccess) return e;
+  kernel<<<(total + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb,
+                                                                            (bf16_t *)C, Mo, No, K, tiles_n, total);
+  return hipGetLastError();
+}
+
 // C[i] = bf16(sum_s part[s][i]), 4 elements per thread, fixed summation order
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, int splits, long long n,
                                                            bf16_t *__restrict__ C) {
@@ -375,8 +570,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 }
 
 // Number of K splits: minimise (rounds on 256 CUs) x (slabs per split) x (time of one 256x256x64 slab at ~70 % of
-// the MFMA rate, 1.2 us) + the traffic of the fp32 partial sums (written once, read once, ~3 TB/s).
-int tn_splits(int Mo, int No, long long K) {
+// the MFMA rate, 1.2 us) + the traffic of the fp32 partial sums (written once, read once, ~3 TB/s).  `us`: that minimum.
+int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
   const long long tiles = (long long)((Mo + BM - 1) / BM) * ((No + TN_BN - 1) / TN_BN);
   const long long nk = (K + BK - 1) / BK;
   int best = 1;
@@ -388,6 +583,7 @@ int tn_splits(int Mo, int No, long long K) {
     const double t = (double)((tiles * sp + 255) / 256) * (double)per * 1.2e-6 + (double)sp * Mo * No * 8.0 / 3e12;
     if (best_t < 0 || t < best_t) best_t = t, best = sp;
   }
+  if (us) *us = best_t * 1e6;
   return best;
 }
 
@@ -505,58 +701,8 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_d
     buf = buf == STAGES - 1 ? 0 : buf + 1;
   }
   __syncthreads();
-  if constexpr (WAVES_K > 1) {  // the other parts of the contraction are added through LDS, in order
-    constexpr int PER_LANE = MI * NI * 16;
-    float *sp = reinterpret_cast<float *>(smem) + (size_t)wmn * (PER_LANE * 64) + lane;
-    constexpr int PART = WAVES_M * WAVES_N * PER_LANE * 64;
-    if (wk > 0) {
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sp[(wk - 1) * PART + ((ni * MI + mi) * 16 + r) * 64] = acc[ni][mi][r];
-    }
-    __syncthreads();
-    if (wk == 0) {
-#pragma unroll
-      for (int g = 0; g < WAVES_K - 1; ++g)
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-          for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[ni][mi][r] += sp[g * PART + ((ni * MI + mi) * 16 + r) * 64];
-    }
-    __syncthreads();
-  }
-  constexpr int ROW_BYTES = TN * 2 + 16;
-  unsigned char *sC = smem;
-  if (wk == 0) {
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        const int m = wm * WM + mi * 32 + l32;
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int n = wn * WN + ni * 32 + rg * 8 + half * 4;
-          u32x2 p;
-          p.x = pack_bf16x2(acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1]);
-          p.y = pack_bf16x2(acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]);
-          *reinterpret_cast<u32x2 *>(sC + m * ROW_BYTES + n * 2) = p;
-        }
-      }
-  }
-  __syncthreads();
-  constexpr int CH_ROW = TN / 8;
-  for (int id = tid; id < TM * CH_ROW; id += NTHREADS) {
-    const int r = id / CH_ROW, c = id % CH_ROW;
-    const long long gm = m0 + r;
-    const int gn = n0 + c * 8;
-    if (gm < M && gn < N)
-      *reinterpret_cast<u32x4 *>(C + gm * N + gn) = *reinterpret_cast<const u32x4 *>(sC + r * ROW_BYTES + c * 16);
-  }
+  add_wave_parts<WAVES_M * WAVES_N, WAVES_K>(acc, smem, wk, wmn, lane);
+  store_tile_bf16<TM, TN, NTHREADS>(acc, smem, wk == 0, wm, wn, tid, C, m0, M, n0, N);
 }
 
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
@@ -667,9 +813,27 @@ size_t gemm_tn_scratch_bytes(int Mo, int No, long long K) {
 
 hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No,
                              long long K, float *part, hipStream_t s) {
+  // Small tiles without partial sums or 256 x 256 tiles split over K, by estimated time (us).  Fits to back-to-back
+  // timings over K = 64 ... 16384 tokens of (rounds) x (slabs x time per slab + fill and epilogue): 128 x 128 (0.63, 3.5),
+  // 64 x 128 (0.50, 3.0), 64 x 64 (0.34, 1.5) up to one workgroup per CU and (0.60, 1.5) at two; the split form takes 4 us
+  // more than the estimate of tn_splits.  2048 x 1536 over 1024 tokens 30.8 -> 13.9 us, over 4000 53.1 -> 43.4, over 8000
+  // split 68.6 against 81.9; 1024 x 2048 over 1024 tokens 31.3 -> 11.1, over 16384 split 85.9 against 132.8.
+  const double slabs = (double)((K + BK - 1) / BK);
+  auto tiles = [&](int tm, int tn) { return (long long)((Mo + tm - 1) / tm) * ((No + tn - 1) / tn); };
+  double split_us;
+  const int splits = tn_splits(Mo, No, K, &split_us);
+  const long long t64 = tiles(64, 64);
+  const double c128 = (double)((tiles(128, 128) + 255) / 256) * (slabs * 0.63 + 3.5),
+               c64x128 = (double)((tiles(64, 128) + 255) / 256) * (slabs * 0.50 + 3.0),
+               c64 = t64 <= 256 ? slabs * 0.34 + 1.5 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
+  const double small = fmin(c128, fmin(c64x128, c64));
+  if (small < split_us + 4.0) {
+    if (c64 == small) return launch_tn_deep<64, 64, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
+    if (c64x128 == small) return launch_tn_deep<64, 128, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
+    return launch_tn_deep<128, 128, 2, 4, 1, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
+  }
   const int tiles_m = (Mo + BM - 1) / BM, tiles_n = (No + TN_BN - 1) / TN_BN;
   const int total = tiles_m * tiles_n, per_xcd = (total + 7) / 8;
-  const int splits = tn_splits(Mo, No, K);
   const long long nk = (K + BK - 1) / BK;
   const int per = (int)((nk + splits - 1) / splits);
   constexpr size_t smem = 2ull * 2 * BK * TN_ROW;

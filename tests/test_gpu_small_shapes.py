@@ -47,3 +47,22 @@ def test_projection_tiles(M, Hq, Hk, dh, E):
     torch.cuda.synchronize()
     check_product(lat[0], x[0].double() @ w_down.double(), E)
     check_product(out[0], o[0].double() @ w_out.double(), cfg.e_q)
+
+
+# token rows x (query heads, head width, E): d W_out (e_q, E) = o^T d_out on every tile shape of the weight-gradient GEMM
+# (64 x 64, 64 x 128, 128 x 128, split 256 x 256), with no, one and a few tokens in the last slab of 64
+WGRAD_CASES = [(1, 1, 64, 64), (63, 3, 64, 256), (1000, 8, 64, 1024), (64, 8, 128, 2048), (129, 8, 128, 2048),
+               (1023, 8, 128, 2048), (512, 12, 128, 2048), (2001, 12, 128, 2048), (9001, 8, 128, 2048)]
+
+
+@pytest.mark.parametrize("rows,Hq,dh,E", WGRAD_CASES)
+def test_weight_gradient_tiles(rows, Hq, dh, E):
+    say("weight gradient", rows, Hq, dh, E)
+    cfg = P.CCAConfig(B=1, T=rows, d_model=E, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, flags=P.CCA_FLAGS_MHA)
+    w = P.CCAWeights(w_down=rnd(E, cfg.n_lat, seed=2, scale=0.02), w_out=rnd(cfg.e_q, E, seed=4, scale=0.02))
+    x, d_out = rnd(1, rows, E, seed=1), rnd(1, rows, E, seed=5)
+    saved = P.CCASaved.allocate(cfg, "cuda")
+    P.cca_forward(cfg, w, x, saved=saved)
+    _, g = P.cca_backward(cfg, w, x, saved, d_out, grads=P.CCAGrads(w_out=torch.full_like(w.w_out, float("nan"))))
+    torch.cuda.synchronize()
+    check_product(g.w_out, saved.o[0].double().t().contiguous() @ d_out[0].double(), rows)
