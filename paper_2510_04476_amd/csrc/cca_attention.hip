@@ -7,7 +7,10 @@
 // MFMA tile) and all of d_h, so the softmax statistics of a row never leave a
 // wavefront.  Keys / values arrive in tiles of 64 through double-buffered LDS:
 // a tile travels HBM -> registers during one tile step and registers -> LDS
-// during the next.
+// during the next.  Where that grid would leave CUs idle (split_keys below)
+// a workgroup owns 128 rows instead and its two groups of four wavefronts
+// take the even and the odd key tiles; the two partial results of a row are
+// merged through LDS.
 //
 // The scores are produced transposed, S^T = K Q^T, with the 32x32x16 bf16
 // MFMA.  Its accumulator layout then gives every lane 16 keys of ONE query
@@ -41,6 +44,8 @@
 // Two code paths share the kernel: the generic one (running reference max,
 // one tile at a time) and, for bounded scores, a software-pipelined one
 // (attn_fwd_pipelined below).
+#include <math.h>
+
 #include <type_traits>
 
 #include "cca_internal.h"
@@ -115,20 +120,22 @@ __device__ __forceinline__ void load_q_frags(const bf16_t *__restrict__ Q, long 
   }
 }
 
+__device__ __forceinline__ float both_halves(float x) { return x + __shfl_xor(x, 32); }  // each half-wave sums half of the keys
+
 // Epilogue of one 32-row tile: lane (l32, half) holds o[t][32 dt + 8 rg + 4 half + e] / l in oacc[dt][4 rg + e].
 // Normalises by the row sum, rounds once to bf16, stores 8 bytes per (dt, rg); o_lo (optional) gets what the
 // rounding dropped (the backward pass forms <dO, O> from o + o_lo); lse = ln of the row sum in the caller's
 // units: (log2 l + shift) ln 2, with shift the reference max the scores were taken against.
-template <int DH>
-__device__ __forceinline__ void store_rows(const f32x16 *oacc, float l_part, float shift, bf16_t *__restrict__ O,
+// [DT0, DT1): the 32-channel tiles this wavefront holds.
+template <int DH, int DT0 = 0, int DT1 = DH / 32>
+__device__ __forceinline__ void store_rows(const f32x16 *oacc, float l, float shift, bf16_t *__restrict__ O,
                                            bf16_t *__restrict__ OLO, float *__restrict__ LSE, int b, int h, int t, int T,
                                            int Hq, int half) {
-  const float l = l_part + __shfl_xor(l_part, 32);  // each half-wave has summed half of the keys
   if (t >= T) return;
   const float inv = 1.f / l;
   const long long off = (((long long)b * T + t) * Hq + h) * DH;
 #pragma unroll
-  for (int dt = 0; dt < DH / 32; ++dt)
+  for (int dt = DT0; dt < DT1; ++dt)
 #pragma unroll
     for (int rg = 0; rg < 4; ++rg) {
       u32x2 w;
@@ -142,7 +149,63 @@ __device__ __forceinline__ void store_rows(const f32x16 *oacc, float l_part, flo
         *reinterpret_cast<u32x2 *>(OLO + off + dt * 32 + rg * 8 + half * 4) = x;
       }
     }
-  if (LSE && half == 0) LSE[((long long)b * Hq + h) * T + t] = (log2f(l) + shift) * 0.69314718055994530942f;
+  if (DT0 == 0 && LSE && half == 0) LSE[((long long)b * Hq + h) * T + t] = (log2f(l) + shift) * 0.69314718055994530942f;
+}
+
+
+// Two groups of wavefronts walked the two halves of the keys of the same rows (KS = 2): the partial results of a row,
+// taken against the reference maxima m (a group that saw no key of the row has l = 0), are added through LDS.  Each group
+// ends with the output tiles [kg * DT / 2, (kg + 1) * DT / 2) of its wavefront's rows; l and m are the row's afterwards.
+// The K / V tiles in `smem` are no longer read by anyone when this is called.
+template <int DH>
+__device__ __forceinline__ void merge_key_groups(f32x16 *oacc, float &l, float &m, int kg, int wave_g, int lane,
+                                                 unsigned char *smem) {
+  constexpr int HT = DH / 64;  // output tiles a group keeps
+  float *const buf = reinterpret_cast<float *>(smem) + lane;
+  float *const mine = buf + (kg * 4 + wave_g) * (HT * 16 + 2) * 64, *const other = buf + ((1 - kg) * 4 + wave_g) * (HT * 16 + 2) * 64;
+  // (values are selected, never array elements: a selected element would move the accumulators to scratch memory)
+#pragma unroll
+  for (int x = 0; x < HT; ++x)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float first = oacc[x][r], second = oacc[HT + x][r];
+      mine[(x * 16 + r) * 64] = kg == 0 ? second : first;
+    }
+  mine[HT * 16 * 64] = l;
+  mine[(HT * 16 + 1) * 64] = m;
+  __syncthreads();
+  const float lo = other[HT * 16 * 64], mo = other[(HT * 16 + 1) * 64];
+  const float M = l == 0.f ? mo : lo == 0.f ? m : fmaxf(m, mo);
+  const float f = l == 0.f ? 0.f : __builtin_amdgcn_exp2f(m - M), fo = lo == 0.f ? 0.f : __builtin_amdgcn_exp2f(mo - M);
+  l = l * f + lo * fo;
+  m = M;
+#pragma unroll
+  for (int x = 0; x < HT; ++x)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float first = oacc[x][r], second = oacc[HT + x][r];
+      const float sum = (kg == 0 ? first : second) * f + other[(x * 16 + r) * 64] * fo;
+      oacc[x][r] = kg == 0 ? sum : first;
+      oacc[HT + x][r] = kg == 0 ? second : sum;
+    }
+  __syncthreads();  // the buffer may hold K / V tiles again
+}
+
+// Epilogue of a wavefront: the row sums over both half-waves, with KS = 2 the other group's part, then the rows.
+template <int DH, int KS>
+__device__ __forceinline__ void finish_rows(f32x16 *oacc, float l_part, float m, int kg, int wave_g, int lane, bool live,
+                                            unsigned char *smem, bf16_t *__restrict__ O, bf16_t *__restrict__ OLO,
+                                            float *__restrict__ LSE, int b, int h, int t, int T, int Hq) {
+  float l = both_halves(l_part);
+  const int half = lane >> 5;
+  if constexpr (KS == 1) {
+    if (live) store_rows<DH>(oacc, l, m, O, OLO, LSE, b, h, t, T, Hq, half);
+  } else {
+    merge_key_groups<DH>(oacc, l, m, kg, wave_g, lane, smem);
+    if (!live) return;
+    if (kg == 0) store_rows<DH, 0, DH / 64>(oacc, l, m, O, OLO, LSE, b, h, t, T, Hq, half);
+    else store_rows<DH, DH / 64, DH / 32>(oacc, l, m, O, OLO, LSE, b, h, t, T, Hq, half);
+  }
 }
 
 // BOUNDED: the caller guarantees |score| <= bound (log2 units) for every query / key pair, as the QK L2-norm
@@ -150,7 +213,9 @@ __device__ __forceinline__ void store_rows(const f32x16 *oacc, float l_part, flo
 // of every row: no row max, no rescaling, and exp2 arguments lie in [-2*bound, 0].
 // NTH threads = NTH / 64 wavefronts x 32 rows = BQ_ query rows per workgroup: 512 threads (256 rows, two wavefronts
 // per SIMD) for d_h <= 128, 256 threads (128 rows, one wavefront per SIMD and twice the registers) for d_h = 256.
-template <int DH, bool CAUSAL, bool BOUNDED, bool RSUM, int NTH = NT>
+// KS = 2: two groups of NTH / 2 threads share the rows of one group (BQ_ = 128 at 512 threads); group kg takes the key
+// tiles 2 j + kg through LDS buffers of its own, and the two partial results of a row are merged at the end.
+template <int DH, bool CAUSAL, bool BOUNDED, bool RSUM, int NTH = NT, int KS = 1>
 __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                               const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
                                               bf16_t *__restrict__ OLO, float *__restrict__ LSE, int T, int Hq, int Hk,
@@ -164,13 +229,15 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
   constexpr int VROW = DH * 2 + 64;    // padded value row: the 4 rows x 32 bytes a transposing read touches per
                                        // 16 lanes fall into disjoint banks
   constexpr int VBUF = BKV * VROW;     // bytes per V buffer
-  constexpr int K_PER_THREAD = BKV * KCH / NTH;
-  constexpr int K_ROWS_PER_PASS = NTH / KCH;
-  constexpr int BQ_ = NTH / 64 * 32;
-  unsigned char *const sKb = smem;
-  unsigned char *const sVb = smem + 2 * KBUF;
+  constexpr int NTG = NTH / KS;        // threads of a key group
+  constexpr int K_PER_THREAD = BKV * KCH / NTG;
+  constexpr int K_ROWS_PER_PASS = NTG / KCH;
+  constexpr int BQ_ = NTG / 64 * 32;
+  const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTG);
+  unsigned char *const sKb = smem + kg * 2 * (KBUF + VBUF);
+  unsigned char *const sVb = sKb + 2 * KBUF;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x % NTG, lane = tid & 63, wave = tid >> 6;  // within the key group
   const int l32 = lane & 31, half = lane >> 5;
   const int idx = blockIdx.x;
   const int bh = idx % BH;  // head index fastest: with B*Hq a multiple of 8 an XCD keeps one head's K/V in its L2
@@ -249,21 +316,21 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
     float l_run = 0.f, l_run2 = 0.f;  // running sums of probabilities (two chains); each half-wave keeps its own part
 
     const int kv_end = CAUSAL ? min(q0 + BQ_, T) : T;  // keys [0, kv_end) matter to this workgroup
-    const int ntiles = (kv_end + BKV - 1) / BKV;
+    const int ntiles = ((kv_end + BKV - 1) / BKV + KS - 1) / KS;  // of a key group (the last one may lie past the end)
 
     auto tile = [&](int j, auto buf_c) {
       constexpr int BUF = decltype(buf_c)::value;
-      const int kv0 = j * BKV;
+      const int kv0 = (j * KS + kg) * BKV;
       // Tile j+1 is already in registers (loaded while tile j-1 was multiplied): put it into the other LDS
       // buffer right away, so that its stores drain under this tile's MFMAs instead of in front of the
       // barrier, then start the loads of tile j+2 into the same registers.
       if (j + 1 < ntiles) store_tile(BUF ^ 1);  // that buffer was last read before the barrier ending tile j-1
-      if (j + 2 < ntiles) load_tile(kv0 + 2 * BKV);
-      if (wave_live && !(CAUSAL && kv0 > wave_last)) {
+      if (j + 2 < ntiles) load_tile(kv0 + 2 * KS * BKV);
+      if (wave_live && kv0 <= (CAUSAL ? wave_last : T - 1)) {
         const unsigned char *kp = sKb + BUF * KBUF + kr_off;
         // ---- S^T - m = K Q^T - m for 64 keys x 32 query rows (log2 units)
         // (one wavefront per SIMD: inline-assembly MFMAs keep the scores in ordinary vector registers, see above)
-        constexpr bool INLINE_S = NTH == 256;
+        constexpr bool INLINE_S = DH == 256;
         f32x16 sacc[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
@@ -307,7 +374,7 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
           // Move the reference max only on the first tile (to the tile's own max) or when a score
           // exceeds it by more than 2^RESCALE_LOG2; exp2 arguments stay <= RESCALE_LOG2.
           if (j == 0 || __any(mx > RESCALE_LOG2)) {
-            const float delta = (j == 0) ? mx : fmaxf(mx, 0.f);  // finite: key 0 is visible to every row
+            const float delta = (j == 0) ? mx : fmaxf(mx, 0.f);  // finite: a tile's first key is visible to every row of the wavefront
             const float alpha = __builtin_amdgcn_exp2f(-delta);
             l_run *= alpha;
             l_run2 *= alpha;
@@ -359,9 +426,9 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
       __syncthreads();
     };
 
-    load_tile(0);
+    load_tile(kg * BKV);
     store_tile(0);
-    if (ntiles > 1) load_tile(BKV);
+    if (ntiles > 1) load_tile((KS + kg) * BKV);
     __syncthreads();
     for (int j = 0; j < ntiles; j += 2) {
       tile(j, std::integral_constant<int, 0>{});
@@ -369,7 +436,7 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
     }
 
     // ---- epilogue: normalise, round once to bf16, store; log-sum-exp of the scaled logits
-    if (wave_live) store_rows<DH>(oacc, l_run + l_run2, -negm[0], O, OLO, LSE, b, h, qw0 + l32, T, Hq, half);
+    finish_rows<DH, KS>(oacc, l_run + l_run2, -negm[0], kg, wave, lane, wave_live, smem, O, OLO, LSE, b, h, qw0 + l32, T, Hq);
   }
 }
 
@@ -386,7 +453,7 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
 constexpr int PF = 3;  // operand fetches run this many MFMAs ahead
 enum { IT_PRO = 0, IT_FULL = 1, IT_FINAL = 2, IT_IDLE = 3 };
 
-template <int DH, bool CAUSAL, bool RSUM>
+template <int DH, bool CAUSAL, bool RSUM, int KS>
 __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                    const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
                                                    bf16_t *__restrict__ OLO, float *__restrict__ LSE, int T, int Hq,
@@ -394,17 +461,19 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
                                                    unsigned char *smem) {
   constexpr int KK = DH / 16, DT = DH / 32, KCH = DH / 8;
   constexpr int KROW = DH * 2 + 16, KBUF = BKV * KROW, VROW = DH * 2 + 64, VBUF = BKV * VROW;
-  constexpr int K_PER_THREAD = BKV * KCH / NT, K_ROWS_PER_PASS = NT / KCH;
+  constexpr int NTG = NT / KS, K_PER_THREAD = BKV * KCH / NTG, K_ROWS_PER_PASS = NTG / KCH, BQ_ = NTG / 64 * 32;
   constexpr int NB = KK;  // MFMAs per (half-tile score | half-tile PV) block; 2 * DT == KK
   static_assert(2 * DT == KK, "block sizes");
-  unsigned char *const sKb = smem;
-  unsigned char *const sVb = smem + 2 * KBUF;
+  const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTG);  // key group (see attn_fwd_body)
+  unsigned char *const sKb = smem + kg * 2 * (KBUF + VBUF);
+  unsigned char *const sVb = sKb + 2 * KBUF;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x % NTG, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
   // Wavefronts w and w + 4 share a SIMD.  Under the causal mask a row block needs more key tiles the further
   // down it lies, so the 32-row blocks are dealt such that every SIMD gets a light and a heavy one (0 and 7,
-  // 1 and 6, ...): the SIMDs then carry equal work through the diagonal tiles of a query block.
+  // 1 and 6, ...): the SIMDs then carry equal work through the diagonal tiles of a query block.  (With two key groups
+  // they own the same rows.)
   const int wave_r = wave < 4 ? wave : 11 - wave;
   const int idx = blockIdx.x;
   const int bh = idx % BH;
@@ -429,8 +498,9 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
   int k_goff[K_PER_THREAD];
 #pragma unroll
   for (int i = 0; i < K_PER_THREAD; ++i) k_goff[i] = (k_r0 + i * K_ROWS_PER_PASS) * row_bytes + k_ch * 16;
-  auto load_rows = [&](const unsigned char *base, int kt, u32x4 *dst) {  // kt * BKV < T
-    const int first = kt * BKV * row_bytes;
+  auto load_rows = [&](const unsigned char *base, int j, u32x4 *dst) {  // tile j of this key group
+    // (a group's last tile may start past the end when the other group has one more: it is loaded from tile 0 and never used)
+    const int kt = j * KS + kg, first = KS == 1 || kt * BKV < T ? kt * BKV * row_bytes : 0;
     const __amdgpu_buffer_rsrc_t res =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(base) + first, 0, kv_span - first, 0x00020000);
 #pragma unroll
@@ -454,7 +524,7 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
     const int slot = idx / BH;
     const int qb = (paired && pass == 1) ? slot : nqb - 1 - slot;
     if (pass == 1 && slot >= nqb - 1 - slot) break;
-    const int q0 = qb * BQ, qw0 = q0 + wave_r * 32;
+    const int q0 = qb * BQ_, qw0 = q0 + wave_r * 32;
     const bool wave_live = qw0 < T;
     const int wave_last = min(qw0 + 31, T - 1);
 
@@ -470,9 +540,10 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
     for (int r = 0; r < 16; ++r) negm[r] = -bound;
     float l_run = 0.f, l_run2 = 0.f;
 
-    const int kv_end = CAUSAL ? min(q0 + BQ, T) : T;
-    const int ntiles = (kv_end + BKV - 1) / BKV;
-    const int my_tiles = !wave_live ? 0 : CAUSAL ? min(ntiles, wave_last / BKV + 1) : ntiles;
+    const int kv_end = CAUSAL ? min(q0 + BQ_, T) : T;
+    const int all_tiles = (kv_end + BKV - 1) / BKV, ntiles = (all_tiles + KS - 1) / KS;  // of the block, of a key group
+    const int vis_tiles = CAUSAL ? min(all_tiles, wave_last / BKV + 1) : all_tiles;      // with keys this wavefront's rows see
+    const int my_tiles = !wave_live ? 0 : (vis_tiles - kg + KS - 1) / KS;
     const int t_lim = (CAUSAL ? min(qw0 + l32, T - 1) : T - 1) - 4 * half;  // last visible key (minus the lane's offset)
 
     f32x16 sacc[2];      // scores of the two halves: [0] of tile j+1, [1] of tile j while iteration j runs
@@ -483,7 +554,7 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
     auto unit_exp = [&](int hs, int u, int kt, bool mask) {
       float s0 = sacc[hs][2 * u], s1 = sacc[hs][2 * u + 1];
       if (mask) {
-        const int key = kt * BKV + hs * 32 + 8 * ((2 * u) >> 2) + ((2 * u) & 3);
+        const int key = (kt * KS + kg) * BKV + hs * 32 + 8 * ((2 * u) >> 2) + ((2 * u) & 3);
         if (key > t_lim) s0 = -INFINITY;
         if (key + 1 > t_lim) s1 = -INFINITY;
       }
@@ -622,7 +693,7 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
     for (; j < ntiles; ++j) iter(j, IDLE_{}, F_{});
 
     // ---- epilogue: normalise, round once to bf16, store; log-sum-exp of the scaled logits
-    if (wave_live) store_rows<DH>(oacc, l_run + l_run2, bound, O, OLO, LSE, b, h, qw0 + l32, T, Hq, half);
+    finish_rows<DH, KS>(oacc, l_run + l_run2, bound, kg, wave, lane, wave_live, smem, O, OLO, LSE, b, h, qw0 + l32, T, Hq);
   }
 }
 
@@ -905,7 +976,7 @@ __device__ __forceinline__ void attn_fwd_pipelined_wide(const bf16_t *__restrict
     if (wave_live) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
-        store_rows<DH>(oacc[rb], l_run[rb] + l_run2[rb], 0.f, O, OLO, LSE, b, h, qw0 + rb * 32 + l32, T, Hq, half);
+        store_rows<DH>(oacc[rb], both_halves(l_run[rb] + l_run2[rb]), 0.f, O, OLO, LSE, b, h, qw0 + rb * 32 + l32, T, Hq, half);
     }
   }
 }
@@ -931,12 +1002,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 // RSUM: the row sum adds the bf16-rounded probabilities, so that o is the exact convex combination the PV
 // product formed; chosen when the caller saves lse / o_lo for a backward pass (see the file header).
-template <int DH, bool CAUSAL, bool RSUM>
+// KS: key groups per workgroup (attn_fwd_body)
+template <int DH, bool CAUSAL, bool RSUM, int KS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
     bf16_t *__restrict__ OLO, float *__restrict__ LSE, const float *__restrict__ temp, int qk_normed, int T, int Hq, int Hk, int BH, int nqb,
     int paired, float scale) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BKV * (DH * 2 + 16) + 2 * BKV * (DH * 2 + 64)];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[KS * 2 * BKV * (DH * 2 + 16 + DH * 2 + 64)];
   float bound = INFINITY;
   if (qk_normed) {
     // |q.k| <= d_h * beta; 2 % head-room for the bf16 rounding of the stored q and k
@@ -946,23 +1018,48 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   }
   // exp2 arguments reach -2*bound: keep them inside the fp32 exponent range
   if (bound <= 60.f)
-    attn_fwd_pipelined<DH, CAUSAL, RSUM>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, bound, smem);
+    attn_fwd_pipelined<DH, CAUSAL, RSUM, KS>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, bound, smem);
   else
-    attn_fwd_body<DH, CAUSAL, false, RSUM>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, 0.f, smem);
+    attn_fwd_body<DH, CAUSAL, false, RSUM, NT, KS>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, 0.f, smem);
 }
 
-template <int DH>
+// Query blocks of `bq` rows; whether each workgroup takes two of them.
+// Causal work per query block grows with its index.  With one 8-wavefront workgroup per CU, giving every
+// workgroup one heavy and one light block (equal work for all) measured ~20% faster at B*Hq = 8 than issuing
+// the heavy blocks first; only worth it while it still leaves a workgroup for each of the 256 CUs.
+int query_blocks(const Dims &d, int bq) { return (d.T + bq - 1) / bq; }
+bool pair_blocks(const Dims &d, int nqb) {
+  return (d.flags & CCA_CAUSAL) && (long long)d.B * d.Hq * ((nqb + 1) / 2) >= 256;
+}
+
+// Two key groups per workgroup (128 query rows, half the key tiles for each group) or one (256 rows)?  A grid takes as
+// long as its busiest CU, counted in steps of one key tile per group: 256-row blocks leave most CUs idle until B * H_q * T
+// reaches about 32 k rows, and each walks all keys of its rows.  The split form costs 12 % more per step (a tile is staged
+// for 128 rows instead of 256) and about 1.5 steps for the merge.  Measured (T, B * H_q, d_h: one group -> two, us, causal):
+// 512, 8, 128: 19.1 -> 16.2; 2048, 8, 128: 47.6 -> 33.6; 4096, 8, 128: 85.0 -> 57.7; 8192, 8, 128: 171.6 -> 134.2;
+// 4096, 16, 128 without bound: 101.8 -> 81.8; 1531, 24, 64: 26.6 -> 19.4; kept on one group: 64, 8: 6.2 -> 7.8;
+// 16384, 8, 128: 446 -> 501; 1999, 64, 64: 44.7 -> 54.7.  256 threads and 128 rows without the split: 2048, 8: 38.1.
+bool split_keys(const Dims &d) {
+  const long long BH = (long long)d.B * d.Hq;
+  auto busiest = [&](int bq) {  // steps: a block of bq rows takes (its tiles) * bq / 256 of them
+    const long long n = query_blocks(d, bq), blocks = BH * n;
+    if (!(d.flags & CCA_CAUSAL)) return (double)((blocks + 255) / 256) * (double)((d.T + BKV - 1) / BKV) * bq / 256;
+    const double per = (double)(bq / BKV) * bq / 256;  // steps of the first block; the i-th takes i times as many
+    if (pair_blocks(d, (int)n)) return (double)((BH * ((n + 1) / 2) + 255) / 256) * per * (double)(n + 1);
+    return per * fmax((double)n, (double)BH * (double)n * (double)(n + 1) / 512.0);
+  };
+  return 1.12 * busiest(BQ / 2) + 1.5 < busiest(BQ);
+}
+
+template <int DH, int KS>
 hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo, float *lse,
                   const float *temp, hipStream_t s) {
   constexpr bool WIDE = DH > 128;             // one wavefront per SIMD, 128-row query blocks
-  constexpr int BQL = WIDE ? 128 : BQ;
-  const int nqb = (d.T + BQL - 1) / BQL;
+  constexpr int BQL = WIDE ? 128 : BQ / KS;
+  const int nqb = query_blocks(d, BQL);
   const int BH = d.B * d.Hq;
   const bool causal = d.flags & CCA_CAUSAL;
-  // Causal work per query block grows with its index.  With one 8-wavefront workgroup per CU, giving every
-  // workgroup one heavy and one light block (equal work for all) measured ~20% faster at B*Hq = 8 than issuing
-  // the heavy blocks first; only worth it while it still leaves a workgroup for each of the 256 CUs.
-  const int paired = causal && (long long)BH * ((nqb + 1) / 2) >= 256 ? 1 : 0;
+  const int paired = pair_blocks(d, nqb) ? 1 : 0;
   const long long blocks = (long long)BH * (paired ? (nqb + 1) / 2 : nqb);
   const int qk_normed = (d.flags & CCA_QK_NORM) ? 1 : 0;
   if (!(d.flags & CCA_KEY_TEMP)) temp = nullptr;
@@ -974,7 +1071,7 @@ hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, vo
                                                                     temp, qk_normed, d.T, d.Hq, d.Hk, BH, nqb, paired,  \
                                                                     d.scale);                                          \
   else                                                                                                                 \
-    attn_fwd_kernel<DH, C, R><<<(unsigned)blocks, NT, 0, s>>>((const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,  \
+    attn_fwd_kernel<DH, C, R, KS><<<(unsigned)blocks, NT, 0, s>>>((const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,  \
                                                               (bf16_t *)o, (bf16_t *)o_lo, lse, temp, qk_normed, d.T,   \
                                                               d.Hq, d.Hk, BH, nqb, paired, d.scale)
   if (causal) {
@@ -997,9 +1094,10 @@ bool attention_mfma_supported(const Dims &d) {
 
 hipError_t attention_mfma_bf16(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo,
                                float *lse, const float *temp, hipStream_t s) {
-  return d.dh == 256   ? launch<256>(d, q, k, v, o, o_lo, lse, temp, s)
-         : d.dh == 128 ? launch<128>(d, q, k, v, o, o_lo, lse, temp, s)
-                       : launch<64>(d, q, k, v, o, o_lo, lse, temp, s);
+  const bool halves = d.dh <= 128 && split_keys(d);
+  return d.dh == 256   ? launch<256, 1>(d, q, k, v, o, o_lo, lse, temp, s)
+         : d.dh == 128 ? (halves ? launch<128, 2>(d, q, k, v, o, o_lo, lse, temp, s) : launch<128, 1>(d, q, k, v, o, o_lo, lse, temp, s))
+                       : (halves ? launch<64, 2>(d, q, k, v, o, o_lo, lse, temp, s) : launch<64, 1>(d, q, k, v, o, o_lo, lse, temp, s));
 }
 
 }  // namespace cca

@@ -66,3 +66,67 @@ def test_weight_gradient_tiles(rows, Hq, dh, E):
     _, g = P.cca_backward(cfg, w, x, saved, d_out, grads=P.CCAGrads(w_out=torch.full_like(w.w_out, float("nan"))))
     torch.cuda.synchronize()
     check_product(g.w_out, saved.o[0].double().t().contiguous() @ d_out[0].double(), rows)
+
+
+def split_of(B, T, Hq, causal):
+    """Whether the launcher splits the keys of a workgroup over two groups (the rule of csrc/cca_attention.hip)."""
+    BH = B * Hq
+
+    def busiest(bq):
+        n = -(-T // bq)
+        if not causal:
+            return -(-BH * n // 256) * -(-T // 64) * bq / 256
+        per = bq / 64 * bq / 256
+        if BH * ((n + 1) // 2) >= 256:
+            return -(-BH * ((n + 1) // 2) // 256) * per * (n + 1)
+        return per * max(n, BH * n * (n + 1) / 512)
+
+    return 1.12 * busiest(128) + 1.5 < busiest(256)
+
+
+# B, T, Hq, Hk, d_h, causal, normalised: odd lengths, one tile more or less than a pair, rows whose second key group is
+# empty, several query blocks, paired and unpaired grids; scores bounded and not
+SPLIT_CASES = [(1, 300, 2, 1, 128, True, True), (1, 321, 3, 3, 64, True, False), (2, 385, 2, 2, 128, False, True),
+               (1, 449, 4, 2, 128, False, False), (1, 1000, 4, 2, 64, True, True), (3, 1531, 8, 8, 64, True, True),
+               (1, 2047, 16, 16, 128, True, False), (1, 4096, 16, 16, 64, True, False), (2, 513, 4, 1, 128, True, False),
+               (1, 4097, 8, 2, 128, True, True)]
+
+
+@pytest.mark.parametrize("B,T,Hq,Hk,dh,causal,normed", SPLIT_CASES)
+def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
+    """o against fp64 softmax attention on the same bf16 inputs.  P enters the PV product rounded to bf16 (2^-9 of each
+    probability, independent) and o is rounded once: 2^-8 of the value plus, per element, the rounding noise of the sum.
+    q * scale * log2 e is rounded to bf16 once more (2^-9 of each logit)."""
+    say("split attention", B, T, Hq, Hk, dh, causal, normed)
+    assert split_of(B, T, Hq, causal)
+    flags = (P.CCA_CAUSAL if causal else 0) | (P.CCA_QK_NORM if normed else 0)
+    cfg = P.CCAConfig(B=B, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, flags=flags)
+    q, k = rnd(B, T, Hq, dh, seed=1, dtype=torch.float32), rnd(B, T, Hk, dh, seed=2, dtype=torch.float32)
+    if normed:
+        q, k = (t * (dh ** 0.5 / t.norm(dim=-1, keepdim=True)) for t in (q, k))
+    else:
+        q[:, ::7] *= 6.0  # rows whose maximum moves from tile to tile
+    q, k, v = q.bfloat16(), k.bfloat16(), rnd(B, T, Hk, dh, seed=3)
+    nan = lambda *s, dtype=torch.bfloat16: torch.full(s, float("nan"), dtype=dtype, device="cuda")
+    o_inf, o, o_lo, lse = nan(B, T, Hq * dh), nan(B, T, Hq * dh), nan(B, T, Hq * dh), nan(B, Hq, T, dtype=torch.float32)
+    P.cca_attention(cfg, q, k, v, o=o_inf)
+    P.cca_attention(cfg, q, k, v, o=o, o_lo=o_lo, lse=lse)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for h in range(Hq):
+            s = q[b, :, h].double() @ k[b, :, h // (Hq // Hk)].double().t().contiguous() / dh ** 0.5
+            s_max = float(s.abs().max())
+            if causal:
+                s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+            p = torch.softmax(s, -1)
+            vh = v[b, :, h // (Hq // Hk)].double()
+            ref, ref_lse = p @ vh, torch.logsumexp(s, -1)
+            # noise of a row: each |p v| term carries a relative error of 2^-9 (P) + 2^-9 s_max (its logit), independent
+            noise = 2.0 ** -9 * (1.0 + s_max) * (p.square() @ vh.square()).sqrt()
+            bound = 2.0 ** -8 * ref.abs() + 6.0 * noise + 1e-6
+            for got in (o_inf, o):
+                worst = float(((got[b, :, h * dh:(h + 1) * dh].double() - ref).abs() / bound).max())
+                assert worst <= 1.0, (b, h, worst)
+            exact = o[b, :, h * dh:(h + 1) * dh].double() + o_lo[b, :, h * dh:(h + 1) * dh].double()
+            assert float(((exact - ref).abs() / (2.0 ** -15 * ref.abs() + 6.0 * noise + 1e-6)).max()) <= 1.0
+            assert float((lse[b, h].double() - ref_lse).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
