@@ -75,33 +75,112 @@ __device__ __forceinline__ void load_vec(const bf16_t *p, float *dst) {
   }
 }
 
+// 8 consecutive elements as they lie in memory, converted when they are used: a conversion right behind the load would wait
+// for it
+template <typename T>
+struct Raw8;
+template <>
+struct Raw8<bf16_t> {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  u4 v;
+  __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const u4 *>(p); }
+  __device__ __forceinline__ float get(int e) const {
+    const uint32_t w = v[e >> 1];
+    return __uint_as_float((e & 1) ? w & 0xffff0000u : w << 16);
+  }
+};
+template <>
+struct Raw8<float> {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  f4 a, b;
+  __device__ __forceinline__ void load(const float *p) {
+    a = *reinterpret_cast<const f4 *>(p);
+    b = *reinterpret_cast<const f4 *>(p + 4);
+  }
+  __device__ __forceinline__ float get(int e) const { return e < 4 ? a[e & 3] : b[e & 3]; }
+};
+
 // latent row of token `tok` of sequence b: ring slot tok % P (the new token's row is written there by the projection)
 template <typename T>
 __device__ __forceinline__ const T *lat_row(const DecArgs &a, const T *hist, int b, int tok) {
   return hist + ((long long)b * a.P + tok % a.P) * a.n_lat;
 }
 
+constexpr int MAX_PARTS = 8;
+// Channel `ch` of the new token's latent row: with `part` (the down-projection left `nparts` fp32 partial sums per element,
+// (nparts, B, N_lat)) their sum in index order, rounded to the storage type; else the ring already holds the row.
+template <typename T>
+struct NewRow {
+  const T *ring;        // the new token's slot
+  const float *part;    // this sequence's row of the first partial sum, or null
+  long long stride;     // from one partial sum to the next
+  int nparts;
+  // No load here hides behind a condition: all of a thread's loads are in flight together (addresses past the last part
+  // repeat it, the value is dropped).
+  template <int N>
+  __device__ __forceinline__ void many(const int (&ch)[N], float (&out)[N]) const {
+    if (!part) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) out[i] = load_f(ring + ch[i]);
+      return;
+    }
+    float v[N][MAX_PARTS];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int s = 0; s < MAX_PARTS; ++s) v[i][s] = part[min(s, nparts - 1) * stride + ch[i]];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      float a = 0.f;
+#pragma unroll
+      for (int s = 0; s < MAX_PARTS; ++s) a += s < nparts ? v[i][s] : 0.f;
+      T r;
+      store_f(&r, a);
+      out[i] = load_f(&r);
+    }
+  }
+  __device__ __forceinline__ float at(int ch) const {
+    const int c[1] = {ch};
+    float o[1];
+    many(c, o);
+    return o[0];
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Transforms of the new token: one workgroup per (sequence, head); heads 0..Hq-1 query, then Hk key, then Hk value.
-// Same arithmetic, in the same order, as the shape-generic prefill prologue.
+// What bounds it is latency, so everything that does not depend on something else is requested or computed first: the
+// filter rows of the first outputs, then (under those loads) the rotary angles, then the rows the taps reach.  LPO = 8 or
+// 16 lanes share an output channel's filter row (128 adjacent bytes per load: the memory pipeline works per cache line)
+// and add their parts on the vector ALU; and no load hides behind a condition (each would be waited for). At B = 32,
+// d_h = 128: 14.2 us including the sum of the down-projection's parts, against 12.7 + 4.9 us for one thread per filter row
+// behind a kernel that added them; at B = 1 7.7 against 8.6 + 3.5.  CH = 16- (fp32: 32-) byte chunks of a filter row per lane.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ void decode_prologue_kernel(DecArgs a, const T *__restrict__ hist,
-                                       const T *__restrict__ w0, const T *__restrict__ w1,
-                                       const float *__restrict__ temp, float *__restrict__ q_new,
-                                       T *__restrict__ k_cache, T *__restrict__ v_cache) {
-  extern __shared__ float sm[];  // y0[dh][k_ch] | red[blockDim] | yrot[dh]
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+
+template <typename T, int CH, int LPO>
+__global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__restrict__ hist, const float *__restrict__ part,
+                                                             int nparts, const T *__restrict__ w0, const T *__restrict__ w1,
+                                                             const float *__restrict__ temp, float *__restrict__ q_new,
+                                                             T *__restrict__ k_cache, T *__restrict__ v_cache) {
+  extern __shared__ __attribute__((aligned(16))) float sm[];  // y0[dh][k_ch] | yrot[dh] | cos[dh/2] | sin[dh/2]
   const int b = blockIdx.x, head = blockIdx.y, dh = a.dh, tid = threadIdx.x, t = seq_pos(a, b);
   const long long crow = (long long)b * a.S + t;  // cache row of the new token
+  T *const slot = hist + ((long long)b * a.P + t % a.P) * a.n_lat;
+  const NewRow<T> now{slot, part ? part + (long long)b * a.n_lat : nullptr, (long long)a.B * a.n_lat, nparts};
 
   if (head >= a.Hq + a.Hk) {  // value head: second stream delayed by one token
-    const int g = head - a.Hq - a.Hk;
-    const T *cur = lat_row(a, hist, b, t) + a.e_q + a.e_kv;
-    const T *prev = t > 0 ? lat_row(a, hist, b, t - 1) + a.e_q + a.e_kv : nullptr;
+    const int g = head - a.Hq - a.Hk, v0 = a.e_q + a.e_kv;
+    const T *prev = t > 0 ? lat_row(a, hist, b, t - 1) + v0 : nullptr;
     for (int i = tid; i < dh; i += blockDim.x) {
       const int c = g * dh + i;
+      const float cur = now.at(v0 + c);
+      if (part) store_f(slot + v0 + c, cur);
       float val;
-      if (c < a.v_half || !(a.flags & CCA_V_SHIFT)) val = load_f(cur + c);
+      if (c < a.v_half || !(a.flags & CCA_V_SHIFT)) val = cur;
       else val = prev ? load_f(prev + c) : 0.f;
       store_f(v_cache + crow * a.e_kv + c, val);
     }
@@ -112,77 +191,134 @@ __global__ void decode_prologue_kernel(DecArgs a, const T *__restrict__ hist,
   const int ch0 = is_q ? head * dh : a.e_q + (head - a.Hq) * dh;
   const int kc = (a.flags & CCA_CONV_CH) ? a.k_ch : 1;
   const int ks = (a.flags & CCA_CONV_SEQ) ? a.k_seq : 1;
-  float *y0 = sm, *red = sm + kc * dh, *yrot = red + blockDim.x;
+  float *y0 = sm, *yrot = sm + kc * dh, *cos_t = yrot + dh, *sin_t = cos_t + dh / 2;
 
-  for (int idx = tid; idx < kc * dh; idx += blockDim.x) {
-    const int j = idx / dh, i = idx % dh;
-    const int tj = t - (kc - 1) + j;
+  // the first outputs' filter rows: lane lo of an output takes chunks lo, lo + LPO, ...
+  const int lo = tid % LPO, opp = blockDim.x / LPO, nch = dh * kc / 8;  // outputs per pass; chunks per filter row
+  Raw8<T> wv[2][CH];
+  auto load_w = [&](int o, Raw8<T> (&w)[CH]) {
+    const T *wp = w1 + ((long long)head * dh + min(o, dh - 1)) * dh * kc;
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const int c = j * LPO + lo;
+      w[j].load(wp + min(c, nch - 1) * 8);  // chunks past the row repeat its last one and meet zeros
+    }
+  };
+  const bool conv = a.flags & CCA_CONV_CH;
+  if (conv) load_w(tid / LPO, wv[0]);
+
+  // The new row's channels, one output per thread (d_h <= 256 <= threads; the others repeat the last one): the head's own
+  // and the qk-mean's other stream.
+  const int oc = min(tid, dh - 1);
+  float own, mean = 0.f;
+  if (is_q) {
+    float x[2];
+    now.many({ch0 + oc, a.e_q + (head / a.R) * dh + oc}, x);
+    own = x[0];
+    mean = 0.5f * (own + x[1]);
+  } else {
+    const int q0 = (head - a.Hq) * a.R * dh + oc;
+    float sq = 0.f;
+    own = now.at(ch0 + oc);
+    for (int r = 0; r < a.R; r += 4) {
+      float x[4];
+      now.many({q0 + r * dh, q0 + min(r + 1, a.R - 1) * dh, q0 + min(r + 2, a.R - 1) * dh, q0 + min(r + 3, a.R - 1) * dh}, x);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sq += r + u < a.R ? x[u] : 0.f;
+    }
+    mean = 0.5f * (sq / (float)a.R + own);
+  }
+  // conv1_seq outputs at the k_ch times conv2 needs, of which one channel and time each: the part from earlier tokens here,
+  // the new token's term (always the last tap) once its row is shared
+  const int n_y0 = kc * dh;  // <= 1024: two per thread at most
+  const bool seq = a.flags & CCA_CONV_SEQ;
+  const T *const f0p = seq ? w0 : hist;  // without the convolution: any readable row, the value is dropped
+  float y_old[2], w_new[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int idx = min(tid + u * (int)blockDim.x, n_y0 - 1), j = idx / dh, i = idx % dh, tj = t - (kc - 1) + j;
+    float xs[4], f0[4];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {  // rows outside the sequence (or still to come) are read from some slot and dropped
+      const int ts = tj - (ks - 1) + jj;
+      xs[jj] = load_f(lat_row(a, hist, b, max(ts, 0)) + ch0 + i);
+      f0[jj] = load_f(f0p + (long long)(ch0 + i) * ks + min(jj, ks - 1));
+    }
     float acc = 0.f;
-    if (tj >= 0) {
-      if (a.flags & CCA_CONV_SEQ) {
-        for (int jj = 0; jj < ks; ++jj) {
-          const int ts = tj - (ks - 1) + jj;
-          if (ts >= 0)
-            acc = fmaf(load_f(w0 + (long long)(ch0 + i) * ks + jj), load_f(lat_row(a, hist, b, ts) + ch0 + i), acc);
-        }
-      } else {
-        acc = load_f(lat_row(a, hist, b, tj) + ch0 + i);
-      }
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int ts = tj - (ks - 1) + jj;
+      f0[jj] = seq ? f0[jj] : 1.f;
+      acc = jj < ks && ts >= 0 && ts < t ? fmaf(f0[jj], xs[jj], acc) : acc;
     }
-    y0[i * kc + j] = acc;  // in the order the channel filter stores its (input channel, tap) pairs
+    y_old[u] = acc;
+    w_new[u] = f0[3];  // the last tap (min above)
   }
+  if (a.flags & CCA_ROPE) {
+    for (int i = tid; i < dh / 2; i += blockDim.x) {
+      const double theta = pow((double)a.rope_base, -2.0 * (double)i / (double)dh);
+      double sn, cs;
+      sincos((double)t * theta, &sn, &cs);
+      cos_t[i] = (float)cs;
+      sin_t[i] = (float)sn;
+    }
+  }
+  if (tid < dh) {
+    yrot[tid] = own;  // shared for the taps; the outputs replace it
+    if (part) store_f(slot + ch0 + tid, own);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int idx = tid + u * blockDim.x;
+    if (idx >= n_y0) continue;
+    const int j = idx / dh, i = idx % dh;
+    // in the order the channel filter stores its (input channel, tap) pairs
+    y0[i * kc + j] = j == kc - 1 ? fmaf(w_new[u], yrot[i], y_old[u]) : y_old[u];
+  }
+  __syncthreads();
+  if (tid < dh) yrot[tid] = (a.flags & CCA_QK_MEAN) ? mean : 0.f;
   __syncthreads();
 
-  const T *me = lat_row(a, hist, b, t);
-  float ssq = 0.f;
-  for (int o = tid; o < dh; o += blockDim.x) {
-    float y;
-    if (a.flags & CCA_CONV_CH) {
-      y = 0.f;
-      const T *wp = w1 + ((long long)head * dh + o) * dh * kc;  // one contiguous row of d_h * k_ch weights
-      int c8 = 0;
-      for (; c8 + 32 <= dh * kc; c8 += 32) {  // four 16-byte loads in flight; the sum keeps its order
-        float wv[4][8];
+  if (conv) {
+    float yv[CH][8];  // this lane's chunks of y0, zero past the row
 #pragma unroll
-        for (int u = 0; u < 4; ++u) load_vec<8>(wp + c8 + 8 * u, wv[u]);
+    for (int j = 0; j < CH; ++j) {
+      const int c = j * LPO + lo;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) y = fmaf(wv[u][e], y0[c8 + 8 * u + e], y);
-      }
-      for (; c8 < dh * kc; c8 += 8) {
-        float wv[8];
-        load_vec<8>(wp + c8, wv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) y = fmaf(wv[e], y0[c8 + e], y);
-      }
-    } else {
-      y = y0[o * kc + (kc - 1)];
+      for (int e = 0; e < 8; ++e) yv[j][e] = c < nch ? y0[c * 8 + e] : 0.f;
     }
-    if (a.flags & CCA_QK_MEAN) {
-      float m;
-      if (is_q) {
-        m = 0.5f * (load_f(me + head * dh + o) + load_f(me + a.e_q + (head / a.R) * dh + o));
-      } else {
-        const int g = head - a.Hq;
-        float sq = 0.f;
-        for (int r = 0; r < a.R; ++r) sq += load_f(me + (g * a.R + r) * dh + o);
-        m = 0.5f * (sq / (float)a.R + load_f(me + a.e_q + g * dh + o));
+    auto pass = [&](int o, const Raw8<T> (&w)[CH]) {
+      float y = 0.f;
+#pragma unroll
+      for (int j = 0; j < CH; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y = fmaf(w[j].get(e), yv[j][e], y);
+      y = dpp_add<0xB1>(y);   // quad_perm [1,0,3,2]
+      y = dpp_add<0x4E>(y);   // quad_perm [2,3,0,1]
+      y = dpp_add<0x141>(y);  // row_half_mirror: 8 lanes hold their sum
+      if constexpr (LPO == 16) y = dpp_add<0x140>(y);  // row_mirror
+      if (lo == 0 && o < dh) yrot[o] += y;
+    };
+    for (int o = tid / LPO; o < dh; o += 2 * opp) {  // (the lanes of an output agree on the conditions)
+      if (o + opp < dh) load_w(o + opp, wv[1]);
+      pass(o, wv[0]);
+      if (o + opp < dh) {
+        if (o + 2 * opp < dh) load_w(o + 2 * opp, wv[0]);
+        pass(o + opp, wv[1]);
       }
-      y += m;
     }
-    yrot[o] = y;
-    ssq = fmaf(y, y, ssq);
+  } else {
+    for (int o = tid; o < dh; o += blockDim.x) yrot[o] += y0[o * kc + (kc - 1)];
   }
-  red[tid] = ssq;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (tid < s) red[tid] += red[tid + s];
-    __syncthreads();
-  }
   float mul = 1.f;
-  if (a.flags & CCA_QK_NORM) {
-    mul = sqrtf((float)dh) / sqrtf(red[0] + a.norm_eps);
+  if (a.flags & CCA_QK_NORM) {  // every wavefront forms the sum by itself: no further barrier
+    float ssq = 0.f;
+    for (int o = tid & 63; o < dh; o += 64) ssq = fmaf(yrot[o], yrot[o], ssq);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) ssq += __shfl_xor(ssq, off);
+    mul = sqrtf((float)dh) / sqrtf(ssq + a.norm_eps);
     if (!is_q && (a.flags & CCA_KEY_TEMP)) mul *= expf(temp[head - a.Hq]);
   }
   for (int o = tid; o < dh; o += blockDim.x) {
@@ -196,11 +332,8 @@ __global__ void decode_prologue_kernel(DecArgs a, const T *__restrict__ hist,
       } else {
         pair = o % half; first = o < half; partner = first ? o + half : o - half;
       }
-      const double theta = pow((double)a.rope_base, -2.0 * (double)pair / (double)dh);
-      double sn, cs;
-      sincos((double)t * theta, &sn, &cs);
       const float yp = yrot[partner] * mul;
-      y = first ? (y * (float)cs - yp * (float)sn) : (y * (float)cs + yp * (float)sn);
+      y = first ? (y * cos_t[pair] - yp * sin_t[pair]) : (y * cos_t[pair] + yp * sin_t[pair]);
     }
     if (is_q) {
       // the query goes through the storage type once, as the prefill's q does, then stays fp32 for the dot products
@@ -226,7 +359,7 @@ template <typename T, int CPL, int DHC>
 __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(DecArgs a, const float *__restrict__ q_new,
                                                                     const T *__restrict__ k_cache,
                                                                     const T *__restrict__ v_cache,
-                                                                    float *__restrict__ part, int nsplit, int r0) {
+                                                                    float *__restrict__ part, int nsplit, int per, int r0) {
   extern __shared__ float sm[];
   const int dh = DHC ? DHC : a.dh;
   const int split = blockIdx.x % nsplit, g = (blockIdx.x / nsplit) % a.Hk, b = blockIdx.x / (nsplit * a.Hk);
@@ -244,7 +377,6 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(DecArgs a, 
   __syncthreads();
 
   // keys of this split, dealt to the wavefronts in blocks of 64
-  const int per = (len + nsplit - 1) / nsplit;
   const int k_begin = split * per, k_end = min(len, k_begin + per);
   float m[R_MAX], l[R_MAX], o[R_MAX][CPL];
 #pragma unroll
@@ -366,16 +498,11 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(DecArgs a, 
 // current one have left the K registers and the next V loads after the P V step, so a wavefront always has one or
 // two blocks of loads in flight.  NR = query heads per pass, U = load instructions (groups of rows) per block.
 // ---------------------------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float x) {
-  return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
-
 template <int NR, int DH, int U>
 __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArgs a, const float *__restrict__ q_new,
                                                                          const bf16_t *__restrict__ k_cache,
                                                                          const bf16_t *__restrict__ v_cache,
-                                                                         float *__restrict__ part, int nsplit, int r0) {
+                                                                         float *__restrict__ part, int nsplit, int per, int r0) {
   constexpr int LPR = DH / 8, RPL = 64 / LPR, BLK = U * RPL;  // lanes per row, rows per load, rows per block
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   typedef float f4 __attribute__((ext_vector_type(4)));
@@ -411,7 +538,6 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[r][e] = 0.f;
   }
-  const int per = (len + nsplit - 1) / nsplit;
   const int k_begin = split * per, k_end = min(len, k_begin + per);
   int k0 = k_begin + wave * BLK;
   if (k0 < k_end) {  // wave-uniform
@@ -669,93 +795,132 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(const T *__restrict__ 
   }
 }
 
-// The same product on the matrix cores for bf16 (N and K multiples of 8).  The W tile (a K slice x 128 columns) is
-// staged row-major in LDS and read as MFMA fragments with the transposing LDS read (the contraction index is the ROW
-// of W); the fragments of A (32 rows x 16 k) come straight from memory: lane (row l % 32, half l / 32) holds
-// k = 4*half .. +3 and 8 + 4*half .. +3 of each group of 16, the order the transposing read delivers W in.  Each
-// wavefront owns 32 of the 128 columns over the whole slice, so nothing is added across wavefronts.
+// The same product on the matrix cores for bf16 (N and K multiples of 8), in one launch without partial sums in memory.
+// Workgroup = 32 columns x all of K: its panel of W (64 bytes per row) and the rows of A are requested together, straight
+// into LDS, as much of K at a time as fits (all 2048 for up to 8 rows, 1024 for 32), so one memory latency is paid per
+// pass - what bounds a product this small is latency and launches, not bytes.  The panel is read as MFMA fragments with the
+// transposing LDS read (rows lie 64 bytes apart, so the 8 rows a read touches are 512 adjacent bytes: no bank conflicts, no
+// padding); A lies row-major with chunk c of row r at c ^ (r mod 16).  (Read as fragments straight from memory, 32 rows x
+// 32 bytes per load instruction, A cost 9 of 14.6 us at 32 rows and K = 2048: the memory pipeline works per cache line.)
+// The 8 wavefronts take an eighth of the k each and their sums are added through LDS in order.  A CU takes in about 29 GB/s
+// of 64-byte pieces, so the grid is split over K as well where the next kernel adds the parts anyway (the down-projection:
+// K = 2048 whole 6.7 us at one row, in 5 slices 4.4).  Up-projection, K x N = 1024 x 2048: 3.4 us at one row, 5.8 at 32,
+// against 6.4 + 4.7 us for one workgroup per CU with partial sums and a kernel to add them.
 typedef __bf16 sk_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float sk_f32x16 __attribute__((ext_vector_type(16)));
-typedef float sk_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t sk_u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t sk_u32x2 __attribute__((ext_vector_type(2)));
 typedef short sk_v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) sk_v4i16 sk_lds_v4i16;
-constexpr int SM_ROW = SK_COLS * 2 + 64;  // LDS row of the W tile, bytes: padded so that the 4 rows a transposing read touches differ in bank group
+constexpr int PN_COLS = 32, PN_NT = 512, PN_WAVES = PN_NT / 64;
+constexpr size_t PN_LDS = 160 * 1024, PN_SUMS = (size_t)PN_WAVES * 32 * 33 * 4;
 
-__global__ __launch_bounds__(256) void gemm_skinny_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W,
-                                                              float *__restrict__ part, int M, int N, int K, int chunk) {
-  __shared__ __attribute__((aligned(16))) unsigned char wt[SK_MAXCHUNK * SM_ROW];
-  constexpr int NK16 = SK_MAXCHUNK / 16, STAGE = SK_MAXCHUNK * 16 / 256;  // k groups of a slice; 16-byte chunks per thread
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
-  const int n0 = blockIdx.x * SK_COLS;
-  const int k_begin = blockIdx.y * chunk, k_end = min(K, k_begin + chunk);
-  const int nk16 = (k_end - k_begin + 15) / 16;
-  // W tile: all loads first, then the LDS stores; rows past the slice and columns past N are zero
-  sk_u32x4 wv[STAGE];
-#pragma unroll
-  for (int i = 0; i < STAGE; ++i) {
-    const int id = tid + i * 256, row = id >> 4, c = id & 15;
-    sk_u32x4 v = {0, 0, 0, 0};
-    if (row < nk16 * 16 && k_begin + row < k_end && n0 + c * 8 < N)
-      v = *reinterpret_cast<const sk_u32x4 *>(W + (long long)(k_begin + row) * N + n0 + c * 8);
-    wv[i] = v;
-  }
-  // fragments of the first 32 rows of A for the whole slice (k past the slice reads as zero)
-  auto load_a = [&](int m0, sk_u32x4 (&xa)[NK16]) {
-    const bf16_t *ap = A + (long long)min(m0 + l32, M - 1) * K + k_begin + 4 * half;
-#pragma unroll
-    for (int kk = 0; kk < NK16; ++kk) {
-      sk_u32x2 lo = {0, 0}, hi = {0, 0};
-      if (kk < nk16) {
-        if (k_begin + kk * 16 + 4 * half < k_end) lo = *reinterpret_cast<const sk_u32x2 *>(ap + kk * 16);
-        if (k_begin + kk * 16 + 8 + 4 * half < k_end) hi = *reinterpret_cast<const sk_u32x2 *>(ap + kk * 16 + 8);
-      }
-      xa[kk] = sk_u32x4{lo.x, lo.y, hi.x, hi.y};
+// rows of W per pass: all of K in as few equal passes as the LDS allows, in whole 256-byte lines of A
+int panel_rows(int M, int K) {
+  const int fit = (int)(PN_LDS / (PN_COLS * 2 + 2 * (size_t)(M < 32 ? M : 32))) / 128 * 128;
+  const int passes = (K + fit - 1) / fit;
+  return ((K + passes - 1) / passes + 127) / 128 * 128;
+}
+
+// C row m starts at C + m * ldc (the rows of a projection may go straight into a strided destination).  With `row_pos`
+// row m goes to ring slot clamp(row_pos[m], 0, pos_max) % ring of its sequence: C + m * ldc + slot * N.
+struct RowDest {
+  long long ldc;
+  const int *row_pos;
+  int pos_max, ring;
+  __device__ __forceinline__ long long at(int m, int N) const {
+    long long o = m * ldc;
+    if (row_pos) {
+      const int p = row_pos[m];
+      o += (long long)((p < 0 ? 0 : (p > pos_max ? pos_max : p)) % ring) * N;
     }
-  };
-  sk_u32x4 xa[NK16];
-  load_a(0, xa);
-#pragma unroll
-  for (int i = 0; i < STAGE; ++i) {
-    const int id = tid + i * 256, row = id >> 4, c = id & 15;
-    if (row < nk16 * 16) *reinterpret_cast<sk_u32x4 *>(wt + row * SM_ROW + c * 16) = wv[i];
+    return o;
   }
-  __syncthreads();
-  const unsigned char *pw = wt + (4 * half + ((lane & 15) >> 2)) * SM_ROW + (wave * 32 + ((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2;
+};
+
+// (a body inlined with restrict arguments: without them the compiler makes the transposing LDS reads of a later pass wait
+// for loads into LDS that they do not touch)
+__device__ __forceinline__ void gemm_panel_body(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, bf16_t *__restrict__ C,
+                                                RowDest dest, int M, int N, int K, int kp, int k_slice, float *__restrict__ part, unsigned char *smem) {
+  typedef __attribute__((address_space(3))) void lds_void;
+  typedef __attribute__((address_space(1))) void glb_void;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int n0 = blockIdx.x * PN_COLS;
+  const int col = n0 + (lane & 3) * 8 < N ? n0 + (lane & 3) * 8 : 0;  // columns past N feed outputs that are not stored
+  unsigned char *const sA = smem + kp * (PN_COLS * 2);
+  // transposing read: this lane's 8 bytes of row 8 * half + (lane & 15) / 4 (+ 4) of a group, column block (lane >> 4) & 1
+  const unsigned char *const pw = smem + (8 * half + ((lane & 15) >> 2)) * 64 + (((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2;
+  const int cpr = kp / 8;  // 16-byte chunks of a row of A
+  const int k_begin = blockIdx.y * k_slice, k_end = min(K, k_begin + k_slice);
   for (int m0 = 0; m0 < M; m0 += 32) {
-    if (m0 > 0) load_a(m0, xa);
+    const int mrows = min(32, M - m0);
     sk_f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < NK16; ++kk) {
-      if (kk < nk16) {
-        const unsigned char *p = pw + kk * 16 * SM_ROW;
-        const sk_v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16 *)p);
-        const sk_v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16 *)(p + 8 * SM_ROW));
+    for (int k0 = k_begin; k0 < k_end; k0 += kp) {
+      const int rows = min(kp, k_end - k0), groups = (rows + 15) / 16;
+      __syncthreads();  // what lies in LDS is no longer read
+      // whole groups of 16 k: k past the end are zero in both operands
+      for (int g = wave; g < groups; g += PN_WAVES) {
+        const int r = g * 16 + (lane >> 2);
+        if (r < rows)
+          __builtin_amdgcn_global_load_lds((glb_void *)(W + (long long)(k0 + r) * N + col), (lds_void *)(smem + g * 1024), 16, 0, 0);
+        else
+          *reinterpret_cast<sk_u32x4 *>(smem + g * 1024 + lane * 16) = sk_u32x4{0, 0, 0, 0};
+      }
+      for (int i = wave; i < (mrows * cpr + 63) / 64; i += PN_WAVES) {
+        const int pos = i * 64 + lane, r = pos / cpr, p = pos % cpr, k = (p ^ (r & 15)) * 8;
+        if (r < mrows) {
+          if (k < rows)
+            __builtin_amdgcn_global_load_lds((glb_void *)(A + (long long)(m0 + r) * K + k0 + k), (lds_void *)(sA + i * 1024), 16, 0, 0);
+          else
+            *reinterpret_cast<sk_u32x4 *>(sA + pos * 16) = sk_u32x4{0, 0, 0, 0};
+        }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      const int per = (groups + PN_WAVES - 1) / PN_WAVES, g_end = min(groups, (wave + 1) * per);
+      const int ra = min(l32, mrows - 1);  // rows past M repeat the last one; they are not stored
+      const unsigned char *const pa = sA + ra * (kp * 2);
+#pragma unroll 4
+      for (int g = wave * per; g < g_end; ++g) {
+        const unsigned char *const q = pw + g * 1024;
+        const sk_bf16x8 fa = __builtin_bit_cast(sk_bf16x8, *reinterpret_cast<const sk_u32x4 *>(pa + (((2 * g + half) ^ (ra & 15)) * 16)));
+        const sk_v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16 *)q);
+        const sk_v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sk_lds_v4i16 *)(q + 256));
         const sk_bf16x8 fw = __builtin_bit_cast(sk_bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw, __builtin_bit_cast(sk_bf16x8, xa[kk]), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw, fa, acc, 0, 0, 0);
       }
     }
-    // acc[r] = C[m0 + l32][n0 + 32*wave + 8*(r/4) + 4*half + r%4]
-    const int m = m0 + l32;
-    if (m < M) {
-      float *dst = part + ((long long)blockIdx.y * M + m) * N + n0 + wave * 32 + half * 4;
+    // acc[r] = this wavefront's part of C[m0 + l32][n0 + 8*(r/4) + 4*half + r%4]
+    float *const red = reinterpret_cast<float *>(smem);
+    __syncthreads();
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg)
-        if (n0 + wave * 32 + rg * 8 + half * 4 < N)  // N % 8 == 0: the four columns are inside
-          *reinterpret_cast<sk_f32x4 *>(dst + rg * 8) = sk_f32x4{acc[rg * 4], acc[rg * 4 + 1], acc[rg * 4 + 2], acc[rg * 4 + 3]};
+    for (int r = 0; r < 16; ++r) red[(wave * 32 + l32) * 33 + 8 * (r >> 2) + 4 * half + (r & 3)] = acc[r];
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int m = (tid >> 5) + 16 * x, c = tid & 31;
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < PN_WAVES; ++w) sum += red[(w * 32 + m) * 33 + c];
+      if (m < mrows && n0 + c < N) {
+        if (part) part[((long long)blockIdx.y * M + m0 + m) * N + n0 + c] = sum;
+        else C[dest.at(m0 + m, N) + n0 + c] = f32_to_bf16(sum);
+      }
     }
   }
 }
 
-// C row m starts at C + m * ldc (the rows of a projection may go straight into a strided destination).  With
-// `row_pos` row m goes to ring slot clamp(row_pos[m], 0, pos_max) % ring of its sequence: C + m * ldc + slot * N.
+__global__ __launch_bounds__(PN_NT) void gemm_panel_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W,
+                                                          bf16_t *__restrict__ C, RowDest dest, int M, int N, int K, int kp,
+                                                          int k_slice, float *__restrict__ part) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char psm[];
+  gemm_panel_body(A, W, C, dest, M, N, K, kp, k_slice, part, psm);
+}
+
 template <typename T>
-__global__ void skinny_reduce_kernel(const float *__restrict__ part, T *__restrict__ C, long long mn, int N,
-                                     long long ldc, int splits, const int *__restrict__ row_pos, int pos_max,
-                                     int ring) {
+__global__ void skinny_reduce_kernel(const float *__restrict__ part, T *__restrict__ C, RowDest dest, long long mn, int N,
+                                     int splits) {
   const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
   if (id >= mn) return;
   float a = 0.f;
@@ -768,13 +933,7 @@ __global__ void skinny_reduce_kernel(const float *__restrict__ part, T *__restri
     for (int u = 0; u < 8; ++u) a += v[u];
   }
   for (; s < splits; ++s) a += part[(long long)s * mn + id];
-  const long long m = id / N;
-  long long slot_off = 0;
-  if (row_pos) {
-    const int p = row_pos[m];
-    slot_off = (long long)((p < 0 ? 0 : (p > pos_max ? pos_max : p)) % ring) * N;
-  }
-  store_f(C + m * ldc + slot_off + id % N, a);
+  store_f(C + dest.at((int)(id / N), N) + id % N, a);
 }
 
 int skinny_splits(int N, int K) {
@@ -786,32 +945,33 @@ int skinny_splits(int N, int K) {
 }
 size_t skinny_scratch_bytes(int M, int N, int K) { return (size_t)skinny_splits(N, K) * M * N * sizeof(float); }
 
+bool panel_supported(int N, int K) { return N % 8 == 0 && K % 8 == 0; }
+
+// slices = 1: C.  More: `part` gets that many partial sums (slices, M, N) for the caller's next kernel to add.
+hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest, float *part, int slices, int M, int N, int K,
+                      hipStream_t s) {
+  if (hipError_t e = raise_lds_limit<gemm_panel_kernel>(PN_LDS); e != hipSuccess) return e;
+  const int k_slice = ((K + slices - 1) / slices + 127) / 128 * 128;
+  const int kp = panel_rows(M, K < k_slice ? K : k_slice);
+  const size_t pass = (size_t)kp * (PN_COLS * 2 + 2 * (M < 32 ? M : 32)), lds = pass > PN_SUMS ? pass : PN_SUMS;
+  gemm_panel_kernel<<<dim3((N + PN_COLS - 1) / PN_COLS, slices), PN_NT, lds, s>>>(A, W, C, dest, M, N, K, kp, k_slice,
+                                                                                 slices > 1 ? part : nullptr);
+  return hipGetLastError();
+}
+
 template <typename T>
-hipError_t gemm_skinny(const T *A, const T *W, T *C, long long ldc, float *part, int M, int N, int K, hipStream_t s,
-                       const int *row_pos = nullptr, int pos_max = 0, int ring = 1) {
+hipError_t gemm_skinny(const T *A, const T *W, T *C, RowDest dest, float *part, int M, int N, int K, hipStream_t s) {
+  if constexpr (std::is_same<T, bf16_t>::value)
+    if (panel_supported(N, K)) return gemm_panel(A, W, C, dest, part, 1, M, N, K, s);
   const int splits = skinny_splits(N, K);
-  int chunk = (K + splits - 1) / splits;
+  const int chunk = (K + splits - 1) / splits;
   const dim3 grid((N + SK_COLS - 1) / SK_COLS, (K + chunk - 1) / chunk);
-  if constexpr (std::is_same<T, bf16_t>::value) {
-    if (N % 8 == 0 && K % 8 == 0) {
-      chunk = (chunk + 15) / 16 * 16;  // whole groups of 16 k (never above SK_MAXCHUNK, itself a multiple of 16)
-      const dim3 grid_m((N + SK_COLS - 1) / SK_COLS, (K + chunk - 1) / chunk);
-      gemm_skinny_mfma_kernel<<<grid_m, 256, 0, s>>>(A, W, part, M, N, K, chunk);
-      hipError_t em = hipGetLastError();
-      if (em != hipSuccess) return em;
-      const long long mn_m = (long long)M * N;
-      skinny_reduce_kernel<T><<<(unsigned)((mn_m + 255) / 256), 256, 0, s>>>(part, C, mn_m, N, ldc, (int)grid_m.y, row_pos,
-                                                                             pos_max, ring);
-      return hipGetLastError();
-    }
-  }
   if (M > 16) gemm_skinny_kernel<T, 32><<<grid, 256, 0, s>>>(A, W, part, M, N, K, chunk);
   else gemm_skinny_kernel<T, 16><<<grid, 256, 0, s>>>(A, W, part, M, N, K, chunk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const long long mn = (long long)M * N;
-  skinny_reduce_kernel<T><<<(unsigned)((mn + 255) / 256), 256, 0, s>>>(part, C, mn, N, ldc, (int)grid.y, row_pos, pos_max,
-                                                                         ring);
+  skinny_reduce_kernel<T><<<(unsigned)((mn + 255) / 256), 256, 0, s>>>(part, C, dest, mn, N, (int)grid.y);
   return hipGetLastError();
 }
 
@@ -821,6 +981,17 @@ int ring_rows(const Dims &d) {
   const int ks = (d.flags & CCA_CONV_SEQ) ? d.k_seq : 1, kc = (d.flags & CCA_CONV_CH) ? d.k_ch : 1;
   const int taps = ks + kc - 1;
   return (taps - 1 > 1 ? taps - 1 : 1) + 1;
+}
+
+// K slices of the down-projection on the matrix cores: enough workgroups for the chip, slices of 256 k at least, and no
+// more than the scratch of the split form holds (skinny_scratch_bytes)
+int down_slices(const Dims &d) {
+  const int cols = (d.n_lat + PN_COLS - 1) / PN_COLS, most = skinny_splits(d.n_lat, d.E);
+  int s = 256 / cols;
+  s = s < d.E / 256 ? s : d.E / 256;
+  s = s < most ? s : most;
+  s = s < MAX_PARTS ? s : MAX_PARTS;
+  return s < 1 ? 1 : s;
 }
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
@@ -857,29 +1028,45 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
   T *o = reinterpret_cast<T *>(ws + L.o);
   float *part = reinterpret_cast<float *>(ws + L.part);
   float *gpart = reinterpret_cast<float *>(ws + L.gemm);
-  // the new latent rows go straight into their ring slot
-  hipError_t e = pos_seq ? gemm_skinny<T>((const T *)x_new, (const T *)w.w_down, (T *)hist, (long long)P * d.n_lat, gpart,
-                                          d.B, d.n_lat, d.E, s, pos_seq, pos, P)
-                         : gemm_skinny<T>((const T *)x_new, (const T *)w.w_down,
-                                          (T *)hist + (long long)(pos % P) * d.n_lat, (long long)P * d.n_lat, gpart, d.B,
-                                          d.n_lat, d.E, s);
+  // The down-projection.  On the matrix cores it is split over K so that more CUs pull the weight (one CU takes in about 29
+  // GB/s of 64-byte pieces): the prologue adds the parts and writes the new latent rows into their ring slot.  Otherwise the
+  // rows go straight into the ring.
+  const long long ring_stride = (long long)P * d.n_lat;
+  const RowDest ring = pos_seq ? RowDest{ring_stride, pos_seq, pos, P} : RowDest{ring_stride, nullptr, 0, 1};
+  T *const ring_c = (T *)hist + (pos_seq ? 0 : (long long)(pos % P) * d.n_lat);
+  int nparts = 1;
+  hipError_t e;
+  if (std::is_same<T, bf16_t>::value && panel_supported(d.n_lat, d.E)) {
+    nparts = down_slices(d);
+    e = gemm_panel((const bf16_t *)x_new, (const bf16_t *)w.w_down, (bf16_t *)ring_c, ring, gpart, nparts, d.B, d.n_lat, d.E, s);
+  } else {
+    e = gemm_skinny<T>((const T *)x_new, (const T *)w.w_down, ring_c, ring, gpart, d.B, d.n_lat, d.E, s);
+  }
   if (e != hipSuccess) return e;
   {
-    int threads = 64;
-    while (threads < d.dh && threads < 256) threads *= 2;
     const int kc = (d.flags & CCA_CONV_CH) ? d.k_ch : 1;
-    const size_t smem = sizeof(float) * ((size_t)kc * d.dh + threads + d.dh);
-    decode_prologue_kernel<T><<<dim3(d.B, d.Hq + 2 * d.Hk), threads, smem, s>>>(
-        a, (const T *)hist, (const T *)w.w_conv_seq, (const T *)w.w_conv_ch, w.temp, q_new, (T *)k_cache,
-        (T *)v_cache);
+    const int threads = d.dh <= 64 ? 256 : 512, per_lane = (d.dh * kc / 8 + 7) / 8;  // filter chunks per lane of 8
+    const size_t smem = sizeof(float) * ((size_t)kc * d.dh + 2 * d.dh);
+#define CCA_DEC_PRO(CH, LPO)                                                                                              \
+  decode_prologue_kernel<T, CH, LPO><<<dim3(d.B, d.Hq + 2 * d.Hk), threads, smem, s>>>(                                    \
+      a, (T *)hist, nparts > 1 ? gpart : nullptr, nparts, (const T *)w.w_conv_seq, (const T *)w.w_conv_ch, w.temp, q_new, \
+      (T *)k_cache, (T *)v_cache)
+    if (per_lane <= 2) CCA_DEC_PRO(2, 8);
+    else if (per_lane <= 4) CCA_DEC_PRO(4, 8);
+    else if (per_lane <= 8) CCA_DEC_PRO(8, 8);
+    else CCA_DEC_PRO(8, 16);
+#undef CCA_DEC_PRO
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   {
     const int len = pos + 1;  // the longest sequence sizes the splits
-    // enough workgroups to fill the chip, at least 256 keys each, at most MAX_SPLITS
-    int nsplit = (1024 + d.B * d.Hk - 1) / (d.B * d.Hk);
-    nsplit = nsplit < (len + 255) / 256 ? nsplit : (len + 255) / 256;
-    nsplit = nsplit < 1 ? 1 : (nsplit > MAX_SPLITS ? MAX_SPLITS : nsplit);
+    // Every split but a sequence's last holds `per` keys: whole rounds of the row kernel's four wavefronts (a wavefront takes
+    // 4 KB of keys at a time), as few as leave about 1024 workgroups on the chip, at most MAX_SPLITS splits.
+    const int unit = d.dh <= 64 ? 256 : d.dh <= 128 ? 128 : 64;
+    const long long want = (1024 + (long long)d.B * d.Hk - 1) / ((long long)d.B * d.Hk);
+    const long long most = want < MAX_SPLITS ? want : MAX_SPLITS;
+    const int per = (int)(((len + most - 1) / most + unit - 1) / unit) * unit;
+    const int nsplit = (len + per - 1) / per;
     const size_t smem = sizeof(float) * ((size_t)R_MAX * d.dh + DEC_WAVES * 64 * R_MAX + DEC_WAVES * R_MAX * (2 + d.dh));
     const unsigned grid = (unsigned)((long long)d.B * d.Hk * nsplit);
     if constexpr (std::is_same<T, bf16_t>::value) {
@@ -889,7 +1076,7 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
           const int left = d.R - r0;
 #define CCA_DEC_ROWS(NR, DH, U)                                                                                    \
   decode_attn_rows_kernel<NR, DH, U><<<grid, DEC_WAVES * 64, 0, s>>>(a, q_new, (const bf16_t *)k_cache,             \
-                                                                     (const bf16_t *)v_cache, part, nsplit, r0)
+                                                                     (const bf16_t *)v_cache, part, nsplit, per, r0)
 #define CCA_DEC_ROWS_DH(NR, U)                                                                                     \
   {                                                                                                                \
     if (d.dh == 64) CCA_DEC_ROWS(NR, 64, U);                                                                       \
@@ -906,7 +1093,7 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
         }
         decode_combine_kernel<T><<<(unsigned)(d.B * d.Hq), 128, 0, s>>>(a, part, nsplit, o);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        return gemm_skinny<T>(o, (const T *)w.w_out, (T *)out, d.E, gpart, d.B, d.E, d.e_q, s);
+        return gemm_skinny<T>(o, (const T *)w.w_out, (T *)out, RowDest{d.E, nullptr, 0, 1}, gpart, d.B, d.E, d.e_q, s);
       }
     }
     for (int r0 = 0; r0 < d.R; r0 += R_MAX) {
@@ -915,7 +1102,7 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
     e = raise_lds_limit<decode_attn_kernel<T, CPL, DHC>>(smem);                                                 \
     if (e != hipSuccess) return e;                                                                              \
     decode_attn_kernel<T, CPL, DHC><<<grid, DEC_WAVES * 64, smem, s>>>(a, q_new, (const T *)k_cache,              \
-                                                                           (const T *)v_cache, part, nsplit, r0); \
+                                                                           (const T *)v_cache, part, nsplit, per, r0); \
   }
       if (d.dh == 64) CCA_DEC_ATTN(1, 64)
       else if (d.dh == 128) CCA_DEC_ATTN(2, 128)
@@ -929,7 +1116,7 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
     decode_combine_kernel<T><<<(unsigned)(d.B * d.Hq), 128, 0, s>>>(a, part, nsplit, o);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  return gemm_skinny<T>(o, (const T *)w.w_out, (T *)out, d.E, gpart, d.B, d.E, d.e_q, s);
+  return gemm_skinny<T>(o, (const T *)w.w_out, (T *)out, RowDest{d.E, nullptr, 0, 1}, gpart, d.B, d.E, d.e_q, s);
 }
 
 }  // namespace

@@ -6,6 +6,8 @@ import pytest
 import torch
 
 import paper_2510_04476_amd as P
+from synth_inputs import make_inputs
+from util import check_out, check_tap, oracle_forward, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -130,3 +132,47 @@ def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
             exact = o[b, :, h * dh:(h + 1) * dh].double() + o_lo[b, :, h * dh:(h + 1) * dh].double()
             assert float(((exact - ref).abs() / (2.0 ** -15 * ref.abs() + 6.0 * noise + 1e-6)).max()) <= 1.0
             assert float((lse[b, h].double() - ref_lse).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
+
+
+# the decode step's projections (several passes through LDS, K slices of the down-projection, lengths that are not whole
+# groups) and filter layouts: widths 256 and 64 with up to 4 + 4 taps, 5 query heads per KV head
+DECODE_CASES = [dict(B=9, T=5, E=4104, Hq=4, Hk=2, dh=64, k_seq=2, k_ch=2), dict(B=2, T=9, E=2056, Hq=4, Hk=2, dh=256, k_seq=4, k_ch=4),
+                dict(B=3, T=7, E=640, Hq=5, Hk=1, dh=64, k_seq=1, k_ch=4), dict(B=1, T=6, E=512, Hq=2, Hk=1, dh=256, k_seq=3, k_ch=3)]
+
+
+@pytest.mark.parametrize("i", range(len(DECODE_CASES)))
+def test_decode_projections_and_filters(i):
+    """Ring slots of tokens before the sequence's start may hold anything: they start as NaN here."""
+    w = dict(DECODE_CASES[i], dtype="bf16", paper_flags=True)
+    say("decode", w)
+    inp = make_inputs(w, seed=170 + i, conv_visible=True)
+    cfg = P.config_from_workload(w)
+    x, wt = P.weights_to_device(cfg, inp)
+    state = P.CCADecodeState.allocate(cfg, "cuda")
+    state.lat_ring.fill_(float("nan"))
+    outs = [P.cca_decode_step(cfg, wt, x[:, t].contiguous(), state, t) for t in range(w["T"])]
+    torch.cuda.synchronize()
+    ref = oracle_forward(w, inp)
+    say(check_out(to_np(torch.stack(outs, 1)), ref["out"], "bf16"))
+    say(check_tap(to_np(state.k_cache), ref["k"], "bf16", "k_cache"))
+    say(check_tap(to_np(state.v_cache), ref["v"], "bf16", "v_cache"))
+
+
+@pytest.mark.parametrize("Hq,Hk,dh", [(4, 2, 64), (4, 1, 128), (2, 2, 256)])
+def test_decode_split_edges(Hq, Hk, dh):
+    """Positions around the edges of the splits of the key range (units of 64, 128 and 256 keys)."""
+    w = dict(B=1, T=1100, E=512, Hq=Hq, Hk=Hk, dh=dh, k_seq=2, k_ch=2, dtype="bf16", paper_flags=True)
+    inp = make_inputs(w, seed=180, conv_visible=True)
+    cfg = P.config_from_workload(w)
+    x, wt = P.weights_to_device(cfg, inp)
+    saved = P.CCASaved.allocate(cfg, "cuda")
+    P.cca_forward(cfg, wt, x, saved=saved)
+    ref = oracle_forward(w, inp)["out"]
+    for pos in (0, 63, 64, 126, 127, 128, 255, 256, 511, 513, 1023, 1099):
+        say("decode split", Hq, Hk, dh, pos)
+        state = P.CCADecodeState.allocate(cfg, "cuda")
+        state.k_cache.fill_(float("nan")), state.v_cache.fill_(float("nan"))
+        state.load_prefill(saved, pos)
+        out = P.cca_decode_step(cfg, wt, x[:, pos].contiguous(), state, pos)
+        torch.cuda.synchronize()
+        check_out(to_np(out), ref[:, pos], "bf16")
