@@ -1,70 +1,94 @@
 // Shape-generic kernels for every stage of the CCA block: fp32 or bf16 storage,
-// fp32 arithmetic on the vector ALUs.  They serve the fp32 configuration and
-// every bf16 shape the MFMA kernels do not cover.  Simple data-parallel
-// mappings, no tuning.
-#include "cca_internal.h"
+// fp32 arithmetic (the contractions on the fp32 matrix cores).  They serve the fp32
+// configuration and every bf16 shape the bf16 MFMA kernels do not cover.
+#include "cca_generic.h"
 
 namespace cca {
 
 // ---------------------------------------------------------------------------
-// GEMM: C (M,N) = A (M,K) * Bm (K,N).  64x64 tile, 256 threads, 4x4 per thread.
+// GEMM: C (M,N) = op(A) op(B), op(A)[m][k] = TA ? A[k*lda + m] : A[m*lda + k], op(B)[k][n] = TB ? B[n*ldb + k] : B[k*ldb + n].
+// Workgroup = one 32 x 32 tile of C, the contraction dealt to its 8 wavefronts 8 terms at a time and their sums added
+// through LDS in order: these products are small (the fp32 configuration, odd bf16 shapes), so a walk along all of K by one
+// wavefront is what they would wait for.  K is a multiple of 4 where an operand is stored along it; lda, ldb likewise.
+// fp32, us, 64 x 64 tiles through LDS on the vector ALU -> this: 1000 x 192 over K = 256 31 -> 5.2, 256 x 192 over K = 1000
+// tokens 132 -> 12.1.
 // ---------------------------------------------------------------------------
+constexpr int GG_NT = 512, GG_WAVES = GG_NT / 64;
+
+template <typename T, bool TA, bool TB>
+__global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict__ A, long long lda, const T *__restrict__ Bm,
+                                                            long long ldb, T *__restrict__ C, long long ldc, long long M, int N,
+                                                            long long K) {
+  __shared__ float red[GG_WAVES][32][33];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int tiles_n = (N + 31) / 32;
+  const long long m0 = (long long)(blockIdx.x / tiles_n) * 32;
+  const int n0 = blockIdx.x % tiles_n * 32;
+  const long long m = m0 + l32 < M ? m0 + l32 : M - 1;  // rows and columns past the edge feed outputs that are not stored
+  const int n = n0 + l32 < N ? n0 + l32 : N - 1;
+  gen_f32x16 acc = zero16();
+  const long long last = K - 1;
+#pragma unroll 4
+  for (long long k0 = wave * 8 + 4 * half; k0 - 4 * half < K; k0 += GG_WAVES * 8) {
+    float a[4], b[4];
+    // terms past K: some readable value, dropped below
+    if constexpr (TA) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = load_f(A + (k0 + i < last ? k0 + i : last) * lda + m);
+    } else {
+      const gen_f32x4 v = load4(A + m * lda + (k0 < K ? k0 : 0));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = v[i];
+    }
+    if constexpr (TB) {
+      const gen_f32x4 v = load4(Bm + n * ldb + (k0 < K ? k0 : 0));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i] = v[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i] = load_f(Bm + (k0 + i < last ? k0 + i : last) * ldb + n);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool in = k0 + i < K;
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a[i] : 0.f, in ? b[i] : 0.f, acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[wave][tile_row(r, half)][l32] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < 32 * 32 / GG_NT; ++x) {
+    const int r = (tid >> 5) + x * (GG_NT / 32), c = tid & 31;
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < GG_WAVES; ++w) sum += red[w][r][c];
+    if (m0 + r < M && n0 + c < N) store_f(C + (m0 + r) * ldc + n0 + c, sum);
+  }
+}
+
 template <typename T>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ Bm,
-                                                          T *__restrict__ C, long long M, int N, int K) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 1];
-  __shared__ float Bs[BK][BN + 1];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const long long m0 = (long long)blockIdx.y * BM;
-  const int n0 = blockIdx.x * BN;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    for (int i = tid; i < BM * BK; i += 256) {
-      int r = i / BK, c = i % BK;
-      long long gm = m0 + r;
-      int gk = k0 + c;
-      As[c][r] = (gm < M && gk < K) ? load_f(A + gm * K + gk) : 0.f;
-    }
-    for (int i = tid; i < BK * BN; i += 256) {
-      int r = i / BN, c = i % BN;
-      int gk = k0 + r, gn = n0 + c;
-      Bs[r][c] = (gk < K && gn < N) ? load_f(Bm + (long long)gk * N + gn) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 4; ++i) {
-    long long gm = m0 + ty * 4 + i;
-    if (gm >= M) continue;
-    for (int j = 0; j < 4; ++j) {
-      int gn = n0 + tx * 4 + j;
-      if (gn < N) store_f(C + gm * N + gn, acc[i][j]);
-    }
-  }
+static hipError_t gemm_generic_t(const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb, void *C,
+                                 long long ldc, long long M, int N, long long K, hipStream_t s) {
+  const unsigned grid = (unsigned)((M + 31) / 32 * ((N + 31) / 32));
+#define GO(TA, TB) gemm_generic_kernel<T, TA, TB><<<grid, GG_NT, 0, s>>>((const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K)
+  if (ta && tb) GO(true, true);
+  else if (ta) GO(true, false);
+  else if (tb) GO(false, true);
+  else GO(false, false);
+#undef GO
+  return hipGetLastError();
+}
+
+hipError_t gemm_generic_ex(bool bf16, const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb,
+                           void *C, long long ldc, long long M, int N, long long K, hipStream_t s) {
+  return bf16 ? gemm_generic_t<bf16_t>(A, lda, ta, Bm, ldb, tb, C, ldc, M, N, K, s)
+              : gemm_generic_t<float>(A, lda, ta, Bm, ldb, tb, C, ldc, M, N, K, s);
 }
 
 hipError_t gemm_generic(bool bf16, const void *A, const void *Bm, void *C, long long M, int N, int K,
                         hipStream_t s) {
-  dim3 grid((N + 63) / 64, (unsigned)((M + 63) / 64));
-  if (bf16)
-    gemm_generic_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)A, (const bf16_t *)Bm, (bf16_t *)C, M, N, K);
-  else
-    gemm_generic_kernel<float><<<grid, 256, 0, s>>>((const float *)A, (const float *)Bm, (float *)C, M, N, K);
-  return hipGetLastError();
+  return gemm_generic_ex(bf16, A, K, false, Bm, N, false, C, N, M, N, K, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -216,71 +240,100 @@ hipError_t prologue_generic(const Dims &d, const cca_weights &w, const void *lat
 }
 
 // ---------------------------------------------------------------------------
-// Attention: one wavefront per query row (b, h, t).  Lane l walks keys
-// l, l+64, ... with its own running (max, sum, accumulator); the 64 partial
-// results are merged at the end.  DH_MAX bounds the per-lane accumulator.
+// Attention.  Workgroup = 32 query rows of one (batch, head); its 8 wavefronts take the 32-key tiles in turn, each with its
+// own running (max, sum, accumulator), merged through LDS at the end.  Scores come out transposed (lane = query, registers =
+// keys), so the row statistics are in-lane with one exchange between the half-waves and the probabilities are the second
+// operand of O^T += V^T P^T as they stand.  T = 1000, 2 heads of 32, fp32: 21.5 us; one wavefront per row on the vector ALU
+// took 100.
 // ---------------------------------------------------------------------------
-template <typename T, int DH_MAX>
-__global__ __launch_bounds__(64) void attention_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
-                                                              const T *__restrict__ v, T *__restrict__ o,
-                                                              T *__restrict__ o_lo, float *__restrict__ lse, int Tn,
-                                                              int Hq, int Hk, int dh,
-                                                              float scale, int causal) {
-  __shared__ float qs[DH_MAX];
-  const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int g = h / (Hq / Hk);
-  const int lane = threadIdx.x;
-  const long long qrow = ((long long)b * Tn + t) * Hq + h;
-  for (int i = lane; i < dh; i += 64) qs[i] = load_f(q + qrow * dh + i) * scale;
+constexpr int GA_NT = 512, GA_WAVES = GA_NT / 64;
+
+template <typename T, int DHM>
+__global__ __launch_bounds__(GA_NT) void attention_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                                 const T *__restrict__ v, T *__restrict__ o,
+                                                                 T *__restrict__ o_lo, float *__restrict__ lse, int Tn, int Hq,
+                                                                 int Hk, int dh, float scale, int causal) {
+  constexpr int DT = DHM / 32;
+  __shared__ __attribute__((aligned(16))) float sq[32 * (DHM + 4)];
+  __shared__ float sm_[GA_WAVES][32], sl[GA_WAVES][32], so[GA_WAVES][16][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int qb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z, g = h / (Hq / Hk);  // causal: long rows first
+  const int q0 = qb * 32, t = q0 + l32;
+  const T *const kb = k + ((long long)b * Tn * Hk + g) * dh, *const vb = v + ((long long)b * Tn * Hk + g) * dh;
+  const long long ks = (long long)Hk * dh;
+  stage_rows32<DHM>(sq, q + ((long long)b * Tn * Hq + h) * dh, (long long)Hq * dh, q0, Tn - 1, dh, [=](float x) { return x * scale; });
   __syncthreads();
-  float m = -INFINITY, z = 0.f;
-  float acc[DH_MAX];
+  float m = -INFINITY, l = 0.f;
+  gen_f32x16 acc[DT];
 #pragma unroll
-  for (int i = 0; i < DH_MAX; ++i) acc[i] = 0.f;
-  const int s_end = causal ? t + 1 : Tn;
-  for (int s = lane; s < s_end; s += 64) {
-    const long long krow = ((long long)b * Tn + s) * Hk + g;
-    const T *kp = k + krow * dh;
-    float dot = 0.f;
-    for (int i = 0; i < dh; ++i) dot = fmaf(qs[i], load_f(kp + i), dot);
-    const float mn = fmaxf(m, dot);
-    const float corr = expf(m - mn);  // exp(-inf) = 0 on the first key
-    const float p = expf(dot - mn);
-    z = z * corr + p;
-    const T *vp = v + krow * dh;
+  for (int dt = 0; dt < DT; ++dt) acc[dt] = zero16();
+  const int end = causal ? min(q0 + 32, Tn) : Tn;  // keys [0, end) matter
+  for (int k0 = wave * 32; k0 < end; k0 += GA_WAVES * 32) {
+    const gen_f32x16 s = dot_tile<DHM>(kb + min(k0 + l32, Tn - 1) * ks, sq + l32 * (DHM + 4), dh, half, [](float x) { return x; });
+    const bool mixed = k0 + 32 > Tn || (causal && k0 + 31 > q0);
+    float w[16], mx = m;
 #pragma unroll
-    for (int i = 0; i < DH_MAX; ++i)
-      if (i < dh) acc[i] = fmaf(p, load_f(vp + i), acc[i] * corr);
-    m = mn;
+    for (int r = 0; r < 16; ++r) {
+      const int key = k0 + tile_row(r, half);
+      w[r] = key < Tn && (!causal || key <= t) ? s[r] : -INFINITY;
+      mx = fmaxf(mx, w[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32));  // finite: a tile's first key is visible to every row of the block
+    const float corr = expf(m - mx);     // 0 on the first tile
+    l *= corr;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      w[r] = expf(w[r] - mx);
+      l += w[r];
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[dt][r] *= corr;
+    add_outer<DT, T>(acc, w, [=](int x) { return vb + min(k0 + x, Tn - 1) * ks; }, dh, lane, mixed);
+    m = mx;
   }
-  // merge the 64 lanes
-  float M = m;
-  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-  const float f = (m == -INFINITY) ? 0.f : expf(m - M);
-  float Z = z * f;
-  for (int off = 32; off > 0; off >>= 1) Z += __shfl_xor(Z, off);
-  const float inv = 1.f / Z;
+  l += __shfl_xor(l, 32);  // each half-wave has summed half of the keys
+  if (half == 0) sm_[wave][l32] = m, sl[wave][l32] = l;
+  __syncthreads();
+  float M = -INFINITY, L = 0.f, f[GA_WAVES];  // of query l32, the same for every wavefront
 #pragma unroll
-  for (int i = 0; i < DH_MAX; ++i) {
-    if (i < dh) {
-      float a = acc[i] * f;
-      for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-      if (lane == 0) {
-        store_f(o + qrow * dh + i, a * inv);
-        if (o_lo) store_f(o_lo + qrow * dh + i, a * inv - load_f(o + qrow * dh + i));  // what the rounding dropped
+  for (int x = 0; x < GA_WAVES; ++x) M = fmaxf(M, sm_[x][l32]);
+#pragma unroll
+  for (int x = 0; x < GA_WAVES; ++x) {
+    f[x] = sm_[x][l32] == -INFINITY ? 0.f : expf(sm_[x][l32] - M);
+    L += sl[x][l32] * f[x];
+  }
+  const float inv = 1.f / L;
+  const long long orow = (((long long)b * Tn + t) * Hq + h) * dh;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) {
+    if (dt > 0) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) so[wave][r][lane] = acc[dt][r];
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 16 / GA_WAVES; ++x) {
+      const int r = wave * (16 / GA_WAVES) + x, ch = 32 * dt + tile_row(r, half);
+      float sum = 0.f;
+#pragma unroll
+      for (int y = 0; y < GA_WAVES; ++y) sum += f[y] == 0.f ? 0.f : so[y][r][lane] * f[y];
+      if (t < Tn && ch < dh) {
+        store_f(o + orow + ch, sum * inv);
+        if (o_lo) store_f(o_lo + orow + ch, sum * inv - load_f(o + orow + ch));  // what the rounding dropped
       }
     }
   }
-  if (lse && lane == 0) lse[((long long)b * Hq + h) * Tn + t] = M + logf(Z);
+  if (lse && wave == 0 && half == 0 && t < Tn) lse[((long long)b * Hq + h) * Tn + t] = M + logf(L);
 }
 
 template <typename T>
 static hipError_t attention_generic_t(const Dims &d, const void *q, const void *k, const void *v, void *o,
                                       void *o_lo, float *lse, hipStream_t s) {
-  dim3 grid(d.T, d.Hq, d.B);
+  dim3 grid((d.T + 31) / 32, d.Hq, d.B);
   const int causal = (d.flags & CCA_CAUSAL) ? 1 : 0;
 #define LAUNCH(DH)                                                                                      \
-  attention_generic_kernel<T, DH><<<grid, 64, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (T *)o, (T *)o_lo, lse, d.T, \
+  attention_generic_kernel<T, DH><<<grid, GA_NT, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (T *)o, (T *)o_lo, lse, d.T, \
                                                       d.Hq, d.Hk, d.dh, d.scale, causal)
   if (d.dh <= 32) LAUNCH(32);
   else if (d.dh <= 64) LAUNCH(64);

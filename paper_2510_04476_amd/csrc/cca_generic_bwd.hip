@@ -1,78 +1,11 @@
 // Shape-generic backward kernels (adjoints of the steps of Sec. 2.2, which the
-// paper states forward only): fp32 or bf16 storage, fp32 arithmetic on the
-// vector ALUs.  They serve the fp32 configuration and every bf16 shape the
-// MFMA backward kernels do not cover.  Every sum runs in a fixed order (no
+// paper states forward only): fp32 or bf16 storage, fp32 arithmetic (the
+// contractions on the fp32 matrix cores).  They serve the fp32 configuration and
+// every bf16 shape the bf16 MFMA backward kernels do not cover.  Every sum runs in a fixed order (no
 // atomics), so results are reproducible bit for bit.
-#include "cca_internal.h"
+#include "cca_generic.h"
 
 namespace cca {
-
-// ---------------------------------------------------------------------------
-// GEMM with optional transposes: C (M,N) = op(A) * op(B),
-//   op(A)[m][k] = ta ? A[k*lda + m] : A[m*lda + k],  op(B)[k][n] = tb ? B[n*ldb + k] : B[k*ldb + n].
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_generic_ex_kernel(const T *__restrict__ A, long long lda, int ta,
-                                                             const T *__restrict__ Bm, long long ldb, int tb,
-                                                             T *__restrict__ C, long long ldc, long long M, int N,
-                                                             long long K) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 1];
-  __shared__ float Bs[BK][BN + 1];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const long long m0 = (long long)blockIdx.y * BM;
-  const int n0 = blockIdx.x * BN;
-  float acc[4][4] = {};
-  for (long long k0 = 0; k0 < K; k0 += BK) {
-    for (int i = tid; i < BM * BK; i += 256) {
-      // walk the contiguous direction of A with consecutive threads
-      const int r = ta ? i % BM : i / BK, c = ta ? i / BM : i % BK;
-      const long long gm = m0 + r, gk = k0 + c;
-      As[c][r] = (gm < M && gk < K) ? load_f(A + (ta ? gk * lda + gm : gm * lda + gk)) : 0.f;
-    }
-    for (int i = tid; i < BK * BN; i += 256) {
-      const int r = tb ? i % BK : i / BN, c = tb ? i / BK : i % BN;
-      const long long gk = k0 + r;
-      const int gn = n0 + c;
-      Bs[r][c] = (gk < K && gn < N) ? load_f(Bm + (tb ? (long long)gn * ldb + gk : gk * ldb + gn)) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 4; ++i) {
-    const long long gm = m0 + ty * 4 + i;
-    if (gm >= M) continue;
-    for (int j = 0; j < 4; ++j) {
-      const int gn = n0 + tx * 4 + j;
-      if (gn < N) store_f(C + gm * ldc + gn, acc[i][j]);
-    }
-  }
-}
-
-hipError_t gemm_generic_ex(bool bf16, const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb,
-                           void *C, long long ldc, long long M, int N, long long K, hipStream_t s) {
-  dim3 grid((N + 63) / 64, (unsigned)((M + 63) / 64));
-  if (bf16)
-    gemm_generic_ex_kernel<bf16_t><<<grid, 256, 0, s>>>((const bf16_t *)A, lda, ta, (const bf16_t *)Bm, ldb, tb,
-                                                       (bf16_t *)C, ldc, M, N, K);
-  else
-    gemm_generic_ex_kernel<float><<<grid, 256, 0, s>>>((const float *)A, lda, ta, (const float *)Bm, ldb, tb,
-                                                      (float *)C, ldc, M, N, K);
-  return hipGetLastError();
-}
 
 // ---------------------------------------------------------------------------
 // Attention backward.  With P = softmax(scale Q K^T) row-wise and
@@ -98,104 +31,130 @@ __global__ __launch_bounds__(256) void delta_generic_kernel(const T *__restrict_
 __device__ __forceinline__ float q_log2_rounded(float q, float c) { return bf16_to_f32(f32_to_bf16(q * c)); }
 constexpr float kLog2e = 1.44269504088896340736f;
 
-// one wavefront per query row (b, h, t); lane l walks keys l, l + 64, ...
-template <typename T, int DH_MAX>
-__global__ __launch_bounds__(64) void attn_bwd_dq_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
-                                                                const T *__restrict__ v, const T *__restrict__ dO,
-                                                                const float *__restrict__ lse,
-                                                                const float *__restrict__ delta, T *__restrict__ dq,
-                                                                int Tn, int Hq, int Hk, int dh, float scale,
-                                                                int causal, int q_rounded) {
-  __shared__ float qs[DH_MAX], ds_[DH_MAX];
-  const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int g = h / (Hq / Hk);
-  const int lane = threadIdx.x;
-  const long long qrow = ((long long)b * Tn + t) * Hq + h;
-  for (int i = lane; i < dh; i += 64) {
-    const float qv = load_f(q + qrow * dh + i);
-    qs[i] = q_rounded ? q_log2_rounded(qv, scale * kLog2e) : qv * scale;
-    ds_[i] = load_f(dO + qrow * dh + i);
-  }
-  __syncthreads();
-  const float L = lse[((long long)b * Hq + h) * Tn + t] * (q_rounded ? kLog2e : 1.f);
-  const float Dl = delta[((long long)b * Hq + h) * Tn + t];
-  float acc[DH_MAX];
+constexpr int GB_NT = 512, GB_WAVES = GB_NT / 64;
+
+// Sums of the wavefronts' accumulators, in wavefront order: out(channel, column l32, sum) once per element of the tile
+template <int DT, typename F>
+__device__ __forceinline__ void sum_wavefronts(const gen_f32x16 (&acc)[DT], float (*so)[16][64], int wave, int lane, F &&out) {
 #pragma unroll
-  for (int i = 0; i < DH_MAX; ++i) acc[i] = 0.f;
-  const int s_end = causal ? t + 1 : Tn;
-  for (int s = lane; s < s_end; s += 64) {
-    const long long krow = ((long long)b * Tn + s) * Hk + g;
-    const T *kp = k + krow * dh, *vp = v + krow * dh;
-    float dot = 0.f, dp = 0.f;
-    for (int i = 0; i < dh; ++i) {
-      dot = fmaf(qs[i], load_f(kp + i), dot);
-      dp = fmaf(ds_[i], load_f(vp + i), dp);
-    }
-    const float dsv = (q_rounded ? exp2f(dot - L) : expf(dot - L)) * (dp - Dl);
+  for (int dt = 0; dt < DT; ++dt) {
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < DH_MAX; ++i)
-      if (i < dh) acc[i] = fmaf(dsv, load_f(kp + i), acc[i]);
-  }
+    for (int r = 0; r < 16; ++r) so[wave][r][lane] = acc[dt][r];
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < DH_MAX; ++i) {
-    if (i < dh) {
-      float a = acc[i];
-      for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-      if (lane == 0) store_f(dq + qrow * dh + i, a * scale);
+    for (int x = 0; x < 16 / GB_WAVES; ++x) {
+      const int r = wave * (16 / GB_WAVES) + x;
+      float sum = 0.f;
+#pragma unroll
+      for (int y = 0; y < GB_WAVES; ++y) sum += so[y][r][lane];
+      out(32 * dt + tile_row(r, lane >> 5), sum);
     }
   }
 }
 
-// one wavefront per key (b, g, s); lanes walk the (query head of the group, query row) pairs that see the key.
-// WHICH = 0: dK, 1: dV (one accumulator per lane).
-template <typename T, int DH_MAX, int WHICH>
-__global__ __launch_bounds__(64) void attn_bwd_dkv_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
-                                                                 const T *__restrict__ v, const T *__restrict__ dO,
-                                                                 const float *__restrict__ lse,
-                                                                 const float *__restrict__ delta, T *__restrict__ out,
-                                                                 int Tn, int Hq, int Hk, int dh, float scale,
-                                                                 int causal, int q_rounded) {
-  __shared__ float ks[DH_MAX], vs[DH_MAX];
-  const int s = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
-  const int R = Hq / Hk;
-  const int lane = threadIdx.x;
-  const long long krow = ((long long)b * Tn + s) * Hk + g;
-  for (int i = lane; i < dh; i += 64) {
-    ks[i] = load_f(k + krow * dh + i) * (q_rounded ? 1.f : scale);
-    vs[i] = load_f(v + krow * dh + i);
-  }
+// Workgroup = 32 query rows of one head, the key tiles dealt to its 8 wavefronts; S^T and dP^T with one query per lane, dS^T
+// is the second operand of dQ^T += K^T dS^T as it stands.  T = 1000, 2 heads of 32, fp32: 26 us; one wavefront per row on
+// the vector ALU took 117.
+template <typename T, int DHM>
+__global__ __launch_bounds__(GB_NT) void attn_bwd_dq_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                                   const T *__restrict__ v, const T *__restrict__ dO,
+                                                                   const float *__restrict__ lse,
+                                                                   const float *__restrict__ delta, T *__restrict__ dq, int Tn,
+                                                                   int Hq, int Hk, int dh, float scale, int causal,
+                                                                   int q_rounded) {
+  constexpr int DT = DHM / 32;
+  __shared__ __attribute__((aligned(16))) float sq[32 * (DHM + 4)], sd[32 * (DHM + 4)];
+  __shared__ float so[GB_WAVES][16][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int qb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z, g = h / (Hq / Hk);
+  const int q0 = qb * 32, t = q0 + l32, tc = min(t, Tn - 1);
+  const T *const kb = k + ((long long)b * Tn * Hk + g) * dh, *const vb = v + ((long long)b * Tn * Hk + g) * dh;
+  const long long ks = (long long)Hk * dh, qs = (long long)Hq * dh, q_off = ((long long)b * Tn * Hq + h) * dh;
+  stage_rows32<DHM>(sq, q + q_off, qs, q0, Tn - 1, dh,
+                    [=](float x) { return q_rounded ? q_log2_rounded(x, scale * kLog2e) : x * scale; });
+  stage_rows32<DHM>(sd, dO + q_off, qs, q0, Tn - 1, dh, [](float x) { return x; });
+  const float L = lse[((long long)b * Hq + h) * Tn + tc] * (q_rounded ? kLog2e : 1.f);
+  const float Dl = delta[((long long)b * Hq + h) * Tn + tc];
   __syncthreads();
-  float acc[DH_MAX];
+  gen_f32x16 acc[DT];
 #pragma unroll
-  for (int i = 0; i < DH_MAX; ++i) acc[i] = 0.f;
-  const int t_begin = causal ? s : 0;
-  const int nt = Tn - t_begin;
-  for (int idx = lane; idx < nt * R; idx += 64) {
-    const int h = g * R + idx / nt, t = t_begin + idx % nt;
-    const long long qrow = ((long long)b * Tn + t) * Hq + h;
-    const T *qp = q + qrow * dh, *dp_ = dO + qrow * dh;
-    float dot = 0.f, dp = 0.f;
-    for (int i = 0; i < dh; ++i) {
-      const float qv = load_f(qp + i);
-      dot = fmaf(ks[i], q_rounded ? q_log2_rounded(qv, scale * kLog2e) : qv, dot);
-      dp = fmaf(vs[i], load_f(dp_ + i), dp);
+  for (int dt = 0; dt < DT; ++dt) acc[dt] = zero16();
+  const int end = causal ? min(q0 + 32, Tn) : Tn;
+  auto same = [](float x) { return x; };
+  for (int k0 = wave * 32; k0 < end; k0 += GB_WAVES * 32) {
+    const long long krow = min(k0 + l32, Tn - 1) * ks;
+    const gen_f32x16 s = dot_tile<DHM>(kb + krow, sq + l32 * (DHM + 4), dh, half, same);
+    const gen_f32x16 dp = dot_tile<DHM>(vb + krow, sd + l32 * (DHM + 4), dh, half, same);
+    const bool mixed = k0 + 32 > Tn || (causal && k0 + 31 > q0);
+    float w[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = k0 + tile_row(r, half);
+      const float x = (q_rounded ? exp2f(s[r] - L) : expf(s[r] - L)) * (dp[r] - Dl);
+      w[r] = key < Tn && (!causal || key <= t) ? x : 0.f;
     }
-    const long long st = ((long long)b * Hq + h) * Tn + t;
-    const float p = q_rounded ? exp2f(dot - lse[st] * kLog2e) : expf(dot - lse[st]);
-    const float w = WHICH == 0 ? p * (dp - delta[st]) * scale : p;
-    const T *src = WHICH == 0 ? qp : dp_;
-#pragma unroll
-    for (int i = 0; i < DH_MAX; ++i)
-      if (i < dh) acc[i] = fmaf(w, load_f(src + i), acc[i]);
+    add_outer<DT, T>(acc, w, [=](int x) { return kb + min(k0 + x, Tn - 1) * ks; }, dh, lane, mixed);
   }
+  sum_wavefronts(acc, so, wave, lane, [&](int ch, float sum) {
+    if (t < Tn && ch < dh) store_f(dq + q_off + t * qs + ch, sum * scale);
+  });
+}
+
+// Workgroup = 32 keys of one KV head, the (query head of the group, query tile) pairs that see them dealt to its 8
+// wavefronts; S and dP with one key per lane.  WHICH: 1 = dK, 2 = dV, 3 = both (d_h <= 128: two sets of accumulators fit).
+// T = 1000, 2 heads of 32, fp32: 41.5 us; one wavefront per key, dK and dV apart, on the vector ALU took 305 + 189.
+template <typename T, int DHM, int WHICH>
+__global__ __launch_bounds__(GB_NT) void attn_bwd_dkv_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                                    const T *__restrict__ v, const T *__restrict__ dO,
+                                                                    const float *__restrict__ lse,
+                                                                    const float *__restrict__ delta, T *__restrict__ dk,
+                                                                    T *__restrict__ dv, int Tn, int Hq, int Hk, int dh,
+                                                                    float scale, int causal, int q_rounded) {
+  constexpr int DT = DHM / 32;
+  __shared__ __attribute__((aligned(16))) float sk[32 * (DHM + 4)], sv[32 * (DHM + 4)];
+  __shared__ float so[GB_WAVES][16][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int k0 = blockIdx.x * 32, g = blockIdx.y, b = blockIdx.z, R = Hq / Hk, key = k0 + l32;
+  const long long ks = (long long)Hk * dh, qs = (long long)Hq * dh, k_off = ((long long)b * Tn * Hk + g) * dh;
+  stage_rows32<DHM>(sk, k + k_off, ks, k0, Tn - 1, dh, [=](float x) { return x * (q_rounded ? 1.f : scale); });
+  stage_rows32<DHM>(sv, v + k_off, ks, k0, Tn - 1, dh, [](float x) { return x; });
+  __syncthreads();
+  gen_f32x16 ak[WHICH & 1 ? DT : 1], av[WHICH & 2 ? DT : 1];
 #pragma unroll
-  for (int i = 0; i < DH_MAX; ++i) {
-    if (i < dh) {
-      float a = acc[i];
-      for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-      if (lane == 0) store_f(out + krow * dh + i, a);
+  for (int dt = 0; dt < (WHICH & 1 ? DT : 1); ++dt) ak[dt] = zero16();
+#pragma unroll
+  for (int dt = 0; dt < (WHICH & 2 ? DT : 1); ++dt) av[dt] = zero16();
+  const int first = causal ? k0 / 32 : 0, tiles = (Tn + 31) / 32 - first;
+  for (int idx = wave; idx < R * tiles; idx += GB_WAVES) {
+    const int h = g * R + idx / tiles, t0 = (first + idx % tiles) * 32;
+    const T *const qb = q + ((long long)b * Tn * Hq + h) * dh, *const db = dO + ((long long)b * Tn * Hq + h) * dh;
+    const long long qrow = min(t0 + l32, Tn - 1) * qs, st = ((long long)b * Hq + h) * Tn;
+    const gen_f32x16 s = dot_tile<DHM>(qb + qrow, sk + l32 * (DHM + 4), dh, half,
+                                       [=](float x) { return q_rounded ? q_log2_rounded(x, scale * kLog2e) : x; });
+    gen_f32x16 dp;
+    if constexpr (WHICH & 1) dp = dot_tile<DHM>(db + qrow, sv + l32 * (DHM + 4), dh, half, [](float x) { return x; });
+    const bool mixed = t0 + 32 > Tn || (causal && t0 < k0 + 31);
+    float p[16], ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int t = t0 + tile_row(r, half), tc = min(t, Tn - 1);
+      const float L = lse[st + tc];
+      const bool in = t < Tn && (!causal || key <= t);
+      p[r] = in ? (q_rounded ? exp2f(s[r] - L * kLog2e) : expf(s[r] - L)) : 0.f;
+      if constexpr (WHICH & 1) ds[r] = in ? p[r] * (dp[r] - delta[st + tc]) * scale : 0.f;
     }
+    if constexpr (WHICH & 2) add_outer<DT, T>(av, p, [=](int x) { return db + min(t0 + x, Tn - 1) * qs; }, dh, lane, mixed);
+    if constexpr (WHICH & 1) add_outer<DT, T>(ak, ds, [=](int x) { return qb + min(t0 + x, Tn - 1) * qs; }, dh, lane, mixed);
   }
+  if constexpr (WHICH & 1)
+    sum_wavefronts(ak, so, wave, lane, [&](int ch, float sum) {
+      if (key < Tn && ch < dh) store_f(dk + k_off + key * ks + ch, sum);
+    });
+  if constexpr (WHICH & 2)
+    sum_wavefronts(av, so, wave, lane, [&](int ch, float sum) {
+      if (key < Tn && ch < dh) store_f(dv + k_off + key * ks + ch, sum);
+    });
 }
 
 template <typename T>
@@ -207,24 +166,31 @@ static hipError_t attention_bwd_generic_t(const Dims &d, const void *q, const vo
                                                                           d.T, d.Hq, d.dh);
   const int causal = (d.flags & CCA_CAUSAL) ? 1 : 0;
   const int q_rounded = attention_mfma_supported(d) ? 1 : 0;  // lse then comes from the MFMA forward kernel
-  dim3 gq(d.T, d.Hq, d.B), gk(d.T, d.Hk, d.B);
-#define LAUNCH(DH)                                                                                                    \
-  do {                                                                                                                \
-    attn_bwd_dq_generic_kernel<T, DH><<<gq, 64, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (const T *)d_o, lse, \
-                                                        delta, (T *)d_q, d.T, d.Hq, d.Hk, d.dh, d.scale, causal,      \
-                                                        q_rounded);                                                   \
-    attn_bwd_dkv_generic_kernel<T, DH, 0><<<gk, 64, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (const T *)d_o,  \
-                                                            lse, delta, (T *)d_k, d.T, d.Hq, d.Hk, d.dh, d.scale,     \
-                                                            causal, q_rounded);                                       \
-    attn_bwd_dkv_generic_kernel<T, DH, 1><<<gk, 64, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (const T *)d_o,  \
-                                                            lse, delta, (T *)d_v, d.T, d.Hq, d.Hk, d.dh, d.scale,     \
-                                                            causal, q_rounded);                                       \
+  const dim3 gq((d.T + 31) / 32, d.Hq, d.B), gk((d.T + 31) / 32, d.Hk, d.B);
+#define DQ(DH)                                                                                                          \
+  attn_bwd_dq_generic_kernel<T, DH><<<gq, GB_NT, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (const T *)d_o, lse, \
+                                                         delta, (T *)d_q, d.T, d.Hq, d.Hk, d.dh, d.scale, causal, q_rounded)
+#define DKV(DH, W)                                                                                                      \
+  attn_bwd_dkv_generic_kernel<T, DH, W><<<gk, GB_NT, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (const T *)d_o,  \
+                                                             lse, delta, (T *)d_k, (T *)d_v, d.T, d.Hq, d.Hk, d.dh,     \
+                                                             d.scale, causal, q_rounded)
+#define LAUNCH(DH)          \
+  do {                      \
+    DQ(DH);                 \
+    if constexpr (DH <= 128) { \
+      DKV(DH, 3);           \
+    } else {                \
+      DKV(DH, 1);           \
+      DKV(DH, 2);           \
+    }                       \
   } while (0)
   if (d.dh <= 32) LAUNCH(32);
   else if (d.dh <= 64) LAUNCH(64);
   else if (d.dh <= 128) LAUNCH(128);
   else LAUNCH(256);
 #undef LAUNCH
+#undef DKV
+#undef DQ
   return hipGetLastError();
 }
 
@@ -390,55 +356,83 @@ __global__ __launch_bounds__(256) void pro_bwd_dlat_generic_kernel(ProBwdArgs a,
   store_f(d_lat + id, val);
 }
 
-// conv1_seq output u1[row, ch] recomputed from the pre-conv latent (zero before the sequence start)
+// dw1[h,o,i,j] = sum_rows d3[row,h,o] * u1[row - (k_ch-1-j), h, i], u1 = the conv1_seq output, recomputed from the pre-conv
+// latent (zero before the sequence start).  Workgroup = (head, tap j, 32 outputs o, 32 inputs i), the rows dealt to its 8
+// wavefronts 8 at a time.  T = 1000, 4 heads of 32, k_ch = 2, fp32: 37 us; one thread per filter element took 535.
 template <typename T>
-__device__ __forceinline__ float conv_seq_at(const ProBwdArgs &a, const T *__restrict__ lat, const T *__restrict__ w0,
-                                             long long row, int t, int ch) {
-  if (!(a.flags & CCA_CONV_SEQ)) return load_f(lat + row * a.n_lat + ch);
-  float acc = 0.f;
-  for (int jj = 0; jj < a.k_seq; ++jj) {
-    const int back = a.k_seq - 1 - jj;
-    if (t >= back) acc = fmaf(load_f(w0 + (long long)ch * a.k_seq + jj), load_f(lat + (row - back) * a.n_lat + ch), acc);
+__global__ __launch_bounds__(GB_NT) void pro_bwd_dw1_generic_kernel(ProBwdArgs a, const T *__restrict__ lat,
+                                                                   const T *__restrict__ w0, const float *__restrict__ d3,
+                                                                   T *__restrict__ dw1) {
+  __shared__ float so[GB_WAVES][16][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int dh = a.dh, kc = a.k_ch, nt = (dh + 31) / 32, ks = (a.flags & CCA_CONV_SEQ) ? a.k_seq : 1;
+  const int h = blockIdx.y, j = blockIdx.z, o0 = blockIdx.x / nt * 32, i0 = blockIdx.x % nt * 32;
+  const int ch0 = h < a.Hq ? h * dh : a.e_q + (h - a.Hq) * dh, ld = a.e_q + a.e_kv, back = kc - 1 - j;
+  const int oc = ch0 + min(o0 + l32, dh - 1), ic = ch0 + min(i0 + l32, dh - 1);  // past the head: results not stored
+  float f[4];
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj)
+    f[jj] = (a.flags & CCA_CONV_SEQ) ? load_f(w0 + (long long)ic * a.k_seq + min(jj, a.k_seq - 1)) : 1.f;
+  gen_f32x16 acc[1] = {zero16()};
+#pragma unroll 2
+  for (long long r0 = wave * 8 + 4 * half; r0 - 4 * half < a.rows; r0 += GB_WAVES * 8) {
+    float x[4], y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const long long row = r0 + e < a.rows ? r0 + e : a.rows - 1;
+      const int t = (int)(row % a.T);
+      x[e] = d3[row * ld + oc];
+      float u = 0.f;
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const int dist = back + ks - 1 - jj;  // tokens back from the row
+        const bool in = jj < ks && t >= dist;
+        const float l = load_f(lat + (in ? row - dist : row) * a.n_lat + ic);
+        u = in ? fmaf(f[jj], l, u) : u;
+      }
+      const bool live = r0 + e < a.rows && t >= back;
+      x[e] = live ? x[e] : 0.f;
+      y[e] = live ? u : 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc[0], 0, 0, 0);
   }
-  return acc;
+  sum_wavefronts(acc, so, wave, lane, [&](int o, float sum) {
+    if (o0 + o < dh && i0 + l32 < dh) store_f(dw1 + (((long long)h * dh + o0 + o) * dh + i0 + l32) * kc + j, sum);
+  });
 }
 
-// dw1[h,o,i,j] = sum_rows d3[row,h,o] * u1[row - (k_ch-1-j), h, i]; one thread per filter element
+// dw0[c,jj] = sum_rows d1[row,c] * lat[row - (k_seq-1-jj), c].  Workgroup = 32 channels x 32 groups of rows, all taps at
+// once; the groups' sums are added through LDS in order.  T = 1000, 128 channels, 2 taps: 21.5 us; one thread per element
+// took 288.
 template <typename T>
-__global__ __launch_bounds__(256) void pro_bwd_dw1_generic_kernel(ProBwdArgs a, const T *__restrict__ lat,
-                                                                 const T *__restrict__ w0,
-                                                                 const float *__restrict__ d3, T *__restrict__ dw1) {
-  const int dh = a.dh, kc = a.k_ch;
-  const long long id = (long long)blockIdx.x * 256 + threadIdx.x;  // ((h*dh + o)*kc + j)*dh + i: i fastest
-  if (id >= (long long)(a.Hq + a.Hk) * dh * dh * kc) return;
-  const int i = (int)(id % dh), j = (int)((id / dh) % kc), o = (int)((id / ((long long)dh * kc)) % dh);
-  const int h = (int)(id / ((long long)dh * kc * dh));
-  const int ch0 = h < a.Hq ? h * dh : a.e_q + (h - a.Hq) * dh;
-  const int ld = a.e_q + a.e_kv, back = kc - 1 - j;
-  float acc = 0.f;
-  for (long long row = 0; row < a.rows; ++row) {
+__global__ __launch_bounds__(1024) void pro_bwd_dw0_generic_kernel(ProBwdArgs a, const T *__restrict__ lat,
+                                                                  const float *__restrict__ d1, T *__restrict__ dw0) {
+  __shared__ float red[32][4][33];
+  const int ld = a.e_q + a.e_kv, cl = threadIdx.x & 31, grp = threadIdx.x >> 5, ks = a.k_seq;
+  const int c = blockIdx.x * 32 + cl, cc = min(c, ld - 1);
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (long long row = grp; row < a.rows; row += 32) {
     const int t = (int)(row % a.T);
-    if (t < back) continue;
-    acc = fmaf(d3[row * ld + ch0 + o], conv_seq_at(a, lat, w0, row - back, t - back, ch0 + i), acc);
+    const float g = d1[row * ld + cc];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int back = ks - 1 - jj;
+      const bool in = jj < ks && t >= back;
+      const float l = load_f(lat + (in ? row - back : row) * a.n_lat + cc);
+      acc[jj] = in ? fmaf(g, l, acc[jj]) : acc[jj];
+    }
   }
-  store_f(dw1 + (((long long)h * dh + o) * dh + i) * kc + j, acc);
-}
-
-// dw0[c,jj] = sum_rows d1[row,c] * lat[row - (k_seq-1-jj), c]; one thread per filter element
-template <typename T>
-__global__ __launch_bounds__(256) void pro_bwd_dw0_generic_kernel(ProBwdArgs a, const T *__restrict__ lat,
-                                                                 const float *__restrict__ d1, T *__restrict__ dw0) {
-  const int ld = a.e_q + a.e_kv;
-  const int id = blockIdx.x * 256 + threadIdx.x;  // jj * ld + c: c fastest
-  if (id >= ld * a.k_seq) return;
-  const int c = id % ld, jj = id / ld, back = a.k_seq - 1 - jj;
-  float acc = 0.f;
-  for (long long row = 0; row < a.rows; ++row) {
-    const int t = (int)(row % a.T);
-    if (t < back) continue;
-    acc = fmaf(d1[row * ld + c], load_f(lat + (row - back) * a.n_lat + c), acc);
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj) red[grp][jj][cl] = acc[jj];
+  __syncthreads();
+  if (grp < ks && c < ld) {  // group jj adds tap jj
+    float sum = 0.f;
+#pragma unroll
+    for (int x = 0; x < 32; ++x) sum += red[x][grp][cl];
+    store_f(dw0 + (long long)c * ks + grp, sum);
   }
-  store_f(dw0 + (long long)c * a.k_seq + jj, acc);
 }
 
 size_t prologue_bwd_generic_scratch_bytes(const Dims &d) {
@@ -474,15 +468,12 @@ static hipError_t prologue_bwd_generic_t(const Dims &d, const cca_weights &w, co
   pro_bwd_dlat_generic_kernel<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a, (const T *)w.w_conv_seq, d3, d1,
                                                                             (const T *)d_v, (T *)d_lat);
   if ((d.flags & CCA_CONV_CH) && gr && gr->w_conv_ch) {
-    const long long nw = (long long)NH * d.dh * d.dh * d.k_ch;
-    pro_bwd_dw1_generic_kernel<T><<<(unsigned)((nw + 255) / 256), 256, 0, s>>>(a, (const T *)lat,
-                                                                              (const T *)w.w_conv_seq, d3,
-                                                                              (T *)gr->w_conv_ch);
+    const int nt = (d.dh + 31) / 32;
+    pro_bwd_dw1_generic_kernel<T><<<dim3(nt * nt, NH, d.k_ch), GB_NT, 0, s>>>(a, (const T *)lat, (const T *)w.w_conv_seq, d3,
+                                                                             (T *)gr->w_conv_ch);
   }
-  if ((d.flags & CCA_CONV_SEQ) && gr && gr->w_conv_seq) {
-    const int nw = (d.e_q + d.e_kv) * d.k_seq;
-    pro_bwd_dw0_generic_kernel<T><<<(nw + 255) / 256, 256, 0, s>>>(a, (const T *)lat, d1, (T *)gr->w_conv_seq);
-  }
+  if ((d.flags & CCA_CONV_SEQ) && gr && gr->w_conv_seq)
+    pro_bwd_dw0_generic_kernel<T><<<(d.e_q + d.e_kv + 31) / 32, 1024, 0, s>>>(a, (const T *)lat, d1, (T *)gr->w_conv_seq);
   return hipGetLastError();
 }
 

@@ -2,11 +2,13 @@
 products of the same bf16 inputs."""
 import sys
 
+import numpy as np
 import pytest
 import torch
 
 import paper_2510_04476_amd as P
-from synth_inputs import make_inputs
+from oracle import cca_oracle as O
+from synth_inputs import make_inputs, make_upstream_grad
 from util import check_out, check_tap, oracle_forward, to_np
 
 pytestmark = pytest.mark.gpu
@@ -176,3 +178,65 @@ def test_decode_split_edges(Hq, Hk, dh):
         out = P.cca_decode_step(cfg, wt, x[:, pos].contiguous(), state, pos)
         torch.cuda.synchronize()
         check_out(to_np(out), ref[:, pos], "bf16")
+
+
+# shape-generic kernels: widths that are no multiple of 32, one token, a token more than a tile, group sizes 1 and 3, every
+# instantiation of the head width; fp32 against the oracle at its 1e-5, forward and backward
+GENERIC_CASES = [dict(B=1, T=1, E=48, Hq=2, Hk=1, dh=12, k_seq=2, k_ch=2), dict(B=2, T=33, E=120, Hq=3, Hk=1, dh=40, k_seq=4, k_ch=3),
+                 dict(B=1, T=97, E=288, Hq=3, Hk=3, dh=96, k_seq=1, k_ch=2), dict(B=1, T=70, E=264, Hq=1, Hk=1, dh=200, k_seq=2, k_ch=1),
+                 dict(B=3, T=300, E=64, Hq=6, Hk=2, dh=4, k_seq=3, k_ch=4)]
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("i", range(len(GENERIC_CASES)))
+def test_generic_kernels_fp32(i, causal):
+    w = dict(GENERIC_CASES[i], dtype="f32", paper_flags=True)
+    say("generic fp32", w, causal)
+    inp = make_inputs(w, seed=190 + i, conv_visible=True)
+    flags = P.CCA_FLAGS_PAPER if causal else P.CCA_FLAGS_PAPER & ~P.CCA_CAUSAL
+    cfg = P.config_from_workload(w, flags=flags)
+    x, wt = P.weights_to_device(cfg, inp)
+    saved = P.CCASaved.allocate(cfg, "cuda")
+    out = P.cca_forward(cfg, wt, x, saved=saved)
+    d_out = make_upstream_grad(w, seed=3)
+    d_x, g = P.cca_backward(cfg, wt, x, saved, torch.from_numpy(d_out).cuda())
+    torch.cuda.synchronize()
+    say(check_out(to_np(out), oracle_forward(w, inp, causal=causal)["out"], "f32"))
+    ref = O.cca_backward(inp["x"], inp["w_down"], inp["w_conv_seq"], inp["w_conv_ch"], inp["temp"], inp["w_out"], d_out,
+                         n_q_heads=w["Hq"], n_kv_heads=w["Hk"], head_dim=w["dh"], causal=causal)
+    for name, got in (("d_x", d_x), ("d_w_down", g.w_down), ("d_w_conv_seq", g.w_conv_seq), ("d_w_conv_ch", g.w_conv_ch),
+                      ("d_w_out", g.w_out)):
+        r = ref[name]
+        err = float(np.linalg.norm(to_np(got) - r))
+        # one token: softmax over one key is constant, the exact gradient of q and k is zero and only rounding is left
+        assert err <= 1e-5 * float(np.linalg.norm(r)) + 1e-6, (name, err, float(np.linalg.norm(r)))
+
+
+def test_generic_attention_hides_masked_infinities():
+    """fp32, causal: a NaN or infinity in a later token's key, value or query must not reach earlier rows or their gradients."""
+    T, cut = 75, 41
+    cfg = P.CCAConfig(B=1, T=T, d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=32, dtype=P.CCA_F32, flags=P.CCA_FLAGS_MHA)
+    q, k, v, d_o = (rnd(1, T, h, 32, seed=20 + h + s, dtype=torch.float32) for s, h in ((0, 2), (5, 1), (9, 1), (13, 2)))
+    run = lambda q, k, v, d_o: (lambda o, lse: (o, lse) + tuple(P.cca_attention_backward(cfg, q, k, v, o, lse, d_o.reshape(1, T, 64))))(
+        *P.cca_attention(cfg, q, k, v, want_lse=True))
+    clean = run(q, k, v, d_o)
+    bad = [t.clone() for t in (q, k, v, d_o)]
+    bad[0][0, cut, :, 3], bad[1][0, cut + 1, :, 4], bad[2][0, cut, :, 5] = float("nan"), float("inf"), float("-inf")
+    dirty = run(*bad)
+    torch.cuda.synchronize()
+    say("masked infinities")
+
+    # the sums of a tile that holds such a value run in another order: at most 2 T 2^-24 of the sum of magnitudes apart,
+    # which is below T times the largest value here
+    def same(a, b):
+        return bool(torch.isfinite(b).all()) and float((a - b).abs().max()) <= 2 * T * 2.0 ** -24 * T * float(a.abs().max())
+
+    assert same(clean[0][:, :cut], dirty[0][:, :cut]) and same(clean[1][:, :, :cut], dirty[1][:, :, :cut])
+    assert same(clean[2][:, :cut], dirty[2][:, :cut])  # d_q of earlier rows
+    assert not torch.isfinite(dirty[0][:, cut]).all()
+    # a row before a key does not count in that key's gradients
+    late = [t.clone() for t in (q, k, v, d_o)]
+    late[0][0, cut], late[3][0, cut] = float("nan"), float("inf")
+    dk, dv = run(*late)[3:]
+    torch.cuda.synchronize()
+    assert same(clean[3][:, cut + 1:], dk[:, cut + 1:]) and same(clean[4][:, cut + 1:], dv[:, cut + 1:])
