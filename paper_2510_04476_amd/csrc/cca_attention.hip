@@ -1023,40 +1023,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     attn_fwd_body<DH, CAUSAL, false, RSUM, NT, KS>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, 0.f, smem);
 }
 
-// Query blocks of `bq` rows; whether each workgroup takes two of them.
-// Causal work per query block grows with its index.  With one 8-wavefront workgroup per CU, giving every
-// workgroup one heavy and one light block (equal work for all) measured ~20% faster at B*Hq = 8 than issuing
-// the heavy blocks first; only worth it while it still leaves a workgroup for each of the 256 CUs.
-int query_blocks(const Dims &d, int bq) { return (d.T + bq - 1) / bq; }
-bool pair_blocks(const Dims &d, int nqb) {
-  return (d.flags & CCA_CAUSAL) && (long long)d.B * d.Hq * ((nqb + 1) / 2) >= 256;
-}
-
-// Two key groups per workgroup (128 query rows, half the key tiles for each group) or one (256 rows)?  A grid takes as
-// long as its busiest CU, counted in steps of one key tile per group: 256-row blocks leave most CUs idle until B * H_q * T
+// Two key groups per workgroup (128 query rows, half the key tiles for each group) or one (256 rows)?  256-row blocks leave most CUs idle until B * H_q * T
 // reaches about 32 k rows, and each walks all keys of its rows.  The split form costs 12 % more per step (a tile is staged
 // for 128 rows instead of 256) and about 1.5 steps for the merge.  Measured (T, B * H_q, d_h: one group -> two, us, causal):
 // 512, 8, 128: 19.1 -> 16.2; 2048, 8, 128: 47.6 -> 33.6; 4096, 8, 128: 85.0 -> 57.7; 8192, 8, 128: 171.6 -> 134.2;
 // 4096, 16, 128 without bound: 101.8 -> 81.8; 1531, 24, 64: 26.6 -> 19.4; kept on one group: 64, 8: 6.2 -> 7.8;
 // 16384, 8, 128: 446 -> 501; 1999, 64, 64: 44.7 -> 54.7.  256 threads and 128 rows without the split: 2048, 8: 38.1.
-bool split_keys(const Dims &d) {
-  const long long BH = (long long)d.B * d.Hq;
-  auto busiest = [&](int bq) {  // steps: a block of bq rows takes (its tiles) * bq / 256 of them
-    const long long n = query_blocks(d, bq), blocks = BH * n;
-    if (!(d.flags & CCA_CAUSAL)) return (double)((blocks + 255) / 256) * (double)((d.T + BKV - 1) / BKV) * bq / 256;
-    const double per = (double)(bq / BKV) * bq / 256;  // steps of the first block; the i-th takes i times as many
-    if (pair_blocks(d, (int)n)) return (double)((BH * ((n + 1) / 2) + 255) / 256) * per * (double)(n + 1);
-    return per * fmax((double)n, (double)BH * (double)n * (double)(n + 1) / 512.0);
-  };
-  return 1.12 * busiest(BQ / 2) + 1.5 < busiest(BQ);
-}
+bool split_keys(const Dims &d) { return 1.12 * busiest_cu(d, BQ / 2, true) + 1.5 < busiest_cu(d, BQ, true); }
 
 template <int DH, int KS>
 hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo, float *lse,
                   const float *temp, hipStream_t s) {
   constexpr bool WIDE = DH > 128;             // one wavefront per SIMD, 128-row query blocks
   constexpr int BQL = WIDE ? 128 : BQ / KS;
-  const int nqb = query_blocks(d, BQL);
+  const int nqb = row_blocks(d, BQL);
   const int BH = d.B * d.Hq;
   const bool causal = d.flags & CCA_CAUSAL;
   const int paired = pair_blocks(d, nqb) ? 1 : 0;

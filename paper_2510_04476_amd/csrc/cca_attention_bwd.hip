@@ -148,6 +148,35 @@ __device__ __forceinline__ void chain_fence(f32x16 &acc) { asm volatile("" : "+v
 __device__ __forceinline__ void chain_fence(f32x16 &acc, f32x16 &other) { asm volatile("" : "+v"(acc), "+v"(other)); }
 __device__ __forceinline__ void chain_fence(f32x16 &acc, u32x4 &a, u32x4 &b) { asm volatile("" : "+v"(acc), "+v"(a), "+v"(b)); }
 
+// Two groups of wavefronts summed the two halves of a contraction into the same DT output tiles (KS = 2): each hands half
+// of its tiles to the other through LDS and ends with the sums of tiles [kg * DT / 2, (kg + 1) * DT / 2).  Nobody reads the
+// tiles in `smem` any more when this is called.  (Values are selected, never array elements: a selected element would move
+// the accumulators to scratch memory.)
+template <int DT>
+__device__ __forceinline__ void add_groups(f32x16 *acc, int kg, int wave_g, int lane, unsigned char *smem) {
+  constexpr int HT = DT / 2;
+  float *const buf = reinterpret_cast<float *>(smem) + lane;
+  float *const mine = buf + (kg * 4 + wave_g) * (HT * 16 * 64), *const other = buf + ((1 - kg) * 4 + wave_g) * (HT * 16 * 64);
+#pragma unroll
+  for (int x = 0; x < HT; ++x)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float first = acc[x][r], second = acc[HT + x][r];
+      mine[(x * 16 + r) * 64] = kg == 0 ? second : first;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < HT; ++x)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float first = acc[x][r], second = acc[HT + x][r], part = other[(x * 16 + r) * 64];
+      // group 0's part first, whoever adds
+      acc[x][r] = kg == 0 ? first + part : first;
+      acc[HT + x][r] = kg == 0 ? second : part + second;
+    }
+  __syncthreads();  // the buffer may be written again
+}
+
 // ---------------------------------------------------------------------------
 // Delta[b,h,t] = sum_d dO[b,t,h,d] * O[b,t,h,d]; d_h / 8 lanes x 16 bytes per (t,h) row
 // ---------------------------------------------------------------------------
@@ -189,21 +218,24 @@ constexpr int DQ_NT = 512, BKV = 64;
 
 // DQ_NT_ threads = DQ_NT_ / 64 wavefronts x 32 query rows per workgroup: 512 threads (two wavefronts per SIMD) for
 // d_h <= 128; 256 threads (one wavefront per SIMD, twice the registers: the 32 x 256 accumulator moves to the
-// accumulation registers) for d_h = 256.
-template <int DH, bool CAUSAL, int DQ_NT_>
+// accumulation registers) for d_h = 256.  KS = 2: two groups of DQ_NT_ / 2 threads share the rows of one group and take the
+// even and the odd key tiles (the forward kernel's split, for the same grids); their sums are added through LDS.
+template <int DH, bool CAUSAL, int DQ_NT_, int KS = 1>
 __device__ __forceinline__ void attn_bwd_dq_body(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
     const bf16_t *__restrict__ dO, const float *__restrict__ LSE, const float *__restrict__ DELTA,
     bf16_t *__restrict__ dQ, int T, int Hq, int Hk, int BH, int nqb, int paired, float scale, unsigned char *smem) {
   CCA_BWD_GEOMETRY(DH);
-  constexpr int DQ_BQ = DQ_NT_ / 2;
-  constexpr bool WIDE = DQ_NT_ == 256;
+  constexpr int NTG = DQ_NT_ / KS, DQ_BQ = NTG / 2;  // threads of a key group; query rows
+  constexpr bool WIDE = DH > 128;
+  static_assert(!WIDE || KS == 1, "one key group at one wavefront per SIMD");
   constexpr int TILE = BKV * ROW;
-  constexpr int PER_THREAD = BKV * KCH / DQ_NT_;  // 16-byte chunks of K (and of V) per thread per tile
-  constexpr int ROWS_PER_PASS = DQ_NT_ / KCH;
-  unsigned char *const sK = smem, *const sV = smem + 2 * TILE;  // K0 K1 V0 V1
+  constexpr int PER_THREAD = BKV * KCH / NTG;  // 16-byte chunks of K (and of V) per thread per tile
+  constexpr int ROWS_PER_PASS = NTG / KCH;
+  const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTG);
+  unsigned char *const sK = smem + kg * 4 * TILE, *const sV = sK + 2 * TILE;  // K0 K1 V0 V1 of each key group
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x % NTG, lane = tid & 63, wave = tid >> 6;  // within the key group
   const int l32 = lane & 31, half = lane >> 5;
   const int idx = blockIdx.x;
   const int bh = idx % BH, slot = idx / BH;
@@ -221,10 +253,34 @@ __device__ __forceinline__ void attn_bwd_dq_body(
   const uint32_t s_off_odd = ROWS_PER_PASS % 16 == 0 ? s_off : (s_off ^ 32u);
   const LaneSwz LS = lane_swz<DH>(lane);
 
+  // KS = 2: the tiles travel global -> LDS directly, as in the dK / dV kernel (a group of 256 threads would need twice the
+  // staging registers, and with those the kernel spilled 22 to 120 registers): wave instruction i deposits 64 chunks at
+  // positions [64 i, 64 i + 64) of the tile, each lane fetching the chunk the layout puts there (padding: a duplicate).
+  typedef __attribute__((address_space(3))) void lds_void;
+  typedef __attribute__((address_space(1))) void glb_void;
+  constexpr int CPR = ROW / 16, DMA_PER_WAVE = KS == 1 ? 1 : BKV * CPR / 64 / (NTG / 64);
+  static_assert(KS == 1 || DMA_PER_WAVE * (NTG / 64) * 64 == BKV * CPR, "tile must be a whole number of wave instructions");
+  uint32_t dma_rc[DMA_PER_WAVE];  // row of the tile | chunk << 16
+  if constexpr (KS == 2) {
+#pragma unroll
+    for (int u = 0; u < DMA_PER_WAVE; ++u) {
+      const int L = (wave + u * (NTG / 64)) * 64 + lane, row = L / CPR, ch = min(L % CPR, KCH - 1) ^ swz(row);
+      dma_rc[u] = (uint32_t)row | ((uint32_t)ch << 16);
+    }
+  }
+  auto issue_tile = [&](int kv0, int buf) {
+#pragma unroll
+    for (int u = 0; u < DMA_PER_WAVE; ++u) {
+      const int s = min(kv0 + (int)(dma_rc[u] & 0xffffu), T - 1);  // clamped keys are masked below
+      const uint32_t off = (uint32_t)s * (uint32_t)row_bytes + (dma_rc[u] >> 16) * 16, dst = buf * TILE + (wave + u * (NTG / 64)) * 1024;
+      __builtin_amdgcn_global_load_lds((glb_void *)(Kg + off), (lds_void *)(sK + dst), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((glb_void *)(Vg + off), (lds_void *)(sV + dst), 16, 0, 0);
+    }
+  };
   // Staging registers of the next tile.  One wavefront per SIMD: a single set carries K and V in turn (K of tile
   // j+1 is put into LDS and V of tile j+1 requested before tile j is multiplied, V put down and K of tile j+2
   // requested after), because the query and dO fragments alone take half of the ordinary registers.
-  u32x4 rk[PER_THREAD], rv[WIDE ? 1 : PER_THREAD];
+  u32x4 rk[KS == 2 ? 1 : PER_THREAD], rv[WIDE || KS == 2 ? 1 : PER_THREAD];
   auto load_half = [&](const unsigned char *src, u32x4 *r, int kv0) {
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
@@ -240,13 +296,13 @@ __device__ __forceinline__ void attn_bwd_dq_body(
     }
   };
   auto load_tile = [&](int kv0) {  // two wavefronts per SIMD only
-    if constexpr (!WIDE) {
+    if constexpr (!WIDE && KS == 1) {
       load_half(Kg, rk, kv0);
       load_half(Vg, rv, kv0);
     }
   };
   auto store_tile = [&](int buf) {
-    if constexpr (!WIDE) {
+    if constexpr (!WIDE && KS == 1) {
       store_half(sK, rk, buf);
       store_half(sV, rv, buf);
     }
@@ -391,13 +447,16 @@ __device__ __forceinline__ void attn_bwd_dq_body(
   };
 
   const int kv_end = CAUSAL ? min(q0 + DQ_BQ, T) : T;
-  const int ntiles = (kv_end + BKV - 1) / BKV;
+  const int ntiles = ((kv_end + BKV - 1) / BKV + KS - 1) / KS;  // of a key group (the last one may lie past the end)
   if constexpr (WIDE) {
     load_half(Kg, rk, 0);
     store_half(sK, rk, 0);
     load_half(Vg, rk, 0);
     store_half(sV, rk, 0);
     if (ntiles > 1) load_half(Kg, rk, BKV);
+  } else if constexpr (KS == 2) {
+    issue_tile(kg * BKV, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
     load_tile(0);
     store_tile(0);
@@ -405,21 +464,23 @@ __device__ __forceinline__ void attn_bwd_dq_body(
   }
   __syncthreads();
   for (int j = 0; j < ntiles; ++j) {
-    const int kv0 = j * BKV, buf = j & 1;
+    const int kv0 = (j * KS + kg) * BKV, buf = j & 1;
     if constexpr (WIDE) {
       if (j + 1 < ntiles) {
         store_half(sK, rk, buf ^ 1);
         load_half(Vg, rk, kv0 + BKV);
       }
+    } else if constexpr (KS == 2) {
+      if (j + 1 < ntiles) issue_tile(kv0 + KS * BKV, buf ^ 1);  // that buffer was last read before the previous barrier
     } else {
       if (j + 1 < ntiles) store_tile(buf ^ 1);
       if (j + 2 < ntiles) load_tile(kv0 + 2 * BKV);
     }
-    if (wave_live && !(CAUSAL && kv0 > wave_last)) {
+    if (wave_live && kv0 <= (CAUSAL ? wave_last : T - 1)) {
       const unsigned char *kp = sK + buf * TILE, *vp = sV + buf * TILE;
       // wave-uniform: tiles below the diagonal and inside the sequence need no mask
       const bool need_mask = (CAUSAL && kv0 + BKV - 1 > qw0) || (kv0 + BKV > T);
-      if (WIDE || need_mask) {
+      if (WIDE || (KS == 2 && !CAUSAL) || need_mask) {
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) block(kp, vp, kv0, ks, std::true_type{});
       } else {
@@ -433,16 +494,19 @@ __device__ __forceinline__ void attn_bwd_dq_body(
         if (j + 2 < ntiles) load_half(Kg, rk, kv0 + 2 * BKV);
       }
     }
+    if constexpr (KS == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   }
   if constexpr (WIDE) {
     static_assert(!WIDE || DT == 8, "acc_settle takes 8 accumulators");
     acc_settle(acc);
   }
+  if constexpr (KS == 2) add_groups<DT>(acc, kg, wave, lane, smem);
   if (wave_live && qw0 + l32 < T) {
     bf16_t *row = dQ + (((long long)b * T + qw0 + l32) * Hq + h) * DH;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
+      if (KS == 1 || dt / (DT / 2) == kg)
 #pragma unroll
       for (int rg = 0; rg < 4; ++rg) {
         u32x2 w;
@@ -454,13 +518,18 @@ __device__ __forceinline__ void attn_bwd_dq_body(
   }  // pass
 }
 
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, int KS>
 __global__ __launch_bounds__(DQ_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
     const bf16_t *__restrict__ dO, const float *__restrict__ LSE, const float *__restrict__ DELTA,
     bf16_t *__restrict__ dQ, int T, int Hq, int Hk, int BH, int nqb, int paired, float scale) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BKV * (DH * 2 + 64)];
-  attn_bwd_dq_body<DH, CAUSAL, DQ_NT>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, smem);
+  if constexpr (KS == 1) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BKV * (DH * 2 + 64)];
+    attn_bwd_dq_body<DH, CAUSAL, DQ_NT, KS>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, smem);
+  } else {  // dynamic LDS: with a static array every LDS read would wait for the tile loads in flight
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
+    attn_bwd_dq_body<DH, CAUSAL, DQ_NT, KS>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, dyn_smem);
+  }
 }
 
 template <int DH, bool CAUSAL>
@@ -502,31 +571,36 @@ constexpr int KV_NT = 512;  // threads; a workgroup owns KV_NT / 2 keys
 // for d_h <= 128; 256 (one wavefront per SIMD, 32-row tiles so that tiles and V fragments fit the LDS) for d_h = 256,
 // where dK and dV, 128 registers each, fill the accumulation registers and the S and dP chains run as inline assembly
 // on ordinary registers (chain_mfma above).
-constexpr int kv_tile_rows(int threads) { return threads == 256 ? 32 : 64; }
+// KS = 2: two groups of KV_NT_ / 2 threads share the keys of one group and take the even and the odd query tiles (32 rows
+// each, so that both groups' tiles fit the LDS); their sums are added through LDS.
+constexpr int kv_tile_rows(int threads, int ks) { return threads == 256 || ks == 2 ? 32 : 64; }
 
-template <int DH, bool CAUSAL, bool PARTIAL, int KV_NT_>
+template <int DH, bool CAUSAL, bool PARTIAL, int KV_NT_, int KS = 1>
 __device__ __forceinline__ void attn_bwd_dkdv_body(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
     const bf16_t *__restrict__ dO, const float *__restrict__ LSE, const float *__restrict__ DELTA,
     bf16_t *__restrict__ dK, bf16_t *__restrict__ dV, float *__restrict__ dKp, float *__restrict__ dVp, int T, int Hq,
     int Hk, int BH, int nkb, float scale, unsigned char *smem) {
   CCA_BWD_GEOMETRY(DH);
-  constexpr int KV_NT = KV_NT_, KV_BK = KV_NT_ / 2, BQT = kv_tile_rows(KV_NT_);
-  constexpr bool WIDE = KV_NT_ == 256;
+  constexpr int KV_NT = KV_NT_ / KS, KV_BK = KV_NT / 2, BQT = kv_tile_rows(KV_NT_, KS);  // threads of a group; its keys
+  constexpr bool WIDE = DH > 128;
+  static_assert(!WIDE || KS == 1, "one group at one wavefront per SIMD");
   constexpr int TILE = BQT * ROW;
   // smem: Q0 Q1 dO0 dO1, 4 * TILE bytes of dynamic LDS (with a static array the compiler makes every LDS read wait
   // for the tile loads in flight (vmcnt(0): a load into LDS might alias what is read), which puts the latency of the
   // next tile's loads in front of each step)
   // [buf][-lse2 | -Delta][row]: the S and dP chains START from these (lane = key, register = query row), so that the
   // chains deliver S - lse and dP - Delta and the arithmetic needs no subtraction
-  __shared__ __attribute__((aligned(16))) float sStat[2][2][BQT];
+  __shared__ __attribute__((aligned(16))) float sStat_[KS][2][2][BQT];
   // this workgroup's V rows as MFMA operand fragments, [wavefront][kk][lane] x 16 bytes: each wavefront keeps its own
   // (read back one fragment per dP product; holding them in registers next to the K fragments and the two
   // accumulators leaves no room for fragments requested ahead of their use)
   __shared__ __attribute__((aligned(16))) u32x4 sVf[KV_NT / 64][KK][64];
-  unsigned char *const sQ = smem, *const sD = smem + 2 * TILE;
+  const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / KV_NT);
+  unsigned char *const sQ = smem + kg * 4 * TILE, *const sD = sQ + 2 * TILE;
+  float (*const sStat)[2][BQT] = sStat_[kg];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x % KV_NT, lane = tid & 63, wave = tid >> 6;  // within the group
   const int l32 = lane & 31, half = lane >> 5;
   const int idx = blockIdx.x;
   const int bh = idx % BH, kb = idx / BH;  // early key blocks (most query tiles when causal) first
@@ -546,7 +620,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(pk + kk * 16));
-      sVf[wave][kk][lane] = *reinterpret_cast<const u32x4 *>(pv + kk * 16);
+      if (kg == 0) sVf[wave][kk][lane] = *reinterpret_cast<const u32x4 *>(pv + kk * 16);  // the groups share them
     }
   }
   f32x16 dk[DT], dv[DT];  // dK^T, dV^T: lane = key, registers = channels
@@ -564,7 +638,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
   // query tiles that see keys of this block
   const int qt_first = CAUSAL ? k0 / BQT : 0;
   const int nqt = (T + BQT - 1) / BQT;
-  const int steps = nqt - qt_first;
+  const int steps = (nqt - qt_first + KS - 1) / KS;  // of a group (the last one may lie past the end)
 
   // Q (pre-scaled) and dO tiles travel global -> LDS directly: wave instruction i deposits 64 x 16 bytes at LDS
   // chunks [i*64, i*64+64) of the tile, so each lane fetches the chunk that the layout puts at its position (lanes
@@ -590,7 +664,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
     dma_rc[u] = (uint32_t)row | ((uint32_t)ch << 12);  // ch * 16 = dma_rc >> 8 with the row bits masked off
   }
   auto issue_tile = [&](int step, int buf) {
-    const int t0 = (qt_first + step) * BQT;
+    const int t0 = (qt_first + step * KS + kg) * BQT;
     // the row statistics first, untouched until they land: arithmetic on them here would wait for them and, loads
     // completing in order, for every tile load issued before
     if (tid < 2 * BQT) {
@@ -772,9 +846,9 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
   }
   for (int step = 0; step < steps; ++step) {
     const int buf = step & 1;
-    const int t0 = (qt_first + step) * BQT;
+    const int t0 = (qt_first + step * KS + kg) * BQT;
     if (step + 1 < steps) issue_tile(step + 1, buf ^ 1);  // that buffer was last read before the previous barrier
-    if (wave_live && !(CAUSAL && t0 + BQT - 1 < kw0)) {
+    if (wave_live && (KS == 1 || t0 < T) && !(CAUSAL && t0 + BQT - 1 < kw0)) {
       const unsigned char *qp = sQ + buf * TILE, *dp_ = sD + buf * TILE;
       // wave-uniform: tiles away from the diagonal and from the end of the sequence need no mask at all
       const bool need_mask = (CAUSAL && t0 < kw0 + 31) || (t0 + BQT > T) || (kw0 + 32 > T);
@@ -793,12 +867,17 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
     static_assert(!WIDE || DT == 8, "acc_settle takes 8 + 8 accumulators");
     acc_settle(dk, dv);
   }
+  if constexpr (KS == 2) {
+    add_groups<DT>(dk, kg, wave, lane, smem);
+    add_groups<DT>(dv, kg, wave, lane, smem);
+  }
   if (PARTIAL) {
     if (wave_live && kw0 + l32 < T) {
       float *rk_ = dKp + (((long long)b * T + kw0 + l32) * Hq + h) * DH;
       float *rv_ = dVp + (((long long)b * T + kw0 + l32) * Hq + h) * DH;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
+        if (KS == 1 || dt / (DT / 2) == kg)
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
           const f32x4 w = {dk[dt][rg * 4 + 0] * LN2, dk[dt][rg * 4 + 1] * LN2, dk[dt][rg * 4 + 2] * LN2,
@@ -815,6 +894,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
     bf16_t *rv_ = dV + (((long long)b * T + kw0 + l32) * Hk + g) * DH;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
+      if (KS == 1 || dt / (DT / 2) == kg)
 #pragma unroll
       for (int rg = 0; rg < 4; ++rg) {
         u32x2 w, x;
@@ -828,14 +908,14 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
   }
 }
 
-template <int DH, bool CAUSAL, bool PARTIAL>
+template <int DH, bool CAUSAL, bool PARTIAL, int KS>
 __global__ __launch_bounds__(KV_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkdv_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
     const bf16_t *__restrict__ dO, const float *__restrict__ LSE, const float *__restrict__ DELTA,
     bf16_t *__restrict__ dK, bf16_t *__restrict__ dV, float *__restrict__ dKp, float *__restrict__ dVp, int T, int Hq,
     int Hk, int BH, int nkb, float scale) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  attn_bwd_dkdv_body<DH, CAUSAL, PARTIAL, KV_NT>(Q, K, V, dO, LSE, DELTA, dK, dV, dKp, dVp, T, Hq, Hk, BH, nkb, scale, smem);
+  attn_bwd_dkdv_body<DH, CAUSAL, PARTIAL, KV_NT, KS>(Q, K, V, dO, LSE, DELTA, dK, dV, dKp, dVp, T, Hq, Hk, BH, nkb, scale, smem);
 }
 
 template <int DH, bool CAUSAL, bool PARTIAL>
@@ -899,10 +979,16 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
   if (e != hipSuccess) return e;
   constexpr bool WIDE = DH > 128;                 // one wavefront per SIMD, half as many rows per workgroup
   constexpr int NTH = WIDE ? 256 : DQ_NT;         // threads of both kernels (DQ_NT == KV_NT)
-  constexpr int ROWS = NTH / 2;                   // query rows (dQ) or keys (dK / dV) per workgroup
   static_assert(DQ_NT == KV_NT, "one thread count for both kernels");
-  const int BH = d.B * d.Hq, nqb = (d.T + ROWS - 1) / ROWS;
-  const int nkb = (d.T + ROWS - 1) / ROWS;
+  // Two groups of wavefronts per workgroup where 256-row blocks leave CUs idle, by the busiest CU's steps; the split form
+  // measured 5 to 8 % slower per step (T = 16384, B * H_q = 8, d_h = 128: dQ + 49, dK / dV + 41 us of 1660) and loses about a
+  // step to the merge.  Attention backward, us, neither -> dQ -> dK / dV -> both split, causal, d_h = 128: T = 512, B * H_q
+  // = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115; 8192, 8: 658 -> 590 -> 546 -> 478; 4096, 16 MHA: 343 ->
+  // 312 -> 290 -> 258; d_h = 64, 1531, 24: 95 -> 83 -> 78 -> 65; kept whole: 1999, 64: 174 -> 181 -> 185 -> 194.
+  const bool dq_halves = !WIDE && 1.08 * busiest_cu(d, NTH / 4, true) + 1.0 < busiest_cu(d, NTH / 2, true);
+  const bool kv_halves = !WIDE && 1.08 * busiest_cu(d, NTH / 4, false) + 1.0 < busiest_cu(d, NTH / 2, false);
+  const int dq_rows = dq_halves ? NTH / 4 : NTH / 2, kv_rows = kv_halves ? NTH / 4 : NTH / 2;  // rows, keys per workgroup
+  const int BH = d.B * d.Hq, nqb = row_blocks(d, dq_rows), nkb = row_blocks(d, kv_rows);
   float *pk = reinterpret_cast<float *>(reinterpret_cast<char *>(delta) + delta_bytes(d));
   float *pv = pk + (size_t)d.rows() * d.e_q;
   bf16_t *qs = reinterpret_cast<bf16_t *>(reinterpret_cast<char *>(delta) + delta_bytes(d) +
@@ -916,25 +1002,36 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
 #define ARGS_KV (const bf16_t *)qs, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)d_o, lse, delta, (bf16_t *)d_k, \
                 (bf16_t *)d_v, pk, pv, d.T, d.Hq, d.Hk, BH, nkb, d.scale
   const unsigned gkv = (unsigned)((long long)BH * nkb);
-  constexpr size_t kv_smem = 4ull * kv_tile_rows(NTH) * (DH * 2 + 64);  // the Q / dO tiles of the dK / dV kernel
+  // the Q / dO tiles of the dK / dV kernel (both groups' with KS = 2: the same bytes)
+  constexpr size_t dq_smem = 8ull * BKV * (DH * 2 + 64);  // dQ with two key groups
+  constexpr size_t kv_smem = 4ull * kv_tile_rows(NTH, 1) * (DH * 2 + 64);
   // pairing query blocks only pays while it still leaves a workgroup for each of the 256 CUs; the dK / dV kernel
   // gains nothing from it (measured)
-  const int paired = causal && (long long)BH * ((nqb + 1) / 2) >= 256 ? 1 : 0;
+  const int paired = pair_blocks(d, nqb) ? 1 : 0;
   const bool partial = d.R > 1;
   // (the dynamic-LDS limit is raised once per kernel and device: raise_lds_limit)
+#define LAUNCH_KV_KS(C_, P_, KS_)                                                                             \
+  {                                                                                                           \
+    e = raise_lds_limit<attn_bwd_dkdv_kernel<DH, C_, P_, KS_>>(kv_smem);                                      \
+    if (e != hipSuccess) return e;                                                                            \
+    attn_bwd_dkdv_kernel<DH, C_, P_, KS_><<<gkv, NTH, kv_smem, s>>>(ARGS_KV);                                  \
+  }
 #define LAUNCH_KV(C_, P_)                                                                                     \
   if constexpr (WIDE) {                                                                                       \
     e = raise_lds_limit<attn_bwd_dkdv_wide_kernel<DH, C_, P_>>(kv_smem);                                      \
     if (e != hipSuccess) return e;                                                                            \
     attn_bwd_dkdv_wide_kernel<DH, C_, P_><<<gkv, NTH, kv_smem, s>>>(ARGS_KV);                                  \
   } else {                                                                                                    \
-    e = raise_lds_limit<attn_bwd_dkdv_kernel<DH, C_, P_>>(kv_smem);                                           \
-    if (e != hipSuccess) return e;                                                                            \
-    attn_bwd_dkdv_kernel<DH, C_, P_><<<gkv, NTH, kv_smem, s>>>(ARGS_KV);                                       \
+    if (kv_halves) LAUNCH_KV_KS(C_, P_, 2) else LAUNCH_KV_KS(C_, P_, 1)                                       \
   }
 #define LAUNCH_DQ(C_, G_)                                                                                     \
   if constexpr (WIDE) attn_bwd_dq_wide_kernel<DH, C_><<<(unsigned)(G_), NTH, 0, s>>>(ARGS_DQ);                 \
-  else attn_bwd_dq_kernel<DH, C_><<<(unsigned)(G_), NTH, 0, s>>>(ARGS_DQ);
+  else if (dq_halves) {                                                                                        \
+    e = raise_lds_limit<attn_bwd_dq_kernel<DH, C_, 2>>(dq_smem);                                               \
+    if (e != hipSuccess) return e;                                                                            \
+    attn_bwd_dq_kernel<DH, C_, 2><<<(unsigned)(G_), NTH, dq_smem, s>>>(ARGS_DQ);                               \
+  }                                                                                                           \
+  else attn_bwd_dq_kernel<DH, C_, 1><<<(unsigned)(G_), NTH, 0, s>>>(ARGS_DQ);
   if (causal) {
     LAUNCH_DQ(true, (long long)BH * (paired ? (nqb + 1) / 2 : nqb));
     if (partial) {
@@ -951,6 +1048,7 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
     }
   }
 #undef LAUNCH_KV
+#undef LAUNCH_KV_KS
 #undef LAUNCH_DQ
 #undef ARGS_DQ
 #undef ARGS_KV
