@@ -6,12 +6,11 @@
 // dK and dV summed over the query heads that share a KV head (CCGQA paragraph).
 //
 // Three kernels, no atomics, deterministic:
-//   delta_kernel      Delta (B,H_q,T) fp32.
+//   delta_scale_q     Delta (B,H_q,T) fp32, and q * scale * log2(e) rounded to bf16 (what the forward kernel multiplies).
 //   attn_bwd_dq       one workgroup = 256 query rows of one head (8 wavefronts x 32 rows), loops over key
 //                     tiles like the forward kernel; S^T and dP^T come out with one query row per lane, dS^T
 //                     packed to bf16 is the second MFMA operand of dQ^T += K^T dS^T, K^T fetched with the
 //                     transposing LDS read.
-//   scale_q           q * scale * log2(e) rounded to bf16 (what the forward kernel multiplies), once, for the next kernel.
 //   attn_bwd_dkdv     one workgroup = 256 keys x one QUERY head (8 wavefronts x 32 keys), loops over the query
 //                     tiles of that head; S and dP come out with one key per lane, P and dS packed to bf16 are
 //                     the second operands of dV^T += dO^T P and dK^T += Q^T dS, with dO^T and Q^T fetched by
@@ -178,11 +177,15 @@ __device__ __forceinline__ void add_groups(f32x16 *acc, int kg, int wave_g, int 
 }
 
 // ---------------------------------------------------------------------------
-// Delta[b,h,t] = sum_d dO[b,t,h,d] * O[b,t,h,d]; d_h / 8 lanes x 16 bytes per (t,h) row
+// Delta[b,h,t] = sum_d dO[b,t,h,d] * O[b,t,h,d]; d_h / 8 lanes x 16 bytes per (t,h) row.
+// The same lanes write q in log2 units, rounded to bf16 exactly as the forward kernel rounds it (see the note at the top),
+// so that the dK / dV kernel can move its Q tiles global -> LDS directly.  One launch: bound by memory at length (T = 16384:
+// 18.3 + 12.2 us in two, 28.8 in one), by the launch at short lengths (4.8 us each).
 // ---------------------------------------------------------------------------
 template <int DH>
-__global__ __launch_bounds__(256) void delta_kernel(const bf16_t *__restrict__ dO, const bf16_t *__restrict__ O,
+__global__ __launch_bounds__(256) void delta_scale_q_kernel(const bf16_t *__restrict__ dO, const bf16_t *__restrict__ O,
                                                    const bf16_t *__restrict__ OLO, float *__restrict__ delta,
+                                                   const bf16_t *__restrict__ Q, bf16_t *__restrict__ Qs, float c,
                                                    long long n_rows, int T, int Hq) {
   constexpr int LPR = DH / 8;  // lanes per row
   const long long row = (long long)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;  // row = (b*T + t)*Hq + h
@@ -191,13 +194,17 @@ __global__ __launch_bounds__(256) void delta_kernel(const bf16_t *__restrict__ d
   if (row < n_rows) {
     const u32x4 a = *reinterpret_cast<const u32x4 *>(dO + row * DH + sub * 8);
     const u32x4 b = *reinterpret_cast<const u32x4 *>(O + row * DH + sub * 8);
+    u32x4 w = *reinterpret_cast<const u32x4 *>(Q + row * DH + sub * 8);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = pack2(bf_lo(w[i]) * c, bf_hi(w[i]) * c);
+    *reinterpret_cast<u32x4 *>(Qs + row * DH + sub * 8) = w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc += bf_lo(a[i]) * bf_lo(b[i]) + bf_hi(a[i]) * bf_hi(b[i]);
     if (OLO) {  // O to ~16 mantissa bits: with O rounded to bf16 alone, the error of Delta dominates dQ and dK
                 // whenever the softmax is flat (measured 2 % at T = 700 with 0.02-scaled weights)
-      const u32x4 c = *reinterpret_cast<const u32x4 *>(OLO + row * DH + sub * 8);
+      const u32x4 l = *reinterpret_cast<const u32x4 *>(OLO + row * DH + sub * 8);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc += bf_lo(a[i]) * bf_lo(c[i]) + bf_hi(a[i]) * bf_hi(c[i]);
+      for (int i = 0; i < 4; ++i) acc += bf_lo(a[i]) * bf_lo(l[i]) + bf_hi(a[i]) * bf_hi(l[i]);
     }
   }
 #pragma unroll
@@ -541,20 +548,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   attn_bwd_dq_body<DH, CAUSAL, 256>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, smem);
 }
 
-// q in log2 units, rounded to bf16 exactly as the forward kernel rounds it (see the note at the top): written once
-// so that the dK / dV kernel can move its Q tiles global -> LDS directly
-__global__ __launch_bounds__(256) void scale_q_kernel(const bf16_t *__restrict__ Q, bf16_t *__restrict__ Qs, long long n8,
-                                                     float c) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n8) return;
-  u32x4 w = *reinterpret_cast<const u32x4 *>(Q + i * 8);
-  w.x = pack2(bf_lo(w.x) * c, bf_hi(w.x) * c);
-  w.y = pack2(bf_lo(w.y) * c, bf_hi(w.y) * c);
-  w.z = pack2(bf_lo(w.z) * c, bf_hi(w.z) * c);
-  w.w = pack2(bf_lo(w.w) * c, bf_hi(w.w) * c);
-  *reinterpret_cast<u32x4 *>(Qs + i * 8) = w;
-}
-
 // ---------------------------------------------------------------------------
 // dK, dV
 // ---------------------------------------------------------------------------
@@ -564,7 +557,7 @@ constexpr int KV_NT = 512;  // threads; a workgroup owns KV_NT / 2 keys
 // PARTIAL = true: this head's contribution written as fp32 to dKp, dVp (B,T,H_q,d_h).
 // dK and dV in one pass (S, dP, dV, dK).  The two accumulators and the resident K / V fragments take 192 of the 256
 // registers two wavefronts per SIMD leave each lane: the Q and dO tiles therefore go global -> LDS directly (no
-// staging registers; q arrives pre-scaled from scale_q_kernel), S is turned into bf16 P before dP is formed, and
+// staging registers; q arrives pre-scaled from delta_scale_q_kernel), S is turned into bf16 P before dP is formed, and
 // dS is computed from that bf16 P.  (With register staging and fp32 P the pass spilled 98 registers; split into a
 // dV pass and a dK pass it cost a fifth contraction.)
 // KV_NT_ threads = KV_NT_ / 64 wavefronts x 32 keys per workgroup: 512 (two wavefronts per SIMD, 64-row Q / dO tiles)
@@ -971,12 +964,7 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
                                     float *delta, hipStream_t s) {
   const bool causal = d.flags & CCA_CAUSAL;
   const long long n_rows = d.rows() * d.Hq;
-  constexpr int DELTA_ROWS = 256 / (DH / 8);  // rows per workgroup of delta_kernel
-  delta_kernel<DH><<<(unsigned)((n_rows + DELTA_ROWS - 1) / DELTA_ROWS), 256, 0, s>>>((const bf16_t *)d_o, (const bf16_t *)o, (const bf16_t *)o_lo, delta,
-                                                             n_rows, d.T,
-                                                             d.Hq);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  constexpr int DELTA_ROWS = 256 / (DH / 8);  // rows per workgroup of delta_scale_q_kernel
   constexpr bool WIDE = DH > 128;                 // one wavefront per SIMD, half as many rows per workgroup
   constexpr int NTH = WIDE ? 256 : DQ_NT;         // threads of both kernels (DQ_NT == KV_NT)
   static_assert(DQ_NT == KV_NT, "one thread count for both kernels");
@@ -993,10 +981,11 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
   float *pv = pk + (size_t)d.rows() * d.e_q;
   bf16_t *qs = reinterpret_cast<bf16_t *>(reinterpret_cast<char *>(delta) + delta_bytes(d) +
                                           (d.R > 1 ? 2 * (size_t)d.rows() * d.e_q * sizeof(float) : 0));
-  {
-    const long long n8 = d.rows() * d.e_q / 8;
-    scale_q_kernel<<<(unsigned)((n8 + 255) / 256), 256, 0, s>>>((const bf16_t *)q, qs, n8, d.scale * LOG2E);
-  }
+  delta_scale_q_kernel<DH><<<(unsigned)((n_rows + DELTA_ROWS - 1) / DELTA_ROWS), 256, 0, s>>>(
+      (const bf16_t *)d_o, (const bf16_t *)o, (const bf16_t *)o_lo, delta, (const bf16_t *)q, qs, d.scale * LOG2E, n_rows, d.T,
+      d.Hq);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
 #define ARGS_DQ (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)d_o, lse, delta, (bf16_t *)d_q, \
                 d.T, d.Hq, d.Hk, BH, nqb, paired, d.scale
 #define ARGS_KV (const bf16_t *)qs, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)d_o, lse, delta, (bf16_t *)d_k, \
