@@ -67,10 +67,20 @@ __device__ __forceinline__ float lo_f(uint32_t w) { return __uint_as_float(w << 
 __device__ __forceinline__ float hi_f(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
 // ---------------------------------------------------------------------------
-// set-up: folded filters Wc [h][o][d][i] (bf16) and the two RoPE tables
+// set-up: folded filters Wc [h][o][d][i] (bf16; d_h = 256: in the slab order of prologue_stream_kernel) and the two RoPE
+// tables
 //   ropeA [t_hi][i]            float2 (cos, sin) of t_hi * 128 * theta_i
 //   ropeB [i / 4][t_lo][i % 4] float2 (cos, sin) of t_lo * theta_i
 // ---------------------------------------------------------------------------
+// d_h = 256: the filter as prologue_stream_kernel moves it, in slabs of all 256 rows x 32 contracted channels of one tap,
+// each slab exactly as it lies in LDS (two rows share a 128-byte line; 16-byte chunk c of row r at line r / 2, position
+// (4 (r mod 2) + c) ^ ((r / 4) mod 4): 16 consecutive rows of one chunk column fall in 16 different bank groups).
+constexpr int SLAB_K = 32, SLAB_BYTES = 256 * SLAB_K * 2;
+__device__ __forceinline__ long long slab_elem(int h, int D, int r, int d, int k) {
+  const int c = (k & 31) >> 3;
+  return ((long long)(h * D + d) * (256 / SLAB_K) + (k >> 5)) * (SLAB_BYTES / 2) + ((r >> 1) * 8 + ((((r & 1) << 2) | c) ^ ((r >> 2) & 3))) * 8 + (k & 7);
+}
+
 __global__ __launch_bounds__(256) void prologue_setup_kernel(FusedArgs a, int D, const bf16_t *__restrict__ w0,
                                                             const bf16_t *__restrict__ w1, bf16_t *__restrict__ wc,
                                                             float2 *__restrict__ ropeA, float2 *__restrict__ ropeB,
@@ -91,8 +101,8 @@ __global__ __launch_bounds__(256) void prologue_setup_kernel(FusedArgs a, int D,
         acc = fmaf(bf16_to_f32(w1[(((long long)h * DH + o) * DH + i) * kc + j]), f0, acc);
       }
       // the adjoint convolution contracts over the output channel: filter stored [h][i][d][o]
-      if (transposed) wc[(((long long)h * DH + i) * D + d) * DH + o] = f32_to_bf16(acc);
-      else wc[(((long long)h * DH + o) * D + d) * DH + i] = f32_to_bf16(acc);
+      const int r = transposed ? i : o, k = transposed ? o : i;
+      wc[DH == 256 ? slab_elem(h, D, r, d, k) : (((long long)h * DH + r) * D + d) * DH + k] = f32_to_bf16(acc);
     }
     return;
   }
@@ -448,27 +458,33 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
 // ---------------------------------------------------------------------------
 // The same prologue for d_h = 256, where one head's folded filter (D x 256 x 256 bf16 = 128 KB per tap) cannot
-// stay in LDS: the filter is STREAMED through a double-buffered LDS slab of 256 outputs x 64 input channels
-// (one slab per tap and quarter of the head width), all 8 wavefronts of a workgroup walking the slabs in step.
-// Workgroup = one head x 256 tokens, wavefront = 32 tokens x all 256 outputs (8 accumulator tiles).  The token
-// operands of a slab (4 fragments) come straight from the latent rows as in the kernel above; the qk-mean, norm,
-// temperature, RoPE and the value role are the same code.  BWD = true is the adjoint, as for the kernel above:
+// stay in LDS: the filter is STREAMED through a ring of four LDS slabs (16 KB each, three in flight while one is
+// multiplied, requested straight into LDS with one bare barrier per slab), all 4 wavefronts of a workgroup walking
+// the slabs in step.  Workgroup = one head x 128 tokens, wavefront = 32 tokens x all 256 outputs (8 accumulator
+// tiles), one wavefront per SIMD.  The token rows of a wavefront (its 32 and the D - 1 its taps reach) are fetched
+// once, whole, into its own staging rows in LDS and read from there tap by tap, and results leave through the same
+// rows: as fragments straight from memory a load instruction touches 32 rows with 32 bytes each, and the memory
+// pipeline takes about 4.6 cycles per cache line - with 256-token workgroups and two slabs that was what the kernel
+// waited for (6000 tokens, 4 / 1 heads: 50.7 us, now 32.4).  BWD = true is the adjoint, as for the kernel above:
 // transposed filter, taps reaching forward in time, the value shift running backwards; the host passes only the
 // qk-mean and value-shift flags, so the norm and RoPE steps are skipped.
 // ---------------------------------------------------------------------------
-template <int DH, int D, bool BWD>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void prologue_stream_kernel(
-    FusedArgs a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
+constexpr int ST_NT = 256, ST_WAVES = ST_NT / 64, ST_RING = 4;
+constexpr int stream_rows(int D) { return (32 + D - 1 + 1) / 2 * 2; }  // staged rows of a wavefront, whole load instructions
+constexpr size_t stream_lds(int D) { return (size_t)ST_RING * SLAB_BYTES + (size_t)ST_WAVES * stream_rows(D) * 512; }
+
+// (a body inlined with restrict arguments and dynamic LDS: otherwise the compiler makes LDS reads wait for the loads into
+// LDS in flight)
+template <int D, bool BWD>
+__device__ __forceinline__ void prologue_stream_body(
+    const FusedArgs &a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
     const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB, const float *__restrict__ temp,
-    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm) {
-  constexpr int NTL = DH / 32, CPR = DH / 8;
-  constexpr int WROW = D * CPR;              // 16-byte chunks per filter row (one output channel) in memory
-  constexpr int KC = 64, KCK = KC / 16;      // input channels per slab, MFMA k-steps per slab
-  constexpr int NCH = DH / KC, NSLAB = D * NCH;
-  constexpr int SROW = KC * 2 + 16;          // padded slab row in LDS: conflict-free 16-byte reads down a column of rows
-  constexpr int SLAB = DH * SROW;
-  constexpr int W_PER_THREAD = DH * (KC / 8) / NT;  // 16-byte chunks of a slab per thread
-  __shared__ __attribute__((aligned(16))) unsigned char sW[2 * SLAB];
+    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm, unsigned char *smem) {
+  constexpr int DH = 256, NTL = DH / 32, CPR = DH / 8, ROWB = DH * 2;
+  constexpr int QS = DH / SLAB_K, NSLAB = D * QS;              // slabs per tap, slabs
+  constexpr int SLAB_INSTR = SLAB_BYTES / 1024 / ST_WAVES;     // load instructions of a wavefront per slab
+  typedef __attribute__((address_space(3))) void lds_void;
+  typedef __attribute__((address_space(1))) void glb_void;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
@@ -477,9 +493,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // ---- value-shift role (as in prologue_fused_kernel)
     const int cpr = a.e_kv / 8;
     const long long total = a.rows * cpr;
-    const long long first = ((long long)blockIdx.x - a.n_conv_blocks) * (NT * 4);
+    const long long first = ((long long)blockIdx.x - a.n_conv_blocks) * (ST_NT * 4);
     for (int it = 0; it < 4; ++it) {
-      const long long id = first + it * NT + tid;
+      const long long id = first + it * ST_NT + tid;
       if (id >= total) break;
       const long long row = id / cpr;
       const int ch = (int)(id % cpr) * 8;
@@ -497,15 +513,47 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const bool is_q = (int)blockIdx.x >= a.n_k_blocks;
   const int bid = is_q ? (int)blockIdx.x - a.n_k_blocks : (int)blockIdx.x;
   const int head = is_q ? bid % a.Hq : a.Hq + bid % a.Hk;
-  const long long row_begin = (long long)(bid / (is_q ? a.Hq : a.Hk)) * 256;
   const int g = is_q ? head / a.R : head - a.Hq;
   const int ch0 = is_q ? head * DH : a.e_q + g * DH;
   const float beta = (!is_q && (a.flags & CCA_KEY_TEMP)) ? expf(temp[g]) : 1.f;
   bf16_t *dst = is_q ? q + head * DH : k + g * DH;
   const int dst_stride = is_q ? a.q_stride : a.k_stride;
 
-  // qk-mean weights as identity fragments (see prologue_fused_kernel); the other stream's are made after the
-  // convolution, when fewer registers are live
+  // this wavefront's 32 tokens (a wavefront past the end keeps walking the slabs: it loads filter chunks too)
+  const long long trow0 = (long long)(bid / (is_q ? a.Hq : a.Hk)) * (ST_WAVES * 32) + wave * 32;
+  const long long row = trow0 + l32;
+  const long long rowc = row < a.rows ? row : a.rows - 1;
+  const int tpos = (int)(rowc % a.T);
+  const bool any_pad = __any(BWD ? tpos + D - 1 >= a.T : tpos < D - 1) != 0;
+
+  unsigned char *const ring = smem, *const stg = smem + ST_RING * SLAB_BYTES + wave * (stream_rows(D) * ROWB);
+  // 2 rows per load instruction; chunk c of staged row j lies at c ^ (j mod 16); rows outside the tensor repeat an end row
+  // (they lie outside the token's sequence: zeroed or dropped below)
+  auto fetch_rows = [&](unsigned char *to, int col, int first, int n_instr) {
+    for (int i = 0; i < n_instr; ++i) {
+      const int j = 2 * i + (lane >> 5), p = lane & 31;
+      long long r = trow0 + first + j;
+      r = r < 0 ? 0 : (r > a.rows - 1 ? a.rows - 1 : r);
+      __builtin_amdgcn_global_load_lds((glb_void *)(lat + r * a.src_stride + col + (p ^ (j & 15)) * 8), (lds_void *)(to + i * 1024), 16, 0, 0);
+    }
+  };
+  auto row_frag = [&](const unsigned char *from, int j, int kk) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(from + j * ROWB + (((2 * kk + half) ^ (j & 15)) * 16)));
+  };
+  const u32x4 *const wsrc = wc + (long long)head * NSLAB * (SLAB_BYTES / 16) + lane;
+  auto fetch_slab = [&](int s_) {
+#pragma unroll
+    for (int u = 0; u < SLAB_INSTR; ++u) {
+      const int i = wave * SLAB_INSTR + u;
+      __builtin_amdgcn_global_load_lds((glb_void *)(wsrc + (long long)s_ * (SLAB_BYTES / 16) + i * 64),
+                                       (lds_void *)(ring + (s_ % ST_RING) * SLAB_BYTES + i * 1024), 16, 0, 0);
+    }
+  };
+  fetch_rows(stg, ch0, BWD ? 0 : -(D - 1), stream_rows(D) / 2);
+#pragma unroll
+  for (int s_ = 0; s_ < ST_RING - 1; ++s_) fetch_slab(s_);
+
+  // qk-mean weights as identity fragments (see prologue_fused_kernel)
   const bool mean = a.flags & CCA_QK_MEAN;
   auto identity_frag = [&](bf16_t wbits, int j) {
     const bool on = ((l32 >> 4) == j) && (((l32 >> 3) & 1) == half);
@@ -514,34 +562,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     if (on) w[e >> 1] = (uint32_t)wbits << ((e & 1) * 16);
     return __builtin_bit_cast(bf16x8, w);
   };
-  bf16x8 id_half[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) id_half[j] = identity_frag(f32_to_bf16(0.5f), j);
-
-  // this wavefront's 32 tokens (a wavefront past the end keeps walking the slabs: it stages filter chunks too)
-  const long long trow0 = row_begin + wave * 32;
-  const long long row = trow0 + l32;
-  const long long rowc = row < a.rows ? row : a.rows - 1;
-  const int tpos = (int)(rowc % a.T);
-
-  // slab s = (tap d = s / NCH, channel quarter c = s % NCH): rows o = 0..DH-1, bytes [c*128, c*128+128) of tap d
-  const u32x4 *wsrc = wc + (long long)head * DH * WROW;
-  u32x4 wreg[W_PER_THREAD];
-  auto load_slab = [&](int s_) {
-    const int d = s_ / NCH, c = s_ % NCH;
-#pragma unroll
-    for (int i = 0; i < W_PER_THREAD; ++i) {
-      const int id = tid + i * NT, o = id / (KC / 8), cc = id % (KC / 8);
-      wreg[i] = wsrc[o * WROW + d * CPR + c * (KC / 8) + cc];
-    }
-  };
-  auto store_slab = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < W_PER_THREAD; ++i) {
-      const int id = tid + i * NT, o = id / (KC / 8), cc = id % (KC / 8);
-      *reinterpret_cast<u32x4 *>(sW + buf * SLAB + o * SROW + cc * 16) = wreg[i];
-    }
-  };
+  const bf16x8 id_half[2] = {identity_frag(f32_to_bf16(0.5f), 0), identity_frag(f32_to_bf16(0.5f), 1)};
 
   f32x16 acc[NTL];
 #pragma unroll
@@ -549,81 +570,83 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
 
-  load_slab(0);
-  store_slab(0);
-#pragma unroll  // tap and channel quarter must be compile-time: they pick accumulator tiles
-  for (int s_ = 0; s_ < NSLAB; ++s_) {
-    const int d = s_ / NCH, c = s_ % NCH;
-    if (s_ + 1 < NSLAB) load_slab(s_ + 1);
-    // token operands of this slab: row t - (D-1-d) (adjoint: t + (D-1-d)), channels c*64 .. c*64+63; rows outside
-    // the token's sequence are zero
-    const int back = D - 1 - d;
-    bf16x8 uf[KCK];
-    {
-      long long src_row = BWD ? rowc + back : rowc - back;
-      src_row = src_row < 0 ? 0 : (src_row > a.rows - 1 ? a.rows - 1 : src_row);
-      const bf16_t *p = lat + src_row * a.src_stride + ch0 + c * KC + half * 8;
+  // this lane's two 16-byte reads of row l32 of a slab (k-steps 0 and 1); output tile nt lies 2 KB further per tile
+  uint32_t woff[2];
 #pragma unroll
-      for (int kk = 0; kk < KCK; ++kk) {
-        u32x4 raw = *reinterpret_cast<const u32x4 *>(p + kk * 16);
-        if (BWD ? tpos + back >= a.T : tpos < back) raw = u32x4{0, 0, 0, 0};
-        uf[kk] = __builtin_bit_cast(bf16x8, raw);
+  for (int kk = 0; kk < 2; ++kk) woff[kk] = ((l32 >> 1) * 8 + ((((l32 & 1) << 2) | (2 * kk + half)) ^ ((l32 >> 2) & 3))) * 16;
+#pragma unroll 1
+  for (int d = 0; d < D; ++d) {
+    const int back = D - 1 - d, j = BWD ? l32 + back : l32 + D - 1 - back;
+    const bool outside = any_pad && (BWD ? tpos + back >= a.T : tpos < back);
+#pragma unroll
+    for (int c = 0; c < QS; ++c) {  // compile-time: the channel group picks accumulator tiles of the qk-mean
+      const int s_ = d * QS + c;
+      // slab s_ has landed when only the two after it are in flight; the first wait covers the token rows as well
+      if (s_ + 2 < NSLAB) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * SLAB_INSTR) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (s_ + ST_RING - 1 < NSLAB) fetch_slab(s_ + ST_RING - 1);  // its place was read in the step before: free since the barrier
+      const unsigned char *const sw = ring + (s_ % ST_RING) * SLAB_BYTES;
+      bf16x8 uf[2], wf[2][NTL];
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        uf[kk] = row_frag(stg, j, 2 * c + kk);
+#pragma unroll
+        for (int nt = 0; nt < NTL; ++nt) wf[kk][nt] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(sw + woff[kk] + nt * 2048));
+        __builtin_amdgcn_sched_barrier(0);  // the second k-step's fragments are on their way under the first's products
       }
-    }
-    __syncthreads();  // slab s_ is in LDS (stored one step ago); the other buffer is no longer read
-    if (s_ + 1 < NSLAB) store_slab((s_ + 1) & 1);
-    const unsigned char *sw = sW + (s_ & 1) * SLAB + l32 * SROW + half * 16;
 #pragma unroll
-    for (int kk = 0; kk < KCK; ++kk)
+      for (int kk = 0; kk < 2; ++kk)
+        if (outside) uf[kk] = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
 #pragma unroll
-      for (int nt = 0; nt < NTL; ++nt) {
-        const bf16x8 wf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(sw + nt * 32 * SROW + kk * 32));
-        acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, uf[kk], acc[nt], 0, 0, 0);
-      }
-    if (mean && d == D - 1) {  // own stream of the qk-mean: + 1/2 of the token's own latent row
+      for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int kk = 0; kk < KCK; ++kk) {
-        // channels c*64 + kk*16 .. +15 lie in output tile 2c + kk/2, half kk % 2 of it
+        for (int nt = 0; nt < NTL; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk][nt], uf[kk], acc[nt], 0, 0, 0);
+      if (mean && back == 0) {  // own stream of the qk-mean: + 1/2 of the token's own row; channels 32 c .. lie in tile c
 #pragma unroll
-        for (int nt = 0; nt < NTL; ++nt)
-          if (nt == 2 * c + kk / 2) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[kk & 1], uf[kk], acc[nt], 0, 0, 0);
+        for (int kk = 0; kk < 2; ++kk) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[kk], uf[kk], acc[c], 0, 0, 0);
       }
     }
   }
 
-  // ---- other stream of the qk-mean, a quarter of the head width at a time
+  // ---- other stream of the qk-mean: each source's rows fetched whole, alternately into this wavefront's quarter of the
+  //      ring and its staging rows, the next source's on the way while one is added
+  __syncthreads();  // the ring is no longer read
   if (mean) {
     const float w_other = is_q ? a.mean_q_other : a.mean_k_other;
     const bf16_t w_other_hi = f32_to_bf16(w_other);
     const bf16_t w_other_lo = f32_to_bf16(w_other - bf16_to_f32(w_other_hi));
     const bool grp_lo = (w_other_lo & 0x7fffu) != 0;  // uniform over the workgroup
-    bf16x8 id_grp[2], id_grp_lo[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      id_grp[j] = identity_frag(w_other_hi, j);
-      id_grp_lo[j] = identity_frag(w_other_lo, j);
-    }
+    const bf16x8 id_hi[2] = {identity_frag(w_other_hi, 0), identity_frag(w_other_hi, 1)};
+    const bf16x8 id_lo[2] = {identity_frag(w_other_lo, 0), identity_frag(w_other_lo, 1)};
+    unsigned char *const buf0 = ring + wave * (32 * ROWB);
     const int nsrc = is_q ? 1 : a.R;
-    for (int sidx = 0; sidx < nsrc; ++sidx) {
-      const int col = is_q ? a.e_q + g * DH : (g * a.R + sidx) * DH;
-      const bf16_t *p = lat + rowc * a.src_stride + col + half * 8;
+    auto fetch_src = [&](int x) { fetch_rows(x & 1 ? stg : buf0, is_q ? a.e_q + g * DH : (g * a.R + x) * DH, 0, 16); };
+    fetch_src(0);
+    for (int x = 0; x < nsrc; ++x) {
+      if (x + 1 < nsrc) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        fetch_src(x + 1);
+        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      const unsigned char *const from = x & 1 ? stg : buf0;
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        bf16x8 mf[KCK];
-#pragma unroll
-        for (int kk = 0; kk < KCK; ++kk)
-          mf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p + c * KC + kk * 16));
-#pragma unroll
-        for (int kk = 0; kk < KCK; ++kk) {
-          acc[2 * c + kk / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_grp[kk & 1], mf[kk], acc[2 * c + kk / 2], 0, 0, 0);
-          if (grp_lo)
-            acc[2 * c + kk / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_grp_lo[kk & 1], mf[kk], acc[2 * c + kk / 2], 0, 0, 0);
+      for (int c = 0; c < QS; ++c) {
+        const bf16x8 m0 = row_frag(from, l32, 2 * c), m1 = row_frag(from, l32, 2 * c + 1);
+        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_hi[0], m0, acc[c], 0, 0, 0);
+        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_hi[1], m1, acc[c], 0, 0, 0);
+        if (grp_lo) {
+          acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_lo[0], m0, acc[c], 0, 0, 0);
+          acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_lo[1], m1, acc[c], 0, 0, 0);
         }
       }
     }
   }
 
-  // ---- per token: norm, temperature, RoPE, store (lane (l32, half): channels 32*nt + 8*rg + 4*half + e)
+  // ---- per token: norm, temperature, RoPE (lane (l32, half): channels 32*nt + 8*rg + 4*half + e)
   if (a.flags & CCA_QK_NORM) {
     float ssq = 0.f;
 #pragma unroll
@@ -646,7 +669,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     for (int nt = 0; nt < NTL / 2; ++nt)
 #pragma unroll
       for (int rg = 0; rg < 4; ++rg) {
-        const int i0 = nt * 32 + rg * 8 + half * 4;
+        const int i0 = nt * 32 + rg * 8 + half * 4;  // 4 consecutive pair indices
         const f32x4 *pa = reinterpret_cast<const f32x4 *>(ropeA + thi * (DH / 2) + i0);
         const f32x4 *pb = reinterpret_cast<const f32x4 *>(ropeB + ((i0 >> 2) * 128 + tlo) * 4);
         const f32x4 a01 = pa[0], a23 = pa[1], b01 = pb[0], b23 = pb[1];
@@ -662,18 +685,35 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         }
       }
   }
-  if (row < a.rows) {
-    bf16_t *orow = dst + row * dst_stride;
+  // ---- round once to bf16; through this wavefront's staging rows (16-byte chunk c of row r at c ^ r), out as whole rows
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows' last readers are done
 #pragma unroll
-    for (int nt = 0; nt < NTL; ++nt)
+  for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        u32x2 w;
-        w.x = pack2(acc[nt][rg * 4 + 0], acc[nt][rg * 4 + 1]);
-        w.y = pack2(acc[nt][rg * 4 + 2], acc[nt][rg * 4 + 3]);
-        *reinterpret_cast<u32x2 *>(orow + nt * 32 + rg * 8 + half * 4) = w;
-      }
+    for (int rg = 0; rg < 4; ++rg) {
+      u32x2 w;
+      w.x = pack2(acc[nt][rg * 4 + 0], acc[nt][rg * 4 + 1]);
+      w.y = pack2(acc[nt][rg * 4 + 2], acc[nt][rg * 4 + 3]);
+      *reinterpret_cast<u32x2 *>(stg + l32 * ROWB + ((nt * 4 + rg) ^ l32) * 16 + half * 8) = w;
+    }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // LDS handles a wavefront's accesses in order
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+  for (int it = 0; it < 16; ++it) {
+    const int rr = it * 2 + (lane >> 5), p = lane & 31, c = p ^ rr;
+    const u32x4 val = *reinterpret_cast<const u32x4 *>(stg + rr * ROWB + p * 16);
+    if (trow0 + rr < a.rows) *reinterpret_cast<u32x4 *>(dst + (trow0 + rr) * dst_stride + c * 8) = val;
   }
+}
+
+template <int D, bool BWD>
+__global__ __launch_bounds__(ST_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void prologue_stream_kernel(
+    FusedArgs a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
+    const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB, const float *__restrict__ temp,
+    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char stream_smem[];
+  prologue_stream_body<D, BWD>(a, lat, vsrc, wc, ropeA, ropeB, temp, q, k, v, rnorm, stream_smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -858,14 +898,15 @@ hipError_t prologue_fused_prepare(const Dims &d, const cca_weights &w, void *scr
 template <int D, bool BWD>
 static hipError_t launch_stream(const Dims &d, FusedArgs a, const float *temp, const void *lat, const void *vsrc,
                                 const FusedScratch &fs, void *q, void *k, void *v, float *rnorm, hipStream_t s) {
-  // one 256-token block per workgroup for every head, key heads first (the kernel's block map)
-  const long long blocks = (d.rows() + 255) / 256;
+  // one 128-token block per workgroup for every head, key heads first (the kernel's block map)
+  const long long blocks = (d.rows() + ST_WAVES * 32 - 1) / (ST_WAVES * 32);
   a.tiles_per_wave = a.tiles_per_wave_k = 1;
   a.n_k_blocks = (int)(d.Hk * blocks);
   a.n_conv_blocks = (int)((d.Hq + d.Hk) * blocks);
   const long long v_chunks = d.rows() * (d.e_kv / 8);
-  const int grid = a.n_conv_blocks + (int)((v_chunks + NT * 4 - 1) / (NT * 4));
-  prologue_stream_kernel<256, D, BWD><<<grid, NT, 0, s>>>(a, (const bf16_t *)lat, (const bf16_t *)vsrc,
+  const int grid = a.n_conv_blocks + (int)((v_chunks + ST_NT * 4 - 1) / (ST_NT * 4));
+  if (hipError_t e = raise_lds_limit<prologue_stream_kernel<D, BWD>>(stream_lds(D)); e != hipSuccess) return e;
+  prologue_stream_kernel<D, BWD><<<grid, ST_NT, stream_lds(D), s>>>(a, (const bf16_t *)lat, (const bf16_t *)vsrc,
                                                         (const u32x4 *)fs.wc, fs.ropeA, fs.ropeB, temp, (bf16_t *)q,
                                                         (bf16_t *)k, (bf16_t *)v, rnorm);
   return hipGetLastError();
