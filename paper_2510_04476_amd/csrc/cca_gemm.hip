@@ -77,7 +77,8 @@ __device__ __forceinline__ void add_wave_parts(f32x16 (&acc)[NI][MI], unsigned c
 // at (m0, n0): packed to bf16, staged in LDS and written as whole rows.  `owner`: this wavefront holds sums to store.
 template <int TM, int TN, int NTHREADS, int NI, int MI>
 __device__ __forceinline__ void store_tile_bf16(const f32x16 (&acc)[NI][MI], unsigned char *smem, bool owner, int wm, int wn,
-                                                int tid, bf16_t *__restrict__ C, long long m0, long long M, int n0, int N) {
+                                                int tid, bf16_t *__restrict__ C, long long m0, long long M, int n0, int N,
+                                                const ColumnSplit &split = ColumnSplit{}) {
   constexpr int ROW_BYTES = TN * 2 + 16;  // padded row: 8-byte column writes of 32 rows hit distinct banks
   const int l32 = tid & 31, half = (tid >> 5) & 1;
   if (owner) {
@@ -102,8 +103,15 @@ __device__ __forceinline__ void store_tile_bf16(const f32x16 (&acc)[NI][MI], uns
     const int r = id / CH_ROW, c = id % CH_ROW;
     const long long gm = m0 + r;
     const int gn = n0 + c * 8;
-    if (gm < M && gn < N)
-      *reinterpret_cast<u32x4 *>(C + gm * N + gn) = *reinterpret_cast<const u32x4 *>(smem + r * ROW_BYTES + c * 16);
+    if (gm >= M || gn >= N) continue;
+    const u32x4 val = *reinterpret_cast<const u32x4 *>(smem + r * ROW_BYTES + c * 16);
+    if (C) *reinterpret_cast<u32x4 *>(C + gm * N + gn) = val;
+    if (split.q) {
+      const int ek = gn - split.e_q, ev = ek - split.e_kv;
+      bf16_t *const to = ek < 0 ? (bf16_t *)split.q + gm * split.e_q + gn
+                                : (ev < 0 ? (bf16_t *)split.k + gm * split.e_kv + ek : (bf16_t *)split.v + gm * split.e_kv + ev);
+      *reinterpret_cast<u32x4 *>(to) = val;
+    }
   }
 }
 
@@ -111,7 +119,7 @@ template <int BN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(const bf16_t *__restrict__ A,
                                                                const bf16_t *__restrict__ Bt,
                                                                bf16_t *__restrict__ C, long long M, int N, int K,
-                                                               int tiles_n, int tiles_total) {
+                                                               int tiles_n, int tiles_total, ColumnSplit split) {
   constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave tile
   constexpr int MI = WM / 32, NI = WN / 32;            // 32x32 MFMA tiles per wave
@@ -226,7 +234,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   }
-  store_tile_bf16<BM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N);
+  store_tile_bf16<BM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N, split);
 }
 
 // Up to two independent transposes in one launch (both projection weights of a forward pass): workgroups
@@ -588,7 +596,8 @@ int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
 }
 
 template <int BN, int WAVES_M, int WAVES_N>
-hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s) {
+hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
+                       hipStream_t s) {
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int total = tiles_m * tiles_n;
   const int per_xcd = (total + 7) / 8;
@@ -597,7 +606,7 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
   constexpr size_t smem = main_bytes > epi_bytes ? main_bytes : epi_bytes;
   if (hipError_t e = raise_lds_limit<gemm_bf16_nt_kernel<BN, WAVES_M, WAVES_N>>(smem); e != hipSuccess) return e;
   gemm_bf16_nt_kernel<BN, WAVES_M, WAVES_N><<<per_xcd * 8, WAVES_M * WAVES_N * 64, smem, s>>>((const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N,
-                                                             K, tiles_n, total);
+                                                             K, tiles_n, total, split);
   return hipGetLastError();
 }
 
@@ -617,7 +626,7 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_deep_kernel(
     const bf16_t *__restrict__ A, const bf16_t *__restrict__ Bt, bf16_t *__restrict__ C, long long M, int N, int K,
-    int tiles_n, int tiles_total) {
+    int tiles_n, int tiles_total, ColumnSplit split) {
   constexpr int NWAVES = WAVES_M * WAVES_N * WAVES_K, NTHREADS = NWAVES * 64;
   constexpr int WM = TM / WAVES_M, WN = TN / WAVES_N, MI = WM / 32, NI = WN / 32;
   static_assert(MI * 32 == WM && NI * 32 == WN, "wave tile must be a multiple of 32");
@@ -702,11 +711,12 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_d
   }
   __syncthreads();
   add_wave_parts<WAVES_M * WAVES_N, WAVES_K>(acc, smem, wk, wmn, lane);
-  store_tile_bf16<TM, TN, NTHREADS>(acc, smem, wk == 0, wm, wn, tid, C, m0, M, n0, N);
+  store_tile_bf16<TM, TN, NTHREADS>(acc, smem, wk == 0, wm, wn, tid, C, m0, M, n0, N, split);
 }
 
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
-hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s) {
+hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
+                            hipStream_t s) {
   const int tiles_m = (int)((M + TM - 1) / TM), tiles_n = (N + TN - 1) / TN;
   const int total = tiles_m * tiles_n;
   constexpr size_t epi_bytes = (size_t)TM * (TN * 2 + 16), sum_bytes = (size_t)(WAVES_K - 1) * TM * TN * 4;
@@ -715,7 +725,7 @@ hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M,
   static_assert(smem <= 160 * 1024, "LDS");
   if (hipError_t e = raise_lds_limit<gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>>(smem); e != hipSuccess) return e;
   gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES><<<(total + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>(
-      (const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N, K, tiles_n, total);
+      (const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N, K, tiles_n, total, split);
   return hipGetLastError();
 }
 
@@ -779,7 +789,8 @@ hipError_t mfma_probe(float *out, int blocks, int iters, bool random_operands, h
 
 bool gemm_mfma_supported(long long M, int N, int K) { return M >= 1 && K % BK == 0 && K >= BK && N % 8 == 0 && N >= 8; }
 
-hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s) {
+hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s,
+                          const ColumnSplit &split) {
   // A tile shape costs (rounds of the grid over the chip) x (64-wide slabs x time per slab + fill and epilogue).  The two
   // numbers of each shape (us) are fits to back-to-back timings at K = 1024 and 2048, M = 64 ... 16384:
   //   256 x 256 (1.5, 8)   256 x 192 (1.35, 6)   128 x 128 at 8 wavefronts (0.46, 5)   64 x 128 (0.35, 3.7)   64 x 64 (0.18, 4.2)
@@ -798,11 +809,11 @@ hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, i
   const double c64x128 = halves ? cost(64, 128, 0.35, 3.7) : 1e30, c64 = halves ? cost(64, 64, 0.18, 4.2) : 1e30;
   const double small = fmin(fmin(c128, c128x2), fmin(c64x128, c64));
   if (fmin(c192, c256) <= small)
-    return c192 < c256 ? launch_gemm<192, 4, 2>(A, Bt, C, M, N, K, s) : launch_gemm<256, 2, 4>(A, Bt, C, M, N, K, s);
-  if (c64 == small) return launch_gemm_deep<64, 64, 2, 2, 2, 3>(A, Bt, C, M, N, K, s);
-  if (c64x128 == small) return launch_gemm_deep<64, 128, 1, 4, 2, 3>(A, Bt, C, M, N, K, s);
-  if (c128 == small) return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, s);
-  return launch_gemm_deep<128, 128, 2, 2, 1, 2>(A, Bt, C, M, N, K, s);
+    return c192 < c256 ? launch_gemm<192, 4, 2>(A, Bt, C, M, N, K, split, s) : launch_gemm<256, 2, 4>(A, Bt, C, M, N, K, split, s);
+  if (c64 == small) return launch_gemm_deep<64, 64, 2, 2, 2, 3>(A, Bt, C, M, N, K, split, s);
+  if (c64x128 == small) return launch_gemm_deep<64, 128, 1, 4, 2, 3>(A, Bt, C, M, N, K, split, s);
+  if (c128 == small) return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, split, s);
+  return launch_gemm_deep<128, 128, 2, 2, 1, 2>(A, Bt, C, M, N, K, split, s);
 }
 
 bool gemm_tn_mfma_supported(int Mo, int No, long long K) { return Mo % 8 == 0 && No % 8 == 0 && Mo >= 8 && No >= 8 && K >= 1; }

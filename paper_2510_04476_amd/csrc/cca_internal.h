@@ -68,7 +68,14 @@ hipError_t attention_generic(const Dims &d, const void *q, const void *k, const 
 // ---- gfx950 MFMA kernels (bf16 storage) -----------------------------------
 // C (M,N) = A (M,K) * Bt (N,K)^T; Bt is the K-contiguous ("transposed") weight.
 bool gemm_mfma_supported(long long M, int N, int K);
-hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s);
+// Where the product goes as well as, or (C = NULL) instead of, to C: columns [0, e_q) to q, the next e_kv to k, the last e_kv
+// to v, each with rows of its own width.  Both widths are multiples of 8 (a 16-byte store never straddles two parts).
+struct ColumnSplit {
+  void *q, *k, *v;
+  int e_q, e_kv;
+};
+hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s,
+                          const ColumnSplit &split = ColumnSplit{});
 // dst (cols, rows) = src (rows, cols)^T, bf16.
 hipError_t transpose_bf16(const void *src, void *dst, int rows, int cols, hipStream_t s);
 // two independent transposes in one launch (src2 may be NULL)
@@ -106,6 +113,8 @@ hipError_t attention_mfma_bf16(const Dims &d, const void *q, const void *k, cons
 
 // no transform selected: q, k, v are slices of the latent rows (plus the optional value-shift)
 bool prologue_is_split_copy(const Dims &d);
+// the inverse norms of the identity prologue: ones (rnorm may be NULL)
+hipError_t prologue_split_norms(const Dims &d, float *rnorm, hipStream_t s);
 hipError_t prologue_split_copy(const Dims &d, const void *lat, void *q, void *k, void *v, float *rnorm, hipStream_t s);
 // its adjoint: no weights, no scratch
 hipError_t prologue_split_copy_bwd(const Dims &d, const void *d_q, const void *d_k, const void *d_v, void *d_lat,

@@ -855,8 +855,14 @@ __global__ void fill_f32_kernel(float *p, long long n, float val) {
     p[i] = val;
 }
 
+hipError_t prologue_split_norms(const Dims &d, float *rnorm, hipStream_t s) {
+  if (!rnorm) return hipSuccess;
+  fill_f32_kernel<<<256, 256, 0, s>>>(rnorm, d.rows() * (d.Hq + d.Hk), 1.f);
+  return hipGetLastError();
+}
+
 hipError_t prologue_split_copy(const Dims &d, const void *lat, void *q, void *k, void *v, float *rnorm, hipStream_t s) {
-  if (rnorm) fill_f32_kernel<<<256, 256, 0, s>>>(rnorm, d.rows() * (d.Hq + d.Hk), 1.f);
+  if (hipError_t e = prologue_split_norms(d, rnorm, s); e != hipSuccess) return e;
   const long long total = d.rows() * ((long long)d.n_lat * d.esize() / 16);
   const int grid = (int)((total + 255) / 256 < 256 * 64 ? (total + 255) / 256 : 256 * 64);
   split_copy_kernel<<<grid, 256, 0, s>>>((const unsigned char *)lat, (unsigned char *)q, (unsigned char *)k,

@@ -283,3 +283,35 @@ def test_attention_backward_with_split_rows(B, T, Hq, Hk, dh, causal):
         worst = float((a.double() - r).abs().max() / r.abs().max())
         say(name, rel, worst)
         assert rel <= 1e-2 and worst <= 2e-2, (name, rel, worst)
+
+
+@pytest.mark.parametrize("T,Hq,Hk,dh,E", [(1, 1, 1, 64, 64), (67, 3, 1, 64, 320), (511, 8, 2, 128, 1024),
+                                           (2050, 5, 5, 40, 2048), (4593, 8, 8, 64, 2048), (4097, 16, 16, 128, 2048)])
+@pytest.mark.parametrize("shift", [0, P.CCA_V_SHIFT])
+def test_projection_stores_heads_of_plain_attention(T, Hq, Hk, dh, E, shift):
+    """Without transforms q, k, v are the column ranges of the latent rows, bit for bit, whether or not the rows are kept."""
+    say("plain heads", T, Hq, Hk, dh, E, shift)
+    cfg = P.CCAConfig(B=2, T=T, d_model=E, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, k_seq=1, k_ch=1,
+                      flags=P.CCA_FLAGS_MHA | shift)
+    x, w_down = rnd(2, T, E, seed=1), rnd(E, cfg.n_lat, seed=2, scale=0.02)
+    w = P.CCAWeights(w_down=w_down, w_out=rnd(cfg.e_q, E, seed=4, scale=0.02))
+    saved = P.CCASaved.allocate(cfg, "cuda")
+    for t in (saved.lat, saved.q, saved.k, saved.v):
+        t.fill_(float("nan"))
+    saved.rnorm.fill_(float("nan"))
+    out = P.cca_forward(cfg, w, x, saved=saved)
+    bare = P.cca_forward(cfg, w, x)
+    lat = P.cca_down_project(cfg, x, w_down)
+    torch.cuda.synchronize()
+    check_product(lat.view(2 * T, -1), x.view(2 * T, E).double() @ w_down.double(), E)
+    assert torch.equal(saved.lat, lat)
+    e_q, e_k = cfg.e_q, cfg.e_q + cfg.e_kv
+    assert torch.equal(saved.q.reshape(2, T, -1), lat[..., :e_q])
+    assert torch.equal(saved.k.reshape(2, T, -1), lat[..., e_q:e_k])
+    v = lat[..., e_k:].clone()
+    if shift:
+        v[:, 1:, cfg.e_kv // 2:] = lat[:, :-1, e_k + cfg.e_kv // 2:]
+        v[:, 0, cfg.e_kv // 2:] = 0
+    assert torch.equal(saved.v.reshape(2, T, -1), v)
+    assert bool((saved.rnorm == 1).all())
+    assert float((out.double() - bare.double()).norm()) <= 2.0 ** -7 * float(out.double().norm())
