@@ -478,8 +478,9 @@ cca_status cca_forward(const cca_config *cfg, const cca_weights *w, const void *
     return CCA_ERR_LAUNCH;
   if (both && prologue_is_split_copy(d) && !(d.flags & CCA_V_SHIFT)) {
     // Plain MHA / GQA: q, k and v are column ranges of the latent rows, so the projection stores them itself, and the latent
-    // row only where a caller keeps it (it is not read again in this pass).  B = 2, T = 2048, 16 heads of 128: the copy
-    // launch was 15.7 us; the pass goes from 255 to 236 us.  With the value-shift a tile's rows would go to two tokens: left to the copy kernel.
+    // row only where a caller keeps it (it is not read again in this pass).  T = 4096, 16 heads of 128: the copy
+    // launch was 15.7 us; the pass goes from 255 to 236 us.
+    // With the value-shift a tile's rows would go to two tokens: left to the copy kernel.
     void *kept = saved ? saved->lat : nullptr;
     if (gemm_mfma_bf16(x, pre + L.wt_down, kept, d.rows(), d.n_lat, d.E, s, ColumnSplit{q, k, v, d.e_q, d.e_kv}) != hipSuccess ||
         prologue_split_norms(d, rnorm, s) != hipSuccess)
