@@ -363,7 +363,8 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(DecArgs a, 
   extern __shared__ float sm[];
   const int dh = DHC ? DHC : a.dh;
   const int split = blockIdx.x % nsplit, g = (blockIdx.x / nsplit) % a.Hk, b = blockIdx.x / (nsplit * a.Hk);
-  const int len = seq_pos(a, b) + 1;  // a short sequence leaves its last splits empty: they write (-inf, 0, 0)
+  const int len = seq_pos(a, b) + 1;
+  if (split * per >= len) return;  // a short sequence has fewer splits: nobody reads the others' place
   const int nr = min(R_MAX, a.R - r0);  // query heads of this pass: g*R + r0 .. + nr
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float *qs = sm;                             // [R_MAX][dh], scaled to log2 units
@@ -479,11 +480,37 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(DecArgs a, 
     }
     float *out = part + (((long long)b * a.Hq + g * a.R + r0 + r) * nsplit + split) * stride;
     if (ch == 0) {
-      out[0] = M;  // -inf when the split holds no key
+      out[0] = M;
       out[1] = L;
     }
     out[2 + ch] = acc;
   }
+}
+
+// Lane exchanges that stay in the vector registers.  The swaps hand (a, b) back as (a's lower half | b's lower half, a's upper
+// half | b's upper half) of the wavefront (32) or of each pair of 16-lane rows (16): with a = b = x a sum or maximum over lane
+// and lane ^ 32 (16), with two values their two sums, the first in the lower and the second in the upper lanes.
+__device__ __forceinline__ float halves32_add(float a, float b) {
+  const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
+__device__ __forceinline__ float halves16_add(float a, float b) {
+  const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
+__device__ __forceinline__ float xor32_add(float x) { return halves32_add(x, x); }
+__device__ __forceinline__ float xor16_add(float x) { return halves16_add(x, x); }
+__device__ __forceinline__ float xor32_max(float x) {
+  const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]));
+}
+__device__ __forceinline__ float xor16_max(float x) {
+  const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]));
+}
+// the value of lane ^ 8 (a rotation by 8 inside each row of 16 lanes)
+__device__ __forceinline__ float ror8(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, true));
 }
 
 // ---------------------------------------------------------------------------
@@ -496,7 +523,14 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(DecArgs a, 
 // online-softmax state (m, l, o over its 8 channels) so the main loop has no other cross-lane step; the groups, then
 // the wavefronts, are merged once at the end.  The next block's K loads are issued as soon as the scores of the
 // current one have left the K registers and the next V loads after the P V step, so a wavefront always has one or
-// two blocks of loads in flight.  NR = query heads per pass, U = load instructions (groups of rows) per block.
+// two blocks of loads in flight.  NR = query heads per pass, U = load instructions (groups of rows) per block: 8 for one or
+// two heads; 4 above, where the accumulators and 8 groups' rows leave two workgroups on a CU (four heads: 134 registers for
+// 4 groups, 200 for 8; eight heads x 128, 20 sequences below 8000 keys: 30.6 us for 4 groups, 33.4 for 2).
+// What bounds it: a full batch over long caches the cache itself (32 x 16384 keys of 1 KB: 99.5 us, 5.4 TB/s), a short or
+// ragged one the time a workgroup needs besides its keys.  13 sequences of up to 5003 keys, 4 KV heads x 64, 19.5 -> 12.8 us:
+// splits past a sequence's end leave at once (they merged and wrote empty states: with every sequence empty the kernel
+// took 15 us, now 6), the last block requests no next one, and the merge of the row groups stays in the vector registers (it was 3 x
+// 10 lane exchanges through LDS per head).
 // ---------------------------------------------------------------------------
 template <int NR, int DH, int U>
 __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArgs a, const float *__restrict__ q_new,
@@ -509,7 +543,6 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
   typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
   __shared__ float mrg[DEC_WAVES][NR][2 + DH];
   const int split = blockIdx.x % nsplit, g = (blockIdx.x / nsplit) % a.Hk, b = blockIdx.x / (nsplit * a.Hk);
-  const int len = seq_pos(a, b) + 1;  // a short sequence leaves its last splits empty: they write (-inf, 0, 0)
   const int nr = min(NR, a.R - r0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rr = lane / LPR, cc = lane % LPR;
@@ -529,6 +562,9 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
     q2[r][2] = (__float_as_uint(hi.x) >> 16) | (__float_as_uint(hi.y) & 0xffff0000u);
     q2[r][3] = (__float_as_uint(hi.z) >> 16) | (__float_as_uint(hi.w) & 0xffff0000u);
   }
+
+  const int len = seq_pos(a, b) + 1;  // after the query's loads: one latency for both
+  if (split * per >= len) return;     // a short sequence has fewer splits: nobody reads the others' place
 
   float m[NR], l[NR], o[NR][8];
 #pragma unroll
@@ -559,7 +595,10 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
 #pragma unroll
     for (int u = 0; u < U; ++u) vr[u] = *reinterpret_cast<const u4 *>(vb + off[u]);
     __builtin_amdgcn_sched_barrier(0);
-    for (; k0 < k_end; k0 += DEC_WAVES * BLK) {
+    // One block: its scores, the next block's K loads, softmax, P V, the next block's V loads.  A wavefront's last block has no
+    // next one, and only that one may reach past the end of the split.
+    auto block = [&](auto last_) __attribute__((always_inline)) {
+      constexpr bool LAST = decltype(last_)::value;
       float s[U][NR];
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -573,15 +612,16 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
           }
           s[u][r] = acc;
         }
-      // the next block of this wavefront (clamped to the last row when there is none): K now, V after the P V step
-      offsets(k0 + DEC_WAVES * BLK);
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!LAST) {
+        offsets(k0 + DEC_WAVES * BLK);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < U; ++u) kr[u] = *reinterpret_cast<const u4 *>(kb + off[u]);
+        for (int u = 0; u < U; ++u) kr[u] = *reinterpret_cast<const u4 *>(kb + off[u]);
+      }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const bool live = k0 + u * RPL + rr < k_end;
+        const bool live = !LAST || k0 + u * RPL + rr < k_end;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
           float x = s[u][r];
@@ -589,7 +629,7 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
           x = dpp_add<0x4E>(x);   // quad_perm [2,3,0,1]
           x = dpp_add<0x141>(x);  // row_half_mirror
           if constexpr (LPR >= 16) x = dpp_add<0x140>(x);  // row_mirror
-          if constexpr (LPR >= 32) x += __shfl_xor(x, 16);
+          if constexpr (LPR >= 32) x = xor16_add(x);
           s[u][r] = live ? x * c : -INFINITY;
         }
       }
@@ -626,35 +666,47 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[r][e] = fmaf(s[u][r], vf[e], o[r][e]);
       }
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!LAST) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < U; ++u) vr[u] = *reinterpret_cast<const u4 *>(vb + off[u]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  // merge the row groups of the wavefront (lane <-> lane ^ step), then the wavefronts through LDS
-#pragma unroll
-  for (int step = LPR; step < 64; step *= 2) {
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const float mo = __shfl_xor(m[r], step), lo = __shfl_xor(l[r], step);
-      const float M = fmaxf(m[r], mo), Ms = M == -INFINITY ? 0.f : M;
-      const float f = exp2f(m[r] - Ms), fo = exp2f(mo - Ms);
-      l[r] = l[r] * f + lo * fo;
-      m[r] = M;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[r][e] = o[r][e] * f + __shfl_xor(o[r][e], step) * fo;
-    }
-  }
-  if (rr == 0) {
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if (cc == 0) {
-        mrg[wave][r][0] = m[r];
-        mrg[wave][r][1] = l[r];
+        for (int u = 0; u < U; ++u) vr[u] = *reinterpret_cast<const u4 *>(vb + off[u]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    for (; k0 + DEC_WAVES * BLK < k_end; k0 += DEC_WAVES * BLK) block(std::false_type{});
+    block(std::true_type{});
+  }
+  // Merge the row groups of the wavefront: the maximum first, each group's state scaled to it once, then sums over the lanes
+  // that hold the same channels, each step leaving half of the channels to either half of the lanes (lane bit 5, then 4, 3).
+  constexpr int OWN = 8 * LPR / 64;  // channels of a lane afterwards
 #pragma unroll
-      for (int e = 0; e < 8; ++e) mrg[wave][r][2 + cc * 8 + e] = o[r][e];
+  for (int r = 0; r < NR; ++r) {
+    float M = xor32_max(m[r]);
+    if constexpr (LPR <= 16) M = xor16_max(M);
+    if constexpr (LPR == 8) M = fmaxf(M, ror8(M));
+    const float f = exp2f(m[r] - (M == -INFINITY ? 0.f : M));  // no live key in the wavefront: every state is (-inf, 0, 0)
+    float lr = xor32_add(l[r] * f);
+    if constexpr (LPR <= 16) lr = xor16_add(lr);
+    if constexpr (LPR == 8) lr += ror8(lr);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[r][e] *= f;
+    float h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = halves32_add(o[r][e], o[r][e + 4]);
+    if constexpr (LPR <= 16) {
+      h[0] = halves16_add(h[0], h[2]);
+      h[1] = halves16_add(h[1], h[3]);
+    }
+    if constexpr (LPR == 8) {
+      const float keep = (lane & 8) ? h[1] : h[0], give = (lane & 8) ? h[0] : h[1];
+      h[0] = keep + ror8(give);
+    }
+    const int ch = cc * 8 + (lane >> 5) * 4 + (LPR <= 16 ? ((lane >> 4) & 1) * 2 : 0) + (LPR == 8 ? (lane >> 3) & 1 : 0);
+#pragma unroll
+    for (int e = 0; e < OWN; ++e) mrg[wave][r][2 + ch + e] = h[e];
+    if (lane == 0) {
+      mrg[wave][r][0] = M;
+      mrg[wave][r][1] = lr;
     }
   }
   __syncthreads();
@@ -673,36 +725,51 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
     }
     float *out = part + (((long long)b * a.Hq + g * a.R + r0 + r) * nsplit + split) * stride;
     if (ch == 0) {
-      out[0] = M;  // -inf when the split holds no key
+      out[0] = M;
       out[1] = L;
     }
     out[2 + ch] = acc;
   }
 }
 
-// o[b, h, :] = sum_s part_o * 2^(m_s - M) / sum_s l_s * 2^(m_s - M), splits in index order
+// o[b, h, :] = sum_s part_o * 2^(m_s - M) / sum_s l_s * 2^(m_s - M), splits in index order.  A thread per channel; its values
+// of up to MAX_SPLITS splits are requested with the states, before the length of the sequence is known (a place that no split
+// wrote is read, never used): one memory latency for both.
 template <typename T>
-__global__ __launch_bounds__(128) void decode_combine_kernel(DecArgs a, const float *__restrict__ part, int nsplit,
+__global__ __launch_bounds__(256) void decode_combine_kernel(DecArgs a, const float *__restrict__ part, int nsplit, int per,
                                                             T *__restrict__ o) {
-  __shared__ float f[MAX_SPLITS];  // 2^(m_s - M) / L per split (0 for an empty split)
+  __shared__ float f[MAX_SPLITS];  // 2^(m_s - M) / L per split (0 beyond the sequence's last)
   const int bh = blockIdx.x, dh = a.dh, stride = 2 + dh, tid = threadIdx.x;
   const float *src = part + (long long)bh * nsplit * stride;
+  const float *mine = src + 2 + min(tid, dh - 1);
+  float val[MAX_SPLITS];
+#pragma unroll
+  for (int s0 = 0; s0 < MAX_SPLITS; s0 += 8)
+    if (s0 < nsplit) {
+#pragma unroll
+      for (int s = s0; s < s0 + 8; ++s) val[s] = mine[min(s, nsplit - 1) * stride];
+    }
+  const int len = seq_pos(a, bh / a.Hq) + 1, n = min(nsplit, (len + per - 1) / per);
   if (tid < 64) {  // one wavefront: lane s holds split s
-    const float ms = tid < nsplit ? src[tid * stride] : -INFINITY;
-    const float ls = tid < nsplit ? src[tid * stride + 1] : 0.f;
+    const int at = min(tid, nsplit - 1) * stride;
+    const float m0 = src[at], l0 = src[at + 1];
+    const float ms = tid < n ? m0 : -INFINITY, ls = tid < n ? l0 : 0.f;
     float M = ms;
     for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
     const float w = ms == -INFINITY ? 0.f : exp2f(ms - M);
     float L = 0.f;
-    for (int s = 0; s < nsplit; ++s) L += __shfl(ls * w, s);  // index order
-    if (tid < nsplit) f[tid] = w / L;
+    for (int s = 0; s < n; ++s) L += __shfl(ls * w, s);  // index order
+    if (tid < MAX_SPLITS) f[tid] = w / L;
   }
   __syncthreads();
-  for (int ch = tid; ch < dh; ch += blockDim.x) {
-    float acc = 0.f;
-    for (int s = 0; s < nsplit; ++s) acc = fmaf(src[s * stride + 2 + ch], f[s], acc);
-    store_f(o + (long long)bh * dh + ch, acc);
-  }
+  float acc = 0.f;
+#pragma unroll
+  for (int s0 = 0; s0 < MAX_SPLITS; s0 += 8)
+    if (s0 < n) {
+#pragma unroll
+      for (int s = s0; s < s0 + 8; ++s) acc = s < n ? fmaf(val[s], f[s], acc) : acc;
+    }
+  if (tid < dh) store_f(o + (long long)bh * dh + tid, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1060,8 +1127,9 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
   }
   {
     const int len = pos + 1;  // the longest sequence sizes the splits
-    // Every split but a sequence's last holds `per` keys: whole rounds of the row kernel's four wavefronts (a wavefront takes
-    // 4 KB of keys at a time), as few as leave about 1024 workgroups on the chip, at most MAX_SPLITS splits.
+    // Every split but a sequence's last holds `per` keys: one or two rounds of the row kernel's four wavefronts (a wavefront
+    // takes 8 load instructions of keys per round, 4 for three and more heads to a group), as few as leave about 1024
+    // workgroups on the chip, at most MAX_SPLITS splits.
     const int unit = d.dh <= 64 ? 256 : d.dh <= 128 ? 128 : 64;
     const long long want = (1024 + (long long)d.B * d.Hk - 1) / ((long long)d.B * d.Hk);
     const long long most = want < MAX_SPLITS ? want : MAX_SPLITS;
@@ -1085,13 +1153,13 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
   }
           if (left == 1) CCA_DEC_ROWS_DH(1, 8)
           else if (left == 2) CCA_DEC_ROWS_DH(2, 8)
-          else if (left <= 4) CCA_DEC_ROWS_DH(4, 8)
+          else if (left <= 4) CCA_DEC_ROWS_DH(4, 4)
           else CCA_DEC_ROWS_DH(8, 4)
 #undef CCA_DEC_ROWS_DH
 #undef CCA_DEC_ROWS
           if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        decode_combine_kernel<T><<<(unsigned)(d.B * d.Hq), 128, 0, s>>>(a, part, nsplit, o);
+        decode_combine_kernel<T><<<(unsigned)(d.B * d.Hq), (d.dh + 63) / 64 * 64, 0, s>>>(a, part, nsplit, per, o);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         return gemm_skinny<T>(o, (const T *)w.w_out, (T *)out, RowDest{d.E, nullptr, 0, 1}, gpart, d.B, d.E, d.e_q, s);
       }
@@ -1113,7 +1181,7 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
 #undef CCA_DEC_ATTN
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    decode_combine_kernel<T><<<(unsigned)(d.B * d.Hq), 128, 0, s>>>(a, part, nsplit, o);
+    decode_combine_kernel<T><<<(unsigned)(d.B * d.Hq), (d.dh + 63) / 64 * 64, 0, s>>>(a, part, nsplit, per, o);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return gemm_skinny<T>(o, (const T *)w.w_out, (T *)out, RowDest{d.E, nullptr, 0, 1}, gpart, d.B, d.E, d.e_q, s);

@@ -315,3 +315,34 @@ def test_projection_stores_heads_of_plain_attention(T, Hq, Hk, dh, E, shift):
     assert torch.equal(saved.v.reshape(2, T, -1), v)
     assert bool((saved.rnorm == 1).all())
     assert float((out.double() - bare.double()).norm()) <= 2.0 ** -7 * float(out.double().norm())
+
+
+@pytest.mark.parametrize("Hq,Hk,dh", [(2, 2, 64), (4, 2, 64), (4, 1, 64), (8, 1, 64), (3, 1, 128), (8, 1, 128), (1, 1, 256),
+                                      (4, 1, 256)])
+def test_decode_ragged_leaves_empty_splits_alone(Hq, Hk, dh):
+    """Sequences from one key to the whole cache in one step, over a workspace full of NaN: each row is the row of a step of
+    that sequence alone.  Both are the same sums in another split, rounded to bf16 before the projection (2^-9) and after."""
+    say("ragged", Hq, Hk, dh)
+    T, E = 1500, 1024
+    pos = [0, 1, 31, 32, 63, 64, 127, 128, 255, 256, 511, 700, T - 1]
+    B = len(pos)
+    cfg = P.CCAConfig(B=B, T=T, d_model=E, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh)
+    one = P.CCAConfig(B=1, T=T, d_model=E, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh)
+    w = P.CCAWeights(w_down=rnd(E, cfg.n_lat, seed=1, scale=0.02), w_out=rnd(cfg.e_q, E, seed=2, scale=0.05),
+                     w_conv_seq=rnd(cfg.e_q + cfg.e_kv, 2, seed=3), w_conv_ch=rnd(Hq + Hk, dh, dh, 2, seed=4, scale=(2 * dh) ** -0.5),
+                     temp=rnd(Hk, seed=5, dtype=torch.float32))
+    x = rnd(B, E, seed=6)
+
+    def state(c, rows):
+        s = P.CCADecodeState.allocate(c, "cuda")
+        s.k_cache.copy_(rnd(B, T, Hk, dh, seed=7).reshape(B, *s.k_cache.shape[1:])[rows])
+        s.v_cache.copy_(rnd(B, T, Hk, dh, seed=8).reshape(B, *s.v_cache.shape[1:])[rows])
+        s.lat_ring.copy_(rnd(*((B,) + tuple(s.lat_ring.shape[1:])), seed=9)[rows])
+        s.workspace.view(torch.float32).fill_(float("nan")) if s.workspace.numel() % 4 == 0 else s.workspace.fill_(255)
+        return s
+
+    out = P.cca_decode_step_ragged(cfg, w, x, state(cfg, slice(0, B)), torch.tensor(pos, dtype=torch.int32, device="cuda"), T - 1)
+    for b, p in enumerate(pos):
+        ref = P.cca_decode_step(one, w, x[b:b + 1], state(one, slice(b, b + 1)), p).double()
+        assert bool(ref.isfinite().all())
+        assert float((out[b].double() - ref[0]).norm()) <= 2.0 ** -7 * float(ref.norm()), (b, p)
