@@ -294,7 +294,7 @@ __device__ __forceinline__ bf16x8 tr_frag_tn(const unsigned char *base, int r0, 
 __global__ __launch_bounds__(512) void gemm_bf16_tn_kernel(const bf16_t *__restrict__ A, long long lda,
                                                           const bf16_t *__restrict__ Bm, long long ldb,
                                                           float *__restrict__ part, int Mo, int No, long long K,
-                                                          int tiles_n, int tiles_total, int slabs_per_split) {
+                                                          int tiles_n, int tiles_total, int splits, int slabs_per_split) {
   constexpr int NTHREADS = 512, WAVES_N = 4;
   constexpr int WM = BM / 2, WN = TN_BN / WAVES_N;  // 128 x 64 wave tile
   constexpr int MI = WM / 32, NI = WN / 32;
@@ -302,12 +302,14 @@ __global__ __launch_bounds__(512) void gemm_bf16_tn_kernel(const bf16_t *__restr
   constexpr int TILE = BK * TN_ROW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [2 stages][A tile | B tile]
 
-  const int wg = blockIdx.x;
-  const int per_xcd = (tiles_total + 7) / 8;
-  const int tile = (wg % 8) * per_xcd + wg / 8;
-  if (tile >= tiles_total) return;
+  // Units (split, tile) in split order, a contiguous range of them to each XCD: the tiles of a split read the same token rows,
+  // so an XCD's L2 is filled with its share of A and B instead of all of both, and every XCD gets the same number of units
+  // (1024 x 2048 over 16384 tokens, 8 splits: 85.4 -> 82.5 us; 36 tiles x 7 splits over 12000 tokens, five tiles to an XCD and
+  // so two rounds before: 116 -> 75).
+  const int units = tiles_total * splits, per_xcd = (units + 7) / 8, unit = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (unit >= units) return;
+  const int split = unit / tiles_total, tile = unit % tiles_total;
   const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * TN_BN;
-  const int split = blockIdx.y;
   const long long nk_all = (K + BK - 1) / BK;
   const long long slab0 = (long long)split * slabs_per_split;
   const int nk = (int)((slab0 + slabs_per_split <= nk_all ? slabs_per_split : nk_all - slab0));
@@ -387,21 +389,21 @@ __global__ __launch_bounds__(512) void gemm_bf16_tn_kernel(const bf16_t *__restr
     }
     __syncthreads();
   }
-  // acc[ni][mi][r] = C[m][n], m = m0 + wm*WM + mi*32 + l32, n = n0 + wn*WN + ni*32 + 8*(r/4) + 4*half + r%4
-  float *out = part + (long long)split * Mo * No;
+  // Partial sums leave as the lanes hold them, 32 x 32 blocks of [r / 4][lane][r % 4] (block (i, j) of a split at i * blocks_n
+  // + j): 1 KB per store instruction, where rows of the matrix would be 32 bytes of 32 cache lines (2048 x 1536 over 7996
+  // tokens, 5 splits: 69.5 -> 67.6 us with the reduction).
+  const int blocks_m = (Mo + 31) / 32, blocks_n = (No + 31) / 32;
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
-      const int m = m0 + wm * WM + mi * 32 + l32;
-      if (m >= Mo) continue;
+      const int bi = m0 / 32 + wm * MI + mi, bj = n0 / 32 + wn * NI + ni;
+      if (bi >= blocks_m || bj >= blocks_n) continue;
+      float *out = part + (((long long)split * blocks_m + bi) * blocks_n + bj) * 1024 + lane * 4;
 #pragma unroll
       for (int rg = 0; rg < 4; ++rg) {
-        const int n = n0 + wn * WN + ni * 32 + rg * 8 + half * 4;
-        if (n < No) {  // No % 8 == 0 and n % 4 == 0: the four columns are inside
-          f32x4 v4 = {acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1], acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]};
-          *reinterpret_cast<f32x4 *>(out + (long long)m * No + n) = v4;
-        }
+        f32x4 v4 = {acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1], acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]};
+        *reinterpret_cast<f32x4 *>(out + rg * 256) = v4;
       }
     }
 }
@@ -561,24 +563,60 @@ hipError_t launch_tn_deep(const void *A, long long lda, const void *Bm, long lon
   return hipGetLastError();
 }
 
-// C[i] = bf16(sum_s part[s][i]), 4 elements per thread, fixed summation order
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, int splits, long long n,
+// C = bf16(sum over splits, in order).  Workgroup = 32 rows x 128 columns, a wavefront per 32 x 32 block of the partial sums;
+// the rounded rows go through LDS so that they leave 256 bytes at a time.
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, int splits, int Mo, int No,
                                                            bf16_t *__restrict__ C) {
-  const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i >= n) return;
-  f32x4 acc = *reinterpret_cast<const f32x4 *>(part + i);
-  for (int s = 1; s < splits; ++s) {
-    const f32x4 v = *reinterpret_cast<const f32x4 *>(part + (long long)s * n + i);
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  constexpr int ROW_BYTES = 128 * 2 + 16;
+  __shared__ __attribute__((aligned(16))) unsigned char tile[32 * ROW_BYTES];
+  const int blocks_m = (Mo + 31) / 32, blocks_n = (No + 31) / 32, strips = (blocks_n + 3) / 4;
+  const int bi = blockIdx.x / strips, j0 = (blockIdx.x % strips) * 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  if (j0 + wave < blocks_n) {
+    const float *p = part + ((long long)bi * blocks_n + j0 + wave) * 1024 + lane * 4;
+    const long long step = (long long)blocks_m * blocks_n * 1024;
+    f32x4 acc[4];
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) acc[rg] = *reinterpret_cast<const f32x4 *>(p + rg * 256);
+    auto add = [&](int s, auto n_) __attribute__((always_inline)) {  // n splits' loads in flight
+      constexpr int N = decltype(n_)::value;
+      f32x4 v[N][4];
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) v[u][rg] = *reinterpret_cast<const f32x4 *>(p + (s + u) * step + rg * 256);
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[rg][e] += v[u][rg][e];
+    };
+    int s = 1;
+    for (; s + 4 <= splits; s += 4) add(s, std::integral_constant<int, 4>{});
+    for (; s < splits; ++s) add(s, std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) {
+      u32x2 w;
+      w.x = pack_bf16x2(acc[rg][0], acc[rg][1]);
+      w.y = pack_bf16x2(acc[rg][2], acc[rg][3]);
+      *reinterpret_cast<u32x2 *>(tile + l32 * ROW_BYTES + (wave * 32 + rg * 8 + half * 4) * 2) = w;
+    }
   }
-  u32x2 w;
-  w.x = pack_bf16x2(acc.x, acc.y);
-  w.y = pack_bf16x2(acc.z, acc.w);
-  *reinterpret_cast<u32x2 *>(C + i) = w;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int id = tid + i * 256, r = id / 16, c = id % 16, m = bi * 32 + r, n = j0 * 32 + c * 8;
+    if (m < Mo && n < No)  // No % 8 == 0
+      *reinterpret_cast<u32x4 *>(C + (long long)m * No + n) = *reinterpret_cast<const u32x4 *>(tile + r * ROW_BYTES + c * 16);
+  }
 }
 
-// Number of K splits: minimise (rounds on 256 CUs) x (slabs per split) x (time of one 256x256x64 slab at ~70 % of
-// the MFMA rate, 1.2 us) + the traffic of the fp32 partial sums (written once, read once, ~3 TB/s).  `us`: that minimum.
+// Number of K splits: minimise (rounds on 256 CUs) x (slabs per split) x (time of a 256 x 256 x 64 slab) + the two launches
+// and the fp32 partial sums, written and read once.  Fits to back-to-back timings of 2 ... 16 splits at K = 4000 ... 16384: a slab
+// takes 1.5 us on a few CUs and 2.0 with all of them at work (192: 1.7, 240: 1.9), the rest 5 us + the bytes at 9 TB/s.  `us`: that
+// minimum.  1024 x 2048 over 8000 tokens: 5 splits 55.9, 8 splits 51.6 us; 2048 x 2048 over 8192: 5 splits 116.6, 4 splits 81.8;
+// 512 x 512 over 12000: 16 splits 33.3, 32 splits 29.1.
 int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
   const long long tiles = (long long)((Mo + BM - 1) / BM) * ((No + TN_BN - 1) / TN_BN);
   const long long nk = (K + BK - 1) / BK;
@@ -588,10 +626,12 @@ int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
     const long long per = (nk + sp - 1) / sp;
     if (sp > 1 && per < 4) break;
     if ((per * (sp - 1)) >= nk) continue;  // an empty last split
-    const double t = (double)((tiles * sp + 255) / 256) * (double)per * 1.2e-6 + (double)sp * Mo * No * 8.0 / 3e12;
+    const double busy = tiles * sp < 256 ? (double)(tiles * sp) / 256.0 : 1.0;
+    const double t = (double)((tiles * sp + 255) / 256) * (double)per * (1.5 + 0.5 * busy * busy * busy) + 5.0 +
+                     (double)sp * Mo * No * 8.0 / 9e6;
     if (best_t < 0 || t < best_t) best_t = t, best = sp;
   }
-  if (us) *us = best_t * 1e6;
+  if (us) *us = best_t;
   return best;
 }
 
@@ -819,16 +859,16 @@ hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, i
 bool gemm_tn_mfma_supported(int Mo, int No, long long K) { return Mo % 8 == 0 && No % 8 == 0 && Mo >= 8 && No >= 8 && K >= 1; }
 
 size_t gemm_tn_scratch_bytes(int Mo, int No, long long K) {
-  return (size_t)tn_splits(Mo, No, K) * Mo * No * sizeof(float);
+  return (size_t)tn_splits(Mo, No, K) * ((Mo + 31) / 32) * ((No + 31) / 32) * 1024 * sizeof(float);
 }
 
 hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No,
                              long long K, float *part, hipStream_t s) {
   // Small tiles without partial sums or 256 x 256 tiles split over K, by estimated time (us).  Fits to back-to-back
   // timings over K = 64 ... 16384 tokens of (rounds) x (slabs x time per slab + fill and epilogue): 128 x 128 (0.63, 3.5),
-  // 64 x 128 (0.50, 3.0), 64 x 64 (0.34, 1.5) up to one workgroup per CU and (0.60, 1.5) at two; the split form takes 4 us
-  // more than the estimate of tn_splits.  2048 x 1536 over 1024 tokens 30.8 -> 13.9 us, over 4000 53.1 -> 43.4, over 8000
-  // split 68.6 against 81.9; 1024 x 2048 over 1024 tokens 31.3 -> 11.1, over 16384 split 85.9 against 132.8.
+  // 64 x 128 (0.50, 3.0), 64 x 64 (0.34, 1.5) up to one workgroup per CU and (0.60, 1.5) at two; the split form as in
+  // tn_splits.  2048 x 1536 over 1024 tokens split 30.8 us, 13.9 this way, over 4000 44.7 and 43.8, over 8000 66.7 and 83.0;
+  // 1024 x 2048 over 1024 tokens 31.3 and 11.1, over 16384 82.5 and 136.9.
   const double slabs = (double)((K + BK - 1) / BK);
   auto tiles = [&](int tm, int tn) { return (long long)((Mo + tm - 1) / tm) * ((No + tn - 1) / tn); };
   double split_us;
@@ -838,23 +878,23 @@ hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long 
                c64x128 = (double)((tiles(64, 128) + 255) / 256) * (slabs * 0.50 + 3.0),
                c64 = t64 <= 256 ? slabs * 0.34 + 1.5 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
   const double small = fmin(c128, fmin(c64x128, c64));
-  if (small < split_us + 4.0) {
+  if (small < split_us) {
     if (c64 == small) return launch_tn_deep<64, 64, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
     if (c64x128 == small) return launch_tn_deep<64, 128, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
     return launch_tn_deep<128, 128, 2, 4, 1, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
   }
   const int tiles_m = (Mo + BM - 1) / BM, tiles_n = (No + TN_BN - 1) / TN_BN;
-  const int total = tiles_m * tiles_n, per_xcd = (total + 7) / 8;
+  const int total = tiles_m * tiles_n;
   const long long nk = (K + BK - 1) / BK;
   const int per = (int)((nk + splits - 1) / splits);
   constexpr size_t smem = 2ull * 2 * BK * TN_ROW;
   if (hipError_t e = raise_lds_limit<gemm_bf16_tn_kernel>(smem); e != hipSuccess) return e;
-  gemm_bf16_tn_kernel<<<dim3(per_xcd * 8, splits), 512, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb, part,
-                                                                  Mo, No, K, tiles_n, total, per);
+  gemm_bf16_tn_kernel<<<(total * splits + 7) / 8 * 8, 512, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb, part, Mo,
+                                                                       No, K, tiles_n, total, splits, per);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long long n = (long long)Mo * No;
-  splitk_reduce_kernel<<<(unsigned)((n / 4 + 255) / 256), 256, 0, s>>>(part, splits, n, (bf16_t *)C);
+  const int blocks = ((Mo + 31) / 32) * ((No + 127) / 128);
+  splitk_reduce_kernel<<<blocks, 256, 0, s>>>(part, splits, Mo, No, (bf16_t *)C);
   return hipGetLastError();
 }
 

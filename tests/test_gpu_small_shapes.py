@@ -54,9 +54,11 @@ def test_projection_tiles(M, Hq, Hk, dh, E):
 
 
 # token rows x (query heads, head width, E): d W_out (e_q, E) = o^T d_out on every tile shape of the weight-gradient GEMM
-# (64 x 64, 64 x 128, 128 x 128, split 256 x 256), with no, one and a few tokens in the last slab of 64
+# (64 x 64, 64 x 128, 128 x 128, split 256 x 256), with no, one and a few tokens in the last slab of 64; the last three split, on
+# a number of tiles that 8 does not divide and on widths that are no multiple of the 32 x 32 blocks of the partial sums
 WGRAD_CASES = [(1, 1, 64, 64), (63, 3, 64, 256), (1000, 8, 64, 1024), (64, 8, 128, 2048), (129, 8, 128, 2048),
-               (1023, 8, 128, 2048), (512, 12, 128, 2048), (2001, 12, 128, 2048), (9001, 8, 128, 2048)]
+               (1023, 8, 128, 2048), (512, 12, 128, 2048), (2001, 12, 128, 2048), (9001, 8, 128, 2048),
+               (9001, 12, 128, 1536), (8003, 25, 40, 1160), (7001, 3, 72, 1032)]
 
 
 @pytest.mark.parametrize("rows,Hq,dh,E", WGRAD_CASES)
