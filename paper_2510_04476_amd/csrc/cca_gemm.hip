@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "cca_internal.h"
+#include "cca_transpose.h"
 
 namespace cca {
 
@@ -237,38 +238,9 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
   store_tile_bf16<BM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N, split);
 }
 
-// Up to two independent transposes in one launch (both projection weights of a forward pass): workgroups
-// [0, n1) serve the first matrix, the rest the second.  64 x 64 tiles; both sizes are multiples of 8 (checked by the
-// launcher) and a thread moves 16 bytes per memory access (the tile is transposed element by element on its way into LDS).
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16_t *__restrict__ src1, bf16_t *__restrict__ dst1,
-                                                            int rows1, int cols1, int n1,
-                                                            const bf16_t *__restrict__ src2, bf16_t *__restrict__ dst2,
-                                                            int rows2, int cols2) {
-  __shared__ __attribute__((aligned(16))) bf16_t tile[64][72];  // [source column][source row], rows of 144 bytes
-  const bool second = (int)blockIdx.x >= n1;
-  const bf16_t *src = second ? src2 : src1;
-  bf16_t *dst = second ? dst2 : dst1;
-  const int rows = second ? rows2 : rows1, cols = second ? cols2 : cols1;
-  const int id = second ? blockIdx.x - n1 : blockIdx.x, tiles_c = (cols + 63) / 64;
-  const int c0 = (id % tiles_c) * 64, r0 = (id / tiles_c) * 64;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int ch = threadIdx.x + i * 256, r = ch >> 3, c = (ch & 7) * 8;  // chunk of 8 columns of source row r0 + r
-    u32x4 v = {0, 0, 0, 0};
-    if (r0 + r < rows && c0 + c < cols) v = *reinterpret_cast<const u32x4 *>(src + (long long)(r0 + r) * cols + c0 + c);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      tile[c + 2 * e][r] = (bf16_t)(v[e] & 0xffffu);
-      tile[c + 2 * e + 1][r] = (bf16_t)(v[e] >> 16);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int ch = threadIdx.x + i * 256, c = ch >> 3, r = (ch & 7) * 8;  // 8 source rows of source column c0 + c
-    if (c0 + c < cols && r0 + r < rows)
-      *reinterpret_cast<u32x4 *>(dst + (long long)(c0 + c) * rows + r0 + r) = *reinterpret_cast<const u32x4 *>(&tile[c][r]);
-  }
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(TransposePair p) {
+  __shared__ TransposeTile tile;
+  transpose_block(p, blockIdx.x, tile);
 }
 
 // ---------------------------------------------------------------------------
@@ -899,16 +871,22 @@ hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long 
 }
 
 hipError_t transpose_bf16(const void *src, void *dst, int rows, int cols, hipStream_t s) {
-  return transpose2_bf16(src, dst, rows, cols, nullptr, nullptr, 0, 0, s);
+  TransposePair p;
+  if (hipError_t e = make_transposes(src, dst, rows, cols, nullptr, nullptr, 0, 0, &p); e != hipSuccess) return e;
+  return transpose2_bf16(p, s);
 }
 
-hipError_t transpose2_bf16(const void *src1, void *dst1, int rows1, int cols1, const void *src2, void *dst2, int rows2,
-                           int cols2, hipStream_t s) {
+hipError_t make_transposes(const void *src1, void *dst1, int rows1, int cols1, const void *src2, void *dst2, int rows2, int cols2,
+                           TransposePair *pair) {
   if (rows1 % 8 || cols1 % 8 || (src2 && (rows2 % 8 || cols2 % 8))) return hipErrorInvalidValue;
-  const int n1 = ((cols1 + 63) / 64) * ((rows1 + 63) / 64);
-  const int n2 = src2 ? ((cols2 + 63) / 64) * ((rows2 + 63) / 64) : 0;
-  transpose_bf16_kernel<<<n1 + n2, 256, 0, s>>>((const bf16_t *)src1, (bf16_t *)dst1, rows1, cols1, n1,
-                                                 (const bf16_t *)src2, (bf16_t *)dst2, rows2, cols2);
+  *pair = TransposePair{(const bf16_t *)src1, (const bf16_t *)src2, (bf16_t *)dst1, (bf16_t *)dst2, rows1, cols1,
+                        ((cols1 + 63) / 64) * ((rows1 + 63) / 64), rows2, cols2,
+                        src2 ? ((cols2 + 63) / 64) * ((rows2 + 63) / 64) : 0};
+  return hipSuccess;
+}
+
+hipError_t transpose2_bf16(const TransposePair &pair, hipStream_t s) {
+  transpose_bf16_kernel<<<pair.n1 + pair.n2, 256, 0, s>>>(pair);
   return hipGetLastError();
 }
 

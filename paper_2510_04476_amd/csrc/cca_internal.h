@@ -78,9 +78,16 @@ hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, i
                           const ColumnSplit &split = ColumnSplit{});
 // dst (cols, rows) = src (rows, cols)^T, bf16.
 hipError_t transpose_bf16(const void *src, void *dst, int rows, int cols, hipStream_t s);
-// two independent transposes in one launch (src2 may be NULL)
-hipError_t transpose2_bf16(const void *src1, void *dst1, int rows1, int cols1, const void *src2, void *dst2, int rows2,
-                           int cols2, hipStream_t s);
+// Two transposes (both projection weights): dst (cols, rows) = src (rows, cols)^T, bf16; n1, n2 workgroups (64 x 64 tiles).
+struct TransposePair {
+  const bf16_t *src1, *src2;
+  bf16_t *dst1, *dst2;
+  int rows1, cols1, n1, rows2, cols2, n2;
+};
+// src2 may be NULL; rows and columns are multiples of 8 (hipErrorInvalidValue otherwise)
+hipError_t make_transposes(const void *src1, void *dst1, int rows1, int cols1, const void *src2, void *dst2, int rows2, int cols2,
+                           TransposePair *pair);
+hipError_t transpose2_bf16(const TransposePair &pair, hipStream_t s);
 
 // measurement aid: blocks x 4 wavefronts x iters x 4 MFMAs (32x32x16 bf16), one float per thread written to out
 hipError_t mfma_probe(float *out, int blocks, int iters, bool random_operands, hipStream_t s);
@@ -159,7 +166,9 @@ hipError_t prologue_fused_bf16(const Dims &d, const cca_weights &w, const void *
                                float *rnorm, void *scratch, hipStream_t s);
 // The two halves of prologue_fused_bf16: `scratch` (folded filters, RoPE tables) depends on the weights and the
 // config only, so a caller may fill it once (prepare) and run the main kernel many times.
-hipError_t prologue_fused_prepare(const Dims &d, const cca_weights &w, void *scratch, hipStream_t s);
+// `weights`: transposes to make in the same launch (may be NULL)
+hipError_t prologue_fused_prepare(const Dims &d, const cca_weights &w, void *scratch, hipStream_t s,
+                                  const TransposePair *weights = nullptr);
 hipError_t prologue_fused_run(const Dims &d, const cca_weights &w, const void *lat, void *q, void *k, void *v,
                               float *rnorm, const void *scratch, hipStream_t s);
 

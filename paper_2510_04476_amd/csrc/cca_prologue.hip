@@ -25,6 +25,7 @@
 // addition formulas in fp32 (an fp32 product t * theta_i alone is off by up to
 // 1e-3 rad at t ~ 16k).
 #include "cca_internal.h"
+#include "cca_transpose.h"
 
 namespace cca {
 
@@ -84,7 +85,13 @@ __device__ __forceinline__ long long slab_elem(int h, int D, int r, int d, int k
 __global__ __launch_bounds__(256) void prologue_setup_kernel(FusedArgs a, int D, const bf16_t *__restrict__ w0,
                                                             const bf16_t *__restrict__ w1, bf16_t *__restrict__ wc,
                                                             float2 *__restrict__ ropeA, float2 *__restrict__ ropeB,
-                                                            int n_fold_blocks, int n_thi, int transposed, int DH) {
+                                                            int n_fold_blocks, int n_thi, int transposed, int DH,
+                                                            int n_set_up, TransposePair weights) {
+  __shared__ TransposeTile tile;
+  if ((int)blockIdx.x >= n_set_up) {  // the projection weights, where a pass derives everything at once
+    transpose_block(weights, blockIdx.x - n_set_up, tile);
+    return;
+  }
   const int NH = a.Hq + a.Hk;
   if ((int)blockIdx.x < n_fold_blocks) {
     const long long id = (long long)blockIdx.x * 256 + threadIdx.x;  // (h, o, i)
@@ -831,12 +838,14 @@ FusedScratch carve(const Dims &d, void *scratch, int D) {
 }
 
 hipError_t run_setup(const Dims &d, const FusedArgs &a, const cca_weights &w, const FusedScratch &fs, int D,
-                     bool transposed, hipStream_t s) {
+                     bool transposed, hipStream_t s, const TransposePair *weights = nullptr) {
   const int NH = d.Hq + d.Hk, n_thi = (d.T + 127) / 128, DH = d.dh;
   const int n_fold = (NH * DH * DH + 255) / 256;
   const int n_rope = (n_thi * (DH / 2) + (DH / 2) * 128 + 255) / 256;
-  prologue_setup_kernel<<<n_fold + n_rope, 256, 0, s>>>(a, D, (const bf16_t *)w.w_conv_seq, (const bf16_t *)w.w_conv_ch,
-                                                        fs.wc, fs.ropeA, fs.ropeB, n_fold, n_thi, transposed ? 1 : 0, DH);
+  const TransposePair pair = weights ? *weights : TransposePair{};
+  prologue_setup_kernel<<<n_fold + n_rope + pair.n1 + pair.n2, 256, 0, s>>>(
+      a, D, (const bf16_t *)w.w_conv_seq, (const bf16_t *)w.w_conv_ch, fs.wc, fs.ropeA, fs.ropeB, n_fold, n_thi, transposed ? 1 : 0,
+      DH, n_fold + n_rope, pair);
   return hipGetLastError();
 }
 
@@ -896,9 +905,9 @@ static FusedArgs forward_args(const Dims &d) {
                    d.rope_base, d.norm_eps, d.n_lat, d.e_q, d.e_kv, d.n_lat, d.e_kv, 0.5f, 0.5f / (float)d.R};
 }
 
-hipError_t prologue_fused_prepare(const Dims &d, const cca_weights &w, void *scratch, hipStream_t s) {
+hipError_t prologue_fused_prepare(const Dims &d, const cca_weights &w, void *scratch, hipStream_t s, const TransposePair *weights) {
   const int D = taps(d);
-  return run_setup(d, forward_args(d), w, carve(d, scratch, D), D, false, s);
+  return run_setup(d, forward_args(d), w, carve(d, scratch, D), D, false, s, weights);
 }
 
 template <int D, bool BWD>
