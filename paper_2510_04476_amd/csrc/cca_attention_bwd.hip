@@ -242,7 +242,8 @@ __device__ __forceinline__ void attn_bwd_dq_body(
   const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTG);
   unsigned char *const sK = smem + kg * 4 * TILE, *const sV = sK + 2 * TILE;  // K0 K1 V0 V1 of each key group
 
-  const int tid = threadIdx.x % NTG, lane = tid & 63, wave = tid >> 6;  // within the key group
+  // (one group of 256 threads: the plain index, whose range the compiler knows; the remainder changed the shape of the loops)
+  const int tid = WIDE ? threadIdx.x : threadIdx.x % NTG, lane = tid & 63, wave = tid >> 6;  // within the key group
   const int l32 = lane & 31, half = lane >> 5;
   const int idx = blockIdx.x;
   const int bh = idx % BH, slot = idx / BH;
@@ -483,7 +484,7 @@ __device__ __forceinline__ void attn_bwd_dq_body(
       if (j + 1 < ntiles) store_tile(buf ^ 1);
       if (j + 2 < ntiles) load_tile(kv0 + 2 * BKV);
     }
-    if (wave_live && kv0 <= (CAUSAL ? wave_last : T - 1)) {
+    if (wave_live && !(CAUSAL && kv0 > wave_last) && (KS == 1 || kv0 < T)) {  // a split group's last tile may lie past the end
       const unsigned char *kp = sK + buf * TILE, *vp = sV + buf * TILE;
       // wave-uniform: tiles below the diagonal and inside the sequence need no mask
       const bool need_mask = (CAUSAL && kv0 + BKV - 1 > qw0) || (kv0 + BKV > T);
@@ -593,7 +594,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
   unsigned char *const sQ = smem + kg * 4 * TILE, *const sD = sQ + 2 * TILE;
   float (*const sStat)[2][BQT] = sStat_[kg];
 
-  const int tid = threadIdx.x % KV_NT, lane = tid & 63, wave = tid >> 6;  // within the group
+  const int tid = WIDE ? threadIdx.x : threadIdx.x % KV_NT, lane = tid & 63, wave = tid >> 6;  // within the group
   const int l32 = lane & 31, half = lane >> 5;
   const int idx = blockIdx.x;
   const int bh = idx % BH, kb = idx / BH;  // early key blocks (most query tiles when causal) first
@@ -841,7 +842,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
     const int buf = step & 1;
     const int t0 = (qt_first + step * KS + kg) * BQT;
     if (step + 1 < steps) issue_tile(step + 1, buf ^ 1);  // that buffer was last read before the previous barrier
-    if (wave_live && (KS == 1 || t0 < T) && !(CAUSAL && t0 + BQT - 1 < kw0)) {
+    if (wave_live && !(CAUSAL && t0 + BQT - 1 < kw0) && (KS == 1 || t0 < T)) {  // a split group's last tile may lie past the end
       const unsigned char *qp = sQ + buf * TILE, *dp_ = sD + buf * TILE;
       // wave-uniform: tiles away from the diagonal and from the end of the sequence need no mask at all
       const bool need_mask = (CAUSAL && t0 < kw0 + 31) || (t0 + BQT > T) || (kw0 + 32 > T);
