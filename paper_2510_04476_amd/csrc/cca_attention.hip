@@ -154,7 +154,7 @@ __device__ __forceinline__ void store_rows(const f32x16 *oacc, float l, float sh
 
 
 // Two groups of wavefronts walked the two halves of the keys of the same rows (KS = 2): the partial results of a row,
-// taken against the reference maxima m (a group that saw no key of the row has l = 0), are added through LDS.  Each group
+// taken against the reference maxima m (a group that saw no score of the row above -inf has l = 0), are added through LDS.  Each group
 // ends with the output tiles [kg * DT / 2, (kg + 1) * DT / 2) of its wavefront's rows; l and m are the row's afterwards.
 // The K / V tiles in `smem` are no longer read by anyone when this is called.
 template <int DH>
@@ -314,6 +314,7 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
 #pragma unroll
     for (int r = 0; r < 16; ++r) negm[r] = BOUNDED ? -bound : 0.f;
     float l_run = 0.f, l_run2 = 0.f;  // running sums of probabilities (two chains); each half-wave keeps its own part
+    bool unset = true;                // every score of this row was -inf so far: its reference max is still to come
 
     const int kv_end = CAUSAL ? min(q0 + BQ_, T) : T;  // keys [0, kv_end) matter to this workgroup
     const int ntiles = ((kv_end + BKV - 1) / BKV + KS - 1) / KS;  // of a key group (the last one may lie past the end)
@@ -371,10 +372,12 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
             mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
           }
-          // Move the reference max only on the first tile (to the tile's own max) or when a score
-          // exceeds it by more than 2^RESCALE_LOG2; exp2 arguments stay <= RESCALE_LOG2.
-          if (j == 0 || __any(mx > RESCALE_LOG2)) {
-            const float delta = (j == 0) ? mx : fmaxf(mx, 0.f);  // finite: a tile's first key is visible to every row of the wavefront
+          // Move the reference max only on a row's first tile with a score above -inf (to the tile's own max: -inf itself
+          // would leave inf - inf; keys may be masked by scores of -inf, and a key group may hold nothing but such keys) or
+          // when a score exceeds it by more than 2^RESCALE_LOG2; exp2 arguments stay <= RESCALE_LOG2.
+          if (__any(unset || mx > RESCALE_LOG2)) {
+            const float delta = unset ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, 0.f);
+            unset = unset && mx == -INFINITY;
             const float alpha = __builtin_amdgcn_exp2f(-delta);
             l_run *= alpha;
             l_run2 *= alpha;

@@ -138,6 +138,36 @@ def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
             assert float((lse[b, h].double() - ref_lse).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
 
 
+@pytest.mark.parametrize("live", [(0, 40), (70, 140), (129, 300)])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh", [64, 128, 256])
+def test_attention_keys_masked_by_infinite_scores(dh, causal, live):
+    """Scores of -inf (padded keys: a channel of k at -inf that every q reads with a positive weight) in whole key tiles: the
+    rows that see a live key are those of attention over the live keys alone, with the roundings of the test above."""
+    T, Hq, lo, hi = 300, 2, *live
+    say("infinite scores", dh, causal, live)
+    assert split_of(1, T, Hq, causal)
+    cfg = P.CCAConfig(B=1, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, flags=P.CCA_CAUSAL if causal else 0)
+    q, k, v = rnd(1, T, Hq, dh, seed=1), rnd(1, T, Hq, dh, seed=2), rnd(1, T, Hq, dh, seed=3)
+    q[..., 5] = 1.0
+    k[:, :lo, :, 5], k[:, hi:, :, 5] = float("-inf"), float("-inf")
+    o, lse = P.cca_attention(cfg, q, k, v, want_lse=True)
+    torch.cuda.synchronize()
+    first = lo if causal else 0
+    for h in range(Hq):
+        s = q[0, first:, h].double() @ k[0, lo:hi, h].double().t().contiguous() / dh ** 0.5
+        s_max = float(s.abs().max())
+        if causal:
+            s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1)[first:, lo:hi], float("-inf"))
+        p, vh = torch.softmax(s, -1), v[0, lo:hi, h].double()
+        noise = 2.0 ** -9 * (1.0 + s_max) * (p.square() @ vh.square()).sqrt()
+        ref = p @ vh
+        got = o[0, first:, h * dh:(h + 1) * dh].double()
+        assert bool(got.isfinite().all())
+        assert float(((got - ref).abs() / (2.0 ** -8 * ref.abs() + 6.0 * noise + 1e-6)).max()) <= 1.0
+        assert float((lse[0, h, first:].double() - torch.logsumexp(s, -1)).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
+
+
 # the decode step's projections (several passes through LDS, K slices of the down-projection, lengths that are not whole
 # groups) and filter layouts: widths 256 and 64 with up to 4 + 4 taps, 5 query heads per KV head
 DECODE_CASES = [dict(B=9, T=5, E=4104, Hq=4, Hk=2, dh=64, k_seq=2, k_ch=2), dict(B=2, T=9, E=2056, Hq=4, Hk=2, dh=256, k_seq=4, k_ch=4),
