@@ -7,7 +7,7 @@
 // MFMA tile) and all of d_h, so the softmax statistics of a row never leave a
 // wavefront.  Keys / values arrive in tiles of 64 through double-buffered LDS:
 // a tile travels HBM -> registers during one tile step and registers -> LDS
-// during the next.  Where that grid would leave CUs idle (split_keys below)
+// during the next.  Where that grid would leave CUs idle (fwd_splits_keys)
 // a workgroup owns 128 rows instead and its two groups of four wavefronts
 // take the even and the odd key tiles; the two partial results of a row are
 // merged through LDS.
@@ -44,8 +44,6 @@
 // Two code paths share the kernel: the generic one (running reference max,
 // one tile at a time) and, for bounded scores, a software-pipelined one
 // (attn_fwd_pipelined below).
-#include <math.h>
-
 #include <type_traits>
 
 #include "cca_internal.h"
@@ -1026,23 +1024,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     attn_fwd_body<DH, CAUSAL, false, RSUM, NT, KS>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, 0.f, smem);
 }
 
-// Two key groups per workgroup (128 query rows, half the key tiles for each group) or one (256 rows)?  256-row blocks leave most CUs idle until B * H_q * T
-// reaches about 32 k rows, and each walks all keys of its rows.  The split form costs 12 % more per step (a tile is staged
-// for 128 rows instead of 256) and about 1.5 steps for the merge.  Measured (T, B * H_q, d_h: one group -> two, us, causal):
-// 512, 8, 128: 19.1 -> 16.2; 2048, 8, 128: 47.6 -> 33.6; 4096, 8, 128: 85.0 -> 57.7; 8192, 8, 128: 171.6 -> 134.2;
-// 4096, 16, 128 without bound: 101.8 -> 81.8; 1531, 24, 64: 26.6 -> 19.4; kept on one group: 64, 8: 6.2 -> 7.8;
-// 16384, 8, 128: 446 -> 501; 1999, 64, 64: 44.7 -> 54.7.  256 threads and 128 rows without the split: 2048, 8: 38.1.
-bool split_keys(const Dims &d) { return 1.12 * busiest_cu(d, BQ / 2, true) + 1.5 < busiest_cu(d, BQ, true); }
-
 template <int DH, int KS>
 hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo, float *lse,
                   const float *temp, hipStream_t s) {
   constexpr bool WIDE = DH > 128;             // one wavefront per SIMD, 128-row query blocks
   constexpr int BQL = WIDE ? 128 : BQ / KS;
-  const int nqb = row_blocks(d, BQL);
+  const int nqb = row_blocks(d.T, BQL);
   const int BH = d.B * d.Hq;
   const bool causal = d.flags & CCA_CAUSAL;
-  const int paired = pair_blocks(d, nqb) ? 1 : 0;
+  const int paired = pair_blocks(BH, causal, nqb) ? 1 : 0;
   const long long blocks = (long long)BH * (paired ? (nqb + 1) / 2 : nqb);
   const int qk_normed = (d.flags & CCA_QK_NORM) ? 1 : 0;
   if (!(d.flags & CCA_KEY_TEMP)) temp = nullptr;
@@ -1077,7 +1067,7 @@ bool attention_mfma_supported(const Dims &d) {
 
 hipError_t attention_mfma_bf16(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo,
                                float *lse, const float *temp, hipStream_t s) {
-  const bool halves = d.dh <= 128 && split_keys(d);
+  const bool halves = d.dh <= 128 && fwd_splits_keys((long long)d.B * d.Hq, d.T, d.flags & CCA_CAUSAL);
   return d.dh == 256   ? launch<256, 1>(d, q, k, v, o, o_lo, lse, temp, s)
          : d.dh == 128 ? (halves ? launch<128, 2>(d, q, k, v, o, o_lo, lse, temp, s) : launch<128, 1>(d, q, k, v, o, o_lo, lse, temp, s))
                        : (halves ? launch<64, 2>(d, q, k, v, o, o_lo, lse, temp, s) : launch<64, 1>(d, q, k, v, o, o_lo, lse, temp, s));

@@ -969,15 +969,10 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
   constexpr bool WIDE = DH > 128;                 // one wavefront per SIMD, half as many rows per workgroup
   constexpr int NTH = WIDE ? 256 : DQ_NT;         // threads of both kernels (DQ_NT == KV_NT)
   static_assert(DQ_NT == KV_NT, "one thread count for both kernels");
-  // Two groups of wavefronts per workgroup where 256-row blocks leave CUs idle, by the busiest CU's steps; the split form
-  // measured 5 to 8 % slower per step (T = 16384, B * H_q = 8, d_h = 128: dQ + 49, dK / dV + 41 us of 1660) and loses about a
-  // step to the merge.  Attention backward, us, neither -> dQ -> dK / dV -> both split, causal, d_h = 128: T = 512, B * H_q
-  // = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115; 8192, 8: 658 -> 590 -> 546 -> 478; 4096, 16 MHA: 343 ->
-  // 312 -> 290 -> 258; d_h = 64, 1531, 24: 95 -> 83 -> 78 -> 65; kept whole: 1999, 64: 174 -> 181 -> 185 -> 194.
-  const bool dq_halves = !WIDE && 1.08 * busiest_cu(d, NTH / 4, true) + 1.0 < busiest_cu(d, NTH / 2, true);
-  const bool kv_halves = !WIDE && 1.08 * busiest_cu(d, NTH / 4, false) + 1.0 < busiest_cu(d, NTH / 2, false);
+  const int BH = d.B * d.Hq;
+  const bool dq_halves = !WIDE && dq_splits_keys(BH, d.T, causal), kv_halves = !WIDE && dkdv_splits_rows(BH, d.T, causal);
   const int dq_rows = dq_halves ? NTH / 4 : NTH / 2, kv_rows = kv_halves ? NTH / 4 : NTH / 2;  // rows, keys per workgroup
-  const int BH = d.B * d.Hq, nqb = row_blocks(d, dq_rows), nkb = row_blocks(d, kv_rows);
+  const int nqb = row_blocks(d.T, dq_rows), nkb = row_blocks(d.T, kv_rows);
   float *pk = reinterpret_cast<float *>(reinterpret_cast<char *>(delta) + delta_bytes(d));
   float *pv = pk + (size_t)d.rows() * d.e_q;
   bf16_t *qs = reinterpret_cast<bf16_t *>(reinterpret_cast<char *>(delta) + delta_bytes(d) +
@@ -997,7 +992,7 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
   constexpr size_t kv_smem = 4ull * kv_tile_rows(NTH, 1) * (DH * 2 + 64);
   // pairing query blocks only pays while it still leaves a workgroup for each of the 256 CUs; the dK / dV kernel
   // gains nothing from it (measured)
-  const int paired = pair_blocks(d, nqb) ? 1 : 0;
+  const int paired = pair_blocks(BH, causal, nqb) ? 1 : 0;
   const bool partial = d.R > 1;
   // (the dynamic-LDS limit is raised once per kernel and device: raise_lds_limit)
 #define LAUNCH_KV_KS(C_, P_, KS_)                                                                             \

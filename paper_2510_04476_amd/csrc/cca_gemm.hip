@@ -14,8 +14,6 @@
 // which leaves every lane with 4 consecutive output columns of one row, so
 // the epilogue packs them to bf16, stages the tile in LDS and writes whole
 // rows with 16-byte stores.
-#include <math.h>
-
 #include <type_traits>
 
 #include "cca_internal.h"
@@ -584,29 +582,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
   }
 }
 
-// Number of K splits: minimise (rounds on 256 CUs) x (slabs per split) x (time of a 256 x 256 x 64 slab) + the two launches
-// and the fp32 partial sums, written and read once.  Fits to back-to-back timings of 2 ... 16 splits at K = 4000 ... 16384: a slab
-// takes 1.5 us on a few CUs and 2.0 with all of them at work (192: 1.7, 240: 1.9), the rest 5 us + the bytes at 9 TB/s.  `us`: that
-// minimum.  1024 x 2048 over 8000 tokens: 5 splits 55.9, 8 splits 51.6 us; 2048 x 2048 over 8192: 5 splits 116.6, 4 splits 81.8;
-// 512 x 512 over 12000: 16 splits 33.3, 32 splits 29.1.
-int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
-  const long long tiles = (long long)((Mo + BM - 1) / BM) * ((No + TN_BN - 1) / TN_BN);
-  const long long nk = (K + BK - 1) / BK;
-  int best = 1;
-  double best_t = -1.0;
-  for (int sp = 1; sp <= 32; ++sp) {
-    const long long per = (nk + sp - 1) / sp;
-    if (sp > 1 && per < 4) break;
-    if ((per * (sp - 1)) >= nk) continue;  // an empty last split
-    const double busy = tiles * sp < 256 ? (double)(tiles * sp) / 256.0 : 1.0;
-    const double t = (double)((tiles * sp + 255) / 256) * (double)per * (1.5 + 0.5 * busy * busy * busy) + 5.0 +
-                     (double)sp * Mo * No * 8.0 / 9e6;
-    if (best_t < 0 || t < best_t) best_t = t, best = sp;
-  }
-  if (us) *us = best_t;
-  return best;
-}
-
 template <int BN, int WAVES_M, int WAVES_N>
 hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
                        hipStream_t s) {
@@ -803,29 +778,15 @@ bool gemm_mfma_supported(long long M, int N, int K) { return M >= 1 && K % BK ==
 
 hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s,
                           const ColumnSplit &split) {
-  // A tile shape costs (rounds of the grid over the chip) x (64-wide slabs x time per slab + fill and epilogue).  The two
-  // numbers of each shape (us) are fits to back-to-back timings at K = 1024 and 2048, M = 64 ... 16384:
-  //   256 x 256 (1.5, 8)   256 x 192 (1.35, 6)   128 x 128 at 8 wavefronts (0.46, 5)   64 x 128 (0.35, 3.7)   64 x 64 (0.18, 4.2)
-  //   128 x 128 at 4 wavefronts, two workgroups per CU (1.0, 6.4), a last round of one per CU (0.62, 4)
-  // e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).
-  const double slabs = (double)(K / BK);
-  auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-  auto cost = [&](int tm, int tn, double per_slab, double fixed) {
-    return (double)((tiles(tm, tn) + 255) / 256) * (slabs * per_slab + fixed);
-  };
-  const long long t128 = tiles(128, 128), rest = t128 % 512;
-  const double c256 = cost(256, 256, 1.5, 8.0), c192 = cost(256, 192, 1.35, 6.0), c128 = cost(128, 128, 0.46, 5.0),
-               c128x2 = (double)(t128 / 512 + (rest > 256)) * (slabs + 6.4) +
-                        (rest > 0 && rest <= 256 ? slabs * 0.62 + 4.0 : 0.0);
-  const bool halves = K % (2 * BK) == 0;  // the shapes that split a slab over two halves of the wavefronts
-  const double c64x128 = halves ? cost(64, 128, 0.35, 3.7) : 1e30, c64 = halves ? cost(64, 64, 0.18, 4.2) : 1e30;
-  const double small = fmin(fmin(c128, c128x2), fmin(c64x128, c64));
-  if (fmin(c192, c256) <= small)
-    return c192 < c256 ? launch_gemm<192, 4, 2>(A, Bt, C, M, N, K, split, s) : launch_gemm<256, 2, 4>(A, Bt, C, M, N, K, split, s);
-  if (c64 == small) return launch_gemm_deep<64, 64, 2, 2, 2, 3>(A, Bt, C, M, N, K, split, s);
-  if (c64x128 == small) return launch_gemm_deep<64, 128, 1, 4, 2, 3>(A, Bt, C, M, N, K, split, s);
-  if (c128 == small) return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, split, s);
-  return launch_gemm_deep<128, 128, 2, 2, 1, 2>(A, Bt, C, M, N, K, split, s);
+  switch (nt_tile(M, N, K)) {
+    case NT_256x256: return launch_gemm<256, 2, 4>(A, Bt, C, M, N, K, split, s);
+    case NT_256x192: return launch_gemm<192, 4, 2>(A, Bt, C, M, N, K, split, s);
+    case NT_64x64: return launch_gemm_deep<64, 64, 2, 2, 2, 3>(A, Bt, C, M, N, K, split, s);
+    case NT_64x128: return launch_gemm_deep<64, 128, 1, 4, 2, 3>(A, Bt, C, M, N, K, split, s);
+    case NT_128x128_8W: return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, split, s);
+    case NT_128x128_4W: return launch_gemm_deep<128, 128, 2, 2, 1, 2>(A, Bt, C, M, N, K, split, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 bool gemm_tn_mfma_supported(int Mo, int No, long long K) { return Mo % 8 == 0 && No % 8 == 0 && Mo >= 8 && No >= 8 && K >= 1; }
@@ -836,25 +797,13 @@ size_t gemm_tn_scratch_bytes(int Mo, int No, long long K) {
 
 hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No,
                              long long K, float *part, hipStream_t s) {
-  // Small tiles without partial sums or 256 x 256 tiles split over K, by estimated time (us).  Fits to back-to-back
-  // timings over K = 64 ... 16384 tokens of (rounds) x (slabs x time per slab + fill and epilogue): 128 x 128 (0.63, 3.5),
-  // 64 x 128 (0.50, 3.0), 64 x 64 (0.34, 1.5) up to one workgroup per CU and (0.60, 1.5) at two; the split form as in
-  // tn_splits.  2048 x 1536 over 1024 tokens split 30.8 us, 13.9 this way, over 4000 44.7 and 43.8, over 8000 66.7 and 83.0;
-  // 1024 x 2048 over 1024 tokens 31.3 and 11.1, over 16384 82.5 and 136.9.
-  const double slabs = (double)((K + BK - 1) / BK);
-  auto tiles = [&](int tm, int tn) { return (long long)((Mo + tm - 1) / tm) * ((No + tn - 1) / tn); };
-  double split_us;
-  const int splits = tn_splits(Mo, No, K, &split_us);
-  const long long t64 = tiles(64, 64);
-  const double c128 = (double)((tiles(128, 128) + 255) / 256) * (slabs * 0.63 + 3.5),
-               c64x128 = (double)((tiles(64, 128) + 255) / 256) * (slabs * 0.50 + 3.0),
-               c64 = t64 <= 256 ? slabs * 0.34 + 1.5 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
-  const double small = fmin(c128, fmin(c64x128, c64));
-  if (small < split_us) {
-    if (c64 == small) return launch_tn_deep<64, 64, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
-    if (c64x128 == small) return launch_tn_deep<64, 128, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
-    return launch_tn_deep<128, 128, 2, 4, 1, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
+  switch (tn_tile(Mo, No, K)) {
+    case TN_64x64: return launch_tn_deep<64, 64, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
+    case TN_64x128: return launch_tn_deep<64, 128, 2, 2, 2, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
+    case TN_128x128: return launch_tn_deep<128, 128, 2, 4, 1, 4>(A, lda, Bm, ldb, C, Mo, No, K, s);
+    case TN_SPLIT: break;
   }
+  const int splits = tn_splits(Mo, No, K);
   const int tiles_m = (Mo + BM - 1) / BM, tiles_n = (No + TN_BN - 1) / TN_BN;
   const int total = tiles_m * tiles_n;
   const long long nk = (K + BK - 1) / BK;

@@ -8,6 +8,7 @@
 #include <atomic>
 
 #include "cca.h"
+#include "cca_rules.h"
 
 namespace cca {
 
@@ -91,27 +92,6 @@ hipError_t transpose2_bf16(const TransposePair &pair, hipStream_t s);
 
 // measurement aid: blocks x 4 wavefronts x iters x 4 MFMAs (32x32x16 bf16), one float per thread written to out
 hipError_t mfma_probe(float *out, int blocks, int iters, bool random_operands, hipStream_t s);
-
-// ---- grids of the attention kernels (forward and backward, d_h <= 128), one 8-wavefront workgroup per CU ----------------
-// Blocks of `rows` query rows (or keys); whether each workgroup takes two of them.  Causal work per block grows (keys:
-// falls) with its index.  Giving every workgroup one heavy and one light block (equal work for all) measured ~20 % faster
-// in the forward kernel at B*Hq = 8 than issuing the heavy blocks first; only worth it while it still leaves a workgroup
-// for each of the 256 CUs.
-inline int row_blocks(const Dims &d, int rows) { return (d.T + rows - 1) / rows; }
-inline bool pair_blocks(const Dims &d, int blocks) {
-  return (d.flags & CCA_CAUSAL) && (long long)d.B * d.Hq * ((blocks + 1) / 2) >= 256;
-}
-// A grid takes as long as its busiest CU: steps of 64 rows of the other kind per group of wavefronts, with 256 rows per
-// workgroup (one group) or 128 (two groups, each with half of the steps).  `pairs`: the kernel takes paired blocks.
-inline double busiest_cu(const Dims &d, int rows, bool pairs) {
-  const long long BH = (long long)d.B * d.Hq, n = row_blocks(d, rows), blocks = BH * n;
-  const double part = rows / 256.0;
-  if (!(d.flags & CCA_CAUSAL)) return (double)((blocks + 255) / 256) * (double)((d.T + 63) / 64) * part;
-  const double per = rows / 64.0 * part;  // steps of the shortest block; the i-th takes i times as many
-  if (pairs && pair_blocks(d, (int)n)) return (double)((BH * ((n + 1) / 2) + 255) / 256) * per * (double)(n + 1);
-  const double even = (double)BH * (double)n * (double)(n + 1) / 512.0;
-  return per * (even > (double)n ? even : (double)n);
-}
 
 bool attention_mfma_supported(const Dims &d);
 // temp (H_k log-temperatures, device) is read only when d.flags has QK_NORM and KEY_TEMP: it bounds the scores

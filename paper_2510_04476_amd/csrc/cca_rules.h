@@ -1,0 +1,122 @@
+// Which form of a kernel serves a call: rules on sizes alone, in plain host arithmetic (no HIP), so that the launchers and the
+// tests ask the same functions.  Every rule compares estimated times; the constants are fits to measurements, quoted beside
+// them in microseconds.
+#pragma once
+
+#include <math.h>
+
+namespace cca {
+
+// ---- projections: C (M,N) = A (M,K) * Bt (N,K)^T, bf16 -------------------------------------------------------------------
+// tile rows x columns, wavefronts of a workgroup
+enum NtTile { NT_256x256, NT_256x192, NT_64x64, NT_64x128, NT_128x128_8W, NT_128x128_4W };
+
+// A tile shape costs (rounds of the grid over the chip) x (64-wide slabs x time per slab + fill and epilogue).  The two
+// numbers of each shape (us) are fits to back-to-back timings at K = 1024 and 2048, M = 64 ... 16384:
+//   256 x 256 (1.5, 8)   256 x 192 (1.35, 6)   128 x 128 at 8 wavefronts (0.46, 5)   64 x 128 (0.35, 3.7)   64 x 64 (0.18, 4.2)
+//   128 x 128 at 4 wavefronts, two workgroups per CU (1.0, 6.4), a last round of one per CU (0.62, 4)
+// e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).
+inline NtTile nt_tile(long long M, int N, int K) {
+  const double slabs = (double)(K / 64);
+  auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  auto cost = [&](int tm, int tn, double per_slab, double fixed) {
+    return (double)((tiles(tm, tn) + 255) / 256) * (slabs * per_slab + fixed);
+  };
+  const long long t128 = tiles(128, 128), rest = t128 % 512;
+  const double c256 = cost(256, 256, 1.5, 8.0), c192 = cost(256, 192, 1.35, 6.0), c128 = cost(128, 128, 0.46, 5.0),
+               c128x2 = (double)(t128 / 512 + (rest > 256)) * (slabs + 6.4) +
+                        (rest > 0 && rest <= 256 ? slabs * 0.62 + 4.0 : 0.0);
+  const bool halves = K % 128 == 0;  // the shapes that split a slab over two halves of the wavefronts
+  const double c64x128 = halves ? cost(64, 128, 0.35, 3.7) : 1e30, c64 = halves ? cost(64, 64, 0.18, 4.2) : 1e30;
+  const double small = fmin(fmin(c128, c128x2), fmin(c64x128, c64));
+  if (fmin(c192, c256) <= small) return c192 < c256 ? NT_256x192 : NT_256x256;
+  if (c64 == small) return NT_64x64;
+  if (c64x128 == small) return NT_64x128;
+  return c128 == small ? NT_128x128_8W : NT_128x128_4W;
+}
+
+// ---- weight gradients: C (Mo,No) = A (K,Mo)^T * B (K,No), bf16, K tokens -------------------------------------------------
+enum TnTile { TN_SPLIT, TN_64x64, TN_64x128, TN_128x128 };
+
+// Number of K splits: minimise (rounds on 256 CUs) x (slabs per split) x (time of a 256 x 256 x 64 slab) + the two launches
+// and the fp32 partial sums, written and read once.  Fits to back-to-back timings of 2 ... 16 splits at K = 4000 ... 16384: a slab
+// takes 1.5 us on a few CUs and 2.0 with all of them at work (192: 1.7, 240: 1.9), the rest 5 us + the bytes at 9 TB/s.  `us`: that
+// minimum.  1024 x 2048 over 8000 tokens: 5 splits 55.9, 8 splits 51.6 us; 2048 x 2048 over 8192: 5 splits 116.6, 4 splits 81.8;
+// 512 x 512 over 12000: 16 splits 33.3, 32 splits 29.1.
+inline int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
+  const long long tiles = (long long)((Mo + 255) / 256) * ((No + 255) / 256);
+  const long long nk = (K + 63) / 64;
+  int best = 1;
+  double best_t = -1.0;
+  for (int sp = 1; sp <= 32; ++sp) {
+    const long long per = (nk + sp - 1) / sp;
+    if (sp > 1 && per < 4) break;
+    if ((per * (sp - 1)) >= nk) continue;  // an empty last split
+    const double busy = tiles * sp < 256 ? (double)(tiles * sp) / 256.0 : 1.0;
+    const double t = (double)((tiles * sp + 255) / 256) * (double)per * (1.5 + 0.5 * busy * busy * busy) + 5.0 +
+                     (double)sp * Mo * No * 8.0 / 9e6;
+    if (best_t < 0 || t < best_t) best_t = t, best = sp;
+  }
+  if (us) *us = best_t;
+  return best;
+}
+
+// Small tiles without partial sums or 256 x 256 tiles split over K, by estimated time (us).  Fits to back-to-back
+// timings over K = 64 ... 16384 tokens of (rounds) x (slabs x time per slab + fill and epilogue): 128 x 128 (0.63, 3.5),
+// 64 x 128 (0.50, 3.0), 64 x 64 (0.34, 1.5) up to one workgroup per CU and (0.60, 1.5) at two; the split form as in
+// tn_splits.  2048 x 1536 over 1024 tokens split 30.8 us, 13.9 this way, over 4000 44.7 and 43.8, over 8000 66.7 and 83.0;
+// 1024 x 2048 over 1024 tokens 31.3 and 11.1, over 16384 82.5 and 136.9.
+inline TnTile tn_tile(int Mo, int No, long long K) {
+  const double slabs = (double)((K + 63) / 64);
+  auto tiles = [&](int tm, int tn) { return (long long)((Mo + tm - 1) / tm) * ((No + tn - 1) / tn); };
+  double split_us;
+  tn_splits(Mo, No, K, &split_us);
+  const long long t64 = tiles(64, 64);
+  const double c128 = (double)((tiles(128, 128) + 255) / 256) * (slabs * 0.63 + 3.5),
+               c64x128 = (double)((tiles(64, 128) + 255) / 256) * (slabs * 0.50 + 3.0),
+               c64 = t64 <= 256 ? slabs * 0.34 + 1.5 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
+  const double small = fmin(c128, fmin(c64x128, c64));
+  if (small >= split_us) return TN_SPLIT;
+  return c64 == small ? TN_64x64 : c64x128 == small ? TN_64x128 : TN_128x128;
+}
+
+// ---- grids of the attention kernels (forward and backward, d_h <= 128), one 8-wavefront workgroup per CU -----------------
+// BH = batch x query heads.  Blocks of `rows` query rows (or keys); whether each workgroup takes two of them.  Causal work per
+// block grows (keys: falls) with its index.  Giving every workgroup one heavy and one light block (equal work for all)
+// measured ~20 % faster in the forward kernel at BH = 8 than issuing the heavy blocks first; only worth it while it still
+// leaves a workgroup for each of the 256 CUs.
+inline int row_blocks(int T, int rows) { return (T + rows - 1) / rows; }
+inline bool pair_blocks(long long BH, bool causal, int blocks) { return causal && BH * ((blocks + 1) / 2) >= 256; }
+// A grid takes as long as its busiest CU: steps of 64 rows of the other kind per group of wavefronts, with 256 rows per
+// workgroup (one group) or 128 (two groups, each with half of the steps).  `pairs`: the kernel takes paired blocks.
+inline double busiest_cu(long long BH, int T, bool causal, int rows, bool pairs) {
+  const long long n = row_blocks(T, rows), blocks = BH * n;
+  const double part = rows / 256.0;
+  if (!causal) return (double)((blocks + 255) / 256) * (double)((T + 63) / 64) * part;
+  const double per = rows / 64.0 * part;  // steps of the shortest block; the i-th takes i times as many
+  if (pairs && pair_blocks(BH, causal, (int)n)) return (double)((BH * ((n + 1) / 2) + 255) / 256) * per * (double)(n + 1);
+  const double even = (double)BH * (double)n * (double)(n + 1) / 512.0;
+  return per * (even > (double)n ? even : (double)n);
+}
+// Forward: two key groups per workgroup (128 query rows, half the key tiles for each group) or one (256 rows)?  256-row blocks leave most CUs idle until B * H_q * T
+// reaches about 32 k rows, and each walks all keys of its rows.  The split form costs 12 % more per step (a tile is staged
+// for 128 rows instead of 256) and about 1.5 steps for the merge.  Measured (T, B * H_q, d_h: one group -> two, us, causal):
+// 512, 8, 128: 19.1 -> 16.2; 2048, 8, 128: 47.6 -> 33.6; 4096, 8, 128: 85.0 -> 57.7; 8192, 8, 128: 171.6 -> 134.2;
+// 4096, 16, 128 without bound: 101.8 -> 81.8; 1531, 24, 64: 26.6 -> 19.4; kept on one group: 64, 8: 6.2 -> 7.8;
+// 16384, 8, 128: 446 -> 501; 1999, 64, 64: 44.7 -> 54.7.  256 threads and 128 rows without the split: 2048, 8: 38.1.
+inline bool fwd_splits_keys(long long BH, int T, bool causal) {
+  return 1.12 * busiest_cu(BH, T, causal, 128, true) + 1.5 < busiest_cu(BH, T, causal, 256, true);
+}
+// Backward: two groups of wavefronts per workgroup where 256-row blocks leave CUs idle, by the busiest CU's steps; the split form
+// measured 5 to 8 % slower per step (T = 16384, B * H_q = 8, d_h = 128: dQ + 49, dK / dV + 41 us of 1660) and loses about a
+// step to the merge.  Attention backward, us, neither -> dQ -> dK / dV -> both split, causal, d_h = 128: T = 512, B * H_q
+// = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115; 8192, 8: 658 -> 590 -> 546 -> 478; 4096, 16 MHA: 343 ->
+// 312 -> 290 -> 258; d_h = 64, 1531, 24: 95 -> 83 -> 78 -> 65; kept whole: 1999, 64: 174 -> 181 -> 185 -> 194.
+inline bool dq_splits_keys(long long BH, int T, bool causal) {
+  return 1.08 * busiest_cu(BH, T, causal, 128, true) + 1.0 < busiest_cu(BH, T, causal, 256, true);
+}
+inline bool dkdv_splits_rows(long long BH, int T, bool causal) {
+  return 1.08 * busiest_cu(BH, T, causal, 128, false) + 1.0 < busiest_cu(BH, T, causal, 256, false);
+}
+
+}  // namespace cca

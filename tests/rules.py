@@ -1,0 +1,68 @@
+"""The library's dispatch rules (csrc/cca_rules.h), compiled for the host, so that a test can ask which form of a kernel serves
+a size instead of keeping a copy of the rule."""
+import ctypes as C
+import functools
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = r"""
+#include "cca_rules.h"
+using namespace cca;
+extern "C" {
+int r_nt_tile(long long M, int N, int K) { return nt_tile(M, N, K); }
+int r_tn_tile(int Mo, int No, long long K) { return tn_tile(Mo, No, K); }
+int r_tn_splits(int Mo, int No, long long K) { return tn_splits(Mo, No, K); }
+int r_fwd_splits_keys(long long BH, int T, int causal) { return fwd_splits_keys(BH, T, causal); }
+int r_dq_splits_keys(long long BH, int T, int causal) { return dq_splits_keys(BH, T, causal); }
+int r_dkdv_splits_rows(long long BH, int T, int causal) { return dkdv_splits_rows(BH, T, causal); }
+int r_pair_blocks(long long BH, int causal, int blocks) { return pair_blocks(BH, causal, blocks); }
+}
+"""
+NT_TILES = ("256x256", "256x192", "64x64", "64x128", "128x128 8 wavefronts", "128x128 4 wavefronts")
+TN_TILES = ("split", "64x64", "64x128", "128x128")
+
+
+@functools.lru_cache(None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        src, so = os.path.join(d, "rules.cpp"), os.path.join(d, "rules.so")
+        with open(src, "w") as f:
+            f.write(SOURCE)
+        subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
+                        os.path.join(ROOT, "paper_2510_04476_amd", "csrc"), src, "-o", so], check=True)
+        lib = C.CDLL(so)
+    L, I = C.c_longlong, C.c_int
+    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I],
+                           r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I]).items():
+        getattr(lib, name).argtypes = args
+    return lib
+
+
+def nt_tile(M, N, K):
+    return NT_TILES[_lib().r_nt_tile(M, N, K)]
+
+
+def tn_tile(Mo, No, K):
+    return TN_TILES[_lib().r_tn_tile(Mo, No, K)]
+
+
+def tn_splits(Mo, No, K):
+    return _lib().r_tn_splits(Mo, No, K)
+
+
+def fwd_splits_keys(BH, T, causal):
+    return bool(_lib().r_fwd_splits_keys(BH, T, causal))
+
+
+def dq_splits_keys(BH, T, causal):
+    return bool(_lib().r_dq_splits_keys(BH, T, causal))
+
+
+def dkdv_splits_rows(BH, T, causal):
+    return bool(_lib().r_dkdv_splits_rows(BH, T, causal))
+
+
+def pair_blocks(BH, causal, blocks):
+    return bool(_lib().r_pair_blocks(BH, causal, blocks))

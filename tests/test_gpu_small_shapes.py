@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import paper_2510_04476_amd as P
+import rules
 from oracle import cca_oracle as O
 from synth_inputs import make_inputs, make_upstream_grad
 from util import check_out, check_tap, oracle_forward, to_np
@@ -74,22 +75,6 @@ def test_weight_gradient_tiles(rows, Hq, dh, E):
     check_product(g.w_out, saved.o[0].double().t().contiguous() @ d_out[0].double(), rows)
 
 
-def split_of(B, T, Hq, causal):
-    """Whether the launcher splits the keys of a workgroup over two groups (the rule of csrc/cca_attention.hip)."""
-    BH = B * Hq
-
-    def busiest(bq):
-        n = -(-T // bq)
-        if not causal:
-            return -(-BH * n // 256) * -(-T // 64) * bq / 256
-        per = bq / 64 * bq / 256
-        if BH * ((n + 1) // 2) >= 256:
-            return -(-BH * ((n + 1) // 2) // 256) * per * (n + 1)
-        return per * max(n, BH * n * (n + 1) / 512)
-
-    return 1.12 * busiest(128) + 1.5 < busiest(256)
-
-
 # B, T, Hq, Hk, d_h, causal, normalised: odd lengths, one tile more or less than a pair, rows whose second key group is
 # empty, several query blocks, paired and unpaired grids; scores bounded and not
 SPLIT_CASES = [(1, 300, 2, 1, 128, True, True), (1, 321, 3, 3, 64, True, False), (2, 385, 2, 2, 128, False, True),
@@ -104,7 +89,7 @@ def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
     probability, independent) and o is rounded once: 2^-8 of the value plus, per element, the rounding noise of the sum.
     q * scale * log2 e is rounded to bf16 once more (2^-9 of each logit)."""
     say("split attention", B, T, Hq, Hk, dh, causal, normed)
-    assert split_of(B, T, Hq, causal)
+    assert rules.fwd_splits_keys(B * Hq, T, causal)
     flags = (P.CCA_CAUSAL if causal else 0) | (P.CCA_QK_NORM if normed else 0)
     cfg = P.CCAConfig(B=B, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, flags=flags)
     q, k = rnd(B, T, Hq, dh, seed=1, dtype=torch.float32), rnd(B, T, Hk, dh, seed=2, dtype=torch.float32)
@@ -146,7 +131,7 @@ def test_attention_keys_masked_by_infinite_scores(dh, causal, live):
     rows that see a live key are those of attention over the live keys alone, with the roundings of the test above."""
     T, Hq, lo, hi = 300, 2, *live
     say("infinite scores", dh, causal, live)
-    assert split_of(1, T, Hq, causal)
+    assert rules.fwd_splits_keys(Hq, T, causal)
     cfg = P.CCAConfig(B=1, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, flags=P.CCA_CAUSAL if causal else 0)
     q, k, v = rnd(1, T, Hq, dh, seed=1), rnd(1, T, Hq, dh, seed=2), rnd(1, T, Hq, dh, seed=3)
     q[..., 5] = 1.0
@@ -285,6 +270,7 @@ def test_attention_backward_with_split_rows(B, T, Hq, Hk, dh, causal):
     come from the forward's bf16 scores (2^-9 of each logit, |logit| <= 11 here): six roundings of 2^-9 in quadrature on
     q (6e-3 rel-L2, as the whole-block tests measure); the asserted bound is their 1e-2."""
     say("split backward", B, T, Hq, Hk, dh, causal)
+    assert rules.dq_splits_keys(B * Hq, T, causal) and rules.dkdv_splits_rows(B * Hq, T, causal)
     flags = (P.CCA_CAUSAL if causal else 0) | P.CCA_QK_NORM
     cfg = P.CCAConfig(B=B, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, flags=flags)
     q, k = rnd(B, T, Hq, dh, seed=1, dtype=torch.float32), rnd(B, T, Hk, dh, seed=2, dtype=torch.float32)
