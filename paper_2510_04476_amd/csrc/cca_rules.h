@@ -12,10 +12,12 @@ namespace cca {
 enum NtTile { NT_256x256, NT_256x192, NT_64x64, NT_64x128, NT_128x128_8W, NT_128x128_4W };
 
 // A tile shape costs (rounds of the grid over the chip) x (64-wide slabs x time per slab + fill and epilogue).  The two
-// numbers of each shape (us) are fits to back-to-back timings at K = 1024 and 2048, M = 64 ... 16384:
-//   256 x 256 (1.5, 8)   256 x 192 (1.35, 6)   128 x 128 at 8 wavefronts (0.46, 5)   64 x 128 (0.35, 3.7)   64 x 64 (0.18, 4.2)
-//   128 x 128 at 4 wavefronts, two workgroups per CU (1.0, 6.4), a last round of one per CU (0.62, 4)
-// e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).
+// numbers of each shape (us) are least-squares fits (10 % rms) to back-to-back timings of every shape at K = 256 ... 4096,
+// N = 192 ... 4096, M = 64 ... 16384; over those sizes and K = 64 ... 192 the choice costs 0.4 % on average against the best shape:
+//   256 x 256 (1.41, 5.2)  256 x 192 (1.11, 4.8)  128 x 128 at 8 wavefronts (0.528, 3)  64 x 128 (0.354, 3)  64 x 64 (0.232, 2.2)
+//   128 x 128 at 4 wavefronts, two workgroups per CU (1.04, 4.4), a last round of one per CU (0.61, 3.2)
+// e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).  With a fit over K = 1024
+// and 2048 alone, 6000 x 2048 x 4096 ran on 128 x 128 at 8 wavefronts, 126 us where 256 x 192 takes 104; 4593 x 4096 x 4096: 216 for 173.
 inline NtTile nt_tile(long long M, int N, int K) {
   const double slabs = (double)(K / 64);
   auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
@@ -23,11 +25,11 @@ inline NtTile nt_tile(long long M, int N, int K) {
     return (double)((tiles(tm, tn) + 255) / 256) * (slabs * per_slab + fixed);
   };
   const long long t128 = tiles(128, 128), rest = t128 % 512;
-  const double c256 = cost(256, 256, 1.5, 8.0), c192 = cost(256, 192, 1.35, 6.0), c128 = cost(128, 128, 0.46, 5.0),
-               c128x2 = (double)(t128 / 512 + (rest > 256)) * (slabs + 6.4) +
-                        (rest > 0 && rest <= 256 ? slabs * 0.62 + 4.0 : 0.0);
+  const double c256 = cost(256, 256, 1.41, 5.2), c192 = cost(256, 192, 1.11, 4.8), c128 = cost(128, 128, 0.528, 3.0),
+               c128x2 = (double)(t128 / 512 + (rest > 256)) * (slabs * 1.04 + 4.4) +
+                        (rest > 0 && rest <= 256 ? slabs * 0.61 + 3.2 : 0.0);
   const bool halves = K % 128 == 0;  // the shapes that split a slab over two halves of the wavefronts
-  const double c64x128 = halves ? cost(64, 128, 0.35, 3.7) : 1e30, c64 = halves ? cost(64, 64, 0.18, 4.2) : 1e30;
+  const double c64x128 = halves ? cost(64, 128, 0.354, 3.0) : 1e30, c64 = halves ? cost(64, 64, 0.232, 2.2) : 1e30;
   const double small = fmin(fmin(c128, c128x2), fmin(c64x128, c64));
   if (fmin(c192, c256) <= small) return c192 < c256 ? NT_256x192 : NT_256x256;
   if (c64 == small) return NT_64x64;

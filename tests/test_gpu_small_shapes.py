@@ -39,7 +39,7 @@ def check_product(got, ref, K):
 # of a tile's edge, contraction lengths of one slab, an odd number of slabs (no split over halves) and many
 GEMM_CASES = [(1, 1, 1, 64, 64), (65, 1, 1, 64, 192), (127, 3, 1, 64, 320), (512, 8, 2, 128, 2048), (511, 4, 4, 64, 1024),
               (1000, 8, 2, 128, 2048), (1999, 16, 4, 64, 2048), (2050, 5, 5, 64, 1024), (4593, 8, 8, 64, 2048),
-              (3001, 8, 2, 128, 2048), (4097, 16, 16, 128, 2048)]
+              (3001, 8, 2, 128, 2048), (4097, 16, 16, 128, 2048), (4097, 5, 5, 64, 320), (9001, 5, 5, 64, 448)]
 
 
 @pytest.mark.parametrize("M,Hq,Hk,dh,E", GEMM_CASES)
