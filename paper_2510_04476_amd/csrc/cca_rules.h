@@ -90,35 +90,56 @@ inline TnTile tn_tile(int Mo, int No, long long K) {
 inline int row_blocks(int T, int rows) { return (T + rows - 1) / rows; }
 inline bool pair_blocks(long long BH, bool causal, int blocks) { return causal && BH * ((blocks + 1) / 2) >= 256; }
 // A grid takes as long as its busiest CU: steps of 64 rows of the other kind per group of wavefronts, with 256 rows per
-// workgroup (one group) or 128 (two groups, each with half of the steps).  `pairs`: the kernel takes paired blocks.
-inline double busiest_cu(long long BH, int T, bool causal, int rows, bool pairs) {
-  const long long n = row_blocks(T, rows), blocks = BH * n;
-  const double part = rows / 256.0;
-  if (!causal) return (double)((blocks + 255) / 256) * (double)((T + 63) / 64) * part;
-  const double per = rows / 64.0 * part;  // steps of the shortest block; the i-th takes i times as many
-  if (pairs && pair_blocks(BH, causal, (int)n)) return (double)((BH * ((n + 1) / 2) + 255) / 256) * per * (double)(n + 1);
-  const double even = (double)BH * (double)n * (double)(n + 1) / 512.0;
-  return per * (even > (double)n ? even : (double)n);
+// workgroup (one group) or 128 (two groups, each with half of the steps); a block's steps end with the sequence.  Workgroups
+// are issued longest first: up to 256 the longest counts, up to 512 the CU that takes the 256th and the 257th, beyond that an even share.
+// Every block pays `start` steps (its resident rows and first tile); the split form's steps cost `step` each (a tile is staged
+// for half as many rows), its blocks `merge` steps more, and with all CUs at work everything a share `busy` more.  `pairs`: the
+// kernel takes paired blocks.
+struct SplitCost {
+  double start, step, merge, busy;
+};
+inline double busiest_cu(long long BH, int T, bool causal, int rows, bool pairs, const SplitCost &c) {
+  const long long n = row_blocks(T, rows), steps = (T + 63) / 64;
+  const double tile = c.step * rows / 256.0;
+  auto block = [&](long long i) {  // the i-th in the order of its work
+    const long long s = (i + 1) * (rows / 64);
+    return (double)(causal && s < steps ? s : steps) * tile + c.start + c.merge;
+  };
+  const bool paired = pairs && pair_blocks(BH, causal, (int)n);
+  const long long units = paired ? (n + 1) / 2 : n, jobs = BH * units;
+  auto unit = [&](long long i) { return block(n - 1 - i) + (paired && 2 * i < n - 1 ? block(i) : 0.0); };  // as issued
+  const double longest = fmax(unit(0), units > 1 ? unit(1) : 0.0);
+  const double all = causal ? (double)((rows / 64) * (n * (n - 1) / 2) + steps) : (double)(n * steps);
+  const double even = (double)BH * (all * tile + (double)n * (c.start + c.merge)) / 256.0;
+  double t = longest;
+  if (jobs > 512) t = fmax(longest, even + 0.5 * unit(units - 1));
+  else if (jobs > 256) t = fmax(longest, unit(255 / BH) + unit(256 / BH));
+  return t * (1.0 + c.busy * fmin(1.0, even / longest));
 }
-// Forward: two key groups per workgroup (128 query rows, half the key tiles for each group) or one (256 rows)?  256-row blocks leave most CUs idle until B * H_q * T
-// reaches about 32 k rows, and each walks all keys of its rows.  The split form costs 12 % more per step (a tile is staged
-// for 128 rows instead of 256) and about 1.5 steps for the merge.  Measured (T, B * H_q, d_h: one group -> two, us, causal):
-// 512, 8, 128: 19.1 -> 16.2; 2048, 8, 128: 47.6 -> 33.6; 4096, 8, 128: 85.0 -> 57.7; 8192, 8, 128: 171.6 -> 134.2;
-// 4096, 16, 128 without bound: 101.8 -> 81.8; 1531, 24, 64: 26.6 -> 19.4; kept on one group: 64, 8: 6.2 -> 7.8;
-// 16384, 8, 128: 446 -> 501; 1999, 64, 64: 44.7 -> 54.7.  256 threads and 128 rows without the split: 2048, 8: 38.1.
+inline bool split_pays(long long BH, int T, bool causal, bool pairs, const SplitCost &split) {
+  return busiest_cu(BH, T, causal, 128, pairs, split) < busiest_cu(BH, T, causal, 256, pairs, SplitCost{split.start, 1.0, 0.0, 0.0});
+}
+// Forward: two key groups per workgroup (128 query rows, half the key tiles for each group) or one (256 rows)?  256-row blocks
+// leave most CUs idle until B * H_q * T reaches about 32 k rows, and each walks all keys of its rows.  The costs are the
+// best of a grid against timings of both forms at d_h = 64 and 128, B * H_q = 1 ... 128, T = 40 ... 12288, causal with and without
+// a bound on the scores and not causal: over these the choice costs 0.4 % on average against the faster form.
+// Measured (T, B * H_q, d_h: one group -> two, us, causal): split 512, 8, 128: 19.1 -> 16.2; 2048, 8, 128: 47.6 -> 33.6;
+// 8192, 8, 128: 171.6 -> 134.2; 4096, 16, 128 without bound: 101.8 -> 81.8; 1531, 24, 64: 26.6 -> 19.4; kept on one group
+// 64, 8, 64: 4.4 -> 5.4; 128, 8, 128: 8.2 -> 9.4; 400, 96, 64: 10.8 -> 15.6; 640, 64, 64: 12.7 -> 14.1; 16384, 8, 128: 446 ->
+// 501; 1999, 64, 64: 44.7 -> 54.7; the line is soft (777, 48, 128 is split: 24.7 -> 26.0).  256 threads and 128 rows without the split: 2048, 8: 38.1.
 inline bool fwd_splits_keys(long long BH, int T, bool causal) {
-  return 1.12 * busiest_cu(BH, T, causal, 128, true) + 1.5 < busiest_cu(BH, T, causal, 256, true);
+  return split_pays(BH, T, causal, true, SplitCost{3.0, 1.04, 1.0, 0.2});
 }
-// Backward: two groups of wavefronts per workgroup where 256-row blocks leave CUs idle, by the busiest CU's steps; the split form
-// measured 5 to 8 % slower per step (T = 16384, B * H_q = 8, d_h = 128: dQ + 49, dK / dV + 41 us of 1660) and loses about a
-// step to the merge.  Attention backward, us, neither -> dQ -> dK / dV -> both split, causal, d_h = 128: T = 512, B * H_q
-// = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115; 8192, 8: 658 -> 590 -> 546 -> 478; 4096, 16 MHA: 343 ->
-// 312 -> 290 -> 258; d_h = 64, 1531, 24: 95 -> 83 -> 78 -> 65; kept whole: 1999, 64: 174 -> 181 -> 185 -> 194.
+// Backward, likewise (B * H_q = 4 ... 128, T = 64 ... 8192, one and four query heads per KV head; dQ within 0.1 %, dK / dV
+// within 0.2 % of the faster form).  Attention backward, us, neither -> dQ -> dK / dV -> both split, causal, d_h = 128: T = 512, B *
+// H_q = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115; 8192, 8: 658 -> 590 -> 546 -> 478; 4096, 16 MHA: 343 ->
+// 312 -> 290 -> 258; d_h = 64, 1531, 24: 95 -> 83 -> 78 -> 65; kept whole: 1999, 64: 174 -> 181 -> 185 -> 194; dK / dV alone
+// 1531, 64: 104.5 -> 115.3; dQ alone 300, 128: 36.8 -> 38.8.
 inline bool dq_splits_keys(long long BH, int T, bool causal) {
-  return 1.08 * busiest_cu(BH, T, causal, 128, true) + 1.0 < busiest_cu(BH, T, causal, 256, true);
+  return split_pays(BH, T, causal, true, SplitCost{3.0, 1.0, 1.0, 0.0});
 }
 inline bool dkdv_splits_rows(long long BH, int T, bool causal) {
-  return 1.08 * busiest_cu(BH, T, causal, 128, false) + 1.0 < busiest_cu(BH, T, causal, 256, false);
+  return split_pays(BH, T, causal, false, SplitCost{2.0, 1.0, 1.0, 0.1});
 }
 
 }  // namespace cca

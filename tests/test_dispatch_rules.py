@@ -39,3 +39,21 @@ NT_MEASURED = [
 def test_projection_tile_is_the_fastest(M, N, K, us):
     """Within 6 %: the fit's own error (10 % rms) decides between shapes that are closer than that."""
     assert us[rules.NT_TILES.index(rules.nt_tile(M, N, K))] <= 1.06 * min(us)
+
+
+# B * H_q, T, causal and us on one and on two groups of wavefronts (d_h = 64 or 128)
+FWD_MEASURED = [(8, 64, True, 4.4, 5.4), (8, 128, True, 8.2, 9.4), (96, 400, True, 10.8, 15.6), (128, 400, True, 17.9, 25.2),
+                (64, 640, True, 12.7, 14.1), (64, 777, True, 16.2, 18.5), (128, 640, False, 40.6, 57.6), (96, 1280, True, 54.5, 72.3),
+                (8, 200, True, 12.3, 10.1), (8, 2048, True, 47.6, 33.6), (24, 1531, True, 26.6, 19.4), (16, 4096, True, 101.8, 81.8),
+                (16, 512, False, 19.4, 15.5), (64, 1999, True, 44.7, 54.7), (8, 16384, True, 446.0, 501.0)]
+DQ_MEASURED = [(128, 300, True, 36.8, 38.8), (128, 777, True, 147.8, 155.3), (8, 2048, True, 180.0, 156.0), (24, 1531, True, 95.0, 83.0),
+               (64, 1999, True, 174.0, 181.0)]
+DKDV_MEASURED = [(64, 1531, True, 104.5, 115.3), (4, 64, True, 13.0, 13.9), (8, 2048, True, 180.0, 139.0), (24, 1531, True, 95.0, 78.0),
+                 (64, 1999, True, 174.0, 185.0)]
+
+
+@pytest.mark.parametrize("rule,cases", [(rules.fwd_splits_keys, FWD_MEASURED), (rules.dq_splits_keys, DQ_MEASURED),
+                                        (rules.dkdv_splits_rows, DKDV_MEASURED)])
+def test_attention_split_is_the_faster_form(rule, cases):
+    wrong = [(BH, T, causal) for BH, T, causal, one, two in cases if rule(BH, T, causal) != (two < one)]
+    assert not wrong, wrong
