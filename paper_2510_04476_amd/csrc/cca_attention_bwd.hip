@@ -486,7 +486,8 @@ __device__ __forceinline__ void attn_bwd_dq_body(
     }
     if (wave_live && !(CAUSAL && kv0 > wave_last) && (KS == 1 || kv0 < T)) {  // a split group's last tile may lie past the end
       const unsigned char *kp = sK + buf * TILE, *vp = sV + buf * TILE;
-      // wave-uniform: tiles below the diagonal and inside the sequence need no mask
+      // wave-uniform: tiles below the diagonal and inside the sequence need no mask.  (Split without a causal mask every tile
+      // takes the masked form: with the other beside it the d_h = 128 kernel spills 80 registers.)
       const bool need_mask = (CAUSAL && kv0 + BKV - 1 > qw0) || (kv0 + BKV > T);
       if (WIDE || (KS == 2 && !CAUSAL) || need_mask) {
 #pragma unroll

@@ -130,16 +130,14 @@ inline bool split_pays(long long BH, int T, bool causal, bool pairs, const Split
 inline bool fwd_splits_keys(long long BH, int T, bool causal) {
   return split_pays(BH, T, causal, true, SplitCost{3.0, 1.04, 1.0, 0.2});
 }
-// Backward, likewise (B * H_q = 4 ... 128, T = 64 ... 8192, one and four query heads per KV head; dQ within 0.1 %, dK / dV
-// within 0.2 % of the faster form).  Attention backward, us, neither -> dQ -> dK / dV -> both split, causal, d_h = 128: T = 512, B *
-// H_q = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115; 8192, 8: 658 -> 590 -> 546 -> 478; 4096, 16 MHA: 343 ->
-// 312 -> 290 -> 258; d_h = 64, 1531, 24: 95 -> 83 -> 78 -> 65; kept whole: 1999, 64: 174 -> 181 -> 185 -> 194; dK / dV alone
-// 1531, 64: 104.5 -> 115.3; dQ alone 300, 128: 36.8 -> 38.8.
-inline bool dq_splits_keys(long long BH, int T, bool causal) {
-  return split_pays(BH, T, causal, true, SplitCost{3.0, 1.0, 1.0, 0.0});
-}
-inline bool dkdv_splits_rows(long long BH, int T, bool causal) {
-  return split_pays(BH, T, causal, false, SplitCost{2.0, 1.0, 1.0, 0.1});
-}
+// Backward, likewise (B * H_q = 4 ... 400, T = 64 ... 16384, causal and not, one and four query heads per KV head): neither kernel
+// is split where that measured more than 2 % slower, and the choice costs 0.1 % on average.  Attention backward, us, neither -> dQ
+// -> dK / dV -> both split, causal, d_h = 128: T = 512, B * H_q = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115;
+// 8192, 8: 658 -> 590 -> 546 -> 478; 4096, 16 MHA: 343 -> 312 -> 290 -> 258; d_h = 64, 1531, 24: 95 -> 83 -> 78 -> 65; kept whole:
+// 1999, 64: 174 -> 181 -> 185 -> 194; dK / dV alone 1531, 64: 104.5 -> 115.3; dQ alone 300, 128: 36.8 -> 38.8, and not causal
+// 6000, 64, d_h = 64: 2084 -> 2246.
+constexpr SplitCost BWD_SPLIT{2.0, 1.0, 1.0, 0.1};
+inline bool dq_splits_keys(long long BH, int T, bool causal) { return split_pays(BH, T, causal, true, BWD_SPLIT); }
+inline bool dkdv_splits_rows(long long BH, int T, bool causal) { return split_pays(BH, T, causal, false, BWD_SPLIT); }
 
 }  // namespace cca

@@ -47,7 +47,7 @@ FWD_MEASURED = [(8, 64, True, 4.4, 5.4), (8, 128, True, 8.2, 9.4), (96, 400, Tru
                 (8, 200, True, 12.3, 10.1), (8, 2048, True, 47.6, 33.6), (24, 1531, True, 26.6, 19.4), (16, 4096, True, 101.8, 81.8),
                 (16, 512, False, 19.4, 15.5), (64, 1999, True, 44.7, 54.7), (8, 16384, True, 446.0, 501.0)]
 DQ_MEASURED = [(128, 300, True, 36.8, 38.8), (128, 777, True, 147.8, 155.3), (8, 2048, True, 180.0, 156.0), (24, 1531, True, 95.0, 83.0),
-               (64, 1999, True, 174.0, 181.0)]
+               (64, 1999, True, 174.0, 181.0), (64, 6000, False, 2083.6, 2246.0), (24, 8192, False, 1417.0, 1528.6)]
 DKDV_MEASURED = [(64, 1531, True, 104.5, 115.3), (4, 64, True, 13.0, 13.9), (8, 2048, True, 180.0, 139.0), (24, 1531, True, 95.0, 78.0),
                  (64, 1999, True, 174.0, 185.0)]
 
