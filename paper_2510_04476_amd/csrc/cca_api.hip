@@ -98,8 +98,8 @@ static FwdLayout fwd_layout(const Dims &d) {
   const size_t rows = (size_t)d.rows();
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes, 256); return o; };
-  // (the transposed weights are only made when the matrix-core GEMM runs, which does not depend on B: see
-  // both_projections_mfma)
+  // (a transposed weight is only made when its projection runs on the matrix-core GEMM, which does not depend on B: see
+  // down_mfma, up_mfma)
   L.wt_down = take(d.bf16 ? (size_t)d.E * d.n_lat * 2 : 0);
   L.wt_out = take(d.bf16 ? (size_t)d.E * d.e_q * 2 : 0);
   L.pro = take(prologue_fused_scratch_bytes(d));
@@ -223,25 +223,25 @@ static cca_status run_prologue_bwd(const Dims &d, const cca_weights *w, const vo
   return e == hipSuccess ? CCA_OK : CCA_ERR_LAUNCH;
 }
 
-// Both projections of cca_forward on the matrix-core GEMM (then their weights are wanted K-contiguous).  The GEMM's
-// conditions on the row count are met or missed by every B alike only through M = B*T >= 1, so a buffer prepared
-// under one B serves any other.
-static bool both_projections_mfma(const Dims &d) {
-  return d.bf16 && gemm_mfma_supported(d.rows(), d.n_lat, d.E) && gemm_mfma_supported(d.rows(), d.E, d.e_q);
-}
+// Which projections of cca_forward run on the matrix-core GEMM (their weight is then wanted K-contiguous).  The GEMM's conditions
+// on the row count are met or missed by every B alike only through M = B*T >= 1, so a buffer prepared under one B serves any
+// other.
+static bool down_mfma(const Dims &d) { return d.bf16 && gemm_mfma_supported(d.rows(), d.n_lat, d.E); }
+static bool up_mfma(const Dims &d) { return d.bf16 && gemm_mfma_supported(d.rows(), d.E, d.e_q); }
 
-// Everything that depends on the weights only, into `to` (the layout's first three parts): both weight transposes when both
-// projections run on the MFMA GEMM, the folded filters and RoPE tables of the fused prologue, in one launch when both are
-// wanted (two took 3.7 us more of a 220 us training step over 2 x 512 tokens).
+// Everything that depends on the weights only, into `to` (the layout's first three parts): the transpose of each weight whose
+// projection runs on the MFMA GEMM, the folded filters and RoPE tables of the fused prologue, in one launch when both kinds
+// are wanted (two took 3.7 us more of a 220 us training step over 2 x 512 tokens).  Nothing of it is written again afterwards: a
+// prepared buffer may be shared by streams.
 static hipError_t derive_weights(const Dims &d, const cca_weights *w, char *to, const FwdLayout &L, hipStream_t s) {
   TransposePair pair{};
-  const bool both = both_projections_mfma(d), fused = !prologue_is_split_copy(d) && prologue_fused_supported(d);
-  if (both)
-    if (hipError_t e = make_transposes(w->w_down, to + L.wt_down, d.E, d.n_lat, w->w_out, to + L.wt_out, d.e_q, d.E, &pair);
-        e != hipSuccess)
-      return e;
-  if (fused) return prologue_fused_prepare(d, *w, to + L.pro, s, both ? &pair : nullptr);
-  return both ? transpose2_bf16(pair, s) : hipSuccess;
+  const bool down = down_mfma(d), up = up_mfma(d), fused = !prologue_is_split_copy(d) && prologue_fused_supported(d);
+  hipError_t e = hipSuccess;
+  if (down) e = make_transposes(w->w_down, to + L.wt_down, d.E, d.n_lat, up ? w->w_out : nullptr, to + L.wt_out, d.e_q, d.E, &pair);
+  else if (up) e = make_transposes(w->w_out, to + L.wt_out, d.e_q, d.E, nullptr, nullptr, 0, 0, &pair);
+  if (e != hipSuccess) return e;
+  if (fused) return prologue_fused_prepare(d, *w, to + L.pro, s, down || up ? &pair : nullptr);
+  return down || up ? transpose2_bf16(pair, s) : hipSuccess;
 }
 
 static cca_status check_grads(const cca_grads *g) {
@@ -476,12 +476,11 @@ cca_status cca_forward(const cca_config *cfg, const cca_weights *w, const void *
     if (reinterpret_cast<uintptr_t>(rnorm) & 3u) return CCA_ERR_ALIGN;
   }
   hipStream_t s = (hipStream_t)hip_stream;
-  // What depends on the weights only: taken from the caller's prepared buffer, else derived into the workspace.
+  // What depends on the weights only: taken from the caller's prepared buffer (read, never written), else derived into the workspace.
   char *pre = ws;
   if (w->prepared) pre = static_cast<char *>(const_cast<void *>(w->prepared));
   else if (derive_weights(d, w, ws, L, s) != hipSuccess) return CCA_ERR_LAUNCH;
-  const bool both = both_projections_mfma(d);
-  if (both && prologue_is_split_copy(d) && !(d.flags & CCA_V_SHIFT)) {
+  if (down_mfma(d) && up_mfma(d) && prologue_is_split_copy(d) && !(d.flags & CCA_V_SHIFT)) {
     // Plain MHA / GQA: q, k and v are column ranges of the latent rows, so the projection stores them itself, and the latent
     // row only where a caller keeps it (it is not read again in this pass).  T = 4096, 16 heads of 128: the copy
     // launch was 15.7 us; the pass goes from 255 to 236 us.
@@ -491,14 +490,14 @@ cca_status cca_forward(const cca_config *cfg, const cca_weights *w, const void *
         prologue_split_norms(d, rnorm, s) != hipSuccess)
       return CCA_ERR_LAUNCH;
   } else {
-    st = project(d, x, w->w_down, lat, d.rows(), d.n_lat, d.E, pre + L.wt_down, (size_t)d.E * d.n_lat * 2, s, both);
+    st = project(d, x, w->w_down, lat, d.rows(), d.n_lat, d.E, pre + L.wt_down, (size_t)d.E * d.n_lat * 2, s, true);
     if (st != CCA_OK) return st;
     st = run_prologue(d, w, lat, q, k, v, rnorm, pre + L.pro, L.lat - L.pro, s, true);
     if (st != CCA_OK) return st;
   }
   st = run_attention(d, q, k, v, o, o_lo, lse, w->temp, s);
   if (st != CCA_OK) return st;
-  return project(d, o, w->w_out, out, d.rows(), d.E, d.e_q, pre + L.wt_out, (size_t)d.E * d.e_q * 2, s, both);
+  return project(d, o, w->w_out, out, d.rows(), d.E, d.e_q, pre + L.wt_out, (size_t)d.E * d.e_q * 2, s, true);
 }
 
 cca_status cca_decode_workspace_size(const cca_config *cfg, size_t *bytes, int32_t *ring_rows) {

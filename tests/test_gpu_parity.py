@@ -1,6 +1,7 @@
 """GPU parity: the HIP path (through the C ABI) against the fp64 oracle on the
 same seeded inputs.  Tolerances are the spec ones: bf16 rel-L2 <= 1e-2
 and max-abs <= 2e-2 on `out`; fp32 <= 1e-5."""
+import ctypes as C
 import sys
 
 import numpy as np
@@ -475,3 +476,27 @@ def test_prepared_weights_give_identical_results(i):
     for name in ("lat", "q", "k", "v", "o", "lse", "rnorm"):
         assert torch.equal(getattr(s_a, name), getattr(s_b, name)), name
     say(check_out(to_np(out_b), oracle_forward(w, inp)["out"], w["dtype"]))
+
+
+@pytest.mark.parametrize("E,Hq,Hk,dh", [(512, 1, 1, 40), (520, 1, 1, 64), (512, 2, 1, 128), (264, 3, 1, 40)])
+def test_forward_leaves_the_prepared_buffer_alone(E, Hq, Hk, dh):
+    """Streams may share a prepared buffer: a forward only reads it, also where one projection alone runs on the matrix-core
+    GEMM (the contraction E or H_q d_h is a multiple of 64 and the other is not)."""
+    w = dict(B=2, T=67, E=E, Hq=Hq, Hk=Hk, dh=dh, k_seq=2, k_ch=2, dtype="bf16", paper_flags=True)
+    say("prepared buffer", w)
+    inp = make_inputs(w, seed=31, conv_visible=True)
+    cfg = P.config_from_workload(w)
+    x, wt = P.weights_to_device(cfg, inp)
+    buf = torch.full((P.cca_prepared_size(cfg),), 0xA5, dtype=torch.uint8, device=x.device)
+    cc, cw = cfg.c(), wt.c()
+    assert P.load_library().cca_prepare(C.byref(cc), C.byref(cw), buf.data_ptr(), buf.numel(),
+                                        torch.cuda.current_stream().cuda_stream) == 0
+    before = buf.clone()
+    wp = P.CCAWeights(w_down=wt.w_down, w_out=wt.w_out, w_conv_seq=wt.w_conv_seq, w_conv_ch=wt.w_conv_ch, temp=wt.temp, prepared=buf)
+    out = P.cca_forward(cfg, wp, x)
+    again = P.cca_forward(cfg, wp, x)
+    own = P.cca_forward(cfg, wt, x)
+    torch.cuda.synchronize()
+    assert torch.equal(buf, before)
+    assert torch.equal(out, again) and torch.equal(out, own)
+    say(check_out(to_np(out), oracle_forward(w, inp)["out"], "bf16"))
