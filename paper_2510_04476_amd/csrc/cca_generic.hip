@@ -8,22 +8,24 @@ namespace cca {
 // ---------------------------------------------------------------------------
 // GEMM: C (M,N) = op(A) op(B), op(A)[m][k] = TA ? A[k*lda + m] : A[m*lda + k], op(B)[k][n] = TB ? B[n*ldb + k] : B[k*ldb + n].
 // Workgroup = one 32 x 32 tile of C, the contraction dealt to its 8 wavefronts 8 terms at a time and their sums added
-// through LDS in order: these products are small (the fp32 configuration, odd bf16 shapes), so a walk along all of K by one
-// wavefront is what they would wait for.  K is a multiple of 4 where an operand is stored along it; lda, ldb likewise.
-// fp32, us, 64 x 64 tiles through LDS on the vector ALU -> this: 1000 x 192 over K = 256 31 -> 5.2, 256 x 192 over K = 1000
-// tokens 132 -> 12.1.
+// through LDS in order: these products are mostly small (the fp32 configuration, odd bf16 shapes), so a walk along all of K by
+// one wavefront is what they would wait for.  K is a multiple of 4 where an operand is stored along it; lda, ldb likewise.
+// us, 64 x 64 tiles through LDS on the vector ALU -> this, fp32: 1000 x 192 over K = 256 31 -> 5.2, 256 x 192 over K = 1000
+// tokens 132 -> 12.1, 4096 x 1536 over 2048 580 -> 341, 16384 x 1536 over 2048 2087 -> 1356 (there the operand loads, 32 rows
+// apart, bound it); bf16, 16384 x 4056 over 2056 5250 -> 3800.
 // ---------------------------------------------------------------------------
 constexpr int GG_NT = 512, GG_WAVES = GG_NT / 64;
+constexpr long long GG_GRID = 1ll << 22;  // tiles of a launch, which takes fewer than 2^32 threads in one dimension
 
 template <typename T, bool TA, bool TB>
 __global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict__ A, long long lda, const T *__restrict__ Bm,
                                                             long long ldb, T *__restrict__ C, long long ldc, long long M, int N,
-                                                            long long K) {
+                                                            long long K, unsigned tile0) {
   __shared__ float red[GG_WAVES][32][33];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
-  const int tiles_n = (N + 31) / 32;
-  const long long m0 = (long long)(blockIdx.x / tiles_n) * 32;
-  const int n0 = blockIdx.x % tiles_n * 32;
+  const unsigned tiles_n = (N + 31) / 32, tile = tile0 + blockIdx.x;
+  const long long m0 = (long long)(tile / tiles_n) * 32;
+  const int n0 = tile % tiles_n * 32;
   const long long m = m0 + l32 < M ? m0 + l32 : M - 1;  // rows and columns past the edge feed outputs that are not stored
   const int n = n0 + l32 < N ? n0 + l32 : N - 1;
   gen_f32x16 acc = zero16();
@@ -70,14 +72,20 @@ __global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict
 template <typename T>
 static hipError_t gemm_generic_t(const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb, void *C,
                                  long long ldc, long long M, int N, long long K, hipStream_t s) {
-  const unsigned grid = (unsigned)((M + 31) / 32 * ((N + 31) / 32));
-#define GO(TA, TB) gemm_generic_kernel<T, TA, TB><<<grid, GG_NT, 0, s>>>((const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K)
-  if (ta && tb) GO(true, true);
-  else if (ta) GO(true, false);
-  else if (tb) GO(false, true);
-  else GO(false, false);
+  const long long tiles = (M + 31) / 32 * ((N + 31) / 32);
+  if (tiles > UINT32_MAX) return hipErrorInvalidValue;  // (2^42 outputs)
+  for (long long t = 0; t < tiles; t += GG_GRID) {  // one launch below 2^32 outputs; a second grid dimension cost 0.2 of 2.8 us
+    const unsigned grid = (unsigned)(tiles - t < GG_GRID ? tiles - t : GG_GRID);
+#define GO(TA, TB)                                                                                                          \
+  gemm_generic_kernel<T, TA, TB><<<grid, GG_NT, 0, s>>>((const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K, (unsigned)t)
+    if (ta && tb) GO(true, true);
+    else if (ta) GO(true, false);
+    else if (tb) GO(false, true);
+    else GO(false, false);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
 #undef GO
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t gemm_generic_ex(bool bf16, const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb,

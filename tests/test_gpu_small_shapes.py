@@ -229,6 +229,22 @@ def test_generic_kernels_fp32(i, causal):
         assert err <= 1e-5 * float(np.linalg.norm(r)) + 1e-6, (name, err, float(np.linalg.norm(r)))
 
 
+def test_generic_product_beyond_2_to_33_outputs():
+    """A product of more 32 x 32 tiles than one grid dimension holds threads for (2^23 tiles x 512), 17 GB of bf16: every tile
+    is there, and rows from all over are the product."""
+    M, K, N = (1 << 20) + 33, 8, 8200
+    say("generic product", M, K, N)
+    cfg = P.CCAConfig(B=1, T=M, d_model=N, n_q_heads=1, n_kv_heads=1, head_dim=K)
+    o, w = rnd(1, M, K, seed=1), rnd(K, N, seed=2)
+    out = torch.full((1, M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    P.cca_up_project(cfg, o, w, out)
+    torch.cuda.synchronize()
+    for first in range(0, M, 1 << 17):
+        assert not bool(out[0, first:first + (1 << 17)].isnan().any()), first
+    rows = torch.tensor([0, 31, 32, M // 2, M - 34, M - 2, M - 1] + [(i * 2654435761) % M for i in range(200)], device="cuda")
+    check_product(out[0, rows], o[0, rows].double() @ w.double(), K)
+
+
 def test_generic_attention_hides_masked_infinities():
     """fp32, causal: a NaN or infinity in a later token's key, value or query must not reach earlier rows or their gradients."""
     T, cut = 75, 41
