@@ -84,6 +84,12 @@ struct Raw8<bf16_t> {
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   u4 v;
   __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const u4 *>(p); }
+  __device__ __forceinline__ Raw8 keep(bool on) const {  // zeros where not `on`
+    Raw8 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[i] = on ? v[i] : 0u;
+    return r;
+  }
   __device__ __forceinline__ float get(int e) const {
     const uint32_t w = v[e >> 1];
     return __uint_as_float((e & 1) ? w & 0xffff0000u : w << 16);
@@ -96,6 +102,12 @@ struct Raw8<float> {
   __device__ __forceinline__ void load(const float *p) {
     a = *reinterpret_cast<const f4 *>(p);
     b = *reinterpret_cast<const f4 *>(p + 4);
+  }
+  __device__ __forceinline__ Raw8 keep(bool on) const {
+    Raw8 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.a[i] = on ? a[i] : 0.f, r.b[i] = on ? b[i] : 0.f;
+    return r;
   }
   __device__ __forceinline__ float get(int e) const { return e < 4 ? a[e & 3] : b[e & 3]; }
 };
@@ -201,7 +213,7 @@ __global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__re
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
       const int c = j * LPO + lo;
-      w[j].load(wp + min(c, nch - 1) * 8);  // chunks past the row repeat its last one and meet zeros
+      w[j].load(wp + min(c, nch - 1) * 8);  // chunks past the row repeat its last one; dropped below
     }
   };
   const bool conv = a.flags & CCA_CONV_CH;
@@ -291,9 +303,11 @@ __global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__re
     auto pass = [&](int o, const Raw8<T> (&w)[CH]) {
       float y = 0.f;
 #pragma unroll
-      for (int j = 0; j < CH; ++j)
+      for (int j = 0; j < CH; ++j) {
+        const Raw8<T> wj = w[j].keep(j * LPO + lo < nch);  // (a weight may be infinite: zero times it would not be zero)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) y = fmaf(w[j].get(e), yv[j][e], y);
+        for (int e = 0; e < 8; ++e) y = fmaf(wj.get(e), yv[j][e], y);
+      }
       y = dpp_add<0xB1>(y);   // quad_perm [1,0,3,2]
       y = dpp_add<0x4E>(y);   // quad_perm [2,3,0,1]
       y = dpp_add<0x141>(y);  // row_half_mirror: 8 lanes hold their sum

@@ -177,6 +177,34 @@ def test_decode_projections_and_filters(i):
     say(check_tap(to_np(state.v_cache), ref["v"], "bf16", "v_cache"))
 
 
+@pytest.mark.parametrize("dtype", [P.CCA_BF16, P.CCA_F32])
+@pytest.mark.parametrize("dh,k_ch", [(64, 3), (40, 2), (64, 2), (256, 4)])
+def test_decode_infinite_filter_weight(dh, k_ch, dtype):
+    """An infinity in the last weight of a filter row makes that output infinite (not NaN, whatever the row's length leaves
+    of the lanes that share it) and no other."""
+    say("infinite weight", dh, k_ch, dtype)
+    cfg = P.CCAConfig(B=2, T=9, d_model=128 if dh < 256 else 512, n_q_heads=1, n_kv_heads=1, head_dim=dh, k_seq=1, k_ch=k_ch, dtype=dtype,
+                      flags=P.CCA_CAUSAL | P.CCA_CONV_CH)
+    dt = cfg.torch_dtype
+    w = P.CCAWeights(w_down=rnd(cfg.d_model, cfg.n_lat, seed=1, scale=0.1, dtype=dt), w_out=rnd(cfg.e_q, cfg.d_model, seed=2, dtype=dt),
+                     w_conv_ch=rnd(2, dh, dh, k_ch, seed=3, dtype=dt))
+    x = rnd(4, 2, cfg.d_model, seed=4, dtype=dt)
+
+    def cache():
+        st = P.CCADecodeState.allocate(cfg, "cuda")
+        for t in range(4):
+            P.cca_decode_step(cfg, w, x[t], st, t)
+        return st.k_cache[:, :4, 0].float()
+
+    clean = cache()
+    w.w_conv_ch[1, 5, dh - 1, k_ch - 1] = float("inf")
+    dirty = cache()
+    torch.cuda.synchronize()
+    assert bool(dirty[..., 5].isinf().all())
+    keep = [c for c in range(dh) if c != 5]
+    assert bool(clean.isfinite().all()) and torch.equal(dirty[..., keep], clean[..., keep])
+
+
 @pytest.mark.parametrize("Hq,Hk,dh", [(4, 2, 64), (4, 1, 128), (2, 2, 256)])
 def test_decode_split_edges(Hq, Hk, dh):
     """Positions around the edges of the splits of the key range (units of 64, 128 and 256 keys)."""
