@@ -429,11 +429,11 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(DecArgs a, 
     for (int r = 0; r < R_MAX; ++r) {
       float mx = live ? s[r] : -INFINITY;
       for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      const float mn = fmaxf(m[r], mx);  // finite: the block holds at least one live key
-      const float p = live ? exp2f(s[r] - mn) : 0.f;
+      const float mn = fmaxf(m[r], mx), ms = mn == -INFINITY ? 0.f : mn;  // every score so far may be -inf
+      const float p = live ? exp2f(s[r] - ms) : 0.f;
       float sum = p;
       for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-      alpha[r] = exp2f(m[r] - mn);  // 0 on the first block
+      alpha[r] = exp2f(m[r] - ms);  // 0 on the first block
       l[r] = l[r] * alpha[r] + sum;
       m[r] = mn;
       ps[lane * R_MAX + r] = p;

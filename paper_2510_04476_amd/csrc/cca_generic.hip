@@ -286,12 +286,13 @@ __global__ __launch_bounds__(GA_NT) void attention_generic_kernel(const T *__res
       w[r] = key < Tn && (!causal || key <= t) ? s[r] : -INFINITY;
       mx = fmaxf(mx, w[r]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32));  // finite: a tile's first key is visible to every row of the block
-    const float corr = expf(m - mx);     // 0 on the first tile
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float ref = mx == -INFINITY ? 0.f : mx;  // a row whose scores so far are all -inf has no maximum yet
+    const float corr = expf(m - ref);              // 0 on the first tile
     l *= corr;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      w[r] = expf(w[r] - mx);
+      w[r] = expf(w[r] - ref);
       l += w[r];
     }
 #pragma unroll

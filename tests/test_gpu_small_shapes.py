@@ -153,6 +153,64 @@ def test_attention_keys_masked_by_infinite_scores(dh, causal, live):
         assert float((lse[0, h, first:].double() - torch.logsumexp(s, -1)).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
 
 
+@pytest.mark.parametrize("live", [(0, 40), (70, 140), (129, 300)])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh,dtype", [(32, P.CCA_F32), (200, P.CCA_F32), (40, P.CCA_BF16)])
+def test_generic_attention_keys_masked_by_infinite_scores(dh, dtype, causal, live):
+    """The same through the shape-generic kernel: fp32 sums of up to T terms each, bf16 results rounded once."""
+    T, Hq, lo, hi = 300, 2, *live
+    say("infinite scores, generic", dh, dtype, causal, live)
+    cfg = P.CCAConfig(B=1, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, dtype=dtype, flags=P.CCA_CAUSAL if causal else 0)
+    q, k, v = (rnd(1, T, Hq, dh, seed=s, dtype=cfg.torch_dtype) for s in (1, 2, 3))
+    q[..., 5] = 1.0
+    k[:, :lo, :, 5], k[:, hi:, :, 5] = float("-inf"), float("-inf")
+    o, lse = P.cca_attention(cfg, q, k, v, want_lse=True)
+    torch.cuda.synchronize()
+    first = lo if causal else 0
+    for h in range(Hq):
+        s = q[0, first:, h].double() @ k[0, lo:hi, h].double().t().contiguous() / dh ** 0.5
+        if causal:
+            s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1)[first:, lo:hi], float("-inf"))
+        ref = torch.softmax(s, -1) @ v[0, lo:hi, h].double()
+        got = o[0, first:, h * dh:(h + 1) * dh].double()
+        assert bool(got.isfinite().all())
+        bound = (2.0 ** -8 if dtype == P.CCA_BF16 else 0.0) * ref.abs() + 1e-5 * float(ref.abs().max())
+        assert float(((got - ref).abs() / bound).max()) <= 1.0
+        assert float((lse[0, h, first:].double() - torch.logsumexp(s, -1)).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dh,Hk,dtype", [(64, 2, P.CCA_BF16), (128, 1, P.CCA_BF16), (256, 1, P.CCA_BF16), (40, 1, P.CCA_BF16), (64, 1, P.CCA_F32)])
+def test_decode_keys_masked_by_infinite_scores(dh, Hk, dtype):
+    """Whole blocks and splits of the cache at -inf: the step equals a step over the live keys alone (the first `live` ones and
+    the new token's), whose sums run in another order."""
+    T, live, Hq = 900, 37, 2
+    say("infinite scores, decode", dh, Hk, dtype)
+    mk = lambda cap: P.CCAConfig(B=1, T=cap, d_model=512, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, k_seq=1, k_ch=1, dtype=dtype,
+                                 flags=P.CCA_FLAGS_MHA)
+    cfg, few = mk(T), mk(live + 1)
+    w = P.CCAWeights(w_down=rnd(512, cfg.n_lat, seed=1, scale=0.02, dtype=cfg.torch_dtype),
+                     w_out=rnd(cfg.e_q, 512, seed=2, scale=0.05, dtype=cfg.torch_dtype))
+    for h in range(Hq):  # every query reads channel 5 with a positive weight
+        w.w_down[:, h * dh + 5] = 0.01
+    x = rnd(1, 512, seed=3, dtype=cfg.torch_dtype).abs()
+    k, v = rnd(1, T, Hk, dh, seed=4, dtype=cfg.torch_dtype), rnd(1, T, Hk, dh, seed=5, dtype=cfg.torch_dtype)
+
+    def step(c, at, keep):
+        st = P.CCADecodeState.allocate(c, "cuda")
+        st.k_cache.copy_(k[:, :1].expand_as(st.k_cache)), st.v_cache.copy_(v[:, :1].expand_as(st.v_cache))
+        st.k_cache[..., 5] = float("-inf")
+        st.k_cache[:, keep], st.v_cache[:, keep] = k[:, :live], v[:, :live]
+        return P.cca_decode_step(c, w, x, st, at)
+
+    for first in (0, 300, T - 1 - live):
+        out = step(cfg, T - 1, slice(first, first + live))
+        ref = step(few, live, slice(0, live)).double()
+        torch.cuda.synchronize()
+        assert bool(ref.isfinite().all()) and bool(out.isfinite().all()), first
+        tol = 2.0 ** -7 if dtype == P.CCA_BF16 else 1e-5
+        assert float((out.double() - ref).norm()) <= tol * float(ref.norm()), first
+
+
 # the decode step's projections (several passes through LDS, K slices of the down-projection, lengths that are not whole
 # groups) and filter layouts: widths 256 and 64 with up to 4 + 4 taps, 5 query heads per KV head
 DECODE_CASES = [dict(B=9, T=5, E=4104, Hq=4, Hk=2, dh=64, k_seq=2, k_ch=2), dict(B=2, T=9, E=2056, Hq=4, Hk=2, dh=256, k_seq=4, k_ch=4),
