@@ -480,6 +480,86 @@ constexpr int ST_NT = 256, ST_WAVES = ST_NT / 64, ST_RING = 4;
 constexpr int stream_rows(int D) { return (32 + D - 1 + 1) / 2 * 2; }  // staged rows of a wavefront, whole load instructions
 constexpr size_t stream_lds(int D) { return (size_t)ST_RING * SLAB_BYTES + (size_t)ST_WAVES * stream_rows(D) * 512; }
 
+// ---- pieces of the two d_h = 256 kernels
+// Value role: 4 x NTH chunks of 16 bytes from `first` on; the shifted half of the channels one token later (adjoint: earlier).
+template <bool BWD, int NTH>
+__device__ __forceinline__ void value_role(const FusedArgs &a, const bf16_t *__restrict__ vsrc, bf16_t *__restrict__ v, long long first) {
+  const int cpr = a.e_kv / 8;
+  const long long total = a.rows * cpr;
+  for (int it = 0; it < 4; ++it) {
+    const long long id = first + it * NTH + threadIdx.x;
+    if (id >= total) break;
+    const long long row = id / cpr;
+    const int ch = (int)(id % cpr) * 8;
+    const int t = (int)(row % a.T);
+    u32x4 val = {0, 0, 0, 0};
+    const bool shifted = (a.flags & CCA_V_SHIFT) && ch >= a.v_half;
+    const bool live = !shifted || (BWD ? t + 1 < a.T : t > 0);
+    if (live) val = *reinterpret_cast<const u32x4 *>(vsrc + (row + (shifted ? (BWD ? 1 : -1) : 0)) * a.vsrc_stride + ch);
+    *reinterpret_cast<u32x4 *>(v + row * a.vdst_stride + ch) = val;
+  }
+}
+
+// The workgroup's head and its streams
+struct StreamHead {
+  bool is_q;
+  int bid, head, g, ch0;
+  __device__ __forceinline__ explicit StreamHead(const FusedArgs &a) {
+    is_q = (int)blockIdx.x >= a.n_k_blocks;
+    bid = is_q ? (int)blockIdx.x - a.n_k_blocks : (int)blockIdx.x;
+    head = is_q ? bid % a.Hq : a.Hq + bid % a.Hk;
+    g = is_q ? head / a.R : head - a.Hq;
+    ch0 = is_q ? head * 256 : a.e_q + g * 256;
+    bid /= is_q ? a.Hq : a.Hk;  // token block
+  }
+};
+
+// Per token: norm, temperature, RoPE (lane (l32, half): channels 32*nt + 8*rg + 4*half + e)
+__device__ __forceinline__ void norm_and_rope_256(f32x16 (&acc)[8], const FusedArgs &a, int head, float beta, long long row, int tpos,
+                                                  int half, const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB,
+                                                  float *__restrict__ rnorm) {
+  constexpr int DH = 256, NTL = DH / 32;
+  const int NH = a.Hq + a.Hk;
+  if (a.flags & CCA_QK_NORM) {
+    float ssq = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ssq = fmaf(acc[nt][r], acc[nt][r], ssq);
+    ssq += __shfl_xor(ssq, 32);
+    const float mul = sqrtf((float)DH) / sqrtf(ssq + a.norm_eps) * beta;
+#pragma unroll
+    for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[nt][r] *= mul;
+    if (rnorm && half == 0 && row < a.rows) rnorm[row * NH + head] = mul;
+  } else if (rnorm && half == 0 && row < a.rows) {
+    rnorm[row * NH + head] = 1.f;
+  }
+  if (a.flags & CCA_ROPE) {
+    const int thi = tpos >> 7, tlo = tpos & 127;
+#pragma unroll
+    for (int nt = 0; nt < NTL / 2; ++nt)
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg) {
+        const int i0 = nt * 32 + rg * 8 + half * 4;  // 4 consecutive pair indices
+        const f32x4 *pa = reinterpret_cast<const f32x4 *>(ropeA + thi * (DH / 2) + i0);
+        const f32x4 *pb = reinterpret_cast<const f32x4 *>(ropeB + ((i0 >> 2) * 128 + tlo) * 4);
+        const f32x4 a01 = pa[0], a23 = pa[1], b01 = pb[0], b23 = pb[1];
+        const float ca[4] = {a01.x, a01.z, a23.x, a23.z}, sa[4] = {a01.y, a01.w, a23.y, a23.w};
+        const float cb[4] = {b01.x, b01.z, b23.x, b23.z}, sb[4] = {b01.y, b01.w, b23.y, b23.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float cs = ca[e] * cb[e] - sa[e] * sb[e];
+          const float sn = sa[e] * cb[e] + ca[e] * sb[e];
+          const float x1 = acc[nt][rg * 4 + e], x2 = acc[nt + NTL / 2][rg * 4 + e];
+          acc[nt][rg * 4 + e] = x1 * cs - x2 * sn;
+          acc[nt + NTL / 2][rg * 4 + e] = x2 * cs + x1 * sn;
+        }
+      }
+  }
+}
+
 // (a body inlined with restrict arguments and dynamic LDS: otherwise the compiler makes LDS reads wait for the loads into
 // LDS in flight)
 template <int D, bool BWD>
@@ -497,37 +577,19 @@ __device__ __forceinline__ void prologue_stream_body(
   const int l32 = lane & 31, half = lane >> 5;
 
   if ((int)blockIdx.x >= a.n_conv_blocks) {
-    // ---- value-shift role (as in prologue_fused_kernel)
-    const int cpr = a.e_kv / 8;
-    const long long total = a.rows * cpr;
-    const long long first = ((long long)blockIdx.x - a.n_conv_blocks) * (ST_NT * 4);
-    for (int it = 0; it < 4; ++it) {
-      const long long id = first + it * ST_NT + tid;
-      if (id >= total) break;
-      const long long row = id / cpr;
-      const int ch = (int)(id % cpr) * 8;
-      const int t = (int)(row % a.T);
-      u32x4 val = {0, 0, 0, 0};
-      const bool shifted = (a.flags & CCA_V_SHIFT) && ch >= a.v_half;
-      const bool live = !shifted || (BWD ? t + 1 < a.T : t > 0);
-      if (live) val = *reinterpret_cast<const u32x4 *>(vsrc + (row + (shifted ? (BWD ? 1 : -1) : 0)) * a.vsrc_stride + ch);
-      *reinterpret_cast<u32x4 *>(v + row * a.vdst_stride + ch) = val;
-    }
+    value_role<BWD, ST_NT>(a, vsrc, v, ((long long)blockIdx.x - a.n_conv_blocks) * (ST_NT * 4));
     return;
   }
 
-  const int NH = a.Hq + a.Hk;
-  const bool is_q = (int)blockIdx.x >= a.n_k_blocks;
-  const int bid = is_q ? (int)blockIdx.x - a.n_k_blocks : (int)blockIdx.x;
-  const int head = is_q ? bid % a.Hq : a.Hq + bid % a.Hk;
-  const int g = is_q ? head / a.R : head - a.Hq;
-  const int ch0 = is_q ? head * DH : a.e_q + g * DH;
+  const StreamHead hd(a);
+  const bool is_q = hd.is_q;
+  const int g = hd.g, ch0 = hd.ch0;
   const float beta = (!is_q && (a.flags & CCA_KEY_TEMP)) ? expf(temp[g]) : 1.f;
-  bf16_t *dst = is_q ? q + head * DH : k + g * DH;
+  bf16_t *dst = is_q ? q + hd.head * DH : k + g * DH;
   const int dst_stride = is_q ? a.q_stride : a.k_stride;
 
   // this wavefront's 32 tokens (a wavefront past the end keeps walking the slabs: it loads filter chunks too)
-  const long long trow0 = (long long)(bid / (is_q ? a.Hq : a.Hk)) * (ST_WAVES * 32) + wave * 32;
+  const long long trow0 = (long long)hd.bid * (ST_WAVES * 32) + wave * 32;
   const long long row = trow0 + l32;
   const long long rowc = row < a.rows ? row : a.rows - 1;
   const int tpos = (int)(rowc % a.T);
@@ -547,7 +609,7 @@ __device__ __forceinline__ void prologue_stream_body(
   auto row_frag = [&](const unsigned char *from, int j, int kk) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(from + j * ROWB + (((2 * kk + half) ^ (j & 15)) * 16)));
   };
-  const u32x4 *const wsrc = wc + (long long)head * NSLAB * (SLAB_BYTES / 16) + lane;
+  const u32x4 *const wsrc = wc + (long long)hd.head * NSLAB * (SLAB_BYTES / 16) + lane;
   auto fetch_slab = [&](int s_) {
 #pragma unroll
     for (int u = 0; u < SLAB_INSTR; ++u) {
@@ -653,45 +715,7 @@ __device__ __forceinline__ void prologue_stream_body(
     }
   }
 
-  // ---- per token: norm, temperature, RoPE (lane (l32, half): channels 32*nt + 8*rg + 4*half + e)
-  if (a.flags & CCA_QK_NORM) {
-    float ssq = 0.f;
-#pragma unroll
-    for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) ssq = fmaf(acc[nt][r], acc[nt][r], ssq);
-    ssq += __shfl_xor(ssq, 32);
-    const float mul = sqrtf((float)DH) / sqrtf(ssq + a.norm_eps) * beta;
-#pragma unroll
-    for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[nt][r] *= mul;
-    if (rnorm && half == 0 && row < a.rows) rnorm[row * NH + head] = mul;
-  } else if (rnorm && half == 0 && row < a.rows) {
-    rnorm[row * NH + head] = 1.f;
-  }
-  if (a.flags & CCA_ROPE) {
-    const int thi = tpos >> 7, tlo = tpos & 127;
-#pragma unroll
-    for (int nt = 0; nt < NTL / 2; ++nt)
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int i0 = nt * 32 + rg * 8 + half * 4;  // 4 consecutive pair indices
-        const f32x4 *pa = reinterpret_cast<const f32x4 *>(ropeA + thi * (DH / 2) + i0);
-        const f32x4 *pb = reinterpret_cast<const f32x4 *>(ropeB + ((i0 >> 2) * 128 + tlo) * 4);
-        const f32x4 a01 = pa[0], a23 = pa[1], b01 = pb[0], b23 = pb[1];
-        const float ca[4] = {a01.x, a01.z, a23.x, a23.z}, sa[4] = {a01.y, a01.w, a23.y, a23.w};
-        const float cb[4] = {b01.x, b01.z, b23.x, b23.z}, sb[4] = {b01.y, b01.w, b23.y, b23.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float cs = ca[e] * cb[e] - sa[e] * sb[e];
-          const float sn = sa[e] * cb[e] + ca[e] * sb[e];
-          const float x1 = acc[nt][rg * 4 + e], x2 = acc[nt + NTL / 2][rg * 4 + e];
-          acc[nt][rg * 4 + e] = x1 * cs - x2 * sn;
-          acc[nt + NTL / 2][rg * 4 + e] = x2 * cs + x1 * sn;
-        }
-      }
-  }
+  norm_and_rope_256(acc, a, hd.head, beta, row, tpos, half, ropeA, ropeB, rnorm);
   // ---- round once to bf16; through this wavefront's staging rows (16-byte chunk c of row r at c ^ r), out as whole rows
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows' last readers are done
 #pragma unroll
@@ -721,6 +745,158 @@ __global__ __launch_bounds__(ST_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm) {
   extern __shared__ __attribute__((aligned(16))) unsigned char stream_smem[];
   prologue_stream_body<D, BWD>(a, lat, vsrc, wc, ropeA, ropeB, temp, q, k, v, rnorm, stream_smem);
+}
+
+// ---------------------------------------------------------------------------
+// The form for grids of several rounds: 256 tokens per workgroup, 8 wavefronts x 32 tokens, two per SIMD.  Each filter byte
+// that comes into LDS serves twice as many tokens, and a wavefront's waits hide under its SIMD's other one; there is no room
+// for staged token rows, so their fragments come straight from the latent rows, and the filter goes through registers into two
+// buffers of two slabs (64 input channels).  Bound by the filter reads from LDS and the waits between barriers: 16384 tokens, 8 / 8
+// heads 225 us against 261 for the kernel above (6000 tokens, 4 / 1 heads: 48 against 29.5; the rule is stream_takes_256).
+// ---------------------------------------------------------------------------
+template <int D, bool BWD>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void prologue_stream_long_kernel(
+    FusedArgs a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
+    const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB, const float *__restrict__ temp,
+    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm) {
+  constexpr int DH = 256, NTL = DH / 32;
+  constexpr int KC = 2 * SLAB_K, KCK = KC / 16;  // input channels per step, MFMA k-steps per step
+  constexpr int NCH = DH / KC, NSTEP = D * NCH, STEP = 2 * SLAB_BYTES;
+  constexpr int W_PER_THREAD = STEP / 16 / NT;  // 16-byte chunks of a step per thread
+  constexpr int SROW = KC * 2 + 16, BUF = DH * SROW;  // padded row in LDS: conflict-free 16-byte reads down a column of rows
+  static_assert(W_PER_THREAD == 4 && NT * 4 == 2 * DH * 4, "two chunks of each slab per thread, 128 rows apart");
+  __shared__ __attribute__((aligned(16))) unsigned char sW[2 * BUF];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, half = lane >> 5;
+  if ((int)blockIdx.x >= a.n_conv_blocks) {
+    value_role<BWD, NT>(a, vsrc, v, ((long long)blockIdx.x - a.n_conv_blocks) * (NT * 4));
+    return;
+  }
+  const StreamHead hd(a);
+  const bool is_q = hd.is_q;
+  const float beta = (!is_q && (a.flags & CCA_KEY_TEMP)) ? expf(temp[hd.g]) : 1.f;
+
+  // qk-mean weights as identity fragments (see prologue_fused_kernel); the other stream's are made after the
+  // convolution, when fewer registers are live
+  const bool mean = a.flags & CCA_QK_MEAN;
+  auto identity_frag = [&](bf16_t wbits, int j) {
+    const bool on = ((l32 >> 4) == j) && (((l32 >> 3) & 1) == half);
+    u32x4 w = {0, 0, 0, 0};
+    const int e = l32 & 7;
+    if (on) w[e >> 1] = (uint32_t)wbits << ((e & 1) * 16);
+    return __builtin_bit_cast(bf16x8, w);
+  };
+  bf16x8 id_half[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) id_half[j] = identity_frag(f32_to_bf16(0.5f), j);
+
+  // this wavefront's 32 tokens (a wavefront past the end keeps walking the slabs: it stages filter chunks too)
+  const long long row = (long long)hd.bid * 256 + wave * 32 + l32;
+  const long long rowc = row < a.rows ? row : a.rows - 1;
+  const int tpos = (int)(rowc % a.T);
+
+  // step s = (tap s / NCH, channels (s % NCH) * 64 ...): two slabs, one after the other in memory and in LDS
+  const u32x4 *const wsrc = wc + (long long)hd.head * NSTEP * (STEP / 16) + tid;
+  // chunk tid of a slab (slab_elem): row 2 * (tid / 8) + u / 4, chunk u mod 4 of it, with u = tid mod 8 ^ (tid / 16) mod 4
+  const int w_u = (tid & 7) ^ ((tid >> 4) & 3), w_to = (2 * (tid >> 3) + (w_u >> 2)) * SROW + (w_u & 3) * 16;
+  u32x4 wreg[W_PER_THREAD];
+  auto load_step = [&](int s_) {
+#pragma unroll
+    for (int i = 0; i < W_PER_THREAD; ++i) wreg[i] = wsrc[(long long)s_ * (STEP / 16) + i * NT];
+  };
+  auto store_step = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < W_PER_THREAD; ++i)
+      *reinterpret_cast<u32x4 *>(sW + buf * BUF + w_to + (i & 1) * (DH / 2) * SROW + (i >> 1) * SLAB_K * 2) = wreg[i];
+  };
+
+  f32x16 acc[NTL];
+#pragma unroll
+  for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
+
+  load_step(0);
+  store_step(0);
+#pragma unroll  // tap and channel group must be compile-time: they pick accumulator tiles
+  for (int s_ = 0; s_ < NSTEP; ++s_) {
+    const int d = s_ / NCH, c = s_ % NCH, back = D - 1 - d;
+    if (s_ + 1 < NSTEP) load_step(s_ + 1);
+    // token operands: row t - (D-1-d) (adjoint: t + (D-1-d)), channels c*64 .. c*64+63; rows outside the sequence are zero
+    bf16x8 uf[KCK];
+    {
+      long long src_row = BWD ? rowc + back : rowc - back;
+      src_row = src_row < 0 ? 0 : (src_row > a.rows - 1 ? a.rows - 1 : src_row);
+      const bf16_t *p = lat + src_row * a.src_stride + hd.ch0 + c * KC + half * 8;
+#pragma unroll
+      for (int kk = 0; kk < KCK; ++kk) {
+        u32x4 raw = *reinterpret_cast<const u32x4 *>(p + kk * 16);
+        if (BWD ? tpos + back >= a.T : tpos < back) raw = u32x4{0, 0, 0, 0};
+        uf[kk] = __builtin_bit_cast(bf16x8, raw);
+      }
+    }
+    __syncthreads();  // step s_ is in LDS (stored one step ago); the other buffer is no longer read
+    if (s_ + 1 < NSTEP) store_step((s_ + 1) & 1);
+    const unsigned char *const sw = sW + (s_ & 1) * BUF + l32 * SROW + half * 16;
+#pragma unroll
+    for (int kk = 0; kk < KCK; ++kk)
+#pragma unroll
+      for (int nt = 0; nt < NTL; ++nt) {
+        const bf16x8 wf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(sw + nt * 32 * SROW + kk * 32));
+        acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, uf[kk], acc[nt], 0, 0, 0);
+      }
+    if (mean && back == 0) {  // own stream of the qk-mean: + 1/2 of the token's own row; channels c*64 + kk*16 .. lie in tile 2c + kk/2
+#pragma unroll
+      for (int kk = 0; kk < KCK; ++kk)
+        acc[2 * c + kk / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[kk & 1], uf[kk], acc[2 * c + kk / 2], 0, 0, 0);
+    }
+  }
+
+  // ---- other stream of the qk-mean, a quarter of the head width at a time
+  if (mean) {
+    const float w_other = is_q ? a.mean_q_other : a.mean_k_other;
+    const bf16_t w_other_hi = f32_to_bf16(w_other);
+    const bf16_t w_other_lo = f32_to_bf16(w_other - bf16_to_f32(w_other_hi));
+    const bool grp_lo = (w_other_lo & 0x7fffu) != 0;  // uniform over the workgroup
+    bf16x8 id_grp[2], id_grp_lo[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      id_grp[j] = identity_frag(w_other_hi, j);
+      id_grp_lo[j] = identity_frag(w_other_lo, j);
+    }
+    const int nsrc = is_q ? 1 : a.R;
+    for (int x = 0; x < nsrc; ++x) {
+      const bf16_t *p = lat + rowc * a.src_stride + (is_q ? a.e_q + hd.g * DH : (hd.g * a.R + x) * DH) + half * 8;
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        bf16x8 mf[KCK];
+#pragma unroll
+        for (int kk = 0; kk < KCK; ++kk)
+          mf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p + c * KC + kk * 16));
+#pragma unroll
+        for (int kk = 0; kk < KCK; ++kk) {
+          acc[2 * c + kk / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_grp[kk & 1], mf[kk], acc[2 * c + kk / 2], 0, 0, 0);
+          if (grp_lo)
+            acc[2 * c + kk / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_grp_lo[kk & 1], mf[kk], acc[2 * c + kk / 2], 0, 0, 0);
+        }
+      }
+    }
+  }
+
+  norm_and_rope_256(acc, a, hd.head, beta, row, tpos, half, ropeA, ropeB, rnorm);
+  if (row < a.rows) {
+    bf16_t *const orow = is_q ? q + hd.head * DH + row * a.q_stride : k + hd.g * DH + row * a.k_stride;
+#pragma unroll
+    for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg) {
+        u32x2 w;
+        w.x = pack2(acc[nt][rg * 4 + 0], acc[nt][rg * 4 + 1]);
+        w.y = pack2(acc[nt][rg * 4 + 2], acc[nt][rg * 4 + 3]);
+        *reinterpret_cast<u32x2 *>(orow + nt * 32 + rg * 8 + half * 4) = w;
+      }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -913,17 +1089,25 @@ hipError_t prologue_fused_prepare(const Dims &d, const cca_weights &w, void *scr
 template <int D, bool BWD>
 static hipError_t launch_stream(const Dims &d, FusedArgs a, const float *temp, const void *lat, const void *vsrc,
                                 const FusedScratch &fs, void *q, void *k, void *v, float *rnorm, hipStream_t s) {
-  // one 128-token block per workgroup for every head, key heads first (the kernel's block map)
-  const long long blocks = (d.rows() + ST_WAVES * 32 - 1) / (ST_WAVES * 32);
+  // one block of 128 or 256 tokens per workgroup for every head, key heads first (the kernels' block map)
+  const bool wide = stream_takes_256(d.rows(), d.Hq + d.Hk, d.R, D, BWD);
+  const int tokens = wide ? 256 : ST_WAVES * 32, threads = wide ? NT : ST_NT;
+  const long long blocks = (d.rows() + tokens - 1) / tokens;
   a.tiles_per_wave = a.tiles_per_wave_k = 1;
   a.n_k_blocks = (int)(d.Hk * blocks);
   a.n_conv_blocks = (int)((d.Hq + d.Hk) * blocks);
   const long long v_chunks = d.rows() * (d.e_kv / 8);
-  const int grid = a.n_conv_blocks + (int)((v_chunks + ST_NT * 4 - 1) / (ST_NT * 4));
-  if (hipError_t e = raise_lds_limit<prologue_stream_kernel<D, BWD>>(stream_lds(D)); e != hipSuccess) return e;
-  prologue_stream_kernel<D, BWD><<<grid, ST_NT, stream_lds(D), s>>>(a, (const bf16_t *)lat, (const bf16_t *)vsrc,
-                                                        (const u32x4 *)fs.wc, fs.ropeA, fs.ropeB, temp, (bf16_t *)q,
-                                                        (bf16_t *)k, (bf16_t *)v, rnorm);
+  const int grid = a.n_conv_blocks + (int)((v_chunks + threads * 4 - 1) / (threads * 4));
+  const auto launch = [&](auto kernel, size_t lds) {
+    kernel<<<grid, threads, lds, s>>>(a, (const bf16_t *)lat, (const bf16_t *)vsrc, (const u32x4 *)fs.wc, fs.ropeA, fs.ropeB, temp,
+                                      (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, rnorm);
+  };
+  if (wide) {
+    launch(prologue_stream_long_kernel<D, BWD>, 0);
+  } else {
+    if (hipError_t e = raise_lds_limit<prologue_stream_kernel<D, BWD>>(stream_lds(D)); e != hipSuccess) return e;
+    launch(prologue_stream_kernel<D, BWD>, stream_lds(D));
+  }
   return hipGetLastError();
 }
 

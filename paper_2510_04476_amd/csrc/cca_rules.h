@@ -140,4 +140,19 @@ constexpr SplitCost BWD_SPLIT{2.0, 1.0, 1.0, 0.1};
 inline bool dq_splits_keys(long long BH, int T, bool causal) { return split_pays(BH, T, causal, true, BWD_SPLIT); }
 inline bool dkdv_splits_rows(long long BH, int T, bool causal) { return split_pays(BH, T, causal, false, BWD_SPLIT); }
 
+// ---- prologue at d_h = 256: one head x 128 tokens per workgroup (one wavefront per SIMD) or 256 (two) -------------------
+// One workgroup per CU either way.  A lone round of the 128-token form takes half of the other's time (24 against 45 us at two
+// taps each and 6 / 2 heads), a full one 0.6 of it, so it wins while one round is enough (4096 tokens: 31.0 against 46.7) and,
+// by how little a nearly empty last round costs, between 2 and 2.75 of its rounds, where the other begins a second one (9000: 70.5
+// and 79.5; 12288: 85.1 and 81.1); 8192: 57.4 and 50.1, 16384: 113.8 and 92.1, 8 / 8 heads x 32768 520 and 452.  Without a
+// second tap (`taps` = 1) that middle range is not there (16384, 4 / 1 heads: 54.6 and 51.0).  The adjoint with more than two
+// query heads to a group keeps the small form longer: the other fetches all their rows for the key head's mean straight from
+// memory (7000, 6 / 2: 43.6 and 46.0, 12288, 4 / 1: 45.7 and 50.5).
+inline bool stream_takes_256(long long rows, int heads, int R, int taps, bool adjoint) {
+  const long long wgs = (rows + 127) / 128 * heads;
+  if (wgs <= 256) return false;
+  if (wgs <= 512) return !(adjoint && R > 2 && (R > 3 || wgs <= 448));
+  return wgs > 704 || (taps == 1 && !adjoint);
+}
+
 }  // namespace cca

@@ -25,6 +25,15 @@ def test_attention_cases_reach_both_block_orders():
     assert paired == {(True, True), (True, False), (False, False)}
 
 
+def test_wide_head_prologue_cases_reach_both_forms():
+    reached = set()
+    for B, T, Hq, Hk, k_seq, k_ch in small.STREAM_CASES:
+        for adjoint in (False, True):
+            taps = k_seq + k_ch - 1
+            reached.add((taps, adjoint, rules.stream_takes_256(B * T, Hq + Hk, Hq // Hk, taps, adjoint)))
+    assert reached == {(taps, adjoint, wide) for taps in (1, 2, 3) for adjoint in (False, True) for wide in (False, True)}
+
+
 # M, N, K and us of each tile shape in the order of rules.NT_TILES
 NT_MEASURED = [
     (4593, 4096, 4096, (207.5, 171.1, 352.7, 360.1, 215.9, 196.5)), (6000, 2048, 4096, (104.3, 160.1, 237.3, 166.6, 127.7, 119.5)),
@@ -56,4 +65,18 @@ DKDV_MEASURED = [(64, 1531, True, 104.5, 115.3), (4, 64, True, 13.0, 13.9), (8, 
                                         (rules.dkdv_splits_rows, DKDV_MEASURED)])
 def test_attention_split_is_the_faster_form(rule, cases):
     wrong = [(BH, T, causal) for BH, T, causal, one, two in cases if rule(BH, T, causal) != (two < one)]
+    assert not wrong, wrong
+
+
+# rows, query heads, KV heads, taps, adjoint and us with 128 and 256 tokens per workgroup
+STREAM_MEASURED = [(4096, 6, 2, 3, False, 31.3, 46.7), (6000, 4, 1, 3, False, 29.5, 49.0), (8192, 6, 2, 3, False, 57.4, 50.1),
+                   (9000, 6, 2, 3, False, 70.5, 79.5), (12288, 6, 2, 3, False, 85.1, 81.1), (16384, 6, 2, 3, False, 113.8, 92.1),
+                   (32768, 6, 2, 3, False, 233.0, 200.5), (3000, 8, 8, 3, False, 47.9, 41.2), (16384, 8, 8, 3, False, 261.2, 222.7),
+                   (32768, 1, 1, 3, False, 62.0, 49.5), (12288, 2, 2, 3, False, 47.6, 41.9), (16384, 4, 1, 1, False, 54.6, 51.0),
+                   (12288, 6, 2, 1, False, 65.1, 54.2), (7000, 6, 2, 3, True, 43.6, 46.0), (8192, 6, 2, 3, True, 50.3, 47.4),
+                   (12288, 4, 1, 3, True, 45.7, 50.5), (14000, 2, 2, 3, True, 48.6, 42.3), (16384, 6, 2, 3, True, 98.2, 86.9)]
+
+
+def test_wide_head_prologue_takes_the_faster_form():
+    wrong = [c for c in STREAM_MEASURED if rules.stream_takes_256(c[0], c[1] + c[2], c[1] // c[2], c[3], c[4]) != (c[6] < c[5])]
     assert not wrong, wrong

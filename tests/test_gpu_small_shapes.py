@@ -211,6 +211,65 @@ def test_decode_keys_masked_by_infinite_scores(dh, Hk, dtype):
         assert float((out.double() - ref).norm()) <= tol * float(ref.norm()), first
 
 
+def transforms(lat, w0, w1, temp, Hq, Hk, dh):
+    """The block's steps between the down-projection and attention in plain torch: both convolutions, qk-mean, norm and
+    temperature, RoPE, value-shift."""
+    B, T, _ = lat.shape
+    past = lambda u, n: torch.cat([torch.zeros_like(u[:, :n]), u[:, :T - n]], 1) if n else u
+    e_q, e_kv = Hq * dh, Hk * dh
+    u = lat[..., :e_q + e_kv]
+    y = sum(w0[:, j] * past(u, w0.shape[1] - 1 - j) for j in range(w0.shape[1])).view(B, T, Hq + Hk, dh)
+    taps = w1.shape[-1]
+    y = torch.stack([sum(past(y[:, :, h], taps - 1 - j) @ w1[h, :, :, j].t() for j in range(taps)) for h in range(Hq + Hk)], 2)
+    q0, k0 = u[..., :e_q].view(B, T, Hk, Hq // Hk, dh), u[..., e_q:].view(B, T, Hk, 1, dh)
+    m = 0.5 * (q0 + k0)
+    y = y + torch.cat([m.reshape(B, T, Hq, dh), m.mean(3)], 2)
+    y = y * dh ** 0.5 / y.norm(dim=-1, keepdim=True)
+    y = torch.cat([y[:, :, :Hq], y[:, :, Hq:] * temp.exp()[:, None]], 2)
+    t = torch.arange(T, device=lat.device, dtype=lat.dtype)[:, None]
+    ang = t * 10000.0 ** (-2.0 * torch.arange(dh // 2, device=lat.device, dtype=lat.dtype) / dh)
+    c, s = ang.cos()[:, None], ang.sin()[:, None]
+    a, b = y[..., :dh // 2], y[..., dh // 2:]
+    y = torch.cat([a * c - b * s, b * c + a * s], -1)
+    v = lat[..., e_q + e_kv:]
+    v = torch.cat([v[..., :e_kv // 2], past(v[..., e_kv // 2:], 1)], -1).view(B, T, Hk, dh)
+    return y[:, :, :Hq], y[:, :, Hq:], v
+
+
+# d_h = 256, both forms of the prologue and of its adjoint (128 and 256 tokens per workgroup) with 1, 2 and 3 taps: rows that are no
+# multiple of either block or of a wavefront's 32, several sequences in a block, one to four query heads per KV head
+STREAM_CASES = [(3, 45, 1, 1, 1, 1), (2, 131, 4, 1, 2, 2), (1, 1, 2, 2, 2, 1), (1, 257, 4, 2, 3, 1), (5, 421, 8, 8, 2, 2),
+                (1, 2100, 8, 8, 1, 1), (1, 2305, 8, 8, 1, 2), (7, 1801, 4, 1, 3, 1), (2, 7003, 6, 2, 1, 1), (3, 2999, 6, 2, 2, 1)]
+
+
+@pytest.mark.parametrize("B,T,Hq,Hk,k_seq,k_ch", STREAM_CASES)
+def test_wide_head_prologue(B, T, Hq, Hk, k_seq, k_ch):
+    """q, k, v and, through autograd, d_lat against the steps in fp64.  The filters are folded and rounded to bf16 (2^-9 of each
+    weight), q and k rounded once, the gradient entering the convolutions once: the 1e-2 of the whole-block tests."""
+    dh = 256
+    say("wide head prologue", B, T, Hq, Hk, k_seq, k_ch)
+    cfg = P.CCAConfig(B=B, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, k_seq=k_seq, k_ch=k_ch)
+    w = P.CCAWeights(w_down=None, w_out=None, w_conv_seq=rnd(cfg.e_q + cfg.e_kv, k_seq, seed=1, scale=k_seq ** -0.5),
+                     w_conv_ch=rnd(Hq + Hk, dh, dh, k_ch, seed=2, scale=(dh * k_ch) ** -0.5), temp=rnd(Hk, seed=3, scale=0.3, dtype=torch.float32))
+    lat = rnd(B, T, cfg.n_lat, seed=4)
+    nan = lambda *s, dtype=torch.bfloat16: torch.full(s, float("nan"), dtype=dtype, device="cuda")
+    q, k, v, rnorm = nan(B, T, Hq, dh), nan(B, T, Hk, dh), nan(B, T, Hk, dh), nan(B, T, Hq + Hk, dtype=torch.float32)
+    P.cca_prologue(cfg, w, lat, q, k, v, rnorm=rnorm)
+    d_q, d_k, d_v = (rnd(*t.shape, seed=s) for t, s in ((q, 5), (k, 6), (v, 7)))
+    d_lat, g = P.cca_prologue_backward(cfg, w, lat, q, k, rnorm, d_q, d_k, d_v, d_lat=torch.full_like(lat, float("nan")))
+    torch.cuda.synchronize()
+    x = lat.double().requires_grad_()
+    w0, w1, temp = (t.double().requires_grad_() for t in (w.w_conv_seq, w.w_conv_ch, w.temp))
+    ref = transforms(x, w0, w1, temp, Hq, Hk, dh)
+    torch.autograd.backward(ref, [t.double() for t in (d_q, d_k, d_v)])
+    assert torch.equal(v, ref[2].detach().bfloat16())
+    for name, got, r in (("q", q, ref[0]), ("k", k, ref[1]), ("d_lat", d_lat, x.grad), ("d_w_conv_seq", g.w_conv_seq, w0.grad),
+                         ("d_w_conv_ch", g.w_conv_ch, w1.grad), ("d_temp", g.temp, temp.grad)):
+        rel = float((got.double() - r.detach()).norm() / r.detach().norm())
+        say(name, rel)
+        assert rel <= 1e-2, (name, rel)
+
+
 # the decode step's projections (several passes through LDS, K slices of the down-projection, lengths that are not whole
 # groups) and filter layouts: widths 256 and 64 with up to 4 + 4 taps, 5 query heads per KV head
 DECODE_CASES = [dict(B=9, T=5, E=4104, Hq=4, Hk=2, dh=64, k_seq=2, k_ch=2), dict(B=2, T=9, E=2056, Hq=4, Hk=2, dh=256, k_seq=4, k_ch=4),
