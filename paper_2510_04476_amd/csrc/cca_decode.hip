@@ -886,7 +886,10 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(const T *__restrict__ 
 // The 8 wavefronts take an eighth of the k each and their sums are added through LDS in order.  A CU takes in about 29 GB/s
 // of 64-byte pieces, so the grid is split over K as well where the next kernel adds the parts anyway (the down-projection:
 // K = 2048 whole 6.7 us at one row, in 5 slices 4.4).  Up-projection, K x N = 1024 x 2048: 3.4 us at one row, 5.8 at 32,
-// against 6.4 + 4.7 us for one workgroup per CU with partial sums and a kernel to add them.
+// against 6.4 + 4.7 us for one workgroup per CU with partial sums and a kernel to add them.  More than 32 rows: a workgroup per
+// 32 (each reads its panel of W again, mostly from the L2), and the down-projection in fewer slices.  One workgroup for all rows in
+// turn was slower than W staged once (step of 128 sequences over 200 keys, E = 2048, 8 / 2 heads of 128: W staged once 68.3,
+// in turn 70.6, side by side 55.3 us; 512: 177, 234, 167; 40 x 1000, E = 4096: 78, 85, 71).
 typedef __bf16 sk_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float sk_f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t sk_u32x4 __attribute__((ext_vector_type(4)));
@@ -932,7 +935,7 @@ __device__ __forceinline__ void gemm_panel_body(const bf16_t *__restrict__ A, co
   const unsigned char *const pw = smem + (8 * half + ((lane & 15) >> 2)) * 64 + (((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2;
   const int cpr = kp / 8;  // 16-byte chunks of a row of A
   const int k_begin = blockIdx.y * k_slice, k_end = min(K, k_begin + k_slice);
-  for (int m0 = 0; m0 < M; m0 += 32) {
+  for (int m0 = blockIdx.z * 32; m0 < M; m0 += gridDim.z * 32) {
     const int mrows = min(32, M - m0);
     sk_f32x16 acc;
 #pragma unroll
@@ -1032,10 +1035,10 @@ bool panel_supported(int N, int K) { return N % 8 == 0 && K % 8 == 0; }
 hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest, float *part, int slices, int M, int N, int K,
                       hipStream_t s) {
   if (hipError_t e = raise_lds_limit<gemm_panel_kernel>(PN_LDS); e != hipSuccess) return e;
-  const int k_slice = ((K + slices - 1) / slices + 127) / 128 * 128;
+  const int row_blocks = (M + 31) / 32, k_slice = ((K + slices - 1) / slices + 127) / 128 * 128;
   const int kp = panel_rows(M, K < k_slice ? K : k_slice);
   const size_t pass = (size_t)kp * (PN_COLS * 2 + 2 * (M < 32 ? M : 32)), lds = pass > PN_SUMS ? pass : PN_SUMS;
-  gemm_panel_kernel<<<dim3((N + PN_COLS - 1) / PN_COLS, slices), PN_NT, lds, s>>>(A, W, C, dest, M, N, K, kp, k_slice,
+  gemm_panel_kernel<<<dim3((N + PN_COLS - 1) / PN_COLS, slices, row_blocks < 4096 ? row_blocks : 4096), PN_NT, lds, s>>>(A, W, C, dest, M, N, K, kp, k_slice,
                                                                                  slices > 1 ? part : nullptr);
   return hipGetLastError();
 }
@@ -1064,11 +1067,11 @@ int ring_rows(const Dims &d) {
   return (taps - 1 > 1 ? taps - 1 : 1) + 1;
 }
 
-// K slices of the down-projection on the matrix cores: enough workgroups for the chip, slices of 256 k at least, and no
+// K slices of the down-projection on the matrix cores: enough workgroups for the chip (with one per 32 rows), slices of 256 k at least, and no
 // more than the scratch of the split form holds (skinny_scratch_bytes)
 int down_slices(const Dims &d) {
   const int cols = (d.n_lat + PN_COLS - 1) / PN_COLS, most = skinny_splits(d.n_lat, d.E);
-  int s = 256 / cols;
+  int s = 256 / (cols * ((d.B + 31) / 32));
   s = s < d.E / 256 ? s : d.E / 256;
   s = s < most ? s : most;
   s = s < MAX_PARTS ? s : MAX_PARTS;

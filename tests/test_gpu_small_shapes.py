@@ -273,6 +273,7 @@ def test_wide_head_prologue(B, T, Hq, Hk, k_seq, k_ch):
 # the decode step's projections (several passes through LDS, K slices of the down-projection, lengths that are not whole
 # groups) and filter layouts: widths 256 and 64 with up to 4 + 4 taps, 5 query heads per KV head
 DECODE_CASES = [dict(B=9, T=5, E=4104, Hq=4, Hk=2, dh=64, k_seq=2, k_ch=2), dict(B=2, T=9, E=2056, Hq=4, Hk=2, dh=256, k_seq=4, k_ch=4),
+                dict(B=97, T=4, E=520, Hq=3, Hk=1, dh=64, k_seq=2, k_ch=2),  # four blocks of rows, the last of one
                 dict(B=3, T=7, E=640, Hq=5, Hk=1, dh=64, k_seq=1, k_ch=4), dict(B=1, T=6, E=512, Hq=2, Hk=1, dh=256, k_seq=3, k_ch=3)]
 
 
