@@ -1144,19 +1144,15 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
   }
   {
     const int len = pos + 1;  // the longest sequence sizes the splits
-    // Every split but a sequence's last holds `per` keys: one or two rounds of the row kernel's four wavefronts (a wavefront
-    // takes 8 load instructions of keys per round, 4 for three and more heads to a group), as few as leave about 1024
-    // workgroups on the chip, at most MAX_SPLITS splits.
-    const int unit = d.dh <= 64 ? 256 : d.dh <= 128 ? 128 : 64;
-    const long long want = (1024 + (long long)d.B * d.Hk - 1) / ((long long)d.B * d.Hk);
-    const long long most = want < MAX_SPLITS ? want : MAX_SPLITS;
-    const int per = (int)(((len + most - 1) / most + unit - 1) / unit) * unit;
+    // (the row kernel addresses a sequence's cache with 32-bit byte offsets)
+    const bool rows_kernel = std::is_same<T, bf16_t>::value && (d.dh == 64 || d.dh == 128 || d.dh == 256) &&
+                             (long long)d.T * d.Hk * d.dh * 2 < (1ll << 31);
+    const int per = decode_keys_per_split((long long)d.B * d.Hk, len, d.dh, rows_kernel, MAX_SPLITS);
     const int nsplit = (len + per - 1) / per;
     const size_t smem = sizeof(float) * ((size_t)R_MAX * d.dh + DEC_WAVES * 64 * R_MAX + DEC_WAVES * R_MAX * (2 + d.dh));
     const unsigned grid = (unsigned)((long long)d.B * d.Hk * nsplit);
     if constexpr (std::is_same<T, bf16_t>::value) {
-      // the row kernel addresses a sequence's cache with 32-bit byte offsets
-      if ((d.dh == 64 || d.dh == 128 || d.dh == 256) && (long long)d.T * d.Hk * d.dh * 2 < (1ll << 31)) {
+      if (rows_kernel) {
         for (int r0 = 0; r0 < d.R; r0 += R_MAX) {
           const int left = d.R - r0;
 #define CCA_DEC_ROWS(NR, DH, U)                                                                                    \

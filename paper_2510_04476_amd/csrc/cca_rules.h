@@ -155,4 +155,20 @@ inline bool stream_takes_256(long long rows, int heads, int R, int taps, bool ad
   return wgs > 704 || (taps == 1 && !adjoint);
 }
 
+// ---- decode attention: keys of a split -----------------------------------------------------------------------------------
+// Every split but a sequence's last holds this many keys: one or two rounds of the kernel's four wavefronts, as few splits as
+// leave about 1024 workgroups on the chip, at most `max_splits`.  groups = sequences x KV heads.  A wavefront of the row kernel
+// (bf16, d_h 64, 128, 256) takes 8 load instructions of keys per round (4 for three and more heads to a group); one of the general
+// kernel 64 keys, so fewer than 256 leave it wavefronts without any.  That pays only while most CUs are idle (4 sequences x
+// 300 keys, 2 KV heads of 200, fp32, whole steps: 64 keys 58 us, 256 60); else 256 is the least (100 x 300: 197 and 154; 40 x
+// 1000, 2 x 128: 86 and 73; 13 x 4000, 1 x 200: 101 and 72) and it goes on in half rounds (40 x 4000, 2 x 128: 384 keys 146, 320
+// 155, 512 157).
+inline int decode_keys_per_split(long long groups, int len, int dh, bool rows_kernel, int max_splits) {
+  const bool whole = !rows_kernel && groups * ((len + 255) / 256) >= 64;
+  const int unit = dh <= 64 ? 256 : dh <= 128 || whole ? 128 : 64, least = whole ? 256 : unit;
+  const long long want = (1024 + groups - 1) / groups, most = want < max_splits ? want : max_splits;
+  const int even = (int)(((len + most - 1) / most + unit - 1) / unit) * unit;
+  return even > least ? even : least;
+}
+
 }  // namespace cca

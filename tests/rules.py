@@ -17,6 +17,7 @@ int r_tn_splits(int Mo, int No, long long K) { return tn_splits(Mo, No, K); }
 int r_fwd_splits_keys(long long BH, int T, int causal) { return fwd_splits_keys(BH, T, causal); }
 int r_dq_splits_keys(long long BH, int T, int causal) { return dq_splits_keys(BH, T, causal); }
 int r_dkdv_splits_rows(long long BH, int T, int causal) { return dkdv_splits_rows(BH, T, causal); }
+int r_decode_keys_per_split(long long groups, int len, int dh, int rows_kernel) { return decode_keys_per_split(groups, len, dh, rows_kernel, 32); }
 int r_stream_takes_256(long long rows, int heads, int R, int taps, int adjoint) { return stream_takes_256(rows, heads, R, taps, adjoint); }
 int r_pair_blocks(long long BH, int causal, int blocks) { return pair_blocks(BH, causal, blocks); }
 }
@@ -37,7 +38,8 @@ def _lib():
     L, I = C.c_longlong, C.c_int
     for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
-                           r_stream_takes_256=[L, I, I, I, I]).items():
+                           r_stream_takes_256=[L, I, I, I, I],
+                           r_decode_keys_per_split=[L, I, I, I]).items():
         getattr(lib, name).argtypes = args
     return lib
 
@@ -72,3 +74,7 @@ def pair_blocks(BH, causal, blocks):
 
 def stream_takes_256(rows, heads, R, taps, adjoint):
     return bool(_lib().r_stream_takes_256(rows, heads, R, taps, adjoint))
+
+
+def decode_keys_per_split(groups, keys, dh, rows_kernel):
+    return _lib().r_decode_keys_per_split(groups, keys, dh, rows_kernel)

@@ -80,3 +80,19 @@ STREAM_MEASURED = [(4096, 6, 2, 3, False, 31.3, 46.7), (6000, 4, 1, 3, False, 29
 def test_wide_head_prologue_takes_the_faster_form():
     wrong = [c for c in STREAM_MEASURED if rules.stream_takes_256(c[0], c[1] + c[2], c[1] // c[2], c[3], c[4]) != (c[6] < c[5])]
     assert not wrong, wrong
+
+
+@pytest.mark.parametrize("groups,keys,dh,faster", [(80, 1000, 128, 256), (200, 300, 200, 256), (13, 4000, 200, 256), (80, 4000, 128, 384),
+                                                   (8, 300, 200, 64), (200, 300, 96, 256)])
+def test_general_decode_kernel_has_keys_for_its_wavefronts(groups, keys, dh, faster):
+    """The general kernel's four wavefronts take 64 keys each; sizes of splits that measured faster than half or double."""
+    assert rules.decode_keys_per_split(groups, keys, dh, False) == faster
+
+
+def test_decode_splits_cover_the_keys():
+    for groups in (1, 2, 13, 80, 1000):
+        for keys in (1, 63, 64, 65, 255, 256, 257, 1000, 4097, 16384, 1 << 20):
+            for dh in (8, 64, 96, 128, 200, 256):
+                for rows_kernel in (False, True):
+                    per = rules.decode_keys_per_split(groups, keys, dh, rows_kernel)
+                    assert per > 0 and -(-keys // per) <= 32 and (-(-keys // per) - 1) * per < keys
