@@ -102,8 +102,12 @@ __global__ __launch_bounds__(GB_NT) void attn_bwd_dq_generic_kernel(const T *__r
 }
 
 // Workgroup = 32 keys of one KV head, the (query head of the group, query tile) pairs that see them dealt to its 8
-// wavefronts; S and dP with one key per lane.  WHICH: 1 = dK, 2 = dV, 3 = both (d_h <= 128: two sets of accumulators fit).
-// T = 1000, 2 heads of 32, fp32: 41.5 us; one wavefront per key, dK and dV apart, on the vector ALU took 305 + 189.
+// wavefronts; S and dP with one key per lane.  WHICH: 1 = dK, 2 = dV, 3 = both in one pass, up to d_h = 128.  T = 1000, 2 heads of
+// 32, fp32: 41.5 us; one wavefront per key, dK and dV apart, on the vector ALU took 305 + 189.
+// At d_h 65 ... 128 the two sets of accumulators do not quite fit (79 registers spilled, none with one set), and one pass is
+// still the faster: attention backward, fp32, d_h = 128, 1000 tokens, 8 / 1 heads 1130 us against 1323 in two, 4096, 4 / 4
+// 1652 against 1729 (bf16, d_h = 96, 4096 causal the other way, 1879 and 1764).  The d_h = 256 instantiations here and in
+// cca_generic.hip spill 79 to 93 registers of one set: 4096 tokens, 4 / 2 heads, backward 4.1 ms, on the vector ALU 154.
 template <typename T, int DHM, int WHICH>
 __global__ __launch_bounds__(GB_NT) void attn_bwd_dkv_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
                                                                     const T *__restrict__ v, const T *__restrict__ dO,
