@@ -64,19 +64,21 @@ inline int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
 }
 
 // Small tiles without partial sums or 256 x 256 tiles split over K, by estimated time (us).  Fits to back-to-back
-// timings over K = 64 ... 16384 tokens of (rounds) x (slabs x time per slab + fill and epilogue): 128 x 128 (0.63, 3.5),
-// 64 x 128 (0.50, 3.0), 64 x 64 (0.34, 1.5) up to one workgroup per CU and (0.60, 1.5) at two; the split form as in
-// tn_splits.  2048 x 1536 over 1024 tokens split 30.8 us, 13.9 this way, over 4000 44.7 and 43.8, over 8000 66.7 and 83.0;
-// 1024 x 2048 over 1024 tokens 31.3 and 11.1, over 16384 82.5 and 136.9.
+// timings over K = 64 ... 16384 tokens and 4 ... 512 tiles of (rounds) x (slabs x time per slab + fill and epilogue), b the share of
+// the CUs at work: 128 x 128 (0.615 + 0.1 b^4, 3), 64 x 128 (0.455 + 0.045 b^2, 3), 64 x 64 (0.30, 2) up to one workgroup per CU
+// and (0.60, 1.5) at two; the split form as in tn_splits.  2048 x 1536 over 1024 tokens split 30.8 us, 13.9 this way, over
+// 4000 45.4 and 43.3, over 8000 66.7 and 83.0; 1024 x 2048 over 1024 tokens 31.3 and 11.1, over 16384 82.5 and 136.9; 2048 x 2048 over
+// 8000 83.5 and 91.7, over 4000 53.0 and 46.7.
 inline TnTile tn_tile(int Mo, int No, long long K) {
   const double slabs = (double)((K + 63) / 64);
   auto tiles = [&](int tm, int tn) { return (long long)((Mo + tm - 1) / tm) * ((No + tn - 1) / tn); };
+  auto busy = [](long long t) { return t < 256 ? (double)t / 256.0 : 1.0; };
   double split_us;
   tn_splits(Mo, No, K, &split_us);
-  const long long t64 = tiles(64, 64);
-  const double c128 = (double)((tiles(128, 128) + 255) / 256) * (slabs * 0.63 + 3.5),
-               c64x128 = (double)((tiles(64, 128) + 255) / 256) * (slabs * 0.50 + 3.0),
-               c64 = t64 <= 256 ? slabs * 0.34 + 1.5 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
+  const long long t128 = tiles(128, 128), t64x128 = tiles(64, 128), t64 = tiles(64, 64);
+  const double c128 = (double)((t128 + 255) / 256) * (slabs * (0.615 + 0.1 * pow(busy(t128), 4.0)) + 3.0),
+               c64x128 = (double)((t64x128 + 255) / 256) * (slabs * (0.455 + 0.045 * pow(busy(t64x128), 2.0)) + 3.0),
+               c64 = t64 <= 256 ? slabs * 0.30 + 2.0 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
   const double small = fmin(c128, fmin(c64x128, c64));
   if (small >= split_us) return TN_SPLIT;
   return c64 == small ? TN_64x64 : c64x128 == small ? TN_64x128 : TN_128x128;

@@ -50,6 +50,18 @@ def test_projection_tile_is_the_fastest(M, N, K, us):
     assert us[rules.NT_TILES.index(rules.nt_tile(M, N, K))] <= 1.06 * min(us)
 
 
+# Mo, No, tokens and us of the small tiles (in the order of rules.TN_TILES[1:]) and of the best split
+TN_MEASURED = [(2048, 2048, 8000, (168.5, 124.8, 91.7), 83.5), (2048, 2048, 4000, (79.7, 65.7, 46.9), 53.0),
+               (2048, 1536, 8000, (107.3, 120.1, 83.4), 66.7), (1024, 2048, 8000, (80.6, 65.9, 81.3), 51.8), (2048, 6144, 4000, (228.6, 234.3, 145.4), 127.8),
+               (1024, 2048, 1024, (11.4, 11.3, 13.8), 31.3)]
+
+
+@pytest.mark.parametrize("Mo,No,K,small_us,split_us", TN_MEASURED)
+def test_weight_gradient_form_is_the_fastest(Mo, No, K, small_us, split_us):
+    us = dict(zip(rules.TN_TILES[1:], small_us), split=split_us)
+    assert us[rules.tn_tile(Mo, No, K)] <= 1.06 * min(us.values())
+
+
 # B * H_q, T, causal and us on one and on two groups of wavefronts (d_h = 64 or 128)
 FWD_MEASURED = [(8, 64, True, 4.4, 5.4), (8, 128, True, 8.2, 9.4), (96, 400, True, 10.8, 15.6), (128, 400, True, 17.9, 25.2),
                 (64, 640, True, 12.7, 14.1), (64, 777, True, 16.2, 18.5), (128, 640, False, 40.6, 57.6), (96, 1280, True, 54.5, 72.3),
