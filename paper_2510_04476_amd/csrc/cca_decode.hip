@@ -787,7 +787,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecArgs a, const fl
 }
 
 // ---------------------------------------------------------------------------
-// Projections of a decode step: C (M, N) = A (M, K) W (K, N) with M = batch size (a handful of rows), bound by
+// Projections of a decode step in fp32 (bf16: gemm_panel_kernel): C (M, N) = A (M, K) W (K, N) with M = batch size, bound by
 // reading W once.  Workgroup = 128 columns x one slice of K; a lane owns 2 adjacent columns (one 4- or 8-byte load
 // per row of W), the 4 wavefronts take quarters of the slice and are added through LDS, rows of A go through LDS
 // 16 or 32 at a time ([k][rows] floats, so one 16-byte broadcast read feeds 4 rows).  K slices write fp32 partial sums
@@ -1029,9 +1029,7 @@ int skinny_splits(int N, int K) {
 }
 size_t skinny_scratch_bytes(int M, int N, int K) { return (size_t)skinny_splits(N, K) * M * N * sizeof(float); }
 
-bool panel_supported(int N, int K) { return N % 8 == 0 && K % 8 == 0; }
-
-// slices = 1: C.  More: `part` gets that many partial sums (slices, M, N) for the caller's next kernel to add.
+// N and K are multiples of 8, as every bf16 width is (make_dims).  slices = 1: C.  More: `part` gets that many partial sums (slices, M, N) for the caller's next kernel to add.
 hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest, float *part, int slices, int M, int N, int K,
                       hipStream_t s) {
   if (hipError_t e = raise_lds_limit<gemm_panel_kernel>(PN_LDS); e != hipSuccess) return e;
@@ -1045,18 +1043,20 @@ hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest,
 
 template <typename T>
 hipError_t gemm_skinny(const T *A, const T *W, T *C, RowDest dest, float *part, int M, int N, int K, hipStream_t s) {
-  if constexpr (std::is_same<T, bf16_t>::value)
-    if (panel_supported(N, K)) return gemm_panel(A, W, C, dest, part, 1, M, N, K, s);
-  const int splits = skinny_splits(N, K);
-  const int chunk = (K + splits - 1) / splits;
-  const dim3 grid((N + SK_COLS - 1) / SK_COLS, (K + chunk - 1) / chunk);
-  if (M > 16) gemm_skinny_kernel<T, 32><<<grid, 256, 0, s>>>(A, W, part, M, N, K, chunk);
-  else gemm_skinny_kernel<T, 16><<<grid, 256, 0, s>>>(A, W, part, M, N, K, chunk);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const long long mn = (long long)M * N;
-  skinny_reduce_kernel<T><<<(unsigned)((mn + 255) / 256), 256, 0, s>>>(part, C, dest, mn, N, (int)grid.y);
-  return hipGetLastError();
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    return gemm_panel(A, W, C, dest, part, 1, M, N, K, s);
+  } else {
+    const int splits = skinny_splits(N, K);
+    const int chunk = (K + splits - 1) / splits;
+    const dim3 grid((N + SK_COLS - 1) / SK_COLS, (K + chunk - 1) / chunk);
+    if (M > 16) gemm_skinny_kernel<T, 32><<<grid, 256, 0, s>>>(A, W, part, M, N, K, chunk);
+    else gemm_skinny_kernel<T, 16><<<grid, 256, 0, s>>>(A, W, part, M, N, K, chunk);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const long long mn = (long long)M * N;
+    skinny_reduce_kernel<T><<<(unsigned)((mn + 255) / 256), 256, 0, s>>>(part, C, dest, mn, N, (int)grid.y);
+    return hipGetLastError();
+  }
 }
 
 // slots of the latent ring: the taps - 1 earlier rows the convolutions reach back to (one at least, for the value
@@ -1120,7 +1120,7 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
   T *const ring_c = (T *)hist + (pos_seq ? 0 : (long long)(pos % P) * d.n_lat);
   int nparts = 1;
   hipError_t e;
-  if (std::is_same<T, bf16_t>::value && panel_supported(d.n_lat, d.E)) {
+  if constexpr (std::is_same<T, bf16_t>::value) {
     nparts = down_slices(d);
     e = gemm_panel((const bf16_t *)x_new, (const bf16_t *)w.w_down, (bf16_t *)ring_c, ring, gpart, nparts, d.B, d.n_lat, d.E, s);
   } else {
