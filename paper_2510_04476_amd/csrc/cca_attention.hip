@@ -375,8 +375,8 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
           // when a score exceeds it by more than 2^RESCALE_LOG2; exp2 arguments stay <= RESCALE_LOG2.
           if (__any(unset || mx > RESCALE_LOG2)) {
             const float delta = unset ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, 0.f);
+            const float alpha = unset ? 1.f : __builtin_amdgcn_exp2f(-delta);  // nothing summed yet: 2^-delta may be inf
             unset = unset && mx == -INFINITY;
-            const float alpha = __builtin_amdgcn_exp2f(-delta);
             l_run *= alpha;
             l_run2 *= alpha;
   #pragma unroll

@@ -126,16 +126,18 @@ def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
 @pytest.mark.parametrize("live", [(0, 40), (70, 140), (129, 300)])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("dh", [64, 128, 256])
-def test_attention_keys_masked_by_infinite_scores(dh, causal, live):
-    """Scores of -inf (padded keys: a channel of k at -inf that every q reads with a positive weight) in whole key tiles: the
-    rows that see a live key are those of attention over the live keys alone, with the roundings of the test above."""
+@pytest.mark.parametrize("masked", [float("-inf"), -2e4])
+def test_attention_keys_masked_by_infinite_scores(dh, causal, live, masked):
+    """Scores of -inf or far below any other (padded keys: a channel of k at that value that every q reads with a positive weight)
+    in whole key tiles: the rows that see a live key are those of attention over the live keys alone, with the roundings of the
+    test above."""
     T, Hq, lo, hi = 300, 2, *live
-    say("infinite scores", dh, causal, live)
+    say("infinite scores", dh, causal, live, masked)
     assert rules.fwd_splits_keys(Hq, T, causal)
     cfg = P.CCAConfig(B=1, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, flags=P.CCA_CAUSAL if causal else 0)
     q, k, v = rnd(1, T, Hq, dh, seed=1), rnd(1, T, Hq, dh, seed=2), rnd(1, T, Hq, dh, seed=3)
     q[..., 5] = 1.0
-    k[:, :lo, :, 5], k[:, hi:, :, 5] = float("-inf"), float("-inf")
+    k[:, :lo, :, 5], k[:, hi:, :, 5] = masked, masked
     o, lse = P.cca_attention(cfg, q, k, v, want_lse=True)
     torch.cuda.synchronize()
     first = lo if causal else 0
