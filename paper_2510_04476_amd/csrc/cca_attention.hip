@@ -65,6 +65,7 @@ constexpr int BQ = 256;   // query rows per workgroup (8 wavefronts x 32 rows)
 constexpr int BKV = 64;   // keys per LDS tile
 constexpr int NT = 512;   // threads
 constexpr float RESCALE_LOG2 = 8.f;
+constexpr float LOST_LOG2 = 4096.f;  // a reference max this far below the scores rounds them by up to 2^-12
 
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   bf16x2 v = {(__bf16)lo, (__bf16)hi};  // round to nearest even
@@ -154,8 +155,8 @@ __device__ __forceinline__ void store_rows(const f32x16 *oacc, float l, float sh
 // Two groups of wavefronts walked the two halves of the keys of the same rows (KS = 2): the partial results of a row,
 // taken against the reference maxima m (a group that saw no score of the row above -inf has l = 0), are added through LDS.  Each group
 // ends with the output tiles [kg * DT / 2, (kg + 1) * DT / 2) of its wavefront's rows; l and m are the row's afterwards.
-// The K / V tiles in `smem` are no longer read by anyone when this is called.
-template <int DH>
+// The K / V tiles in `smem` are no longer read by anyone when this is called.  MAY_LOSE: l = -inf in either group stays.
+template <int DH, bool MAY_LOSE>
 __device__ __forceinline__ void merge_key_groups(f32x16 *oacc, float &l, float &m, int kg, int wave_g, int lane,
                                                  unsigned char *smem) {
   constexpr int HT = DH / 64;  // output tiles a group keeps
@@ -175,7 +176,7 @@ __device__ __forceinline__ void merge_key_groups(f32x16 *oacc, float &l, float &
   const float lo = other[HT * 16 * 64], mo = other[(HT * 16 + 1) * 64];
   const float M = l == 0.f ? mo : lo == 0.f ? m : fmaxf(m, mo);
   const float f = l == 0.f ? 0.f : __builtin_amdgcn_exp2f(m - M), fo = lo == 0.f ? 0.f : __builtin_amdgcn_exp2f(mo - M);
-  l = l * f + lo * fo;
+  l = MAY_LOSE && fminf(l, lo) < 0.f ? -INFINITY : l * f + lo * fo;
   m = M;
 #pragma unroll
   for (int x = 0; x < HT; ++x)
@@ -189,21 +190,60 @@ __device__ __forceinline__ void merge_key_groups(f32x16 *oacc, float &l, float &
   __syncthreads();  // the buffer may hold K / V tiles again
 }
 
-// Epilogue of a wavefront: the row sums over both half-waves, with KS = 2 the other group's part, then the rows.
-template <int DH, int KS>
-__device__ __forceinline__ void finish_rows(f32x16 *oacc, float l_part, float m, int kg, int wave_g, int lane, bool live,
+// Epilogue of a wavefront: the row sums over both half-waves, with KS = 2 the other group's part, then the rows.  Rows that
+// either group lost (MAY_LOSE: l = -inf) are not stored; true for them.
+template <int DH, int KS, bool MAY_LOSE>
+__device__ __forceinline__ bool finish_rows(f32x16 *oacc, float l_part, float m, int kg, int wave_g, int lane, bool live,
                                             unsigned char *smem, bf16_t *__restrict__ O, bf16_t *__restrict__ OLO,
                                             float *__restrict__ LSE, int b, int h, int t, int T, int Hq) {
   float l = both_halves(l_part);
   const int half = lane >> 5;
+  if constexpr (KS == 2) merge_key_groups<DH, MAY_LOSE>(oacc, l, m, kg, wave_g, lane, smem);
+  if (!live) return false;
+  if (MAY_LOSE && l < 0.f) return true;
   if constexpr (KS == 1) {
-    if (live) store_rows<DH>(oacc, l, m, O, OLO, LSE, b, h, t, T, Hq, half);
+    store_rows<DH>(oacc, l, m, O, OLO, LSE, b, h, t, T, Hq, half);
   } else {
-    merge_key_groups<DH>(oacc, l, m, kg, wave_g, lane, smem);
-    if (!live) return;
     if (kg == 0) store_rows<DH, 0, DH / 64>(oacc, l, m, O, OLO, LSE, b, h, t, T, Hq, half);
     else store_rows<DH, DH / 64, DH / 32>(oacc, l, m, O, OLO, LSE, b, h, t, T, Hq, half);
   }
+  return false;
+}
+
+// One row by one wavefront, straight from memory, a key at a time against the running max itself: for rows whose scores
+// attn_fwd_body could not hold against one reference max.  Lane = DH / 64 channels; same roundings of q and P as there.
+template <int DH, bool RSUM>
+__device__ __forceinline__ void single_row(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
+                                           bf16_t *__restrict__ O, bf16_t *__restrict__ OLO, float *__restrict__ LSE, int b, int h,
+                                           int g, int t, int keys, int T, int Hq, int Hk, float c, int lane) {
+  constexpr int CPL = DH / 64;
+  asm volatile("" : "+v"(lane), "+s"(t));  // nothing of this may be formed ahead, it would take registers in the caller's loop
+  const long long qo = (((long long)b * T + t) * Hq + h) * DH + lane * CPL;
+  float q[CPL], acc[CPL], m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int x = 0; x < CPL; ++x) q[x] = bf_lo(pack2(bf_lo(Q[qo + x]) * c, 0.f)), acc[x] = 0.f;
+  for (int key = 0; key < keys; ++key) {
+    const long long ko = (((long long)b * T + key) * Hk + g) * DH + lane * CPL;
+    float sc = 0.f;
+#pragma unroll
+    for (int x = 0; x < CPL; ++x) sc += q[x] * bf_lo(K[ko + x]);
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) sc += __uint_as_float(__builtin_amdgcn_ds_bpermute((lane ^ d) * 4, __float_as_uint(sc)));
+    const float mn = fmaxf(m, sc), ref = mn == -INFINITY ? 0.f : mn;
+    const float a = __builtin_amdgcn_exp2f(m - ref), p = __builtin_amdgcn_exp2f(sc - ref), pr = bf_lo(pack2(p, 0.f));
+    l = l * a + (RSUM ? pr : p);
+#pragma unroll
+    for (int x = 0; x < CPL; ++x) acc[x] = acc[x] * a + pr * bf_lo(V[ko + x]);
+    m = mn;
+  }
+  const float inv = 1.f / l;
+#pragma unroll
+  for (int x = 0; x < CPL; ++x) {
+    const uint32_t w = pack2(acc[x] * inv, 0.f);
+    O[qo + x] = (bf16_t)w;
+    if (OLO) OLO[qo + x] = (bf16_t)pack2(acc[x] * inv - bf_lo(w), 0.f);
+  }
+  if (LSE && lane == 0) LSE[((long long)b * Hq + h) * T + t] = (log2f(l) + m) * 0.69314718055994530942f;
 }
 
 // BOUNDED: the caller guarantees |score| <= bound (log2 units) for every query / key pair, as the QK L2-norm
@@ -376,9 +416,12 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
           if (__any(unset || mx > RESCALE_LOG2)) {
             const float delta = unset ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, 0.f);
             const float alpha = unset ? 1.f : __builtin_amdgcn_exp2f(-delta);  // nothing summed yet: 2^-delta may be inf
+            // Scores rounded against a reference far below them (keys masked by a type's lowest value ahead of the live ones):
+            // the row is lost, which its sum says for want of a register, and taken again by single_row.
+            const bool lost = (!unset && delta > LOST_LOG2 && negm[0] > LOST_LOG2) || l_run2 == -INFINITY;
             unset = unset && mx == -INFINITY;
             l_run *= alpha;
-            l_run2 *= alpha;
+            l_run2 = lost ? -INFINITY : l_run2 * alpha;
   #pragma unroll
             for (int r = 0; r < 16; ++r) negm[r] -= delta;
   #pragma unroll
@@ -437,7 +480,18 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
     }
 
     // ---- epilogue: normalise, round once to bf16, store; log-sum-exp of the scaled logits
-    finish_rows<DH, KS>(oacc, l_run + l_run2, -negm[0], kg, wave, lane, wave_live, smem, O, OLO, LSE, b, h, qw0 + l32, T, Hq);
+    int te = threadIdx.x;  // (anew, so that no lane or row number takes a register in the loop)
+    asm volatile("" : "+v"(te));
+    const int lane_e = te & 63, wave_e = te % NTG >> 6, qw_e = q0 + wave_e * 32;
+    const bool lost = finish_rows<DH, KS, !BOUNDED>(oacc, l_run + l_run2, -negm[0], kg, wave_e, lane_e, qw_e < T, smem, O, OLO, LSE, b,
+                                                    h, qw_e + (lane_e & 31), T, Hq);
+    if (!BOUNDED && kg == 0 && __any(lost)) {
+      uint32_t rows = (uint32_t)__ballot(lost);
+      for (; rows; rows &= rows - 1) {
+        const int t = __builtin_amdgcn_readfirstlane(qw_e) + __builtin_ctz(rows);
+        if (t < T) single_row<DH, RSUM>(Q, K, V, O, OLO, LSE, b, h, g, t, CAUSAL ? t + 1 : T, T, Hq, Hk, c, lane_e);
+      }
+    }
   }
 }
 
@@ -694,7 +748,7 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
     for (; j < ntiles; ++j) iter(j, IDLE_{}, F_{});
 
     // ---- epilogue: normalise, round once to bf16, store; log-sum-exp of the scaled logits
-    finish_rows<DH, KS>(oacc, l_run + l_run2, bound, kg, wave, lane, wave_live, smem, O, OLO, LSE, b, h, qw0 + l32, T, Hq);
+    finish_rows<DH, KS, false>(oacc, l_run + l_run2, bound, kg, wave, lane, wave_live, smem, O, OLO, LSE, b, h, qw0 + l32, T, Hq);
   }
 }
 

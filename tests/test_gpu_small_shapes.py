@@ -123,36 +123,53 @@ def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
             assert float((lse[b, h].double() - ref_lse).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
 
 
-@pytest.mark.parametrize("live", [(0, 40), (70, 140), (129, 300)])
-@pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("dh", [64, 128, 256])
-@pytest.mark.parametrize("masked", [float("-inf"), -2e4])
-def test_attention_keys_masked_by_infinite_scores(dh, causal, live, masked):
-    """Scores of -inf or far below any other (padded keys: a channel of k at that value that every q reads with a positive weight)
-    in whole key tiles: the rows that see a live key are those of attention over the live keys alone, with the roundings of the
-    test above."""
-    T, Hq, lo, hi = 300, 2, *live
-    say("infinite scores", dh, causal, live, masked)
+def check_masked_keys(dh, causal, live, masked):
+    """Keys outside `live` (a mask over T) score `masked` times a positive number, through a channel of k at that value that every q
+    reads with a positive weight: the rows that see a live key are those of attention over the live keys alone, with the
+    roundings of the test above."""
+    T, Hq = live.numel(), 2
     assert rules.fwd_splits_keys(Hq, T, causal)
     cfg = P.CCAConfig(B=1, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, flags=P.CCA_CAUSAL if causal else 0)
     q, k, v = rnd(1, T, Hq, dh, seed=1), rnd(1, T, Hq, dh, seed=2), rnd(1, T, Hq, dh, seed=3)
     q[..., 5] = 1.0
-    k[:, :lo, :, 5], k[:, hi:, :, 5] = masked, masked
+    k[:, ~live, :, 5] = masked
     o, lse = P.cca_attention(cfg, q, k, v, want_lse=True)
     torch.cuda.synchronize()
-    first = lo if causal else 0
+    first = int(live.nonzero()[0]) if causal else 0
     for h in range(Hq):
-        s = q[0, first:, h].double() @ k[0, lo:hi, h].double().t().contiguous() / dh ** 0.5
+        s = q[0, first:, h].double() @ k[0, live, h].double().t().contiguous() / dh ** 0.5
         s_max = float(s.abs().max())
         if causal:
-            s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1)[first:, lo:hi], float("-inf"))
-        p, vh = torch.softmax(s, -1), v[0, lo:hi, h].double()
+            s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1)[first:, live], float("-inf"))
+        p, vh = torch.softmax(s, -1), v[0, live, h].double()
         noise = 2.0 ** -9 * (1.0 + s_max) * (p.square() @ vh.square()).sqrt()
         ref = p @ vh
         got = o[0, first:, h * dh:(h + 1) * dh].double()
         assert bool(got.isfinite().all())
         assert float(((got - ref).abs() / (2.0 ** -8 * ref.abs() + 6.0 * noise + 1e-6)).max()) <= 1.0
         assert float((lse[0, h, first:].double() - torch.logsumexp(s, -1)).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
+
+
+@pytest.mark.parametrize("live", [(0, 40), (70, 140), (129, 300)])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh", [64, 128, 256])
+@pytest.mark.parametrize("masked", [float("-inf"), -2e4])
+def test_attention_keys_masked_by_infinite_scores(dh, causal, live, masked):
+    """Scores of -inf, or far below any other, in whole key tiles."""
+    say("infinite scores", dh, causal, live, masked)
+    t = torch.arange(300, device="cuda")
+    check_masked_keys(dh, causal, (t >= live[0]) & (t < live[1]), masked)
+
+
+@pytest.mark.parametrize("gap", [(0, 64), (64, 128), (0, 300)])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh", [64, 128, 256])
+def test_attention_keys_masked_by_the_lowest_scores(dh, causal, gap):
+    """Scores near the type's lowest value in the first tiles of one or both key groups: against a reference max taken from them all
+    later scores round to one value."""
+    say("lowest scores", dh, causal, gap)
+    t = torch.arange(1000, device="cuda")
+    check_masked_keys(dh, causal, (t < gap[0]) | (t >= gap[1]), -1e38)
 
 
 @pytest.mark.parametrize("live", [(0, 40), (70, 140), (129, 300)])
