@@ -4,13 +4,12 @@
 //
 // Both operands are K-contiguous, so a lane's 8-element MFMA fragment is one
 // 16-byte LDS read.  Workgroup tile 256 x BN x 64 with 8 wavefronts; LDS is
-// double-buffered and XOR-swizzled per 16-byte chunk; K-slab k+1 travels HBM ->
-// LDS directly (global_load_lds, no staging registers, no ds_write) while slab k
-// is multiplied, its loads spread over the first two of the slab's four 16-wide
-// MFMA steps so that the LDS writes trickle in between the fragment reads
-// instead of arriving in one burst (the LDS write port, ~75 B/clk against ~230 B/clk for
-// reads, is what this kernel feels first: without the stores it runs a third
-// faster).  The MFMA is issued with the weight rows as its first operand,
+// XOR-swizzled per 16-byte chunk; K-slabs travel HBM -> LDS directly
+// (global_load_lds, no staging registers, no ds_write), A two slabs ahead and the
+// weight one, the loads spread over a slab's 16-wide MFMA steps so that the LDS
+// writes trickle in between the fragment reads instead of arriving in one
+// burst (the LDS write port takes ~75 B/clk against ~230 B/clk for
+// reads).  The MFMA is issued with the weight rows as its first operand,
 // which leaves every lane with 4 consecutive output columns of one row, so
 // the epilogue packs them to bf16, stages the tile in LDS and writes whole
 // rows with 16-byte stores.
@@ -30,7 +29,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int BM = 256, BK = 64;
-constexpr int SPREAD = 2;  // k-steps of a slab over which the next slab's loads are issued (4 k-steps per slab)
+constexpr int A_STAGES = 3, B_STAGES = 2;  // slabs of each operand in the LDS of the 256-row product
 
 // LDS position of the 16-byte chunk c (0..7) of row r in a [rows][64] bf16 tile
 __device__ __forceinline__ int swz(int r, int c) { return r * 8 + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
@@ -114,18 +113,27 @@ __device__ __forceinline__ void store_tile_bf16(const f32x16 (&acc)[NI][MI], uns
   }
 }
 
+// LDS holds three slabs of A and two of Bt: A streams from HBM, whose latency a slab's 1.1-1.5 us of MFMAs do not cover; Bt is
+// a weight that stays in the caches, and a third stage of it would not fit (256 columns: 3 x 32 + 2 x 32 KB, all of a CU's LDS).
+// A slab's one barrier stands before its last k-step, when the fragments of that step are in registers: from there on the slab's
+// buffers are free for the next loads, and the next slab's first fragments are read under the last step's MFMAs.
+// 16384 x 1536 x 2048, back to back on random operands: 106.7 us with two slabs of both and the barrier at the slab's end,
+// 101.8 this way; 4096 x 6144 x 2048 112.5 and 103.2, 7996 x 1536 x 2048 51.8 and 49.6 (256 x 192 tiles); 16384 x 2048 x 1024 73.4
+// and 72.1 (256 x 256).  On all-zero operands the first takes 89 us: what bounds the larger shapes is the power the matrix cores
+// draw; with every row of A the same (in the caches) it still takes 104.
 template <int BN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(const bf16_t *__restrict__ A,
                                                                const bf16_t *__restrict__ Bt,
                                                                bf16_t *__restrict__ C, long long M, int N, int K,
                                                                int tiles_n, int tiles_total, ColumnSplit split) {
-  constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
+  constexpr int NWAVES = WAVES_M * WAVES_N, NTHREADS = NWAVES * 64;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave tile
   constexpr int MI = WM / 32, NI = WN / 32;            // 32x32 MFMA tiles per wave
   static_assert(MI * 32 == WM && NI * 32 == WN, "wave tile must be a multiple of 32");
+  static_assert(BK == 64, "four k-steps of 16");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int STAGE = (BM + BN) * 8;  // 16-byte chunks per pipeline stage
-  u32x4 *const sbase = reinterpret_cast<u32x4 *>(smem);
+  constexpr int A_STAGE = BM * 8, B_STAGE = BN * 8;  // 16-byte chunks of a slab
+  u32x4 *const sA = reinterpret_cast<u32x4 *>(smem), *const sB = sA + A_STAGES * A_STAGE;
 
   // XCD-aware tile order: workgroup ids are dealt round-robin over the 8 XCDs,
   // so give each XCD a contiguous range of tiles; within it the N tiles of one
@@ -142,38 +150,36 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int l32 = lane & 31, half = lane >> 5;
 
-  // Direct global -> LDS loads: wave instruction i deposits 64 x 16 bytes at LDS chunks [i*64, i*64+64) of the
-  // stage (A rows first, then B rows; 8 chunks per row), so lane L fetches the chunk that the XOR swizzle puts
-  // at that position.  No staging registers, no ds_write.
-  constexpr int N_INSTR = (BM + BN) * 8 / 64;
-  constexpr int PER_WAVE = N_INSTR / (NTHREADS / 64);
-  static_assert(N_INSTR % (NTHREADS / 64) == 0, "instructions must divide evenly over the wavefronts");
-  const bf16_t *g_src[PER_WAVE];
+  // Direct global -> LDS loads: wave instruction i deposits 64 x 16 bytes at LDS chunks [i*64, i*64+64) of a slab
+  // (8 chunks per row), so lane L fetches the chunk that the XOR swizzle puts at that position.
+  constexpr int A_LOADS = A_STAGE / 64 / NWAVES, B_LOADS = B_STAGE / 64 / NWAVES;  // instructions of a wavefront per slab
+  static_assert(A_LOADS * 64 * NWAVES == A_STAGE && B_LOADS * 64 * NWAVES == B_STAGE && A_LOADS % 2 == 0,
+                "instructions must divide evenly over the wavefronts");
+  const bf16_t *a_src[A_LOADS], *b_src[B_LOADS];
+  const int l_row = (wave * 64 + lane) >> 3, l_cs = lane & 7;  // row and chunk position of this thread's first chunk
 #pragma unroll
-  for (int u = 0; u < PER_WAVE; ++u) {
-    const int i = wave + u * (NTHREADS / 64);
-    const int pos = i * 64 + lane;            // chunk position inside the stage
-    const bool isb = pos >= BM * 8;
-    const int r = (isb ? pos - BM * 8 : pos) >> 3, cs = pos & 7;
-    const int c = cs ^ ((r & 7) ^ ((r >> 3) & 1));  // inverse of swz(): the chunk stored at this position
-    if (!isb) {
-      long long gr = m0 + r;
-      gr = gr < M ? gr : M - 1;
-      g_src[u] = A + gr * K + c * 8;
-    } else {
-      int gr = n0 + r;
-      gr = gr < N ? gr : N - 1;
-      g_src[u] = Bt + (long long)gr * K + c * 8;
-    }
+  for (int u = 0; u < A_LOADS; ++u) {
+    const int r = l_row + u * (NTHREADS / 8), c = l_cs ^ ((r & 7) ^ ((r >> 3) & 1));  // inverse of swz()
+    const long long gr = m0 + r;
+    a_src[u] = A + (gr < M ? gr : M - 1) * K + c * 8;
+  }
+#pragma unroll
+  for (int u = 0; u < B_LOADS; ++u) {
+    const int r = l_row + u * (NTHREADS / 8), c = l_cs ^ ((r & 7) ^ ((r >> 3) & 1));
+    const int gr = n0 + r;
+    b_src[u] = Bt + (long long)(gr < N ? gr : N - 1) * K + c * 8;
   }
   typedef __attribute__((address_space(3))) void lds_void;
   typedef __attribute__((address_space(1))) void glb_void;
-  auto issue_slab = [&](int k0, int buf) {
+  auto issue_a = [&](int kt, int stage, int u0, int u1) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < PER_WAVE; ++u) {
-      const int i = wave + u * (NTHREADS / 64);
-      __builtin_amdgcn_global_load_lds((glb_void *)(g_src[u] + k0), (lds_void *)(sbase + buf * STAGE + i * 64), 16, 0, 0);
-    }
+    for (int u = u0; u < u1; ++u)
+      __builtin_amdgcn_global_load_lds((glb_void *)(a_src[u] + kt * BK), (lds_void *)(sA + stage * A_STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
+  };
+  auto issue_b = [&](int kt, int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < B_LOADS; ++u)
+      __builtin_amdgcn_global_load_lds((glb_void *)(b_src[u] + kt * BK), (lds_void *)(sB + stage * B_STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
   };
 
   f32x16 acc[NI][MI];
@@ -183,56 +189,64 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[ni][mi][r] = 0.f;
+  // two sets of fragments: those of k-step kk+1 are requested before the MFMAs of k-step kk are issued
+  bf16x8 fa[2][MI], fb[2][NI];
+  auto read_frags = [&](int a_stage, int b_stage, int kk, int set) __attribute__((always_inline)) {
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+      fa[set][mi] = __builtin_bit_cast(bf16x8, sA[a_stage * A_STAGE + swz(wm * WM + mi * 32 + l32, kk * 2 + half)]);
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+      fb[set][ni] = __builtin_bit_cast(bf16x8, sB[b_stage * B_STAGE + swz(wn * WN + ni * 32 + l32, kk * 2 + half)]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+        acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][ni], fa[set][mi], acc[ni][mi], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
   const int nk = K / BK;
-  issue_slab(0, 0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  // Within a slab the fragments of k-step kk+1 are requested before the MFMAs of k-step kk are issued (two register
-  // sets): only the first k-step of a slab, right after the slab barrier, pays its LDS latency in the open.
-  // Warm same-box A/B: the projections timed alone, back to back, are 2-5 % SLOWER this way (102 -> 104, 74 -> 78 us),
-  // the forward pass they are part of is 0.8 % faster (0.668 -> 0.6625 ms, repeated in both orders): inside a pass
-  // their operands come from further away than in a loop over the same GEMM.
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    bf16x8 fa[2][MI], fb[2][NI];
-    auto read_frags = [&](int kk, int set) {
-#pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        const int r = wm * WM + mi * 32 + l32;
-        fa[set][mi] = __builtin_bit_cast(bf16x8, sbase[buf * STAGE + swz(r, kk * 2 + half)]);
-      }
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) {
-        const int r = wn * WN + ni * 32 + l32;
-        fb[set][ni] = __builtin_bit_cast(bf16x8, sbase[buf * STAGE + BM * 8 + swz(r, kk * 2 + half)]);
-      }
-    };
-    read_frags(0, 0);
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      // the loads of slab kt+1 are issued over the first SPREAD k-steps: not in one burst (the LDS write port), not
-      // over all four either (the last quarter then has a fraction of a slab to land before the wait below).
-      // Warm same-box A/B of the whole forward pass: spread over 4 / 3 / 2 / 1 steps 0.6935 / 0.687 / 0.6865 / 0.690 ms
-      if (kt + 1 < nk && kk < SPREAD) {
-#pragma unroll
-        for (int u = kk * PER_WAVE / SPREAD; u < (kk + 1) * PER_WAVE / SPREAD; ++u) {
-          const int i = wave + u * (NTHREADS / 64);
-          __builtin_amdgcn_global_load_lds((glb_void *)(g_src[u] + (kt + 1) * BK), (lds_void *)(sbase + (buf ^ 1) * STAGE + i * 64), 16, 0, 0);
-        }
-      }
-      if (kk + 1 < BK / 16) read_frags(kk + 1, (kk + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-          acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk & 1][ni], fa[kk & 1][mi], acc[ni][mi], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  issue_b(0, 0);
+  issue_a(0, 0, 0, A_LOADS);
+  if (nk > 1) {
+    issue_b(1, 1);
+    issue_a(1, 1, 0, A_LOADS);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(A_LOADS + B_LOADS) : "memory");
+  } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
   }
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read_frags(0, 0, 0, 0);
+  int as = 0;  // stage of A that holds slab kt
+  for (int kt = 0; kt < nk; ++kt) {
+    const int bs = kt & 1, as1 = as == 2 ? 0 : as + 1, as2 = as1 == 2 ? 0 : as1 + 1;
+    const bool ahead = kt + 2 < nk;
+    if (ahead) issue_a(kt + 2, as2, 0, A_LOADS / 2);  // into the stage of slab kt - 1
+    read_frags(as, bs, 1, 1);
+    multiply(0);
+    if (ahead) issue_a(kt + 2, as2, A_LOADS / 2, A_LOADS);
+    read_frags(as, bs, 2, 0);
+    multiply(1);
+    read_frags(as, bs, 3, 1);
+    multiply(0);
+    if (kt + 1 < nk) {
+      // slab kt + 1 has landed when no more than the newest loads, A of slab kt + 2, are outstanding
+      if (ahead) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(A_LOADS) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (ahead) issue_b(kt + 2, bs);  // every wavefront holds its last fragments of slab kt
+      read_frags(as1, bs ^ 1, 0, 0);
+    }
+    multiply(1);
+    as = as1;
+  }
+  __syncthreads();
   store_tile_bf16<BM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N, split);
 }
 
@@ -589,8 +603,9 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
   const int total = tiles_m * tiles_n;
   const int per_xcd = (total + 7) / 8;
   constexpr size_t epi_bytes = (size_t)BM * (BN * 2 + 16);
-  constexpr size_t main_bytes = 2ull * (BM + BN) * BK * 2;
+  constexpr size_t main_bytes = (size_t)(A_STAGES * BM + B_STAGES * BN) * BK * 2;
   constexpr size_t smem = main_bytes > epi_bytes ? main_bytes : epi_bytes;
+  static_assert(smem <= 160 * 1024, "LDS");
   if (hipError_t e = raise_lds_limit<gemm_bf16_nt_kernel<BN, WAVES_M, WAVES_N>>(smem); e != hipSuccess) return e;
   gemm_bf16_nt_kernel<BN, WAVES_M, WAVES_N><<<per_xcd * 8, WAVES_M * WAVES_N * 64, smem, s>>>((const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N,
                                                              K, tiles_n, total, split);

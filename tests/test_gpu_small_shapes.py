@@ -54,6 +54,19 @@ def test_projection_tiles(M, Hq, Hk, dh, E):
     check_product(out[0], o[0].double() @ w_out.double(), cfg.e_q)
 
 
+@pytest.mark.parametrize("slabs", [1, 2, 3, 4])
+@pytest.mark.parametrize("M,tile", [(9001, "256x192"), (33001, "256x256")])
+def test_projection_of_few_slabs_on_large_tiles(M, tile, slabs):
+    """Contractions shorter than the three slabs of A and two of the weight that the 256-row kernel holds, and just longer."""
+    say("projection", M, slabs)
+    cfg = P.CCAConfig(B=1, T=M, d_model=1024, n_q_heads=slabs, n_kv_heads=1, head_dim=64)
+    assert rules.nt_tile(M, 1024, 64 * slabs) == tile
+    o, w_out = rnd(1, M, cfg.e_q, seed=3), rnd(cfg.e_q, 1024, seed=4, scale=0.02)
+    out = P.cca_up_project(cfg, o, w_out)
+    torch.cuda.synchronize()
+    check_product(out[0], o[0].double() @ w_out.double(), cfg.e_q)
+
+
 # token rows x (query heads, head width, E): d W_out (e_q, E) = o^T d_out on every tile shape of the weight-gradient GEMM
 # (64 x 64, 64 x 128, 128 x 128, split 256 x 256), with no, one and a few tokens in the last slab of 64; the last three split, on
 # a number of tiles that 8 does not divide and on widths that are no multiple of the 32 x 32 blocks of the partial sums
