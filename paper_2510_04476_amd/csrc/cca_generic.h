@@ -33,7 +33,7 @@ __device__ __forceinline__ int tile_row(int r, int half) { return 8 * (r >> 2) +
 // acc += rows . cols over `dh` channels (a multiple of 4): row l32 of the tile at `rows` (this lane's row), column l32 in LDS
 // at `cols`, zero from dh up to DHM.
 template <int DHM, typename T, typename F>
-__device__ __forceinline__ gen_f32x16 dot_tile(const T *rows, const float *cols, int dh, int half, F &&map) {
+__device__ __forceinline__ gen_f32x16 dot_tile32(const T *rows, const float *cols, int dh, int half, F &&map) {
   gen_f32x16 acc = zero16();
 #pragma unroll 4
   for (int c = 0; c < DHM; c += 8) {
@@ -51,7 +51,7 @@ __device__ __forceinline__ gen_f32x16 dot_tile(const T *rows, const float *cols,
 // pair is masked, and a masked row must not count even where it holds an infinity or NaN (0 * inf): then, and only if such
 // a value is there, the sum runs on the vector ALU and skips zero weights.
 template <int DT, typename T, typename Row>
-__device__ __forceinline__ void add_outer(gen_f32x16 (&acc)[DT], const float (&w)[16], Row &&row, int dh, int lane, bool mixed) {
+__device__ __forceinline__ void add_outer32(gen_f32x16 (&acc)[DT], const float (&w)[16], Row &&row, int dh, int lane, bool mixed) {
   const int l32 = lane & 31, half = lane >> 5;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
@@ -89,14 +89,198 @@ __device__ __forceinline__ void add_outer(gen_f32x16 (&acc)[DT], const float (&w
   }
 }
 
-// 32 rows of `dh` channels -> LDS [32][DHM + 4] floats (rows padded by 16 bytes: conflict-free 16-byte reads down a column
-// of rows), times `map`; rows past `last` repeat it, channels from dh on are zero.
+// ---- 16 x 16 tiles (attention): v_mfma_f32_16x16x4_f32 -------------------------------------------------------------------
+// Lane (l16, g), g = lane / 16, supplies term g of row l16 and of column l16; the result sits as D[4 g + r][l16] in register
+// r, which is again the order of a second operand when MFMA i takes the terms 4 g + i.  Half the rows of the 32 x 32 form: twice
+// the workgroups and half the accumulators for the same rate.
+
+// rows . cols over `dh` channels (a multiple of 4): row l16 of the tile at `rows` (this lane's row), column l16 in LDS
+// at `cols`, zero from dh up to DHM.
 template <int DHM, typename T, typename F>
-__device__ __forceinline__ void stage_rows32(float *dst, const T *base, long long stride, int first, int last, int dh, F &&map) {
-  for (int i = threadIdx.x; i < 32 * DHM; i += blockDim.x) {
+__device__ __forceinline__ gen_f32x4 dot_tile16(const T *rows, const float *cols, int dh, int g, F &&map) {
+  gen_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int CHUNK = DHM <= 64 ? 32 : 64;  // channels in flight
+#pragma unroll 1
+  for (int c0 = 0; c0 < DHM; c0 += CHUNK)
+#pragma unroll
+    for (int c = 0; c < CHUNK; c += 16) {
+      const int ch = c0 + c + 4 * g;
+      gen_f32x4 a = load4(rows + (ch < dh ? ch : 0));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = ch < dh ? map(a[i]) : 0.f;
+      const gen_f32x4 b = load4(cols + ch);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], acc, 0, 0, 0);
+    }
+  return acc;
+}
+
+// add_outer32 for 16 rows: acc[dt][.] (rows: channels 16 dt + ..., column: this lane's)
+template <int DT, typename T, typename Row>
+__device__ __forceinline__ void add_outer16(gen_f32x4 (&acc)[DT], const gen_f32x4 &w, Row &&row, int dh, int lane, bool mixed) {
+  const int l16 = lane & 15, g = lane >> 4;
+  const T *p[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) p[i] = static_cast<const T *>(row(4 * g + i));
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) {
+    const int ch = 16 * dt + l16;
+    float x[4];
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = load_f(p[i] + (ch < dh ? ch : 0));
+      x[i] = ch < dh ? x[i] : 0.f;
+      bad |= !(fabsf(x[i]) < INFINITY);
+    }
+    if (mixed && __any(bad)) {
+#pragma unroll 1
+      for (int k = 0; k < 16; ++k) {
+        float wk = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float o = __shfl(w[i], l16 + 16 * (k >> 2));
+          wk = i == (k & 3) ? o : wk;
+        }
+        const T *pk = static_cast<const T *>(row(k));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = 16 * dt + 4 * g + r;
+          const float v = load_f(pk + (c < dh ? c : 0));
+          acc[dt][r] = wk != 0.f && c < dh ? fmaf(v, wk, acc[dt][r]) : acc[dt][r];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], w[i], acc[dt], 0, 0, 0);
+    }
+  }
+}
+
+// ROWS rows of `dh` channels -> LDS [ROWS][DHM + 4] floats (rows padded by 16 bytes), times `map`; rows past `last` repeat it,
+// channels from dh on are zero.
+template <int DHM, int ROWS, typename T, typename F>
+__device__ __forceinline__ void stage_rows(float *dst, const T *base, long long stride, int first, int last, int dh, F &&map) {
+  for (int i = threadIdx.x; i < ROWS * DHM; i += blockDim.x) {
     const int r = i / DHM, c = i % DHM;
     const float v = load_f(base + (long long)(first + r < last ? first + r : last) * stride + (c < dh ? c : 0));
     dst[r * (DHM + 4) + c] = c < dh ? map(v) : 0.f;
+  }
+}
+
+// Threads of an attention workgroup: the 16-row form's at most (beyond d_h = 64 the accumulators want more than the 128 registers that 1024 leave), and
+// output tiles whose partial sums are added in one go
+constexpr int G32_NT = 512, G32_WAVES = G32_NT / 64;  // the 32-row form
+template <int DHM>
+constexpr int G16_NT = DHM <= 64 ? 1024 : 512;
+constexpr int G16_TILES = 2;
+typedef float G16Partial[G16_TILES][4][64];
+
+// Sums of the wavefronts' accumulators, each times f(wavefront) where that is not 0, in wavefront order: out(channel, sum) once
+// per element of the tile, for column l16 of the calling lane.
+template <int WAVES, int DT, typename W, typename F>
+__device__ __forceinline__ void sum_wavefronts16(const gen_f32x4 (&acc)[DT], G16Partial *so, W &&weight, F &&out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int d0 = 0; d0 < DT; d0 += G16_TILES) {
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < G16_TILES; ++x)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) so[wave][x][r][lane] = acc[d0 + x][r];
+    __syncthreads();
+    static_assert(WAVES >= G16_TILES * 4, "a wavefront per register of the tiles");
+    if (wave < G16_TILES * 4) {
+      const int x = wave >> 2, r = wave & 3;
+      float sum = 0.f;
+#pragma unroll
+      for (int y = 0; y < WAVES; ++y) {
+        const float f = weight(y);
+        sum += f == 0.f ? 0.f : so[y][x][r][lane] * f;
+      }
+      out(16 * (d0 + x) + 4 * (lane >> 4) + r, sum);
+    }
+  }
+}
+
+// ---- prologue and its adjoint: one head x 32 tokens of a sequence per workgroup of four wavefronts ------------------------
+constexpr int GP_NT = 256, GP_WAVES = GP_NT / 64, GP_TOK = 32;
+constexpr int GP_RED = GP_WAVES * 16 * 64;       // floats of gp_sum's buffer
+constexpr size_t GP_MAX_LDS = 160 * 1024;
+constexpr long long GP_GRID = 1ll << 23;         // workgroups of a launch, which takes fewer than 2^32 threads in one dimension
+// Launches `go(first block, blocks)` over B sequences of T tokens
+template <typename F>
+inline hipError_t gp_launches(int B, int T, F &&go) {
+  const long long blocks = (long long)((T + GP_TOK - 1) / GP_TOK) * B;
+  for (long long x = 0; x < blocks; x += GP_GRID) {
+    go((unsigned)x, (unsigned)(blocks - x < GP_GRID ? blocks - x : GP_GRID));
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// cos, sin of the RoPE angles of `rows` tokens from t0 on, (token, pair) to sa[2 (token * d_h / 2 + pair)].  fp64: t * theta loses
+// ~1e-3 rad in fp32 at t ~ 16k.  A thread takes one pair and a run of tokens, whose angles follow from the first by rotation in fp64
+// (the error grows by 1e-16 a token).
+__device__ __forceinline__ void rope_angles(float *sa, float base, int dh, int t0, int rows) {
+  const int half = dh / 2, runs = GP_NT / half > 0 ? GP_NT / half : 1, len = (rows + runs - 1) / runs;
+  for (int id = threadIdx.x; id < half * runs; id += GP_NT) {
+    const int p = id % half, x0 = id / half * len;
+    const double theta = pow((double)base, -2.0 * (double)p / (double)dh);
+    double sn, cs, s1 = 0.0, c1 = 1.0;
+    sincos((double)(t0 + x0) * theta, &sn, &cs);
+    if (len > 1) sincos(theta, &s1, &c1);
+    for (int x = x0; x < x0 + len && x < rows; ++x) {
+      sa[2 * (x * half + p)] = (float)cs;
+      sa[2 * (x * half + p) + 1] = (float)sn;
+      const double c2 = cs * c1 - sn * s1;
+      sn = sn * c1 + cs * s1;
+      cs = c2;
+    }
+  }
+}
+
+// This wavefront's share of sum_n A[row][n] B[n][column] over n < terms (a multiple of 4): lane (l32, half) supplies row l32 as
+// a(n) and column l32 as b(n).
+template <typename FA, typename FB>
+__device__ __forceinline__ gen_f32x16 gp_product(int terms, FA &&a, FB &&b) {
+  const int half = (threadIdx.x >> 5) & 1, wave = threadIdx.x >> 6;
+  gen_f32x16 acc = zero16();
+  constexpr int AHEAD = 2;  // blocks of 8 terms in flight (the compiler does not unroll a loop of MFMAs with an unknown count)
+  for (int b0 = wave * 8; b0 < terms; b0 += AHEAD * GP_WAVES * 8) {
+    float x[AHEAD][4], y[AHEAD][4];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const int n0 = b0 + u * GP_WAVES * 8 + 4 * half;
+      const bool in = n0 < terms;  // a multiple of 4: the four terms of a lane are in or out together
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float va = a(in ? n0 + i : i), vb = b(in ? n0 + i : i);
+        x[u][i] = in ? va : 0.f, y[u][i] = in ? vb : 0.f;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u][i], y[u][i], acc, 0, 0, 0);
+  }
+  return acc;
+}
+// The wavefronts' shares added in order: out(row, column, sum) once per element of the 32 x 32 tile
+template <typename F>
+__device__ __forceinline__ void gp_sum(const gen_f32x16 &acc, float *red, F &&out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[(wave * 16 + r) * 64 + lane] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < 16 / GP_WAVES; ++x) {
+    const int r = wave * (16 / GP_WAVES) + x;
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < GP_WAVES; ++w) sum += red[(w * 16 + r) * 64 + lane];
+    out(tile_row(r, lane >> 5), lane & 31, sum);
   }
 }
 

@@ -17,7 +17,7 @@ namespace cca {
 constexpr int GG_NT = 512, GG_WAVES = GG_NT / 64;
 constexpr long long GG_GRID = 1ll << 22;  // tiles of a launch, which takes fewer than 2^32 threads in one dimension
 
-template <typename T, bool TA, bool TB>
+template <typename T, bool TA, bool TB, int AHEAD>
 __global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict__ A, long long lda, const T *__restrict__ Bm,
                                                             long long ldb, T *__restrict__ C, long long ldc, long long M, int N,
                                                             long long K, unsigned tile0) {
@@ -30,30 +30,42 @@ __global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict
   const int n = n0 + l32 < N ? n0 + l32 : N - 1;
   gen_f32x16 acc = zero16();
   const long long last = K - 1;
-#pragma unroll 4
-  for (long long k0 = wave * 8 + 4 * half; k0 - 4 * half < K; k0 += GG_WAVES * 8) {
-    float a[4], b[4];
-    // terms past K: some readable value, dropped below
-    if constexpr (TA) {
+  // AHEAD blocks of 8 terms in flight (the compiler does not unroll a loop of MFMAs whose count it does not know).  Four where the
+  // chain of a wavefront is what a small grid waits for (256 x 192 over 1000 tokens 12.1 -> 6.5 us); a large one hides its loads behind more
+  // wavefronts, which four blocks' registers do not leave (4096 x 1024 over 512: 62.5 us with one, 66.6 with four).
+  for (long long b0 = wave * 8; b0 < K; b0 += AHEAD * GG_WAVES * 8) {
+    float a[AHEAD][4], b[AHEAD][4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = load_f(A + (k0 + i < last ? k0 + i : last) * lda + m);
-    } else {
-      const gen_f32x4 v = load4(A + m * lda + (k0 < K ? k0 : 0));
+    for (int u = 0; u < AHEAD; ++u) {
+      if (u > 0 && b0 + u * GG_WAVES * 8 >= K) break;
+      const long long k0 = b0 + u * GG_WAVES * 8 + 4 * half;
+      // terms past K: some readable value, dropped below
+      if constexpr (TA) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = v[i];
+        for (int i = 0; i < 4; ++i) a[u][i] = load_f(A + (k0 + i < last ? k0 + i : last) * lda + m);
+      } else {
+        const gen_f32x4 v = load4(A + m * lda + (k0 < K ? k0 : 0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[u][i] = v[i];
+      }
+      if constexpr (TB) {
+        const gen_f32x4 v = load4(Bm + n * ldb + (k0 < K ? k0 : 0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[u][i] = v[i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[u][i] = load_f(Bm + (k0 + i < last ? k0 + i : last) * ldb + n);
+      }
     }
-    if constexpr (TB) {
-      const gen_f32x4 v = load4(Bm + n * ldb + (k0 < K ? k0 : 0));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) b[i] = v[i];
-    } else {
+    for (int u = 0; u < AHEAD; ++u) {
+      if (u > 0 && b0 + u * GG_WAVES * 8 >= K) break;
+      const long long k0 = b0 + u * GG_WAVES * 8 + 4 * half;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) b[i] = load_f(Bm + (k0 + i < last ? k0 + i : last) * ldb + n);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool in = k0 + i < K;
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a[i] : 0.f, in ? b[i] : 0.f, acc, 0, 0, 0);
+      for (int i = 0; i < 4; ++i) {
+        const bool in = k0 + i < K;
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a[u][i] : 0.f, in ? b[u][i] : 0.f, acc, 0, 0, 0);
+      }
     }
   }
 #pragma unroll
@@ -76,8 +88,9 @@ static hipError_t gemm_generic_t(const void *A, long long lda, bool ta, const vo
   if (tiles > UINT32_MAX) return hipErrorInvalidValue;  // (2^42 outputs)
   for (long long t = 0; t < tiles; t += GG_GRID) {  // one launch below 2^32 outputs; a second grid dimension cost 0.2 of 2.8 us
     const unsigned grid = (unsigned)(tiles - t < GG_GRID ? tiles - t : GG_GRID);
-#define GO(TA, TB)                                                                                                          \
-  gemm_generic_kernel<T, TA, TB><<<grid, GG_NT, 0, s>>>((const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K, (unsigned)t)
+#define GO(TA, TB)                                                                                                        \
+  (tiles <= 1024 ? gemm_generic_kernel<T, TA, TB, 4> : gemm_generic_kernel<T, TA, TB, 1>)<<<grid, GG_NT, 0, s>>>(              \
+      (const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K, (unsigned)t)
     if (ta && tb) GO(true, true);
     else if (ta) GO(true, false);
     else if (tb) GO(false, true);
@@ -100,8 +113,11 @@ hipError_t gemm_generic(bool bf16, const void *A, const void *Bm, void *C, long 
 }
 
 // ---------------------------------------------------------------------------
-// Prologue: one workgroup per (token, head).  Heads 0..Hq-1 are query heads,
-// Hq..Hq+Hk-1 key heads, Hq+Hk..Hq+2Hk-1 value heads.
+// Prologue: one workgroup per head and 32 tokens of a sequence.  Heads 0..Hq-1 are query heads,
+// Hq..Hq+Hk-1 key heads, Hq+Hk..Hq+2Hk-1 value heads.  conv2_seq+ch is a product on the fp32 matrix cores (outputs x tokens),
+// its terms (input, tap) dealt to the four wavefronts, so a filter is read once per 32 tokens.
+// fp32, us, a workgroup per token on the vector ALU -> this: 1000 tokens, 2 / 2 heads of 32 21.3 -> 9.0; 500, 2 / 2 x 64 36.0 -> 14.7;
+// 4096, 4 / 2 x 128 1418 -> 72.
 // ---------------------------------------------------------------------------
 struct PrologueArgs {
   int T, Hq, Hk, dh, R, e_q, e_kv, n_lat, v_half, k_seq, k_ch;
@@ -110,26 +126,23 @@ struct PrologueArgs {
 };
 
 template <typename T>
-__global__ void prologue_generic_kernel(PrologueArgs a, const T *__restrict__ lat, const T *__restrict__ w0,
-                                        const T *__restrict__ w1, const float *__restrict__ temp,
-                                        T *__restrict__ q, T *__restrict__ k, T *__restrict__ v,
-                                        float *__restrict__ rnorm) {
-  extern __shared__ float sm[];  // y0[k_ch][dh] | red[blockDim] | yrot[dh]
-  const long long row = blockIdx.x;  // b*T + t
-  const int t = (int)(row % a.T);
-  const int head = blockIdx.y;
-  const int dh = a.dh;
-  const int tid = threadIdx.x;
+__global__ __launch_bounds__(GP_NT) void prologue_generic_kernel(PrologueArgs a, const T *__restrict__ lat, const T *__restrict__ w0,
+                                                                const T *__restrict__ w1, const float *__restrict__ temp,
+                                                                T *__restrict__ q, T *__restrict__ k, T *__restrict__ v,
+                                                                float *__restrict__ rnorm, unsigned block0) {
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  const int head = blockIdx.y, dh = a.dh, tid = threadIdx.x;
+  const unsigned tiles = (a.T + GP_TOK - 1) / GP_TOK, block = block0 + blockIdx.x;
+  const long long row0 = (long long)(block / tiles) * a.T;  // the sequence's first row
+  const int t0 = block % tiles * GP_TOK, n_tok = min(GP_TOK, a.T - t0);
 
   if (head >= a.Hq + a.Hk) {  // value head: copy, second stream delayed by one token
     const int g = head - a.Hq - a.Hk;
-    for (int i = tid; i < dh; i += blockDim.x) {
-      const int c = g * dh + i;  // channel within e_kv
-      float val;
-      if (c < a.v_half || !(a.flags & CCA_V_SHIFT))
-        val = load_f(lat + row * a.n_lat + a.e_q + a.e_kv + c);
-      else
-        val = (t == 0) ? 0.f : load_f(lat + (row - 1) * a.n_lat + a.e_q + a.e_kv + c);
+    for (int id = tid; id < n_tok * dh; id += GP_NT) {
+      const int t = t0 + id / dh, c = g * dh + id % dh;  // channel within e_kv
+      const bool late = c >= a.v_half && (a.flags & CCA_V_SHIFT);
+      const long long row = row0 + t;
+      const float val = late && t == 0 ? 0.f : load_f(lat + (late ? row - 1 : row) * a.n_lat + a.e_q + a.e_kv + c);
       store_f(v + row * a.e_kv + c, val);
     }
     return;
@@ -139,43 +152,52 @@ __global__ void prologue_generic_kernel(PrologueArgs a, const T *__restrict__ la
   const int ch0 = is_q ? head * dh : a.e_q + (head - a.Hq) * dh;  // first packed q|k channel of this head
   const int kc = (a.flags & CCA_CONV_CH) ? a.k_ch : 1;
   const int ks = (a.flags & CCA_CONV_SEQ) ? a.k_seq : 1;
-  float *y0 = sm;                 // [kc][dh]
-  float *red = sm + kc * dh;      // [blockDim.x]
-  float *yrot = red + blockDim.x; // [dh]
+  const int rows = GP_TOK + kc - 1, ldy = dh + 1;
+  float *const y0 = sm;                                    // [rows][ldy]: conv1_seq output from token t0 - (kc - 1) on
+  float *const z = y0 + rows * ldy;                        // [32][ldy]
+  float *const sa = z + GP_TOK * ldy, *const red = sa + GP_TOK * dh;  // cos, sin | sums of the wavefronts
 
-  // conv1_seq output at the kc time steps conv2 needs (zero before the sequence start)
-  for (int idx = tid; idx < kc * dh; idx += blockDim.x) {
-    const int j = idx / dh, i = idx % dh;
-    const int tj = t - (kc - 1) + j;
+  // conv1_seq output at the time steps conv2 needs (zero before the sequence start)
+  for (int id = tid; id < rows * dh; id += GP_NT) {
+    const int i = id % dh, tj = t0 - (kc - 1) + id / dh;
     float acc = 0.f;
-    if (tj >= 0) {
+    if (tj >= 0 && tj < a.T) {
       if (a.flags & CCA_CONV_SEQ) {
         for (int jj = 0; jj < ks; ++jj) {
           const int ts = tj - (ks - 1) + jj;
-          if (ts >= 0)
-            acc = fmaf(load_f(w0 + (long long)(ch0 + i) * ks + jj),
-                       load_f(lat + (row - t + ts) * a.n_lat + ch0 + i), acc);
+          if (ts >= 0) acc = fmaf(load_f(w0 + (long long)(ch0 + i) * ks + jj), load_f(lat + (row0 + ts) * a.n_lat + ch0 + i), acc);
         }
       } else {
-        acc = load_f(lat + (row - t + tj) * a.n_lat + ch0 + i);
+        acc = load_f(lat + (row0 + tj) * a.n_lat + ch0 + i);
       }
     }
-    y0[idx] = acc;
+    y0[id / dh * ldy + i] = acc;
+  }
+  if (a.flags & CCA_ROPE) rope_angles(sa, a.rope_base, dh, t0, GP_TOK);
+  __syncthreads();
+  if (a.flags & CCA_CONV_CH) {
+    const int l32 = tid & 31;
+    for (int o0 = 0; o0 < dh; o0 += 32) {
+      const int o = o0 + l32 < dh ? o0 + l32 : dh - 1;  // past the head: results not kept
+      const T *const wp = w1 + ((long long)head * dh + o) * dh * kc;
+      const gen_f32x16 acc = gp_product(
+          dh * kc, [&](int n) { return load_f(wp + n); }, [&](int n) { return y0[(l32 + n % kc) * ldy + n / kc]; });
+      gp_sum(acc, red, [&](int r, int tok, float sum) {
+        if (o0 + r < dh) z[tok * ldy + o0 + r] = sum;
+      });
+    }
+  } else {
+    for (int id = tid; id < GP_TOK * dh; id += GP_NT) z[id / dh * ldy + id % dh] = y0[id / dh * ldy + id % dh];
   }
   __syncthreads();
-
+  // 8 lanes to a token: mean, norm
+  static_assert(GP_NT == 8 * GP_TOK, "lanes of a token");
+  const int x = tid >> 3, l8 = tid & 7, t = t0 + x;
+  const long long row = row0 + min(t, a.T - 1);
   float ssq = 0.f;
-  // each thread owns output channels o = tid, tid + blockDim, ...
-  for (int o = tid; o < dh; o += blockDim.x) {
-    float y;
-    if (a.flags & CCA_CONV_CH) {
-      y = 0.f;
-      const T *wp = w1 + ((long long)head * dh + o) * dh * kc;
-      for (int i = 0; i < dh; ++i)
-        for (int j = 0; j < kc; ++j) y = fmaf(load_f(wp + i * kc + j), y0[j * dh + i], y);
-    } else {
-      y = y0[(kc - 1) * dh + o];
-    }
+#pragma unroll 4
+  for (int o = l8; o < dh; o += 8) {
+    float y = z[x * ldy + o];
     if (a.flags & CCA_QK_MEAN) {
       float m;
       if (is_q) {
@@ -188,42 +210,33 @@ __global__ void prologue_generic_kernel(PrologueArgs a, const T *__restrict__ la
         m = 0.5f * (sq / (float)a.R + load_f(lat + row * a.n_lat + a.e_q + g * dh + o));
       }
       y += m;
+      z[x * ldy + o] = y;
     }
-    yrot[o] = y;
     ssq = fmaf(y, y, ssq);
   }
-  red[tid] = ssq;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (tid < s) red[tid] += red[tid + s];
-    __syncthreads();
-  }
+#pragma unroll
+  for (int e = 1; e < 8; e *= 2) ssq += __shfl_xor(ssq, e);
   float mul = 1.f;
   if (a.flags & CCA_QK_NORM) {
-    mul = sqrtf((float)dh) / sqrtf(red[0] + a.norm_eps);
+    mul = sqrtf((float)dh) / sqrtf(ssq + a.norm_eps);
     if (!is_q && (a.flags & CCA_KEY_TEMP)) mul *= expf(temp[head - a.Hq]);
   }
-  if (rnorm && tid == 0) rnorm[row * (a.Hq + a.Hk) + head] = mul;
-  T *dst = is_q ? q + row * a.e_q + head * dh : k + row * a.e_kv + (head - a.Hq) * dh;
-  for (int o = tid; o < dh; o += blockDim.x) {
-    float y = yrot[o] * mul;
-    if (a.flags & CCA_ROPE) {
-      const int half = dh / 2;
-      int pair, partner;
-      bool first;
-      if (a.flags & CCA_ROPE_INTERLEAVED) {
-        pair = o / 2; first = (o % 2) == 0; partner = first ? o + 1 : o - 1;
-      } else {
-        pair = o % half; first = o < half; partner = first ? o + half : o - half;
-      }
-      // angle in fp64: t * theta loses ~1e-3 rad in fp32 at t ~ 16k
-      const double theta = pow((double)a.rope_base, -2.0 * (double)pair / (double)dh);
-      double sn, cs;
-      sincos((double)t * theta, &sn, &cs);
-      const float yp = yrot[partner] * mul;
-      y = first ? (y * (float)cs - yp * (float)sn) : (y * (float)cs + yp * (float)sn);
+  if (rnorm && l8 == 0 && t < a.T) rnorm[row * (a.Hq + a.Hk) + head] = mul;
+  __syncthreads();
+  if (t >= a.T) return;
+  T *const dst = is_q ? q + row * a.e_q + head * dh : k + row * a.e_kv + (head - a.Hq) * dh;
+  if (a.flags & CCA_ROPE) {
+    const int half = dh / 2;
+    const bool il = a.flags & CCA_ROPE_INTERLEAVED;
+    for (int p = l8; p < half; p += 8) {
+      const int first = il ? 2 * p : p, second = il ? 2 * p + 1 : p + half;
+      const float cs = sa[2 * (x * half + p)], sn = sa[2 * (x * half + p) + 1];
+      const float u = z[x * ldy + first] * mul, w = z[x * ldy + second] * mul;
+      store_f(dst + first, u * cs - w * sn);
+      store_f(dst + second, w * cs + u * sn);
     }
-    store_f(dst + o, y);
+  } else {
+    for (int o = l8; o < dh; o += 8) store_f(dst + o, z[x * ldy + o] * mul);
   }
 }
 
@@ -231,53 +244,52 @@ hipError_t prologue_generic(const Dims &d, const cca_weights &w, const void *lat
                             float *rnorm, hipStream_t s) {
   PrologueArgs a{d.T, d.Hq, d.Hk, d.dh, d.R, d.e_q, d.e_kv, d.n_lat, d.v_half, d.k_seq, d.k_ch, d.flags, d.rope_base,
                  d.norm_eps};
-  int threads = 64;
-  while (threads < d.dh && threads < 256) threads *= 2;
   const int kc = (d.flags & CCA_CONV_CH) ? d.k_ch : 1;
-  size_t smem = sizeof(float) * ((size_t)kc * d.dh + threads + d.dh);
-  dim3 grid((unsigned)d.rows(), d.Hq + 2 * d.Hk);
-  if (d.bf16)
-    prologue_generic_kernel<bf16_t><<<grid, threads, smem, s>>>(a, (const bf16_t *)lat, (const bf16_t *)w.w_conv_seq,
-                                                               (const bf16_t *)w.w_conv_ch, w.temp, (bf16_t *)q,
-                                                               (bf16_t *)k, (bf16_t *)v, rnorm);
-  else
-    prologue_generic_kernel<float><<<grid, threads, smem, s>>>(a, (const float *)lat, (const float *)w.w_conv_seq,
-                                                              (const float *)w.w_conv_ch, w.temp, (float *)q,
-                                                              (float *)k, (float *)v, rnorm);
-  return hipGetLastError();
+  const size_t smem = sizeof(float) * ((size_t)(2 * GP_TOK + kc - 1) * (d.dh + 1) + (size_t)GP_TOK * d.dh + GP_RED);
+  auto run = [&](auto kernel, auto *lat_, auto *q_, auto *k_, auto *v_, auto *w0, auto *w1) {
+    return gp_launches(d.B, d.T, [&](unsigned first, unsigned blocks) {
+      kernel<<<dim3(blocks, d.Hq + 2 * d.Hk), GP_NT, smem, s>>>(a, lat_, w0, w1, w.temp, q_, k_, v_, rnorm, first);
+    });
+  };
+  if (d.bf16) {
+    if (hipError_t e = raise_lds_limit<prologue_generic_kernel<bf16_t>>(GP_MAX_LDS); e != hipSuccess) return e;
+    return run(prologue_generic_kernel<bf16_t>, (const bf16_t *)lat, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v,
+               (const bf16_t *)w.w_conv_seq, (const bf16_t *)w.w_conv_ch);
+  }
+  if (hipError_t e = raise_lds_limit<prologue_generic_kernel<float>>(GP_MAX_LDS); e != hipSuccess) return e;
+  return run(prologue_generic_kernel<float>, (const float *)lat, (float *)q, (float *)k, (float *)v, (const float *)w.w_conv_seq,
+             (const float *)w.w_conv_ch);
 }
 
 // ---------------------------------------------------------------------------
 // Attention.  Workgroup = 32 query rows of one (batch, head); its 8 wavefronts take the 32-key tiles in turn, each with its
 // own running (max, sum, accumulator), merged through LDS at the end.  Scores come out transposed (lane = query, registers =
 // keys), so the row statistics are in-lane with one exchange between the half-waves and the probabilities are the second
-// operand of O^T += V^T P^T as they stand.  T = 1000, 2 heads of 32, fp32: 21.5 us; one wavefront per row on the vector ALU
-// took 100.
+// operand of O^T += V^T P^T as they stand.  What bounds a small grid is the chain of steps of a wavefront, hence a form with 16 rows
+// and up to 16 wavefronts to a workgroup; a large one is bound by the K and V rows loaded per product (generic_attention_rows).
 // ---------------------------------------------------------------------------
-constexpr int GA_NT = 512, GA_WAVES = GA_NT / 64;
-
 template <typename T, int DHM>
-__global__ __launch_bounds__(GA_NT) void attention_generic_kernel(const T *__restrict__ q, const T *__restrict__ k,
+__global__ __launch_bounds__(G32_NT) void attention_generic32_kernel(const T *__restrict__ q, const T *__restrict__ k,
                                                                  const T *__restrict__ v, T *__restrict__ o,
                                                                  T *__restrict__ o_lo, float *__restrict__ lse, int Tn, int Hq,
                                                                  int Hk, int dh, float scale, int causal) {
   constexpr int DT = DHM / 32;
   __shared__ __attribute__((aligned(16))) float sq[32 * (DHM + 4)];
-  __shared__ float sm_[GA_WAVES][32], sl[GA_WAVES][32], so[GA_WAVES][16][64];
+  __shared__ float sm_[G32_WAVES][32], sl[G32_WAVES][32], so[G32_WAVES][16][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
   const int qb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z, g = h / (Hq / Hk);  // causal: long rows first
   const int q0 = qb * 32, t = q0 + l32;
   const T *const kb = k + ((long long)b * Tn * Hk + g) * dh, *const vb = v + ((long long)b * Tn * Hk + g) * dh;
   const long long ks = (long long)Hk * dh;
-  stage_rows32<DHM>(sq, q + ((long long)b * Tn * Hq + h) * dh, (long long)Hq * dh, q0, Tn - 1, dh, [=](float x) { return x * scale; });
+  stage_rows<DHM, 32>(sq, q + ((long long)b * Tn * Hq + h) * dh, (long long)Hq * dh, q0, Tn - 1, dh, [=](float x) { return x * scale; });
   __syncthreads();
   float m = -INFINITY, l = 0.f;
   gen_f32x16 acc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = zero16();
   const int end = causal ? min(q0 + 32, Tn) : Tn;  // keys [0, end) matter
-  for (int k0 = wave * 32; k0 < end; k0 += GA_WAVES * 32) {
-    const gen_f32x16 s = dot_tile<DHM>(kb + min(k0 + l32, Tn - 1) * ks, sq + l32 * (DHM + 4), dh, half, [](float x) { return x; });
+  for (int k0 = wave * 32; k0 < end; k0 += G32_WAVES * 32) {
+    const gen_f32x16 s = dot_tile32<DHM>(kb + min(k0 + l32, Tn - 1) * ks, sq + l32 * (DHM + 4), dh, half, [](float x) { return x; });
     const bool mixed = k0 + 32 > Tn || (causal && k0 + 31 > q0);
     float w[16], mx = m;
 #pragma unroll
@@ -299,17 +311,17 @@ __global__ __launch_bounds__(GA_NT) void attention_generic_kernel(const T *__res
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[dt][r] *= corr;
-    add_outer<DT, T>(acc, w, [=](int x) { return vb + min(k0 + x, Tn - 1) * ks; }, dh, lane, mixed);
+    add_outer32<DT, T>(acc, w, [=](int x) { return vb + min(k0 + x, Tn - 1) * ks; }, dh, lane, mixed);
     m = mx;
   }
   l += __shfl_xor(l, 32);  // each half-wave has summed half of the keys
   if (half == 0) sm_[wave][l32] = m, sl[wave][l32] = l;
   __syncthreads();
-  float M = -INFINITY, L = 0.f, f[GA_WAVES];  // of query l32, the same for every wavefront
+  float M = -INFINITY, L = 0.f, f[G32_WAVES];  // of query l32, the same for every wavefront
 #pragma unroll
-  for (int x = 0; x < GA_WAVES; ++x) M = fmaxf(M, sm_[x][l32]);
+  for (int x = 0; x < G32_WAVES; ++x) M = fmaxf(M, sm_[x][l32]);
 #pragma unroll
-  for (int x = 0; x < GA_WAVES; ++x) {
+  for (int x = 0; x < G32_WAVES; ++x) {
     f[x] = sm_[x][l32] == -INFINITY ? 0.f : expf(sm_[x][l32] - M);
     L += sl[x][l32] * f[x];
   }
@@ -322,11 +334,11 @@ __global__ __launch_bounds__(GA_NT) void attention_generic_kernel(const T *__res
     for (int r = 0; r < 16; ++r) so[wave][r][lane] = acc[dt][r];
     __syncthreads();
 #pragma unroll
-    for (int x = 0; x < 16 / GA_WAVES; ++x) {
-      const int r = wave * (16 / GA_WAVES) + x, ch = 32 * dt + tile_row(r, half);
+    for (int x = 0; x < 16 / G32_WAVES; ++x) {
+      const int r = wave * (16 / G32_WAVES) + x, ch = 32 * dt + tile_row(r, half);
       float sum = 0.f;
 #pragma unroll
-      for (int y = 0; y < GA_WAVES; ++y) sum += f[y] == 0.f ? 0.f : so[y][r][lane] * f[y];
+      for (int y = 0; y < G32_WAVES; ++y) sum += f[y] == 0.f ? 0.f : so[y][r][lane] * f[y];
       if (t < Tn && ch < dh) {
         store_f(o + orow + ch, sum * inv);
         if (o_lo) store_f(o_lo + orow + ch, sum * inv - load_f(o + orow + ch));  // what the rounding dropped
@@ -336,20 +348,101 @@ __global__ __launch_bounds__(GA_NT) void attention_generic_kernel(const T *__res
   if (lse && wave == 0 && half == 0 && t < Tn) lse[((long long)b * Hq + h) * Tn + t] = M + logf(L);
 }
 
+// The same over 16 rows: NT / 64 wavefronts take the 32-key steps, two 16 x 16 tiles each.
+template <typename T, int DHM, int NT>
+__global__ __launch_bounds__(NT) void attention_generic16_kernel(const T *__restrict__ q, const T *__restrict__ k,
+                                                                const T *__restrict__ v, T *__restrict__ o, T *__restrict__ o_lo,
+                                                                float *__restrict__ lse, int Tn, int Hq, int Hk, int dh,
+                                                                float scale, int causal) {
+  constexpr int DT = DHM / 16, WAVES = NT / 64;
+  __shared__ __attribute__((aligned(16))) float sq[16 * (DHM + 4)];
+  __shared__ float sm_[WAVES][16], sl[WAVES][16];
+  __shared__ G16Partial so[WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, grp = lane >> 4;
+  const int qb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z, g = h / (Hq / Hk);  // causal: long rows first
+  const int q0 = qb * 16, t = q0 + l16;
+  const T *const kb = k + ((long long)b * Tn * Hk + g) * dh, *const vb = v + ((long long)b * Tn * Hk + g) * dh;
+  const long long ks = (long long)Hk * dh;
+  stage_rows<DHM, 16>(sq, q + ((long long)b * Tn * Hq + h) * dh, (long long)Hq * dh, q0, Tn - 1, dh, [=](float x) { return x * scale; });
+  __syncthreads();
+  float m = -INFINITY, l = 0.f;
+  gen_f32x4 acc[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) acc[dt] = gen_f32x4{0.f, 0.f, 0.f, 0.f};
+  const int end = causal ? min(q0 + 16, Tn) : Tn;  // keys [0, end) matter
+  for (int k0 = wave * 32; k0 < end; k0 += WAVES * 32) {
+    const bool mixed = k0 + 32 > Tn || (causal && k0 + 31 > q0);
+    gen_f32x4 w[2];
+    float mx = m;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      w[x] = dot_tile16<DHM>(kb + min(k0 + 16 * x + l16, Tn - 1) * ks, sq + l16 * (DHM + 4), dh, grp, [](float y) { return y; });
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int key = k0 + 16 * x + 4 * grp + r;
+        w[x][r] = key < Tn && (!causal || key <= t) ? w[x][r] : -INFINITY;
+        mx = fmaxf(mx, w[x][r]);
+      }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float ref = mx == -INFINITY ? 0.f : mx;  // a row whose scores so far are all -inf has no maximum yet
+    const float corr = expf(m - ref);              // 0 on the first step
+    l *= corr;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[dt][r] *= corr;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        w[x][r] = expf(w[x][r] - ref);
+        l += w[x][r];
+      }
+      add_outer16<DT, T>(acc, w[x], [=](int y) { return vb + min(k0 + 16 * x + y, Tn - 1) * ks; }, dh, lane, mixed);
+    }
+    m = mx;
+  }
+  l += __shfl_xor(l, 16);  // each lane group has summed a quarter of the keys
+  l += __shfl_xor(l, 32);
+  if (grp == 0) sm_[wave][l16] = m, sl[wave][l16] = l;
+  __syncthreads();
+  float M = -INFINITY, L = 0.f;  // of query l16, the same for every wavefront
+#pragma unroll
+  for (int x = 0; x < WAVES; ++x) M = fmaxf(M, sm_[x][l16]);
+  auto weight = [&](int x) { return sm_[x][l16] == -INFINITY ? 0.f : expf(sm_[x][l16] - M); };
+#pragma unroll
+  for (int x = 0; x < WAVES; ++x) L += sl[x][l16] * weight(x);
+  const float inv = 1.f / L;
+  const long long orow = (((long long)b * Tn + t) * Hq + h) * dh;
+  sum_wavefronts16<WAVES>(acc, so, weight, [&](int ch, float sum) {
+    if (t < Tn && ch < dh) {
+      store_f(o + orow + ch, sum * inv);
+      if (o_lo) store_f(o_lo + orow + ch, sum * inv - load_f(o + orow + ch));  // what the rounding dropped
+    }
+  });
+  if (lse && wave == 0 && grp == 0 && t < Tn) lse[((long long)b * Hq + h) * Tn + t] = M + logf(L);
+}
+
 template <typename T>
 static hipError_t attention_generic_t(const Dims &d, const void *q, const void *k, const void *v, void *o,
                                       void *o_lo, float *lse, hipStream_t s) {
-  dim3 grid((d.T + 31) / 32, d.Hq, d.B);
   const int causal = (d.flags & CCA_CAUSAL) ? 1 : 0;
-#define LAUNCH(DH)                                                                                      \
-  attention_generic_kernel<T, DH><<<grid, GA_NT, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (T *)o, (T *)o_lo, lse, d.T, \
-                                                      d.Hq, d.Hk, d.dh, d.scale, causal)
-  if (d.dh <= 32) LAUNCH(32);
-  else if (d.dh <= 64) LAUNCH(64);
-  else if (d.dh <= 128) LAUNCH(128);
-  else LAUNCH(256);
-#undef LAUNCH
-  return hipGetLastError();
+  auto go = [&](auto kernel, int threads, int rows) {
+    kernel<<<dim3((d.T + rows - 1) / rows, d.Hq, d.B), threads, 0, s>>>((const T *)q, (const T *)k, (const T *)v, (T *)o, (T *)o_lo,
+                                                                        lse, d.T, d.Hq, d.Hk, d.dh, d.scale, causal);
+    return hipGetLastError();
+  };
+  const GenericRows form = generic_attention_rows((long long)d.B * d.Hq, d.T, d.dh, causal);
+#define FORMS(DH)                                                                                        \
+  (form == GR_32               ? go(attention_generic32_kernel<T, DH>, G32_NT, 32)                       \
+   : form == GR_16_WIDE        ? go(attention_generic16_kernel<T, DH, G16_NT<DH>>, G16_NT<DH>, 16)       \
+                               : go(attention_generic16_kernel<T, DH, 512>, 512, 16))
+  return d.dh <= 32 ? FORMS(32) : d.dh <= 64 ? FORMS(64) : d.dh <= 128 ? FORMS(128) : FORMS(256);
+#undef FORMS
 }
 
 hipError_t attention_generic(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo,

@@ -157,6 +157,38 @@ inline bool stream_takes_256(long long rows, int heads, int R, int taps, bool ad
   return wgs > 704 || (taps == 1 && !adjoint);
 }
 
+// ---- generic attention (fp32, other widths): rows and wavefronts of a workgroup ------------------------------------------
+// 16 query rows (or keys) with up to 16 wavefronts walk a chain half as long as 32 rows with 8, but load every row of the other
+// kind for half as many products: the better form while its workgroups fit one round of the chip.  Forward, 32 -> 16 rows, us
+// (fp32, T, batch x query heads, d_h): 1000, 2, 32: 20.5 -> 16.8; 1000, 4, 128: 58.1 -> 48.4; 2000, 1, 32: 36.0 -> 25.4; 1000, 4, 256:
+// 127 -> 98 and 700, 4, 256: 90 -> 74 (but 1500, 2, 256: 184 -> 192); two rounds lose: 700, 8, 64 not causal 0.65 of the speed, 4096, 4, 128: 366 -> 420; causal with one or two heads, where
+// the second round's blocks are short, goes on to 200 blocks of 32 rows (6000, 1, 64: 1.57x; 3000, 2, 128: 1.10x; 1500, 4, 64: 0.94).
+// Up to 320 keys 8 wavefronts do (64, 2, 32: 8.6 -> 6.2; beyond d_h = 64 there are never more).
+// The adjoint's 16-row form is also one launch where the other is two: not causal it wins up to 128 blocks of 32 keys (d_h = 128, 128
+// blocks: 1.09-1.40x, 188: 0.88-1.00), at d_h <= 64 up to 200 (1.13-1.31x, 252: 0.96-1.03); causal, where the 32-key form's
+// blocks are uneven, everywhere up to d_h = 128 (4096 x 4 / 2 heads x 128: 1832 -> 1395; 4096 x 16 / 16 x 64: 1.26x; the worst
+// measured 0.96) and up to 200 blocks at 256 (188: 1.12-1.19x, 252: 0.97).
+enum GenericRows { GR_16, GR_16_WIDE, GR_32 };
+inline GenericRows generic_attention_rows(long long BH, int T, int dh, bool causal) {
+  const long long blocks = BH * ((T + 31) / 32);
+  if (dh > 128 && T > 1000) return GR_32;
+  if (blocks > 128 && !(causal && BH <= 2 && blocks <= 200)) return GR_32;
+  return T > 320 && dh <= 64 ? GR_16_WIDE : GR_16;
+}
+inline bool generic_attention_bwd_16(long long BHk, int T, int dh, bool causal) {
+  const long long blocks = BHk * ((T + 31) / 32);
+  return blocks <= 128 || (blocks <= 200 && dh <= 64) || (causal && (dh <= 128 || blocks <= 200));
+}
+
+// ---- generic filter gradients: workgroups over the rows of each unit of outputs ------------------------------------------
+// About one workgroup per CU, none with fewer than 64 rows (a round of its wavefronts); the sums of the splits are added by a
+// second launch, so a grid that fills the chip by itself is not split.
+inline int grad_splits(long long units, long long rows) {
+  const long long by_rows = (rows + 63) / 64, by_cus = 256 / (units > 0 ? units : 1);
+  const long long s = by_rows < by_cus ? by_rows : by_cus;
+  return s < 2 ? 1 : s > 32 ? 32 : (int)s;
+}
+
 // ---- decode attention: keys of a split -----------------------------------------------------------------------------------
 // Every split but a sequence's last holds this many keys: one or two rounds of the kernel's four wavefronts, as few splits as
 // leave about 1024 workgroups on the chip, at most `max_splits`.  groups = sequences x KV heads.  A wavefront of the row kernel

@@ -19,10 +19,14 @@ int r_dq_splits_keys(long long BH, int T, int causal) { return dq_splits_keys(BH
 int r_dkdv_splits_rows(long long BH, int T, int causal) { return dkdv_splits_rows(BH, T, causal); }
 int r_decode_keys_per_split(long long groups, int len, int dh, int rows_kernel) { return decode_keys_per_split(groups, len, dh, rows_kernel, 32); }
 int r_stream_takes_256(long long rows, int heads, int R, int taps, int adjoint) { return stream_takes_256(rows, heads, R, taps, adjoint); }
+int r_generic_attention_rows(long long BH, int T, int dh, int causal) { return generic_attention_rows(BH, T, dh, causal); }
+int r_generic_attention_bwd_16(long long BHk, int T, int dh, int causal) { return generic_attention_bwd_16(BHk, T, dh, causal); }
+int r_grad_splits(long long units, long long rows) { return grad_splits(units, rows); }
 int r_pair_blocks(long long BH, int causal, int blocks) { return pair_blocks(BH, causal, blocks); }
 }
 """
 NT_TILES = ("256x256", "256x192", "64x64", "64x128", "128x128 8 wavefronts", "128x128 4 wavefronts")
+GENERIC_ROWS = ("16 rows", "16 rows, 16 wavefronts", "32 rows")
 TN_TILES = ("split", "64x64", "64x128", "128x128")
 
 
@@ -38,7 +42,8 @@ def _lib():
     L, I = C.c_longlong, C.c_int
     for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
-                           r_stream_takes_256=[L, I, I, I, I],
+                           r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
+                           r_generic_attention_bwd_16=[L, I, I, I], r_grad_splits=[L, L],
                            r_decode_keys_per_split=[L, I, I, I]).items():
         getattr(lib, name).argtypes = args
     return lib
@@ -78,3 +83,15 @@ def stream_takes_256(rows, heads, R, taps, adjoint):
 
 def decode_keys_per_split(groups, keys, dh, rows_kernel):
     return _lib().r_decode_keys_per_split(groups, keys, dh, rows_kernel)
+
+
+def generic_attention_rows(BH, T, dh, causal):
+    return GENERIC_ROWS[_lib().r_generic_attention_rows(BH, T, dh, causal)]
+
+
+def generic_attention_bwd_16(BHk, T, dh, causal):
+    return bool(_lib().r_generic_attention_bwd_16(BHk, T, dh, causal))
+
+
+def grad_splits(units, rows):
+    return _lib().r_grad_splits(units, rows)

@@ -34,6 +34,28 @@ def test_wide_head_prologue_cases_reach_both_forms():
     assert reached == {(taps, adjoint, wide) for taps in (1, 2, 3) for adjoint in (False, True) for wide in (False, True)}
 
 
+def test_generic_cases_reach_every_form():
+    rows, bwd, splits = set(), set(), set()
+    for c in small.GENERIC_CASES:
+        for causal in (False, True):
+            rows.add(rules.generic_attention_rows(c["B"] * c["Hq"], c["T"], c["dh"], causal))
+            bwd.add(rules.generic_attention_bwd_16(c["B"] * c["Hk"], c["T"], c["dh"], causal))
+        tiles = -(-c["dh"] // 32)
+        splits.add(rules.grad_splits(tiles * tiles * (c["Hq"] + c["Hk"]) * c["k_ch"], c["B"] * c["T"]))
+    assert rows == set(rules.GENERIC_ROWS) and bwd == {True, False}
+    assert 1 in splits and 2 in splits and max(splits) >= 16
+
+
+# T, batch x query heads, d_h, causal and us of 32 rows, of 16
+GENERIC_MEASURED = [(1000, 2, 32, True, 20.5, 16.8), (1000, 4, 128, True, 58.1, 48.4), (2000, 1, 32, True, 36.0, 25.4),
+                    (4096, 4, 128, True, 366.0, 420.0), (4096, 4, 64, False, 246.0, 257.2), (4096, 4, 256, False, 854.1, 1286.9)]
+
+
+@pytest.mark.parametrize("T,BH,dh,causal,us32,us16", GENERIC_MEASURED)
+def test_generic_attention_form_is_the_faster(T, BH, dh, causal, us32, us16):
+    assert (rules.generic_attention_rows(BH, T, dh, causal) == "32 rows") == (us32 < us16)
+
+
 # M, N, K and us of each tile shape in the order of rules.NT_TILES
 NT_MEASURED = [
     (4593, 4096, 4096, (207.5, 171.1, 352.7, 360.1, 215.9, 196.5)), (6000, 2048, 4096, (104.3, 160.1, 237.3, 166.6, 127.7, 119.5)),

@@ -379,7 +379,12 @@ def test_decode_split_edges(Hq, Hk, dh):
 # instantiation of the head width; fp32 against the oracle at its 1e-5, forward and backward
 GENERIC_CASES = [dict(B=1, T=1, E=48, Hq=2, Hk=1, dh=12, k_seq=2, k_ch=2), dict(B=2, T=33, E=120, Hq=3, Hk=1, dh=40, k_seq=4, k_ch=3),
                  dict(B=1, T=97, E=288, Hq=3, Hk=3, dh=96, k_seq=1, k_ch=2), dict(B=1, T=70, E=264, Hq=1, Hk=1, dh=200, k_seq=2, k_ch=1),
-                 dict(B=3, T=300, E=64, Hq=6, Hk=2, dh=4, k_seq=3, k_ch=4)]
+                 dict(B=3, T=300, E=64, Hq=6, Hk=2, dh=4, k_seq=3, k_ch=4),
+                 # tiles of 16 rows and of 32 tokens met exactly and by one; filter gradients whole and in 2, 6 and 16 parts of the rows
+                 dict(B=2, T=161, E=64, Hq=2, Hk=2, dh=32, k_seq=2, k_ch=2), dict(B=3, T=48, E=128, Hq=2, Hk=1, dh=64, k_seq=2, k_ch=2),
+                 dict(B=1, T=31, E=256, Hq=1, Hk=1, dh=256, k_seq=2, k_ch=2), dict(B=1, T=1024, E=64, Hq=2, Hk=2, dh=32, k_seq=2, k_ch=2),
+                 # more workgroups than one round: the attention's 32-row forms (tests/test_dispatch_rules.py)
+                 dict(B=6, T=65, E=192, Hq=24, Hk=12, dh=8, k_seq=2, k_ch=2), dict(B=13, T=161, E=288, Hq=3, Hk=3, dh=96, k_seq=2, k_ch=2)]
 
 
 @pytest.mark.parametrize("causal", [True, False])
