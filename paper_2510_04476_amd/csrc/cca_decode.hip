@@ -119,43 +119,37 @@ __device__ __forceinline__ const T *lat_row(const DecArgs &a, const T *hist, int
 }
 
 constexpr int MAX_PARTS = 8;
-// Channel `ch` of the new token's latent row: with `part` (the down-projection left `nparts` fp32 partial sums per element,
-// (nparts, B, N_lat)) their sum in index order, rounded to the storage type; else the ring already holds the row.
-template <typename T>
+// The new token's latent row: the sum, in index order, of `nparts` fp32 rows that the down-projection left (bf16; (nparts, B, N_lat)),
+// rounded to the storage type - or the row itself, where the projection wrote it to its ring slot (fp32: one part).
+// Requests and sums are apart so that a caller can request everything before it waits for anything, and no load hides behind a
+// condition: a value that two branches load is waited for where they meet (NP >= nparts; addresses past the last part repeat it, the value
+// is dropped).  What bounds a small step is this chain of latencies.  Whole step, E = 2048, 8 query and 2 KV heads of 128, before ->
+// now: one sequence of 200 tokens 23.4 -> 22.1 us, 32 of 2000 43.5 -> 42.2, 256 of 2000 191.5 -> 186.4 (with eight requests whatever
+// nparts is, 96 sequences and more lost 2 ... 6 %).
+template <typename T, int NP>
 struct NewRow {
-  const T *ring;        // the new token's slot
-  const float *part;    // this sequence's row of the first partial sum, or null
-  long long stride;     // from one partial sum to the next
+  const float *part;    // this sequence's row of the first part
+  long long stride;     // from one part to the next
   int nparts;
-  // No load here hides behind a condition: all of a thread's loads are in flight together (addresses past the last part
-  // repeat it, the value is dropped).
   template <int N>
-  __device__ __forceinline__ void many(const int (&ch)[N], float (&out)[N]) const {
-    if (!part) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) out[i] = load_f(ring + ch[i]);
-      return;
-    }
-    float v[N][MAX_PARTS];
+  __device__ __forceinline__ void request(const int (&ch)[N], float (&v)[N][NP]) const {
 #pragma unroll
     for (int i = 0; i < N; ++i)
 #pragma unroll
-      for (int s = 0; s < MAX_PARTS; ++s) v[i][s] = part[min(s, nparts - 1) * stride + ch[i]];
+      for (int s = 0; s < NP; ++s) v[i][s] = part[min(s, nparts - 1) * stride + ch[i]];
+  }
+  __device__ __forceinline__ float value(const float (&v)[NP]) const {
+    float a = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      float a = 0.f;
-#pragma unroll
-      for (int s = 0; s < MAX_PARTS; ++s) a += s < nparts ? v[i][s] : 0.f;
-      T r;
-      store_f(&r, a);
-      out[i] = load_f(&r);
-    }
+    for (int s = 0; s < NP; ++s) a += s < nparts ? v[s] : 0.f;
+    T r;
+    store_f(&r, a);
+    return load_f(&r);
   }
   __device__ __forceinline__ float at(int ch) const {
-    const int c[1] = {ch};
-    float o[1];
-    many(c, o);
-    return o[0];
+    float v[1][NP];
+    request({ch}, v);
+    return value(v[0]);
   }
 };
 
@@ -173,7 +167,7 @@ __device__ __forceinline__ float dpp_add(float x) {
   return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
 }
 
-template <typename T, int CH, int LPO>
+template <typename T, int CH, int LPO, int NP>
 __global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__restrict__ hist, const float *__restrict__ part,
                                                              int nparts, const T *__restrict__ w0, const T *__restrict__ w1,
                                                              const float *__restrict__ temp, float *__restrict__ q_new,
@@ -182,7 +176,10 @@ __global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__re
   const int b = blockIdx.x, head = blockIdx.y, dh = a.dh, tid = threadIdx.x, t = seq_pos(a, b);
   const long long crow = (long long)b * a.S + t;  // cache row of the new token
   T *const slot = hist + ((long long)b * a.P + t % a.P) * a.n_lat;
-  const NewRow<T> now{slot, part ? part + (long long)b * a.n_lat : nullptr, (long long)a.B * a.n_lat, nparts};
+  // (fp32: the projection wrote the rows into the ring itself)
+  const NewRow<T, NP> now{std::is_same<T, float>::value ? reinterpret_cast<const float *>(slot) : part + (long long)b * a.n_lat,
+                      (long long)a.B * a.n_lat, nparts};
+  constexpr bool keep = !std::is_same<T, float>::value;  // the new row goes into the ring here
 
   if (head >= a.Hq + a.Hk) {  // value head: second stream delayed by one token
     const int g = head - a.Hq - a.Hk, v0 = a.e_q + a.e_kv;
@@ -190,7 +187,7 @@ __global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__re
     for (int i = tid; i < dh; i += blockDim.x) {
       const int c = g * dh + i;
       const float cur = now.at(v0 + c);
-      if (part) store_f(slot + v0 + c, cur);
+      if (keep) store_f(slot + v0 + c, cur);
       float val;
       if (c < a.v_half || !(a.flags & CCA_V_SHIFT)) val = cur;
       else val = prev ? load_f(prev + c) : 0.f;
@@ -221,41 +218,53 @@ __global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__re
 
   // The new row's channels, one output per thread (d_h <= 256 <= threads; the others repeat the last one): the head's own
   // and the qk-mean's other stream.
-  const int oc = min(tid, dh - 1);
-  float own, mean = 0.f;
-  if (is_q) {
-    float x[2];
-    now.many({ch0 + oc, a.e_q + (head / a.R) * dh + oc}, x);
-    own = x[0];
-    mean = 0.5f * (own + x[1]);
-  } else {
-    const int q0 = (head - a.Hq) * a.R * dh + oc;
-    float sq = 0.f;
-    own = now.at(ch0 + oc);
-    for (int r = 0; r < a.R; r += 4) {
-      float x[4];
-      now.many({q0 + r * dh, q0 + min(r + 1, a.R - 1) * dh, q0 + min(r + 2, a.R - 1) * dh, q0 + min(r + 3, a.R - 1) * dh}, x);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) sq += r + u < a.R ? x[u] : 0.f;
-    }
-    mean = 0.5f * (sq / (float)a.R + own);
-  }
+  // They are requested here and summed behind the requests for the rows the taps reach: one memory latency for both.
+  const int oc = min(tid, dh - 1), q0 = (head - a.Hq) * a.R * dh + oc;  // (q0: a key head's first query channel)
+  float v_own[1][NP], v_oth[4][NP];
+  now.request({ch0 + oc}, v_own);
+  const int kv = a.e_q + (head / a.R) * dh + oc;  // a query head's other stream
+  now.request({is_q ? kv : q0, is_q ? kv : q0 + min(1, a.R - 1) * dh, is_q ? kv : q0 + min(2, a.R - 1) * dh,
+               is_q ? kv : q0 + min(3, a.R - 1) * dh}, v_oth);
   // conv1_seq outputs at the k_ch times conv2 needs, of which one channel and time each: the part from earlier tokens here,
   // the new token's term (always the last tap) once its row is shared
   const int n_y0 = kc * dh;  // <= 1024: two per thread at most
   const bool seq = a.flags & CCA_CONV_SEQ;
   const T *const f0p = seq ? w0 : hist;  // without the convolution: any readable row, the value is dropped
   float y_old[2], w_new[2];
+  T xs_[2][4], f0_[2][4];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int idx = min(tid + u * (int)blockDim.x, n_y0 - 1), j = idx / dh, i = idx % dh, tj = t - (kc - 1) + j;
-    float xs[4], f0[4];
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {  // rows outside the sequence (or still to come) are read from some slot and dropped
       const int ts = tj - (ks - 1) + jj;
-      xs[jj] = load_f(lat_row(a, hist, b, max(ts, 0)) + ch0 + i);
-      f0[jj] = load_f(f0p + (long long)(ch0 + i) * ks + min(jj, ks - 1));
+      xs_[u][jj] = lat_row(a, hist, b, max(ts, 0))[ch0 + i];
+      f0_[u][jj] = f0p[(long long)(ch0 + i) * ks + min(jj, ks - 1)];
     }
+  }
+  __builtin_amdgcn_sched_barrier(0);  // every request stands before the first use
+  const float own = now.value(v_own[0]);
+  float mean;
+  if (is_q) {
+    mean = 0.5f * (own + now.value(v_oth[0]));
+  } else {
+    float sq = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sq += u < a.R ? now.value(v_oth[u]) : 0.f;
+    for (int r = 4; r < a.R; r += 4) {
+      float x[4][NP];
+      now.request({q0 + r * dh, q0 + min(r + 1, a.R - 1) * dh, q0 + min(r + 2, a.R - 1) * dh, q0 + min(r + 3, a.R - 1) * dh}, x);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sq += r + u < a.R ? now.value(x[u]) : 0.f;
+    }
+    mean = 0.5f * (sq / (float)a.R + own);
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int idx = min(tid + u * (int)blockDim.x, n_y0 - 1), j = idx / dh, tj = t - (kc - 1) + j;
+    float xs[4], f0[4];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) xs[jj] = load_f(&xs_[u][jj]), f0[jj] = load_f(&f0_[u][jj]);
     float acc = 0.f;
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
@@ -277,7 +286,7 @@ __global__ __launch_bounds__(512) void decode_prologue_kernel(DecArgs a, T *__re
   }
   if (tid < dh) {
     yrot[tid] = own;  // shared for the taps; the outputs replace it
-    if (part) store_f(slot + ch0 + tid, own);
+    if (keep) store_f(slot + ch0 + tid, own);
   }
   __syncthreads();
 #pragma unroll
@@ -562,19 +571,12 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
   const int rr = lane / LPR, cc = lane % LPR;
   const float c = a.scale * 1.44269504088896340736f;
 
-  uint32_t q2[NR][4];  // this lane's 8 channels of each query head, bf16 pairs (exact: q_new holds bf16 values)
+  f4 ql[NR], qh[NR];  // heads past the last repeat it; nobody stores their results
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    f4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
-    if (r < nr) {
-      const float *qp = q_new + ((long long)b * a.Hq + g * a.R + r0 + r) * DH + cc * 8;
-      lo = *reinterpret_cast<const f4 *>(qp);
-      hi = *reinterpret_cast<const f4 *>(qp + 4);
-    }
-    q2[r][0] = (__float_as_uint(lo.x) >> 16) | (__float_as_uint(lo.y) & 0xffff0000u);
-    q2[r][1] = (__float_as_uint(lo.z) >> 16) | (__float_as_uint(lo.w) & 0xffff0000u);
-    q2[r][2] = (__float_as_uint(hi.x) >> 16) | (__float_as_uint(hi.y) & 0xffff0000u);
-    q2[r][3] = (__float_as_uint(hi.z) >> 16) | (__float_as_uint(hi.w) & 0xffff0000u);
+    const float *qp = q_new + ((long long)b * a.Hq + g * a.R + r0 + min(r, nr - 1)) * DH + cc * 8;
+    ql[r] = *reinterpret_cast<const f4 *>(qp);
+    qh[r] = *reinterpret_cast<const f4 *>(qp + 4);
   }
 
   const int len = seq_pos(a, b) + 1;  // after the query's loads: one latency for both
@@ -609,6 +611,14 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_rows_kernel(DecArg
 #pragma unroll
     for (int u = 0; u < U; ++u) vr[u] = *reinterpret_cast<const u4 *>(vb + off[u]);
     __builtin_amdgcn_sched_barrier(0);
+    uint32_t q2[NR][4];  // this lane's 8 channels of each query head, bf16 pairs (exact: q_new holds bf16 values)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      q2[r][0] = (__float_as_uint(ql[r].x) >> 16) | (__float_as_uint(ql[r].y) & 0xffff0000u);
+      q2[r][1] = (__float_as_uint(ql[r].z) >> 16) | (__float_as_uint(ql[r].w) & 0xffff0000u);
+      q2[r][2] = (__float_as_uint(qh[r].x) >> 16) | (__float_as_uint(qh[r].y) & 0xffff0000u);
+      q2[r][3] = (__float_as_uint(qh[r].z) >> 16) | (__float_as_uint(qh[r].w) & 0xffff0000u);
+    }
     // One block: its scores, the next block's K loads, softmax, P V, the next block's V loads.  A wavefront's last block has no
     // next one, and only that one may reach past the end of the split.
     auto block = [&](auto last_) __attribute__((always_inline)) {
@@ -763,10 +773,12 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecArgs a, const fl
 #pragma unroll
       for (int s = s0; s < s0 + 8; ++s) val[s] = mine[min(s, nsplit - 1) * stride];
     }
+  // the state of split `tid` (an even number of floats from a 256-byte boundary)
+  const float2 state = *reinterpret_cast<const float2 *>(src + min(tid, nsplit - 1) * stride);
+  __builtin_amdgcn_sched_barrier(0);  // requested with the values
   const int len = seq_pos(a, bh / a.Hq) + 1, n = min(nsplit, (len + per - 1) / per);
   if (tid < 64) {  // one wavefront: lane s holds split s
-    const int at = min(tid, nsplit - 1) * stride;
-    const float m0 = src[at], l0 = src[at + 1];
+    const float m0 = state.x, l0 = state.y;
     const float ms = tid < n ? m0 : -INFINITY, ls = tid < n ? l0 : 0.f;
     float M = ms;
     for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
@@ -1029,7 +1041,8 @@ int skinny_splits(int N, int K) {
 }
 size_t skinny_scratch_bytes(int M, int N, int K) { return (size_t)skinny_splits(N, K) * M * N * sizeof(float); }
 
-// N and K are multiples of 8, as every bf16 width is (make_dims).  slices = 1: C.  More: `part` gets that many partial sums (slices, M, N) for the caller's next kernel to add.
+// N and K are multiples of 8, as every bf16 width is (make_dims).  `part` gets `slices` partial sums (slices, M, N) for the caller's next
+// kernel to add; without it (one slice) the rows go to C.
 hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest, float *part, int slices, int M, int N, int K,
                       hipStream_t s) {
   if (hipError_t e = raise_lds_limit<gemm_panel_kernel>(PN_LDS); e != hipSuccess) return e;
@@ -1037,14 +1050,14 @@ hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest,
   const int kp = panel_rows(M, K < k_slice ? K : k_slice);
   const size_t pass = (size_t)kp * (PN_COLS * 2 + 2 * (M < 32 ? M : 32)), lds = pass > PN_SUMS ? pass : PN_SUMS;
   gemm_panel_kernel<<<dim3((N + PN_COLS - 1) / PN_COLS, slices, row_blocks < 4096 ? row_blocks : 4096), PN_NT, lds, s>>>(A, W, C, dest, M, N, K, kp, k_slice,
-                                                                                 slices > 1 ? part : nullptr);
+                                                                                 part);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t gemm_skinny(const T *A, const T *W, T *C, RowDest dest, float *part, int M, int N, int K, hipStream_t s) {
   if constexpr (std::is_same<T, bf16_t>::value) {
-    return gemm_panel(A, W, C, dest, part, 1, M, N, K, s);
+    return gemm_panel(A, W, C, dest, nullptr, 1, M, N, K, s);
   } else {
     const int splits = skinny_splits(N, K);
     const int chunk = (K + splits - 1) / splits;
@@ -1112,18 +1125,18 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
   T *o = reinterpret_cast<T *>(ws + L.o);
   float *part = reinterpret_cast<float *>(ws + L.part);
   float *gpart = reinterpret_cast<float *>(ws + L.gemm);
-  // The down-projection.  On the matrix cores it is split over K so that more CUs pull the weight (one CU takes in about 29
-  // GB/s of 64-byte pieces): the prologue adds the parts and writes the new latent rows into their ring slot.  Otherwise the
+  // The down-projection.  On the matrix cores (bf16) it is split over K so that more CUs pull the weight (one CU takes in about 29
+  // GB/s of 64-byte pieces): the prologue adds the parts and writes the new latent rows into their ring slot.  In fp32 the
   // rows go straight into the ring.
-  const long long ring_stride = (long long)P * d.n_lat;
-  const RowDest ring = pos_seq ? RowDest{ring_stride, pos_seq, pos, P} : RowDest{ring_stride, nullptr, 0, 1};
-  T *const ring_c = (T *)hist + (pos_seq ? 0 : (long long)(pos % P) * d.n_lat);
   int nparts = 1;
   hipError_t e;
   if constexpr (std::is_same<T, bf16_t>::value) {
     nparts = down_slices(d);
-    e = gemm_panel((const bf16_t *)x_new, (const bf16_t *)w.w_down, (bf16_t *)ring_c, ring, gpart, nparts, d.B, d.n_lat, d.E, s);
+    e = gemm_panel((const bf16_t *)x_new, (const bf16_t *)w.w_down, nullptr, RowDest{}, gpart, nparts, d.B, d.n_lat, d.E, s);
   } else {
+    const long long ring_stride = (long long)P * d.n_lat;
+    const RowDest ring = pos_seq ? RowDest{ring_stride, pos_seq, pos, P} : RowDest{ring_stride, nullptr, 0, 1};
+    T *const ring_c = (T *)hist + (pos_seq ? 0 : (long long)(pos % P) * d.n_lat);
     e = gemm_skinny<T>((const T *)x_new, (const T *)w.w_down, ring_c, ring, gpart, d.B, d.n_lat, d.E, s);
   }
   if (e != hipSuccess) return e;
@@ -1131,15 +1144,20 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
     const int kc = (d.flags & CCA_CONV_CH) ? d.k_ch : 1;
     const int threads = d.dh <= 64 ? 256 : 512, per_lane = (d.dh * kc / 8 + 7) / 8;  // filter chunks per lane of 8
     const size_t smem = sizeof(float) * ((size_t)kc * d.dh + 2 * d.dh);
+#define CCA_DEC_PRO_NP(CH, LPO, NP)                                                                                       \
+  decode_prologue_kernel<T, CH, LPO, NP><<<dim3(d.B, d.Hq + 2 * d.Hk), threads, smem, s>>>(                                \
+      a, (T *)hist, gpart, nparts, (const T *)w.w_conv_seq, (const T *)w.w_conv_ch, w.temp, q_new, (T *)k_cache, (T *)v_cache)
 #define CCA_DEC_PRO(CH, LPO)                                                                                              \
-  decode_prologue_kernel<T, CH, LPO><<<dim3(d.B, d.Hq + 2 * d.Hk), threads, smem, s>>>(                                    \
-      a, (T *)hist, nparts > 1 ? gpart : nullptr, nparts, (const T *)w.w_conv_seq, (const T *)w.w_conv_ch, w.temp, q_new, \
-      (T *)k_cache, (T *)v_cache)
-    if (per_lane <= 2) CCA_DEC_PRO(2, 8);
-    else if (per_lane <= 4) CCA_DEC_PRO(4, 8);
-    else if (per_lane <= 8) CCA_DEC_PRO(8, 8);
-    else CCA_DEC_PRO(8, 16);
+  if (std::is_same<T, float>::value || nparts == 1) CCA_DEC_PRO_NP(CH, LPO, 1);                                            \
+  else if (nparts == 2) CCA_DEC_PRO_NP(CH, LPO, (std::is_same<T, float>::value ? 1 : 2));                                  \
+  else if (nparts <= 5) CCA_DEC_PRO_NP(CH, LPO, (std::is_same<T, float>::value ? 1 : 5));                                  \
+  else CCA_DEC_PRO_NP(CH, LPO, (std::is_same<T, float>::value ? 1 : MAX_PARTS))
+    if (per_lane <= 2) { CCA_DEC_PRO(2, 8); }
+    else if (per_lane <= 4) { CCA_DEC_PRO(4, 8); }
+    else if (per_lane <= 8) { CCA_DEC_PRO(8, 8); }
+    else { CCA_DEC_PRO(8, 16); }
 #undef CCA_DEC_PRO
+#undef CCA_DEC_PRO_NP
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   {
