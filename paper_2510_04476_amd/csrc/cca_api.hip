@@ -203,6 +203,19 @@ static cca_status weight_grad(const Dims &d, const void *A, const void *Bm, void
   return e == hipSuccess ? CCA_OK : CCA_ERR_LAUNCH;
 }
 
+// The two adjoints of C (rows, n_out) = A (rows, n_in) W (n_in, n_out); d_A or d_W may be NULL (not wanted).
+static cca_status projection_bwd(const Dims &d, const void *d_C, const void *W, void *d_A, const void *A, void *d_W, int n_in, int n_out,
+                                 void *scratch, hipStream_t s) {
+  if (d_A && d_W && d.bf16 && gemm_mfma_supported(d.rows(), n_in, n_out) && tn_mfma(d, n_in, n_out))
+    return gemm_adjoint_pair(d_C, W, d_A, A, d_W, d.rows(), n_in, n_out, static_cast<float *>(scratch), s) == hipSuccess
+               ? CCA_OK
+               : CCA_ERR_LAUNCH;
+  cca_status st = CCA_OK;
+  if (d_W) st = weight_grad(d, A, d_C, d_W, n_in, n_out, scratch, s);
+  if (st == CCA_OK && d_A) st = project_t(d, d_C, W, d_A, d.rows(), n_in, n_out, s);
+  return st;
+}
+
 static cca_status run_attention_bwd(const Dims &d, const void *q, const void *k, const void *v, const void *o,
                                     const void *o_lo, const float *lse, const void *d_o, void *d_q, void *d_k, void *d_v, float *delta,
                                     hipStream_t s) {
@@ -421,11 +434,7 @@ cca_status cca_backward(const cca_config *cfg, const cca_weights *w, const void 
   void *d_o = ws + L.d_o, *d_q = ws + L.d_q, *d_k = ws + L.d_k, *d_v = ws + L.d_v, *d_lat = ws + L.d_lat;
   hipStream_t s = (hipStream_t)hip_stream;
   // last step first: out = o W_O
-  if (grads && grads->w_out) {
-    st = weight_grad(d, saved->o, d_out, grads->w_out, d.e_q, d.E, ws + L.gemm, s);
-    if (st != CCA_OK) return st;
-  }
-  st = project_t(d, d_out, w->w_out, d_o, d.rows(), d.e_q, d.E, s);
+  st = projection_bwd(d, d_out, w->w_out, d_o, saved->o, grads ? grads->w_out : nullptr, d.e_q, d.E, ws + L.gemm, s);
   if (st != CCA_OK) return st;
   st = run_attention_bwd(d, saved->q, saved->k, saved->v, saved->o, saved->o_lo, saved->lse, d_o, d_q, d_k, d_v,
                          reinterpret_cast<float *>(ws + L.delta), s);
@@ -433,15 +442,7 @@ cca_status cca_backward(const cca_config *cfg, const cca_weights *w, const void 
   st = run_prologue_bwd(d, w, saved->lat, saved->q, saved->k, saved->rnorm, d_q, d_k, d_v, d_lat, grads, ws + L.pro,
                         L.pro_bytes, s);
   if (st != CCA_OK) return st;
-  if (d_x) {
-    st = project_t(d, d_lat, w->w_down, d_x, d.rows(), d.E, d.n_lat, s);
-    if (st != CCA_OK) return st;
-  }
-  if (grads && grads->w_down) {
-    st = weight_grad(d, x, d_lat, grads->w_down, d.E, d.n_lat, ws + L.gemm, s);
-    if (st != CCA_OK) return st;
-  }
-  return CCA_OK;
+  return projection_bwd(d, d_lat, w->w_down, d_x, x, grads ? grads->w_down : nullptr, d.E, d.n_lat, ws + L.gemm, s);
 }
 
 cca_status cca_forward(const cca_config *cfg, const cca_weights *w, const void *x, void *out, const cca_saved *saved,

@@ -406,7 +406,7 @@ __device__ __forceinline__ int swz_tn(int r, int c) {  // 16-byte chunk c of tok
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 __device__ __forceinline__ void gemm_bf16_tn_deep_body(
     const bf16_t *__restrict__ A, long long lda, const bf16_t *__restrict__ Bm, long long ldb, bf16_t *__restrict__ C,
-    int Mo, int No, long long K, int tiles_n, int tiles_total, unsigned char *smem) {
+    int Mo, int No, long long K, int tiles_n, int tiles_total, int wg, unsigned char *smem) {
   static_assert((TM == 64 || TM == 128) && (TN == 64 || TN == 128), "swz_tn");
   constexpr int NWAVES = WAVES_M * WAVES_N * WAVES_K, NTHREADS = NWAVES * 64;
   constexpr int MI = TM / WAVES_M / 32, NI = TN / WAVES_N / 32;
@@ -415,7 +415,6 @@ __device__ __forceinline__ void gemm_bf16_tn_deep_body(
   static_assert(PER_WAVE * 64 * NWAVES == STAGE && A_CH % 64 == 0, "instructions must divide evenly over the wavefronts");
   u32x4 *const sbase = reinterpret_cast<u32x4 *>(smem);
 
-  const int wg = blockIdx.x;
   const int per_xcd = (tiles_total + 7) / 8;
   const int tile = (wg % 8) * per_xcd + wg / 8;
   if (tile >= tiles_total) return;
@@ -529,17 +528,21 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_tn_d
     const bf16_t *__restrict__ A, long long lda, const bf16_t *__restrict__ Bm, long long ldb, bf16_t *__restrict__ C,
     int Mo, int No, long long K, int tiles_n, int tiles_total) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  gemm_bf16_tn_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, lda, Bm, ldb, C, Mo, No, K, tiles_n, tiles_total, smem);
+  gemm_bf16_tn_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, lda, Bm, ldb, C, Mo, No, K, tiles_n, tiles_total, blockIdx.x, smem);
+}
+
+// LDS of a small-tile workgroup: its stages (`rows` rows of 64 values), then the wavefronts' sums and the tile on its way out
+constexpr size_t deep_lds(int tm, int tn, int waves_k, int rows) {
+  const size_t epi = (size_t)tm * (tn * 2 + 16), sum = (size_t)(waves_k - 1) * tm * tn * 4, main = (size_t)rows * BK * 2;
+  const size_t most = main > epi ? main : epi;
+  return most > sum ? most : sum;
 }
 
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 hipError_t launch_tn_deep(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No, long long K,
                           hipStream_t s) {
   const int tiles_m = (Mo + TM - 1) / TM, tiles_n = (No + TN - 1) / TN, total = tiles_m * tiles_n;
-  constexpr size_t epi_bytes = (size_t)TM * (TN * 2 + 16), sum_bytes = (size_t)(WAVES_K - 1) * TM * TN * 4;
-  constexpr size_t main_bytes = (size_t)STAGES * BK * (TM + TN) * 2;
-  constexpr size_t smem0 = main_bytes > epi_bytes ? main_bytes : epi_bytes, smem = smem0 > sum_bytes ? smem0 : sum_bytes;
-  static_assert(smem <= 160 * 1024, "LDS");
+  constexpr size_t smem = deep_lds(TM, TN, WAVES_K, STAGES * (TM + TN));
   constexpr auto kernel = gemm_bf16_tn_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>;
   if (hipError_t e = raise_lds_limit<kernel>(smem); e != hipSuccess) return e;
   kernel<<<(total + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb,
@@ -626,19 +629,17 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
 // WAVES_K = 4, a fourth stage at 64 x 64.
 // ---------------------------------------------------------------------------
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
-__global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_deep_kernel(
+__device__ __forceinline__ void gemm_bf16_nt_deep_body(
     const bf16_t *__restrict__ A, const bf16_t *__restrict__ Bt, bf16_t *__restrict__ C, long long M, int N, int K,
-    int tiles_n, int tiles_total, ColumnSplit split) {
+    int tiles_n, int tiles_total, const ColumnSplit &split, int wg, unsigned char *smem) {
   constexpr int NWAVES = WAVES_M * WAVES_N * WAVES_K, NTHREADS = NWAVES * 64;
   constexpr int WM = TM / WAVES_M, WN = TN / WAVES_N, MI = WM / 32, NI = WN / 32;
   static_assert(MI * 32 == WM && NI * 32 == WN, "wave tile must be a multiple of 32");
   constexpr int SUB = (TM + TN) * 8, STAGE = WAVES_K * SUB;  // 16-byte chunks of one 64-wide sub-slab / of a stage
   constexpr int PER_WAVE = STAGE / 64 / NWAVES;              // load instructions of a wavefront per stage
   static_assert(PER_WAVE * 64 * NWAVES == STAGE, "instructions must divide evenly over the wavefronts");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u32x4 *const sbase = reinterpret_cast<u32x4 *>(smem);
 
-  const int wg = blockIdx.x;
   const int per_xcd = (tiles_total + 7) / 8;
   const int tile = (wg % 8) * per_xcd + wg / 8;
   if (tile >= tiles_total) return;
@@ -717,17 +718,78 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_d
 }
 
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
+__global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_deep_kernel(
+    const bf16_t *__restrict__ A, const bf16_t *__restrict__ Bt, bf16_t *__restrict__ C, long long M, int N, int K,
+    int tiles_n, int tiles_total, ColumnSplit split) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  gemm_bf16_nt_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, Bt, C, M, N, K, tiles_n, tiles_total, split, blockIdx.x, smem);
+}
+
+template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
                             hipStream_t s) {
   const int tiles_m = (int)((M + TM - 1) / TM), tiles_n = (N + TN - 1) / TN;
   const int total = tiles_m * tiles_n;
-  constexpr size_t epi_bytes = (size_t)TM * (TN * 2 + 16), sum_bytes = (size_t)(WAVES_K - 1) * TM * TN * 4;
-  constexpr size_t main_bytes = (size_t)STAGES * WAVES_K * (TM + TN) * BK * 2;
-  constexpr size_t smem0 = main_bytes > epi_bytes ? main_bytes : epi_bytes, smem = smem0 > sum_bytes ? smem0 : sum_bytes;
-  static_assert(smem <= 160 * 1024, "LDS");
+  constexpr size_t smem = deep_lds(TM, TN, WAVES_K, STAGES * WAVES_K * (TM + TN));
   if (hipError_t e = raise_lds_limit<gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>>(smem); e != hipSuccess) return e;
   gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES><<<(total + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>(
       (const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N, K, tiles_n, total, split);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// A projection's two adjoints, d_A = d_C W^T (NT) and d_W = A^T d_C (TN), in one launch on small tiles: they are independent, and for
+// the row counts these tiles serve neither fills the chip.  Workgroups [0, first) work on the product with the longer tiles.
+// Backward pass, a launch each -> one (us): 2 x 512 tokens of E = 2048, 8 query and 2 KV heads of 128: 145.0 -> 138.6; 2 x 1024: 218.4 ->
+// 209.6; 1 x 1024 of E = 1024, 8 heads of 64: 106.3 -> 97.0; from about 4000 tokens on each runs in its own best form.
+// ---------------------------------------------------------------------------
+struct NtDeep64x64 { static constexpr int TM = 64, TN = 64, WM = 2, WN = 2, WK = 2, ST = 3; };
+struct NtDeep64x128 { static constexpr int TM = 64, TN = 128, WM = 1, WN = 4, WK = 2, ST = 3; };
+struct NtDeep128x128 { static constexpr int TM = 128, TN = 128, WM = 2, WN = 4, WK = 1, ST = 4; };
+struct TnDeep64x64 { static constexpr int TM = 64, TN = 64, WM = 2, WN = 2, WK = 2, ST = 4; };
+struct TnDeep64x128 { static constexpr int TM = 64, TN = 128, WM = 2, WN = 2, WK = 2, ST = 4; };
+struct TnDeep128x128 { static constexpr int TM = 128, TN = 128, WM = 2, WN = 4, WK = 1, ST = 4; };
+
+struct NtArgs {
+  const bf16_t *A, *Bt;
+  bf16_t *C;
+  long long M;
+  int N, K, tiles_n, tiles;
+};
+struct TnArgs {
+  const bf16_t *A, *B;
+  bf16_t *C;
+  int Mo, No;
+  long long K;
+  int tiles_n, tiles;
+};
+
+template <typename NT_, typename TN_>
+__global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(NtArgs nt, TnArgs tn, int first, int nt_first) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int wg = (int)blockIdx.x < first ? blockIdx.x : blockIdx.x - first;
+  if (((int)blockIdx.x < first) == (nt_first != 0))
+    gemm_bf16_nt_deep_body<NT_::TM, NT_::TN, NT_::WM, NT_::WN, NT_::WK, NT_::ST>(nt.A, nt.Bt, nt.C, nt.M, nt.N, nt.K, nt.tiles_n,
+                                                                                 nt.tiles, ColumnSplit{}, wg, smem);
+  else
+    gemm_bf16_tn_deep_body<TN_::TM, TN_::TN, TN_::WM, TN_::WN, TN_::WK, TN_::ST>(tn.A, tn.Mo, tn.B, tn.No, tn.C, tn.Mo, tn.No, tn.K,
+                                                                                 tn.tiles_n, tn.tiles, wg, smem);
+}
+
+template <typename NT_, typename TN_>
+hipError_t launch_pair(NtArgs nt, TnArgs tn, bool nt_first, hipStream_t s) {
+  static_assert(NT_::WM * NT_::WN * NT_::WK == 8 && TN_::WM * TN_::WN * TN_::WK == 8, "512 threads each");
+  constexpr size_t a = deep_lds(NT_::TM, NT_::TN, NT_::WK, NT_::ST * NT_::WK * (NT_::TM + NT_::TN)),
+                   b = deep_lds(TN_::TM, TN_::TN, TN_::WK, TN_::ST * (TN_::TM + TN_::TN)), smem = a > b ? a : b;
+  static_assert(smem <= 160 * 1024, "LDS");
+  nt.tiles_n = (nt.N + NT_::TN - 1) / NT_::TN;
+  nt.tiles = (int)((nt.M + NT_::TM - 1) / NT_::TM) * nt.tiles_n;
+  tn.tiles_n = (tn.No + TN_::TN - 1) / TN_::TN;
+  tn.tiles = (tn.Mo + TN_::TM - 1) / TN_::TM * tn.tiles_n;
+  const int n_nt = (nt.tiles + 7) / 8 * 8, n_tn = (tn.tiles + 7) / 8 * 8;
+  constexpr auto kernel = gemm_bf16_pair_kernel<NT_, TN_>;
+  if (hipError_t e = raise_lds_limit<kernel>(smem); e != hipSuccess) return e;
+  kernel<<<n_nt + n_tn, 512, smem, s>>>(nt, tn, nt_first ? n_nt : n_tn, nt_first ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -832,6 +894,29 @@ hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long 
   const int blocks = ((Mo + 31) / 32) * ((No + 127) / 128);
   splitk_reduce_kernel<<<blocks, 256, 0, s>>>(part, splits, Mo, No, (bf16_t *)C);
   return hipGetLastError();
+}
+
+hipError_t gemm_adjoint_pair(const void *d_C, const void *W, void *d_A, const void *A, void *d_W, long long rows, int n_in, int n_out,
+                             float *part, hipStream_t s) {
+  const PairForm f = gemm_pair(rows, n_in, n_out);
+  if (!f.one_launch) {
+    if (hipError_t e = gemm_tn_mfma_bf16(A, n_in, d_C, n_out, d_W, n_in, n_out, rows, part, s); e != hipSuccess) return e;
+    return gemm_mfma_bf16(d_C, W, d_A, rows, n_in, n_out, s);
+  }
+  const NtArgs nt{(const bf16_t *)d_C, (const bf16_t *)W, (bf16_t *)d_A, rows, n_in, n_out, 0, 0};
+  const TnArgs tn{(const bf16_t *)A, (const bf16_t *)d_C, (bf16_t *)d_W, n_in, n_out, rows, 0, 0};
+#define PAIR(NT_)                                                                               \
+  switch (f.tn) {                                                                               \
+    case TN_64x64: return launch_pair<NT_, TnDeep64x64>(nt, tn, f.nt_first, s);                 \
+    case TN_64x128: return launch_pair<NT_, TnDeep64x128>(nt, tn, f.nt_first, s);               \
+    default: return launch_pair<NT_, TnDeep128x128>(nt, tn, f.nt_first, s);                     \
+  }
+  switch (f.nt) {
+    case NT_64x64: PAIR(NtDeep64x64)
+    case NT_64x128: PAIR(NtDeep64x128)
+    default: PAIR(NtDeep128x128)
+  }
+#undef PAIR
 }
 
 hipError_t transpose_bf16(const void *src, void *dst, int rows, int cols, hipStream_t s) {

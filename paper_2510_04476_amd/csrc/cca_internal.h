@@ -121,6 +121,11 @@ size_t gemm_tn_scratch_bytes(int Mo, int No, long long K);
 hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No,
                              long long K, float *part, hipStream_t s);
 
+// The two adjoints of C (rows, n_out) = A (rows, n_in) W (n_in, n_out): d_A = d_C W^T and d_W = A^T d_C, in one launch where that is the
+// faster (gemm_pair).  Both products must be supported; `part` as for gemm_tn_mfma_bf16.
+hipError_t gemm_adjoint_pair(const void *d_C, const void *W, void *d_A, const void *A, void *d_W, long long rows, int n_in, int n_out,
+                             float *part, hipStream_t s);
+
 // ---- generic backward kernels (any supported shape, fp32 or bf16 storage) ----
 // C (M,N) = op(A) op(B); ta: A is stored (K,M); tb: B is stored (N,K)
 hipError_t gemm_generic_ex(bool bf16, const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb,

@@ -18,7 +18,7 @@ enum NtTile { NT_256x256, NT_256x192, NT_64x64, NT_64x128, NT_128x128_8W, NT_128
 //   128 x 128 at 4 wavefronts, two workgroups per CU (1.04, 4.4), a last round of one per CU (0.61, 3.2)
 // e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).  With a fit over K = 1024
 // and 2048 alone, 6000 x 2048 x 4096 ran on 128 x 128 at 8 wavefronts, 126 us where 256 x 192 takes 104; 4593 x 4096 x 4096: 216 for 173.
-inline NtTile nt_tile(long long M, int N, int K) {
+inline NtTile nt_tile(long long M, int N, int K, double *us = nullptr) {
   const double slabs = (double)(K / 64);
   auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
   auto cost = [&](int tm, int tn, double per_slab, double fixed) {
@@ -31,6 +31,7 @@ inline NtTile nt_tile(long long M, int N, int K) {
   const bool halves = K % 128 == 0;  // the shapes that split a slab over two halves of the wavefronts
   const double c64x128 = halves ? cost(64, 128, 0.354, 3.0) : 1e30, c64 = halves ? cost(64, 64, 0.232, 2.2) : 1e30;
   const double small = fmin(fmin(c128, c128x2), fmin(c64x128, c64));
+  if (us) *us = fmin(fmin(c192, c256), small);
   if (fmin(c192, c256) <= small) return c192 < c256 ? NT_256x192 : NT_256x256;
   if (c64 == small) return NT_64x64;
   if (c64x128 == small) return NT_64x128;
@@ -69,7 +70,7 @@ inline int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
 // and (0.60, 1.5) at two; the split form as in tn_splits.  2048 x 1536 over 1024 tokens split 30.8 us, 13.9 this way, over
 // 4000 45.4 and 43.3, over 8000 66.7 and 83.0; 1024 x 2048 over 1024 tokens 31.3 and 11.1, over 16384 82.5 and 136.9; 2048 x 2048 over
 // 8000 83.5 and 91.7, over 4000 53.0 and 46.7.
-inline TnTile tn_tile(int Mo, int No, long long K) {
+inline TnTile tn_tile(int Mo, int No, long long K, double *us = nullptr) {
   const double slabs = (double)((K + 63) / 64);
   auto tiles = [&](int tm, int tn) { return (long long)((Mo + tm - 1) / tm) * ((No + tn - 1) / tn); };
   auto busy = [](long long t) { return t < 256 ? (double)t / 256.0 : 1.0; };
@@ -80,8 +81,52 @@ inline TnTile tn_tile(int Mo, int No, long long K) {
                c64x128 = (double)((t64x128 + 255) / 256) * (slabs * (0.455 + 0.045 * pow(busy(t64x128), 2.0)) + 3.0),
                c64 = t64 <= 256 ? slabs * 0.30 + 2.0 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
   const double small = fmin(c128, fmin(c64x128, c64));
+  if (us) *us = fmin(small, split_us);
   if (small >= split_us) return TN_SPLIT;
   return c64 == small ? TN_64x64 : c64x128 == small ? TN_64x128 : TN_128x128;
+}
+
+// ---- the two adjoints of a projection, d_A (rows, n_in) = d_C (rows, n_out) W^T and d_W (n_in, n_out) = A^T d_C -----------------
+// One launch on small tiles of both, one workgroup per CU, the product with the longer tiles first, or a launch each in its own best
+// form.  The time of the one launch is that of dealing the two kinds of tiles to 256 CUs in that order, each tile at its time from
+// the fits above with all CUs at work.
+struct PairForm {
+  bool one_launch;
+  NtTile nt;
+  TnTile tn;
+  bool nt_first;
+};
+inline double dealt(long long n_long, double t_long, long long n_short, double t_short) {
+  const long long full = n_long / 256, more = n_long % 256;  // `more` CUs take one long tile more
+  if (!more) return (double)full * t_long + (double)((n_short + 255) / 256) * t_short;
+  const long long fits = (256 - more) * (long long)(t_long / t_short);  // short tiles beside the last long ones
+  const double low = (double)full * t_long, high = low + t_long;
+  if (n_short > fits) return high + (double)((n_short - fits + 255) / 256) * t_short;
+  return fmax(high, low + (double)((n_short + 255 - more) / (256 - more)) * t_short);
+}
+inline PairForm gemm_pair(long long rows, int n_in, int n_out) {
+  PairForm best{false, NT_256x256, TN_SPLIT, true};
+  double nt_us, tn_us;
+  nt_tile(rows, n_in, n_out, &nt_us);
+  tn_tile(n_in, n_out, rows, &tn_us);
+  double least = nt_us + tn_us + 2.0;
+  const double s_nt = (double)(n_out / 64), s_tn = (double)((rows + 63) / 64);
+  auto tiles = [](long long m, long long n, int tm, int tn) { return ((m + tm - 1) / tm) * ((n + tn - 1) / tn); };
+  const bool halves = n_out % 128 == 0;
+  const struct { NtTile t; int tm, tn; double us; bool ok; } nts[3] = {{NT_64x64, 64, 64, s_nt * 0.232 + 2.2, halves},
+                                                                      {NT_64x128, 64, 128, s_nt * 0.354 + 3.0, halves},
+                                                                      {NT_128x128_8W, 128, 128, s_nt * 0.528 + 3.0, true}};
+  const struct { TnTile t; int tm, tn; double us; } tns[3] = {{TN_64x64, 64, 64, s_tn * 0.30 + 2.0},
+                                                              {TN_64x128, 64, 128, s_tn * 0.50 + 3.0},
+                                                              {TN_128x128, 128, 128, s_tn * 0.715 + 3.0}};
+  for (const auto &a : nts)
+    for (const auto &b : tns) {
+      if (!a.ok) continue;
+      const long long na = tiles(rows, n_in, a.tm, a.tn), nb = tiles(n_in, n_out, b.tm, b.tn);
+      const double us = a.us >= b.us ? dealt(na, a.us, nb, b.us) : dealt(nb, b.us, na, a.us);
+      if (us < least) least = us, best = PairForm{true, a.t, b.t, a.us >= b.us};
+    }
+  return best;
 }
 
 // ---- grids of the attention kernels (forward and backward, d_h <= 128), one 8-wavefront workgroup per CU -----------------

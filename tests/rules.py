@@ -22,6 +22,10 @@ int r_stream_takes_256(long long rows, int heads, int R, int taps, int adjoint) 
 int r_generic_attention_rows(long long BH, int T, int dh, int causal) { return generic_attention_rows(BH, T, dh, causal); }
 int r_generic_attention_bwd_16(long long BHk, int T, int dh, int causal) { return generic_attention_bwd_16(BHk, T, dh, causal); }
 int r_grad_splits(long long units, long long rows) { return grad_splits(units, rows); }
+int r_gemm_pair(long long rows, int n_in, int n_out) {
+  const PairForm f = gemm_pair(rows, n_in, n_out);
+  return f.one_launch ? 1 + f.nt_first + 2 * f.nt + 32 * f.tn : 0;
+}
 int r_pair_blocks(long long BH, int causal, int blocks) { return pair_blocks(BH, causal, blocks); }
 }
 """
@@ -43,7 +47,7 @@ def _lib():
     for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
-                           r_generic_attention_bwd_16=[L, I, I, I], r_grad_splits=[L, L],
+                           r_generic_attention_bwd_16=[L, I, I, I], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
                            r_decode_keys_per_split=[L, I, I, I]).items():
         getattr(lib, name).argtypes = args
     return lib
@@ -95,3 +99,9 @@ def generic_attention_bwd_16(BHk, T, dh, causal):
 
 def grad_splits(units, rows):
     return _lib().r_grad_splits(units, rows)
+
+
+def gemm_pair(rows, n_in, n_out):
+    """None (a launch each) or (tile of the first adjoint, tile of the second, the first one's tiles come first)"""
+    f = _lib().r_gemm_pair(rows, n_in, n_out)
+    return (NT_TILES[(f - 1) // 2 % 16], TN_TILES[(f - 1) // 32], bool((f - 1) % 2)) if f else None

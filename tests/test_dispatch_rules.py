@@ -20,6 +20,22 @@ def test_weight_gradient_cases_reach_every_tile():
     assert len(splits) >= 3 and max(splits) > 16  # few and many parts to add
 
 
+def test_projection_adjoint_cases_reach_every_form():
+    reached = set()
+    for rows, Hq, Hk, dh, E in small.PAIR_CASES:
+        reached |= {rules.gemm_pair(rows, Hq * dh, E), rules.gemm_pair(rows, E, (Hq + 2 * Hk) * dh)}
+    assert None in reached and {True, False} == {f[2] for f in reached if f}
+    # over rows, widths and heads of the repository's layouts: no pair of forms is left out
+    chosen = set()
+    for rows in list(range(64, 2048, 97)) + [2048, 3000, 4096, 6000]:
+        for E in (256, 512, 1024, 1536, 2048):
+            for n in (128, 256, 512, 768, 1024, 1536, 2048, 3072):
+                chosen |= {rules.gemm_pair(rows, n, E), rules.gemm_pair(rows, E, n)}
+    forms = lambda s: {f[:2] for f in s if f}
+    print(sorted(forms(chosen)), sorted(forms(reached)))
+    assert forms(chosen) == forms(reached)
+
+
 def test_attention_cases_reach_both_block_orders():
     paired = {(causal, rules.pair_blocks(B * Hq, causal, -(-T // 128))) for B, T, Hq, Hk, dh, causal, normed in small.SPLIT_CASES}
     assert paired == {(True, True), (True, False), (False, False)}

@@ -88,6 +88,36 @@ def test_weight_gradient_tiles(rows, Hq, dh, E):
     check_product(g.w_out, saved.o[0].double().t().contiguous() @ d_out[0].double(), rows)
 
 
+# rows x (query heads, KV heads, head width, E): the two adjoints of a projection in one launch, every pair of tile forms that the rule
+# chooses, more tiles than CUs, rows short of and past a tile's edge, and products large enough for a launch each
+PAIR_CASES = [(70, 4, 2, 64, 512), (70, 8, 2, 128, 2048), (130, 8, 2, 128, 2048), (400, 8, 2, 128, 2048),
+              (130, 4, 4, 128, 1024), (1000, 8, 2, 128, 2048), (511, 4, 4, 64, 1024), (1025, 8, 8, 64, 1024), (1999, 8, 2, 128, 2048), (300, 12, 12, 64, 1536), (4001, 8, 2, 128, 2048), (2050, 16, 16, 64, 1024)]
+
+
+@pytest.mark.parametrize("rows,Hq,Hk,dh,E", PAIR_CASES)
+def test_projection_adjoints_in_one_launch(rows, Hq, Hk, dh, E):
+    """d W_O against the product of its operands; d_x and d W_down, whose other operand stays inside, against the calls that want
+    only one of them (a launch each, other tiles): the sums differ in order, so each side rounds the same fp32 value to within its
+    error, two bf16 neighbours at most."""
+    say("projection adjoints", rows, Hq, Hk, dh, E)
+    cfg = P.CCAConfig(B=1, T=rows, d_model=E, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, flags=P.CCA_FLAGS_MHA)
+    w = P.CCAWeights(w_down=rnd(E, cfg.n_lat, seed=2, scale=0.02), w_out=rnd(cfg.e_q, E, seed=4, scale=0.02))
+    x, d_out = rnd(1, rows, E, seed=1), rnd(1, rows, E, seed=5)
+    saved = P.CCASaved.allocate(cfg, "cuda")
+    P.cca_forward(cfg, w, x, saved=saved)
+    nan = lambda t: torch.full_like(t, float("nan"))
+    d_x, g = P.cca_backward(cfg, w, x, saved, d_out, d_x=nan(x), grads=P.CCAGrads(w_down=nan(w.w_down), w_out=nan(w.w_out)))
+    only_x, _ = P.cca_backward(cfg, w, x, saved, d_out, d_x=nan(x), grads=P.CCAGrads(w_out=nan(w.w_out)))
+    torch.cuda.synchronize()
+    check_product(g.w_out, saved.o[0].double().t().contiguous() @ d_out[0].double(), rows)
+    # (neighbours in bf16 are up to 2^-7 of the value apart, twice what check_product allows against an exact product)
+    check_product(d_x[0].double() / 2 + only_x[0].double() / 2, only_x[0], cfg.n_lat)
+    # d W_down = x^T d_lat and d_x = d_lat W_down^T: <d W_down, W> = <d_x, x> for any d_lat
+    lhs, rhs = (g.w_down.double() * w.w_down.double()).sum(), (d_x.double() * x.double()).sum()
+    noise = 2.0 ** -8 * float(((d_x.double() * x.double()).square().sum() + (g.w_down.double() * w.w_down.double()).square().sum()).sqrt())
+    assert abs(float(lhs - rhs)) <= 4 * noise, (float(lhs), float(rhs), noise)
+
+
 # B, T, Hq, Hk, d_h, causal, normalised: odd lengths, one tile more or less than a pair, rows whose second key group is
 # empty, several query blocks, paired and unpaired grids; scores bounded and not
 SPLIT_CASES = [(1, 300, 2, 1, 128, True, True), (1, 321, 3, 3, 64, True, False), (2, 385, 2, 2, 128, False, True),
