@@ -231,7 +231,7 @@ template <int DH, bool CAUSAL, int DQ_NT_, int KS = 1>
 __device__ __forceinline__ void attn_bwd_dq_body(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
     const bf16_t *__restrict__ dO, const float *__restrict__ LSE, const float *__restrict__ DELTA,
-    bf16_t *__restrict__ dQ, int T, int Hq, int Hk, int BH, int nqb, int paired, float scale, unsigned char *smem) {
+    bf16_t *__restrict__ dQ, int T, int Hq, int Hk, int BH, int nqb, int paired, float scale, int idx, unsigned char *smem) {
   CCA_BWD_GEOMETRY(DH);
   constexpr int NTG = DQ_NT_ / KS, DQ_BQ = NTG / 2;  // threads of a key group; query rows
   constexpr bool WIDE = DH > 128;
@@ -245,7 +245,6 @@ __device__ __forceinline__ void attn_bwd_dq_body(
   // (one group of 256 threads: the plain index, whose range the compiler knows; the remainder changed the shape of the loops)
   const int tid = WIDE ? threadIdx.x : threadIdx.x % NTG, lane = tid & 63, wave = tid >> 6;  // within the key group
   const int l32 = lane & 31, half = lane >> 5;
-  const int idx = blockIdx.x;
   const int bh = idx % BH, slot = idx / BH;
   const int b = bh / Hq, h = bh % Hq, g = h / (Hq / Hk);
   const float c = scale * LOG2E;
@@ -534,10 +533,10 @@ __global__ __launch_bounds__(DQ_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) v
     bf16_t *__restrict__ dQ, int T, int Hq, int Hk, int BH, int nqb, int paired, float scale) {
   if constexpr (KS == 1) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BKV * (DH * 2 + 64)];
-    attn_bwd_dq_body<DH, CAUSAL, DQ_NT, KS>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, smem);
+    attn_bwd_dq_body<DH, CAUSAL, DQ_NT, KS>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, blockIdx.x, smem);
   } else {  // dynamic LDS: with a static array every LDS read would wait for the tile loads in flight
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
-    attn_bwd_dq_body<DH, CAUSAL, DQ_NT, KS>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, dyn_smem);
+    attn_bwd_dq_body<DH, CAUSAL, DQ_NT, KS>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, blockIdx.x, dyn_smem);
   }
 }
 
@@ -547,7 +546,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const bf16_t *__restrict__ dO, const float *__restrict__ LSE, const float *__restrict__ DELTA,
     bf16_t *__restrict__ dQ, int T, int Hq, int Hk, int BH, int nqb, int paired, float scale) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BKV * (DH * 2 + 64)];
-  attn_bwd_dq_body<DH, CAUSAL, 256>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, smem);
+  attn_bwd_dq_body<DH, CAUSAL, 256>(Q, K, V, dO, LSE, DELTA, dQ, T, Hq, Hk, BH, nqb, paired, scale, blockIdx.x, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -570,12 +569,19 @@ constexpr int KV_NT = 512;  // threads; a workgroup owns KV_NT / 2 keys
 // each, so that both groups' tiles fit the LDS); their sums are added through LDS.
 constexpr int kv_tile_rows(int threads, int ks) { return threads == 256 || ks == 2 ? 32 : 64; }
 
+// What a workgroup keeps in LDS beside the tiles
+template <int DH, int KV_NT_, int KS>
+struct __attribute__((aligned(16))) KvLds {
+  float stat[KS][2][2][kv_tile_rows(KV_NT_, KS)];
+  u32x4 vf[KV_NT_ / KS / 64][DH / 16][64];
+};
+
 template <int DH, bool CAUSAL, bool PARTIAL, int KV_NT_, int KS = 1>
 __device__ __forceinline__ void attn_bwd_dkdv_body(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
     const bf16_t *__restrict__ dO, const float *__restrict__ LSE, const float *__restrict__ DELTA,
     bf16_t *__restrict__ dK, bf16_t *__restrict__ dV, float *__restrict__ dKp, float *__restrict__ dVp, int T, int Hq,
-    int Hk, int BH, int nkb, float scale, unsigned char *smem) {
+    int Hk, int BH, int nkb, float scale, int idx, unsigned char *smem, KvLds<DH, KV_NT_, KS> &lds) {
   CCA_BWD_GEOMETRY(DH);
   constexpr int KV_NT = KV_NT_ / KS, KV_BK = KV_NT / 2, BQT = kv_tile_rows(KV_NT_, KS);  // threads of a group; its keys
   constexpr bool WIDE = DH > 128;
@@ -586,18 +592,17 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
   // next tile's loads in front of each step)
   // [buf][-lse2 | -Delta][row]: the S and dP chains START from these (lane = key, register = query row), so that the
   // chains deliver S - lse and dP - Delta and the arithmetic needs no subtraction
-  __shared__ __attribute__((aligned(16))) float sStat_[KS][2][2][BQT];
+  float (*const sStat_)[2][2][BQT] = lds.stat;
   // this workgroup's V rows as MFMA operand fragments, [wavefront][kk][lane] x 16 bytes: each wavefront keeps its own
   // (read back one fragment per dP product; holding them in registers next to the K fragments and the two
   // accumulators leaves no room for fragments requested ahead of their use)
-  __shared__ __attribute__((aligned(16))) u32x4 sVf[KV_NT / 64][KK][64];
+  u32x4 (*const sVf)[KK][64] = lds.vf;
   const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / KV_NT);
   unsigned char *const sQ = smem + kg * 4 * TILE, *const sD = sQ + 2 * TILE;
   float (*const sStat)[2][BQT] = sStat_[kg];
 
   const int tid = WIDE ? threadIdx.x : threadIdx.x % KV_NT, lane = tid & 63, wave = tid >> 6;  // within the group
   const int l32 = lane & 31, half = lane >> 5;
-  const int idx = blockIdx.x;
   const int bh = idx % BH, kb = idx / BH;  // early key blocks (most query tiles when causal) first
   const int b = bh / Hq, h = bh % Hq, g = h / (Hq / Hk);
   const int k0 = kb * KV_BK, kw0 = k0 + wave * 32;
@@ -612,10 +617,23 @@ __device__ __forceinline__ void attn_bwd_dkdv_body(
     const int s = min(kw0 + l32, T - 1);
     const bf16_t *pk = K + (((long long)b * T + s) * Hk + g) * DH + half * 8;
     const bf16_t *pv = V + (((long long)b * T + s) * Hk + g) * DH + half * 8;
+    if constexpr (KS == 1) {
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(pk + kk * 16));
-      if (kg == 0) sVf[wave][kk][lane] = *reinterpret_cast<const u32x4 *>(pv + kk * 16);  // the groups share them
+      for (int kk = 0; kk < KK; ++kk) {
+        kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(pk + kk * 16));
+        sVf[wave][kk][lane] = *reinterpret_cast<const u32x4 *>(pv + kk * 16);
+      }
+    } else {  // the groups share V.  (Loaded by both: behind the condition each load was waited for before the next.)
+      u32x4 vf[KK];
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(pk + kk * 16));
+        vf[kk] = *reinterpret_cast<const u32x4 *>(pv + kk * 16);
+      }
+      if (kg == 0) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) sVf[wave][kk][lane] = vf[kk];
+      }
     }
   }
   f32x16 dk[DT], dv[DT];  // dK^T, dV^T: lane = key, registers = channels
@@ -910,7 +928,8 @@ __global__ __launch_bounds__(KV_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) v
     bf16_t *__restrict__ dK, bf16_t *__restrict__ dV, float *__restrict__ dKp, float *__restrict__ dVp, int T, int Hq,
     int Hk, int BH, int nkb, float scale) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  attn_bwd_dkdv_body<DH, CAUSAL, PARTIAL, KV_NT, KS>(Q, K, V, dO, LSE, DELTA, dK, dV, dKp, dVp, T, Hq, Hk, BH, nkb, scale, smem);
+  __shared__ KvLds<DH, KV_NT, KS> lds;
+  attn_bwd_dkdv_body<DH, CAUSAL, PARTIAL, KV_NT, KS>(Q, K, V, dO, LSE, DELTA, dK, dV, dKp, dVp, T, Hq, Hk, BH, nkb, scale, blockIdx.x, smem, lds);
 }
 
 template <int DH, bool CAUSAL, bool PARTIAL>
@@ -920,7 +939,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     bf16_t *__restrict__ dK, bf16_t *__restrict__ dV, float *__restrict__ dKp, float *__restrict__ dVp, int T, int Hq,
     int Hk, int BH, int nkb, float scale) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  attn_bwd_dkdv_body<DH, CAUSAL, PARTIAL, 256>(Q, K, V, dO, LSE, DELTA, dK, dV, dKp, dVp, T, Hq, Hk, BH, nkb, scale, smem);
+  __shared__ KvLds<DH, 256, 1> lds;
+  attn_bwd_dkdv_body<DH, CAUSAL, PARTIAL, 256>(Q, K, V, dO, LSE, DELTA, dK, dV, dKp, dVp, T, Hq, Hk, BH, nkb, scale, blockIdx.x, smem, lds);
+}
+
+// Both, for grids that take two groups of wavefronts in either kernel: each leaves CUs idle, and neither needs the other.  The key
+// blocks, the longer chains, come first: workgroups [0, n_kv).  Backward
+// pass, two launches -> this one (us): 2 x 512 tokens, 8 query and 2 KV heads of 128: 138.6 -> 121.9; 2 x 1024: 209.6 -> 185.8;
+// 1 x 512, 8 heads of 64: 73.3 -> 62.5; 1 x 4096: 254.6 -> 218.4.
+struct BwdPairArgs {
+  const bf16_t *Q, *Qs, *K, *V, *dO;
+  const float *LSE, *DELTA;
+  bf16_t *dQ, *dK, *dV;
+  float *dKp, *dVp;
+  int T, Hq, Hk, BH, nqb, nkb, paired, n_kv;
+  float scale;
+};
+template <int DH, bool CAUSAL, bool PARTIAL>
+__global__ __launch_bounds__(KV_NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_pair_kernel(BwdPairArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x < a.n_kv)
+    attn_bwd_dkdv_body<DH, CAUSAL, PARTIAL, KV_NT, 2>(a.Qs, a.K, a.V, a.dO, a.LSE, a.DELTA, a.dK, a.dV, a.dKp, a.dVp, a.T, a.Hq, a.Hk,
+                                                      a.BH, a.nkb, a.scale, blockIdx.x, smem + sizeof(KvLds<DH, KV_NT, 2>),
+                                                      *reinterpret_cast<KvLds<DH, KV_NT, 2> *>(smem));
+  else
+    attn_bwd_dq_body<DH, CAUSAL, DQ_NT, 2>(a.Q, a.K, a.V, a.dO, a.LSE, a.DELTA, a.dQ, a.T, a.Hq, a.Hk, a.BH, a.nqb, a.paired, a.scale,
+                                           (int)blockIdx.x - a.n_kv, smem);
 }
 
 // out[(row, g), :] = bf16(sum_r part[(row, g*R + r), :]) for dK and dV, 4 channels per thread, fixed order
@@ -1018,7 +1062,26 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
     attn_bwd_dq_kernel<DH, C_, 2><<<(unsigned)(G_), NTH, dq_smem, s>>>(ARGS_DQ);                               \
   }                                                                                                           \
   else attn_bwd_dq_kernel<DH, C_, 1><<<(unsigned)(G_), NTH, 0, s>>>(ARGS_DQ);
-  if (causal) {
+  const unsigned gdq = (unsigned)((long long)BH * (paired ? (nqb + 1) / 2 : nqb));
+#define LAUNCH_PAIR(C_, P_)                                                                                       \
+  {                                                                                                               \
+    if constexpr (!WIDE) {                                                                                        \
+      constexpr size_t kv_all = kv_smem + sizeof(KvLds<DH, NTH, 2>), lds = dq_smem > kv_all ? dq_smem : kv_all;     \
+      static_assert(lds <= 160 * 1024, "LDS");                                                                    \
+      e = raise_lds_limit<attn_bwd_pair_kernel<DH, C_, P_>>(lds);                                                 \
+      if (e != hipSuccess) return e;                                                                              \
+      attn_bwd_pair_kernel<DH, C_, P_><<<gkv + gdq, NTH, lds, s>>>(                                               \
+          BwdPairArgs{(const bf16_t *)q, qs, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)d_o, lse, delta, \
+                      (bf16_t *)d_q, (bf16_t *)d_k, (bf16_t *)d_v, pk, pv, d.T, d.Hq, d.Hk, BH, nqb, nkb, paired,   \
+                      (int)gkv, d.scale});                                                                        \
+    }                                                                                                             \
+  }
+  if (dq_halves && kv_halves && (long long)BH * (nkb + nqb) < (1ll << 31)) {
+    if (causal && partial) LAUNCH_PAIR(true, true)
+    else if (causal) LAUNCH_PAIR(true, false)
+    else if (partial) LAUNCH_PAIR(false, true)
+    else LAUNCH_PAIR(false, false)
+  } else if (causal) {
     LAUNCH_DQ(true, (long long)BH * (paired ? (nqb + 1) / 2 : nqb));
     if (partial) {
       LAUNCH_KV(true, true);
@@ -1033,6 +1096,7 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
       LAUNCH_KV(false, false);
     }
   }
+#undef LAUNCH_PAIR
 #undef LAUNCH_KV
 #undef LAUNCH_KV_KS
 #undef LAUNCH_DQ
