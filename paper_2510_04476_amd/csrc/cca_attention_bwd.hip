@@ -27,7 +27,7 @@
 // d_k then contracts dS with the scaled q and is multiplied by ln 2 instead of scale.
 #include <type_traits>
 
-#include "cca_internal.h"
+#include "cca_setup.h"
 
 namespace cca {
 
@@ -186,9 +186,13 @@ template <int DH>
 __global__ __launch_bounds__(256) void delta_scale_q_kernel(const bf16_t *__restrict__ dO, const bf16_t *__restrict__ O,
                                                    const bf16_t *__restrict__ OLO, float *__restrict__ delta,
                                                    const bf16_t *__restrict__ Q, bf16_t *__restrict__ Qs, float c,
-                                                   long long n_rows, int T, int Hq) {
+                                                   long long n_rows, int T, int Hq, PrologueSetup setup) {
+  if ((int)blockIdx.x < setup.n_blocks) {  // (first: a chain of fp64 functions each)
+    setup_block(setup, blockIdx.x);
+    return;
+  }
   constexpr int LPR = DH / 8;  // lanes per row
-  const long long row = (long long)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;  // row = (b*T + t)*Hq + h
+  const long long row = (long long)(blockIdx.x - setup.n_blocks) * (256 / LPR) + threadIdx.x / LPR;  // row = (b*T + t)*Hq + h
   const int sub = threadIdx.x % LPR;
   float acc = 0.f;
   if (row < n_rows) {
@@ -1007,7 +1011,7 @@ size_t attention_bwd_scratch_bytes(const Dims &d) {
 template <int DH>
 static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k, const void *v, const void *o,
                                     const void *o_lo, const float *lse, const void *d_o, void *d_q, void *d_k, void *d_v,
-                                    float *delta, hipStream_t s) {
+                                    float *delta, hipStream_t s, const PrologueSetup *setup_, KvParts *parts) {
   const bool causal = d.flags & CCA_CAUSAL;
   const long long n_rows = d.rows() * d.Hq;
   constexpr int DELTA_ROWS = 256 / (DH / 8);  // rows per workgroup of delta_scale_q_kernel
@@ -1022,9 +1026,10 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
   float *pv = pk + (size_t)d.rows() * d.e_q;
   bf16_t *qs = reinterpret_cast<bf16_t *>(reinterpret_cast<char *>(delta) + delta_bytes(d) +
                                           (d.R > 1 ? 2 * (size_t)d.rows() * d.e_q * sizeof(float) : 0));
-  delta_scale_q_kernel<DH><<<(unsigned)((n_rows + DELTA_ROWS - 1) / DELTA_ROWS), 256, 0, s>>>(
+  const PrologueSetup setup = setup_ ? *setup_ : PrologueSetup{};
+  delta_scale_q_kernel<DH><<<(unsigned)((n_rows + DELTA_ROWS - 1) / DELTA_ROWS) + setup.n_blocks, 256, 0, s>>>(
       (const bf16_t *)d_o, (const bf16_t *)o, (const bf16_t *)o_lo, delta, (const bf16_t *)q, qs, d.scale * LOG2E, n_rows, d.T,
-      d.Hq);
+      d.Hq, setup);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 #define ARGS_DQ (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)d_o, lse, delta, (bf16_t *)d_q, \
@@ -1102,7 +1107,8 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
 #undef LAUNCH_DQ
 #undef ARGS_DQ
 #undef ARGS_KV
-  if (partial) {
+  if (parts) parts->k = partial ? pk : nullptr, parts->v = partial ? pv : nullptr;
+  if (partial && !parts) {
     const long long n_out = d.rows() * d.Hk * (DH / 4);
     group_sum_kernel<DH><<<(unsigned)((n_out + 255) / 256), 256, 0, s>>>(pk, pv, (bf16_t *)d_k, (bf16_t *)d_v, n_out, d.R);
   }
@@ -1111,10 +1117,10 @@ static hipError_t attention_bwd_run(const Dims &d, const void *q, const void *k,
 
 hipError_t attention_bwd_bf16(const Dims &d, const void *q, const void *k, const void *v, const void *o,
                               const void *o_lo, const float *lse, const void *d_o, void *d_q, void *d_k, void *d_v, float *delta,
-                              hipStream_t s) {
-  return d.dh == 64    ? attention_bwd_run<64>(d, q, k, v, o, o_lo, lse, d_o, d_q, d_k, d_v, delta, s)
-         : d.dh == 128 ? attention_bwd_run<128>(d, q, k, v, o, o_lo, lse, d_o, d_q, d_k, d_v, delta, s)
-                       : attention_bwd_run<256>(d, q, k, v, o, o_lo, lse, d_o, d_q, d_k, d_v, delta, s);
+                              hipStream_t s, const PrologueSetup *setup, KvParts *parts) {
+  return d.dh == 64    ? attention_bwd_run<64>(d, q, k, v, o, o_lo, lse, d_o, d_q, d_k, d_v, delta, s, setup, parts)
+         : d.dh == 128 ? attention_bwd_run<128>(d, q, k, v, o, o_lo, lse, d_o, d_q, d_k, d_v, delta, s, setup, parts)
+                       : attention_bwd_run<256>(d, q, k, v, o, o_lo, lse, d_o, d_q, d_k, d_v, delta, s, setup, parts);
 }
 
 }  // namespace cca

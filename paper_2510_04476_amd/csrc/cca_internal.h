@@ -107,12 +107,29 @@ hipError_t prologue_split_copy(const Dims &d, const void *lat, void *q, void *k,
 hipError_t prologue_split_copy_bwd(const Dims &d, const void *d_q, const void *d_k, const void *d_v, void *d_lat,
                                    hipStream_t s);
 
-// ---- backward of the attention stage (bf16, d_h = 128) ----------------------
+// The set-up of the fused prologue or of its adjoint (cca_setup.h): `n_blocks` workgroups of 256 threads, each by itself.
+struct PrologueSetup {
+  const bf16_t *w0, *w1;  // w0 = NULL: no sequence convolution (k_seq = 1)
+  bf16_t *wc;
+  float2 *ropeA, *ropeB;
+  float rope_base;
+  int heads, dh, D, k_seq, k_ch, n_thi, transposed, n_fold, n_blocks;
+};
+
+// ---- backward of the attention stage (bf16, d_h = 64, 128, 256) -------------
 bool attention_bwd_supported(const Dims &d);
 size_t attention_bwd_scratch_bytes(const Dims &d);  // Delta (B,H_q,T) fp32
+// dK and dV as fp32 (B,T,H_q,d_h), one per query head, where their sums over a group are left to the prologue's adjoint, which
+// then also writes d_v (bf16)
+struct KvParts {
+  const float *k, *v;
+  bf16_t *d_v;
+};
+// `setup` (may be NULL): done in the first launch, beside Delta.  `parts` (may be NULL): with more than one query head to a KV head
+// d_k and d_v are not written, and k, v are set (else they are NULL).
 hipError_t attention_bwd_bf16(const Dims &d, const void *q, const void *k, const void *v, const void *o,
                               const void *o_lo, const float *lse, const void *d_o, void *d_q, void *d_k, void *d_v, float *delta,
-                              hipStream_t s);
+                              hipStream_t s, const PrologueSetup *setup = nullptr, KvParts *parts = nullptr);
 
 // C (Mo,No) = A (K,Mo)^T * B (K,No): weight gradients, contraction over token rows, split over K into fp32
 // partial sums in `part` (gemm_tn_scratch_bytes), added in a fixed order.
@@ -143,7 +160,11 @@ bool prologue_bwd_fused_supported(const Dims &d);
 size_t prologue_bwd_fused_scratch_bytes(const Dims &d);
 hipError_t prologue_bwd_fused_bf16(const Dims &d, const cca_weights &w, const void *lat, const void *q, const void *k,
                                    const float *rnorm, const void *d_q, const void *d_k, const void *d_v, void *d_lat,
-                                   const cca_grads *gr, void *scratch, hipStream_t s);
+                                   const cca_grads *gr, void *scratch, hipStream_t s, bool set_up = false,
+                                   const KvParts *parts = nullptr);
+// Its set-up, for a caller that has it done in another launch and then passes `set_up`.  `parts`: instead of d_k and d_v, and d_v is
+// written; may be NULL.
+PrologueSetup prologue_bwd_fused_setup(const Dims &d, const cca_weights &w, void *scratch);
 
 bool prologue_fused_supported(const Dims &d);
 size_t prologue_fused_scratch_bytes(const Dims &d);  // folded filters + RoPE tables; 0 if unsupported

@@ -25,6 +25,8 @@
 // addition formulas in fp32 (an fp32 product t * theta_i alone is off by up to
 // 1e-3 rad at t ~ 16k).
 #include "cca_internal.h"
+#include "cca_dwc.h"
+#include "cca_setup.h"
 #include "cca_transpose.h"
 
 namespace cca {
@@ -68,67 +70,12 @@ __device__ __forceinline__ float lo_f(uint32_t w) { return __uint_as_float(w << 
 __device__ __forceinline__ float hi_f(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
 // ---------------------------------------------------------------------------
-// set-up: folded filters Wc [h][o][d][i] (bf16; d_h = 256: in the slab order of prologue_stream_kernel) and the two RoPE
-// tables
-//   ropeA [t_hi][i]            float2 (cos, sin) of t_hi * 128 * theta_i
-//   ropeB [i / 4][t_lo][i % 4] float2 (cos, sin) of t_lo * theta_i
+// set-up (cca_setup.h), and the transposes of the projection weights where a pass derives everything at once
 // ---------------------------------------------------------------------------
-// d_h = 256: the filter as prologue_stream_kernel moves it, in slabs of all 256 rows x 32 contracted channels of one tap,
-// each slab exactly as it lies in LDS (two rows share a 128-byte line; 16-byte chunk c of row r at line r / 2, position
-// (4 (r mod 2) + c) ^ ((r / 4) mod 4): 16 consecutive rows of one chunk column fall in 16 different bank groups).
-constexpr int SLAB_K = 32, SLAB_BYTES = 256 * SLAB_K * 2;
-__device__ __forceinline__ long long slab_elem(int h, int D, int r, int d, int k) {
-  const int c = (k & 31) >> 3;
-  return ((long long)(h * D + d) * (256 / SLAB_K) + (k >> 5)) * (SLAB_BYTES / 2) + ((r >> 1) * 8 + ((((r & 1) << 2) | c) ^ ((r >> 2) & 3))) * 8 + (k & 7);
-}
-
-__global__ __launch_bounds__(256) void prologue_setup_kernel(FusedArgs a, int D, const bf16_t *__restrict__ w0,
-                                                            const bf16_t *__restrict__ w1, bf16_t *__restrict__ wc,
-                                                            float2 *__restrict__ ropeA, float2 *__restrict__ ropeB,
-                                                            int n_fold_blocks, int n_thi, int transposed, int DH,
-                                                            int n_set_up, TransposePair weights) {
+__global__ __launch_bounds__(256) void prologue_setup_kernel(PrologueSetup setup, TransposePair weights) {
   __shared__ TransposeTile tile;
-  if ((int)blockIdx.x >= n_set_up) {  // the projection weights, where a pass derives everything at once
-    transpose_block(weights, blockIdx.x - n_set_up, tile);
-    return;
-  }
-  const int NH = a.Hq + a.Hk;
-  if ((int)blockIdx.x < n_fold_blocks) {
-    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;  // (h, o, i)
-    if (id >= (long long)NH * DH * DH) return;
-    const int i = (int)(id % DH), o = (int)((id / DH) % DH), h = (int)(id / (DH * DH));
-    const int ch = h * DH + i;  // packed q|k channel: q heads first, then k heads
-    const int ks = (a.flags & CCA_CONV_SEQ) ? a.k_seq : 1, kc = (a.flags & CCA_CONV_CH) ? a.k_ch : 1;
-    for (int d = 0; d < D; ++d) {
-      float acc = 0.f;
-      for (int j = 0; j < kc; ++j) {
-        const int jj = d - j;
-        if (jj < 0 || jj >= ks) continue;
-        const float f0 = (a.flags & CCA_CONV_SEQ) ? bf16_to_f32(w0[(long long)ch * ks + jj]) : 1.f;
-        acc = fmaf(bf16_to_f32(w1[(((long long)h * DH + o) * DH + i) * kc + j]), f0, acc);
-      }
-      // the adjoint convolution contracts over the output channel: filter stored [h][i][d][o]
-      const int r = transposed ? i : o, k = transposed ? o : i;
-      wc[DH == 256 ? slab_elem(h, D, r, d, k) : (((long long)h * DH + r) * D + d) * DH + k] = f32_to_bf16(acc);
-    }
-    return;
-  }
-  const int id = ((int)blockIdx.x - n_fold_blocks) * 256 + threadIdx.x;
-  const int nA = n_thi * (DH / 2), nB = (DH / 2) * 128;
-  if (id < nA) {
-    const int i = id % (DH / 2), thi = id / (DH / 2);
-    const double theta = pow((double)a.rope_base, -2.0 * (double)i / (double)DH);
-    double sn, cs;
-    sincos((double)thi * 128.0 * theta, &sn, &cs);
-    ropeA[id] = make_float2((float)cs, (float)sn);
-  } else if (id < nA + nB) {
-    const int k = id - nA;
-    const int i = k / 128, tlo = k % 128;
-    const double theta = pow((double)a.rope_base, -2.0 * (double)i / (double)DH);
-    double sn, cs;
-    sincos((double)tlo * theta, &sn, &cs);
-    ropeB[((i >> 2) * 128 + tlo) * 4 + (i & 3)] = make_float2((float)cs, (float)sn);
-  }
+  if ((int)blockIdx.x >= setup.n_blocks) transpose_block(weights, blockIdx.x - setup.n_blocks, tile);
+  else setup_block(setup, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -141,23 +88,22 @@ __global__ __launch_bounds__(256) void prologue_setup_kernel(FusedArgs a, int D,
 // DH = d_h (64 or 128): KK fragments of 16 input channels, NTL tiles of 32 output channels, CPR 16-byte chunks per
 // tap of a filter row.
 template <int DH, int D, bool BWD>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void prologue_fused_kernel(
-    FusedArgs a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
+__device__ __forceinline__ void prologue_fused_body(
+    const FusedArgs &a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
     const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB, const float *__restrict__ temp,
-    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm) {
+    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm, int block, unsigned char *smem) {
   constexpr int KK = DH / 16, NTL = DH / 32, CPR = DH / 8;
   constexpr int WROW = D * CPR;  // 16-byte chunks per filter row (one output channel)
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u32x4 *sW = reinterpret_cast<u32x4 *>(smem);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
 
-  if ((int)blockIdx.x >= a.n_conv_blocks) {
+  if (block >= a.n_conv_blocks) {
     // ---- value-shift role: v[t] = [vc[t] | vp[t-1]], 16 bytes per thread, whole rows per wavefront
     const int cpr = a.e_kv / 8;  // chunks per row
     const long long total = a.rows * cpr;
-    const long long first = ((long long)blockIdx.x - a.n_conv_blocks) * (NT * 4);
+    const long long first = ((long long)block - a.n_conv_blocks) * (NT * 4);
     for (int it = 0; it < 4; ++it) {
       const long long id = first + it * NT + tid;
       if (id >= total) break;
@@ -175,8 +121,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   }
 
   const int NH = a.Hq + a.Hk;
-  const bool is_q = (int)blockIdx.x >= a.n_k_blocks;
-  const int bid = is_q ? (int)blockIdx.x - a.n_k_blocks : (int)blockIdx.x;
+  const bool is_q = block >= a.n_k_blocks;
+  const int bid = is_q ? block - a.n_k_blocks : block;
   const int head = is_q ? bid % a.Hq : a.Hq + bid % a.Hk;
   const int tiles_per_wave = is_q ? a.tiles_per_wave : a.tiles_per_wave_k;
   const long long row_begin = (long long)(bid / (is_q ? a.Hq : a.Hk)) * (256 * tiles_per_wave);
@@ -460,6 +406,33 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the next tile's writes come after these reads
       __builtin_amdgcn_wave_barrier();
     }
+  }
+}
+
+template <int DH, int D, bool BWD>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void prologue_fused_kernel(
+    FusedArgs a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
+    const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB, const float *__restrict__ temp,
+    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  prologue_fused_body<DH, D, BWD>(a, lat, vsrc, wc, ropeA, ropeB, temp, q, k, v, rnorm, blockIdx.x, smem);
+}
+
+// The adjoint and, beside it, the partial sums of the filter gradients (cca_dwc.h; two units of 256 threads to a workgroup at d_h = 64):
+// both follow from d3 alone, and on short sequences each leaves most CUs idle.  Workgroups [0, n_adjoint) do the former.  Backward
+// pass, the prologue's adjoint in seven launches -> four (us; set-up beside Delta, group sums in the pointwise pass, these two
+// together): 2 x 512 tokens, 8 query and 2 KV heads of 128: 121.9 -> 109.9; 1 x 512, 8 heads of 64: 62.5 -> 54.3; 2 x 4096: 621 -> 596.
+template <int DH, int D>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void prologue_adjoint_pair_kernel(
+    FusedArgs a, const bf16_t *__restrict__ d3, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc, bf16_t *__restrict__ dq,
+    bf16_t *__restrict__ dk, bf16_t *__restrict__ dv, DwcArgs w, int n_adjoint) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x < n_adjoint) {
+    prologue_fused_body<DH, D, true>(a, d3, vsrc, wc, nullptr, nullptr, nullptr, dq, dk, dv, nullptr, blockIdx.x, smem);
+  } else {
+    constexpr int PER = NT / dwc_threads(DH);
+    const int sub = PER == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / dwc_threads(DH));
+    dwc_body<DH, D, (PER > 1)>(w, ((int)blockIdx.x - n_adjoint) * PER + sub, 0, threadIdx.x % dwc_threads(DH), smem + sub * dwc_lds(DH, D));
   }
 }
 
@@ -968,6 +941,18 @@ hipError_t launch_main(const FusedArgs &a, const void *lat, const void *vsrc, co
   return hipGetLastError();
 }
 
+template <int DH, int D>
+hipError_t launch_adjoint_pair(const FusedArgs &a, const void *d3, const void *vsrc, const void *wc, void *dq, void *dk, void *dv,
+                               const DwcArgs &w, int grid, hipStream_t s) {
+  constexpr size_t adjoint = (size_t)DH * D * (DH / 8) * 16 + (size_t)(NT / 64) * 32 * DH * 2, per = NT / dwc_threads(DH);
+  constexpr size_t smem = adjoint > per * dwc_lds(DH, D) ? adjoint : per * dwc_lds(DH, D);
+  static_assert(smem <= 160 * 1024, "LDS");
+  if (hipError_t e = raise_lds_limit<prologue_adjoint_pair_kernel<DH, D>>(smem); e != hipSuccess) return e;
+  prologue_adjoint_pair_kernel<DH, D><<<grid + (w.units + (int)per - 1) / (int)per, NT, smem, s>>>(
+      a, (const bf16_t *)d3, (const bf16_t *)vsrc, (const u32x4 *)wc, (bf16_t *)dq, (bf16_t *)dk, (bf16_t *)dv, w, grid);
+  return hipGetLastError();
+}
+
 // Tokens per workgroup: each workgroup first loads its head's filter (about one tile's worth of time), and one
 // workgroup fits per CU, so minimise rounds-on-256-CUs x (1 + tiles per wavefront).  Returns the grid size.
 int plan_grid(const Dims &d, FusedArgs &a) {
@@ -1013,15 +998,17 @@ FusedScratch carve(const Dims &d, void *scratch, int D) {
                       reinterpret_cast<float2 *>(base + wc_bytes + ra_bytes), wc_bytes + ra_bytes + rb_bytes};
 }
 
-hipError_t run_setup(const Dims &d, const FusedArgs &a, const cca_weights &w, const FusedScratch &fs, int D,
-                     bool transposed, hipStream_t s, const TransposePair *weights = nullptr) {
+PrologueSetup make_setup(const Dims &d, const cca_weights &w, const FusedScratch &fs, int D, bool transposed) {
   const int NH = d.Hq + d.Hk, n_thi = (d.T + 127) / 128, DH = d.dh;
-  const int n_fold = (NH * DH * DH + 255) / 256;
-  const int n_rope = (n_thi * (DH / 2) + (DH / 2) * 128 + 255) / 256;
+  const int n_fold = (NH * DH * DH + 255) / 256, n_rope = (n_thi * (DH / 2) + (DH / 2) * 128 + 255) / 256;
+  return PrologueSetup{(d.flags & CCA_CONV_SEQ) ? (const bf16_t *)w.w_conv_seq : nullptr, (const bf16_t *)w.w_conv_ch, fs.wc, fs.ropeA,
+                       fs.ropeB, d.rope_base, NH, DH, D, (d.flags & CCA_CONV_SEQ) ? d.k_seq : 1, d.k_ch, n_thi, transposed ? 1 : 0,
+                       n_fold, n_fold + n_rope};
+}
+
+hipError_t run_setup(const PrologueSetup &setup, hipStream_t s, const TransposePair *weights = nullptr) {
   const TransposePair pair = weights ? *weights : TransposePair{};
-  prologue_setup_kernel<<<n_fold + n_rope + pair.n1 + pair.n2, 256, 0, s>>>(
-      a, D, (const bf16_t *)w.w_conv_seq, (const bf16_t *)w.w_conv_ch, fs.wc, fs.ropeA, fs.ropeB, n_fold, n_thi, transposed ? 1 : 0,
-      DH, n_fold + n_rope, pair);
+  prologue_setup_kernel<<<setup.n_blocks + pair.n1 + pair.n2, 256, 0, s>>>(setup, pair);
   return hipGetLastError();
 }
 
@@ -1083,7 +1070,7 @@ static FusedArgs forward_args(const Dims &d) {
 
 hipError_t prologue_fused_prepare(const Dims &d, const cca_weights &w, void *scratch, hipStream_t s, const TransposePair *weights) {
   const int D = taps(d);
-  return run_setup(d, forward_args(d), w, carve(d, scratch, D), D, false, s, weights);
+  return run_setup(make_setup(d, w, carve(d, scratch, D), D, false), s, weights);
 }
 
 template <int D, bool BWD>
@@ -1140,20 +1127,16 @@ hipError_t prologue_fused_bf16(const Dims &d, const cca_weights &w, const void *
   return prologue_fused_run(d, w, lat, q, k, v, rnorm, scratch, s);
 }
 
-// ---- adjoint: d3 (B*T, e_q+e_kv), d_v -> d_lat.  `scratch` as for the forward; the RoPE tables it leaves
-// behind are the ones the pointwise backward kernel reads, so this runs its set-up first (see fused_bwd_setup).
-hipError_t prologue_fused_bwd_setup(const Dims &d, const cca_weights &w, void *scratch, const float2 **ropeA,
-                                    const float2 **ropeB, hipStream_t s) {
+// ---- adjoint: d3 (B*T, e_q+e_kv), d_v -> d_lat.  `scratch` as for the forward; the RoPE tables its set-up leaves there are the ones
+// the pointwise backward kernel reads.
+PrologueSetup prologue_fused_bwd_setup(const Dims &d, const cca_weights &w, void *scratch) {
   const int D = taps(d);
-  FusedArgs a{d.T, d.Hq, d.Hk, d.R, d.e_q, d.e_kv, d.n_lat, d.v_half, d.k_seq, d.k_ch, d.rows(), d.flags, 0, 1,
-              d.rope_base, 0.f, 0, 0, 0, 0, 0, 0.f, 0.f};
-  const FusedScratch fs = carve(d, scratch, D);
-  *ropeA = fs.ropeA;
-  *ropeB = fs.ropeB;
-  return run_setup(d, a, w, fs, D, true, s);
+  return make_setup(d, w, carve(d, scratch, D), D, true);
 }
+hipError_t prologue_set_up(const PrologueSetup &setup, hipStream_t s) { return run_setup(setup, s); }
 
-hipError_t prologue_fused_bwd_dlat(const Dims &d, const void *d3, const void *d_v, void *d_lat, void *scratch,
+// dwc (may be NULL; d_h <= 128): the filter gradients' partial sums, formed in the same launch
+hipError_t prologue_fused_bwd_dlat(const Dims &d, const void *d3, const void *d_v, void *d_lat, void *scratch, const DwcArgs *dwc,
                                    hipStream_t s) {
   const int D = taps(d);
   const int ld = d.e_q + d.e_kv;
@@ -1171,6 +1154,11 @@ hipError_t prologue_fused_bwd_dlat(const Dims &d, const void *d3, const void *d_
     }
   }
   const int grid = plan_grid(d, a);
+  if (dwc) {
+#define PAIR(D_) (d.dh == 64 ? launch_adjoint_pair<64, D_> : launch_adjoint_pair<128, D_>)(a, d3, d_v, fs.wc, dl, dl + d.e_q, dl + ld, *dwc, grid, s)
+    return D == 1 ? PAIR(1) : D == 2 ? PAIR(2) : PAIR(3);
+#undef PAIR
+  }
   switch (D) {
     case 1: return LAUNCH_DH(1, true)(a, d3, d_v, fs.wc, fs.ropeA, fs.ropeB, nullptr, dl, dl + d.e_q, dl + ld, nullptr, grid, s);
     case 2: return LAUNCH_DH(2, true)(a, d3, d_v, fs.wc, fs.ropeA, fs.ropeB, nullptr, dl, dl + d.e_q, dl + ld, nullptr, grid, s);

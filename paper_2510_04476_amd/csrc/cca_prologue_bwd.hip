@@ -19,7 +19,7 @@
 //      in (w0, w1), so d w1[h,o,i,j] = sum_jj dWc[h,o,j+jj,i] w0[c,jj] and
 //      d w0[c,jj] = sum_o sum_j dWc[h,o,j+jj,i] w1[h,o,i,j].
 // No atomics anywhere: a repeated call gives the same bits.
-#include "cca_internal.h"
+#include "cca_dwc.h"
 
 namespace cca {
 
@@ -35,9 +35,9 @@ typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 // from cca_prologue.hip
 bool prologue_fused_supported(const Dims &d);
 size_t prologue_fused_scratch_bytes(const Dims &d);
-hipError_t prologue_fused_bwd_setup(const Dims &d, const cca_weights &w, void *scratch, const float2 **ropeA,
-                                    const float2 **ropeB, hipStream_t s);
-hipError_t prologue_fused_bwd_dlat(const Dims &d, const void *d3, const void *d_v, void *d_lat, void *scratch,
+PrologueSetup prologue_fused_bwd_setup(const Dims &d, const cca_weights &w, void *scratch);
+hipError_t prologue_set_up(const PrologueSetup &setup, hipStream_t s);
+hipError_t prologue_fused_bwd_dlat(const Dims &d, const void *d3, const void *d_v, void *d_lat, void *scratch, const DwcArgs *dwc,
                                    hipStream_t s);
 
 namespace {
@@ -60,9 +60,12 @@ struct PointArgs {
 // ---------------------------------------------------------------------------
 // 1. pointwise: d_h / 8 lanes per (token, head); lane j holds channels 4j..4j+3 and d_h/2 + 4j .. + 3, so the
 //    rotate-half partner sits in the same lane and the row dot product is a butterfly over those lanes.
+//    PARTS: the attention left dK and dV as fp32 per query head (KvParts); a key item adds its group's dK, in head order, and
+//    rounds it once, as group_sum_kernel does, and Hk more items per token add and store dV.  At length the 32-bit
+//    halves of dK and dV are read here instead of by a launch of their own (4 us and a bf16 pass less).
 // ---------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256) void pro_bwd_point_kernel(PointArgs a, const bf16_t *__restrict__ q,
+template <int DH, bool PARTS>
+__global__ __launch_bounds__(256) void pro_bwd_point_kernel(PointArgs a, KvParts kv, const bf16_t *__restrict__ q,
                                                            const bf16_t *__restrict__ k,
                                                            const float *__restrict__ rnorm,
                                                            const float *__restrict__ temp,
@@ -70,21 +73,50 @@ __global__ __launch_bounds__(256) void pro_bwd_point_kernel(PointArgs a, const b
                                                            const float2 *__restrict__ ropeA,
                                                            const float2 *__restrict__ ropeB, bf16_t *__restrict__ d3,
                                                            float *__restrict__ rowdot) {
-  const int NH = a.Hq + a.Hk;
+  const int NH = a.Hq + a.Hk, NI = PARTS ? NH + a.Hk : NH;
   constexpr int LPI = DH / 8, HALF = DH / 2;  // lanes per item
-  const long long item = (long long)blockIdx.x * (256 / LPI) + threadIdx.x / LPI;  // row * NH + head
+  const long long item = (long long)blockIdx.x * (256 / LPI) + threadIdx.x / LPI;  // row * NI + head
   const int j = threadIdx.x % LPI;
-  const bool live = item < a.rows * NH;
+  const bool live = item < a.rows * NI;
   const long long it = live ? item : 0;
-  const long long row = it / NH;
-  const int head = (int)(it % NH);
+  const long long row = it / NI;
+  const int head = (int)(it % NI);
   const int tpos = (int)(row % a.T);
   const bool is_q = head < a.Hq;
-  const int g = head - a.Hq;
+  const int g = min(head, NH - 1) - a.Hq;  // (an item of dV leaves before its key row is used)
   const bf16_t *y5 = is_q ? q + (row * a.Hq + head) * DH : k + (row * a.Hk + g) * DH;
   const bf16_t *dy5 = is_q ? dq + (row * a.Hq + head) * DH : dk + (row * a.Hk + g) * DH;
   const u32x2 ya = *reinterpret_cast<const u32x2 *>(y5 + 4 * j), yb = *reinterpret_cast<const u32x2 *>(y5 + HALF + 4 * j);
-  const u32x2 da = *reinterpret_cast<const u32x2 *>(dy5 + 4 * j), db = *reinterpret_cast<const u32x2 *>(dy5 + HALF + 4 * j);
+  u32x2 da, db;
+  if (PARTS && !is_q) {
+    const int R = a.Hq / a.Hk, gg = head < NH ? g : head - NH;
+    const float *p = (head < NH ? kv.k : kv.v) + (row * a.Hq + gg * R) * DH + 4 * j;
+    f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+    int r = 0;
+    for (; r + 2 <= R; r += 2) {  // two heads' loads in flight
+      const f32x4 l0 = *reinterpret_cast<const f32x4 *>(p + r * DH), h0 = *reinterpret_cast<const f32x4 *>(p + r * DH + HALF);
+      const f32x4 l1 = *reinterpret_cast<const f32x4 *>(p + r * DH + DH), h1 = *reinterpret_cast<const f32x4 *>(p + r * DH + DH + HALF);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lo[e] = lo[e] + l0[e] + l1[e], hi[e] = hi[e] + h0[e] + h1[e];
+    }
+    if (r < R) {
+      const f32x4 l0 = *reinterpret_cast<const f32x4 *>(p + r * DH), h0 = *reinterpret_cast<const f32x4 *>(p + r * DH + HALF);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lo[e] += l0[e], hi[e] += h0[e];
+    }
+    da.x = pack2(lo[0], lo[1]), da.y = pack2(lo[2], lo[3]);
+    db.x = pack2(hi[0], hi[1]), db.y = pack2(hi[2], hi[3]);
+    if (head >= NH) {
+      if (live) {
+        bf16_t *const to = kv.d_v + (row * a.Hk + gg) * DH;
+        *reinterpret_cast<u32x2 *>(to + 4 * j) = da;
+        *reinterpret_cast<u32x2 *>(to + HALF + 4 * j) = db;
+      }
+      return;
+    }
+  } else {
+    da = *reinterpret_cast<const u32x2 *>(dy5 + 4 * j), db = *reinterpret_cast<const u32x2 *>(dy5 + HALF + 4 * j);
+  }
   float y[8] = {bf_lo(ya.x), bf_hi(ya.x), bf_lo(ya.y), bf_hi(ya.y), bf_lo(yb.x), bf_hi(yb.x), bf_lo(yb.y), bf_hi(yb.y)};
   float dy[8] = {bf_lo(da.x), bf_hi(da.x), bf_lo(da.y), bf_hi(da.y), bf_lo(db.x), bf_hi(db.x), bf_lo(db.y), bf_hi(db.y)};
   float dot = 0.f;
@@ -164,150 +196,13 @@ __global__ __launch_bounds__(256) void column_sum_f32_kernel(ColumnSum c) {
 }
 
 // ---------------------------------------------------------------------------
-// 3. folded-filter gradient, partial sums per chunk of tokens.
-//    Workgroup = (head, chunk of `chunk` tokens of one sequence[, slice of the output channels at d_h = 256]);
-//    wavefront w owns OX output-channel tiles starting at OX*(w&1) and IX input-channel tiles starting at
-//    IX*(w>>1), for all D taps (OX = d_h / 64 and IX = 1 up to d_h = 128).
+// 3. folded-filter gradient, partial sums per chunk of tokens: dwc_body (cca_dwc.h), in a launch of its own at d_h = 256, else beside
+//    the adjoint of the prologue (prologue_fused_bwd_dlat).
 // ---------------------------------------------------------------------------
-// MFMA operand fragment of the TRANSPOSE of a row-major LDS tile: lane (c = lane & 31, half) receives
-// tile[r0 + 4*half + {0..3}][c0 + c] and tile[r0 + 8 + 4*half + {0..3}][c0 + c].  `base` already holds the
-// per-lane part  (4*half + ((lane & 15) >> 2)) * ROW + (((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2.
-template <int ROW>
-__device__ __forceinline__ bf16x8 tr_frag(const unsigned char *base, int r0, int c0) {
-  const unsigned char *p = base + r0 * ROW + c0 * 2;
-  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)p);
-  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(p + 8 * ROW));
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-constexpr int DW_BT = 64;  // tokens per LDS tile
-
-// Output slices per head and threads per workgroup: at d_h <= 128 one workgroup of d_h * 4 threads owns all of a head's
-// d_h x D x d_h sums; at d_h = 256 they would not fit its registers, so 512 threads own a slice of 128 (D <= 2) or 64
-// (D = 3) output channels (blockIdx.y) and each such workgroup re-reads the token rows of all 256 input channels.
-constexpr int dwc_slices(int DH, int D) { return DH <= 128 ? 1 : (D <= 2 ? 2 : 4); }
-constexpr int dwc_threads(int DH) { return DH <= 128 ? DH * 4 : 512; }
-
-template <int DH, int D>
-__global__ __launch_bounds__(dwc_threads(DH)) void pro_bwd_dwc_kernel(const bf16_t *__restrict__ d3,
-                                                                      const bf16_t *__restrict__ lat,
-                                                                      float *__restrict__ part, int T, int Hq, int Hk,
-                                                                      int e_q, int e_kv, int n_lat, int chunk,
-                                                                      int chunks_per_seq) {
-  constexpr int OS = dwc_slices(DH, D), DHO = DH / OS, DW_NT = dwc_threads(DH), NW = DW_NT / 64;
-  // LDS rows of the gradient tile (this slice's output channels) and of the token tile (all input channels); the
-  // 64-byte pad keeps the transposing reads conflict-free
-  constexpr int ROWY = DHO * 2 + 64, ROWU = DH * 2 + 64, CPWY = DHO / 8, CPWU = DH / 8;
-  constexpr int OX = DHO / 64, IX = (DH / 32) / (NW / 2);  // output / input channel tiles per wavefront
-  static_assert(OX >= 1 && IX >= 1 && OX * 2 * 32 == DHO && IX * (NW / 2) * 32 == DH, "wavefront tiling");
-  constexpr int UROWS = DW_BT + D - 1;
-  constexpr int DY_TILE = DW_BT * ROWY, U_TILE = UROWS * ROWU;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * (DY_TILE + U_TILE)];
-  unsigned char *const sDy = smem, *const sU = smem + 2 * DY_TILE;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, half = lane >> 5;
-  const int NH = Hq + Hk;
-  const int head = blockIdx.x % NH, cid = blockIdx.x / NH;  // cid = b * chunks_per_seq + chunk index
-  const int o_base = (int)blockIdx.y * DHO;                 // first output channel of this slice
-  const int b = cid / chunks_per_seq, t_begin = (cid % chunks_per_seq) * chunk;
-  const int t_end = min(T, t_begin + chunk);
-  const int ch0 = head < Hq ? head * DH : e_q + (head - Hq) * DH;
-  const int ld3 = e_q + e_kv;
-  const bf16_t *const d3b = d3 + (long long)b * T * ld3 + ch0 + o_base;
-  const bf16_t *const ub = lat + (long long)b * T * n_lat + ch0;
-
-  constexpr int DY_CHUNKS = DW_BT * CPWY, U_CHUNKS = UROWS * CPWU;  // 16-byte chunks per tile
-  constexpr int DY_PER = DY_CHUNKS / DW_NT, U_PER = (U_CHUNKS + DW_NT - 1) / DW_NT;
-  static_assert(DY_CHUNKS % DW_NT == 0, "gradient tile must divide over the threads");
-  u32x4 rdy[DY_PER], ru[U_PER];
-  auto load_tile = [&](int t0) {
-#pragma unroll
-    for (int i = 0; i < DY_PER; ++i) {
-      const int id = tid + i * DW_NT, r = id / CPWY, c = id % CPWY;
-      const int t = t0 + r;
-      u32x4 val = {0, 0, 0, 0};
-      if (t < t_end) val = *reinterpret_cast<const u32x4 *>(d3b + (long long)t * ld3 + c * 8);
-      rdy[i] = val;
-    }
-#pragma unroll
-    for (int i = 0; i < U_PER; ++i) {
-      const int id = tid + i * DW_NT, r = id / CPWU, c = id % CPWU;
-      const int t = t0 - (D - 1) + r;  // row r of the tile holds token t0 - (D-1) + r
-      u32x4 val = {0, 0, 0, 0};
-      if (id < U_CHUNKS && t >= 0 && t < t_end) val = *reinterpret_cast<const u32x4 *>(ub + (long long)t * n_lat + c * 8);
-      ru[i] = val;
-    }
-  };
-  auto store_tile = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < DY_PER; ++i) {
-      const int id = tid + i * DW_NT, r = id / CPWY, c = id % CPWY;
-      *reinterpret_cast<u32x4 *>(sDy + buf * DY_TILE + r * ROWY + c * 16) = rdy[i];
-    }
-#pragma unroll
-    for (int i = 0; i < U_PER; ++i) {
-      const int id = tid + i * DW_NT, r = id / CPWU, c = id % CPWU;
-      if (id < U_CHUNKS) *reinterpret_cast<u32x4 *>(sU + buf * U_TILE + r * ROWU + c * 16) = ru[i];
-    }
-  };
-
-  const uint32_t tr_row = (uint32_t)(4 * half + ((lane & 15) >> 2)), tr_col = (((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2;
-  const uint32_t tr_off_y = tr_row * ROWY + tr_col, tr_off_u = tr_row * ROWU + tr_col;
-  const int o_tile0 = OX * (wave & 1), i_tile0 = IX * (wave >> 1);
-
-  f32x16 acc[OX][IX][D];
-#pragma unroll
-  for (int x = 0; x < OX; ++x)
-#pragma unroll
-    for (int y = 0; y < IX; ++y)
-#pragma unroll
-      for (int d = 0; d < D; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[x][y][d][r] = 0.f;
-
-  const int ntiles = (t_end - t_begin + DW_BT - 1) / DW_BT;
-  load_tile(t_begin);
-  store_tile(0);
-  if (ntiles > 1) load_tile(t_begin + DW_BT);
-  __syncthreads();
-  for (int it = 0; it < ntiles; ++it) {
-    const int buf = it & 1;
-    if (it + 1 < ntiles) store_tile(buf ^ 1);
-    if (it + 2 < ntiles) load_tile(t_begin + (it + 2) * DW_BT);
-    const unsigned char *dyp = sDy + buf * DY_TILE + tr_off_y, *up = sU + buf * U_TILE + tr_off_u;
-#pragma unroll
-    for (int kk = 0; kk < DW_BT / 16; ++kk) {
-      bf16x8 fo[OX], fu[IX][D];
-#pragma unroll
-      for (int x = 0; x < OX; ++x) fo[x] = tr_frag<ROWY>(dyp, kk * 16, (o_tile0 + x) * 32);
-#pragma unroll
-      for (int y = 0; y < IX; ++y)
-#pragma unroll
-        for (int d = 0; d < D; ++d) fu[y][d] = tr_frag<ROWU>(up, kk * 16 + d, (i_tile0 + y) * 32);  // token t - (D-1-d)
-#pragma unroll
-      for (int x = 0; x < OX; ++x)
-#pragma unroll
-        for (int y = 0; y < IX; ++y)
-#pragma unroll
-          for (int d = 0; d < D; ++d)
-            acc[x][y][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[x], fu[y][d], acc[x][y][d], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  // acc[x][y][d][r]: o = o_base + (o_tile0 + x)*32 + 8*(r/4) + 4*half + r%4,  i = (i_tile0 + y)*32 + l32
-  float *out = part + (long long)blockIdx.x * DH * D * DH;  // [o][d][i] of (cid, head); blockIdx.x = cid*NH + head
-#pragma unroll
-  for (int x = 0; x < OX; ++x)
-#pragma unroll
-    for (int y = 0; y < IX; ++y)
-#pragma unroll
-      for (int d = 0; d < D; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int o = o_base + (o_tile0 + x) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-          out[(o * D + d) * DH + (i_tile0 + y) * 32 + l32] = acc[x][y][d][r];
-        }
+template <int D>
+__global__ __launch_bounds__(dwc_threads(256)) void pro_bwd_dwc_kernel(DwcArgs w) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[dwc_lds(256, D)];
+  dwc_body<256, D>(w, blockIdx.x, blockIdx.y, threadIdx.x, smem);
 }
 
 // The last `csum.ncol` workgroups add the columns of d temp instead (a launch of its own cost 5 us).
@@ -433,7 +328,7 @@ size_t prologue_bwd_fused_scratch_bytes(const Dims &d) {
 template <int DH>
 static hipError_t prologue_bwd_run(const Dims &d, const cca_weights &w, const void *lat, const void *q, const void *k,
                                    const float *rnorm, const void *d_q, const void *d_k, const void *d_v, void *d_lat,
-                                   const cca_grads *gr, void *scratch, hipStream_t s) {
+                                   const cca_grads *gr, void *scratch, hipStream_t s, bool set_up, const KvParts *parts) {
   const BwdScratch L = bwd_layout(d);
   char *base = static_cast<char *>(scratch);
   bf16_t *d3 = reinterpret_cast<bf16_t *>(base + L.d3);
@@ -442,40 +337,40 @@ static hipError_t prologue_bwd_run(const Dims &d, const cca_weights &w, const vo
   float *dwc = reinterpret_cast<float *>(base + L.dwc);
   const int D = taps(d), NH = d.Hq + d.Hk;
 
-  const float2 *ropeA, *ropeB;
-  hipError_t e = prologue_fused_bwd_setup(d, w, base + L.fused, &ropeA, &ropeB, s);
+  const PrologueSetup setup = prologue_fused_bwd_setup(d, w, base + L.fused);
+  hipError_t e = set_up ? hipSuccess : prologue_set_up(setup, s);
   if (e != hipSuccess) return e;
 
   const bool want_temp = (d.flags & CCA_KEY_TEMP) && gr && gr->temp;
   PointArgs pa{d.T, d.Hq, d.Hk, d.e_q, d.e_kv, d.rows(), d.flags};
-  const long long items = d.rows() * NH;
+  const long long items = d.rows() * (parts ? NH + d.Hk : NH);
   constexpr int IPB = 256 / (DH / 8);  // items per workgroup of the pointwise kernel
-  pro_bwd_point_kernel<DH><<<(unsigned)((items + IPB - 1) / IPB), 256, 0, s>>>(pa, (const bf16_t *)q, (const bf16_t *)k, rnorm,
-                                                                    w.temp, (const bf16_t *)d_q, (const bf16_t *)d_k,
-                                                                    ropeA, ropeB, d3, want_temp ? rowdot : nullptr);
+  (parts ? pro_bwd_point_kernel<DH, true> : pro_bwd_point_kernel<DH, false>)<<<(unsigned)((items + IPB - 1) / IPB), 256, 0, s>>>(
+      pa, parts ? *parts : KvParts{}, (const bf16_t *)q, (const bf16_t *)k, rnorm, w.temp, (const bf16_t *)d_q, (const bf16_t *)d_k,
+      setup.ropeA, setup.ropeB, d3, want_temp ? rowdot : nullptr);
   ColumnSum csum{rowdot, want_temp ? gr->temp : nullptr, d.rows(), want_temp ? d.Hk : 0};
   e = hipGetLastError();
   if (e != hipSuccess) return e;
 
-  e = prologue_fused_bwd_dlat(d, d3, d_v, d_lat, base + L.fused, s);
-  if (e != hipSuccess) return e;
-
   const bool want_w1 = gr && gr->w_conv_ch;  // CONV_CH is on whenever this path runs
   const bool want_w0 = (d.flags & CCA_CONV_SEQ) && gr && gr->w_conv_seq;
-  if (!want_w1 && !want_w0) {
+  const int chunk = dwc_chunk(d), cps = (d.T + chunk - 1) / chunk, n_chunks = d.B * cps;
+  const DwcArgs dwc_args{d3, (const bf16_t *)lat, part, d.T, d.Hq, d.Hk, d.e_q, d.e_kv, d.n_lat, chunk, cps, n_chunks * NH};
+  const bool filters = want_w1 || want_w0;
+  e = prologue_fused_bwd_dlat(d, d3, d_v, d_lat, base + L.fused, DH <= 128 && filters ? &dwc_args : nullptr, s);
+  if (e != hipSuccess) return e;
+  if (!filters) {
     if (want_temp) column_sum_f32_kernel<<<d.Hk, 256, 0, s>>>(csum);
     return hipGetLastError();
   }
-  const int chunk = dwc_chunk(d), cps = (d.T + chunk - 1) / chunk, n_chunks = d.B * cps;
-#define DWC(DD)                                                                                                     \
-  pro_bwd_dwc_kernel<DH, DD><<<dim3(n_chunks * NH, dwc_slices(DH, DD)), dwc_threads(DH), 0, s>>>(                    \
-      d3, (const bf16_t *)lat, part, d.T, d.Hq, d.Hk, d.e_q, d.e_kv, d.n_lat, chunk, cps)
-  switch (D) {
-    case 1: DWC(1); break;
-    case 2: DWC(2); break;
-    default: DWC(3); break;
+  if constexpr (DH == 256) {
+    const dim3 grid(n_chunks * NH, dwc_slices(DH, D));
+    switch (D) {
+      case 1: pro_bwd_dwc_kernel<1><<<grid, dwc_threads(DH), 0, s>>>(dwc_args); break;
+      case 2: pro_bwd_dwc_kernel<2><<<grid, dwc_threads(DH), 0, s>>>(dwc_args); break;
+      default: pro_bwd_dwc_kernel<3><<<grid, dwc_threads(DH), 0, s>>>(dwc_args); break;
+    }
   }
-#undef DWC
   const int ks = (d.flags & CCA_CONV_SEQ) ? d.k_seq : 1;
   pro_bwd_unfold_w1_kernel<<<(NH * DH * DH + 255) / 256 + csum.ncol, 256, 0, s>>>(part, n_chunks, NH, D, ks, d.k_ch,
                                                                      (d.flags & CCA_CONV_SEQ) ? 1 : 0,
@@ -489,10 +384,14 @@ static hipError_t prologue_bwd_run(const Dims &d, const cca_weights &w, const vo
 
 hipError_t prologue_bwd_fused_bf16(const Dims &d, const cca_weights &w, const void *lat, const void *q, const void *k,
                                    const float *rnorm, const void *d_q, const void *d_k, const void *d_v, void *d_lat,
-                                   const cca_grads *gr, void *scratch, hipStream_t s) {
-  return d.dh == 64    ? prologue_bwd_run<64>(d, w, lat, q, k, rnorm, d_q, d_k, d_v, d_lat, gr, scratch, s)
-         : d.dh == 128 ? prologue_bwd_run<128>(d, w, lat, q, k, rnorm, d_q, d_k, d_v, d_lat, gr, scratch, s)
-                       : prologue_bwd_run<256>(d, w, lat, q, k, rnorm, d_q, d_k, d_v, d_lat, gr, scratch, s);
+                                   const cca_grads *gr, void *scratch, hipStream_t s, bool set_up, const KvParts *parts) {
+  return d.dh == 64    ? prologue_bwd_run<64>(d, w, lat, q, k, rnorm, d_q, d_k, d_v, d_lat, gr, scratch, s, set_up, parts)
+         : d.dh == 128 ? prologue_bwd_run<128>(d, w, lat, q, k, rnorm, d_q, d_k, d_v, d_lat, gr, scratch, s, set_up, parts)
+                       : prologue_bwd_run<256>(d, w, lat, q, k, rnorm, d_q, d_k, d_v, d_lat, gr, scratch, s, set_up, parts);
+}
+
+PrologueSetup prologue_bwd_fused_setup(const Dims &d, const cca_weights &w, void *scratch) {
+  return prologue_fused_bwd_setup(d, w, static_cast<char *>(scratch) + bwd_layout(d).fused);
 }
 
 }  // namespace cca
