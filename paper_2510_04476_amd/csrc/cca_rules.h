@@ -177,6 +177,17 @@ inline bool split_pays(long long BH, int T, bool causal, bool pairs, const Split
 inline bool fwd_splits_keys(long long BH, int T, bool causal) {
   return split_pays(BH, T, causal, true, SplitCost{3.0, 1.04, 1.0, 0.2});
 }
+// Scores without a bound by the QK norm: a pass over the rows for their lengths first, so that the form that needs no running
+// maximum can run?  The pass costs 3.5 ... 4 us; the gain follows the pairs of a query and a key, except at heads wider than 128,
+// where the other form is a third slower for each key and the longest chain of keys decides.  Whole prefill (us, without ->
+// with the pass; T, B * H_q, c = causal): d_h = 256: 64, 8 c: 30.7 -> 32.8; 300, 8 c: 58.9 -> 53.3; 4096, 8 c: 383 -> 290; 8192, 8:
+// 1260 -> 848; d_h = 128: 1531, 24: 85.2 -> 86.1; 1531, 48 c: 219.4 -> 217.8; 2048, 16: 124.1 -> 124.1; 4096, 8 c: 103.7 -> 96.8;
+// 4096, 16 c: 244 -> 235; 8192, 8 c: 216 -> 195; d_h = 64: 2048, 32 c: 92.1 -> 96.2; 1531, 48: 118 -> 113; 4096, 16 c: 97.9 ->
+// 97.3; 1531, 96 c: 182 -> 171; 8192, 32 c: 537 -> 453.
+inline bool fwd_measures_bound(long long BH, int T, int dh, bool causal) {
+  if (dh > 128) return T >= 128;
+  return (double)BH * T * T * (causal ? 0.5 : 1.0) >= (dh > 64 ? 60e6 : 100e6);
+}
 // Backward, likewise (B * H_q = 4 ... 400, T = 64 ... 16384, causal and not, one and four query heads per KV head): neither kernel
 // is split where that measured more than 2 % slower, and the choice costs 0.1 % on average.  Attention backward, us, neither -> dQ
 // -> dK / dV -> both split, causal, d_h = 128: T = 512, B * H_q = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115;

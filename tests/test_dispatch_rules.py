@@ -111,6 +111,15 @@ DKDV_MEASURED = [(64, 1531, True, 104.5, 115.3), (4, 64, True, 13.0, 13.9), (8, 
                  (64, 1999, True, 174.0, 185.0)]
 
 
+# (B * H_q, T, d_h, causal): the lengths of the rows measured first or not
+@pytest.mark.parametrize("BH,T,dh,causal,pays", [(8, 64, 256, True, False), (8, 300, 256, True, True), (8, 8192, 256, False, True),
+                                                 (24, 1531, 128, False, False), (8, 4096, 128, True, True), (16, 4096, 128, True, True),
+                                                 (16, 1024, 128, True, False), (32, 2048, 64, True, False), (48, 1531, 64, False, True),
+                                                 (96, 1531, 64, True, True), (16, 512, 64, False, False)])
+def test_lengths_of_rows_are_measured_where_that_pays(BH, T, dh, causal, pays):
+    assert rules.fwd_measures_bound(BH, T, dh, causal) == pays
+
+
 @pytest.mark.parametrize("rule,cases", [(rules.fwd_splits_keys, FWD_MEASURED), (rules.dq_splits_keys, DQ_MEASURED),
                                         (rules.dkdv_splits_rows, DKDV_MEASURED)])
 def test_attention_split_is_the_faster_form(rule, cases):

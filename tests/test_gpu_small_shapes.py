@@ -166,6 +166,53 @@ def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
             assert float((lse[b, h].double() - ref_lse).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
 
 
+# B, T, H_q, H_k, d_h, causal: the shortest sequence at wide heads, last chunks of one token, the two narrower heads with one and two
+# key groups; the longest row of a head last in its chunk, and in the last one
+BOUND_CASES = [(2, 128, 2, 1, 256, True), (1, 257, 3, 3, 256, False), (1, 2049, 2, 1, 256, True), (1, 4481, 8, 2, 128, True),
+               (1, 2817, 8, 8, 128, False), (1, 3585, 16, 4, 64, True), (26, 1984, 1, 1, 64, False), (30, 1600, 1, 1, 128, False)]
+
+
+@pytest.mark.parametrize("longest", [2.0, 40.0, float("inf"), float("nan")])
+@pytest.mark.parametrize("B,T,Hq,Hk,dh,causal", BOUND_CASES)
+def test_attention_with_measured_bound(B, T, Hq, Hk, dh, causal, longest):
+    """Plain attention whose longest rows let the scores be bounded (2.0) or not.  Where they do not, o and lse are those of the
+    stage alone, which measures nothing, bit for bit.  Where they do, against fp64: P enters the PV product
+    rounded to bf16 (2^-9 of each term), the scaled q too (2^-9 of each logit), and o is rounded once, 2^-8."""
+    say("measured bound", B, T, Hq, Hk, dh, causal, longest)
+    assert rules.fwd_measures_bound(B * Hq, T, dh, causal)
+    cfg = P.CCAConfig(B=B, T=T, d_model=(Hq + 2 * Hk) * dh, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, k_seq=1, k_ch=1,
+                      flags=P.CCA_FLAGS_MHA if causal else P.CCA_FLAGS_MHA & ~P.CCA_CAUSAL)
+    w = P.CCAWeights(w_down=torch.eye(cfg.d_model, dtype=torch.bfloat16, device="cuda"), w_out=rnd(cfg.e_q, cfg.d_model, seed=4, scale=0.02))
+    lat = rnd(B, T, Hq + 2 * Hk, dh, seed=1, dtype=torch.float32)
+    lat[:, :, :Hq + Hk] *= 3.0 / lat[:, :, :Hq + Hk].norm(dim=-1, keepdim=True)  # |q|, |k| = 3
+    lat[:, T - 1, :Hq] *= longest  # the last query of each head, a key at the end of a chunk
+    lat[:, min(T, 64) - 1, Hq:Hq + Hk] *= min(longest, 40.0)
+    x = lat.bfloat16().view(B, T, cfg.d_model)
+    saved = P.CCASaved.allocate(cfg, "cuda")
+    out, bare = P.cca_forward(cfg, w, x, saved=saved), P.cca_forward(cfg, w, x)
+    o, lse = P.cca_attention(cfg, saved.q, saved.k, saved.v, want_lse=True)
+    torch.cuda.synchronize()
+    rows = slice(0, T) if longest == longest and longest < 1e9 else slice(0, T - 1)  # identity times an infinite token: NaN
+    most = float(saved.q[:, rows].float().norm(dim=-1).max() * saved.k[:, rows].float().norm(dim=-1).max()) * dh ** -0.5 * 1.4427
+    if longest != 2.0:
+        assert longest != 40.0 or most > 60.0 * 1.01
+        assert torch.equal(saved.o.view(torch.int16), o.view(torch.int16)) and torch.equal(saved.lse.view(torch.int32), lse.view(torch.int32))
+        return
+    assert most < 48.0 / 1.03
+    assert float((out.double() - bare.double()).norm()) <= 2.0 ** -7 * float(out.double().norm())
+    for b in {0, B - 1}:
+        for h in range(Hq):
+            s = saved.q[b, :, h].double() @ saved.k[b, :, h // (Hq // Hk)].double().t().contiguous() / dh ** 0.5
+            s_max = float(s.abs().max())
+            if causal:
+                s = s.masked_fill(torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+            p, vh = torch.softmax(s, -1), saved.v[b, :, h // (Hq // Hk)].double()
+            ref, noise = p @ vh, 2.0 ** -9 * (1.0 + s_max) * (p.square() @ vh.square()).sqrt()
+            got = saved.o[b, :, h * dh:(h + 1) * dh].double()
+            assert float(((got - ref).abs() / (2.0 ** -8 * ref.abs() + 6.0 * noise + 1e-6)).max()) <= 1.0, (b, h)
+            assert float((saved.lse[b, h].double() - torch.logsumexp(s, -1)).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
+
+
 def check_masked_keys(dh, causal, live, masked):
     """Keys outside `live` (a mask over T) score `masked` times a positive number, through a channel of k at that value that every q
     reads with a positive weight: the rows that see a live key are those of attention over the live keys alone, with the
