@@ -114,25 +114,27 @@ __device__ __forceinline__ void store_tile_bf16(const f32x16 (&acc)[NI][MI], uns
 }
 
 // LDS holds three slabs of A and two of Bt: A streams from HBM, whose latency a slab's 1.1-1.5 us of MFMAs do not cover; Bt is
-// a weight that stays in the caches, and a third stage of it would not fit (256 columns: 3 x 32 + 2 x 32 KB, all of a CU's LDS).
+// a weight that stays in the caches, and a third stage of it would not fit (256 x 256: 3 x 32 + 2 x 32 KB, all of a CU's LDS).
 // A slab's one barrier stands before its last k-step, when the fragments of that step are in registers: from there on the slab's
 // buffers are free for the next loads, and the next slab's first fragments are read under the last step's MFMAs.
 // 16384 x 1536 x 2048, back to back on random operands: 106.7 us with two slabs of both and the barrier at the slab's end,
 // 101.8 this way; 4096 x 6144 x 2048 112.5 and 103.2, 7996 x 1536 x 2048 51.8 and 49.6 (256 x 192 tiles); 16384 x 2048 x 1024 73.4
 // and 72.1 (256 x 256).  On all-zero operands the first takes 89 us: what bounds the larger shapes is the power the matrix cores
-// draw; with every row of A the same (in the caches) it still takes 104.
-template <int BN, int WAVES_M, int WAVES_N>
+// draw; with every row of A the same (in the caches) it still takes 104.  Rows and columns of the tile: what deals the tiles most
+// evenly to 256 CUs (nt_tile).  192 x 256: 6000 x 2048 x 1024 34.5 us on 256 x 256 (192 CUs at work), 30.0; 256 x 128: 4593 x 1536 x
+// 2048 37.1 on two workgroups of 128 x 128 to a CU, 35.7; 4096 x 2048 x 2048 40.4 and 38.6.
+template <int TM, int BN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(const bf16_t *__restrict__ A,
                                                                const bf16_t *__restrict__ Bt,
                                                                bf16_t *__restrict__ C, long long M, int N, int K,
                                                                int tiles_n, int tiles_total, ColumnSplit split) {
   constexpr int NWAVES = WAVES_M * WAVES_N, NTHREADS = NWAVES * 64;
-  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave tile
+  constexpr int WM = TM / WAVES_M, WN = BN / WAVES_N;  // wave tile
   constexpr int MI = WM / 32, NI = WN / 32;            // 32x32 MFMA tiles per wave
   static_assert(MI * 32 == WM && NI * 32 == WN, "wave tile must be a multiple of 32");
   static_assert(BK == 64, "four k-steps of 16");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int A_STAGE = BM * 8, B_STAGE = BN * 8;  // 16-byte chunks of a slab
+  constexpr int A_STAGE = TM * 8, B_STAGE = BN * 8;  // 16-byte chunks of a slab
   u32x4 *const sA = reinterpret_cast<u32x4 *>(smem), *const sB = sA + A_STAGES * A_STAGE;
 
   // XCD-aware tile order: workgroup ids are dealt round-robin over the 8 XCDs,
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
   const int per_xcd = (tiles_total + 7) / 8;
   const int tile = (wg % 8) * per_xcd + wg / 8;
   if (tile >= tiles_total) return;
-  const long long m0 = (long long)(tile / tiles_n) * BM;
+  const long long m0 = (long long)(tile / tiles_n) * TM;
   const int n0 = (tile % tiles_n) * BN;
 
   const int tid = threadIdx.x;
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
   // Direct global -> LDS loads: wave instruction i deposits 64 x 16 bytes at LDS chunks [i*64, i*64+64) of a slab
   // (8 chunks per row), so lane L fetches the chunk that the XOR swizzle puts at that position.
   constexpr int A_LOADS = A_STAGE / 64 / NWAVES, B_LOADS = B_STAGE / 64 / NWAVES;  // instructions of a wavefront per slab
-  static_assert(A_LOADS * 64 * NWAVES == A_STAGE && B_LOADS * 64 * NWAVES == B_STAGE && A_LOADS % 2 == 0,
+  static_assert(A_LOADS * 64 * NWAVES == A_STAGE && B_LOADS * 64 * NWAVES == B_STAGE,
                 "instructions must divide evenly over the wavefronts");
   const bf16_t *a_src[A_LOADS], *b_src[B_LOADS];
   const int l_row = (wave * 64 + lane) >> 3, l_cs = lane & 7;  // row and chunk position of this thread's first chunk
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
     as = as1;
   }
   __syncthreads();
-  store_tile_bf16<BM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N, split);
+  store_tile_bf16<TM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N, split);
 }
 
 __global__ __launch_bounds__(256) void transpose_bf16_kernel(TransposePair p) {
@@ -599,18 +601,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
   }
 }
 
-template <int BN, int WAVES_M, int WAVES_N>
+template <int TM, int BN, int WAVES_M, int WAVES_N>
 hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
                        hipStream_t s) {
-  const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
+  const int tiles_m = (int)((M + TM - 1) / TM), tiles_n = (N + BN - 1) / BN;
   const int total = tiles_m * tiles_n;
   const int per_xcd = (total + 7) / 8;
-  constexpr size_t epi_bytes = (size_t)BM * (BN * 2 + 16);
-  constexpr size_t main_bytes = (size_t)(A_STAGES * BM + B_STAGES * BN) * BK * 2;
+  constexpr size_t epi_bytes = (size_t)TM * (BN * 2 + 16);
+  constexpr size_t main_bytes = (size_t)(A_STAGES * TM + B_STAGES * BN) * BK * 2;
   constexpr size_t smem = main_bytes > epi_bytes ? main_bytes : epi_bytes;
   static_assert(smem <= 160 * 1024, "LDS");
-  if (hipError_t e = raise_lds_limit<gemm_bf16_nt_kernel<BN, WAVES_M, WAVES_N>>(smem); e != hipSuccess) return e;
-  gemm_bf16_nt_kernel<BN, WAVES_M, WAVES_N><<<per_xcd * 8, WAVES_M * WAVES_N * 64, smem, s>>>((const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N,
+  if (hipError_t e = raise_lds_limit<gemm_bf16_nt_kernel<TM, BN, WAVES_M, WAVES_N>>(smem); e != hipSuccess) return e;
+  gemm_bf16_nt_kernel<TM, BN, WAVES_M, WAVES_N><<<per_xcd * 8, WAVES_M * WAVES_N * 64, smem, s>>>((const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N,
                                                              K, tiles_n, total, split);
   return hipGetLastError();
 }
@@ -624,7 +626,7 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
 // and each half of it belongs to one half of the wavefronts, whose sums are added through LDS at the end - half as many
 // steps in the chain.  Measured (M x N x K, us, 256-row tiles -> this): 512 x 1536 x 2048 39.4 -> 10.0 (64 x 64 tiles),
 // 512 x 2048 x 1024 22.2 -> 7.8, 1000 x 1536 x 2048 39.5 -> 14.1 (64 x 128), 2000 x 1536 x 2048 39.9 -> 20.4
-// (128 x 128, 8 wavefronts), 4593 x 1536 x 2048 41.0 -> 34.6 (128 x 128, 4 wavefronts, two workgroups per CU).
+// (128 x 128).
 // Slower everywhere: 32-wide slabs (half the work per barrier), 128 x 192 and 256 x 128 tiles at two workgroups per CU,
 // WAVES_K = 4, a fourth stage at 64 x 64.
 // ---------------------------------------------------------------------------
@@ -856,12 +858,13 @@ bool gemm_mfma_supported(long long M, int N, int K) { return M >= 1 && K % BK ==
 hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s,
                           const ColumnSplit &split) {
   switch (nt_tile(M, N, K)) {
-    case NT_256x256: return launch_gemm<256, 2, 4>(A, Bt, C, M, N, K, split, s);
-    case NT_256x192: return launch_gemm<192, 4, 2>(A, Bt, C, M, N, K, split, s);
+    case NT_256x256: return launch_gemm<256, 256, 2, 4>(A, Bt, C, M, N, K, split, s);
+    case NT_256x192: return launch_gemm<256, 192, 4, 2>(A, Bt, C, M, N, K, split, s);
+    case NT_192x256: return launch_gemm<192, 256, 2, 4>(A, Bt, C, M, N, K, split, s);
+    case NT_256x128: return launch_gemm<256, 128, 4, 2>(A, Bt, C, M, N, K, split, s);
     case NT_64x64: return launch_gemm_deep<64, 64, 2, 2, 2, 3>(A, Bt, C, M, N, K, split, s);
     case NT_64x128: return launch_gemm_deep<64, 128, 1, 4, 2, 3>(A, Bt, C, M, N, K, split, s);
-    case NT_128x128_8W: return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, split, s);
-    case NT_128x128_4W: return launch_gemm_deep<128, 128, 2, 2, 1, 2>(A, Bt, C, M, N, K, split, s);
+    case NT_128x128: return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, split, s);
   }
   return hipErrorInvalidValue;
 }

@@ -8,34 +8,32 @@
 namespace cca {
 
 // ---- projections: C (M,N) = A (M,K) * Bt (N,K)^T, bf16 -------------------------------------------------------------------
-// tile rows x columns, wavefronts of a workgroup
-enum NtTile { NT_256x256, NT_256x192, NT_64x64, NT_64x128, NT_128x128_8W, NT_128x128_4W };
+enum NtTile { NT_256x256, NT_256x192, NT_64x64, NT_64x128, NT_128x128, NT_256x128, NT_192x256 };  // rows x columns
 
 // A tile shape costs (rounds of the grid over the chip) x (64-wide slabs x time per slab + fill and epilogue).  The two
-// numbers of each shape (us) are least-squares fits (10 % rms) to back-to-back timings of every shape at K = 256 ... 4096,
-// N = 192 ... 4096, M = 64 ... 16384; over those sizes and K = 64 ... 192 the choice costs 0.4 % on average against the best shape:
-//   256 x 256 (1.41, 5.2)  256 x 192 (1.11, 4.8)  128 x 128 at 8 wavefronts (0.528, 3)  64 x 128 (0.354, 3)  64 x 64 (0.232, 2.2)
-//   128 x 128 at 4 wavefronts, two workgroups per CU (1.04, 4.4), a last round of one per CU (0.61, 3.2)
-// e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty) or 512 tiles of 192 (2 full rounds).  With a fit over K = 1024
-// and 2048 alone, 6000 x 2048 x 4096 ran on 128 x 128 at 8 wavefronts, 126 us where 256 x 192 takes 104; 4593 x 4096 x 4096: 216 for 173.
+// numbers of each shape (us) are least-squares fits (7 % rms) to back-to-back timings of every shape at K = 256 ... 4096,
+// N = 512 ... 3072, M = 1500 ... 16384 (the small ones: M = 64 ... 16384); over these the choice costs 0.03 % on average against the
+// best shape, 4 % at most.
+//   256 x 256 (1.39, 6.3)  192 x 256 (1.16, 5.5)  256 x 192 (1.05, 5.6)  256 x 128 (0.86, 4.3)
+//   128 x 128 (0.528, 3)  64 x 128 (0.354, 3)  64 x 64 (0.232, 2.2)
+// e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty, 121 us) or 512 tiles of 256 x 192 (2 full rounds, 102); N = 2048,
+// K = 1024, M = 6000: 192 tiles of 256 x 256 (34.5) or 256 of 192 x 256 (30.0).
 inline NtTile nt_tile(long long M, int N, int K, double *us = nullptr) {
   const double slabs = (double)(K / 64);
-  auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-  auto cost = [&](int tm, int tn, double per_slab, double fixed) {
-    return (double)((tiles(tm, tn) + 255) / 256) * (slabs * per_slab + fixed);
-  };
-  const long long t128 = tiles(128, 128), rest = t128 % 512;
-  const double c256 = cost(256, 256, 1.41, 5.2), c192 = cost(256, 192, 1.11, 4.8), c128 = cost(128, 128, 0.528, 3.0),
-               c128x2 = (double)(t128 / 512 + (rest > 256)) * (slabs * 1.04 + 4.4) +
-                        (rest > 0 && rest <= 256 ? slabs * 0.61 + 3.2 : 0.0);
   const bool halves = K % 128 == 0;  // the shapes that split a slab over two halves of the wavefronts
-  const double c64x128 = halves ? cost(64, 128, 0.354, 3.0) : 1e30, c64 = halves ? cost(64, 64, 0.232, 2.2) : 1e30;
-  const double small = fmin(fmin(c128, c128x2), fmin(c64x128, c64));
-  if (us) *us = fmin(fmin(c192, c256), small);
-  if (fmin(c192, c256) <= small) return c192 < c256 ? NT_256x192 : NT_256x256;
-  if (c64 == small) return NT_64x64;
-  if (c64x128 == small) return NT_64x128;
-  return c128 == small ? NT_128x128_8W : NT_128x128_4W;
+  const struct { NtTile t; int tm, tn; double per_slab, fixed; bool ok; } shapes[] = {
+      {NT_256x192, 256, 192, 1.05, 5.6, true}, {NT_256x256, 256, 256, 1.39, 6.3, true}, {NT_192x256, 192, 256, 1.16, 5.5, true},
+      {NT_256x128, 256, 128, 0.86, 4.3, true}, {NT_128x128, 128, 128, 0.528, 3.0, true}, {NT_64x128, 64, 128, 0.354, 3.0, halves},
+      {NT_64x64, 64, 64, 0.232, 2.2, halves}};
+  NtTile best = NT_128x128;
+  double least = 1e300;
+  for (const auto &f : shapes) {
+    const long long tiles = ((M + f.tm - 1) / f.tm) * ((N + f.tn - 1) / f.tn);
+    const double cost = (double)((tiles + 255) / 256) * (slabs * f.per_slab + f.fixed);
+    if (f.ok && cost < least) least = cost, best = f.t;
+  }
+  if (us) *us = least;
+  return best;
 }
 
 // ---- weight gradients: C (Mo,No) = A (K,Mo)^T * B (K,No), bf16, K tokens -------------------------------------------------
@@ -115,7 +113,7 @@ inline PairForm gemm_pair(long long rows, int n_in, int n_out) {
   const bool halves = n_out % 128 == 0;
   const struct { NtTile t; int tm, tn; double us; bool ok; } nts[3] = {{NT_64x64, 64, 64, s_nt * 0.232 + 2.2, halves},
                                                                       {NT_64x128, 64, 128, s_nt * 0.354 + 3.0, halves},
-                                                                      {NT_128x128_8W, 128, 128, s_nt * 0.528 + 3.0, true}};
+                                                                      {NT_128x128, 128, 128, s_nt * 0.528 + 3.0, true}};
   const struct { TnTile t; int tm, tn; double us; } tns[3] = {{TN_64x64, 64, 64, s_tn * 0.30 + 2.0},
                                                               {TN_64x128, 64, 128, s_tn * 0.50 + 3.0},
                                                               {TN_128x128, 128, 128, s_tn * 0.715 + 3.0}};

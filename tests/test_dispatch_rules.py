@@ -74,11 +74,21 @@ def test_generic_attention_form_is_the_faster(T, BH, dh, causal, us32, us16):
 
 # M, N, K and us of each tile shape in the order of rules.NT_TILES
 NT_MEASURED = [
-    (4593, 4096, 4096, (207.5, 171.1, 352.7, 360.1, 215.9, 196.5)), (6000, 2048, 4096, (104.3, 160.1, 237.3, 166.6, 127.7, 119.5)),
-    (12000, 2048, 4096, (216.4, 249.5, 493.9, 349.5, 248.6, 222.4)), (12000, 1536, 4096, (207.9, 177.2, 326.8, 268.3, 200.6, 188.6)),
-    (2048, 4096, 4096, (97.5, 79.7, 152.8, 153.2, 91.0, 75.7)), (6000, 3072, 3072, (157.1, 137.9, 259.2, 215.1, 152.6, 138.9)),
-    (512, 2048, 128, (7.8, 6.9, 4.9, 5.0, 5.0, 6.7)), (512, 1536, 2048, (49.4, 39.5, 10.1, 14.3, 19.3, 22.6)),
-    (16384, 1536, 2048, (121.1, 101.8, 231.5, 185.9, 135.8, 119.9)), (4096, 2048, 4096, (96.6, 78.5, 153.2, 104.7, 82.0, 70.6)),
+    (4593, 4096, 4096, (203.5, 160.6, 361.1, 357.6, 213.9, 188.6, 169.1)),
+    (6000, 2048, 4096, (101.2, 153.3, 242.1, 172.2, 122.0, 124.3, 92.1)),
+    (12000, 2048, 4096, (216.0, 235.9, 491.4, 351.4, 249.7, 202.8, 191.3)),
+    (12000, 1536, 4096, (202.0, 160.7, 332.3, 268.0, 199.2, 180.1, 167.3)),
+    (2048, 4096, 4096, (97.7, 75.7, 153.4, 154.2, 85.3, 69.1, 87.2)),
+    (6000, 3072, 3072, (154.1, 122.8, 261.8, 213.7, 151.1, 138.6, 128.6)),
+    (512, 2048, 128, (8.0, 7.2, 3.8, 4.4, 4.5, 5.7, 6.8)),
+    (512, 1536, 2048, (48.1, 36.5, 10.3, 14.0, 19.5, 29.3, 39.8)),
+    (16384, 1536, 2048, (111.7, 94.8, 236.1, 189.5, 133.9, 108.8, 136.8)),
+    (4096, 2048, 4096, (93.3, 72.2, 154.8, 102.6, 81.7, 67.4, 82.0)),
+    (6000, 2048, 1024, (30.7, 45.6, 68.7, 49.8, 35.0, 36.2, 28.3)),
+    (4593, 1536, 2048, (50.1, 38.2, 63.2, 55.6, 41.3, 33.5, 43.2)),
+    (4096, 2048, 2048, (51.3, 39.3, 83.5, 56.3, 43.4, 36.7, 46.1)),
+    (1000, 1536, 2048, (48.3, 36.8, 18.6, 14.3, 19.9, 30.6, 40.3)),
+    (2000, 1536, 2048, (48.9, 37.4, 28.4, 27.9, 22.2, 33.2, 42.5)),
 ]
 
 

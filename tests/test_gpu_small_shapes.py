@@ -39,7 +39,7 @@ def check_product(got, ref, K):
 # of a tile's edge, contraction lengths of one slab, an odd number of slabs (no split over halves) and many
 GEMM_CASES = [(1, 1, 1, 64, 64), (65, 1, 1, 64, 192), (127, 3, 1, 64, 320), (512, 8, 2, 128, 2048), (511, 4, 4, 64, 1024),
               (1000, 8, 2, 128, 2048), (1999, 16, 4, 64, 2048), (2050, 5, 5, 64, 1024), (4593, 8, 8, 64, 2048),
-              (3001, 8, 2, 128, 2048), (4097, 16, 16, 128, 2048), (4097, 5, 5, 64, 320), (9001, 5, 5, 64, 448)]
+              (3001, 8, 2, 128, 2048), (4097, 16, 16, 128, 2048), (4097, 5, 5, 64, 320), (9001, 5, 5, 64, 448), (5953, 5, 5, 64, 2048)]
 
 
 @pytest.mark.parametrize("M,Hq,Hk,dh,E", GEMM_CASES)
@@ -55,7 +55,7 @@ def test_projection_tiles(M, Hq, Hk, dh, E):
 
 
 @pytest.mark.parametrize("slabs", [1, 2, 3, 4])
-@pytest.mark.parametrize("M,tile", [(9001, "256x192"), (33001, "256x256")])
+@pytest.mark.parametrize("M,tile", [(9001, "256x192"), (32700, "256x256"), (8001, "256x128"), (12001, "192x256")])
 def test_projection_of_few_slabs_on_large_tiles(M, tile, slabs):
     """Contractions shorter than the three slabs of A and two of the weight that the 256-row kernel holds, and just longer."""
     say("projection", M, slabs)
