@@ -473,6 +473,214 @@ __device__ __forceinline__ void value_role(const FusedArgs &a, const bf16_t *__r
   }
 }
 
+// ---------------------------------------------------------------------------
+// The prologue of short sequences, d_h = 64 and 128.  What bounds the kernel above there is one workgroup's chain: the filter in three
+// batches, the rows, R partner rows one after the other, the RoPE tables, each a memory latency, and 256 tokens on one CU while
+// most are idle.  Here a workgroup takes 64 tokens of one head with d_h / 16 wavefronts, wavefront = 32 tokens x 32 output channels,
+// and asks for everything it reads at once: the filter (straight into LDS), the token rows and the halo, the partner rows and the RoPE
+// table entries.  The sums of a token meet in LDS as fp32, where d_h / 16 lanes take its norm, rotate and store.
+// Prologue with its set-up, the kernel above -> this one, us: 1 x 512 tokens, 8 query and 2 KV heads of 128: 18.8 -> 12.4; 8 + 1 heads:
+// 21.0 -> 13.9; 16 + 4 heads of 64: 11.8 -> 8.7.  Prologue's adjoint with its gradients: 35.5 -> 31.8, 37.7 -> 32.3, 27.0 -> 24.0.
+// ---------------------------------------------------------------------------
+constexpr int SH_TOK = 64, SH_SRC = 4;  // tokens of a workgroup; partner rows requested at a time
+constexpr size_t short_u_bytes(int DH, int D) { return (size_t)(SH_TOK + D - 1) * (DH * 2 + 16); }
+constexpr size_t short_lds(int DH, int D) {
+  return (size_t)DH * D * DH * 2 + short_u_bytes(DH, D) + (size_t)SH_TOK * (DH + 4) * sizeof(float);
+}
+
+template <int DH, int D, bool BWD, bool IS_Q>
+__device__ __forceinline__ void prologue_short_head(
+    const FusedArgs &a, const bf16_t *__restrict__ lat, const u32x4 *__restrict__ wc, const float2 *__restrict__ ropeA,
+    const float2 *__restrict__ ropeB, const float *__restrict__ temp, bf16_t *__restrict__ dst_, float *__restrict__ rnorm, int bid,
+    unsigned char *smem) {
+  constexpr int NTH = DH * 4, NW = NTH / 64, KK = DH / 16, NTL = DH / 32, CPR = DH / 8, WROW = D * CPR;
+  constexpr int UROW = DH * 2 + 16, XROW = DH + 4, U_CHUNKS = (SH_TOK + D - 1) * CPR, NU = (U_CHUNKS + NTH - 1) / NTH;
+  constexpr int W_LOADS = DH * WROW / 64 / NW, LPT = DH / 16;  // load instructions of a wavefront; lanes of a token at the end
+  unsigned char *const sW = smem, *const sU = sW + DH * WROW * 16;
+  float *const sX = reinterpret_cast<float *>(sU + short_u_bytes(DH, D));
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = wave % NTL, rg = wave / NTL;
+  const int n_heads = IS_Q ? a.Hq : a.Hk, hl = bid % n_heads, head = IS_Q ? hl : a.Hq + hl, g = IS_Q ? hl / a.R : hl;
+  const long long row0 = (long long)(bid / n_heads) * SH_TOK, last = a.rows - 1;
+  const int ch0 = IS_Q ? hl * DH : a.e_q + g * DH;
+  const long long row = row0 + rg * 32 + l32, rowc = row < last ? row : last;
+  const int tk = tid / LPT, i0 = tid % LPT * 8;  // the token and the pairs of channels this lane finishes
+  const long long rowf = row0 + tk, rowfc = rowf < last ? rowf : last;
+
+  // ---- requests
+  u32x4 u[NU];
+#pragma unroll
+  for (int i = 0; i < NU; ++i) {  // rows outside the tensor repeat its first or last: the taps that reach them are zeroed below
+    const int id = min(tid + i * NTH, U_CHUNKS - 1), r = id / CPR;
+    long long gr = BWD ? row0 + r : row0 + r - (D - 1);
+    gr = gr < 0 ? 0 : gr > last ? last : gr;
+    u[i] = *reinterpret_cast<const u32x4 *>(lat + gr * a.src_stride + ch0 + id % CPR * 8);
+  }
+  const int n_src = IS_Q ? 1 : a.R;
+  constexpr int NS = IS_Q ? 1 : SH_SRC;
+  u32x4 mf[NS][2];
+  auto request_sources = [&](int s0) {  // sources past the last repeat it and are not added
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int col = IS_Q ? a.e_q + g * DH : (g * a.R + min(s0 + s, n_src - 1)) * DH;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        mf[s][j] = *reinterpret_cast<const u32x4 *>(lat + rowc * a.src_stride + col + ((2 * nt + j) * 2 + half) * 8);
+    }
+  };
+  request_sources(0);
+  f32x4 pa[4], pb[4];
+  float beta = 1.f;
+  if constexpr (!BWD) {  // (the tables are set up whatever the flags)
+    const int tpos = (int)(rowfc % a.T), thi = tpos >> 7, tlo = tpos & 127;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      pa[e] = reinterpret_cast<const f32x4 *>(ropeA + thi * (DH / 2) + i0)[e];
+      pb[e] = reinterpret_cast<const f32x4 *>(ropeB + (((i0 >> 2) + (e >> 1)) * 128 + tlo) * 4)[e & 1];
+    }
+    if (!IS_Q && (a.flags & CCA_KEY_TEMP)) beta = expf(temp[g]);
+  }
+  {
+    typedef __attribute__((address_space(3))) void lds_void;
+    typedef __attribute__((address_space(1))) void glb_void;
+    const u32x4 *const src = wc + (long long)head * DH * WROW;
+#pragma unroll
+    for (int i = 0; i < W_LOADS; ++i) {  // instruction p of the filter deposits chunks [64 p, 64 p + 64): chunk c of row o at c ^ o
+      const int at = (i * NW + wave) * 64 + lane, o = at / WROW, c = at % WROW;
+      __builtin_amdgcn_global_load_lds((glb_void *)(src + o * WROW + ((c & ~(CPR - 1)) | ((c ^ o) & (CPR - 1)))),
+                                       (lds_void *)(sW + (i * NW + wave) * 1024), 16, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NU; ++i) {
+    const int id = tid + i * NTH;
+    if (id < U_CHUNKS) *reinterpret_cast<u32x4 *>(sU + id / CPR * UROW + id % CPR * 16) = u[i];
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+
+  // ---- this wavefront's 32 channels of 32 tokens: the taps in order, then the means, all on one accumulator
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const int tposw = (int)(rowc % a.T), o = nt * 32 + l32;
+  const unsigned char *const ur = sU + (rg * 32 + l32 + (BWD ? 0 : D - 1)) * UROW + half * 16;  // the token's own row
+  auto tap = [&](auto d_c) {
+    constexpr int d = decltype(d_c)::value, back = D - 1 - d;
+    const bool outside = BWD ? tposw + back >= a.T : tposw < back;  // reaches out of the token's sequence
+    const unsigned char *const row_at = ur + (BWD ? back : -back) * UROW;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      u32x4 x = *reinterpret_cast<const u32x4 *>(row_at + kk * 32);
+      if (back > 0 && outside) x = u32x4{0, 0, 0, 0};
+      const int c = d * CPR + kk * 2 + half;
+      const u32x4 w = *reinterpret_cast<const u32x4 *>(sW + (o * WROW + ((c & ~(CPR - 1)) | ((c ^ o) & (CPR - 1)))) * 16);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
+    }
+  };
+  tap(std::integral_constant<int, 0>{});
+  if constexpr (D > 1) tap(std::integral_constant<int, 1>{});
+  if constexpr (D > 2) tap(std::integral_constant<int, 2>{});
+  if (a.flags & CCA_QK_MEAN) {  // c * I times the rows (prologue_fused_body): lane (l32, half) holds c in element l32 & 7 of one fragment
+    const float w_other = IS_Q ? a.mean_q_other : a.mean_k_other;
+    const bf16_t hi = f32_to_bf16(w_other), lo = f32_to_bf16(w_other - bf16_to_f32(hi));
+    auto add = [&](bf16_t c, int j, u32x4 x) {
+      const uint32_t cc = ((l32 >> 4) == j && ((l32 >> 3) & 1) == half) ? (uint32_t)c << (l32 & 1) * 16 : 0u;
+      const int e = (l32 & 7) >> 1;
+      const u32x4 w = {e == 0 ? cc : 0u, e == 1 ? cc : 0u, e == 2 ? cc : 0u, e == 3 ? cc : 0u};
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
+    };
+#pragma unroll
+    for (int j = 0; j < 2; ++j) add(f32_to_bf16(0.5f), j, *reinterpret_cast<const u32x4 *>(ur + (2 * nt + j) * 32));
+    for (int s0 = 0;;) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        if (s0 + s >= n_src) break;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) add(hi, j, mf[s][j]);
+        if ((lo & 0x7fffu) != 0) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) add(lo, j, mf[s][j]);
+        }
+      }
+      s0 += NS;
+      if (s0 >= n_src) break;
+      request_sources(s0);
+    }
+  }
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4) {
+    const f32x4 x = {acc[q4 * 4], acc[q4 * 4 + 1], acc[q4 * 4 + 2], acc[q4 * 4 + 3]};
+    *reinterpret_cast<f32x4 *>(sX + (rg * 32 + l32) * XROW + nt * 32 + q4 * 8 + half * 4) = x;
+  }
+  __syncthreads();
+
+  // ---- per token: norm, temperature, RoPE, one rounding
+  float x1[8], x2[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x1[e] = sX[tk * XROW + i0 + e], x2[e] = sX[tk * XROW + DH / 2 + i0 + e];
+  if constexpr (!BWD) {
+    float mul = 1.f;
+    if (a.flags & CCA_QK_NORM) {
+      float ssq = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ssq = fmaf(x1[e], x1[e], fmaf(x2[e], x2[e], ssq));
+#pragma unroll
+      for (int m = 1; m < LPT; m *= 2) ssq += __shfl_xor(ssq, m);
+      mul = sqrtf((float)DH) / sqrtf(ssq + a.norm_eps) * beta;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x1[e] *= mul, x2[e] *= mul;
+    }
+    if (rnorm && i0 == 0 && rowf <= last) rnorm[rowf * (a.Hq + a.Hk) + head] = mul;
+    if (a.flags & CCA_ROPE) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float ca = pa[e >> 1][(e & 1) * 2], sa = pa[e >> 1][(e & 1) * 2 + 1], cb = pb[e >> 1][(e & 1) * 2], sb = pb[e >> 1][(e & 1) * 2 + 1];
+        const float cs = ca * cb - sa * sb, sn = sa * cb + ca * sb, y1 = x1[e], y2 = x2[e];
+        x1[e] = y1 * cs - y2 * sn;
+        x2[e] = y2 * cs + y1 * sn;
+      }
+    }
+  }
+  if (rowf <= last) {
+    bf16_t *const to = dst_ + hl * DH + rowf * (IS_Q ? a.q_stride : a.k_stride) + i0;
+    *reinterpret_cast<u32x4 *>(to) = u32x4{pack2(x1[0], x1[1]), pack2(x1[2], x1[3]), pack2(x1[4], x1[5]), pack2(x1[6], x1[7])};
+    *reinterpret_cast<u32x4 *>(to + DH / 2) = u32x4{pack2(x2[0], x2[1]), pack2(x2[2], x2[3]), pack2(x2[4], x2[5]), pack2(x2[6], x2[7])};
+  }
+}
+
+template <int DH, int D, bool BWD>
+__device__ __forceinline__ void prologue_short_body(
+    const FusedArgs &a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
+    const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB, const float *__restrict__ temp, bf16_t *__restrict__ q,
+    bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm, int block, unsigned char *smem) {
+  if (block >= a.n_conv_blocks) value_role<BWD, DH * 4>(a, vsrc, v, ((long long)block - a.n_conv_blocks) * (DH * 16));
+  else if (block < a.n_k_blocks) prologue_short_head<DH, D, BWD, false>(a, lat, wc, ropeA, ropeB, temp, k, rnorm, block, smem);
+  else prologue_short_head<DH, D, BWD, true>(a, lat, wc, ropeA, ropeB, temp, q, rnorm, block - a.n_k_blocks, smem);
+}
+
+template <int DH, int D, bool BWD>
+__global__ __launch_bounds__(DH * 4) void prologue_short_kernel(
+    FusedArgs a, const bf16_t *__restrict__ lat, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc,
+    const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB, const float *__restrict__ temp,
+    bf16_t *__restrict__ q, bf16_t *__restrict__ k, bf16_t *__restrict__ v, float *__restrict__ rnorm) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  prologue_short_body<DH, D, BWD>(a, lat, vsrc, wc, ropeA, ropeB, temp, q, k, v, rnorm, blockIdx.x, smem);
+}
+
+// Its adjoint beside the filter gradients' partial sums, as prologue_adjoint_pair_kernel (a unit is a workgroup's d_h * 4 threads)
+template <int DH, int D>
+__global__ __launch_bounds__(DH * 4) void prologue_short_pair_kernel(
+    FusedArgs a, const bf16_t *__restrict__ d3, const bf16_t *__restrict__ vsrc, const u32x4 *__restrict__ wc, bf16_t *__restrict__ dq,
+    bf16_t *__restrict__ dk, bf16_t *__restrict__ dv, DwcArgs w, int n_adjoint) {
+  static_assert(dwc_threads(DH) == DH * 4, "threads of both roles");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if ((int)blockIdx.x < n_adjoint)
+    prologue_short_body<DH, D, true>(a, d3, vsrc, wc, nullptr, nullptr, nullptr, dq, dk, dv, nullptr, blockIdx.x, smem);
+  else
+    dwc_body<DH, D>(w, (int)blockIdx.x - n_adjoint, 0, threadIdx.x, smem);
+}
+
 // The workgroup's head and its streams
 struct StreamHead {
   bool is_q;
@@ -983,6 +1191,34 @@ int plan_grid(const Dims &d, FusedArgs &a) {
   return a.n_conv_blocks + v_blocks;
 }
 
+// The short form: 64 tokens of one head per workgroup.  Returns the grid size.
+int plan_short(const Dims &d, FusedArgs &a) {
+  const long long blocks = (d.rows() + SH_TOK - 1) / SH_TOK, per_v = d.dh * 16;
+  a.n_k_blocks = (int)(d.Hk * blocks);
+  a.n_conv_blocks = (int)((d.Hq + d.Hk) * blocks);
+  return a.n_conv_blocks + (int)((d.rows() * (d.e_kv / 8) + per_v - 1) / per_v);
+}
+
+template <int DH, int D, bool BWD>
+hipError_t launch_short(const FusedArgs &a, const void *lat, const void *vsrc, const void *wc, const float2 *ropeA,
+                        const float2 *ropeB, const float *temp, void *q, void *k, void *v, float *rnorm, int grid, hipStream_t s) {
+  static_assert(short_lds(DH, D) <= 160 * 1024, "LDS");
+  if (hipError_t e = raise_lds_limit<prologue_short_kernel<DH, D, BWD>>(short_lds(DH, D)); e != hipSuccess) return e;
+  prologue_short_kernel<DH, D, BWD><<<grid, DH * 4, short_lds(DH, D), s>>>(a, (const bf16_t *)lat, (const bf16_t *)vsrc, (const u32x4 *)wc, ropeA,
+                                                                           ropeB, temp, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, rnorm);
+  return hipGetLastError();
+}
+
+template <int DH, int D>
+hipError_t launch_short_pair(const FusedArgs &a, const void *d3, const void *vsrc, const void *wc, void *dq, void *dk, void *dv,
+                             const DwcArgs &w, int grid, hipStream_t s) {
+  constexpr size_t smem = short_lds(DH, D) > dwc_lds(DH, D) ? short_lds(DH, D) : dwc_lds(DH, D);
+  if (hipError_t e = raise_lds_limit<prologue_short_pair_kernel<DH, D>>(smem); e != hipSuccess) return e;
+  prologue_short_pair_kernel<DH, D><<<grid + w.units, DH * 4, smem, s>>>(a, (const bf16_t *)d3, (const bf16_t *)vsrc, (const u32x4 *)wc,
+                                                                         (bf16_t *)dq, (bf16_t *)dk, (bf16_t *)dv, w, grid);
+  return hipGetLastError();
+}
+
 struct FusedScratch {
   bf16_t *wc;
   float2 *ropeA, *ropeB;
@@ -1111,8 +1347,9 @@ hipError_t prologue_fused_run(const Dims &d, const cca_weights &w, const void *l
       default: return launch_stream<3, false>(d, a, w.temp, lat, vsrc, fs, q, k, v, rnorm, s);
     }
   }
-  const int grid = plan_grid(d, a);
-#define LAUNCH_DH(D_, B_) (d.dh == 64 ? launch_main<64, D_, B_> : launch_main<128, D_, B_>)
+  const bool brief = prologue_is_short(d.rows(), d.Hq + d.Hk, d.R, d.dh, false);
+  const int grid = brief ? plan_short(d, a) : plan_grid(d, a);
+#define LAUNCH_DH(D_, B_) (brief ? d.dh == 64 ? launch_short<64, D_, B_> : launch_short<128, D_, B_> : d.dh == 64 ? launch_main<64, D_, B_> : launch_main<128, D_, B_>)
   switch (D) {
     case 1: return LAUNCH_DH(1, false)(a, lat, vsrc, fs.wc, fs.ropeA, fs.ropeB, w.temp, q, k, v, rnorm, grid, s);
     case 2: return LAUNCH_DH(2, false)(a, lat, vsrc, fs.wc, fs.ropeA, fs.ropeB, w.temp, q, k, v, rnorm, grid, s);
@@ -1153,9 +1390,11 @@ hipError_t prologue_fused_bwd_dlat(const Dims &d, const void *d3, const void *d_
       default: return launch_stream<3, true>(d, a, nullptr, d3, d_v, fs, dl, dl + d.e_q, dl + ld, nullptr, s);
     }
   }
-  const int grid = plan_grid(d, a);
+  const bool brief = prologue_is_short(d.rows(), d.Hq + d.Hk, d.R, d.dh, true);
+  const int grid = brief ? plan_short(d, a) : plan_grid(d, a);
   if (dwc) {
-#define PAIR(D_) (d.dh == 64 ? launch_adjoint_pair<64, D_> : launch_adjoint_pair<128, D_>)(a, d3, d_v, fs.wc, dl, dl + d.e_q, dl + ld, *dwc, grid, s)
+#define PAIR(D_) (brief ? d.dh == 64 ? launch_short_pair<64, D_> : launch_short_pair<128, D_> : d.dh == 64 ? launch_adjoint_pair<64, D_> : launch_adjoint_pair<128, D_>) \
+      (a, d3, d_v, fs.wc, dl, dl + d.e_q, dl + ld, *dwc, grid, s)
     return D == 1 ? PAIR(1) : D == 2 ? PAIR(2) : PAIR(3);
 #undef PAIR
   }

@@ -196,6 +196,20 @@ constexpr SplitCost BWD_SPLIT{2.0, 1.0, 1.0, 0.1};
 inline bool dq_splits_keys(long long BH, int T, bool causal) { return split_pays(BH, T, causal, true, BWD_SPLIT); }
 inline bool dkdv_splits_rows(long long BH, int T, bool causal) { return split_pays(BH, T, causal, false, BWD_SPLIT); }
 
+// ---- prologue at d_h = 64, 128: 64 tokens of one head per workgroup, everything requested at once, or 256 and more ------------
+// The short form reads the whole filter for every 64 tokens (d_h = 128: one workgroup per CU, 64: three), the long one's workgroups
+// are a chain of ten memory latencies, longer where a key head adds the rows of several query heads.  Its lead ends with the first
+// round of the grid, at R > 1 with the second.  Prologue with its set-up, short and long, us (heads, rows): d_h = 128: 8 + 2, 512:
+// 12.4, 18.8; 3000: 19.1, 20.0; 4593: 25.5, 21.2; 4 + 4, 2048: 13.3, 16.7; 3000: 19.0, 16.9; 32 + 8, 512: 20.1, 22.7; 1024: 26.5,
+// 23.3; d_h = 64: 16 + 4, 1024: 10.2, 12.0; 2048: 12.1, 12.6; 3000: 14.9, 14.1; 8 + 8, 3000: 13.2, 12.1.  The adjoint shares its
+// launch with the filter gradients: d_h = 128: 8 + 2, 1024: 35.7, 38.5; 2048: 48.6, 47.2; 4 + 4, 2048: 41.5, 39.1; d_h = 64: 16 + 4,
+// 3000: 36.0, 37.8; 4593: 43.2, 43.8; 8000: 56.6, 56.0.
+inline bool prologue_is_short(long long rows, int heads, int R, int dh, bool adjoint) {
+  const long long blocks = (rows + 63) / 64 * heads;
+  if (dh == 64) return blocks <= (adjoint ? 1536 : 640);
+  return blocks <= (adjoint ? 240 : R > 1 ? 512 : 256);
+}
+
 // ---- prologue at d_h = 256: one head x 128 tokens per workgroup (one wavefront per SIMD) or 256 (two) -------------------
 // One workgroup per CU either way.  A lone round of the 128-token form takes half of the other's time (24 against 45 us at two
 // taps each and 6 / 2 heads), a full one 0.6 of it, so it wins while one round is enough (4096 tokens: 31.0 against 46.7) and,

@@ -50,6 +50,27 @@ def test_wide_head_prologue_cases_reach_both_forms():
     assert reached == {(taps, adjoint, wide) for taps in (1, 2, 3) for adjoint in (False, True) for wide in (False, True)}
 
 
+def test_prologue_cases_reach_both_forms():
+    reached = set()
+    for B, T, Hq, Hk, k_seq, k_ch, dh in small.PROLOGUE_CASES:
+        for adjoint in (False, True):
+            reached.add((dh, k_seq + k_ch - 1, adjoint, rules.prologue_is_short(B * T, Hq + Hk, Hq // Hk, dh, adjoint)))
+    assert reached == {(dh, taps, adjoint, short) for dh in (64, 128) for taps in (1, 2, 3) for adjoint in (False, True) for short in (False, True)}
+
+
+# rows, query and KV heads, d_h, adjoint and us of the short and of the long form
+PROLOGUE_MEASURED = [(512, 8, 2, 128, False, 12.4, 18.8), (3000, 8, 2, 128, False, 19.1, 20.0), (4593, 8, 2, 128, False, 25.5, 21.2),
+                     (3000, 4, 4, 128, False, 19.0, 16.9), (2048, 4, 4, 128, False, 13.3, 16.7), (1024, 32, 8, 128, False, 26.5, 23.3),
+                     (2048, 16, 4, 64, False, 12.1, 12.6), (3000, 16, 4, 64, False, 14.9, 14.1), (3000, 8, 8, 64, False, 13.2, 12.1),
+                     (1024, 8, 2, 128, True, 35.7, 38.5), (2048, 8, 2, 128, True, 48.6, 47.2), (2048, 4, 4, 128, True, 41.5, 39.1),
+                     (3000, 16, 4, 64, True, 36.0, 37.8), (7996, 16, 4, 64, True, 56.6, 56.0)]
+
+
+@pytest.mark.parametrize("rows,Hq,Hk,dh,adjoint,short_us,long_us", PROLOGUE_MEASURED)
+def test_prologue_form_is_the_faster(rows, Hq, Hk, dh, adjoint, short_us, long_us):
+    assert rules.prologue_is_short(rows, Hq + Hk, Hq // Hk, dh, adjoint) == (short_us < long_us)
+
+
 def test_generic_cases_reach_every_form():
     rows, bwd, splits = set(), set(), set()
     for c in small.GENERIC_CASES:

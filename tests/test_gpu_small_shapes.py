@@ -353,10 +353,28 @@ STREAM_CASES = [(3, 45, 1, 1, 1, 1), (2, 131, 4, 1, 2, 2), (1, 1, 2, 2, 2, 1), (
 
 @pytest.mark.parametrize("B,T,Hq,Hk,k_seq,k_ch", STREAM_CASES)
 def test_wide_head_prologue(B, T, Hq, Hk, k_seq, k_ch):
+    say("wide head prologue", B, T, Hq, Hk, k_seq, k_ch)
+    check_prologue(B, T, Hq, Hk, k_seq, k_ch, 256)
+
+
+# d_h = 64 and 128, the short and the long form, forward and adjoint, with 1, 2 and 3 taps: sequences shorter than the taps reach, many
+# of them in a workgroup's 64 tokens, one token more and less than 64, one to five query heads per KV head (their mean's weight
+# exact in bf16 or not, more partner rows than are requested at a time)
+PROLOGUE_CASES = [(1, 1, 2, 2, 2, 1, 64), (1, 1, 1, 1, 1, 1, 128), (13, 5, 4, 2, 2, 2, 128), (70, 2, 2, 1, 2, 2, 64), (1, 63, 3, 1, 2, 2, 128),
+                  (1, 64, 5, 1, 3, 1, 64), (2, 65, 10, 2, 1, 2, 128), (1, 129, 8, 8, 1, 1, 64), (3, 131, 6, 2, 1, 1, 128), (1, 3900, 5, 1, 2, 2, 128),
+                  (1, 7900, 1, 1, 1, 1, 128), (1, 8300, 1, 1, 2, 1, 128), (2, 4400, 2, 2, 2, 2, 128), (1, 8300, 1, 1, 1, 1, 128),
+                  (1, 20601, 1, 1, 1, 1, 64), (3, 16421, 1, 1, 1, 2, 64), (4, 6151, 4, 4, 2, 2, 64), (3, 16421, 1, 1, 1, 1, 64)]
+
+
+@pytest.mark.parametrize("B,T,Hq,Hk,k_seq,k_ch,dh", PROLOGUE_CASES)
+def test_prologue_forms(B, T, Hq, Hk, k_seq, k_ch, dh):
+    say("prologue", B, T, Hq, Hk, k_seq, k_ch, dh)
+    check_prologue(B, T, Hq, Hk, k_seq, k_ch, dh)
+
+
+def check_prologue(B, T, Hq, Hk, k_seq, k_ch, dh):
     """q, k, v and, through autograd, d_lat against the steps in fp64.  The filters are folded and rounded to bf16 (2^-9 of each
     weight), q and k rounded once, the gradient entering the convolutions once: the 1e-2 of the whole-block tests."""
-    dh = 256
-    say("wide head prologue", B, T, Hq, Hk, k_seq, k_ch)
     cfg = P.CCAConfig(B=B, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, k_seq=k_seq, k_ch=k_ch)
     w = P.CCAWeights(w_down=None, w_out=None, w_conv_seq=rnd(cfg.e_q + cfg.e_kv, k_seq, seed=1, scale=k_seq ** -0.5),
                      w_conv_ch=rnd(Hq + Hk, dh, dh, k_ch, seed=2, scale=(dh * k_ch) ** -0.5), temp=rnd(Hk, seed=3, scale=0.3, dtype=torch.float32))
@@ -376,7 +394,10 @@ def test_wide_head_prologue(B, T, Hq, Hk, k_seq, k_ch):
                          ("d_w_conv_ch", g.w_conv_ch, w1.grad), ("d_temp", g.temp, temp.grad)):
         rel = float((got.double() - r.detach()).norm() / r.detach().norm())
         say(name, rel)
-        assert rel <= 1e-2, (name, rel)
+        # d_temp is one sum over d_k k per head, of either sign: k's rounding (2^-9 of a term, 2^-9 / sqrt(3) on average) does not cancel
+        # with the terms
+        noise = 4 * 2.0 ** -9 * float((d_k.double() * ref[1].detach()).norm() / r.detach().norm()) if name == "d_temp" else 0.0
+        assert rel <= 1e-2 + noise, (name, rel, noise)
 
 
 # the decode step's projections (several passes through LDS, K slices of the down-projection, lengths that are not whole
