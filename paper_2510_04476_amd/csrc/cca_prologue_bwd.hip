@@ -234,8 +234,20 @@ __global__ __launch_bounds__(256) void pro_bwd_unfold_w1_kernel(const float *__r
 #pragma unroll
       for (int d = 0; d < 3; ++d) sum[d] += v[u][d];
   }
-  for (; c < n_chunks; ++c)
-    for (int d = 0; d < D; ++d) sum[d] += p0[c * cstride + d * DH];
+  if (c < n_chunks) {  // the rest, again all in flight: past the last chunk they repeat it and are not added
+    float v[7][3];
+    const float *p = p0 + c * cstride;
+#pragma unroll
+    for (int u = 0; u < 7; ++u) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) v[u][d] = p[(d < D ? d : 0) * DH];
+      if (c + u + 1 < n_chunks) p += cstride;
+    }
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+#pragma unroll
+      for (int d = 0; d < 3; ++d) sum[d] += c + u < n_chunks ? v[u][d] : 0.f;
+  }
   for (int d = 0; d < D; ++d) dwc[(((long long)h * DH + o) * D + d) * DH + i] = sum[d];
   if (!dw1) return;
   for (int j = 0; j < kc; ++j) {
@@ -291,11 +303,15 @@ __global__ __launch_bounds__(W0_IW * 8) void pro_bwd_unfold_w0_kernel(const floa
 
 int taps(const Dims &d) { return ((d.flags & CCA_CONV_SEQ) ? d.k_seq : 1) + d.k_ch - 1; }
 
-// tokens per chunk of the filter-gradient kernel: the largest of 512..64 that still gives >= 256 workgroups
+// Tokens per chunk of the filter-gradient kernel: the largest of 512..64 that still gives 80 workgroups.  They run beside the
+// adjoint's, and every chunk's sums (196 KB a head at d_h = 128) are written and read once more: with 256 workgroups and a unit's
+// last few chunks added one after the other the backward pass took (us, then now) 2 x 512 tokens, 8 query and 2 KV heads of 128:
+// 105.7, 99.5; 2 x 2048: 266.0, 251.6; 1 x 2048, 6 + 6 heads: 179.7, 165.3; 1 x 4096, 4 + 1 heads of 256: 638, 631; 40 workgroups:
+// 98.1, 256.6, 165.7, 628.
 int dwc_chunk(const Dims &d) {
   const int NH = d.Hq + d.Hk, os = dwc_slices(d.dh, taps(d));
   for (int c = 512; c > 64; c >>= 1)
-    if ((long long)d.B * ((d.T + c - 1) / c) * NH * os >= 256) return c;
+    if ((long long)d.B * ((d.T + c - 1) / c) * NH * os >= 80) return c;
   return 64;
 }
 
