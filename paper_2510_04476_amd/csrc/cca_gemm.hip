@@ -71,6 +71,24 @@ __device__ __forceinline__ void add_wave_parts(f32x16 (&acc)[NI][MI], unsigned c
   }
 }
 
+// Tile (row tm, column tn) of workgroup wg; false: none.  Workgroups are dealt round-robin over the 8 XCDs, each with an L2 of its own, so
+// every XCD gets a contiguous range of tiles; the order runs down panels of `panel` columns of tiles (tile_panel).
+struct TileGrid {
+  int tiles_n, tiles, panel;
+};
+__device__ __forceinline__ bool tile_of(const TileGrid &g, int wg, int &tm, int &tn) {
+  const int tile = (wg % 8) * ((g.tiles + 7) / 8) + wg / 8;
+  if (tile >= g.tiles) return false;
+  const int full = g.panel * (g.tiles / g.tiles_n), p = tile / full, r = tile - p * full, width = min(g.panel, g.tiles_n - p * g.panel);
+  tm = r / width;
+  tn = p * g.panel + r - tm * width;
+  return true;
+}
+TileGrid tile_grid(long long M, int N, int tm, int tn) {
+  const int tiles_m = (int)((M + tm - 1) / tm), tiles_n = (N + tn - 1) / tn;
+  return TileGrid{tiles_n, tiles_m * tiles_n, tile_panel(tiles_m, tiles_n, tm, tn)};
+}
+
 // acc[ni][mi][r] = C[m][n] with m = wm*32*MI + mi*32 + l32 and n = wn*32*NI + ni*32 + 8*(r/4) + 4*half + r%4 of the tile
 // at (m0, n0): packed to bf16, staged in LDS and written as whole rows.  `owner`: this wavefront holds sums to store.
 template <int TM, int TN, int NTHREADS, int NI, int MI>
@@ -127,7 +145,7 @@ template <int TM, int BN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(const bf16_t *__restrict__ A,
                                                                const bf16_t *__restrict__ Bt,
                                                                bf16_t *__restrict__ C, long long M, int N, int K,
-                                                               int tiles_n, int tiles_total, ColumnSplit split) {
+                                                               TileGrid grid, ColumnSplit split) {
   constexpr int NWAVES = WAVES_M * WAVES_N, NTHREADS = NWAVES * 64;
   constexpr int WM = TM / WAVES_M, WN = BN / WAVES_N;  // wave tile
   constexpr int MI = WM / 32, NI = WN / 32;            // 32x32 MFMA tiles per wave
@@ -137,15 +155,10 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
   constexpr int A_STAGE = TM * 8, B_STAGE = BN * 8;  // 16-byte chunks of a slab
   u32x4 *const sA = reinterpret_cast<u32x4 *>(smem), *const sB = sA + A_STAGES * A_STAGE;
 
-  // XCD-aware tile order: workgroup ids are dealt round-robin over the 8 XCDs,
-  // so give each XCD a contiguous range of tiles; within it the N tiles of one
-  // M block are adjacent and share the A panel in that XCD's L2.
-  const int wg = blockIdx.x;
-  const int per_xcd = (tiles_total + 7) / 8;
-  const int tile = (wg % 8) * per_xcd + wg / 8;
-  if (tile >= tiles_total) return;
-  const long long m0 = (long long)(tile / tiles_n) * TM;
-  const int n0 = (tile % tiles_n) * BN;
+  int tm, tn;
+  if (!tile_of(grid, blockIdx.x, tm, tn)) return;
+  const long long m0 = (long long)tm * TM;
+  const int n0 = tn * BN;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -408,7 +421,7 @@ __device__ __forceinline__ int swz_tn(int r, int c) {  // 16-byte chunk c of tok
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 __device__ __forceinline__ void gemm_bf16_tn_deep_body(
     const bf16_t *__restrict__ A, long long lda, const bf16_t *__restrict__ Bm, long long ldb, bf16_t *__restrict__ C,
-    int Mo, int No, long long K, int tiles_n, int tiles_total, int wg, unsigned char *smem) {
+    int Mo, int No, long long K, const TileGrid &grid, int wg, unsigned char *smem) {
   static_assert((TM == 64 || TM == 128) && (TN == 64 || TN == 128), "swz_tn");
   constexpr int NWAVES = WAVES_M * WAVES_N * WAVES_K, NTHREADS = NWAVES * 64;
   constexpr int MI = TM / WAVES_M / 32, NI = TN / WAVES_N / 32;
@@ -417,10 +430,9 @@ __device__ __forceinline__ void gemm_bf16_tn_deep_body(
   static_assert(PER_WAVE * 64 * NWAVES == STAGE && A_CH % 64 == 0, "instructions must divide evenly over the wavefronts");
   u32x4 *const sbase = reinterpret_cast<u32x4 *>(smem);
 
-  const int per_xcd = (tiles_total + 7) / 8;
-  const int tile = (wg % 8) * per_xcd + wg / 8;
-  if (tile >= tiles_total) return;
-  const int m0 = (tile / tiles_n) * TM, n0 = (tile % tiles_n) * TN;
+  int tm, tn;
+  if (!tile_of(grid, wg, tm, tn)) return;
+  const int m0 = tm * TM, n0 = tn * TN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
   const int wk = wave / (WAVES_M * WAVES_N), wmn = wave % (WAVES_M * WAVES_N), wm = wmn / WAVES_N, wn = wmn % WAVES_N;
 
@@ -528,9 +540,9 @@ __device__ __forceinline__ void gemm_bf16_tn_deep_body(
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_tn_deep_kernel(
     const bf16_t *__restrict__ A, long long lda, const bf16_t *__restrict__ Bm, long long ldb, bf16_t *__restrict__ C,
-    int Mo, int No, long long K, int tiles_n, int tiles_total) {
+    int Mo, int No, long long K, TileGrid grid) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  gemm_bf16_tn_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, lda, Bm, ldb, C, Mo, No, K, tiles_n, tiles_total, blockIdx.x, smem);
+  gemm_bf16_tn_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, lda, Bm, ldb, C, Mo, No, K, grid, blockIdx.x, smem);
 }
 
 // LDS of a small-tile workgroup: its stages (`rows` rows of 64 values), then the wavefronts' sums and the tile on its way out
@@ -543,12 +555,12 @@ constexpr size_t deep_lds(int tm, int tn, int waves_k, int rows) {
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 hipError_t launch_tn_deep(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No, long long K,
                           hipStream_t s) {
-  const int tiles_m = (Mo + TM - 1) / TM, tiles_n = (No + TN - 1) / TN, total = tiles_m * tiles_n;
+  const TileGrid grid = tile_grid(Mo, No, TM, TN);
   constexpr size_t smem = deep_lds(TM, TN, WAVES_K, STAGES * (TM + TN));
   constexpr auto kernel = gemm_bf16_tn_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>;
   if (hipError_t e = raise_lds_limit<kernel>(smem); e != hipSuccess) return e;
-  kernel<<<(total + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb,
-                                                                            (bf16_t *)C, Mo, No, K, tiles_n, total);
+  kernel<<<(grid.tiles + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb,
+                                                                            (bf16_t *)C, Mo, No, K, grid);
   return hipGetLastError();
 }
 
@@ -604,16 +616,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 template <int TM, int BN, int WAVES_M, int WAVES_N>
 hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
                        hipStream_t s) {
-  const int tiles_m = (int)((M + TM - 1) / TM), tiles_n = (N + BN - 1) / BN;
-  const int total = tiles_m * tiles_n;
-  const int per_xcd = (total + 7) / 8;
+  const TileGrid grid = tile_grid(M, N, TM, BN);
   constexpr size_t epi_bytes = (size_t)TM * (BN * 2 + 16);
   constexpr size_t main_bytes = (size_t)(A_STAGES * TM + B_STAGES * BN) * BK * 2;
   constexpr size_t smem = main_bytes > epi_bytes ? main_bytes : epi_bytes;
   static_assert(smem <= 160 * 1024, "LDS");
   if (hipError_t e = raise_lds_limit<gemm_bf16_nt_kernel<TM, BN, WAVES_M, WAVES_N>>(smem); e != hipSuccess) return e;
-  gemm_bf16_nt_kernel<TM, BN, WAVES_M, WAVES_N><<<per_xcd * 8, WAVES_M * WAVES_N * 64, smem, s>>>((const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N,
-                                                             K, tiles_n, total, split);
+  gemm_bf16_nt_kernel<TM, BN, WAVES_M, WAVES_N><<<(grid.tiles + 7) / 8 * 8, WAVES_M * WAVES_N * 64, smem, s>>>((const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N,
+                                                             K, grid, split);
   return hipGetLastError();
 }
 
@@ -633,7 +643,7 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 __device__ __forceinline__ void gemm_bf16_nt_deep_body(
     const bf16_t *__restrict__ A, const bf16_t *__restrict__ Bt, bf16_t *__restrict__ C, long long M, int N, int K,
-    int tiles_n, int tiles_total, const ColumnSplit &split, int wg, unsigned char *smem) {
+    const TileGrid &grid, const ColumnSplit &split, int wg, unsigned char *smem) {
   constexpr int NWAVES = WAVES_M * WAVES_N * WAVES_K, NTHREADS = NWAVES * 64;
   constexpr int WM = TM / WAVES_M, WN = TN / WAVES_N, MI = WM / 32, NI = WN / 32;
   static_assert(MI * 32 == WM && NI * 32 == WN, "wave tile must be a multiple of 32");
@@ -642,11 +652,10 @@ __device__ __forceinline__ void gemm_bf16_nt_deep_body(
   static_assert(PER_WAVE * 64 * NWAVES == STAGE, "instructions must divide evenly over the wavefronts");
   u32x4 *const sbase = reinterpret_cast<u32x4 *>(smem);
 
-  const int per_xcd = (tiles_total + 7) / 8;
-  const int tile = (wg % 8) * per_xcd + wg / 8;
-  if (tile >= tiles_total) return;
-  const long long m0 = (long long)(tile / tiles_n) * TM;
-  const int n0 = (tile % tiles_n) * TN;
+  int tm, tn;
+  if (!tile_of(grid, wg, tm, tn)) return;
+  const long long m0 = (long long)tm * TM;
+  const int n0 = tn * TN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
   const int wk = wave / (WAVES_M * WAVES_N), wmn = wave % (WAVES_M * WAVES_N), wm = wmn / WAVES_N, wn = wmn % WAVES_N;
 
@@ -722,20 +731,19 @@ __device__ __forceinline__ void gemm_bf16_nt_deep_body(
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_deep_kernel(
     const bf16_t *__restrict__ A, const bf16_t *__restrict__ Bt, bf16_t *__restrict__ C, long long M, int N, int K,
-    int tiles_n, int tiles_total, ColumnSplit split) {
+    TileGrid grid, ColumnSplit split) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  gemm_bf16_nt_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, Bt, C, M, N, K, tiles_n, tiles_total, split, blockIdx.x, smem);
+  gemm_bf16_nt_deep_body<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>(A, Bt, C, M, N, K, grid, split, blockIdx.x, smem);
 }
 
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
                             hipStream_t s) {
-  const int tiles_m = (int)((M + TM - 1) / TM), tiles_n = (N + TN - 1) / TN;
-  const int total = tiles_m * tiles_n;
+  const TileGrid grid = tile_grid(M, N, TM, TN);
   constexpr size_t smem = deep_lds(TM, TN, WAVES_K, STAGES * WAVES_K * (TM + TN));
   if (hipError_t e = raise_lds_limit<gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>>(smem); e != hipSuccess) return e;
-  gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES><<<(total + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>(
-      (const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N, K, tiles_n, total, split);
+  gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES><<<(grid.tiles + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>(
+      (const bf16_t *)A, (const bf16_t *)Bt, (bf16_t *)C, M, N, K, grid, split);
   return hipGetLastError();
 }
 
@@ -756,14 +764,15 @@ struct NtArgs {
   const bf16_t *A, *Bt;
   bf16_t *C;
   long long M;
-  int N, K, tiles_n, tiles;
+  int N, K;
+  TileGrid grid;
 };
 struct TnArgs {
   const bf16_t *A, *B;
   bf16_t *C;
   int Mo, No;
   long long K;
-  int tiles_n, tiles;
+  TileGrid grid;
 };
 
 template <typename NT_, typename TN_>
@@ -771,11 +780,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_pair_kernel(NtArgs nt, TnArgs t
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int wg = (int)blockIdx.x < first ? blockIdx.x : blockIdx.x - first;
   if (((int)blockIdx.x < first) == (nt_first != 0))
-    gemm_bf16_nt_deep_body<NT_::TM, NT_::TN, NT_::WM, NT_::WN, NT_::WK, NT_::ST>(nt.A, nt.Bt, nt.C, nt.M, nt.N, nt.K, nt.tiles_n,
-                                                                                 nt.tiles, ColumnSplit{}, wg, smem);
+    gemm_bf16_nt_deep_body<NT_::TM, NT_::TN, NT_::WM, NT_::WN, NT_::WK, NT_::ST>(nt.A, nt.Bt, nt.C, nt.M, nt.N, nt.K, nt.grid,
+                                                                                 ColumnSplit{}, wg, smem);
   else
     gemm_bf16_tn_deep_body<TN_::TM, TN_::TN, TN_::WM, TN_::WN, TN_::WK, TN_::ST>(tn.A, tn.Mo, tn.B, tn.No, tn.C, tn.Mo, tn.No, tn.K,
-                                                                                 tn.tiles_n, tn.tiles, wg, smem);
+                                                                                 tn.grid, wg, smem);
 }
 
 template <typename NT_, typename TN_>
@@ -784,11 +793,9 @@ hipError_t launch_pair(NtArgs nt, TnArgs tn, bool nt_first, hipStream_t s) {
   constexpr size_t a = deep_lds(NT_::TM, NT_::TN, NT_::WK, NT_::ST * NT_::WK * (NT_::TM + NT_::TN)),
                    b = deep_lds(TN_::TM, TN_::TN, TN_::WK, TN_::ST * (TN_::TM + TN_::TN)), smem = a > b ? a : b;
   static_assert(smem <= 160 * 1024, "LDS");
-  nt.tiles_n = (nt.N + NT_::TN - 1) / NT_::TN;
-  nt.tiles = (int)((nt.M + NT_::TM - 1) / NT_::TM) * nt.tiles_n;
-  tn.tiles_n = (tn.No + TN_::TN - 1) / TN_::TN;
-  tn.tiles = (tn.Mo + TN_::TM - 1) / TN_::TM * tn.tiles_n;
-  const int n_nt = (nt.tiles + 7) / 8 * 8, n_tn = (tn.tiles + 7) / 8 * 8;
+  nt.grid = tile_grid(nt.M, nt.N, NT_::TM, NT_::TN);
+  tn.grid = tile_grid(tn.Mo, tn.No, TN_::TM, TN_::TN);
+  const int n_nt = (nt.grid.tiles + 7) / 8 * 8, n_tn = (tn.grid.tiles + 7) / 8 * 8;
   constexpr auto kernel = gemm_bf16_pair_kernel<NT_, TN_>;
   if (hipError_t e = raise_lds_limit<kernel>(smem); e != hipSuccess) return e;
   kernel<<<n_nt + n_tn, 512, smem, s>>>(nt, tn, nt_first ? n_nt : n_tn, nt_first ? 1 : 0);
@@ -906,8 +913,8 @@ hipError_t gemm_adjoint_pair(const void *d_C, const void *W, void *d_A, const vo
     if (hipError_t e = gemm_tn_mfma_bf16(A, n_in, d_C, n_out, d_W, n_in, n_out, rows, part, s); e != hipSuccess) return e;
     return gemm_mfma_bf16(d_C, W, d_A, rows, n_in, n_out, s);
   }
-  const NtArgs nt{(const bf16_t *)d_C, (const bf16_t *)W, (bf16_t *)d_A, rows, n_in, n_out, 0, 0};
-  const TnArgs tn{(const bf16_t *)A, (const bf16_t *)d_C, (bf16_t *)d_W, n_in, n_out, rows, 0, 0};
+  const NtArgs nt{(const bf16_t *)d_C, (const bf16_t *)W, (bf16_t *)d_A, rows, n_in, n_out, {}};
+  const TnArgs tn{(const bf16_t *)A, (const bf16_t *)d_C, (bf16_t *)d_W, n_in, n_out, rows, {}};
 #define PAIR(NT_)                                                                               \
   switch (f.tn) {                                                                               \
     case TN_64x64: return launch_pair<NT_, TnDeep64x64>(nt, tn, f.nt_first, s);                 \

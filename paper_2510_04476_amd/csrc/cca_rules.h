@@ -36,6 +36,40 @@ inline NtTile nt_tile(long long M, int N, int K, double *us = nullptr) {
   return best;
 }
 
+// ---- order of the tiles of a product ---------------------------------------------------------------------------------------
+// Each XCD gets a contiguous range of tiles, taken down panels of `panel` columns of tiles.  Its L2 has to bring in the rows of both
+// operands that its range touches (the first 32 tiles of it, one per CU): the panel width that makes the fewest of them.
+// Row by row -> in panels, us (rows x columns x contraction): 300 x 1536 x 2048 18.0 -> 15.0, 300 x 2048 x 1024 13.1 -> 10.8, 300 x 3072
+// x 4096 32.8 -> 27.4 (64 x 64 tiles), 1000 x 2048 x 1024 16.7 -> 15.1 (64 x 128), 1000 x 4096 x 2048 34.8 -> 33.7, 12000 x 4096 x 2048
+// 209 -> 200 (256 x 256).  Tiles 128 columns wide and as high lost 1 ... 4 % where the panels save less than half of the rows (1531 x 1536
+// x 2048 27.1 -> 27.8) and keep the row order there.
+inline int tile_panel(int tiles_m, int tiles_n, int tm, int tn) {
+  const long long tiles = (long long)tiles_m * tiles_n, range = (tiles + 7) / 8, at_once = range < 32 ? range : 32;
+  int best = tiles_n;
+  long long least = -1, row_major = 0;
+  for (int panels = 1; panels <= tiles_n; ++panels) {
+    const int w = (tiles_n + panels - 1) / panels;
+    if (w == best && panels > 1) continue;
+    const long long full = (long long)w * tiles_m;
+    long long cost = 0;
+    for (int x = 0; x < 8; ++x) {
+      const long long a = x * range, b = a + at_once < tiles ? a + at_once : tiles;
+      long long rows = 0, cols = 0;
+      for (long long p = a / full; p * full < b && a < b; ++p) {
+        const long long lo = a > p * full ? a - p * full : 0, hi = b < (p + 1) * full ? b - p * full : full;
+        const long long width = p * w + w < tiles_n ? w : tiles_n - p * w;
+        rows += (hi - 1) / width - lo / width + 1;
+        cols += hi - lo < width ? hi - lo : width;
+      }
+      cost += (rows < tiles_m ? rows : tiles_m) * tm + cols * tn;
+    }
+    if (panels == 1) row_major = cost;
+    if (least < 0 || cost < least) least = cost, best = w;
+    if (w == 1) break;
+  }
+  return tn == 128 && tm >= 128 && 2 * least > row_major ? tiles_n : best;
+}
+
 // ---- weight gradients: C (Mo,No) = A (K,Mo)^T * B (K,No), bf16, K tokens -------------------------------------------------
 enum TnTile { TN_SPLIT, TN_64x64, TN_64x128, TN_128x128 };
 

@@ -13,6 +13,18 @@ def test_projection_cases_reach_every_tile():
     assert reached == set(rules.NT_TILES)
 
 
+def test_projection_cases_reach_every_order_of_tiles():
+    orders = set()
+    for M, Hq, Hk, dh, E in small.GEMM_CASES:
+        for N, K in (((Hq + 2 * Hk) * dh, E), (E, Hq * dh)):
+            tm, tn = (int(x) for x in rules.nt_tile(M, N, K).split("x"))
+            tiles_n = -(-N // tn)
+            panel = rules.tile_panel(-(-M // tm), tiles_n, tm, tn)
+            assert 1 <= panel <= tiles_n
+            orders.add((tm <= 64, "rows" if panel == tiles_n else "whole panels" if tiles_n % panel == 0 else "a narrower one"))
+    assert {(False, "rows")} | {(small_tile, o) for small_tile in (True, False) for o in ("whole panels", "a narrower one")} <= orders
+
+
 def test_weight_gradient_cases_reach_every_tile():
     forms = {(r, Hq, dh, E): rules.tn_tile(Hq * dh, E, r) for r, Hq, dh, E in small.WGRAD_CASES}
     assert set(forms.values()) == set(rules.TN_TILES)
