@@ -935,8 +935,73 @@ struct RowDest {
 
 // (a body inlined with restrict arguments: without them the compiler makes the transposing LDS reads of a later pass wait
 // for loads into LDS that they do not touch)
+// COMBINE: A is not in memory yet, its rows are the sums over the splits of the attention (`cmb`, as decode_combine_kernel forms them),
+// made here while the panel of W is on its way; one pass over all of K, B * H_q d_h <= 4 PN_NT, d_h >= 64, at most COMBINE_SPLITS splits.
+constexpr int COMBINE_SPLITS = 8;
+struct CombineArgs {
+  DecArgs a;
+  const float *part;
+  int nsplit, per;
+};
+// Rows of A into LDS: a thread per four channels, the values of all splits requested with the states, before the length of the
+// sequence is known
+__device__ __forceinline__ void combine_rows(const CombineArgs &c, int M, int K, int kp, unsigned char *sA) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  __shared__ float f[4 * PN_NT / 64 * COMBINE_SPLITS];  // 2^(m_s - M) / L of every row, head and split (0 beyond the sequence's last); d_h >= 64 here
+  const int tid = threadIdx.x, dh = c.a.dh, Hq = c.a.Hq, stride = 2 + dh, per_row = K / 4;
+  const int item = min(tid, M * per_row - 1), row = item / per_row, k = item % per_row * 4, head = k / dh;
+  const float *const mine = c.part + (long long)(row * Hq + head) * c.nsplit * stride + 2 + k % dh;  // (8-byte aligned: dh is even)
+  f2 lo[COMBINE_SPLITS], hi[COMBINE_SPLITS];
+#pragma unroll
+  for (int s0 = 0; s0 < COMBINE_SPLITS; s0 += 4)
+    if (s0 < c.nsplit) {
+#pragma unroll
+      for (int s = s0; s < s0 + 4; ++s) {
+        const f2 *const at = reinterpret_cast<const f2 *>(mine + min(s, c.nsplit - 1) * stride);
+        lo[s] = at[0], hi[s] = at[1];
+      }
+    }
+  // the factors: COMBINE_SPLITS lanes per row and head, lane = split
+  for (int bh0 = 0; bh0 < M * Hq; bh0 += PN_NT / COMBINE_SPLITS) {
+    const int bh = min(bh0 + tid / COMBINE_SPLITS, M * Hq - 1), s = tid % COMBINE_SPLITS;
+    const f2 state = *reinterpret_cast<const f2 *>(c.part + ((long long)bh * c.nsplit + min(s, c.nsplit - 1)) * stride);
+    const int len = seq_pos(c.a, bh / Hq) + 1, n = min(c.nsplit, (len + c.per - 1) / c.per);
+    const float ms = s < n ? state.x : -INFINITY, ls = s < n ? state.y : 0.f;
+    float m = ms;
+#pragma unroll
+    for (int off = COMBINE_SPLITS / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    const float w = ms == -INFINITY ? 0.f : exp2f(ms - m);
+    float l = 0.f;
+#pragma unroll
+    for (int x = 0; x < COMBINE_SPLITS; ++x) {  // index order; past the last split nothing
+      const float lx = __shfl(ls * w, (tid & 63) / COMBINE_SPLITS * COMBINE_SPLITS + x);
+      l = x < n ? l + lx : l;
+    }
+    f[bh * COMBINE_SPLITS + s] = s < n ? w / l : 0.f;
+  }
+  __syncthreads();
+  const int len = seq_pos(c.a, row) + 1, n = min(c.nsplit, (len + c.per - 1) / c.per);
+  f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < COMBINE_SPLITS; ++s)
+    if (s < n) {
+      const float w = f[(row * Hq + head) * COMBINE_SPLITS + s];
+      acc.x = fmaf(lo[s].x, w, acc.x), acc.y = fmaf(lo[s].y, w, acc.y);
+      acc.z = fmaf(hi[s].x, w, acc.z), acc.w = fmaf(hi[s].y, w, acc.w);
+    }
+  unsigned char *const at = sA + row * (kp * 2);
+  if (tid < M * per_row) {
+    const uint32_t p[2] = {(uint32_t)f32_to_bf16(acc.x) | (uint32_t)f32_to_bf16(acc.y) << 16, (uint32_t)f32_to_bf16(acc.z) | (uint32_t)f32_to_bf16(acc.w) << 16};
+    uint32_t *const to = reinterpret_cast<uint32_t *>(at + (((k / 8) ^ (row & 15)) * 16) + (k & 4) * 2);
+    to[0] = p[0], to[1] = p[1];
+  }
+}
+
+template <bool COMBINE>
 __device__ __forceinline__ void gemm_panel_body(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, bf16_t *__restrict__ C,
-                                                RowDest dest, int M, int N, int K, int kp, int k_slice, float *__restrict__ part, unsigned char *smem) {
+                                                RowDest dest, int M, int N, int K, int kp, int k_slice, float *__restrict__ part,
+                                                const CombineArgs &cmb, unsigned char *smem) {
   typedef __attribute__((address_space(3))) void lds_void;
   typedef __attribute__((address_space(1))) void glb_void;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
@@ -963,7 +1028,8 @@ __device__ __forceinline__ void gemm_panel_body(const bf16_t *__restrict__ A, co
         else
           *reinterpret_cast<sk_u32x4 *>(smem + g * 1024 + lane * 16) = sk_u32x4{0, 0, 0, 0};
       }
-      for (int i = wave; i < (mrows * cpr + 63) / 64; i += PN_WAVES) {
+      if constexpr (COMBINE) combine_rows(cmb, M, K, kp, sA);
+      else for (int i = wave; i < (mrows * cpr + 63) / 64; i += PN_WAVES) {
         const int pos = i * 64 + lane, r = pos / cpr, p = pos % cpr, k = (p ^ (r & 15)) * 8;
         if (r < mrows) {
           if (k < rows)
@@ -1011,7 +1077,14 @@ __global__ __launch_bounds__(PN_NT) void gemm_panel_kernel(const bf16_t *__restr
                                                           bf16_t *__restrict__ C, RowDest dest, int M, int N, int K, int kp,
                                                           int k_slice, float *__restrict__ part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char psm[];
-  gemm_panel_body(A, W, C, dest, M, N, K, kp, k_slice, part, psm);
+  gemm_panel_body<false>(A, W, C, dest, M, N, K, kp, k_slice, part, CombineArgs{}, psm);
+}
+
+// The up-projection of a few rows whose attention ran in a few splits: the launch that combines them saved (figures: decode_up_combines)
+__global__ __launch_bounds__(PN_NT) void gemm_panel_combine_kernel(CombineArgs cmb, const bf16_t *__restrict__ W, bf16_t *__restrict__ C, RowDest dest,
+                                                                  int M, int N, int K, int kp) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char psm[];
+  gemm_panel_body<true>(nullptr, W, C, dest, M, N, K, kp, K, nullptr, cmb, psm);
 }
 
 template <typename T>
@@ -1051,6 +1124,14 @@ hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest,
   const size_t pass = (size_t)kp * (PN_COLS * 2 + 2 * (M < 32 ? M : 32)), lds = pass > PN_SUMS ? pass : PN_SUMS;
   gemm_panel_kernel<<<dim3((N + PN_COLS - 1) / PN_COLS, slices, row_blocks < 4096 ? row_blocks : 4096), PN_NT, lds, s>>>(A, W, C, dest, M, N, K, kp, k_slice,
                                                                                  part);
+  return hipGetLastError();
+}
+
+hipError_t up_combined(const DecArgs &a, const float *attn, int nsplit, int per, const bf16_t *W, bf16_t *out, int N, int K, hipStream_t s) {
+  if (hipError_t e = raise_lds_limit<gemm_panel_combine_kernel>(PN_LDS - 32 * 1024); e != hipSuccess) return e;
+  const int kp = (K + 127) / 128 * 128;
+  const size_t pass = (size_t)kp * (PN_COLS * 2 + 2 * a.B), lds = pass > PN_SUMS ? pass : PN_SUMS;
+  gemm_panel_combine_kernel<<<(N + PN_COLS - 1) / PN_COLS, PN_NT, lds, s>>>(CombineArgs{a, attn, nsplit, per}, W, out, RowDest{N, nullptr, 0, 1}, a.B, N, K, kp);
   return hipGetLastError();
 }
 
@@ -1190,6 +1271,8 @@ hipError_t step_t(const Dims &d, const cca_weights &w, const void *x_new, void *
 #undef CCA_DEC_ROWS
           if ((e = hipGetLastError()) != hipSuccess) return e;
         }
+        if constexpr (std::is_same<T, bf16_t>::value)
+          if (decode_up_combines(d.B, d.e_q, nsplit, COMBINE_SPLITS)) return up_combined(a, part, nsplit, per, (const bf16_t *)w.w_out, (bf16_t *)out, d.E, d.e_q, s);
         decode_combine_kernel<T><<<(unsigned)(d.B * d.Hq), (d.dh + 63) / 64 * 64, 0, s>>>(a, part, nsplit, per, o);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         return gemm_skinny<T>(o, (const T *)w.w_out, (T *)out, RowDest{d.E, nullptr, 0, 1}, gpart, d.B, d.E, d.e_q, s);

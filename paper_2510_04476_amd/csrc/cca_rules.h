@@ -307,4 +307,10 @@ inline int decode_keys_per_split(long long groups, int len, int dh, bool rows_ke
   return even > least ? even : least;
 }
 
+// Decode: the up-projection combines the splits of the attention itself?  Every one of its workgroups then reads all of them, a thread
+// per four channels (2048 channels at most), which by 16 splits costs what the launch did.  Step with the launch, without, us (sequences x
+// tokens): E = 2048, 8 / 2 heads of 128: 1 x 200 22.1, 21.4; 1 x 1000 (8 splits) 22.5, 22.2; 2 x 500 22.5, 21.8; 1 x 2000 (16) 23.1, 22.9;
+// 2 x 2000 24.0, 24.0; 4 / 4 of 64, 8 x 1000 18.8, 18.1; 8 x 4000 (16) 22.4, 22.8; 4 / 1 of 256, 1 x 4000 29.8, 30.2.
+inline bool decode_up_combines(long long B, int e_q, int nsplit, int max_splits) { return B * e_q <= 2048 && nsplit <= max_splits; }
+
 }  // namespace cca

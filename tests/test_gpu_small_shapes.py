@@ -662,3 +662,35 @@ def test_decode_ragged_leaves_empty_splits_alone(Hq, Hk, dh):
         ref = P.cca_decode_step(one, w, x[b:b + 1], state(one, slice(b, b + 1)), p).double()
         assert bool(ref.isfinite().all())
         assert float((out[b].double() - ref[0]).norm()) <= 2.0 ** -7 * float(ref.norm()), (b, p)
+
+
+@pytest.mark.parametrize("B,Hq,Hk,dh,E,last", [(8, 4, 4, 64, 512, 1999), (32, 1, 1, 64, 72, 599), (8, 2, 1, 128, 256, 1023), (2, 4, 1, 256, 1032, 511),
+                                                (1, 8, 2, 128, 1024, 900), (1, 16, 2, 128, 2056, 127)])
+def test_up_projection_combines_the_splits(B, Hq, Hk, dh, E, last):
+    """Up to 2048 channels and eight splits the up-projection adds the splits itself, over a workspace full of NaN: bit for bit the rows
+    of a step with one sequence (and so a launch) more, whose keys are split the same way."""
+    say("combine", B, Hq, Hk, dh, E, last)
+    per = [rules.decode_keys_per_split(n * Hk, last + 1, dh, True) for n in (B, 2 * B + 1)]
+    splits = -(-(last + 1) // per[0])
+    assert rules.decode_up_combines(B, Hq * dh, splits) and not rules.decode_up_combines(2 * B + 1, Hq * dh, splits) and per[0] == per[1]
+    T, C = last + 1, 2 * B + 1
+    cfg = lambda n: P.CCAConfig(B=n, T=T, d_model=E, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh)
+    c = cfg(C)
+    w = P.CCAWeights(w_down=rnd(E, c.n_lat, seed=1, scale=0.02), w_out=rnd(c.e_q, E, seed=2, scale=0.05),
+                     w_conv_seq=rnd(c.e_q + c.e_kv, 2, seed=3), w_conv_ch=rnd(Hq + Hk, dh, dh, 2, seed=4, scale=(2 * dh) ** -0.5),
+                     temp=rnd(Hk, seed=5, dtype=torch.float32))
+    x = rnd(C, E, seed=6)
+    edges = [last, 0, per[0] - 1, per[0], last // 2, 1, last - 1, 2 * per[0]]
+    pos = [min(edges[b % 8], last) for b in range(C)]
+
+    def step(n):
+        s = P.CCADecodeState.allocate(cfg(n), "cuda")
+        s.k_cache.copy_(rnd(C, T, Hk, dh, seed=7).reshape(C, *s.k_cache.shape[1:])[:n])
+        s.v_cache.copy_(rnd(C, T, Hk, dh, seed=8).reshape(C, *s.v_cache.shape[1:])[:n])
+        s.lat_ring.copy_(rnd(*((C,) + tuple(s.lat_ring.shape[1:])), seed=9)[:n])
+        s.workspace.fill_(255)
+        return P.cca_decode_step_ragged(cfg(n), w, x[:n], s, torch.tensor(pos[:n], dtype=torch.int32, device="cuda"), last)
+
+    few, more = step(B), step(C)
+    torch.cuda.synchronize()
+    assert bool(few.isfinite().all()) and torch.equal(few, more[:B])
