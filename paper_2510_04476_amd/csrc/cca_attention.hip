@@ -251,7 +251,7 @@ __device__ __forceinline__ void single_row(const bf16_t *__restrict__ Q, const b
 // of every row: no row max, no rescaling, and exp2 arguments lie in [-2*bound, 0].
 // NTH threads = NTH / 64 wavefronts x 32 rows = BQ_ query rows per workgroup: 512 threads (256 rows, two wavefronts
 // per SIMD) for d_h <= 128, 256 threads (128 rows, one wavefront per SIMD and twice the registers) for d_h = 256.
-// KS = 2: two groups of NTH / 2 threads share the rows of one group (BQ_ = 128 at 512 threads); group kg takes the key
+// KS = 2: two groups of NTH / 2 threads share the rows of one group (BQ_ = 128 at 512 threads, 64 at 256: fwd_takes_64_rows); group kg takes the key
 // tiles 2 j + kg through LDS buffers of its own, and the two partial results of a row are merged at the end.
 template <int DH, bool CAUSAL, bool BOUNDED, bool RSUM, int NTH = NT, int KS = 1>
 __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
@@ -508,7 +508,7 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
 constexpr int PF = 3;  // operand fetches run this many MFMAs ahead
 enum { IT_PRO = 0, IT_FULL = 1, IT_FINAL = 2, IT_IDLE = 3 };
 
-template <int DH, bool CAUSAL, bool RSUM, int KS>
+template <int DH, bool CAUSAL, bool RSUM, int KS, int NTH>
 __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                    const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
                                                    bf16_t *__restrict__ OLO, float *__restrict__ LSE, int T, int Hq,
@@ -516,7 +516,7 @@ __device__ __forceinline__ void attn_fwd_pipelined(const bf16_t *__restrict__ Q,
                                                    unsigned char *smem) {
   constexpr int KK = DH / 16, DT = DH / 32, KCH = DH / 8;
   constexpr int KROW = DH * 2 + 16, KBUF = BKV * KROW, VROW = DH * 2 + 64, VBUF = BKV * VROW;
-  constexpr int NTG = NT / KS, K_PER_THREAD = BKV * KCH / NTG, K_ROWS_PER_PASS = NTG / KCH, BQ_ = NTG / 64 * 32;
+  constexpr int NTG = NTH / KS, K_PER_THREAD = BKV * KCH / NTG, K_ROWS_PER_PASS = NTG / KCH, BQ_ = NTG / 64 * 32;
   constexpr int NB = KK;  // MFMAs per (half-tile score | half-tile PV) block; 2 * DT == KK
   static_assert(2 * DT == KK, "block sizes");
   const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTG);  // key group (see attn_fwd_body)
@@ -1120,8 +1120,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // RSUM: the row sum adds the bf16-rounded probabilities, so that o is the exact convex combination the PV
 // product formed; chosen when the caller saves lse / o_lo for a backward pass (see the file header).
 // KS: key groups per workgroup (attn_fwd_body)
-template <int DH, bool CAUSAL, bool RSUM, int KS>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(
+template <int DH, bool CAUSAL, bool RSUM, int KS, int NTH>
+__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NTH / 256, NTH / 256))) void attn_fwd_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
     bf16_t *__restrict__ OLO, float *__restrict__ LSE, const float *__restrict__ temp, int qk_normed, int T, int Hq, int Hk, int BH, int nqb,
     int paired, float scale, RowNorms norms) {
@@ -1139,16 +1139,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   }
   // exp2 arguments reach -2*bound: keep them inside the fp32 exponent range
   if (bound <= 60.f)
-    attn_fwd_pipelined<DH, CAUSAL, RSUM, KS>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, bound, smem);
+    attn_fwd_pipelined<DH, CAUSAL, RSUM, KS, NTH>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, bound, smem);
   else
-    attn_fwd_body<DH, CAUSAL, false, RSUM, NT, KS>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, 0.f, smem);
+    attn_fwd_body<DH, CAUSAL, false, RSUM, NTH, KS>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, 0.f, smem);
 }
 
-template <int DH, int KS>
+template <int DH, int KS, int NTH>
 hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo, float *lse,
                   const float *temp, float *norms_, hipStream_t s) {
   constexpr bool WIDE = DH > 128;             // one wavefront per SIMD, 128-row query blocks
-  constexpr int BQL = WIDE ? 128 : BQ / KS;
+  constexpr int BQL = WIDE ? 128 : NTH / 2 / KS;
   const int nqb = row_blocks(d.T, BQL);
   const int BH = d.B * d.Hq;
   const bool causal = d.flags & CCA_CAUSAL;
@@ -1171,7 +1171,7 @@ hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, vo
                                                                     temp, qk_normed, d.T, d.Hq, d.Hk, BH, nqb, paired,  \
                                                                     d.scale, norms);                                   \
   else                                                                                                                 \
-    attn_fwd_kernel<DH, C, R, KS><<<(unsigned)blocks, NT, 0, s>>>((const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,  \
+    attn_fwd_kernel<DH, C, R, KS, NTH><<<(unsigned)blocks, NTH, 0, s>>>((const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,  \
                                                               (bf16_t *)o, (bf16_t *)o_lo, lse, temp, qk_normed, d.T,   \
                                                               d.Hq, d.Hk, BH, nqb, paired, d.scale, norms)
   if (causal) {
@@ -1196,10 +1196,14 @@ size_t attention_norms_bytes(const Dims &d) { return (size_t)d.B * (d.Hq + d.Hk)
 
 hipError_t attention_mfma_bf16(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo,
                                float *lse, const float *temp, float *norms, hipStream_t s) {
-  const bool halves = d.dh <= 128 && fwd_splits_keys((long long)d.B * d.Hq, d.T, d.flags & CCA_CAUSAL);
-  return d.dh == 256   ? launch<256, 1>(d, q, k, v, o, o_lo, lse, temp, norms, s)
-         : d.dh == 128 ? (halves ? launch<128, 2>(d, q, k, v, o, o_lo, lse, temp, norms, s) : launch<128, 1>(d, q, k, v, o, o_lo, lse, temp, norms, s))
-                       : (halves ? launch<64, 2>(d, q, k, v, o, o_lo, lse, temp, norms, s) : launch<64, 1>(d, q, k, v, o, o_lo, lse, temp, norms, s));
+  const long long BH = (long long)d.B * d.Hq;
+  const bool causal = d.flags & CCA_CAUSAL;
+#define ARGS d, q, k, v, o, o_lo, lse, temp, norms, s
+  if (d.dh == 256) return launch<256, 1, 256>(ARGS);
+  if (!fwd_splits_keys(BH, d.T, causal)) return d.dh == 128 ? launch<128, 1, 512>(ARGS) : launch<64, 1, 512>(ARGS);
+  if (fwd_takes_64_rows(BH, d.T, d.flags & CCA_QK_NORM)) return d.dh == 128 ? launch<128, 2, 256>(ARGS) : launch<64, 2, 256>(ARGS);
+  return d.dh == 128 ? launch<128, 2, 512>(ARGS) : launch<64, 2, 512>(ARGS);
+#undef ARGS
 }
 
 }  // namespace cca

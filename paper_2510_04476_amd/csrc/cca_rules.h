@@ -209,6 +209,12 @@ inline bool split_pays(long long BH, int T, bool causal, bool pairs, const Split
 inline bool fwd_splits_keys(long long BH, int T, bool causal) {
   return split_pays(BH, T, causal, true, SplitCost{3.0, 1.04, 1.0, 0.2});
 }
+// Two key groups: blocks of 64 rows (256 threads, one wavefront per SIMD) where they still are one round of the grid, or of 128?  A
+// step over a key tile is then shorter by what two wavefronts of a SIMD cost each other (us, 128 rows -> 64; B * H_q, d_h): T = 400, 8,
+// 128: 13.4 -> 12.0; 512, 8, 128: 15.0 -> 13.5; 512, 24, 64: 10.1 -> 9.0; 777, 8, 128: 17.7 -> 16.7; 1024, 16, 64: 13.5 -> 12.5; 1280,
+// 4, 64: 15.2 -> 14.1; 1531, 8, 128: 25.8 -> 25.6; 2048, 8: 31.5 -> 31.6; beyond a round 777, 24, 64: 12.1 -> 12.7, not causal 13.0 ->
+// 22.9; without a bound on the scores 512, 16, 64: 9.9 -> 9.8, 777: 12.1 -> 13.0.
+inline bool fwd_takes_64_rows(long long BH, int T, bool normed) { return normed && T <= 1536 && BH * ((T + 63) / 64) <= 256; }
 // Scores without a bound by the QK norm: a pass over the rows for their lengths first, so that the form that needs no running
 // maximum can run?  The pass costs 3.5 ... 4 us; the gain follows the pairs of a query and a key, except at heads wider than 128,
 // where the other form is a third slower for each key and the longest chain of keys decides.  Whole prefill (us, without ->

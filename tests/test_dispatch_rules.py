@@ -53,6 +53,10 @@ def test_attention_cases_reach_both_block_orders():
     assert paired == {(True, True), (True, False), (False, False)}
 
 
+def test_attention_cases_reach_both_block_heights():
+    assert {rules.fwd_takes_64_rows(B * Hq, T, normed) for B, T, Hq, Hk, dh, causal, normed in small.SPLIT_CASES} == {True, False}
+
+
 def test_wide_head_prologue_cases_reach_both_forms():
     reached = set()
     for B, T, Hq, Hk, k_seq, k_ch in small.STREAM_CASES:

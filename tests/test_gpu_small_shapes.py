@@ -124,7 +124,10 @@ def test_projection_adjoints_in_one_launch(rows, Hq, Hk, dh, E):
 SPLIT_CASES = [(1, 300, 2, 1, 128, True, True), (1, 321, 3, 3, 64, True, False), (2, 385, 2, 2, 128, False, True),
                (1, 449, 4, 2, 128, False, False), (1, 1000, 4, 2, 64, True, True), (3, 1531, 8, 8, 64, True, True),
                (1, 2047, 16, 16, 128, True, False), (1, 4096, 16, 16, 64, True, False), (2, 513, 4, 1, 128, True, False),
-               (1, 4097, 8, 2, 128, True, True)]
+               (1, 4097, 8, 2, 128, True, True),
+               # blocks of 64 rows up to their edges: the longest sequence, one round of the grid exactly, and one block more
+               (1, 1536, 8, 2, 64, True, True), (1, 513, 28, 7, 128, False, True), (1, 449, 32, 8, 64, True, True),
+               (1, 513, 29, 29, 64, False, True)]
 
 
 @pytest.mark.parametrize("B,T,Hq,Hk,dh,causal,normed", SPLIT_CASES)
@@ -214,17 +217,19 @@ def test_attention_with_measured_bound(B, T, Hq, Hk, dh, causal, longest):
             assert float((saved.lse[b, h].double() - torch.logsumexp(s, -1)).abs().max()) <= 2.0 ** -8 * (s_max + 1.0) + 1e-3
 
 
-def check_masked_keys(dh, causal, live, masked):
+def check_masked_keys(dh, causal, live, masked, hot=False):
     """Keys outside `live` (a mask over T) score `masked` times a positive number, through a channel of k at that value that every q
     reads with a positive weight: the rows that see a live key are those of attention over the live keys alone, with the
     roundings of the test above."""
     T, Hq = live.numel(), 2
     assert rules.fwd_splits_keys(Hq, T, causal)
-    cfg = P.CCAConfig(B=1, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, flags=P.CCA_CAUSAL if causal else 0)
+    # hot: normalised heads, whose temperature leaves the scores without a usable bound
+    flags = (P.CCA_CAUSAL if causal else 0) | (P.CCA_QK_NORM | P.CCA_KEY_TEMP if hot else 0)
+    cfg = P.CCAConfig(B=1, T=T, d_model=Hq * dh, n_q_heads=Hq, n_kv_heads=Hq, head_dim=dh, flags=flags)
     q, k, v = rnd(1, T, Hq, dh, seed=1), rnd(1, T, Hq, dh, seed=2), rnd(1, T, Hq, dh, seed=3)
     q[..., 5] = 1.0
     k[:, ~live, :, 5] = masked
-    o, lse = P.cca_attention(cfg, q, k, v, want_lse=True)
+    o, lse = P.cca_attention(cfg, q, k, v, want_lse=True, temp=torch.full((Hq,), 9.0, device="cuda") if hot else None)
     torch.cuda.synchronize()
     first = int(live.nonzero()[0]) if causal else 0
     for h in range(Hq):
@@ -250,6 +255,17 @@ def test_attention_keys_masked_by_infinite_scores(dh, causal, live, masked):
     say("infinite scores", dh, causal, live, masked)
     t = torch.arange(300, device="cuda")
     check_masked_keys(dh, causal, (t >= live[0]) & (t < live[1]), masked)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("masked", [float("-inf"), -2e4, -1e38])
+def test_attention_on_64_rows_without_a_bound(dh, causal, masked):
+    """The same in blocks of 64 rows, which only normalised heads take."""
+    say("64 rows", dh, causal, masked)
+    assert rules.fwd_takes_64_rows(2, 300, True)
+    t = torch.arange(300, device="cuda")
+    check_masked_keys(dh, causal, (t >= 129) & (t < 290), masked, hot=True)
 
 
 @pytest.mark.parametrize("gap", [(0, 64), (64, 128), (0, 300)])
