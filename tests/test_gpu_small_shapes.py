@@ -173,7 +173,7 @@ def test_attention_with_split_keys(B, T, Hq, Hk, dh, causal, normed):
 # B, T, H_q, H_k, d_h, causal: the shortest sequence at wide heads, last chunks of one token, the two narrower heads with one and two
 # key groups; the longest row of a head last in its chunk, and in the last one
 BOUND_CASES = [(2, 128, 2, 1, 256, True), (1, 257, 3, 3, 256, False), (1, 2049, 2, 1, 256, True), (1, 4481, 8, 2, 128, True),
-               (1, 2817, 8, 8, 128, False), (1, 3585, 16, 4, 64, True), (26, 1984, 1, 1, 64, False), (30, 1600, 1, 1, 128, False)]
+               (1, 4097, 2, 2, 128, False), (1, 4609, 16, 4, 64, True), (26, 1984, 1, 1, 64, False), (24, 4096, 1, 1, 128, False)]
 
 
 @pytest.mark.parametrize("longest", [2.0, 40.0, float("inf"), float("nan")])
