@@ -3,7 +3,7 @@
 // block):  C (M,N) = A (M,K) * Bt (N,K)^T, fp32 accumulation, bf16 output.
 //
 // Both operands are K-contiguous, so a lane's 8-element MFMA fragment is one
-// 16-byte LDS read.  Workgroup tile 256 x BN x 64 with 8 wavefronts; LDS is
+// 16-byte LDS read.  Workgroup tile TM x BN x 64 with 8 wavefronts; LDS is
 // XOR-swizzled per 16-byte chunk; K-slabs travel HBM -> LDS directly
 // (global_load_lds, no staging registers, no ds_write), A two slabs ahead and the
 // weight one, the loads spread over a slab's 16-wide MFMA steps so that the LDS
