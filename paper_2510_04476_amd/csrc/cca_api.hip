@@ -146,8 +146,8 @@ static cca_status run_prologue(const Dims &d, const cca_weights *w, const void *
 }
 
 static cca_status run_attention(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo,
-                                float *lse, const float *temp, hipStream_t s, float *norms = nullptr) {
-  hipError_t e = attention_mfma_supported(d) ? attention_mfma_bf16(d, q, k, v, o, o_lo, lse, temp, norms, s)
+                                float *lse, const float *temp, hipStream_t s) {
+  hipError_t e = attention_mfma_supported(d) ? attention_mfma_bf16(d, q, k, v, o, o_lo, lse, temp, s)
                                              : attention_generic(d, q, k, v, o, o_lo, lse, s);
   return e == hipSuccess ? CCA_OK : CCA_ERR_LAUNCH;
 }
@@ -506,9 +506,7 @@ cca_status cca_forward(const cca_config *cfg, const cca_weights *w, const void *
     st = run_prologue(d, w, lat, q, k, v, rnorm, pre + L.pro, L.lat - L.pro, s, true);
     if (st != CCA_OK) return st;
   }
-  // (the workspace's latent rows are no longer read: room for the lengths of the rows, where there is as much)
-  float *const norms = L.q - L.lat >= attention_norms_bytes(d) ? reinterpret_cast<float *>(ws + L.lat) : nullptr;
-  st = run_attention(d, q, k, v, o, o_lo, lse, w->temp, s, norms);
+  st = run_attention(d, q, k, v, o, o_lo, lse, w->temp, s);
   if (st != CCA_OK) return st;
   return project(d, o, w->w_out, out, d.rows(), d.E, d.e_q, pre + L.wt_out, (size_t)d.E * d.e_q * 2, s, true);
 }

@@ -1036,80 +1036,18 @@ __device__ __forceinline__ void attn_fwd_pipelined_wide(const bf16_t *__restrict
   }
 }
 
-// The bound that Cauchy and Schwarz give on one head's scores (log2 units): the longest query row times the longest key row, from the
-// squared lengths that row_norms_kernel left per chunk of tokens; 1 % head-room for the rounding of scaled q to bf16.  Not a number or
-// infinite where a row is.
-struct RowNorms {
-  const float *sq;  // (B, H_q + H_k, chunks) largest squared length in each chunk, or NULL
-  int chunks;       // <= 32
-};
-constexpr int NORM_CHUNKS = 32;
-// A measured bound leaves the scores of a row anywhere in [-bound, bound]: at the low end its probabilities are 2^(-2 bound) and
-// must keep their fp32 precision and the sum of a million that are 2^-10 of the largest.
-constexpr float MEASURED_BOUND = 48.f;
-__device__ __forceinline__ float measured_bound(const RowNorms &n, int b, int h, int g, int Hq, int Hk, float scale) {
-  const int lane = threadIdx.x & 63;
-  const long long head = (long long)b * (Hq + Hk) + (lane < 32 ? h : Hq + g);
-  float m = n.sq[head * n.chunks + min(lane & 31, n.chunks - 1)];
-  // as integers: of non-negative floats the order is the same, and a NaN is above them all
-#pragma unroll
-  for (int d = 1; d < 32; d *= 2) m = __int_as_float(max(__float_as_int(m), __float_as_int(__shfl_xor(m, d))));
-  const float other = __shfl_xor(m, 32);
-  return 1.01f * sqrtf(m) * sqrtf(other) * fabsf(scale) * 1.44269504088896340736f;
-}
-
-// The largest squared length of a head's rows in each chunk of tokens.  Workgroup = (chunk, query or KV head, batch item); d_h / 8 lanes
-// to a row.  A wavefront's score pass then needs no row maximum (attn_fwd_pipelined), which pays for the rows read once more from
-// some size on (fwd_measures_bound).
-template <int DH>
-__global__ __launch_bounds__(256) void row_norms_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, float *__restrict__ sq,
-                                                        int T, int Hq, int Hk, int per) {
-  constexpr int LPR = DH / 8, ROWS = 256 / LPR, U = 4;
-  __shared__ int most[4];
-  const int head = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, heads = head < Hq ? Hq : Hk;
-  const bf16_t *const base = (head < Hq ? Q + ((long long)b * T * Hq + head) * DH : K + ((long long)b * T * Hk + head - Hq) * DH);
-  const int t_end = min(T, ((int)blockIdx.x + 1) * per);
-  int m = 0;
-  for (int t0 = blockIdx.x * per + tid / LPR; t0 < t_end; t0 += ROWS * U) {
-    u32x4 w[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u)  // rows past the chunk repeat its last one
-      w[u] = *reinterpret_cast<const u32x4 *>(base + (long long)min(t0 + u * ROWS, t_end - 1) * heads * DH + tid % LPR * 8);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s += bf_lo(w[u][i]) * bf_lo(w[u][i]) + bf_hi(w[u][i]) * bf_hi(w[u][i]);
-#pragma unroll
-      for (int d = 1; d < LPR; d *= 2) s += __shfl_xor(s, d);
-      m = max(m, __float_as_int(s) & 0x7fffffff);  // (a NaN of either sign is the largest)
-    }
-  }
-#pragma unroll
-  for (int d = LPR; d < 64; d *= 2) m = max(m, __shfl_xor(m, d));
-  if ((tid & 63) == 0) most[tid >> 6] = m;
-  __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < 4; ++w) m = max(m, most[w]);
-    sq[((long long)b * (Hq + Hk) + head) * gridDim.x + blockIdx.x] = __int_as_float(m);
-  }
-}
-
 // d_h = 256: 256 threads, one wavefront per SIMD, 128 query rows per workgroup.
 template <int DH, bool CAUSAL, bool RSUM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_fwd_wide_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
     bf16_t *__restrict__ OLO, float *__restrict__ LSE, const float *__restrict__ temp, int qk_normed, int T, int Hq,
-    int Hk, int BH, int nqb, int paired, float scale, RowNorms norms) {
+    int Hk, int BH, int nqb, int paired, float scale) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BKV * (DH * 2 + 16) + 2 * BKV * (DH * 2 + 64)];
   float bound = INFINITY;
   if (qk_normed) {  // |q.k| <= d_h * beta; 2 % head-room for the bf16 rounding of the stored q and k
     const int g = ((int)blockIdx.x % BH % Hq) / (Hq / Hk);
     const float beta = temp ? expf(temp[g]) : 1.f;
     bound = 1.02f * (float)DH * beta * scale * 1.44269504088896340736f;
-  } else if (norms.sq) {
-    const int bh = (int)blockIdx.x % BH, h = bh % Hq;
-    bound = measured_bound(norms, bh / Hq, h, h / (Hq / Hk), Hq, Hk, scale);  // (this form takes no reference: |score| <= 60 will do)
   }
   if (bound <= 60.f)
     attn_fwd_pipelined_wide<DH, CAUSAL, RSUM, 1>(Q, K, V, O, OLO, LSE, T, Hq, Hk, BH, nqb, paired, scale, smem);
@@ -1124,7 +1062,7 @@ template <int DH, bool CAUSAL, bool RSUM, int KS, int NTH>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NTH / 256, NTH / 256))) void attn_fwd_kernel(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K, const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
     bf16_t *__restrict__ OLO, float *__restrict__ LSE, const float *__restrict__ temp, int qk_normed, int T, int Hq, int Hk, int BH, int nqb,
-    int paired, float scale, RowNorms norms) {
+    int paired, float scale) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[KS * 2 * BKV * (DH * 2 + 16 + DH * 2 + 64)];
   float bound = INFINITY;
   if (qk_normed) {
@@ -1132,10 +1070,6 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NTH / 256, 
     const int g = ((int)blockIdx.x % BH % Hq) / (Hq / Hk);
     const float beta = temp ? expf(temp[g]) : 1.f;
     bound = 1.02f * (float)DH * beta * scale * 1.44269504088896340736f;
-  } else if (norms.sq) {
-    const int bh = (int)blockIdx.x % BH, h = bh % Hq;
-    bound = measured_bound(norms, bh / Hq, h, h / (Hq / Hk), Hq, Hk, scale);
-    bound = bound <= MEASURED_BOUND ? bound : INFINITY;
   }
   // exp2 arguments reach -2*bound: keep them inside the fp32 exponent range
   if (bound <= 60.f)
@@ -1146,7 +1080,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NTH / 256, 
 
 template <int DH, int KS, int NTH>
 hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo, float *lse,
-                  const float *temp, float *norms_, hipStream_t s) {
+                  const float *temp, hipStream_t s) {
   constexpr bool WIDE = DH > 128;             // one wavefront per SIMD, 128-row query blocks
   constexpr int BQL = WIDE ? 128 : NTH / 2 / KS;
   const int nqb = row_blocks(d.T, BQL);
@@ -1157,23 +1091,16 @@ hipError_t launch(const Dims &d, const void *q, const void *k, const void *v, vo
   const int qk_normed = (d.flags & CCA_QK_NORM) ? 1 : 0;
   if (!(d.flags & CCA_KEY_TEMP)) temp = nullptr;
   const bool rsum = lse != nullptr || o_lo != nullptr;
-  RowNorms norms{nullptr, 0};
-  if (norms_ && !qk_normed && fwd_measures_bound(BH, d.T, DH, causal)) {
-    const int per = ((d.T + NORM_CHUNKS - 1) / NORM_CHUNKS + 63) / 64 * 64;
-    norms = RowNorms{norms_, (d.T + per - 1) / per};
-    row_norms_kernel<DH><<<dim3(norms.chunks, d.Hq + d.Hk, d.B), 256, 0, s>>>((const bf16_t *)q, (const bf16_t *)k, norms_, d.T, d.Hq, d.Hk, per);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  }
 #define CCA_ATTN_LAUNCH(C, R)                                                                                          \
   if constexpr (WIDE)                                                                                                  \
     attn_fwd_wide_kernel<DH, C, R><<<(unsigned)blocks, 256, 0, s>>>((const bf16_t *)q, (const bf16_t *)k,               \
                                                                     (const bf16_t *)v, (bf16_t *)o, (bf16_t *)o_lo, lse, \
                                                                     temp, qk_normed, d.T, d.Hq, d.Hk, BH, nqb, paired,  \
-                                                                    d.scale, norms);                                   \
+                                                                    d.scale);                                          \
   else                                                                                                                 \
     attn_fwd_kernel<DH, C, R, KS, NTH><<<(unsigned)blocks, NTH, 0, s>>>((const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,  \
                                                               (bf16_t *)o, (bf16_t *)o_lo, lse, temp, qk_normed, d.T,   \
-                                                              d.Hq, d.Hk, BH, nqb, paired, d.scale, norms)
+                                                              d.Hq, d.Hk, BH, nqb, paired, d.scale)
   if (causal) {
     if (rsum) { CCA_ATTN_LAUNCH(true, true); }
     else { CCA_ATTN_LAUNCH(true, false); }
@@ -1192,13 +1119,11 @@ bool attention_mfma_supported(const Dims &d) {
          (long long)d.T * d.Hk * d.dh * 2 < (1ll << 31);
 }
 
-size_t attention_norms_bytes(const Dims &d) { return (size_t)d.B * (d.Hq + d.Hk) * NORM_CHUNKS * sizeof(float); }
-
 hipError_t attention_mfma_bf16(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo,
-                               float *lse, const float *temp, float *norms, hipStream_t s) {
+                               float *lse, const float *temp, hipStream_t s) {
   const long long BH = (long long)d.B * d.Hq;
   const bool causal = d.flags & CCA_CAUSAL;
-#define ARGS d, q, k, v, o, o_lo, lse, temp, norms, s
+#define ARGS d, q, k, v, o, o_lo, lse, temp, s
   if (d.dh == 256) return launch<256, 1, 256>(ARGS);
   if (!fwd_splits_keys(BH, d.T, causal)) return d.dh == 128 ? launch<128, 1, 512>(ARGS) : launch<64, 1, 512>(ARGS);
   if (fwd_takes_64_rows(BH, d.T, d.flags & CCA_QK_NORM)) return d.dh == 128 ? launch<128, 2, 256>(ARGS) : launch<64, 2, 256>(ARGS);

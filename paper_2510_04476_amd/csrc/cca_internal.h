@@ -95,10 +95,8 @@ hipError_t mfma_probe(float *out, int blocks, int iters, bool random_operands, h
 
 bool attention_mfma_supported(const Dims &d);
 // temp (H_k log-temperatures, device) is read only when d.flags has QK_NORM and KEY_TEMP: it bounds the scores
-// `norms`: attention_norms_bytes of scratch for the lengths of the rows, which bound the scores where the QK norm does not; may be NULL
-size_t attention_norms_bytes(const Dims &d);
 hipError_t attention_mfma_bf16(const Dims &d, const void *q, const void *k, const void *v, void *o, void *o_lo,
-                               float *lse, const float *temp, float *norms, hipStream_t s);
+                               float *lse, const float *temp, hipStream_t s);
 
 // no transform selected: q, k, v are slices of the latent rows (plus the optional value-shift)
 bool prologue_is_split_copy(const Dims &d);

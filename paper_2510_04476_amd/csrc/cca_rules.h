@@ -215,18 +215,6 @@ inline bool fwd_splits_keys(long long BH, int T, bool causal) {
 // 4, 64: 15.2 -> 14.1; 1531, 8, 128: 25.8 -> 25.6; 2048, 8: 31.5 -> 31.6; beyond a round 777, 24, 64: 12.1 -> 12.7, not causal 13.0 ->
 // 22.9; without a bound on the scores 512, 16, 64: 9.9 -> 9.8, 777: 12.1 -> 13.0.
 inline bool fwd_takes_64_rows(long long BH, int T, bool normed) { return normed && T <= 1536 && BH * ((T + 63) / 64) <= 256; }
-// Scores without a bound by the QK norm: a pass over the rows for their lengths first, so that the form that needs no running
-// maximum can run?  The pass costs 3.5 ... 4 us.  At heads wider than 128 the other form is a third slower for each key; at 128 the gain
-// comes with long sequences, at 64, where the maximum is a larger part of a tile's work, with the rows in all.  Whole prefill, without
-// -> with the pass, us (T, B * H_q, c = causal): d_h = 256: 64, 8 c: 31.8 -> 33.1; 300, 8 c: 52.7 -> 47.2; 4096, 8 c: 363 -> 277; 8192, 8:
-// 1157 -> 782; d_h = 128: 1531, 48 c: 207.1 -> 208.5; 2048, 16: 118.1 -> 119.5; 2048, 8 c: 59.6 -> 57.7; 4096, 8 c: 100.7 -> 93.9; 4096, 16
-// c: 227.5 -> 223.9; 8192, 16 c: 509 -> 488; d_h = 64: 2048, 32 c: 89.2 -> 92.0; 2048, 32: 104.2 -> 100.5; 1531, 48 c: 84.1 -> 83.2; 4096, 16 c:
-// 93.5 -> 95.5; 4096, 16: 127 -> 115; 1531, 96 c: 173 -> 165; 8192, 32 c: 478 -> 421.
-inline bool fwd_measures_bound(long long BH, int T, int dh, bool causal) {
-  if (dh > 128) return T >= 128;
-  if (dh > 64) return T >= 4096;
-  return BH * T * (causal ? 1 : 2) >= 72000;
-}
 // Backward, likewise (B * H_q = 4 ... 400, T = 64 ... 16384, causal and not, one and four query heads per KV head): neither kernel
 // is split where that measured more than 2 % slower, and the choice costs 0.1 % on average.  Attention backward, us, neither -> dQ
 // -> dK / dV -> both split, causal, d_h = 128: T = 512, B * H_q = 16: 71 -> 64 -> 59 -> 53; 2048, 8: 180 -> 156 -> 139 -> 115;

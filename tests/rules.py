@@ -18,7 +18,6 @@ int r_prologue_is_short(long long rows, int heads, int R, int dh, int adjoint) {
 int r_tile_panel(int tiles_m, int tiles_n, int tm, int tn) { return tile_panel(tiles_m, tiles_n, tm, tn); }
 int r_decode_up_combines(long long B, int e_q, int nsplit) { return decode_up_combines(B, e_q, nsplit, 8); }
 int r_fwd_takes_64_rows(long long BH, int T, int normed) { return fwd_takes_64_rows(BH, T, normed); }
-int r_fwd_measures_bound(long long BH, int T, int dh, int causal) { return fwd_measures_bound(BH, T, dh, causal); }
 int r_fwd_splits_keys(long long BH, int T, int causal) { return fwd_splits_keys(BH, T, causal); }
 int r_dq_splits_keys(long long BH, int T, int causal) { return dq_splits_keys(BH, T, causal); }
 int r_dkdv_splits_rows(long long BH, int T, int causal) { return dkdv_splits_rows(BH, T, causal); }
@@ -49,7 +48,7 @@ def _lib():
                         os.path.join(ROOT, "paper_2510_04476_amd", "csrc"), src, "-o", so], check=True)
         lib = C.CDLL(so)
     L, I = C.c_longlong, C.c_int
-    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_tile_panel=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I], r_fwd_measures_bound=[L, I, I, I],
+    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_tile_panel=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
                            r_generic_attention_bwd_16=[L, I, I, I], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
@@ -84,10 +83,6 @@ def decode_up_combines(B, e_q, nsplit):
 
 def fwd_takes_64_rows(BH, T, normed):
     return bool(_lib().r_fwd_takes_64_rows(BH, T, normed))
-
-
-def fwd_measures_bound(BH, T, dh, causal):
-    return bool(_lib().r_fwd_measures_bound(BH, T, dh, causal))
 
 
 def fwd_splits_keys(BH, T, causal):

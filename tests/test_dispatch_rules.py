@@ -158,19 +158,6 @@ DKDV_MEASURED = [(64, 1531, True, 104.5, 115.3), (4, 64, True, 13.0, 13.9), (8, 
                  (64, 1999, True, 174.0, 185.0)]
 
 
-# B * H_q, T, d_h, causal and us of a whole prefill without the rows' lengths measured first and with
-BOUND_MEASURED = [(8, 64, 256, True, 31.8, 33.1), (8, 300, 256, True, 52.7, 47.2), (8, 8192, 256, False, 1157.2, 782.3),
-                  (48, 1531, 128, True, 207.1, 208.5), (16, 2048, 128, False, 118.1, 119.5), (8, 4096, 128, True, 100.7, 93.9),
-                  (16, 4096, 128, True, 227.5, 223.9), (16, 1024, 128, True, 71.5, 73.0), (32, 2048, 64, True, 89.2, 92.0),
-                  (32, 2048, 64, False, 104.2, 100.5), (16, 4096, 64, True, 93.5, 95.5), (48, 1531, 64, False, 114.3, 109.7),
-                  (96, 1531, 64, True, 173.3, 165.2), (16, 512, 64, False, 26.7, 31.2)]
-
-
-@pytest.mark.parametrize("BH,T,dh,causal,without,measured", BOUND_MEASURED)
-def test_lengths_of_rows_are_measured_where_that_pays(BH, T, dh, causal, without, measured):
-    assert rules.fwd_measures_bound(BH, T, dh, causal) == (measured < without)
-
-
 @pytest.mark.parametrize("rule,cases", [(rules.fwd_splits_keys, FWD_MEASURED), (rules.dq_splits_keys, DQ_MEASURED),
                                         (rules.dkdv_splits_rows, DKDV_MEASURED)])
 def test_attention_split_is_the_faster_form(rule, cases):
