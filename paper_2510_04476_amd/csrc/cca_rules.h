@@ -43,32 +43,59 @@ inline NtTile nt_tile(long long M, int N, int K, double *us = nullptr) {
 // x 4096 32.8 -> 27.4 (64 x 64 tiles), 1000 x 2048 x 1024 16.7 -> 15.1 (64 x 128), 1000 x 4096 x 2048 34.8 -> 33.7, 12000 x 4096 x 2048
 // 209 -> 200 (256 x 256).  Tiles 128 columns wide and as high lost 1 ... 4 % where the panels save less than half of the rows (1531 x 1536
 // x 2048 27.1 -> 27.8) and keep the row order there.
-inline int tile_panel(int tiles_m, int tiles_n, int tm, int tn) {
-  const long long tiles = (long long)tiles_m * tiles_n, range = (tiles + 7) / 8, at_once = range < 32 ? range : 32;
-  int best = tiles_n;
-  long long least = -1, row_major = 0;
-  for (int panels = 1; panels <= tiles_n; ++panels) {
-    const int w = (tiles_n + panels - 1) / panels;
-    if (w == best && panels > 1) continue;
-    const long long full = (long long)w * tiles_m;
-    long long cost = 0;
-    for (int x = 0; x < 8; ++x) {
-      const long long a = x * range, b = a + at_once < tiles ? a + at_once : tiles;
-      long long rows = 0, cols = 0;
-      for (long long p = a / full; p * full < b && a < b; ++p) {
-        const long long lo = a > p * full ? a - p * full : 0, hi = b < (p + 1) * full ? b - p * full : full;
-        const long long width = p * w + w < tiles_n ? w : tiles_n - p * w;
+// The choice is made on the host for every launch, so it looks at few widths: whole rows, whole columns, and between those that put a
+// range into one or two panels and are no wider than 16, where the rows an XCD's 32 tiles touch are fewest; of these only such
+// that could beat the best so far.  The cost is that of a search over every width (up to 300 x 1024 tiles of every shape), in 0.2 ... 0.6 us
+// a launch; the search took 3.1 at 512 x 1536 x 2048, 31 at 128 x 12288 x 8192, 380 at 1024 columns of tiles.
+struct TilePanel {
+  unsigned tiles_m, tiles_n, tm, tn, tiles, range, at_once;  // range: tiles of an XCD; at_once: those that run first
+  TilePanel(int tiles_m_, int tiles_n_, int tm_, int tn_)
+      : tiles_m(tiles_m_), tiles_n(tiles_n_), tm(tm_), tn(tn_), tiles(tiles_m * tiles_n), range((tiles + 7) / 8), at_once(range < 32 ? range : 32) {}
+  // rows of both operands that the ranges touch with panels of w columns
+  unsigned touched(unsigned w) const {
+    const unsigned full = w * tiles_m;
+    unsigned sum = 0;
+    for (unsigned a = 0; a < tiles; a += range) {
+      const unsigned b = a + at_once < tiles ? a + at_once : tiles;
+      if (w == 1) {  // whole columns one after the other
+        sum += (b - a < tiles_m ? b - a : tiles_m) * tm + ((b - 1) / tiles_m - a / tiles_m + 1) * tn;
+        continue;
+      }
+      unsigned rows = 0, cols = 0;
+      for (unsigned p = a / full, start = p * full; start < b; ++p, start += full) {
+        const unsigned lo = a > start ? a - start : 0, hi = b - start < full ? b - start : full, left = tiles_n - p * w, width = w < left ? w : left;
         rows += (hi - 1) / width - lo / width + 1;
         cols += hi - lo < width ? hi - lo : width;
       }
-      cost += (rows < tiles_m ? rows : tiles_m) * tm + cols * tn;
+      sum += (rows < tiles_m ? rows : tiles_m) * tm + cols * tn;
     }
-    if (panels == 1) row_major = cost;
-    if (least < 0 || cost < least) least = cost, best = w;
-    if (w == 1) break;
+    return sum;
   }
-  return tn == 128 && tm >= 128 && 2 * least > row_major ? tiles_n : best;
-}
+  // the widths of ceil(tiles_n / w) panels as even as can be
+  unsigned even(unsigned w) const {
+    const unsigned panels = (tiles_n + w - 1) / w;
+    return (tiles_n + panels - 1) / panels;
+  }
+  unsigned best() const {
+    const unsigned row_major = touched(tiles_n), ranges = (tiles - at_once) / range + 1;  // ranges of at_once tiles
+    unsigned width = tiles_n, least = row_major;
+    auto look_at = [&](unsigned w) {
+      const unsigned cost = touched(w);
+      if (cost < least || (cost == least && w > width)) least = cost, width = w;
+    };
+    const unsigned square = even((unsigned)fmin(sqrt((double)at_once * tm / tn) + 0.5, (double)tiles_n));
+    if (square < tiles_n) look_at(square);
+    const unsigned narrow = at_once / tiles_m > 2 ? at_once / tiles_m : 2;  // (narrower, a range takes several panels whole: no fewer columns)
+    for (unsigned w = tiles_n - 1 < 16 ? tiles_n - 1 : 16; w >= narrow; --w) {
+      w = even(w);
+      const unsigned rows = (at_once + w - 1) / w, cols = w < at_once ? w : at_once;
+      if (w != square && w > 1 && ranges * ((rows < tiles_m ? rows : tiles_m) * tm + cols * tn) <= least + least / 16) look_at(w);  // (a narrower last panel touches a little less)
+    }
+    if (tiles_n > 1) look_at(1);
+    return tn == 128 && tm >= 128 && 2 * least > row_major ? tiles_n : width;
+  }
+};
+inline int tile_panel(int tiles_m, int tiles_n, int tm, int tn) { return (int)TilePanel(tiles_m, tiles_n, tm, tn).best(); }
 
 // ---- weight gradients: C (Mo,No) = A (K,Mo)^T * B (K,No), bf16, K tokens -------------------------------------------------
 enum TnTile { TN_SPLIT, TN_64x64, TN_64x128, TN_128x128 };

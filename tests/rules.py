@@ -8,6 +8,8 @@ import tempfile
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = r"""
+#include <chrono>
+
 #include "cca_rules.h"
 using namespace cca;
 extern "C" {
@@ -16,6 +18,18 @@ int r_tn_tile(int Mo, int No, long long K) { return tn_tile(Mo, No, K); }
 int r_tn_splits(int Mo, int No, long long K) { return tn_splits(Mo, No, K); }
 int r_prologue_is_short(long long rows, int heads, int R, int dh, int adjoint) { return prologue_is_short(rows, heads, R, dh, adjoint); }
 int r_tile_panel(int tiles_m, int tiles_n, int tm, int tn) { return tile_panel(tiles_m, tiles_n, tm, tn); }
+int r_panel_touches(int tiles_m, int tiles_n, int tm, int tn, int w) { return TilePanel(tiles_m, tiles_n, tm, tn).touched(w); }
+double r_tile_panel_us(int tiles_m, int tiles_n, int tm, int tn) {  // of one choice: the fastest of ten batches
+  double least = 1e9;
+  for (int batch = 0; batch < 10; ++batch) {
+    volatile int sum = 0;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int i = 0; i < 20; ++i) sum = sum + tile_panel(tiles_m, tiles_n, tm, tn);
+    const double us = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 1e6 / 20;
+    least = us < least ? us : least;
+  }
+  return least;
+}
 int r_decode_up_combines(long long B, int e_q, int nsplit) { return decode_up_combines(B, e_q, nsplit, 8); }
 int r_fwd_takes_64_rows(long long BH, int T, int normed) { return fwd_takes_64_rows(BH, T, normed); }
 int r_fwd_splits_keys(long long BH, int T, int causal) { return fwd_splits_keys(BH, T, causal); }
@@ -48,12 +62,13 @@ def _lib():
                         os.path.join(ROOT, "paper_2510_04476_amd", "csrc"), src, "-o", so], check=True)
         lib = C.CDLL(so)
     L, I = C.c_longlong, C.c_int
-    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_tile_panel=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
+    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_tile_panel=[I, I, I, I], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
                            r_generic_attention_bwd_16=[L, I, I, I], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
                            r_decode_keys_per_split=[L, I, I, I]).items():
         getattr(lib, name).argtypes = args
+    lib.r_tile_panel_us.restype = C.c_double
     return lib
 
 
@@ -75,6 +90,14 @@ def prologue_is_short(rows, heads, R, dh, adjoint):
 
 def tile_panel(tiles_m, tiles_n, tm, tn):
     return _lib().r_tile_panel(tiles_m, tiles_n, tm, tn)
+
+
+def panel_touches(tiles_m, tiles_n, tm, tn, width):
+    return _lib().r_panel_touches(tiles_m, tiles_n, tm, tn, width)
+
+
+def tile_panel_us(tiles_m, tiles_n, tm, tn):
+    return _lib().r_tile_panel_us(tiles_m, tiles_n, tm, tn)
 
 
 def decode_up_combines(B, e_q, nsplit):

@@ -25,6 +25,52 @@ def test_projection_cases_reach_every_order_of_tiles():
     assert {(False, "rows")} | {(small_tile, o) for small_tile in (True, False) for o in ("whole panels", "a narrower one")} <= orders
 
 
+TILE_SHAPES = [(256, 256), (192, 256), (256, 192), (256, 128), (128, 128), (64, 128), (64, 64)]
+
+
+def touched(tiles_m, tiles_n, tm, tn, w):
+    """Rows of both operands that the first 32 tiles of each XCD's range touch, tile by tile"""
+    tiles = tiles_m * tiles_n
+    n = -(-tiles // 8)
+    total = 0
+    for a in range(0, tiles, n):
+        rows, cols = 0, set()
+        panels = {}
+        for t in range(a, min(a + min(n, 32), tiles)):
+            p, r = divmod(t, w * tiles_m)
+            width = min(w, tiles_n - p * w)
+            panels.setdefault(p, set()).add(r // width)
+            cols.add(p * w + r % width)
+        rows = sum(len(v) for v in panels.values())
+        total += min(rows, tiles_m) * tm + len(cols) * tn
+    return total
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n", [(1, 1), (1, 40), (2, 17), (3, 5), (5, 24), (7, 9), (8, 44), (19, 6), (40, 8), (64, 13)])
+def test_rows_touched_by_a_panel_are_counted(tiles_m, tiles_n):
+    for tm, tn in TILE_SHAPES[:4]:
+        for w in range(1, tiles_n + 1):
+            assert rules.panel_touches(tiles_m, tiles_n, tm, tn, w) == touched(tiles_m, tiles_n, tm, tn, w), w
+
+
+def test_panels_touch_as_few_rows_as_any_width():
+    for tm, tn in TILE_SHAPES:
+        for tiles_m in [*range(1, 41), 63, 100, 171, 255]:
+            for tiles_n in [*range(1, 34), 48, 64, 96, 177, 300]:
+                cost = {w: rules.panel_touches(tiles_m, tiles_n, tm, tn, w) for w in {-(-tiles_n // p) for p in range(1, tiles_n + 1)}}
+                kept = tn == 128 and tm >= 128 and 2 * min(cost.values()) > cost[tiles_n]  # the row order, by its own rule
+                panel = rules.tile_panel(tiles_m, tiles_n, tm, tn)
+                assert panel == tiles_n if kept else cost[panel] <= 1.02 * min(cost.values()), (tiles_m, tiles_n, tm, tn, panel)
+
+
+# 512 x 1536 x 2048, 512 x 2048 x 1024, 128 x 12288 x 8192, 64 x 24576 x 16384, 64 x 16384 x 8192, 1 x 65536 x 65536, and long and wide
+@pytest.mark.parametrize("tiles_m,tiles_n,tm,tn", [(8, 24, 64, 64), (8, 32, 64, 64), (2, 96, 64, 128), (1, 192, 64, 128), (1, 256, 64, 64), (2, 1024, 64, 64),
+                                                   (3, 1000, 64, 64), (64, 8, 256, 192), (4096, 256, 256, 256)])
+def test_order_of_tiles_is_chosen_in_no_time(tiles_m, tiles_n, tm, tn):
+    """It runs on the host at every launch of a product, which itself takes about 5 us."""
+    assert rules.tile_panel_us(tiles_m, tiles_n, tm, tn) <= 2.0
+
+
 def test_weight_gradient_cases_reach_every_tile():
     forms = {(r, Hq, dh, E): rules.tn_tile(Hq * dh, E, r) for r, Hq, dh, E in small.WGRAD_CASES}
     assert set(forms.values()) == set(rules.TN_TILES)
