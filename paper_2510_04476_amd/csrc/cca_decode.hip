@@ -1128,9 +1128,11 @@ hipError_t gemm_panel(const bf16_t *A, const bf16_t *W, bf16_t *C, RowDest dest,
 }
 
 hipError_t up_combined(const DecArgs &a, const float *attn, int nsplit, int per, const bf16_t *W, bf16_t *out, int N, int K, hipStream_t s) {
-  if (hipError_t e = raise_lds_limit<gemm_panel_combine_kernel>(PN_LDS - 32 * 1024); e != hipSuccess) return e;
+  static_assert(PN_COLS == 32 && PN_SUMS <= DECODE_UP_LDS && DECODE_UP_LDS + 4 * PN_NT / 64 * COMBINE_SPLITS * sizeof(float) <= PN_LDS, "LDS");
+  if (hipError_t e = raise_lds_limit<gemm_panel_combine_kernel>(DECODE_UP_LDS); e != hipSuccess) return e;
   const int kp = (K + 127) / 128 * 128;
-  const size_t pass = (size_t)kp * (PN_COLS * 2 + 2 * a.B), lds = pass > PN_SUMS ? pass : PN_SUMS;
+  const size_t pass = decode_up_lds(a.B, K), lds = pass > PN_SUMS ? pass : PN_SUMS;
+  if (lds > DECODE_UP_LDS) return hipErrorInvalidValue;
   gemm_panel_combine_kernel<<<(N + PN_COLS - 1) / PN_COLS, PN_NT, lds, s>>>(CombineArgs{a, attn, nsplit, per}, W, out, RowDest{N, nullptr, 0, 1}, a.B, N, K, kp);
   return hipGetLastError();
 }

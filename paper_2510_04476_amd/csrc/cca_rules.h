@@ -4,6 +4,7 @@
 #pragma once
 
 #include <math.h>
+#include <stddef.h>
 
 namespace cca {
 
@@ -333,6 +334,11 @@ inline int decode_keys_per_split(long long groups, int len, int dh, bool rows_ke
 // per four channels (2048 channels at most), which by 16 splits costs what the launch did.  Step with the launch, without, us (sequences x
 // tokens): E = 2048, 8 / 2 heads of 128: 1 x 200 22.1, 21.4; 1 x 1000 (8 splits) 22.5, 22.2; 2 x 500 22.5, 21.8; 1 x 2000 (16) 23.1, 22.9;
 // 2 x 2000 24.0, 24.0; 4 / 4 of 64, 8 x 1000 18.8, 18.1; 8 x 4000 (16) 22.4, 22.8; 4 / 1 of 256, 1 x 4000 29.8, 30.2.
-inline bool decode_up_combines(long long B, int e_q, int nsplit, int max_splits) { return B * e_q <= 2048 && nsplit <= max_splits; }
+constexpr int UP_CHANNELS = 2048;
+inline bool decode_up_combines(long long B, int e_q, int nsplit, int max_splits) { return B * e_q <= UP_CHANNELS && nsplit <= max_splits; }
+// Dynamic LDS of that up-projection: 32 columns of W and the B rows that multiply them, bf16, all channels in whole lines of 128; the most
+// that any step asks for is that of one sequence (the lines' padding is at most 64 channels a row)
+constexpr size_t decode_up_lds(long long B, int e_q) { return (size_t)((e_q + 127) / 128 * 128) * (size_t)(64 + 2 * B); }
+constexpr size_t DECODE_UP_LDS = decode_up_lds(1, UP_CHANNELS);
 
 }  // namespace cca

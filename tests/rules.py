@@ -31,6 +31,8 @@ double r_tile_panel_us(int tiles_m, int tiles_n, int tm, int tn) {  // of one ch
   return least;
 }
 int r_decode_up_combines(long long B, int e_q, int nsplit) { return decode_up_combines(B, e_q, nsplit, 8); }
+int r_decode_up_lds(long long B, int e_q) { return (int)decode_up_lds(B, e_q); }
+int r_decode_up_lds_limit() { return (int)DECODE_UP_LDS; }
 int r_fwd_takes_64_rows(long long BH, int T, int normed) { return fwd_takes_64_rows(BH, T, normed); }
 int r_fwd_splits_keys(long long BH, int T, int causal) { return fwd_splits_keys(BH, T, causal); }
 int r_dq_splits_keys(long long BH, int T, int causal) { return dq_splits_keys(BH, T, causal); }
@@ -62,7 +64,7 @@ def _lib():
                         os.path.join(ROOT, "paper_2510_04476_amd", "csrc"), src, "-o", so], check=True)
         lib = C.CDLL(so)
     L, I = C.c_longlong, C.c_int
-    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_tile_panel=[I, I, I, I], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
+    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_decode_up_lds=[L, I], r_decode_up_lds_limit=[], r_tile_panel=[I, I, I, I], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
                            r_generic_attention_bwd_16=[L, I, I, I], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
@@ -102,6 +104,14 @@ def tile_panel_us(tiles_m, tiles_n, tm, tn):
 
 def decode_up_combines(B, e_q, nsplit):
     return bool(_lib().r_decode_up_combines(B, e_q, nsplit))
+
+
+def decode_up_lds(B, e_q):
+    return _lib().r_decode_up_lds(B, e_q)
+
+
+def decode_up_lds_limit():
+    return _lib().r_decode_up_lds_limit()
 
 
 def fwd_takes_64_rows(BH, T, normed):

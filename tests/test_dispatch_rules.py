@@ -94,6 +94,16 @@ def test_projection_adjoint_cases_reach_every_form():
     assert forms(chosen) == forms(reached)
 
 
+def test_combining_up_projection_fits_the_lds_it_declares():
+    for dh in (64, 128, 256):  # the widths whose attention leaves splits to combine
+        for e_q in range(dh, 4097, dh):
+            for B in range(1, 80):
+                if rules.decode_up_combines(B, e_q, 8):
+                    # 64 bytes of W and 2 of each row for every channel, in lines of 128
+                    assert rules.decode_up_lds(B, e_q) == -(-e_q // 128) * 128 * (64 + 2 * B) <= rules.decode_up_lds_limit(), (B, e_q)
+    assert rules.decode_up_combines(1, 2048, 8) and rules.decode_up_lds_limit() + 1024 <= 160 * 1024
+
+
 def test_attention_cases_reach_both_block_orders():
     paired = {(causal, rules.pair_blocks(B * Hq, causal, -(-T // 128))) for B, T, Hq, Hk, dh, causal, normed in small.SPLIT_CASES}
     assert paired == {(True, True), (True, False), (False, False)}
