@@ -97,9 +97,8 @@ PAIR_CASES = [(70, 4, 2, 64, 512), (70, 8, 2, 128, 2048), (130, 8, 2, 128, 2048)
 
 @pytest.mark.parametrize("rows,Hq,Hk,dh,E", PAIR_CASES)
 def test_projection_adjoints_in_one_launch(rows, Hq, Hk, dh, E):
-    """d W_O against the product of its operands; d_x and d W_down, whose other operand stays inside, against the calls that want
-    only one of them (a launch each, other tiles): the sums differ in order, so each side rounds the same fp32 value to within its
-    error, two bf16 neighbours at most."""
+    """Every gradient against the product of its operands in fp64.  d_lat, which stays inside, does not depend on x: with rows of the
+    identity for x, d W_down is d_lat, E rows at a time and exactly (sums of one term)."""
     say("projection adjoints", rows, Hq, Hk, dh, E)
     cfg = P.CCAConfig(B=1, T=rows, d_model=E, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, flags=P.CCA_FLAGS_MHA)
     w = P.CCAWeights(w_down=rnd(E, cfg.n_lat, seed=2, scale=0.02), w_out=rnd(cfg.e_q, E, seed=4, scale=0.02))
@@ -107,16 +106,19 @@ def test_projection_adjoints_in_one_launch(rows, Hq, Hk, dh, E):
     saved = P.CCASaved.allocate(cfg, "cuda")
     P.cca_forward(cfg, w, x, saved=saved)
     nan = lambda t: torch.full_like(t, float("nan"))
-    d_x, g = P.cca_backward(cfg, w, x, saved, d_out, d_x=nan(x), grads=P.CCAGrads(w_down=nan(w.w_down), w_out=nan(w.w_out)))
-    only_x, _ = P.cca_backward(cfg, w, x, saved, d_out, d_x=nan(x), grads=P.CCAGrads(w_out=nan(w.w_out)))
+    backward = lambda x_: P.cca_backward(cfg, w, x_, saved, d_out, d_x=nan(x), grads=P.CCAGrads(w_down=nan(w.w_down), w_out=nan(w.w_out)))
+    d_x, g = backward(x)
+    d_lat = []
+    for r0 in range(0, rows, E):
+        n = min(E, rows - r0)
+        one = torch.zeros_like(x)
+        one[0, torch.arange(r0, r0 + n), torch.arange(n)] = 1.0
+        d_lat.append(backward(one)[1].w_down[:n])
+    d_lat = torch.cat(d_lat).double()
     torch.cuda.synchronize()
     check_product(g.w_out, saved.o[0].double().t().contiguous() @ d_out[0].double(), rows)
-    # (neighbours in bf16 are up to 2^-7 of the value apart, twice what check_product allows against an exact product)
-    check_product(d_x[0].double() / 2 + only_x[0].double() / 2, only_x[0], cfg.n_lat)
-    # d W_down = x^T d_lat and d_x = d_lat W_down^T: <d W_down, W> = <d_x, x> for any d_lat
-    lhs, rhs = (g.w_down.double() * w.w_down.double()).sum(), (d_x.double() * x.double()).sum()
-    noise = 2.0 ** -8 * float(((d_x.double() * x.double()).square().sum() + (g.w_down.double() * w.w_down.double()).square().sum()).sqrt())
-    assert abs(float(lhs - rhs)) <= 4 * noise, (float(lhs), float(rhs), noise)
+    check_product(d_x[0], d_lat @ w.w_down.double().t().contiguous(), cfg.n_lat)
+    check_product(g.w_down, x[0].double().t().contiguous() @ d_lat, rows)
 
 
 # B, T, Hq, Hk, d_h, causal, normalised: odd lengths, one tile more or less than a pair, rows whose second key group is
@@ -423,14 +425,16 @@ def check_prologue(B, T, Hq, Hk, k_seq, k_ch, dh):
     ref = transforms(x, w0, w1, temp, Hq, Hk, dh)
     torch.autograd.backward(ref, [t.double() for t in (d_q, d_k, d_v)])
     assert torch.equal(v, ref[2].detach().bfloat16())
+    d_temp, ref_temp = g.temp, temp.grad
+    if dh < 256:  # one sum over <d_k, k> per head, of terms of either sign: with a pull of d_k along k, so that they do not cancel
+        along = (d_k.float() + 0.25 * k.float()).bfloat16()
+        d_temp = P.cca_prologue_backward(cfg, w, lat, q, k, rnorm, d_q, along, d_v)[1].temp
+        ref_temp = (along.double() * ref[1].detach()).sum((0, 1, 3))  # k is exp(temp) times what does not depend on it
     for name, got, r in (("q", q, ref[0]), ("k", k, ref[1]), ("d_lat", d_lat, x.grad), ("d_w_conv_seq", g.w_conv_seq, w0.grad),
-                         ("d_w_conv_ch", g.w_conv_ch, w1.grad), ("d_temp", g.temp, temp.grad)):
+                         ("d_w_conv_ch", g.w_conv_ch, w1.grad), ("d_temp", d_temp, ref_temp)):
         rel = float((got.double() - r.detach()).norm() / r.detach().norm())
         say(name, rel)
-        # d_temp is one sum over d_k k per head, of either sign: k's rounding (2^-9 of a term, 2^-9 / sqrt(3) on average) does not cancel
-        # with the terms
-        noise = 4 * 2.0 ** -9 * float((d_k.double() * ref[1].detach()).norm() / r.detach().norm()) if name == "d_temp" else 0.0
-        assert rel <= 1e-2 + noise, (name, rel, noise)
+        assert rel <= 1e-2, (name, rel)
 
 
 # the decode step's projections (several passes through LDS, K slices of the down-projection, lengths that are not whole
