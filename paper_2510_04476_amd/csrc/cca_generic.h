@@ -8,6 +8,8 @@
 // a tile of results is the second operand of the next product as it stands.
 #pragma once
 
+#include <type_traits>
+
 #include "cca_internal.h"
 
 namespace cca {
@@ -21,6 +23,21 @@ __device__ __forceinline__ gen_f32x4 load4(const bf16_t *p) {
   const gen_u32x2 w = *reinterpret_cast<const gen_u32x2 *>(p);
   return gen_f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
                    __uint_as_float(w.y & 0xffff0000u)};
+}
+// Four values as they lie in memory, and their conversion
+__device__ __forceinline__ gen_f32x4 raw4(const float *p) { return *reinterpret_cast<const gen_f32x4 *>(p); }
+__device__ __forceinline__ gen_u32x2 raw4(const bf16_t *p) { return *reinterpret_cast<const gen_u32x2 *>(p); }
+template <typename T>
+struct Raw4 {
+  T v[4];
+};
+__device__ __forceinline__ gen_f32x4 raw_to_f32(gen_f32x4 r) { return r; }
+__device__ __forceinline__ gen_f32x4 raw_to_f32(gen_u32x2 w) {
+  return gen_f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
+}
+template <typename T>
+__device__ __forceinline__ gen_f32x4 raw_to_f32(const Raw4<T> &r) {
+  return gen_f32x4{load_f(r.v), load_f(r.v + 1), load_f(r.v + 2), load_f(r.v + 3)};
 }
 __device__ __forceinline__ gen_f32x16 zero16() {
   gen_f32x16 z;
@@ -208,10 +225,10 @@ constexpr int GP_NT = 256, GP_WAVES = GP_NT / 64, GP_TOK = 32;
 constexpr int GP_RED = GP_WAVES * 16 * 64;       // floats of gp_sum's buffer
 constexpr size_t GP_MAX_LDS = 160 * 1024;
 constexpr long long GP_GRID = 1ll << 23;         // workgroups of a launch, which takes fewer than 2^32 threads in one dimension
-// Launches `go(first block, blocks)` over B sequences of T tokens
+// Launches `go(first block, blocks)` over B sequences of T tokens, `tok` of them to a workgroup
 template <typename F>
-inline hipError_t gp_launches(int B, int T, F &&go) {
-  const long long blocks = (long long)((T + GP_TOK - 1) / GP_TOK) * B;
+inline hipError_t gp_launches(int B, int T, int tok, F &&go) {
+  const long long blocks = (long long)((T + tok - 1) / tok) * B;
   for (long long x = 0; x < blocks; x += GP_GRID) {
     go((unsigned)x, (unsigned)(blocks - x < GP_GRID ? blocks - x : GP_GRID));
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
@@ -240,32 +257,15 @@ __device__ __forceinline__ void rope_angles(float *sa, float base, int dh, int t
   }
 }
 
-// This wavefront's share of sum_n A[row][n] B[n][column] over n < terms (a multiple of 4): lane (l32, half) supplies row l32 as
-// a(n) and column l32 as b(n).
-template <typename FA, typename FB>
-__device__ __forceinline__ gen_f32x16 gp_product(int terms, FA &&a, FB &&b) {
-  const int half = (threadIdx.x >> 5) & 1, wave = threadIdx.x >> 6;
-  gen_f32x16 acc = zero16();
-  constexpr int AHEAD = 2;  // blocks of 8 terms in flight (the compiler does not unroll a loop of MFMAs with an unknown count)
-  for (int b0 = wave * 8; b0 < terms; b0 += AHEAD * GP_WAVES * 8) {
-    float x[AHEAD][4], y[AHEAD][4];
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) {
-      const int n0 = b0 + u * GP_WAVES * 8 + 4 * half;
-      const bool in = n0 < terms;  // a multiple of 4: the four terms of a lane are in or out together
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float va = a(in ? n0 + i : i), vb = b(in ? n0 + i : i);
-        x[u][i] = in ? va : 0.f, y[u][i] = in ? vb : 0.f;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u][i], y[u][i], acc, 0, 0, 0);
-  }
-  return acc;
+// go(std::integral_constant<int, n>) for n = 1 ... 4: a tap count the compiler knows, so that an index costs no division
+template <typename F>
+__device__ __forceinline__ void gp_taps(int n, F &&go) {
+  if (n == 1) go(std::integral_constant<int, 1>{});
+  else if (n == 2) go(std::integral_constant<int, 2>{});
+  else if (n == 3) go(std::integral_constant<int, 3>{});
+  else go(std::integral_constant<int, 4>{});
 }
+
 // The wavefronts' shares added in order: out(row, column, sum) once per element of the 32 x 32 tile
 template <typename F>
 __device__ __forceinline__ void gp_sum(const gen_f32x16 &acc, float *red, F &&out) {
@@ -281,6 +281,50 @@ __device__ __forceinline__ void gp_sum(const gen_f32x16 &acc, float *red, F &&ou
 #pragma unroll
     for (int w = 0; w < GP_WAVES; ++w) sum += red[(w * 16 + r) * 64 + lane];
     out(tile_row(r, lane >> 5), lane & 31, sum);
+  }
+}
+
+// sum_n A[row][n] B[n][column] over the terms n = c * TAPS + j, c < dh (a multiple of 4), j < TAPS, for ceil(rows / 32) tiles of 32 rows one
+// after the other, the terms dealt to the wavefronts in blocks of 8: lane (l32, half) supplies row r as a4(r, n), terms n ... n + 3 (n a
+// multiple of 4) as they lie in memory, and column l32 as b(c, j); out(row, column, sum).  What bounds it is the latency of a's loads,
+// so those of a tile's first AHEAD blocks per wavefront are requested before the sums of the tile before it are added.
+template <int TAPS, int AHEAD, typename FA, typename FB, typename F>
+__device__ __forceinline__ void gp_product(int dh, int rows, float *red, FA &&a4, FB &&b, F &&out) {
+  constexpr int STEP = GP_WAVES * 8;
+  const int terms = dh * TAPS, half = (threadIdx.x >> 5) & 1, l32 = threadIdx.x & 31, first = (threadIdx.x >> 6) * 8;
+  decltype(a4(0, 0)) x[AHEAD];
+  auto request = [&](int r0, int b0) __attribute__((always_inline)) {
+    const int r = r0 + l32 < rows ? r0 + l32 : rows - 1;  // past the last: results not kept
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      if (b0 + u * STEP >= terms) break;
+      const int n = b0 + u * STEP + 4 * half;
+      x[u] = a4(r, n < terms ? n : 0);
+    }
+  };
+  request(0, first);
+  for (int r0 = 0; r0 < rows; r0 += 32) {
+    gen_f32x16 acc = zero16();
+    for (int b0 = first; b0 < terms; b0 += AHEAD * STEP) {
+      if (b0 != first) request(r0, b0);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        if (b0 + u * STEP >= terms) break;
+        const int n0 = b0 + u * STEP + 4 * half;
+        const bool in = n0 < terms;  // a multiple of 4: the four terms of a lane are in or out together
+        const int n = in ? n0 : 0;
+        const gen_f32x4 v = raw_to_f32(x[u]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float y = TAPS == 3 ? b((n + i) / 3, (n + i) % 3) : b(n / TAPS + i / TAPS, i % TAPS);
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? v[i] : 0.f, in ? y : 0.f, acc, 0, 0, 0);
+        }
+      }
+    }
+    if (r0 + 32 < rows) request(r0 + 32, first);
+    gp_sum(acc, red, [&](int r, int column, float sum) {
+      if (r0 + r < rows) out(r0 + r, column, sum);
+    });
   }
 }
 

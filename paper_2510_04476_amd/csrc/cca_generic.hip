@@ -113,11 +113,13 @@ hipError_t gemm_generic(bool bf16, const void *A, const void *Bm, void *C, long 
 }
 
 // ---------------------------------------------------------------------------
-// Prologue: one workgroup per head and 32 tokens of a sequence.  Heads 0..Hq-1 are query heads,
+// Prologue: one workgroup per head and TOK = 32 or 8 tokens of a sequence (generic_prologue_takes_8).  Heads 0..Hq-1 are query heads,
 // Hq..Hq+Hk-1 key heads, Hq+Hk..Hq+2Hk-1 value heads.  conv2_seq+ch is a product on the fp32 matrix cores (outputs x tokens),
-// its terms (input, tap) dealt to the four wavefronts, so a filter is read once per 32 tokens.
-// fp32, us, a workgroup per token on the vector ALU -> this: 1000 tokens, 2 / 2 heads of 32 21.3 -> 9.0; 500, 2 / 2 x 64 36.0 -> 14.7;
-// 4096, 4 / 2 x 128 1418 -> 72.
+// its terms (input, tap) dealt to the four wavefronts, so a filter is read once per workgroup.  What bounds it is the chain of its
+// loads and, on few workgroups, the instructions of one wavefront per SIMD: loads of several channels and of the next outputs' filter rows in
+// flight, no division in a loop.  A narrow head (d_h <= 16) keeps fewer in flight, for more wavefronts to a CU.
+// us, a workgroup per token on the vector ALU -> this: fp32, 1000 tokens, 2 / 2 heads of 32 21.4 -> 7.4; 500, 2 / 2 x 64 36.2 -> 10.4;
+// 4096, 4 / 2 x 128 1422 -> 45; bf16, 64 tokens, 2 / 2 x 40 12.0 -> 9.0; x 200 46.9 -> 34.4; with k_ch = 1 25.5 -> 24.1.
 // ---------------------------------------------------------------------------
 struct PrologueArgs {
   int T, Hq, Hk, dh, R, e_q, e_kv, n_lat, v_half, k_seq, k_ch;
@@ -125,16 +127,17 @@ struct PrologueArgs {
   float rope_base, norm_eps;
 };
 
-template <typename T>
+template <typename T, int TOK, bool NARROW>
 __global__ __launch_bounds__(GP_NT) void prologue_generic_kernel(PrologueArgs a, const T *__restrict__ lat, const T *__restrict__ w0,
                                                                 const T *__restrict__ w1, const float *__restrict__ temp,
                                                                 T *__restrict__ q, T *__restrict__ k, T *__restrict__ v,
                                                                 float *__restrict__ rnorm, unsigned block0) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
   const int head = blockIdx.y, dh = a.dh, tid = threadIdx.x;
-  const unsigned tiles = (a.T + GP_TOK - 1) / GP_TOK, block = block0 + blockIdx.x;
+  constexpr int LANES = GP_NT / TOK, U = NARROW ? 2 : 4;  // lanes of a token; channels of a lane whose loads are in flight together
+  const unsigned tiles = (a.T + TOK - 1) / TOK, block = block0 + blockIdx.x;
   const long long row0 = (long long)(block / tiles) * a.T;  // the sequence's first row
-  const int t0 = block % tiles * GP_TOK, n_tok = min(GP_TOK, a.T - t0);
+  const int t0 = block % tiles * TOK, n_tok = min(TOK, a.T - t0);
 
   if (head >= a.Hq + a.Hk) {  // value head: copy, second stream delayed by one token
     const int g = head - a.Hq - a.Hk;
@@ -152,83 +155,109 @@ __global__ __launch_bounds__(GP_NT) void prologue_generic_kernel(PrologueArgs a,
   const int ch0 = is_q ? head * dh : a.e_q + (head - a.Hq) * dh;  // first packed q|k channel of this head
   const int kc = (a.flags & CCA_CONV_CH) ? a.k_ch : 1;
   const int ks = (a.flags & CCA_CONV_SEQ) ? a.k_seq : 1;
-  const int rows = GP_TOK + kc - 1, ldy = dh + 1;
+  const int rows = TOK + kc - 1, ldy = dh + 1;
   float *const y0 = sm;                                    // [rows][ldy]: conv1_seq output from token t0 - (kc - 1) on
-  float *const z = y0 + rows * ldy;                        // [32][ldy]
-  float *const sa = z + GP_TOK * ldy, *const red = sa + GP_TOK * dh;  // cos, sin | sums of the wavefronts
+  float *const z = y0 + rows * ldy;                        // [TOK][ldy]
+  float *const sa = z + TOK * ldy, *const red = sa + TOK * dh;  // cos, sin | sums of the wavefronts
 
   // conv1_seq output at the time steps conv2 needs (zero before the sequence start)
-  for (int id = tid; id < rows * dh; id += GP_NT) {
-    const int i = id % dh, tj = t0 - (kc - 1) + id / dh;
-    float acc = 0.f;
-    if (tj >= 0 && tj < a.T) {
-      if (a.flags & CCA_CONV_SEQ) {
-        for (int jj = 0; jj < ks; ++jj) {
-          const int ts = tj - (ks - 1) + jj;
-          if (ts >= 0) acc = fmaf(load_f(w0 + (long long)(ch0 + i) * ks + jj), load_f(lat + (row0 + ts) * a.n_lat + ch0 + i), acc);
-        }
-      } else {
-        acc = load_f(lat + (row0 + tj) * a.n_lat + ch0 + i);
+  // The kc - 1 tokens before the first are dealt to all threads.
+  const int x = tid / LANES, ln = tid % LANES, t = t0 + x;
+  const long long row = row0 + min(t, a.T - 1);
+  const bool mean = a.flags & CCA_QK_MEAN;  // z starts as the mean of the row's streams
+  const T *const lat_row = lat + row * a.n_lat, *const other = lat_row + (is_q ? a.e_q + head / a.R * dh : (head - a.Hq) * a.R * dh);
+  const int n_other = is_q ? 1 : a.R;  // key heads: their query heads
+  gp_taps(ks, [&](auto taps_c) __attribute__((always_inline)) {
+    constexpr int TAPS = decltype(taps_c)::value;
+    const bool conv = a.flags & CCA_CONV_SEQ;
+    struct Token {  // the rows its taps read: those outside the sequence are read from the nearest and dropped
+      const T *row[TAPS];
+      bool in[TAPS];
+    };
+    auto token = [&](int tj) __attribute__((always_inline)) {
+      Token k;
+#pragma unroll
+      for (int jj = 0; jj < TAPS; ++jj) {
+        const int ts = tj - (TAPS - 1) + jj;
+        k.row[jj] = lat + (row0 + min(max(ts, 0), a.T - 1)) * a.n_lat + ch0;
+        k.in[jj] = ts >= 0 && tj < a.T;
       }
+      return k;
+    };
+    const T *const f0 = conv ? w0 + (long long)ch0 * TAPS : w0;
+    auto element = [&](const Token &k, int i) __attribute__((always_inline)) {
+      float v[TAPS], f[TAPS], acc = 0.f;
+#pragma unroll
+      for (int jj = 0; jj < TAPS; ++jj) v[jj] = load_f(k.row[jj] + i), f[jj] = conv ? load_f(f0 + i * TAPS + jj) : 1.f;
+#pragma unroll
+      for (int jj = 0; jj < TAPS; ++jj) acc = k.in[jj] ? (conv ? fmaf(f[jj], v[jj], acc) : v[jj]) : acc;
+      return acc;
+    };
+    const Token now = token(t0 + x);
+    float *const to = y0 + (kc - 1 + x) * ldy;
+    for (int i0 = ln; i0 < dh; i0 += U * LANES) {  // (past the head its last channel again)
+      float y[U], own[U], sum[U];
+      int at[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum[u] = 0.f, at[u] = min(i0 + u * LANES, dh - 1);
+#pragma unroll
+      for (int u = 0; u < U; ++u) own[u] = load_f(lat_row + ch0 + at[u]);
+      if (mean) {
+#pragma unroll 4
+        for (int r = 0; r < n_other; ++r)
+#pragma unroll
+          for (int u = 0; u < U; ++u) sum[u] += load_f(other + r * dh + at[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) y[u] = element(now, at[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + u * LANES < dh) {
+          to[at[u]] = y[u];
+          z[x * ldy + at[u]] = mean ? 0.5f * (is_q ? own[u] + sum[u] : sum[u] / (float)a.R + own[u]) : 0.f;
+        }
     }
-    y0[id / dh * ldy + i] = acc;
-  }
-  if (a.flags & CCA_ROPE) rope_angles(sa, a.rope_base, dh, t0, GP_TOK);
+    for (int i = tid; i < (kc - 1) * dh; i += GP_NT) {
+      const int r = (i >= dh) + (i >= 2 * dh);
+      y0[r * ldy + i - r * dh] = element(token(t0 - (kc - 1) + r), i - r * dh);
+    }
+  });
+  if (a.flags & CCA_ROPE) rope_angles(sa, a.rope_base, dh, t0, TOK);
   __syncthreads();
   if (a.flags & CCA_CONV_CH) {
-    const int l32 = tid & 31;
-    for (int o0 = 0; o0 < dh; o0 += 32) {
-      const int o = o0 + l32 < dh ? o0 + l32 : dh - 1;  // past the head: results not kept
-      const T *const wp = w1 + ((long long)head * dh + o) * dh * kc;
-      const gen_f32x16 acc = gp_product(
-          dh * kc, [&](int n) { return load_f(wp + n); }, [&](int n) { return y0[(l32 + n % kc) * ldy + n / kc]; });
-      gp_sum(acc, red, [&](int r, int tok, float sum) {
-        if (o0 + r < dh) z[tok * ldy + o0 + r] = sum;
-      });
-    }
+    const T *const wh = w1 + (long long)head * dh * dh * kc;
+    gp_taps(kc, [&](auto taps_c) __attribute__((always_inline)) {
+      constexpr int TAPS = decltype(taps_c)::value;
+      const int column = min(tid & 31, TOK - 1);  // (8 tokens: the other columns repeat the last)
+      gp_product<TAPS, NARROW ? 2 : 8>(
+          dh, dh, red, [&](int o, int n) { return raw4(wh + o * dh * TAPS + n); }, [&](int c, int j) { return y0[(column + j) * ldy + c]; },
+          [&](int o, int tok, float sum) {
+            if (tok < TOK) z[tok * ldy + o] = mean ? sum + z[tok * ldy + o] : sum;
+          });
+    });
   } else {
-    for (int id = tid; id < GP_TOK * dh; id += GP_NT) z[id / dh * ldy + id % dh] = y0[id / dh * ldy + id % dh];
+    for (int o = ln; o < dh; o += LANES) z[x * ldy + o] = mean ? y0[x * ldy + o] + z[x * ldy + o] : y0[x * ldy + o];
   }
   __syncthreads();
-  // 8 lanes to a token: mean, norm
-  static_assert(GP_NT == 8 * GP_TOK, "lanes of a token");
-  const int x = tid >> 3, l8 = tid & 7, t = t0 + x;
-  const long long row = row0 + min(t, a.T - 1);
   float ssq = 0.f;
 #pragma unroll 4
-  for (int o = l8; o < dh; o += 8) {
-    float y = z[x * ldy + o];
-    if (a.flags & CCA_QK_MEAN) {
-      float m;
-      if (is_q) {
-        m = 0.5f * (load_f(lat + row * a.n_lat + head * dh + o) +
-                    load_f(lat + row * a.n_lat + a.e_q + (head / a.R) * dh + o));
-      } else {
-        const int g = head - a.Hq;
-        float sq = 0.f;
-        for (int r = 0; r < a.R; ++r) sq += load_f(lat + row * a.n_lat + (g * a.R + r) * dh + o);
-        m = 0.5f * (sq / (float)a.R + load_f(lat + row * a.n_lat + a.e_q + g * dh + o));
-      }
-      y += m;
-      z[x * ldy + o] = y;
-    }
-    ssq = fmaf(y, y, ssq);
-  }
+  for (int o = ln; o < dh; o += LANES) ssq = fmaf(z[x * ldy + o], z[x * ldy + o], ssq);
 #pragma unroll
-  for (int e = 1; e < 8; e *= 2) ssq += __shfl_xor(ssq, e);
+  for (int e = 1; e < LANES; e *= 2) ssq += __shfl_xor(ssq, e);
   float mul = 1.f;
   if (a.flags & CCA_QK_NORM) {
     mul = sqrtf((float)dh) / sqrtf(ssq + a.norm_eps);
     if (!is_q && (a.flags & CCA_KEY_TEMP)) mul *= expf(temp[head - a.Hq]);
   }
-  if (rnorm && l8 == 0 && t < a.T) rnorm[row * (a.Hq + a.Hk) + head] = mul;
+  if (rnorm && ln == 0 && t < a.T) rnorm[row * (a.Hq + a.Hk) + head] = mul;
   __syncthreads();
   if (t >= a.T) return;
   T *const dst = is_q ? q + row * a.e_q + head * dh : k + row * a.e_kv + (head - a.Hq) * dh;
   if (a.flags & CCA_ROPE) {
     const int half = dh / 2;
     const bool il = a.flags & CCA_ROPE_INTERLEAVED;
-    for (int p = l8; p < half; p += 8) {
+#pragma unroll 2
+    for (int p = ln; p < half; p += LANES) {
       const int first = il ? 2 * p : p, second = il ? 2 * p + 1 : p + half;
       const float cs = sa[2 * (x * half + p)], sn = sa[2 * (x * half + p) + 1];
       const float u = z[x * ldy + first] * mul, w = z[x * ldy + second] * mul;
@@ -236,7 +265,7 @@ __global__ __launch_bounds__(GP_NT) void prologue_generic_kernel(PrologueArgs a,
       store_f(dst + second, w * cs + u * sn);
     }
   } else {
-    for (int o = l8; o < dh; o += 8) store_f(dst + o, z[x * ldy + o] * mul);
+    for (int o = ln; o < dh; o += LANES) store_f(dst + o, z[x * ldy + o] * mul);
   }
 }
 
@@ -245,20 +274,23 @@ hipError_t prologue_generic(const Dims &d, const cca_weights &w, const void *lat
   PrologueArgs a{d.T, d.Hq, d.Hk, d.dh, d.R, d.e_q, d.e_kv, d.n_lat, d.v_half, d.k_seq, d.k_ch, d.flags, d.rope_base,
                  d.norm_eps};
   const int kc = (d.flags & CCA_CONV_CH) ? d.k_ch : 1;
-  const size_t smem = sizeof(float) * ((size_t)(2 * GP_TOK + kc - 1) * (d.dh + 1) + (size_t)GP_TOK * d.dh + GP_RED);
-  auto run = [&](auto kernel, auto *lat_, auto *q_, auto *k_, auto *v_, auto *w0, auto *w1) {
-    return gp_launches(d.B, d.T, [&](unsigned first, unsigned blocks) {
-      kernel<<<dim3(blocks, d.Hq + 2 * d.Hk), GP_NT, smem, s>>>(a, lat_, w0, w1, w.temp, q_, k_, v_, rnorm, first);
+  auto run = [&](auto tok_c, auto narrow_c, auto t) {
+    using T = decltype(t);
+    constexpr int TOK = decltype(tok_c)::value;
+    constexpr bool NARROW = decltype(narrow_c)::value;
+    const size_t smem = sizeof(float) * ((size_t)(2 * TOK + kc - 1) * (d.dh + 1) + (size_t)TOK * d.dh + GP_RED);
+    if (hipError_t e = raise_lds_limit<prologue_generic_kernel<T, TOK, NARROW>>(GP_MAX_LDS); e != hipSuccess) return e;
+    return gp_launches(d.B, d.T, TOK, [&](unsigned first, unsigned blocks) {
+      prologue_generic_kernel<T, TOK, NARROW><<<dim3(blocks, d.Hq + 2 * d.Hk), GP_NT, smem, s>>>(
+          a, (const T *)lat, (const T *)w.w_conv_seq, (const T *)w.w_conv_ch, w.temp, (T *)q, (T *)k, (T *)v, rnorm, first);
     });
   };
-  if (d.bf16) {
-    if (hipError_t e = raise_lds_limit<prologue_generic_kernel<bf16_t>>(GP_MAX_LDS); e != hipSuccess) return e;
-    return run(prologue_generic_kernel<bf16_t>, (const bf16_t *)lat, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v,
-               (const bf16_t *)w.w_conv_seq, (const bf16_t *)w.w_conv_ch);
-  }
-  if (hipError_t e = raise_lds_limit<prologue_generic_kernel<float>>(GP_MAX_LDS); e != hipSuccess) return e;
-  return run(prologue_generic_kernel<float>, (const float *)lat, (float *)q, (float *)k, (float *)v, (const float *)w.w_conv_seq,
-             (const float *)w.w_conv_ch);
+  auto run_narrow = [&](auto tok_c, auto t) { return d.dh <= 16 ? run(tok_c, std::true_type{}, t) : run(tok_c, std::false_type{}, t); };
+  auto run_tok = [&](auto t) {
+    return generic_prologue_takes_8(d.B, d.T, d.Hq + d.Hk) ? run_narrow(std::integral_constant<int, 8>{}, t)
+                                                               : run_narrow(std::integral_constant<int, 32>{}, t);
+  };
+  return d.bf16 ? run_tok(bf16_t{}) : run_tok(float{});
 }
 
 // ---------------------------------------------------------------------------

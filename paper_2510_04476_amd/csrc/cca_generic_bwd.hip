@@ -362,9 +362,9 @@ struct ProBwdArgs {
 // then (CONV_CH) conv2_seq+ch transposed: d1[t,h,i] = sum_j sum_o w1[h,o,i,j] d3[t + (k_ch-1-j), h, o] within the sequence.
 // Workgroup = one q or k head x 32 tokens of a sequence, whose d3 rows (and the k_ch - 1 after them, formed again by the next
 // workgroup) stay in LDS for the convolution, a product on the fp32 matrix cores with its terms (j, o) dealt to the four
-// wavefronts.  With the gradients below, fp32, us, a workgroup per token and unsplit sums -> this: 1000 tokens, 2 / 2 heads of 32
-// 83.7 -> 21.3; 4096, 4 / 2 x 128 710 -> 193.
-template <typename T>
+// wavefronts (gp_product).  With the gradients below, us, a workgroup per token and unsplit sums -> this: fp32, 1000 tokens, 2 / 2 heads of 32
+// 81.9 -> 20.7; 4096, 4 / 2 x 128 710 -> 164; 64 tokens, 2 / 2 x 256 69.0 -> 64.7; bf16, 64, 2 / 2 x 200 60.1 -> 53.3.
+template <typename T, bool NARROW>
 __global__ __launch_bounds__(GP_NT) void pro_bwd_point_generic_kernel(ProBwdArgs a, const T *__restrict__ q, const T *__restrict__ k,
                                                                      const float *__restrict__ rnorm,
                                                                      const float *__restrict__ temp, const T *__restrict__ dq,
@@ -389,12 +389,14 @@ __global__ __launch_bounds__(GP_NT) void pro_bwd_point_generic_kernel(ProBwdArgs
     const bool in = t < a.T;
     const long long row = row0 + (in ? t : a.T - 1);
     float dot = 0.f;
+#pragma unroll 8
     for (int o = l8; o < dh; o += 8) dot = fmaf(load_f(y5 + row * ldq + o), load_f(dy5 + row * ldq + o), dot);
 #pragma unroll
     for (int e = 1; e < 8; e *= 2) dot += __shfl_xor(dot, e);
     if (!is_q && rowdot && in && x < GP_TOK && l8 == 0) rowdot[row * a.Hk + g] = dot;
     const bool norm = a.flags & CCA_QK_NORM;
     const float c = norm ? dot / ((float)dh * beta2) : 0.f, mul = norm ? rnorm[row * (a.Hq + a.Hk) + head] : 1.f;
+#pragma unroll 8
     for (int o = l8; o < dh; o += 8)
       sx[x * ldy + o] = in ? (load_f(dy5 + row * ldq + o) - load_f(y5 + row * ldq + o) * c) * mul : 0.f;
   }
@@ -402,33 +404,39 @@ __global__ __launch_bounds__(GP_NT) void pro_bwd_point_generic_kernel(ProBwdArgs
   if (a.flags & CCA_ROPE) {
     // forward: (a, b) -> (a c - b s, b c + a s); adjoint rotates back
     const int half = dh / 2;
-    for (int id = tid; id < rows * half; id += GP_NT) {
-      const int x = id / half, p = id % half;
-      const bool il = a.flags & CCA_ROPE_INTERLEAVED;
-      float *const f = sx + x * ldy + (il ? 2 * p : p), *const e = f + (il ? 1 : half);
-      const float cs = sa[2 * id], sn = sa[2 * id + 1], u = *f, v = *e;
-      *f = u * cs + v * sn;
-      *e = v * cs - u * sn;
-    }
+    for (int x = tid >> 3; x < rows; x += GP_NT / 8)
+      for (int p = tid & 7; p < half; p += 8) {
+        const bool il = a.flags & CCA_ROPE_INTERLEAVED;
+        float *const f = sx + x * ldy + (il ? 2 * p : p), *const e = f + (il ? 1 : half);
+        const float cs = sa[2 * (x * half + p)], sn = sa[2 * (x * half + p) + 1], u = *f, v = *e;
+        *f = u * cs + v * sn;
+        *e = v * cs - u * sn;
+      }
     __syncthreads();
   }
-  for (int id = tid; id < GP_TOK * dh; id += GP_NT) {
-    const int x = id / dh, o = id % dh;
-    if (t0 + x < a.T) d3[(row0 + t0 + x) * ld + ch0 + o] = sx[x * ldy + o];
-  }
+  if (const int x = tid >> 3; t0 + x < a.T)
+    for (int o = tid & 7; o < dh; o += 8) d3[(row0 + t0 + x) * ld + ch0 + o] = sx[x * ldy + o];
   if (!(a.flags & CCA_CONV_CH)) return;
-  const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const T *const wh = w1 + (long long)head * dh * dh * kc;
-  for (int i0 = 0; i0 < dh; i0 += 32) {
-    const int i = i0 + l32 < dh ? i0 + l32 : dh - 1;  // past the head: results not stored
-    // term n = o * k_ch + j, output channel o of the forward convolution and tap j
-    const gen_f32x16 acc = gp_product(
-        dh * kc, [&](int n) { return load_f(wh + ((long long)(n / kc) * dh + i) * kc + n % kc); },
-        [&](int n) { return sx[(l32 + kc - 1 - n % kc) * ldy + n / kc]; });
-    gp_sum(acc, red, [&](int r, int tok, float sum) {
-      if (i0 + r < dh && t0 + tok < a.T) d1[(row0 + t0 + tok) * ld + ch0 + i0 + r] = sum;
-    });
-  }
+  gp_taps(kc, [&](auto taps_c) __attribute__((always_inline)) {  // terms: output channel o of the forward convolution, tap j
+    constexpr int TAPS = decltype(taps_c)::value;
+    const int l32 = tid & 31;
+    gp_product<TAPS, NARROW ? 2 : 8>(
+        dh, dh, red,
+        [&](int i, int n) {
+          Raw4<T> w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int o = TAPS == 3 ? (n + e) / 3 : n / TAPS + e / TAPS, j = TAPS == 3 ? (n + e) % 3 : e % TAPS;
+            w.v[e] = wh[(o * dh + i) * TAPS + j];
+          }
+          return w;
+        },
+        [&](int o, int j) { return sx[(l32 + TAPS - 1 - j) * ldy + o]; },
+        [&](int i, int tok, float sum) {
+          if (t0 + tok < a.T) d1[(row0 + t0 + tok) * ld + ch0 + i] = sum;
+        });
+  });
 }
 
 // conv1_seq transposed + qk-mean adjoint + value-shift adjoint: one thread per element of d_lat
@@ -686,12 +694,16 @@ static hipError_t prologue_bwd_generic_t(const Dims &d, const cca_weights &w, co
   const bool want1 = (d.flags & CCA_CONV_CH) && gr && gr->w_conv_ch, want0 = (d.flags & CCA_CONV_SEQ) && gr && gr->w_conv_seq;
   const int kc = (d.flags & CCA_CONV_CH) ? d.k_ch : 1, n_tok = GP_TOK + kc - 1;
   const size_t smem = sizeof(float) * ((size_t)n_tok * (d.dh + 1) + (size_t)n_tok * d.dh + GP_RED);
-  if (hipError_t e = raise_lds_limit<pro_bwd_point_generic_kernel<T>>(GP_MAX_LDS); e != hipSuccess) return e;
-  hipError_t e = gp_launches(d.B, d.T, [&](unsigned first, unsigned blocks) {
-    pro_bwd_point_generic_kernel<T><<<dim3(blocks, d.Hq + d.Hk), GP_NT, smem, s>>>(
-        a, (const T *)q, (const T *)k, rnorm, w.temp, (const T *)d_q, (const T *)d_k, (const T *)w.w_conv_ch, d3, d1,
-        want_temp ? rowdot : nullptr, first);
-  });
+  auto point = [&](auto narrow_c) {
+    constexpr bool NARROW = decltype(narrow_c)::value;
+    if (hipError_t e = raise_lds_limit<pro_bwd_point_generic_kernel<T, NARROW>>(GP_MAX_LDS); e != hipSuccess) return e;
+    return gp_launches(d.B, d.T, GP_TOK, [&](unsigned first, unsigned blocks) {
+      pro_bwd_point_generic_kernel<T, NARROW><<<dim3(blocks, d.Hq + d.Hk), GP_NT, smem, s>>>(
+          a, (const T *)q, (const T *)k, rnorm, w.temp, (const T *)d_q, (const T *)d_k, (const T *)w.w_conv_ch, d3, d1,
+          want_temp ? rowdot : nullptr, first);
+    });
+  };
+  hipError_t e = d.dh <= 32 ? point(std::true_type{}) : point(std::false_type{});
   if (e != hipSuccess) return e;
   const long long n = d.rows() * d.n_lat;
   pro_bwd_dlat_generic_kernel<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a, (const T *)w.w_conv_seq, d3, d1,

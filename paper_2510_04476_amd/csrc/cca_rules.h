@@ -305,6 +305,13 @@ inline bool generic_attention_bwd_16(long long BHk, int T, int dh, bool causal) 
   return blocks <= 128 || (blocks <= 200 && dh <= 64) || (causal && (dh <= 128 || blocks <= 200));
 }
 
+// ---- generic prologue: tokens of a workgroup, 32 or 8 ---------------------------------------------------------------------
+// The chain of a workgroup's loads before and after the convolution is four times shorter with 8 tokens, the convolution itself (32
+// columns of a matrix instruction either way) takes as long: the better form while its query and key heads are one round of the grid.
+// 32 -> 8 tokens, us (T, H_q + H_k, d_h, k_ch): 300, 6, 40, 1: 10.5 -> 8.7; 128, 10, 128, 2: 19.1 -> 15.8; 64, 32, 64, 2: 10.4 -> 8.9;
+// beyond a round 300, 10, 128, 2: 19.2 -> 21.3; 64, 40, 128, 2: 19.1 -> 21.9.
+inline bool generic_prologue_takes_8(long long B, int T, int heads) { return B * ((T + 7) / 8) * heads <= 256; }
+
 // ---- generic filter gradients: workgroups over the rows of each unit of outputs ------------------------------------------
 // About one workgroup per CU, none with fewer than 64 rows (a round of its wavefronts); the sums of the splits are added by a
 // second launch, so a grid that fills the chip by itself is not split.

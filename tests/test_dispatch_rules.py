@@ -152,7 +152,15 @@ def test_generic_cases_reach_every_form():
         tiles = -(-c["dh"] // 32)
         splits.add(rules.grad_splits(tiles * tiles * (c["Hq"] + c["Hk"]) * c["k_ch"], c["B"] * c["T"]))
     assert rows == set(rules.GENERIC_ROWS) and bwd == {True, False}
+    assert {(rules.generic_prologue_takes_8(c["B"], c["T"], c["Hq"] + c["Hk"]), c["dh"] <= 16, c["dh"] <= 32) for c in small.GENERIC_CASES} == {
+        (few, *narrow) for few in (True, False) for narrow in ((True, True), (False, True), (False, False))}
     assert 1 in splits and 2 in splits and max(splits) >= 16
+
+
+# T, query and key heads and us of the prologue with 32 tokens a workgroup, with 8
+@pytest.mark.parametrize("T,heads,us32,us8", [(300, 6, 10.5, 8.7), (128, 10, 19.1, 15.8), (64, 32, 10.4, 8.9), (300, 10, 19.2, 21.3), (64, 40, 19.1, 21.9)])
+def test_generic_prologue_form_is_the_faster(T, heads, us32, us8):
+    assert rules.generic_prologue_takes_8(1, T, heads) == (us8 < us32)
 
 
 # T, batch x query heads, d_h, causal and us of 32 rows, of 16
