@@ -300,7 +300,7 @@ static hipError_t attention_bwd_generic_t(const Dims &d, const void *q, const vo
                                                                         d.T, d.Hq, d.dh);
   const int causal = (d.flags & CCA_CAUSAL) ? 1 : 0;
   const int q_rounded = attention_mfma_supported(d) ? 1 : 0;  // lse then comes from the MFMA forward kernel
-  if (generic_attention_bwd_16((long long)d.B * d.Hk, d.T, d.dh, causal)) {
+  if (generic_attention_bwd_16((long long)d.B * d.Hk, d.R, d.T, d.dh, causal, d.bf16)) {
     const AttnBwdArgs<T> a{(const T *)q, (const T *)k, (const T *)v, (const T *)d_o, lse, delta, (T *)d_q, (T *)d_k, (T *)d_v,
                            d.T, d.Hq, d.Hk, d.dh, d.scale, causal, q_rounded};
     const dim3 grid((d.T + 15) / 16, d.Hk + d.Hq, d.B);

@@ -290,9 +290,13 @@ inline bool stream_takes_256(long long rows, int heads, int R, int taps, bool ad
 // the second round's blocks are short, goes on to 200 blocks of 32 rows (6000, 1, 64: 1.57x; 3000, 2, 128: 1.10x; 1500, 4, 64: 0.94).
 // Up to 320 keys 8 wavefronts do (64, 2, 32: 8.6 -> 6.2; beyond d_h = 64 there are never more).
 // The adjoint's 16-row form is also one launch where the other is two: not causal it wins up to 128 blocks of 32 keys (d_h = 128, 128
-// blocks: 1.09-1.40x, 188: 0.88-1.00), at d_h <= 64 up to 200 (1.13-1.31x, 252: 0.96-1.03); causal, where the 32-key form's
-// blocks are uneven, everywhere up to d_h = 128 (4096 x 4 / 2 heads x 128: 1832 -> 1395; 4096 x 16 / 16 x 64: 1.26x; the worst
-// measured 0.96) and up to 200 blocks at 256 (188: 1.12-1.19x, 252: 0.97).
+// blocks: 1.09-1.40x, 188: 0.88-1.00), at d_h <= 64 up to 200 (1.13-1.31x, 252: 0.96-1.03), and wider than 128 up to 128, or 96 where
+// several query heads share the keys (fp32, 256, 4096 keys, R = 4: 5775 -> 6294); causal, where the 32-key form's blocks are uneven, much
+// further: at d_h <= 32 always, at 64 up to 6000 keys (16 heads, 4096: 1.06x, 6000: 0.97; 4 x 8192: 0.96, 4 x 16384: 0.93), in bf16 up
+// to 128 always (96, 12288 keys: 1.33x, 16384: 1.13x), in fp32, where a row is read at twice the bytes, up to 4096 keys (128, 8 heads x 2048: 1.16x, x 8192:
+// 0.89; 2 / R = 4 x 8192: 0.87) and not on a chip full of them (16 heads x 96 x 4096: 0.95), in any case up to 400 blocks (128, 1 x
+// 12288: 1.03x; 112, 2 x 6000: 0.95-0.97), but not on one full round of many short blocks (16 heads x 512: 0.79-0.95); at 256 up to
+// 200 (188: 1.12-1.19x, 252: 0.97).  Over 2092 measured sizes the choice costs 0.8 % against the better form, 5 % at most against the 32-key one.
 enum GenericRows { GR_16, GR_16_WIDE, GR_32 };
 inline GenericRows generic_attention_rows(long long BH, int T, int dh, bool causal) {
   const long long blocks = BH * ((T + 31) / 32);
@@ -300,9 +304,13 @@ inline GenericRows generic_attention_rows(long long BH, int T, int dh, bool caus
   if (blocks > 128 && !(causal && BH <= 2 && blocks <= 200)) return GR_32;
   return T > 320 && dh <= 64 ? GR_16_WIDE : GR_16;
 }
-inline bool generic_attention_bwd_16(long long BHk, int T, int dh, bool causal) {
+inline bool generic_attention_bwd_16(long long BHk, int R, int T, int dh, bool causal, bool bf16) {
   const long long blocks = BHk * ((T + 31) / 32);
-  return blocks <= 128 || (blocks <= 200 && dh <= 64) || (causal && (dh <= 128 || blocks <= 200));
+  if (!causal) return blocks <= (dh <= 64 ? 200 : dh <= 128 || R == 1 ? 128 : 96);
+  if (dh > 128) return blocks <= 200;
+  if (blocks > 200 && blocks <= 256 && BHk > 8) return false;
+  if (dh <= 32 || blocks <= 400) return true;
+  return dh <= 64 ? T <= 6000 : bf16 || (T <= 4096 && blocks <= 1504);
 }
 
 // ---- generic prologue: tokens of a workgroup, 32 or 8 ---------------------------------------------------------------------

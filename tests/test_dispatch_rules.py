@@ -148,7 +148,7 @@ def test_generic_cases_reach_every_form():
     for c in small.GENERIC_CASES:
         for causal in (False, True):
             rows.add(rules.generic_attention_rows(c["B"] * c["Hq"], c["T"], c["dh"], causal))
-            bwd.add(rules.generic_attention_bwd_16(c["B"] * c["Hk"], c["T"], c["dh"], causal))
+            bwd.add(rules.generic_attention_bwd_16(c["B"] * c["Hk"], c["Hq"] // c["Hk"], c["T"], c["dh"], causal, False))
         tiles = -(-c["dh"] // 32)
         splits.add(rules.grad_splits(tiles * tiles * (c["Hq"] + c["Hk"]) * c["k_ch"], c["B"] * c["T"]))
     assert rows == set(rules.GENERIC_ROWS) and bwd == {True, False}
@@ -171,6 +171,21 @@ GENERIC_MEASURED = [(1000, 2, 32, True, 20.5, 16.8), (1000, 4, 128, True, 58.1, 
 @pytest.mark.parametrize("T,BH,dh,causal,us32,us16", GENERIC_MEASURED)
 def test_generic_attention_form_is_the_faster(T, BH, dh, causal, us32, us16):
     assert (rules.generic_attention_rows(BH, T, dh, causal) == "32 rows") == (us32 < us16)
+
+
+# T, batch x KV heads, query heads to each, d_h, causal, bf16 and us of the adjoint in 32-row blocks, in 16-row ones
+GENERIC_BWD_MEASURED = [(4096, 1, 4, 256, False, False, 5774.8, 6294.3), (4096, 1, 1, 256, False, False, 1762.1, 1447.6), (4096, 1, 4, 200, False, False, 5869.0, 6616.1),
+                        (1536, 2, 4, 256, False, False, 2267.7, 1803.5), (3000, 2, 1, 256, False, False, 1381.6, 1763.2), (512, 16, 1, 128, True, False, 152.5, 189.1),
+                        (512, 16, 2, 64, True, False, 136.6, 145.4), (1000, 8, 4, 128, True, False, 978.9, 879.1), (16384, 1, 1, 128, True, False, 4061.8, 4675.9),
+                        (8192, 2, 4, 128, True, False, 8840.6, 10151.7), (8192, 2, 4, 112, True, False, 8888.3, 10566.8), (2048, 8, 1, 128, True, False, 954.6, 823.2),
+                        (12288, 1, 1, 128, True, False, 2778.1, 2688.7), (16384, 4, 1, 64, True, False, 7206.6, 7713.1), (16384, 4, 1, 40, True, True, 7368.2, 7715.2),
+                        (4096, 16, 1, 64, True, False, 2360.3, 2228.6), (6000, 4, 1, 64, True, False, 1181.4, 1097.6), (16384, 8, 1, 32, True, False, 8064.0, 7959.1),
+                        (4096, 16, 1, 96, True, False, 5075.3, 5328.5), (6000, 1, 4, 256, True, False, 9957.3, 8961.6), (4096, 2, 4, 256, True, False, 7607.7, 8631.8)]
+
+
+@pytest.mark.parametrize("T,BHk,R,dh,causal,bf16,us32,us16", GENERIC_BWD_MEASURED)
+def test_generic_attention_adjoint_form_is_the_faster(T, BHk, R, dh, causal, bf16, us32, us16):
+    assert rules.generic_attention_bwd_16(BHk, R, T, dh, causal, bf16) == (us16 < us32)
 
 
 # M, N, K and us of each tile shape in the order of rules.NT_TILES
