@@ -30,9 +30,7 @@ __global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict
   const int n = n0 + l32 < N ? n0 + l32 : N - 1;
   gen_f32x16 acc = zero16();
   const long long last = K - 1;
-  // AHEAD blocks of 8 terms in flight (the compiler does not unroll a loop of MFMAs whose count it does not know).  Four where the
-  // chain of a wavefront is what a small grid waits for (256 x 192 over 1000 tokens 12.1 -> 6.5 us); a large one hides its loads behind more
-  // wavefronts, which four blocks' registers do not leave (4096 x 1024 over 512: 62.5 us with one, 66.6 with four).
+  // AHEAD blocks of 8 terms in flight (the compiler does not unroll a loop of MFMAs whose count it does not know): generic_product_looks_ahead
   for (long long b0 = wave * 8; b0 < K; b0 += AHEAD * GG_WAVES * 8) {
     float a[AHEAD][4], b[AHEAD][4];
 #pragma unroll
@@ -89,7 +87,7 @@ static hipError_t gemm_generic_t(const void *A, long long lda, bool ta, const vo
   for (long long t = 0; t < tiles; t += GG_GRID) {  // one launch below 2^32 outputs; a second grid dimension cost 0.2 of 2.8 us
     const unsigned grid = (unsigned)(tiles - t < GG_GRID ? tiles - t : GG_GRID);
 #define GO(TA, TB)                                                                                                        \
-  (tiles <= 1024 ? gemm_generic_kernel<T, TA, TB, 4> : gemm_generic_kernel<T, TA, TB, 1>)<<<grid, GG_NT, 0, s>>>(              \
+  (generic_product_looks_ahead(tiles, K) ? gemm_generic_kernel<T, TA, TB, 4> : gemm_generic_kernel<T, TA, TB, 1>)<<<grid, GG_NT, 0, s>>>(              \
       (const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K, (unsigned)t)
     if (ta && tb) GO(true, true);
     else if (ta) GO(true, false);

@@ -313,6 +313,13 @@ inline bool generic_attention_bwd_16(long long BHk, int R, int T, int dh, bool c
   return dh <= 64 ? T <= 6000 : bf16 || (T <= 4096 && blocks <= 1504);
 }
 
+// ---- generic product: blocks of terms that a wavefront has in flight, one or four ------------------------------------------
+// Its eight wavefronts take 64 terms a round, so four need 256 of them.  A small grid waits for the chain of a wavefront; a large one hides its
+// loads behind more wavefronts, which four blocks' registers do not leave.  One -> four, us or the gain (tiles of 32 x 32, terms): a weight
+// gradient of 48, 1000: 12.9 -> 12.4; 8 ... 256 tiles, 256 ... 2048 terms 1.03-1.10x, 384 and 512 tiles 0.99-1.10x; 1024 0.96-1.01x, 4096 0.91-0.96x;
+// 64 terms 0.87-0.99x, the fewer the more tiles; 192 terms, 256 tiles 4.31 -> 4.42.
+inline bool generic_product_looks_ahead(long long tiles, long long K) { return K >= 256 && tiles <= 512; }
+
 // ---- generic prologue: tokens of a workgroup, 32 or 8 ---------------------------------------------------------------------
 // The chain of a workgroup's loads before and after the convolution is four times shorter with 8 tokens, the convolution itself (32
 // columns of a matrix instruction either way) takes as long: the better form while its query and key heads are one round of the grid.

@@ -157,6 +157,22 @@ def test_generic_cases_reach_every_form():
     assert 1 in splits and 2 in splits and max(splits) >= 16
 
 
+# tiles, terms and us of the generic product with one block of terms in flight, with four
+@pytest.mark.parametrize("tiles,K,one,four", [(48, 1000, 12.9, 12.4), (192, 1024, 11.1, 10.6), (256, 512, 6.8, 6.5), (256, 192, 4.31, 4.42), (1024, 64, 5.1, 5.7),
+                                              (1536, 256, 15.6, 16.8), (2048, 1024, 62.1, 63.2), (3072, 512, 47.8, 50.6)])
+def test_generic_product_form_is_the_faster(tiles, K, one, four):
+    assert rules.generic_product_looks_ahead(tiles, K) == (four < one)
+
+
+def test_generic_cases_reach_both_products():
+    tiles = lambda m, n: -(-m // 32) * -(-n // 32)
+    ahead = set()
+    for c in small.GENERIC_CASES:
+        rows, n_lat = c["B"] * c["T"], (c["Hq"] + 2 * c["Hk"]) * c["dh"]
+        ahead |= {(False, rules.generic_product_looks_ahead(tiles(rows, n_lat), c["E"])), (True, rules.generic_product_looks_ahead(tiles(c["E"], n_lat), rows))}
+    assert ahead == {(transposed, four) for transposed in (False, True) for four in (False, True)}
+
+
 # T, query and key heads and us of the prologue with 32 tokens a workgroup, with 8
 @pytest.mark.parametrize("T,heads,us32,us8", [(300, 6, 10.5, 8.7), (128, 10, 19.1, 15.8), (64, 32, 10.4, 8.9), (300, 10, 19.2, 21.3), (64, 40, 19.1, 21.9)])
 def test_generic_prologue_form_is_the_faster(T, heads, us32, us8):
