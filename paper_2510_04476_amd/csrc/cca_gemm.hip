@@ -84,9 +84,9 @@ __device__ __forceinline__ bool tile_of(const TileGrid &g, int wg, int &tm, int 
   tn = p * g.panel + r - tm * width;
   return true;
 }
-TileGrid tile_grid(long long M, int N, int tm, int tn) {
+TileGrid tile_grid(long long M, int N, long long K, int tm, int tn) {
   const int tiles_m = (int)((M + tm - 1) / tm), tiles_n = (N + tn - 1) / tn;
-  return TileGrid{tiles_n, tiles_m * tiles_n, tile_panel(tiles_m, tiles_n, tm, tn)};
+  return TileGrid{tiles_n, tiles_m * tiles_n, tile_panel(tiles_m, tiles_n, tm, tn, K)};
 }
 
 // acc[ni][mi][r] = C[m][n] with m = wm*32*MI + mi*32 + l32 and n = wn*32*NI + ni*32 + 8*(r/4) + 4*half + r%4 of the tile
@@ -555,7 +555,7 @@ constexpr size_t deep_lds(int tm, int tn, int waves_k, int rows) {
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 hipError_t launch_tn_deep(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No, long long K,
                           hipStream_t s) {
-  const TileGrid grid = tile_grid(Mo, No, TM, TN);
+  const TileGrid grid = tile_grid(Mo, No, K, TM, TN);
   constexpr size_t smem = deep_lds(TM, TN, WAVES_K, STAGES * (TM + TN));
   constexpr auto kernel = gemm_bf16_tn_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>;
   if (hipError_t e = raise_lds_limit<kernel>(smem); e != hipSuccess) return e;
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 template <int TM, int BN, int WAVES_M, int WAVES_N>
 hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
                        hipStream_t s) {
-  const TileGrid grid = tile_grid(M, N, TM, BN);
+  const TileGrid grid = tile_grid(M, N, K, TM, BN);
   constexpr size_t epi_bytes = (size_t)TM * (BN * 2 + 16);
   constexpr size_t main_bytes = (size_t)(A_STAGES * TM + B_STAGES * BN) * BK * 2;
   constexpr size_t smem = main_bytes > epi_bytes ? main_bytes : epi_bytes;
@@ -739,7 +739,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WAVES_K * 64) void gemm_bf16_nt_d
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M, int N, int K, const ColumnSplit &split,
                             hipStream_t s) {
-  const TileGrid grid = tile_grid(M, N, TM, TN);
+  const TileGrid grid = tile_grid(M, N, K, TM, TN);
   constexpr size_t smem = deep_lds(TM, TN, WAVES_K, STAGES * WAVES_K * (TM + TN));
   if (hipError_t e = raise_lds_limit<gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES>>(smem); e != hipSuccess) return e;
   gemm_bf16_nt_deep_kernel<TM, TN, WAVES_M, WAVES_N, WAVES_K, STAGES><<<(grid.tiles + 7) / 8 * 8, WAVES_M * WAVES_N * WAVES_K * 64, smem, s>>>(
@@ -793,8 +793,8 @@ hipError_t launch_pair(NtArgs nt, TnArgs tn, bool nt_first, hipStream_t s) {
   constexpr size_t a = deep_lds(NT_::TM, NT_::TN, NT_::WK, NT_::ST * NT_::WK * (NT_::TM + NT_::TN)),
                    b = deep_lds(TN_::TM, TN_::TN, TN_::WK, TN_::ST * (TN_::TM + TN_::TN)), smem = a > b ? a : b;
   static_assert(smem <= 160 * 1024, "LDS");
-  nt.grid = tile_grid(nt.M, nt.N, NT_::TM, NT_::TN);
-  tn.grid = tile_grid(tn.Mo, tn.No, TN_::TM, TN_::TN);
+  nt.grid = tile_grid(nt.M, nt.N, nt.K, NT_::TM, NT_::TN);
+  tn.grid = tile_grid(tn.Mo, tn.No, tn.K, TN_::TM, TN_::TN);
   const int n_nt = (nt.grid.tiles + 7) / 8 * 8, n_tn = (tn.grid.tiles + 7) / 8 * 8;
   constexpr auto kernel = gemm_bf16_pair_kernel<NT_, TN_>;
   if (hipError_t e = raise_lds_limit<kernel>(smem); e != hipSuccess) return e;

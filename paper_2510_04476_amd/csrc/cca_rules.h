@@ -39,8 +39,12 @@ inline NtTile nt_tile(long long M, int N, int K, double *us = nullptr) {
 
 // ---- order of the tiles of a product ---------------------------------------------------------------------------------------
 // Each XCD gets a contiguous range of tiles, taken down panels of `panel` columns of tiles.  Its L2 has to bring in the rows of both
-// operands that its range touches (the first 32 tiles of it, one per CU): the panel width that makes the fewest of them.
-// Row by row -> in panels, us (rows x columns x contraction): 300 x 1536 x 2048 18.0 -> 15.0, 300 x 2048 x 1024 13.1 -> 10.8, 300 x 3072
+// operands that its range touches (the first 32 tiles of it, one per CU): the panel width that makes the fewest of them, unless row by row they
+// fit its 4 MB anyway.  There a panel saves nothing, and the next kernel finds its rows in other L2s than their reader's: whole prefill, us, row
+// by row -> in panels (tokens, E, H_q + 2 H_k, d_h; MB row by row of the two products): 1024, 1024, 20, 64 (2.8, 2.2): 26.9 -> 28.2 and 31.1
+// -> 32.4; 1024, 1536, 12, 64 (2.6, 1.2): 32.9 -> 33.9; above it 512, 2048, 48, 64 (12.2, 4.1): 41.2 -> 37.2; 200, 2048, 96, 64 (12.2, 4.2):
+// 35.3 -> 31.8; 1024, 2048, 32, 64 (8.5, 4.2): 46.7 -> 45.0.  The same with the weights of twelve layers in turn (0.94-0.98, 1.02-1.08x).
+// Row by row -> in panels, us (rows x columns x contraction): 300 x 1536 x 2048 18.0 -> 15.0, 300 x 3072
 // x 4096 32.8 -> 27.4 (64 x 64 tiles), 1000 x 2048 x 1024 16.7 -> 15.1 (64 x 128), 1000 x 4096 x 2048 34.8 -> 33.7, 12000 x 4096 x 2048
 // 209 -> 200 (256 x 256).  Tiles 128 columns wide and as high lost 1 ... 4 % where the panels save less than half of the rows (1531 x 1536
 // x 2048 27.1 -> 27.8) and keep the row order there.
@@ -96,7 +100,11 @@ struct TilePanel {
     return tn == 128 && tm >= 128 && 2 * least > row_major ? tiles_n : width;
   }
 };
-inline int tile_panel(int tiles_m, int tiles_n, int tm, int tn) { return (int)TilePanel(tiles_m, tiles_n, tm, tn).best(); }
+// Columns of a panel; `K`: terms of the contraction, two bytes each
+inline int tile_panel(int tiles_m, int tiles_n, int tm, int tn, long long K) {
+  const TilePanel p(tiles_m, tiles_n, tm, tn);
+  return (long long)p.touched((unsigned)tiles_n) * K * 2 <= 8 * (4ll << 20) ? tiles_n : (int)p.best();
+}
 
 // ---- weight gradients: C (Mo,No) = A (K,Mo)^T * B (K,No), bf16, K tokens -------------------------------------------------
 enum TnTile { TN_SPLIT, TN_64x64, TN_64x128, TN_128x128 };

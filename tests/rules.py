@@ -17,14 +17,14 @@ int r_nt_tile(long long M, int N, int K) { return nt_tile(M, N, K); }
 int r_tn_tile(int Mo, int No, long long K) { return tn_tile(Mo, No, K); }
 int r_tn_splits(int Mo, int No, long long K) { return tn_splits(Mo, No, K); }
 int r_prologue_is_short(long long rows, int heads, int R, int dh, int adjoint) { return prologue_is_short(rows, heads, R, dh, adjoint); }
-int r_tile_panel(int tiles_m, int tiles_n, int tm, int tn) { return tile_panel(tiles_m, tiles_n, tm, tn); }
+int r_tile_panel(int tiles_m, int tiles_n, int tm, int tn, long long K) { return tile_panel(tiles_m, tiles_n, tm, tn, K); }
 int r_panel_touches(int tiles_m, int tiles_n, int tm, int tn, int w) { return TilePanel(tiles_m, tiles_n, tm, tn).touched(w); }
 double r_tile_panel_us(int tiles_m, int tiles_n, int tm, int tn) {  // of one choice: the fastest of ten batches
   double least = 1e9;
   for (int batch = 0; batch < 10; ++batch) {
     volatile int sum = 0;
     const auto t0 = std::chrono::steady_clock::now();
-    for (int i = 0; i < 20; ++i) sum = sum + tile_panel(tiles_m, tiles_n, tm, tn);
+    for (int i = 0; i < 20; ++i) sum = sum + tile_panel(tiles_m, tiles_n, tm, tn, 1 << 20);
     const double us = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 1e6 / 20;
     least = us < least ? us : least;
   }
@@ -66,7 +66,7 @@ def _lib():
                         os.path.join(ROOT, "paper_2510_04476_amd", "csrc"), src, "-o", so], check=True)
         lib = C.CDLL(so)
     L, I = C.c_longlong, C.c_int
-    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_decode_up_lds=[L, I], r_decode_up_lds_limit=[], r_tile_panel=[I, I, I, I], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
+    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_decode_up_lds=[L, I], r_decode_up_lds_limit=[], r_tile_panel=[I, I, I, I, L], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
                            r_generic_attention_bwd_16=[L, I, I, I, I, I], r_generic_prologue_takes_8=[L, I, I], r_generic_product_looks_ahead=[L, L], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
@@ -92,8 +92,8 @@ def prologue_is_short(rows, heads, R, dh, adjoint):
     return bool(_lib().r_prologue_is_short(rows, heads, R, dh, adjoint))
 
 
-def tile_panel(tiles_m, tiles_n, tm, tn):
-    return _lib().r_tile_panel(tiles_m, tiles_n, tm, tn)
+def tile_panel(tiles_m, tiles_n, tm, tn, K):
+    return _lib().r_tile_panel(tiles_m, tiles_n, tm, tn, K)
 
 
 def panel_touches(tiles_m, tiles_n, tm, tn, width):

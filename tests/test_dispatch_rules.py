@@ -19,7 +19,7 @@ def test_projection_cases_reach_every_order_of_tiles():
         for N, K in (((Hq + 2 * Hk) * dh, E), (E, Hq * dh)):
             tm, tn = (int(x) for x in rules.nt_tile(M, N, K).split("x"))
             tiles_n = -(-N // tn)
-            panel = rules.tile_panel(-(-M // tm), tiles_n, tm, tn)
+            panel = rules.tile_panel(-(-M // tm), tiles_n, tm, tn, K)
             assert 1 <= panel <= tiles_n
             orders.add((tm <= 64, "rows" if panel == tiles_n else "whole panels" if tiles_n % panel == 0 else "a narrower one"))
     assert {(False, "rows")} | {(small_tile, o) for small_tile in (True, False) for o in ("whole panels", "a narrower one")} <= orders
@@ -59,8 +59,17 @@ def test_panels_touch_as_few_rows_as_any_width():
             for tiles_n in [*range(1, 34), 48, 64, 96, 177, 300]:
                 cost = {w: rules.panel_touches(tiles_m, tiles_n, tm, tn, w) for w in {-(-tiles_n // p) for p in range(1, tiles_n + 1)}}
                 kept = tn == 128 and tm >= 128 and 2 * min(cost.values()) > cost[tiles_n]  # the row order, by its own rule
-                panel = rules.tile_panel(tiles_m, tiles_n, tm, tn)
+                panel = rules.tile_panel(tiles_m, tiles_n, tm, tn, 1 << 20)
                 assert panel == tiles_n if kept else cost[panel] <= 1.02 * min(cost.values()), (tiles_m, tiles_n, tm, tn, panel)
+
+
+# rows, columns and terms of a product and whether it is taken row by row: what an XCD then brings in fits its 4 MB, or not
+@pytest.mark.parametrize("M,N,K,by_rows", [(1024, 1280, 1024, True), (1024, 1024, 1024, True), (1024, 768, 1536, True), (512, 3072, 2048, False),
+                                           (200, 6144, 2048, False), (1024, 2048, 2048, False), (300, 1536, 2048, False)])
+def test_products_that_fit_an_l2_keep_their_rows(M, N, K, by_rows):
+    tm, tn = (int(x) for x in rules.nt_tile(M, N, K).split("x"))
+    tiles_n = -(-N // tn)
+    assert (rules.tile_panel(-(-M // tm), tiles_n, tm, tn, K) == tiles_n) == by_rows
 
 
 # 512 x 1536 x 2048, 512 x 2048 x 1024, 128 x 12288 x 8192, 64 x 24576 x 16384, 64 x 16384 x 8192, 1 x 65536 x 65536, and long and wide
