@@ -304,10 +304,12 @@ __global__ __launch_bounds__(W0_IW * 8) void pro_bwd_unfold_w0_kernel(const floa
 int taps(const Dims &d) { return ((d.flags & CCA_CONV_SEQ) ? d.k_seq : 1) + d.k_ch - 1; }
 
 // Tokens per chunk of the filter-gradient kernel: the largest of 512..64 that still gives 80 workgroups.  They run beside the
-// adjoint's, and every chunk's sums (196 KB a head at d_h = 128) are written and read once more: with 256 workgroups and a unit's
+// adjoint's (at d_h = 256 in a launch of their own), and every chunk's sums (196 KB a head at d_h = 128) are written and read once more: with 256 workgroups and a unit's
 // last few chunks added one after the other the backward pass took (us, then now) 2 x 512 tokens, 8 query and 2 KV heads of 128:
 // 105.7, 99.5; 2 x 2048: 266.0, 251.6; 1 x 2048, 6 + 6 heads: 179.7, 165.3; 1 x 4096, 4 + 1 heads of 256: 638, 631; 40 workgroups:
-// 98.1, 256.6, 165.7, 628.
+// 98.1, 256.6, 165.7, 628.  The prologue's adjoint alone at d_h = 256 (heads, tokens; before this chunk and other changes of its adjoint, and
+// after): 4 + 1, 1024: 70.5, 59.7; 2048: 76.2, 67.0; 6000: 101.0, 85.7; 16384: 197.7, 195.7; 8 + 8, 2048: 110.2, 106.0; 9000: 357.5, 360.3; 2 + 2,
+// 3000: 75.8, 63.6.
 int dwc_chunk(const Dims &d) {
   const int NH = d.Hq + d.Hk, os = dwc_slices(d.dh, taps(d));
   for (int c = 512; c > 64; c >>= 1)
