@@ -5,11 +5,9 @@
 // Both operands are K-contiguous, so a lane's 8-element MFMA fragment is one
 // 16-byte LDS read.  Workgroup tile TM x BN x 64 with 8 wavefronts; LDS is
 // XOR-swizzled per 16-byte chunk; K-slabs travel HBM -> LDS directly
-// (global_load_lds, no staging registers, no ds_write), A two slabs ahead and the
-// weight one, the loads spread over a slab's 16-wide MFMA steps so that the LDS
-// writes trickle in between the fragment reads instead of arriving in one
-// burst (the LDS write port takes ~75 B/clk against ~230 B/clk for
-// reads).  The MFMA is issued with the weight rows as its first operand,
+// (buffer_load ... lds, no staging registers, no ds_write), A two slabs ahead and the
+// weight one, the loads and the next k-step's fragment reads dealt out between a
+// slab's MFMAs.  The MFMA is issued with the weight rows as its first operand,
 // which leaves every lane with 4 consecutive output columns of one row, so
 // the epilogue packs them to bf16, stages the tile in LDS and writes whole
 // rows with 16-byte stores.
@@ -28,11 +26,28 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
+// Operands of s_waitcnt: vector memory operations that may be outstanding (and any LDS operation); no LDS operation; with &, none of these
+// either.
+constexpr int wait_vm(int n) { return 0x0f70 | (n & 15) | n >> 4 << 14; }
+constexpr int WAIT_LDS = 0xc07f, WAIT_LDS_TOO = 0xf0ff;
+
 constexpr int BM = 256, BK = 64;
 constexpr int A_STAGES = 3, B_STAGES = 2;  // slabs of each operand in the LDS of the 256-row product
 
 // LDS position of the 16-byte chunk c (0..7) of row r in a [rows][64] bf16 tile
 __device__ __forceinline__ int swz(int r, int c) { return r * 8 + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
+
+// Direct load to LDS, 16 bytes a lane: lane i of the wavefront fills chunk i behind `to` (the same for all lanes) from `bytes` bytes
+// at `base` (0 beyond them), `lane_off` + `off` bytes into them.  (A buffer load: while a global load into LDS is outstanding the
+// compiler counts it as an LDS operation that may come back out of order, and every wait for a fragment becomes one for all of them.)
+template <typename T>
+__device__ __forceinline__ void load_to_lds(const T *base, unsigned bytes, unsigned lane_off, int off, u32x4 *to) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef __attribute__((address_space(3))) void lds_void;
+  const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), 0, (int)bytes, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void *)to, 16, lane_off, off, 0, 0);
+#endif
+}
 
 // two floats -> one word of two bf16 (round to nearest even) with the hardware conversion instruction
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -89,23 +104,25 @@ TileGrid tile_grid(long long M, int N, long long K, int tm, int tn) {
   return TileGrid{tiles_n, tiles_m * tiles_n, tile_panel(tiles_m, tiles_n, tm, tn, K)};
 }
 
-// acc[ni][mi][r] = C[m][n] with m = wm*32*MI + mi*32 + l32 and n = wn*32*NI + ni*32 + 8*(r/4) + 4*half + r%4 of the tile
-// at (m0, n0): packed to bf16, staged in LDS and written as whole rows.  `owner`: this wavefront holds sums to store.
-template <int TM, int TN, int NTHREADS, int NI, int MI>
-__device__ __forceinline__ void store_tile_bf16(const f32x16 (&acc)[NI][MI], unsigned char *smem, bool owner, int wm, int wn,
+// Products of F x F blocks (F = 32 or 16): acc[ni][mi][r] = C[m][n] with m = (wm*MI + mi)*F + lane%F and n = (wn*NI + ni)*F + 8*(r/4) +
+// 4*(lane/F) + r%4 of the tile at (m0, n0): packed to bf16, staged in LDS and written as whole rows.  `owner`: this wavefront holds
+// sums to store.
+template <int TM, int TN, int NTHREADS, int NI, int MI, typename Acc>
+__device__ __forceinline__ void store_tile_bf16(const Acc (&acc)[NI][MI], unsigned char *smem, bool owner, int wm, int wn,
                                                 int tid, bf16_t *__restrict__ C, long long m0, long long M, int n0, int N,
                                                 const ColumnSplit &split = ColumnSplit{}) {
   constexpr int ROW_BYTES = TN * 2 + 16;  // padded row: 8-byte column writes of 32 rows hit distinct banks
-  const int l32 = tid & 31, half = (tid >> 5) & 1;
+  constexpr int F = sizeof(Acc) == 64 ? 32 : 16;
+  const int row = tid & (F - 1), group = (tid & 63) / F;
   if (owner) {
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
-        const int m = (wm * MI + mi) * 32 + l32;
+        const int m = (wm * MI + mi) * F + row;
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int n = (wn * NI + ni) * 32 + rg * 8 + half * 4;
+        for (int rg = 0; rg < F * F / 256; ++rg) {
+          const int n = (wn * NI + ni) * F + rg * 8 + group * 4;
           u32x2 p;
           p.x = pack_bf16x2(acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1]);
           p.y = pack_bf16x2(acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]);
@@ -133,24 +150,30 @@ __device__ __forceinline__ void store_tile_bf16(const f32x16 (&acc)[NI][MI], uns
 
 // LDS holds three slabs of A and two of Bt: A streams from HBM, whose latency a slab's 1.1-1.5 us of MFMAs do not cover; Bt is
 // a weight that stays in the caches, and a third stage of it would not fit (256 x 256: 3 x 32 + 2 x 32 KB, all of a CU's LDS).
-// A slab's one barrier stands before its last k-step, when the fragments of that step are in registers: from there on the slab's
-// buffers are free for the next loads, and the next slab's first fragments are read under the last step's MFMAs.
-// 16384 x 1536 x 2048, back to back on random operands: 106.7 us with two slabs of both and the barrier at the slab's end,
-// 101.8 this way; 4096 x 6144 x 2048 112.5 and 103.2, 7996 x 1536 x 2048 51.8 and 49.6 (256 x 192 tiles); 16384 x 2048 x 1024 73.4
-// and 72.1 (256 x 256).  On all-zero operands the first takes 89 us: what bounds the larger shapes is the power the matrix cores
-// draw; with every row of A the same (in the caches) it still takes 104.  Rows and columns of the tile: what deals the tiles most
-// evenly to 256 CUs (nt_tile).  192 x 256: 6000 x 2048 x 1024 34.5 us on 256 x 256 (192 CUs at work), 30.0; 256 x 128: 4593 x 1536 x
-// 2048 37.1 on two workgroups of 128 x 128 to a CU, 35.7; 4096 x 2048 x 2048 40.4 and 38.6.
+// A slab's one barrier stands near the end of its first k-step, when the fragments of the last are in registers: from there on the
+// slab's buffers are free for the next loads, and the next slab's first fragments are read under the last step's MFMAs.
+// Every fragment read and every load stands between two MFMAs of its own, in the order of use, so the matrix core never waits behind a
+// burst of them; scheduling barriers keep the order.  The loop has no branch and no scalar load in flight: either makes the
+// compiler wait for the fragments just requested instead of those it needs.  Random operands, us, a k-step's reads in a burst, loads into
+// LDS counted among them and 32x32x16 instructions -> this: 16384 x 1536 x 2048 101.4 -> 86.2, 4096 x 6144 x 2048 99.7 -> 82.7, 7996 x 2048
+// x 1024 37.1 -> 30.6, 6000 x 1536 x 2048 45.5 -> 35.6, 8192 x 8192 x 8192 955 -> 732.
+// What bounds it: the power the matrix cores draw (8192^3 on all-zero operands: 607 us).  16x16x32 instructions draw less than
+// 32x32x16 ones on the same fragments: 8192^3 877 -> 796 us on random operands, 601 -> 607 on zeros.
+// Not faster: s_setprio around the MFMAs, any other order of them, the barrier four MFMAs earlier, A's loads closer
+// together or further apart, 4 wavefronts of 128 x 128 (half the fragment reads).  Rows and columns of the tile: what deals the tiles most
+// evenly to 256 CUs (nt_tile).
 template <int TM, int BN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(const bf16_t *__restrict__ A,
                                                                const bf16_t *__restrict__ Bt,
                                                                bf16_t *__restrict__ C, long long M, int N, int K,
                                                                TileGrid grid, ColumnSplit split) {
+  // the epilogue's arguments are loaded here
+  asm volatile("" : "+s"(C), "+s"(split.q), "+s"(split.k), "+s"(split.v), "+s"(split.e_q), "+s"(split.e_kv));
   constexpr int NWAVES = WAVES_M * WAVES_N, NTHREADS = NWAVES * 64;
   constexpr int WM = TM / WAVES_M, WN = BN / WAVES_N;  // wave tile
-  constexpr int MI = WM / 32, NI = WN / 32;            // 32x32 MFMA tiles per wave
-  static_assert(MI * 32 == WM && NI * 32 == WN, "wave tile must be a multiple of 32");
-  static_assert(BK == 64, "four k-steps of 16");
+  constexpr int MI = WM / 16, NI = WN / 16;            // 16x16 MFMA tiles per wave
+  static_assert(MI * 16 == WM && NI * 16 == WN, "wave tile must be a multiple of 16");
+  static_assert(BK == 64, "two k-steps of 32");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int A_STAGE = TM * 8, B_STAGE = BN * 8;  // 16-byte chunks of a slab
   u32x4 *const sA = reinterpret_cast<u32x4 *>(smem), *const sB = sA + A_STAGES * A_STAGE;
@@ -161,106 +184,112 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
   const int n0 = tn * BN;
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = tid >> 6, first_wave = __builtin_amdgcn_readfirstlane(wave);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int l32 = lane & 31, half = lane >> 5;
+  const int row = lane & 15, quad = lane >> 4;
 
-  // Direct global -> LDS loads: wave instruction i deposits 64 x 16 bytes at LDS chunks [i*64, i*64+64) of a slab
-  // (8 chunks per row), so lane L fetches the chunk that the XOR swizzle puts at that position.
+  // Direct loads to LDS: wave instruction i deposits 64 x 16 bytes at LDS chunks [i*64, i*64+64) of a slab
+  // (8 chunks per row), so lane L fetches the chunk that the XOR swizzle puts at that position.  Rows past the end of the
+  // matrix are its last one.
   constexpr int A_LOADS = A_STAGE / 64 / NWAVES, B_LOADS = B_STAGE / 64 / NWAVES;  // instructions of a wavefront per slab
   static_assert(A_LOADS * 64 * NWAVES == A_STAGE && B_LOADS * 64 * NWAVES == B_STAGE,
                 "instructions must divide evenly over the wavefronts");
-  const bf16_t *a_src[A_LOADS], *b_src[B_LOADS];
+  const int a_rows = (int)(M - m0 < TM ? M - m0 : TM), b_rows = N - n0 < BN ? N - n0 : BN;
   const int l_row = (wave * 64 + lane) >> 3, l_cs = lane & 7;  // row and chunk position of this thread's first chunk
+  unsigned a_off[A_LOADS], b_off[B_LOADS];  // bytes from the tile's first row (256 rows of K: below 2^31, gemm_mfma_supported)
 #pragma unroll
   for (int u = 0; u < A_LOADS; ++u) {
     const int r = l_row + u * (NTHREADS / 8), c = l_cs ^ ((r & 7) ^ ((r >> 3) & 1));  // inverse of swz()
-    const long long gr = m0 + r;
-    a_src[u] = A + (gr < M ? gr : M - 1) * K + c * 8;
+    a_off[u] = (unsigned)(r < a_rows ? r : a_rows - 1) * K * 2 + c * 16;
   }
 #pragma unroll
   for (int u = 0; u < B_LOADS; ++u) {
     const int r = l_row + u * (NTHREADS / 8), c = l_cs ^ ((r & 7) ^ ((r >> 3) & 1));
-    const int gr = n0 + r;
-    b_src[u] = Bt + (long long)(gr < N ? gr : N - 1) * K + c * 8;
+    b_off[u] = (unsigned)(r < b_rows ? r : b_rows - 1) * K * 2 + c * 16;
   }
-  typedef __attribute__((address_space(3))) void lds_void;
-  typedef __attribute__((address_space(1))) void glb_void;
-  auto issue_a = [&](int kt, int stage, int u0, int u1) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = u0; u < u1; ++u)
-      __builtin_amdgcn_global_load_lds((glb_void *)(a_src[u] + kt * BK), (lds_void *)(sA + stage * A_STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
+  const bf16_t *const a_base = A + m0 * K, *const b_base = Bt + (long long)n0 * K;
+  auto load_a = [&](int kt, int stage, int u) __attribute__((always_inline)) {
+    load_to_lds(a_base, (unsigned)a_rows * K * 2, a_off[u], kt * (BK * 2), sA + stage * A_STAGE + (first_wave + u * NWAVES) * 64);
   };
-  auto issue_b = [&](int kt, int stage) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < B_LOADS; ++u)
-      __builtin_amdgcn_global_load_lds((glb_void *)(b_src[u] + kt * BK), (lds_void *)(sB + stage * B_STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
+  auto load_b = [&](int kt, int stage, int u) __attribute__((always_inline)) {
+    load_to_lds(b_base, (unsigned)b_rows * K * 2, b_off[u], kt * (BK * 2), sB + stage * B_STAGE + (first_wave + u * NWAVES) * 64);
   };
 
-  f32x16 acc[NI][MI];
+  f32x4 acc[NI][MI];
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[ni][mi][r] = 0.f;
-  // two sets of fragments: those of k-step kk+1 are requested before the MFMAs of k-step kk are issued
+      for (int r = 0; r < 4; ++r) acc[ni][mi][r] = 0.f;
+  // two sets of fragments, one for each k-step: set s ^ 1 is read between the MFMAs of set s, in the order they need it
   bf16x8 fa[2][MI], fb[2][NI];
-  auto read_frags = [&](int a_stage, int b_stage, int kk, int set) __attribute__((always_inline)) {
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-      fa[set][mi] = __builtin_bit_cast(bf16x8, sA[a_stage * A_STAGE + swz(wm * WM + mi * 32 + l32, kk * 2 + half)]);
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-      fb[set][ni] = __builtin_bit_cast(bf16x8, sB[b_stage * B_STAGE + swz(wn * WN + ni * 32 + l32, kk * 2 + half)]);
+  constexpr int READS = MI + NI, MFMAS = MI * NI, PER_READ = MFMAS / READS;
+  static_assert(PER_READ >= 1, "a read behind every PER_READ-th MFMA");
+  auto read = [&](int a_stage, int b_stage, int set, int j) __attribute__((always_inline)) {
+    if (j >= 1 && j <= MI)
+      fa[set][j - 1] = __builtin_bit_cast(bf16x8, sA[a_stage * A_STAGE + swz(wm * WM + (j - 1) * 16 + row, set * 4 + quad)]);
+    else
+      fb[set][j ? j - MI : 0] = __builtin_bit_cast(bf16x8, sB[b_stage * B_STAGE + swz(wn * WN + (j ? j - MI : 0) * 16 + row, set * 4 + quad)]);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto multiply = [&](int set) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-      for (int mi = 0; mi < MI; ++mi)
-        acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][ni], fa[set][mi], acc[ni][mi], 0, 0, 0);
+  auto multiply = [&](int set, int i) __attribute__((always_inline)) {
+    const int ni = i / MI, mi = i % MI;
+    acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][ni], fa[set][mi], acc[ni][mi], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
 
   const int nk = K / BK;
-  issue_b(0, 0);
-  issue_a(0, 0, 0, A_LOADS);
+#pragma unroll
+  for (int u = 0; u < B_LOADS; ++u) load_b(0, 0, u);
+#pragma unroll
+  for (int u = 0; u < A_LOADS; ++u) load_a(0, 0, u);
   if (nk > 1) {
-    issue_b(1, 1);
-    issue_a(1, 1, 0, A_LOADS);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(A_LOADS + B_LOADS) : "memory");
+#pragma unroll
+    for (int u = 0; u < B_LOADS; ++u) load_b(1, 1, u);
+#pragma unroll
+    for (int u = 0; u < A_LOADS; ++u) load_a(1, 1, u);
+    __builtin_amdgcn_s_waitcnt(wait_vm(A_LOADS + B_LOADS));
   } else {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));
   }
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  read_frags(0, 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < READS; ++j) read(0, 0, 0, j);
+  __builtin_amdgcn_s_waitcnt(WAIT_LDS);
+
   int as = 0;  // stage of A that holds slab kt
-  for (int kt = 0; kt < nk; ++kt) {
+  // `next`: there is a slab kt + 1, `ahead`: and a slab kt + 2
+  auto slab = [&](int kt, auto ahead_, auto next_) __attribute__((always_inline)) {
+    constexpr bool ahead = decltype(ahead_)::value, next = decltype(next_)::value;
+    constexpr int A_EVERY = 2 * A_LOADS <= MFMAS - 4 ? 2 : 1, B_EVERY = 2 * B_LOADS <= MFMAS ? 2 : 1;
     const int bs = kt & 1, as1 = as == 2 ? 0 : as + 1, as2 = as1 == 2 ? 0 : as1 + 1;
-    const bool ahead = kt + 2 < nk;
-    if (ahead) issue_a(kt + 2, as2, 0, A_LOADS / 2);  // into the stage of slab kt - 1
-    read_frags(as, bs, 1, 1);
-    multiply(0);
-    if (ahead) issue_a(kt + 2, as2, A_LOADS / 2, A_LOADS);
-    read_frags(as, bs, 2, 0);
-    multiply(1);
-    read_frags(as, bs, 3, 1);
-    multiply(0);
-    if (kt + 1 < nk) {
+#pragma unroll
+    for (int i = 0; i < MFMAS; ++i) {
+      multiply(0, i);
+      if (i % PER_READ == 0 && i / PER_READ < READS) read(as, bs, 1, i / PER_READ);
+      if (ahead && i % A_EVERY == A_EVERY - 1 && i / A_EVERY < A_LOADS) load_a(kt + 2, as2, i / A_EVERY);  // into the stage of slab kt - 1
+    }
+    if (next) {
       // slab kt + 1 has landed when no more than the newest loads, A of slab kt + 2, are outstanding
-      if (ahead) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(A_LOADS) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(wait_vm(ahead ? A_LOADS : 0) & WAIT_LDS_TOO);
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      if (ahead) issue_b(kt + 2, bs);  // every wavefront holds its last fragments of slab kt
-      read_frags(as1, bs ^ 1, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    multiply(1);
+#pragma unroll
+    for (int i = 0; i < MFMAS; ++i) {
+      multiply(1, i);
+      if (next && i % PER_READ == 0 && i / PER_READ < READS) read(as1, bs ^ 1, 0, i / PER_READ);
+      if (ahead && i % B_EVERY == B_EVERY - 1 && i / B_EVERY < B_LOADS) load_b(kt + 2, bs, i / B_EVERY);  // every wavefront holds its last fragments of slab kt
+    }
     as = as1;
-  }
+  };
+  int kt = 0;
+  for (; kt + 2 < nk; ++kt) slab(kt, std::true_type{}, std::true_type{});
+  if (kt + 1 < nk) slab(kt++, std::false_type{}, std::true_type{});
+  slab(kt, std::false_type{}, std::false_type{});
   __syncthreads();
   store_tile_bf16<TM, BN, NTHREADS>(acc, smem, true, wm, wn, tid, C, m0, M, n0, N, split);
 }
@@ -860,15 +889,17 @@ hipError_t mfma_probe(float *out, int blocks, int iters, bool random_operands, h
   return hipGetLastError();
 }
 
-bool gemm_mfma_supported(long long M, int N, int K) { return M >= 1 && K % BK == 0 && K >= BK && N % 8 == 0 && N >= 8; }
+// (a tile's 256 rows are addressed with 32 bits)
+bool gemm_mfma_supported(long long M, int N, int K) { return M >= 1 && K % BK == 0 && K >= BK && K < 1 << 22 && N % 8 == 0 && N >= 8; }
 
 hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, int N, int K, hipStream_t s,
                           const ColumnSplit &split) {
   switch (nt_tile(M, N, K)) {
     case NT_256x256: return launch_gemm<256, 256, 2, 4>(A, Bt, C, M, N, K, split, s);
-    case NT_256x192: return launch_gemm<256, 192, 4, 2>(A, Bt, C, M, N, K, split, s);
+    case NT_256x192: return launch_gemm<256, 192, 2, 4>(A, Bt, C, M, N, K, split, s);
     case NT_192x256: return launch_gemm<192, 256, 2, 4>(A, Bt, C, M, N, K, split, s);
     case NT_256x128: return launch_gemm<256, 128, 4, 2>(A, Bt, C, M, N, K, split, s);
+    case NT_192x192: return launch_gemm<192, 192, 2, 4>(A, Bt, C, M, N, K, split, s);
     case NT_64x64: return launch_gemm_deep<64, 64, 2, 2, 2, 3>(A, Bt, C, M, N, K, split, s);
     case NT_64x128: return launch_gemm_deep<64, 128, 1, 4, 2, 3>(A, Bt, C, M, N, K, split, s);
     case NT_128x128: return launch_gemm_deep<128, 128, 2, 4, 1, 4>(A, Bt, C, M, N, K, split, s);

@@ -51,7 +51,7 @@ int r_gemm_pair(long long rows, int n_in, int n_out) {
 int r_pair_blocks(long long BH, int causal, int blocks) { return pair_blocks(BH, causal, blocks); }
 }
 """
-NT_TILES = ("256x256", "256x192", "64x64", "64x128", "128x128", "256x128", "192x256")
+NT_TILES = ("256x256", "256x192", "64x64", "64x128", "128x128", "256x128", "192x256", "192x192")
 GENERIC_ROWS = ("16 rows", "16 rows, 16 wavefronts", "32 rows")
 TN_TILES = ("split", "64x64", "64x128", "128x128")
 

@@ -40,7 +40,7 @@ def check_product(got, ref, K):
 # panels and with a narrower last panel
 GEMM_CASES = [(1, 1, 1, 64, 64), (65, 1, 1, 64, 192), (127, 3, 1, 64, 320), (512, 8, 2, 128, 2048), (511, 4, 4, 64, 1024),
               (1000, 8, 2, 128, 2048), (1999, 16, 4, 64, 2048), (2050, 5, 5, 64, 1024), (4593, 8, 8, 64, 2048),
-              (3001, 8, 2, 128, 2048), (4097, 16, 16, 128, 2048), (4097, 5, 5, 64, 320), (9001, 5, 5, 64, 448), (5953, 5, 5, 64, 2048), (65, 3, 1, 64, 256), (581, 24, 1, 64, 1536)]
+              (3001, 8, 2, 128, 2048), (4097, 16, 16, 128, 2048), (4097, 5, 5, 64, 320), (9001, 5, 5, 64, 448), (5953, 5, 5, 64, 2048), (65, 3, 1, 64, 256), (581, 24, 1, 64, 1536), (5999, 8, 2, 128, 2048)]
 
 
 @pytest.mark.parametrize("M,Hq,Hk,dh,E", GEMM_CASES)
@@ -56,13 +56,14 @@ def test_projection_tiles(M, Hq, Hk, dh, E):
 
 
 @pytest.mark.parametrize("slabs", [1, 2, 3, 4])
-@pytest.mark.parametrize("M,tile", [(9001, "256x192"), (32700, "256x256"), (8001, "256x128"), (12001, "192x256")])
-def test_projection_of_few_slabs_on_large_tiles(M, tile, slabs):
+@pytest.mark.parametrize("M,tile,E", [(9001, "256x192", 1024), (32700, "256x256", 1024), (8001, "256x128", 1024), (12001, "192x256", 1024),
+                                      (5999, "192x192", 1536)])
+def test_projection_of_few_slabs_on_large_tiles(M, tile, E, slabs):
     """Contractions shorter than the three slabs of A and two of the weight that the 256-row kernel holds, and just longer."""
     say("projection", M, slabs)
-    cfg = P.CCAConfig(B=1, T=M, d_model=1024, n_q_heads=slabs, n_kv_heads=1, head_dim=64)
-    assert rules.nt_tile(M, 1024, 64 * slabs) == tile
-    o, w_out = rnd(1, M, cfg.e_q, seed=3), rnd(cfg.e_q, 1024, seed=4, scale=0.02)
+    cfg = P.CCAConfig(B=1, T=M, d_model=E, n_q_heads=slabs, n_kv_heads=1, head_dim=64)
+    assert rules.nt_tile(M, E, 64 * slabs) == tile
+    o, w_out = rnd(1, M, cfg.e_q, seed=3), rnd(cfg.e_q, E, seed=4, scale=0.02)
     out = P.cca_up_project(cfg, o, w_out)
     torch.cuda.synchronize()
     check_product(out[0], o[0].double() @ w_out.double(), cfg.e_q)
