@@ -40,11 +40,10 @@ __device__ __forceinline__ int swz(int r, int c) { return r * 8 + (c ^ ((r & 7) 
 // Direct load to LDS, 16 bytes a lane: lane i of the wavefront fills chunk i behind `to` (the same for all lanes) from `bytes` bytes
 // at `base` (0 beyond them), `lane_off` + `off` bytes into them.  (A buffer load: while a global load into LDS is outstanding the
 // compiler counts it as an LDS operation that may come back out of order, and every wait for a fragment becomes one for all of them.)
-template <typename T>
-__device__ __forceinline__ void load_to_lds(const T *base, unsigned bytes, unsigned lane_off, int off, u32x4 *to) {
+__device__ __forceinline__ void load_to_lds(const void *base, unsigned bytes, unsigned lane_off, int off, void *to) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef __attribute__((address_space(3))) void lds_void;
-  const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), 0, (int)bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
   __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void *)to, 16, lane_off, off, 0, 0);
 #endif
 }
@@ -309,26 +308,34 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(TransposePair p) {
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 
-constexpr int TN_BN = 256, TN_ROW = 256 * 2 + 64;  // tile width (both operands); LDS row in bytes, padded by 64 so
-                                                   // that the 4 rows a transposing read touches fall in 4 different bank groups
+constexpr int TN_BN = 256;  // tile width (both operands)
 
-__device__ __forceinline__ bf16x8 tr_frag_tn(const unsigned char *base, int r0, int c0) {
-  const unsigned char *p = base + r0 * TN_ROW + c0 * 2;
+// MFMA fragment of 16 columns of a [64 tokens][256 columns] bf16 tile: lane (column lane & 15, quad = lane / 16) receives tokens 4*quad +
+// 0..3 and 16 + 4*quad + 0..3 behind `base`, which holds the lane's address for the first 16 columns of the tile: token 4*quad +
+// (lane & 15)/4, 8 bytes of the 32 that four lanes share.  Chunk c of token r lies at position c ^ ((r & 7) << 1), so that the 32 bytes
+// that 8 tokens of one read touch fall in 8 different bank groups; the columns are 32 bytes apart in the same low bits.
+__device__ __forceinline__ bf16x8 tr_frag_tn(const unsigned char *tile, unsigned lane_off, int column16) {
+  const unsigned char *p = tile + (lane_off ^ (unsigned)(column16 * 32));
   const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)p);
-  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(p + 8 * TN_ROW));
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(p + 16 * 512));
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-__global__ __launch_bounds__(512) void gemm_bf16_tn_kernel(const bf16_t *__restrict__ A, long long lda,
-                                                          const bf16_t *__restrict__ Bm, long long ldb,
-                                                          float *__restrict__ part, int Mo, int No, long long K,
-                                                          int tiles_n, int tiles_total, int splits, int slabs_per_split) {
-  constexpr int NTHREADS = 512, WAVES_N = 4;
+// The pipeline of gemm_bf16_nt_kernel (slabs of 64 tokens, three of A and two of B in LDS, reads and loads between the MFMAs) on operands
+// whose rows are the contraction index; bound by the matrix cores' power and, with more than one split, by the partial sums (written and
+// read at about 7 TB/s).  With register staging, padded rows and a k-step's fragments read in a burst -> this, reduction included, us (columns x
+// columns over tokens): 2048 x 1536 over 7996 69.3 -> 57.5, over 16384 117.9 -> 94.3; 1024 x 2048 over 7996 52.7 -> 45.3, over 16384 82.6 ->
+// 69.9; 2048 x 6144 over 4096 (one split) 138.7 -> 95.2.
+__device__ __forceinline__ void gemm_bf16_tn_body(const bf16_t *__restrict__ A, long long lda, const bf16_t *__restrict__ Bm, long long ldb,
+                                                  float *__restrict__ part, bf16_t *__restrict__ C, int Mo, int No, long long K,
+                                                  int tiles_n, int tiles_total, int splits, int slabs_per_split,
+                                                  unsigned char *__restrict__ smem) {
+  constexpr int NWAVES = 8, WAVES_N = 4;
   constexpr int WM = BM / 2, WN = TN_BN / WAVES_N;  // 128 x 64 wave tile
-  constexpr int MI = WM / 32, NI = WN / 32;
-  constexpr int CHUNKS = BK * (BM / 8) / NTHREADS;  // 16-byte chunks per thread per operand per slab (4)
-  constexpr int TILE = BK * TN_ROW;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [2 stages][A tile | B tile]
+  constexpr int MI = WM / 16, NI = WN / 16;
+  constexpr int STAGE = BK * 256 * 2;            // bytes of a slab of either operand
+  constexpr int LOADS = STAGE / 1024 / NWAVES;   // load instructions of a wavefront per operand and slab, two tokens each
+  unsigned char *const sA = smem, *const sB = smem + A_STAGES * STAGE;
 
   // Units (split, tile) in split order, a contiguous range of them to each XCD: the tiles of a split read the same token rows,
   // so an XCD's L2 is filled with its share of A and B instead of all of both, and every XCD gets the same number of units
@@ -340,100 +347,125 @@ __global__ __launch_bounds__(512) void gemm_bf16_tn_kernel(const bf16_t *__restr
   const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * TN_BN;
   const long long nk_all = (K + BK - 1) / BK;
   const long long slab0 = (long long)split * slabs_per_split;
-  const int nk = (int)((slab0 + slabs_per_split <= nk_all ? slabs_per_split : nk_all - slab0));
+  const int nk = (int)((slab0 + slabs_per_split <= nk_all ? slabs_per_split : nk_all - slab0));  // at least 1 (tn_splits)
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, first_wave = __builtin_amdgcn_readfirstlane(wave);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int l32 = lane & 31, half = lane >> 5;
 
-  // chunk id -> (row r of the slab, 16-byte column chunk c); columns past the matrix edge are clamped to
-  // column 0 (they only feed outputs that are never stored), rows past K are zero-filled
-  int c_row[CHUNKS], c_col[CHUNKS];
-  const bf16_t *a_src[CHUNKS], *b_src[CHUNKS];
-#pragma unroll
-  for (int i = 0; i < CHUNKS; ++i) {
-    const int id = tid + i * NTHREADS;
-    c_row[i] = id >> 5;
-    c_col[i] = id & 31;
-    const int am = m0 + c_col[i] * 8, bn = n0 + c_col[i] * 8;
-    a_src[i] = A + (am < Mo ? am : 0);
-    b_src[i] = Bm + (bn < No ? bn : 0);
-  }
-  u32x4 ra[CHUNKS], rb[CHUNKS];
-  auto load_slab = [&](long long k0) {
-#pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      const long long gk = k0 + c_row[i];
-      u32x4 va = {0, 0, 0, 0}, vb = {0, 0, 0, 0};
-      if (gk < K) {
-        va = *reinterpret_cast<const u32x4 *>(a_src[i] + gk * lda);
-        vb = *reinterpret_cast<const u32x4 *>(b_src[i] + gk * ldb);
-      }
-      ra[i] = va;
-      rb[i] = vb;
-    }
+  // Load instruction i deposits tokens 2i, 2i + 1 of a slab; a lane fetches the chunk that the swizzle puts at its position (its token
+  // modulo 8 is the same in every load of a wavefront).  Each load has a descriptor of its own that begins with the wavefronts' first
+  // token and ends with the last one there is: tokens past it read as zeros.  Columns past the matrix edge are some others' (they only feed
+  // outputs that are never stored).
+  const int l_row = wave * 2 + (lane >> 5), l_chunk = (lane & 31) ^ ((l_row & 7) << 1);
+  const unsigned a_off = (unsigned)(l_row * lda * 2) + l_chunk * 16, b_off = (unsigned)(l_row * ldb * 2) + l_chunk * 16;
+  const int tokens = (int)(K - slab0 * BK < (long long)nk * BK ? K - slab0 * BK : (long long)nk * BK);
+  const bf16_t *const a_first = A + slab0 * BK * lda + m0, *const b_first = Bm + slab0 * BK * ldb + n0;
+  const int a_width = min(Mo - m0, 256), b_width = min(No - n0, 256);
+  auto load = [&](const bf16_t *first, int ld, int width, int kt, int u, unsigned off, unsigned char *to) __attribute__((always_inline)) {
+    const int token = kt * BK + u * 2 * NWAVES, rows = min(tokens - token, 2 * NWAVES);  // (none left: no bytes, width <= ld)
+    load_to_lds(first + (long long)token * ld, (unsigned)max(((rows - 1) * ld + width) * 2, 0), off, 0, to + (first_wave + u * NWAVES) * 1024);
   };
-  auto store_slab = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      *reinterpret_cast<u32x4 *>(smem + buf * 2 * TILE + c_row[i] * TN_ROW + c_col[i] * 16) = ra[i];
-      *reinterpret_cast<u32x4 *>(smem + buf * 2 * TILE + TILE + c_row[i] * TN_ROW + c_col[i] * 16) = rb[i];
-    }
-  };
+  auto load_a = [&](int kt, int stage, int u) __attribute__((always_inline)) { load(a_first, (int)lda, a_width, kt, u, a_off, sA + stage * STAGE); };
+  auto load_b = [&](int kt, int stage, int u) __attribute__((always_inline)) { load(b_first, (int)ldb, b_width, kt, u, b_off, sB + stage * STAGE); };
 
-  f32x16 acc[NI][MI];
+  f32x4 acc[NI][MI];
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[ni][mi][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[ni][mi][r] = 0.f;
 
-  const uint32_t tr_off = (uint32_t)(4 * half + ((lane & 15) >> 2)) * TN_ROW + (((lane >> 4) & 1) * 16 + 4 * (lane & 3)) * 2;
-  const long long kbase = slab0 * BK;
-  if (nk > 0) {
-    load_slab(kbase);
-    store_slab(0);
-    if (nk > 1) load_slab(kbase + BK);
+  const int quad = lane >> 4, t_row = 4 * quad + ((lane & 15) >> 2);  // the lane's token of a transposing read
+  const unsigned lane_off = t_row * 512 + (((t_row & 7) << 1) ^ ((lane & 3) >> 1)) * 16 + (lane & 1) * 8;
+  const unsigned a_lane = lane_off ^ (wm * MI * 32u), b_lane = lane_off ^ (wn * NI * 32u);
+  bf16x8 fa[2][MI], fb[2][NI];
+  constexpr int READS = MI + NI, MFMAS = MI * NI, PER_READ = MFMAS / READS;
+  auto read = [&](int a_stage, int b_stage, int set, int j) __attribute__((always_inline)) {
+    if (j >= 1 && j <= MI) fa[set][j - 1] = tr_frag_tn(sA + a_stage * STAGE + set * 32 * 512, a_lane, j - 1);
+    else fb[set][j ? j - MI : 0] = tr_frag_tn(sB + b_stage * STAGE + set * 32 * 512, b_lane, j ? j - MI : 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int set, int i) __attribute__((always_inline)) {
+    const int ni = i / MI, mi = i % MI;
+    acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][ni], fa[set][mi], acc[ni][mi], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) load_b(0, 0, u);
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) load_a(0, 0, u);
+  if (nk > 1) {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) load_b(1, 1, u);
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) load_a(1, 1, u);
+    __builtin_amdgcn_s_waitcnt(wait_vm(2 * LOADS));
+  } else {
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));
   }
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) store_slab(buf ^ 1);
-    if (kt + 2 < nk) load_slab(kbase + (long long)(kt + 2) * BK);
-    const unsigned char *pa = smem + buf * 2 * TILE + tr_off, *pb = pa + TILE;
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 #pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      bf16x8 fa[MI], fb[NI];
+  for (int j = 0; j < READS; ++j) read(0, 0, 0, j);
+  __builtin_amdgcn_s_waitcnt(WAIT_LDS);
+
+  int as = 0;  // stage of A that holds slab kt
+  auto slab = [&](int kt, auto ahead_, auto next_) __attribute__((always_inline)) {  // as in gemm_bf16_nt_kernel
+    constexpr bool ahead = decltype(ahead_)::value, next = decltype(next_)::value;
+    const int bs = kt & 1, as1 = as == 2 ? 0 : as + 1, as2 = as1 == 2 ? 0 : as1 + 1;
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) fa[mi] = tr_frag_tn(pa, kk * 16, wm * WM + mi * 32);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) fb[ni] = tr_frag_tn(pb, kk * 16, wn * WN + ni * 32);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-          acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ni], fa[mi], acc[ni][mi], 0, 0, 0);
+    for (int i = 0; i < MFMAS; ++i) {
+      multiply(0, i);
+      if (i % PER_READ == 0 && i / PER_READ < READS) read(as, bs, 1, i / PER_READ);
+      if (ahead && i % 2 == 1 && i / 2 < LOADS) load_a(kt + 2, as2, i / 2);
     }
+    if (next) {
+      __builtin_amdgcn_s_waitcnt(wait_vm(ahead ? LOADS : 0) & WAIT_LDS_TOO);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < MFMAS; ++i) {
+      multiply(1, i);
+      if (next && i % PER_READ == 0 && i / PER_READ < READS) read(as1, bs ^ 1, 0, i / PER_READ);
+      if (ahead && i % 2 == 1 && i / 2 < LOADS) load_b(kt + 2, bs, i / 2);
+    }
+    as = as1;
+  };
+  int kt = 0;
+  for (; kt + 2 < nk; ++kt) slab(kt, std::true_type{}, std::true_type{});
+  if (kt + 1 < nk) slab(kt++, std::false_type{}, std::true_type{});
+  slab(kt, std::false_type{}, std::false_type{});
+
+  if (splits == 1) {  // the result itself (2048 x 6144 over 4096 tokens, written as fp32 and read again: 105.4 us, 95.2)
     __syncthreads();
+    store_tile_bf16<BM, TN_BN, 512>(acc, smem, true, wm, wn, tid, C, m0, Mo, n0, No);
+    return;
   }
-  // Partial sums leave as the lanes hold them, 32 x 32 blocks of [r / 4][lane][r % 4] (block (i, j) of a split at i * blocks_n
-  // + j): 1 KB per store instruction, where rows of the matrix would be 32 bytes of 32 cache lines (2048 x 1536 over 7996
-  // tokens, 5 splits: 69.5 -> 67.6 us with the reduction).
+  // Partial sums leave as the lanes hold them, in 32 x 32 blocks of four 16 x 16 ones of [lane][r] (block (i, j) of a split at i *
+  // blocks_n + j): 1 KB per store instruction, where rows of the matrix would be 64 bytes of 16 cache lines.
   const int blocks_m = (Mo + 31) / 32, blocks_n = (No + 31) / 32;
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
-      const int bi = m0 / 32 + wm * MI + mi, bj = n0 / 32 + wn * NI + ni;
+      const int bi = m0 / 32 + (wm * MI + mi) / 2, bj = n0 / 32 + (wn * NI + ni) / 2;
       if (bi >= blocks_m || bj >= blocks_n) continue;
-      float *out = part + (((long long)split * blocks_m + bi) * blocks_n + bj) * 1024 + lane * 4;
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        f32x4 v4 = {acc[ni][mi][rg * 4 + 0], acc[ni][mi][rg * 4 + 1], acc[ni][mi][rg * 4 + 2], acc[ni][mi][rg * 4 + 3]};
-        *reinterpret_cast<f32x4 *>(out + rg * 256) = v4;
-      }
+      *reinterpret_cast<f32x4 *>(part + (((long long)split * blocks_m + bi) * blocks_n + bj) * 1024 + ((mi & 1) * 2 + (ni & 1)) * 256 + lane * 4) =
+          acc[ni][mi];
     }
+}
+
+// (a body inlined with restrict arguments: without them the compiler makes every transposing LDS read wait for the loads
+// into LDS in flight)
+__global__ __launch_bounds__(512) void gemm_bf16_tn_kernel(const bf16_t *__restrict__ A, long long lda,
+                                                          const bf16_t *__restrict__ Bm, long long ldb,
+                                                          float *__restrict__ part, bf16_t *__restrict__ C, int Mo, int No, long long K,
+                                                          int tiles_n, int tiles_total, int splits, int slabs_per_split) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  gemm_bf16_tn_body(A, lda, Bm, ldb, part, C, Mo, No, K, tiles_n, tiles_total, splits, slabs_per_split, smem);
 }
 
 // The weight-gradient product on smaller tiles, for token counts whose 256 x 256 tiles would have to be split many ways
@@ -465,34 +497,32 @@ __device__ __forceinline__ void gemm_bf16_tn_deep_body(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
   const int wk = wave / (WAVES_M * WAVES_N), wmn = wave % (WAVES_M * WAVES_N), wm = wmn / WAVES_N, wn = wmn % WAVES_N;
 
-  // Load instruction wave + u * NWAVES fills 64 chunks of the stage; columns past the matrix edge are read from column 0
-  // (they only feed outputs that are never stored), rows past K from the last row (zeroed in LDS before they are used).
-  const bf16_t *g_col[PER_WAVE];
-  long long g_ld[PER_WAVE];
-  int g_row[PER_WAVE];
+  // Load instruction wave + u * NWAVES fills 64 chunks of the stage.  A slab is read through descriptors that begin at its first token and
+  // end with the last one there is: tokens past it read as zeros.  Columns past the matrix edge are some others' (they only feed
+  // outputs that are never stored).
+  const int first_wave = __builtin_amdgcn_readfirstlane(wave);
+  const int a_width = min(Mo - m0, TM), b_width = min(No - n0, TN);
+  unsigned off[PER_WAVE];
 #pragma unroll
   for (int u = 0; u < PER_WAVE; ++u) {
-    const int pos = (wave + u * NWAVES) * 64 + lane;
-    if (pos < A_CH) {
+    const int i = first_wave + u * NWAVES, pos = i * 64 + lane;
+    if (i < A_CH / 64) {
       const int r = pos / (TM / 8), c = (pos % (TM / 8)) ^ (TM == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2);
-      g_row[u] = r;
-      g_ld[u] = lda;
-      g_col[u] = A + (m0 + c * 8 < Mo ? m0 + c * 8 : 0);
+      off[u] = (unsigned)(r * lda + c * 8) * 2;
     } else {
       const int p = pos - A_CH, r = p / (TN / 8), c = (p % (TN / 8)) ^ (TN == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2);
-      g_row[u] = r;
-      g_ld[u] = ldb;
-      g_col[u] = Bm + (n0 + c * 8 < No ? n0 + c * 8 : 0);
+      off[u] = (unsigned)(r * ldb + c * 8) * 2;
     }
   }
-  typedef __attribute__((address_space(3))) void lds_void;
-  typedef __attribute__((address_space(1))) void glb_void;
-  auto issue = [&](long long kt, int buf) {
+  auto issue = [&](long long kt, int buf) __attribute__((always_inline)) {
+    const long long left = K - kt * BK;
+    const int tokens = left < BK ? (int)left : BK;
+    const unsigned a_bytes = ((tokens - 1) * (int)lda + a_width) * 2, b_bytes = ((tokens - 1) * (int)ldb + b_width) * 2;
+    const bf16_t *const a_first = A + kt * BK * lda + m0, *const b_first = Bm + kt * BK * ldb + n0;
 #pragma unroll
     for (int u = 0; u < PER_WAVE; ++u) {
-      const long long row = kt * BK + g_row[u];
-      __builtin_amdgcn_global_load_lds((glb_void *)(g_col[u] + (row < K ? row : K - 1) * g_ld[u]),
-                                       (lds_void *)(sbase + buf * STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
+      const int i = first_wave + u * NWAVES;
+      load_to_lds(i < A_CH / 64 ? a_first : b_first, i < A_CH / 64 ? a_bytes : b_bytes, off[u], 0, sbase + buf * STAGE + i * 64);
     }
   };
   f32x16 acc[NI][MI];
@@ -505,7 +535,7 @@ __device__ __forceinline__ void gemm_bf16_tn_deep_body(
 
   // a lane's place in a transposing read: row 4*half + (lane & 15)/4 of each group of 8, 8 bytes of a 64-byte column group
   const int tr = 4 * half + ((lane & 15) >> 2), tc = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1), tb = (lane & 1) * 8;
-  const int nk = (int)((K + BK - 1) / BK), nfull = (int)(K / BK);
+  const int nk = (int)((K + BK - 1) / BK);
 #pragma unroll
   for (int i = 0; i < STAGES - 1; ++i)
     if (i < nk) issue(i, i);
@@ -528,6 +558,7 @@ __device__ __forceinline__ void gemm_bf16_tn_deep_body(
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni) fb[k2][ni] = frag(pb, std::integral_constant<int, TN>{}, (wn * NI + ni) * 32);
     }
+    if constexpr (WAVES_K == 1) __builtin_amdgcn_sched_barrier(0);  // every fragment is requested before the first is used (1-2 % at 128 x 128)
 #pragma unroll
     for (int k2 = 0; k2 < STEPS; ++k2)
 #pragma unroll
@@ -536,28 +567,14 @@ __device__ __forceinline__ void gemm_bf16_tn_deep_body(
         for (int mi = 0; mi < MI; ++mi)
           acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[k2][ni], fa[k2][mi], acc[ni][mi], 0, 0, 0);
   };
-  for (int kt = 0; kt < nfull; ++kt) {
-    if (kt + STAGES - 1 <= nk)
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((STAGES - 2) * PER_WAVE) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  for (int kt = 0; kt < nk; ++kt) {
+    if (kt + STAGES - 1 <= nk) __builtin_amdgcn_s_waitcnt(wait_vm((STAGES - 2) * PER_WAVE) & WAIT_LDS_TOO);
+    else __builtin_amdgcn_s_waitcnt(wait_vm(0) & WAIT_LDS_TOO);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, buf == 0 ? STAGES - 1 : buf - 1);
     multiply();
     buf = buf == STAGES - 1 ? 0 : buf + 1;
-  }
-  if (nfull < nk) {  // a short last slab: its missing tokens are zeroed
-    const int live = (int)(K - (long long)nfull * BK);
-    const u32x4 zero = {0, 0, 0, 0};
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    for (int id = tid; id < STAGE; id += NTHREADS) {
-      const int r = id < A_CH ? id / (TM / 8) : (id - A_CH) / (TN / 8);
-      if (r >= live) sbase[buf * STAGE + id] = zero;
-    }
-    __syncthreads();
-    multiply();
   }
   __syncthreads();
   add_wave_parts<WAVES_M * WAVES_N, WAVES_K>(acc, smem, wk, wmn, lane);
@@ -601,7 +618,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
   __shared__ __attribute__((aligned(16))) unsigned char tile[32 * ROW_BYTES];
   const int blocks_m = (Mo + 31) / 32, blocks_n = (No + 31) / 32, strips = (blocks_n + 3) / 4;
   const int bi = blockIdx.x / strips, j0 = (blockIdx.x % strips) * 4;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (j0 + wave < blocks_n) {
     const float *p = part + ((long long)bi * blocks_n + j0 + wave) * 1024 + lane * 4;
     const long long step = (long long)blocks_m * blocks_n * 1024;
@@ -630,7 +647,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
       u32x2 w;
       w.x = pack_bf16x2(acc[rg][0], acc[rg][1]);
       w.y = pack_bf16x2(acc[rg][2], acc[rg][3]);
-      *reinterpret_cast<u32x2 *>(tile + l32 * ROW_BYTES + (wave * 32 + rg * 8 + half * 4) * 2) = w;
+      // (16 x 16 block rg of the 32 x 32: rows rg / 2, columns rg % 2)
+      *reinterpret_cast<u32x2 *>(tile + (rg / 2 * 16 + (lane & 15)) * ROW_BYTES + (wave * 32 + rg % 2 * 16 + lane / 16 * 4) * 2) = w;
     }
   }
   __syncthreads();
@@ -665,9 +683,10 @@ hipError_t launch_gemm(const void *A, const void *Bt, void *C, long long M, int 
 // and each half of it belongs to one half of the wavefronts, whose sums are added through LDS at the end - half as many
 // steps in the chain.  Measured (M x N x K, us, 256-row tiles -> this): 512 x 1536 x 2048 39.4 -> 10.0 (64 x 64 tiles),
 // 512 x 2048 x 1024 22.2 -> 7.8, 1000 x 1536 x 2048 39.5 -> 14.1 (64 x 128), 2000 x 1536 x 2048 39.9 -> 20.4
-// (128 x 128).
-// Slower everywhere: 32-wide slabs (half the work per barrier), 128 x 192 and 256 x 128 tiles at two workgroups per CU,
-// WAVES_K = 4, a fourth stage at 64 x 64.
+// (128 x 128); its loads as buffer loads (load_to_lds): 1000 x 1536 x 2048 14.2 -> 13.8, 2000 x 1536 x 2048 20.9 -> 19.6; likewise the weight
+// gradients' small tiles: 2048 x 1536 over 1024 tokens 14.5 -> 12.9, 2048 x 2048 over 4000 48.1 -> 41.1.
+// Slower everywhere: 16x16x32 instructions (twice as many for a chain that waits for LDS), more stages, 32-wide slabs (half the work per barrier), 128 x 192 and 256 x 128 tiles at two workgroups per CU,
+// WAVES_K = 4.
 // ---------------------------------------------------------------------------
 template <int TM, int TN, int WAVES_M, int WAVES_N, int WAVES_K, int STAGES>
 __device__ __forceinline__ void gemm_bf16_nt_deep_body(
@@ -688,29 +707,25 @@ __device__ __forceinline__ void gemm_bf16_nt_deep_body(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
   const int wk = wave / (WAVES_M * WAVES_N), wmn = wave % (WAVES_M * WAVES_N), wm = wmn / WAVES_N, wn = wmn % WAVES_N;
 
-  const bf16_t *g_src[PER_WAVE];
+  const int a_rows = (int)(M - m0 < TM ? M - m0 : TM), b_rows = N - n0 < TN ? N - n0 : TN;
+  const bf16_t *const a_base = A + m0 * K, *const b_base = Bt + (long long)n0 * K;
+  const int first_wave = __builtin_amdgcn_readfirstlane(wave);
+  constexpr int SLAB = BK * WAVES_K;
+  unsigned off[PER_WAVE];  // bytes from the tile's first row of A or Bt (256 rows of K: below 2^31, gemm_mfma_supported)
 #pragma unroll
   for (int u = 0; u < PER_WAVE; ++u) {
-    const int pos = (wave + u * NWAVES) * 64 + lane;  // chunk position inside the stage
-    const int ks = pos / SUB, p = pos % SUB;
-    const bool isb = p >= TM * 8;
-    const int r = (isb ? p - TM * 8 : p) >> 3, c = (p & 7) ^ ((r & 7) ^ ((r >> 3) & 1));
-    if (!isb) {
-      const long long gr = m0 + r;
-      g_src[u] = A + (gr < M ? gr : M - 1) * K + ks * BK + c * 8;
-    } else {
-      const int gr = n0 + r;
-      g_src[u] = Bt + (long long)(gr < N ? gr : N - 1) * K + ks * BK + c * 8;
-    }
+    const int i = first_wave + u * NWAVES, ks = i / (SUB / 64), p = i % (SUB / 64) * 64 + lane;  // chunk position inside the sub-slab
+    const bool isb = i % (SUB / 64) >= TM / 8;
+    const int r = (isb ? p - TM * 8 : p) >> 3, c = (p & 7) ^ ((r & 7) ^ ((r >> 3) & 1)), rows = isb ? b_rows : a_rows;
+    off[u] = ((unsigned)(r < rows ? r : rows - 1) * K + ks * BK) * 2 + c * 16;
   }
-  typedef __attribute__((address_space(3))) void lds_void;
-  typedef __attribute__((address_space(1))) void glb_void;
-  constexpr int SLAB = BK * WAVES_K;
-  auto issue = [&](int kt, int buf) {
+  auto issue = [&](int kt, int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < PER_WAVE; ++u)
-      __builtin_amdgcn_global_load_lds((glb_void *)(g_src[u] + (long long)kt * SLAB),
-                                       (lds_void *)(sbase + buf * STAGE + (wave + u * NWAVES) * 64), 16, 0, 0);
+    for (int u = 0; u < PER_WAVE; ++u) {
+      const int i = first_wave + u * NWAVES;
+      const bool isb = i % (SUB / 64) >= TM / 8;
+      load_to_lds(isb ? b_base : a_base, (unsigned)(isb ? b_rows : a_rows) * K * 2, off[u], kt * (SLAB * 2), sbase + buf * STAGE + i * 64);
+    }
   };
   f32x16 acc[NI][MI];
 #pragma unroll
@@ -726,10 +741,8 @@ __device__ __forceinline__ void gemm_bf16_nt_deep_body(
     if (i < nk) issue(i, i);
   int buf = 0;
   for (int kt = 0; kt < nk; ++kt) {
-    if (kt + STAGES - 1 <= nk)
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((STAGES - 2) * PER_WAVE) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (kt + STAGES - 1 <= nk) __builtin_amdgcn_s_waitcnt(wait_vm((STAGES - 2) * PER_WAVE) & WAIT_LDS_TOO);
+    else __builtin_amdgcn_s_waitcnt(wait_vm(0) & WAIT_LDS_TOO);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     const int nbuf = buf == 0 ? STAGES - 1 : buf - 1;  // read in the previous step: free since the barrier
@@ -779,8 +792,8 @@ hipError_t launch_gemm_deep(const void *A, const void *Bt, void *C, long long M,
 // ---------------------------------------------------------------------------
 // A projection's two adjoints, d_A = d_C W^T (NT) and d_W = A^T d_C (TN), in one launch on small tiles: they are independent, and for
 // the row counts these tiles serve neither fills the chip.  Workgroups [0, first) work on the product with the longer tiles.
-// Backward pass, a launch each -> one (us): 2 x 512 tokens of E = 2048, 8 query and 2 KV heads of 128: 145.0 -> 138.6; 2 x 1024: 218.4 ->
-// 209.6; 1 x 1024 of E = 1024, 8 heads of 64: 106.3 -> 97.0; from about 4000 tokens on each runs in its own best form.
+// Whole backward pass, a launch each -> one (us): 512 tokens of E = 2048, 8 query and 2 KV heads of 128: 86.0 -> 80.3; 2048: 173.0 ->
+// 163.2; 1000 of E = 1024, 8 heads of 64: 78.7 -> 67.7; from about 4000 to 8000 tokens on each runs in its own best form.
 // ---------------------------------------------------------------------------
 struct NtDeep64x64 { static constexpr int TM = 64, TN = 64, WM = 2, WN = 2, WK = 2, ST = 3; };
 struct NtDeep64x128 { static constexpr int TM = 64, TN = 128, WM = 1, WN = 4, WK = 2, ST = 3; };
@@ -907,7 +920,10 @@ hipError_t gemm_mfma_bf16(const void *A, const void *Bt, void *C, long long M, i
   return hipErrorInvalidValue;
 }
 
-bool gemm_tn_mfma_supported(int Mo, int No, long long K) { return Mo % 8 == 0 && No % 8 == 0 && Mo >= 8 && No >= 8 && K >= 1; }
+// (64 tokens are addressed with 32 bits)
+bool gemm_tn_mfma_supported(int Mo, int No, long long K) {
+  return Mo % 8 == 0 && No % 8 == 0 && Mo >= 8 && No >= 8 && Mo < 1 << 23 && No < 1 << 23 && K >= 1;
+}
 
 size_t gemm_tn_scratch_bytes(int Mo, int No, long long K) {
   return (size_t)tn_splits(Mo, No, K) * ((Mo + 31) / 32) * ((No + 31) / 32) * 1024 * sizeof(float);
@@ -926,12 +942,12 @@ hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long 
   const int total = tiles_m * tiles_n;
   const long long nk = (K + BK - 1) / BK;
   const int per = (int)((nk + splits - 1) / splits);
-  constexpr size_t smem = 2ull * 2 * BK * TN_ROW;
+  constexpr size_t smem = (size_t)(A_STAGES + B_STAGES) * BK * 256 * 2;
   if (hipError_t e = raise_lds_limit<gemm_bf16_tn_kernel>(smem); e != hipSuccess) return e;
-  gemm_bf16_tn_kernel<<<(total * splits + 7) / 8 * 8, 512, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb, part, Mo,
-                                                                       No, K, tiles_n, total, splits, per);
+  gemm_bf16_tn_kernel<<<(total * splits + 7) / 8 * 8, 512, smem, s>>>((const bf16_t *)A, lda, (const bf16_t *)Bm, ldb, part, (bf16_t *)C,
+                                                                       Mo, No, K, tiles_n, total, splits, per);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || splits == 1) return e;
   const int blocks = ((Mo + 31) / 32) * ((No + 127) / 128);
   splitk_reduce_kernel<<<blocks, 256, 0, s>>>(part, splits, Mo, No, (bf16_t *)C);
   return hipGetLastError();

@@ -112,10 +112,10 @@ inline int tile_panel(int tiles_m, int tiles_n, int tm, int tn, long long K) {
 enum TnTile { TN_SPLIT, TN_64x64, TN_64x128, TN_128x128 };
 
 // Number of K splits: minimise (rounds on 256 CUs) x (slabs per split) x (time of a 256 x 256 x 64 slab) + the two launches
-// and the fp32 partial sums, written and read once.  Fits to back-to-back timings of 2 ... 16 splits at K = 4000 ... 16384: a slab
-// takes 1.5 us on a few CUs and 2.0 with all of them at work (192: 1.7, 240: 1.9), the rest 5 us + the bytes at 9 TB/s.  `us`: that
-// minimum.  1024 x 2048 over 8000 tokens: 5 splits 55.9, 8 splits 51.6 us; 2048 x 2048 over 8192: 5 splits 116.6, 4 splits 81.8;
-// 512 x 512 over 12000: 16 splits 33.3, 32 splits 29.1.
+// and the fp32 partial sums, written and read once (one split stores the result itself).  Fits (8 % rms) to back-to-back timings of 1 ...
+// 32 splits at K = 256 ... 16384, 2 ... 192 tiles: a slab takes 0.92 us on a few CUs and 1.13 with all of them at work, the rest 9.6 us +
+// the bytes at 7.2 TB/s, 4.6 without partial sums.  `us`: that minimum.  1024 x 2048 over 7996 tokens: 5 splits 47.2, 7 splits 45.3, 10
+// splits 62.4 us; 2048 x 2048 over 8192: 5 splits 98.0, 4 splits 69.9; 512 x 512 over 12000: 16 splits 28.3, 32 splits 26.7.
 inline int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
   const long long tiles = (long long)((Mo + 255) / 256) * ((No + 255) / 256);
   const long long nk = (K + 63) / 64;
@@ -126,20 +126,20 @@ inline int tn_splits(int Mo, int No, long long K, double *us = nullptr) {
     if (sp > 1 && per < 4) break;
     if ((per * (sp - 1)) >= nk) continue;  // an empty last split
     const double busy = tiles * sp < 256 ? (double)(tiles * sp) / 256.0 : 1.0;
-    const double t = (double)((tiles * sp + 255) / 256) * (double)per * (1.5 + 0.5 * busy * busy * busy) + 5.0 +
-                     (double)sp * Mo * No * 8.0 / 9e6;
+    const double t = (double)((tiles * sp + 255) / 256) * (double)per * (0.92 + 0.21 * busy * busy * busy) +
+                     (sp == 1 ? 4.6 : 9.6 + (double)sp * Mo * No * 8.0 / 7.2e6);
     if (best_t < 0 || t < best_t) best_t = t, best = sp;
   }
   if (us) *us = best_t;
   return best;
 }
 
-// Small tiles without partial sums or 256 x 256 tiles split over K, by estimated time (us).  Fits to back-to-back
-// timings over K = 64 ... 16384 tokens and 4 ... 512 tiles of (rounds) x (slabs x time per slab + fill and epilogue), b the share of
-// the CUs at work: 128 x 128 (0.615 + 0.1 b^4, 3), 64 x 128 (0.455 + 0.045 b^2, 3), 64 x 64 (0.30, 2) up to one workgroup per CU
-// and (0.60, 1.5) at two; the split form as in tn_splits.  2048 x 1536 over 1024 tokens split 30.8 us, 13.9 this way, over
-// 4000 45.4 and 43.3, over 8000 66.7 and 83.0; 1024 x 2048 over 1024 tokens 31.3 and 11.1, over 16384 82.5 and 136.9; 2048 x 2048 over
-// 8000 83.5 and 91.7, over 4000 53.0 and 46.7.
+// Small tiles without partial sums or 256 x 256 tiles split over K, by estimated time (us).  Fits (8 % rms) to back-to-back
+// timings over K = 256 ... 16384 tokens and 8 ... 768 tiles of (rounds) x (slabs x time per slab + fill and epilogue), b the share of
+// the CUs at work: 128 x 128 (0.509 + 0.051 b^4, 4.1), 64 x 128 (0.336 + 0.023 b^2, 3.6), 64 x 64 (0.209, 3.7) up to one workgroup per CU
+// and (0.488, 3.2) at two; the split form as in tn_splits.  Over these the choice costs 0.5 % on average, 13 % at most.  2048 x 1536 over
+// 1024 tokens 128 x 128 12.9 us, 64 x 64 15.5, over 4000 38.1 and split 39.4, over 7996 split 57.5; 2048 x 2048 over 4000 128 x 128 41.1,
+// over 8192 split 69.9.
 inline TnTile tn_tile(int Mo, int No, long long K, double *us = nullptr) {
   const double slabs = (double)((K + 63) / 64);
   auto tiles = [&](int tm, int tn) { return (long long)((Mo + tm - 1) / tm) * ((No + tn - 1) / tn); };
@@ -147,9 +147,9 @@ inline TnTile tn_tile(int Mo, int No, long long K, double *us = nullptr) {
   double split_us;
   tn_splits(Mo, No, K, &split_us);
   const long long t128 = tiles(128, 128), t64x128 = tiles(64, 128), t64 = tiles(64, 64);
-  const double c128 = (double)((t128 + 255) / 256) * (slabs * (0.615 + 0.1 * pow(busy(t128), 4.0)) + 3.0),
-               c64x128 = (double)((t64x128 + 255) / 256) * (slabs * (0.455 + 0.045 * pow(busy(t64x128), 2.0)) + 3.0),
-               c64 = t64 <= 256 ? slabs * 0.30 + 2.0 : (double)((t64 + 511) / 512) * (slabs * 0.60 + 1.5);
+  const double c128 = (double)((t128 + 255) / 256) * (slabs * (0.509 + 0.051 * pow(busy(t128), 4.0)) + 4.1),
+               c64x128 = (double)((t64x128 + 255) / 256) * (slabs * (0.336 + 0.023 * pow(busy(t64x128), 2.0)) + 3.6),
+               c64 = t64 <= 256 ? slabs * 0.209 + 3.7 : (double)((t64 + 511) / 512) * (slabs * 0.488 + 3.2);
   const double small = fmin(c128, fmin(c64x128, c64));
   if (us) *us = fmin(small, split_us);
   if (small >= split_us) return TN_SPLIT;
@@ -158,7 +158,7 @@ inline TnTile tn_tile(int Mo, int No, long long K, double *us = nullptr) {
 
 // ---- the two adjoints of a projection, d_A (rows, n_in) = d_C (rows, n_out) W^T and d_W (n_in, n_out) = A^T d_C -----------------
 // One launch on small tiles of both, one workgroup per CU, the product with the longer tiles first, or a launch each in its own best
-// form.  The time of the one launch is that of dealing the two kinds of tiles to 256 CUs in that order, each tile at its time from
+// form (4 us more).  The time of the one launch is that of dealing the two kinds of tiles to 256 CUs in that order, each tile at its time from
 // the fits above with all CUs at work.
 struct PairForm {
   bool one_launch;
@@ -179,16 +179,16 @@ inline PairForm gemm_pair(long long rows, int n_in, int n_out) {
   double nt_us, tn_us;
   nt_tile(rows, n_in, n_out, &nt_us);
   tn_tile(n_in, n_out, rows, &tn_us);
-  double least = nt_us + tn_us + 2.0;
+  double least = nt_us + tn_us + 4.0;
   const double s_nt = (double)(n_out / 64), s_tn = (double)((rows + 63) / 64);
   auto tiles = [](long long m, long long n, int tm, int tn) { return ((m + tm - 1) / tm) * ((n + tn - 1) / tn); };
   const bool halves = n_out % 128 == 0;
   const struct { NtTile t; int tm, tn; double us; bool ok; } nts[3] = {{NT_64x64, 64, 64, s_nt * 0.232 + 2.2, halves},
                                                                       {NT_64x128, 64, 128, s_nt * 0.354 + 3.0, halves},
                                                                       {NT_128x128, 128, 128, s_nt * 0.528 + 3.0, true}};
-  const struct { TnTile t; int tm, tn; double us; } tns[3] = {{TN_64x64, 64, 64, s_tn * 0.30 + 2.0},
-                                                              {TN_64x128, 64, 128, s_tn * 0.50 + 3.0},
-                                                              {TN_128x128, 128, 128, s_tn * 0.715 + 3.0}};
+  const struct { TnTile t; int tm, tn; double us; } tns[3] = {{TN_64x64, 64, 64, s_tn * 0.209 + 3.7},
+                                                              {TN_64x128, 64, 128, s_tn * 0.359 + 3.6},
+                                                              {TN_128x128, 128, 128, s_tn * 0.56 + 4.1}};
   for (const auto &a : nts)
     for (const auto &b : tns) {
       if (!a.ok) continue;

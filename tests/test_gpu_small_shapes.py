@@ -74,7 +74,9 @@ def test_projection_of_few_slabs_on_large_tiles(M, tile, E, slabs):
 # a number of tiles that 8 does not divide and on widths that are no multiple of the 32 x 32 blocks of the partial sums
 WGRAD_CASES = [(1, 1, 64, 64), (63, 3, 64, 256), (1000, 8, 64, 1024), (64, 8, 128, 2048), (129, 8, 128, 2048),
                (1023, 8, 128, 2048), (512, 12, 128, 2048), (2001, 12, 128, 2048), (9001, 8, 128, 2048),
-               (9001, 12, 128, 1536), (8003, 25, 40, 1160), (7001, 3, 72, 1032)]
+               (9001, 12, 128, 1536), (8003, 25, 40, 1160), (7001, 3, 72, 1032),
+               # one split (stored directly), of one, two, three and many slabs
+               (60, 32, 128, 4096), (100, 32, 128, 4096), (190, 49, 80, 4000), (1111, 49, 80, 4000)]
 
 
 @pytest.mark.parametrize("rows,Hq,dh,E", WGRAD_CASES)
