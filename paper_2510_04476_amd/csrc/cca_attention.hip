@@ -64,6 +64,7 @@ namespace {
 constexpr int BQ = 256;   // query rows per workgroup (8 wavefronts x 32 rows)
 constexpr int BKV = 64;   // keys per LDS tile
 constexpr int NT = 512;   // threads
+constexpr int PF = 3;     // operand fetches run this many MFMAs ahead
 constexpr float RESCALE_LOG2 = 8.f;
 constexpr float LOST_LOG2 = 4096.f;  // a reference max this far below the scores rounds them by up to 2^-12
 
@@ -371,21 +372,49 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
         // (one wavefront per SIMD: inline-assembly MFMAs keep the scores in ordinary vector registers, see above)
         constexpr bool INLINE_S = DH == 256;
         f32x16 sacc[2];
+        // Fragments are requested PF_ products ahead, one behind each product, and the second half's exponentials stand between the
+        // first half's products: left to the compiler a fragment was read, waited for and multiplied, and all exponentials came
+        // before the first product of V.  One wavefront per SIMD has nothing else to hide that behind.  Causal, before -> now, us (heads,
+        // sequences x tokens): d_h = 256, 8, 1 x 1024 64.2 -> 52.6, 1 x 4096 224 -> 179; 128, 16, 1 x 2048 39.7 -> 37.4, 1 x 4096 84.2
+        // -> 80.4, 1 x 8192 248.0 -> 247.4; 64, 32, 2 x 6000 368 -> 359.
+        constexpr int PF_ = INLINE_S ? 4 : PF;
+        bf16x8 fr[2 * KK], vr[4 * DT];
+        auto kfrag = [&](int i) __attribute__((always_inline)) {  // product i: half i % 2 of the keys, k-step i / 2
+          fr[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kp + (i & 1) * 32 * KROW + (i >> 1) * 32));
+        };
+        const unsigned char *vp = sVb + BUF * VBUF + vr_off;
+        auto vfrag = [&](int i) __attribute__((always_inline)) {  // product i: (half, 16 keys of it, 32 channels)
+          const unsigned char *a = vp + (i / DT) * 16 * VROW + (i % DT) * 64;
+          const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)a);
+          const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(a + 8 * VROW));
+          vr[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        };
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kp + ks * 32 * KROW));
-          sacc[ks] = INLINE_S ? score_mfma_from(kf, qf[0], negm)
-                              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[0], negm, 0, 0, 0);
+        for (int i = 0; i < PF_; ++i) kfrag(i);
+        __builtin_amdgcn_sched_barrier(0);
+        // (inline-assembly MFMAs: a query fragment that lives in the accumulation registers is copied out two products before its first use,
+        // for the compiler does not keep the copy and an inline MFMA apart)
+        bf16x8 qn[2] = {qf[0], qf[0]};
+        if constexpr (INLINE_S) {
+          asm volatile("" : "+v"(qn[0]));
+          asm volatile("s_nop 3");
         }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int kk = 1; kk < KK; ++kk)
-#pragma unroll
-          for (int ks = 0; ks < 2; ++ks) {
-            const bf16x8 kf =
-                __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kp + ks * 32 * KROW + kk * 32));
-            sacc[ks] = INLINE_S ? score_mfma(kf, qf[kk], sacc[ks])
-                                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], sacc[ks], 0, 0, 0);
-          }
+        for (int i = 0; i < 2 * KK; ++i) {
+          const int kk = i >> 1;
+          if constexpr (INLINE_S)
+            if (!(i & 1) && kk + 1 < KK) {
+              qn[(kk + 1) & 1] = qf[kk + 1];
+              asm volatile("" : "+v"(qn[(kk + 1) & 1]));
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          if (i + PF_ < 2 * KK) kfrag(i + PF_);
+          f32x16 &sc = sacc[i & 1];
+          if constexpr (INLINE_S) sc = i < 2 ? score_mfma_from(fr[i], qn[0], negm) : score_mfma(fr[i], qn[kk & 1], sc);
+          else sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], qf[kk], i < 2 ? negm : sc, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         if (INLINE_S) score_mfma_settle(sacc[0], sacc[1]);
 
         // ---- lane (l32, half) holds keys kv0 + ks*32 + 8*(r/4) + 4*half + r%4 of row qw0 + l32
@@ -434,38 +463,33 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
               for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
           }
         }
-        bf16x8 pf[2][2];
+        // probabilities of the first half, then those of the second between the first half's products
+        u32x4 pw[2][2];
+        auto unit = [&](int ks, int u) __attribute__((always_inline)) {  // scores 2u, 2u + 1
+          const float x0 = __builtin_amdgcn_exp2f(sacc[ks][2 * u]), x1 = __builtin_amdgcn_exp2f(sacc[ks][2 * u + 1]);
+          const uint32_t w = pack2(x0, x1);
+          pw[ks][u >> 2][u & 3] = w;
+          l_run += RSUM ? bf_lo(w) : x0;
+          l_run2 += RSUM ? bf_hi(w) : x1;
+        };
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int i = 0; i < PF_; ++i) vfrag(i);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int jj = 0; jj < 2; ++jj) {
-            u32x4 w;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float x0 = __builtin_amdgcn_exp2f(sacc[ks][8 * jj + 2 * e]);
-              const float x1 = __builtin_amdgcn_exp2f(sacc[ks][8 * jj + 2 * e + 1]);
-              w[e] = pack2(x0, x1);
-              l_run += RSUM ? bf_lo(w[e]) : x0;
-              l_run2 += RSUM ? bf_hi(w[e]) : x1;
-            }
-            pf[ks][jj] = __builtin_bit_cast(bf16x8, w);
-          }
-
+        for (int u = 0; u < 8; ++u) unit(0, u);
+        __builtin_amdgcn_sched_barrier(0);
         // ---- O^T += V^T P^T
-        const unsigned char *vp = sVb + BUF * VBUF + vr_off;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int i = 0; i < 4 * DT; ++i) {
+          if (i + PF_ < 4 * DT) vfrag(i + PF_);
+          const int ks = i / (2 * DT), jj = i / DT & 1;
+          oacc[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[i], __builtin_bit_cast(bf16x8, pw[ks][jj]), oacc[i % DT], 0, 0, 0);
+          // (8 pairs of scores behind 2 DT products)
 #pragma unroll
-          for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-              const unsigned char *a = vp + (ks * 32 + jj * 16) * VROW + dt * 64;
-              const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)a);
-              const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(a + 8 * VROW));
-              const v8i16 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-              oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[ks][jj], oacc[dt],
-                                                                 0, 0, 0);
-            }
+          for (int u = i * 4 / DT; u < (i + 1) * 4 / DT; ++u)
+            if (u < 8) unit(1, u);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       __syncthreads();
     };
@@ -505,7 +529,6 @@ __device__ __forceinline__ void attn_fwd_body(const bf16_t *__restrict__ Q, cons
 //   S0(j+1), PV0(j) alternating  |  exp2 / pack / row-sum of S1(j)   -> P1(j)
 //   S1(j+1), PV1(j) alternating  |  exp2 / pack / row-sum of S0(j+1) -> P0(j+1)
 // where 0 / 1 are the two 32-key halves of a tile.  K therefore runs one tile ahead of V in LDS.
-constexpr int PF = 3;  // operand fetches run this many MFMAs ahead
 enum { IT_PRO = 0, IT_FULL = 1, IT_FINAL = 2, IT_IDLE = 3 };
 
 template <int DH, bool CAUSAL, bool RSUM, int KS, int NTH>

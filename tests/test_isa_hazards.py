@@ -142,6 +142,18 @@ def test_inline_mfma_results_are_not_read_too_early(source, kernel, count):
     assert checked >= count
 
 
+def test_forward_copies_out_of_the_accumulation_registers_stand_apart():
+    """In the forward kernel operands that live in the accumulation registers are copied out at least four slots ahead as well: right
+    in front of the MFMA they gave wrong scores on the GPU."""
+    text = _isa("cca_attention.hip")
+    bodies = re.findall(r"^_ZN3cca\S*attn_fwd_wide_kernel\S*:.*?s_endpgm", text, flags=re.S | re.M)
+    assert len(bodies) >= 4
+    for body in bodies:
+        ins = [(op.replace("v_accvgpr_read", "v_mov"), *rest) for op, *rest in _parse(body.splitlines())]
+        age, which = _min_operand_age(ins)
+        assert age is not None and age >= 4, which
+
+
 @pytest.mark.parametrize("kernel,count", [("attn_bwd_dq_wide_kernel", 2), ("attn_bwd_dkdv_wide_kernel", 4)])
 def test_backward_wide_loops_keep_their_accumulators_in_place(kernel, count):
     """Every basic block of these kernels that holds MFMAs of the main loop (more than 32 of them) is free of
