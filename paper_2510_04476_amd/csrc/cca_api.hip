@@ -210,6 +210,9 @@ static cca_status projection_bwd(const Dims &d, const void *d_C, const void *W, 
     return gemm_adjoint_pair(d_C, W, d_A, A, d_W, d.rows(), n_in, n_out, static_cast<float *>(scratch), s) == hipSuccess
                ? CCA_OK
                : CCA_ERR_LAUNCH;
+  const bool a_generic = !(d.bf16 && gemm_mfma_supported(d.rows(), n_in, n_out));  // (as project_t and weight_grad choose)
+  if (d_A && d_W && a_generic && !tn_mfma(d, n_in, n_out) && gemm_generic_pair_supported(d.rows(), n_in, n_out))
+    return gemm_generic_pair(d.bf16, d_C, W, d_A, A, d_W, d.rows(), n_in, n_out, s) == hipSuccess ? CCA_OK : CCA_ERR_LAUNCH;
   cca_status st = CCA_OK;
   if (d_W) st = weight_grad(d, A, d_C, d_W, n_in, n_out, scratch, s);
   if (st == CCA_OK && d_A) st = project_t(d, d_C, W, d_A, d.rows(), n_in, n_out, s);

@@ -17,13 +17,25 @@ namespace cca {
 constexpr int GG_NT = 512, GG_WAVES = GG_NT / 64;
 constexpr long long GG_GRID = 1ll << 22;  // tiles of a launch, which takes fewer than 2^32 threads in one dimension
 
+template <typename T>
+struct GenericProduct {
+  const T *A;
+  long long lda;
+  const T *B;
+  long long ldb;
+  T *C;
+  long long ldc, M;
+  int N;
+  long long K;
+};
+typedef float GgSums[GG_WAVES][32][33];
+
 template <typename T, bool TA, bool TB, int AHEAD>
-__global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict__ A, long long lda, const T *__restrict__ Bm,
-                                                            long long ldb, T *__restrict__ C, long long ldc, long long M, int N,
-                                                            long long K, unsigned tile0) {
-  __shared__ float red[GG_WAVES][32][33];
+__device__ __forceinline__ void gemm_generic_tile(const T *__restrict__ A, long long lda, const T *__restrict__ Bm, long long ldb,
+                                                  T *__restrict__ C, long long ldc, long long M, int N, long long K, unsigned tile,
+                                                  GgSums &red) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
-  const unsigned tiles_n = (N + 31) / 32, tile = tile0 + blockIdx.x;
+  const unsigned tiles_n = (N + 31) / 32;
   const long long m0 = (long long)(tile / tiles_n) * 32;
   const int n0 = tile % tiles_n * 32;
   const long long m = m0 + l32 < M ? m0 + l32 : M - 1;  // rows and columns past the edge feed outputs that are not stored
@@ -79,6 +91,46 @@ __global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(const T *__restrict
   }
 }
 
+template <typename T, bool TA, bool TB, int AHEAD>
+__global__ __launch_bounds__(GG_NT) void gemm_generic_kernel(GenericProduct<T> p, unsigned tile0) {
+  __shared__ GgSums red;
+  gemm_generic_tile<T, TA, TB, AHEAD>(p.A, p.lda, p.B, p.ldb, p.C, p.ldc, p.M, p.N, p.K, tile0 + blockIdx.x, red);
+}
+
+// A projection's two adjoints, d_W = A^T d_C (its tiles first: the longer chains) and d_A = d_C W^T: independent, and where the tiles of
+// both are on the chip at once (generic_products_share) one launch takes as long as the longer of the two.
+template <typename T, int AHEAD_W, int AHEAD_A>
+__global__ __launch_bounds__(GG_NT) void gemm_generic_pair_kernel(GenericProduct<T> w, GenericProduct<T> a, unsigned tiles_w) {
+  __shared__ GgSums red;
+  if (blockIdx.x < tiles_w) gemm_generic_tile<T, true, false, AHEAD_W>(w.A, w.lda, w.B, w.ldb, w.C, w.ldc, w.M, w.N, w.K, blockIdx.x, red);
+  else gemm_generic_tile<T, false, true, AHEAD_A>(a.A, a.lda, a.B, a.ldb, a.C, a.ldc, a.M, a.N, a.K, blockIdx.x - tiles_w, red);
+}
+
+template <typename T>
+static hipError_t gemm_generic_pair_t(const GenericProduct<T> &w, const GenericProduct<T> &a, hipStream_t s) {
+  const long long tiles_w = (w.M + 31) / 32 * ((w.N + 31) / 32), tiles_a = (a.M + 31) / 32 * ((a.N + 31) / 32);
+  const bool ahead_w = generic_product_looks_ahead(tiles_w, w.K), ahead_a = generic_product_looks_ahead(tiles_a, a.K);
+  (ahead_w ? (ahead_a ? gemm_generic_pair_kernel<T, 4, 4> : gemm_generic_pair_kernel<T, 4, 1>)
+           : (ahead_a ? gemm_generic_pair_kernel<T, 1, 4> : gemm_generic_pair_kernel<T, 1, 1>))<<<(unsigned)(tiles_w + tiles_a), GG_NT, 0, s>>>(
+      w, a, (unsigned)tiles_w);
+  return hipGetLastError();
+}
+
+bool gemm_generic_pair_supported(long long rows, int n_in, int n_out) {
+  const long long rt = (rows + 31) / 32, in = (n_in + 31) / 32, out = (n_out + 31) / 32;
+  return generic_products_share(in * out + rt * in);
+}
+
+hipError_t gemm_generic_pair(bool bf16, const void *d_C, const void *W, void *d_A, const void *A, void *d_W, long long rows, int n_in,
+                             int n_out, hipStream_t s) {
+  auto go = [&](auto zero) {
+    typedef decltype(zero) T;
+    return gemm_generic_pair_t<T>({(const T *)A, n_in, (const T *)d_C, n_out, (T *)d_W, n_out, n_in, n_out, rows},
+                                  {(const T *)d_C, n_out, (const T *)W, n_out, (T *)d_A, n_in, rows, n_in, n_out}, s);
+  };
+  return bf16 ? go(bf16_t{}) : go(float{});
+}
+
 template <typename T>
 static hipError_t gemm_generic_t(const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb, void *C,
                                  long long ldc, long long M, int N, long long K, hipStream_t s) {
@@ -88,7 +140,7 @@ static hipError_t gemm_generic_t(const void *A, long long lda, bool ta, const vo
     const unsigned grid = (unsigned)(tiles - t < GG_GRID ? tiles - t : GG_GRID);
 #define GO(TA, TB)                                                                                                        \
   (generic_product_looks_ahead(tiles, K) ? gemm_generic_kernel<T, TA, TB, 4> : gemm_generic_kernel<T, TA, TB, 1>)<<<grid, GG_NT, 0, s>>>(              \
-      (const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K, (unsigned)t)
+      GenericProduct<T>{(const T *)A, lda, (const T *)Bm, ldb, (T *)C, ldc, M, N, K}, (unsigned)t)
     if (ta && tb) GO(true, true);
     else if (ta) GO(true, false);
     else if (tb) GO(false, true);

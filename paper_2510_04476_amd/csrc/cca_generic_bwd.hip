@@ -439,13 +439,10 @@ __global__ __launch_bounds__(GP_NT) void pro_bwd_point_generic_kernel(ProBwdArgs
   });
 }
 
-// conv1_seq transposed + qk-mean adjoint + value-shift adjoint: one thread per element of d_lat
+// conv1_seq transposed + qk-mean adjoint + value-shift adjoint: element `id` of d_lat
 template <typename T>
-__global__ __launch_bounds__(256) void pro_bwd_dlat_generic_kernel(ProBwdArgs a, const T *__restrict__ w0,
-                                                                  const float *__restrict__ d3,
-                                                                  const float *__restrict__ d1,
-                                                                  const T *__restrict__ dv, T *__restrict__ d_lat) {
-  const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void dlat_element(const ProBwdArgs &a, const T *__restrict__ w0, const float *__restrict__ d3,
+                                             const float *__restrict__ d1, const T *__restrict__ dv, T *__restrict__ d_lat, long long id) {
   if (id >= a.rows * a.n_lat) return;
   const long long row = id / a.n_lat;
   const int c = (int)(id % a.n_lat);
@@ -483,6 +480,14 @@ __global__ __launch_bounds__(256) void pro_bwd_dlat_generic_kernel(ProBwdArgs a,
   store_f(d_lat + id, val);
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void pro_bwd_dlat_generic_kernel(ProBwdArgs a, const T *__restrict__ w0,
+                                                                  const float *__restrict__ d3,
+                                                                  const float *__restrict__ d1,
+                                                                  const T *__restrict__ dv, T *__restrict__ d_lat) {
+  dlat_element(a, w0, d3, d1, dv, d_lat, (long long)blockIdx.x * 256 + threadIdx.x);
+}
+
 // The parameters' gradients, sums over all rows:
 //   dw1[h,o,i,j] = sum_rows d3[row,h,o] * u1[row - (k_ch-1-j), h, i], u1 = the conv1_seq output, recomputed from the pre-conv
 //   latent (zero before the sequence start).  Unit = (head, tap j, 32 outputs o, 32 inputs i), the rows dealt to its 8
@@ -491,7 +496,9 @@ __global__ __launch_bounds__(256) void pro_bwd_dlat_generic_kernel(ProBwdArgs a,
 //   d_temp[g] = sum_rows rowdot[row,g].  Unit = one column.
 // One launch; each unit of the first two kinds is split over the rows (grad_splits) into workgroups whose sums go to `part` and
 // are added in order by grad_reduce_kernel: a unit's chain of row blocks is what a launch of few units waits for.
-// T = 1000, 4 heads of 32: dw1 37 us, dw0 21.5 and d_temp 4.5 in unsplit launches of their own.
+// T = 1000, 4 heads of 32: dw1 37 us, dw0 21.5 and d_temp 4.5 in unsplit launches of their own.  Behind these units the launch's other
+// workgroups form d_lat, which needs the same d3 and d1 and nothing of theirs (apart 7.8 + 4.3 us, together 7.9);
+// generic_gradients_share.
 struct GradPlan {
   int n1, s1, n0, s0, nt;     // units and splits of dw1 and dw0, d_temp's columns
   long long e1, e0;           // elements of dw1, dw0
@@ -607,7 +614,8 @@ __global__ __launch_bounds__(GR_NT) void pro_bwd_grads_generic_kernel(ProBwdArgs
                                                                      const float *__restrict__ d1,
                                                                      const float *__restrict__ rowdot, T *__restrict__ dw1,
                                                                      T *__restrict__ dw0, float *__restrict__ dtemp,
-                                                                     float *__restrict__ part) {
+                                                                     float *__restrict__ part, const T *__restrict__ dv,
+                                                                     T *__restrict__ d_lat) {
   __shared__ union {
     float w1[GR_WAVES][16][64], w0[GR_NT / 32][4][33], sum[GR_NT];
   } sh;
@@ -630,7 +638,12 @@ __global__ __launch_bounds__(GR_NT) void pro_bwd_grads_generic_kernel(ProBwdArgs
     grad_w0_unit(a, lat, d1, dw0, p.s0 > 1 ? to : nullptr, id % p.n0, r0, r1, sh.w0);
     return;
   }
-  const int col = id - p.n0 * p.s0, tid = threadIdx.x;
+  id -= p.n0 * p.s0;
+  if (id >= p.nt) {
+    dlat_element(a, w0, d3, d1, dv, d_lat, (long long)(id - p.nt) * GR_NT + threadIdx.x);
+    return;
+  }
+  const int col = id, tid = threadIdx.x;
   float acc = 0.f;
 #pragma unroll 4
   for (long long r = tid; r < a.rows; r += GR_NT) acc += rowdot[r * a.Hk + col];
@@ -705,16 +718,17 @@ static hipError_t prologue_bwd_generic_t(const Dims &d, const cca_weights &w, co
   };
   hipError_t e = d.dh <= 32 ? point(std::true_type{}) : point(std::false_type{});
   if (e != hipSuccess) return e;
-  const long long n = d.rows() * d.n_lat;
-  pro_bwd_dlat_generic_kernel<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a, (const T *)w.w_conv_seq, d3, d1,
-                                                                            (const T *)d_v, (T *)d_lat);
   const GradPlan p = grad_plan(d, want1, want0, want_temp);
   const long long units = (long long)p.n1 * p.s1 + (long long)p.n0 * p.s0 + p.nt;
+  const long long n = d.rows() * d.n_lat, blocks = (n + GR_NT - 1) / GR_NT;
+  const bool share = generic_gradients_share(units + blocks);
+  if (!share || !units)
+    pro_bwd_dlat_generic_kernel<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a, (const T *)w.w_conv_seq, d3, d1,
+                                                                              (const T *)d_v, (T *)d_lat);
   if (units)
-    pro_bwd_grads_generic_kernel<T><<<(unsigned)units, GR_NT, 0, s>>>(a, p, (const T *)lat, (const T *)w.w_conv_seq, d3, d1, rowdot,
-                                                                     want1 ? (T *)gr->w_conv_ch : nullptr,
-                                                                     want0 ? (T *)gr->w_conv_seq : nullptr,
-                                                                     want_temp ? gr->temp : nullptr, part);
+    pro_bwd_grads_generic_kernel<T><<<(unsigned)(units + (share ? blocks : 0)), GR_NT, 0, s>>>(
+        a, p, (const T *)lat, (const T *)w.w_conv_seq, d3, d1, rowdot, want1 ? (T *)gr->w_conv_ch : nullptr,
+        want0 ? (T *)gr->w_conv_seq : nullptr, want_temp ? gr->temp : nullptr, part, (const T *)d_v, (T *)d_lat);
   const long long sums = (p.s1 > 1 ? p.e1 : 0) + (p.s0 > 1 ? p.e0 : 0);
   if (sums)
     grad_reduce_kernel<T><<<(unsigned)((sums + 255) / 256), 256, 0, s>>>(p, part, want1 ? (T *)gr->w_conv_ch : nullptr,

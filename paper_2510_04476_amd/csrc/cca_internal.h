@@ -147,6 +147,11 @@ hipError_t gemm_adjoint_pair(const void *d_C, const void *W, void *d_A, const vo
 // C (M,N) = op(A) op(B); ta: A is stored (K,M); tb: B is stored (N,K)
 hipError_t gemm_generic_ex(bool bf16, const void *A, long long lda, bool ta, const void *Bm, long long ldb, bool tb,
                            void *C, long long ldc, long long M, int N, long long K, hipStream_t s);
+// The two adjoints of C (rows, n_out) = A (rows, n_in) W (n_in, n_out) in one launch; widths that are multiples of 4, and only where
+// gemm_generic_pair_supported.
+bool gemm_generic_pair_supported(long long rows, int n_in, int n_out);
+hipError_t gemm_generic_pair(bool bf16, const void *d_C, const void *W, void *d_A, const void *A, void *d_W, long long rows, int n_in,
+                             int n_out, hipStream_t s);
 hipError_t attention_bwd_generic(const Dims &d, const void *q, const void *k, const void *v, const void *o,
                                  const void *o_lo, const float *lse, const void *d_o, void *d_q, void *d_k, void *d_v, float *delta,
                                  hipStream_t s);

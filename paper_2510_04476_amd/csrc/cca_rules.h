@@ -330,6 +330,13 @@ inline bool generic_attention_bwd_16(long long BHk, int R, int T, int dh, bool c
 // 64 terms 0.87-0.99x, the fewer the more tiles; 192 terms, 256 tiles 4.31 -> 4.42.
 inline bool generic_product_looks_ahead(long long tiles, long long K) { return K >= 256 && tiles <= 512; }
 
+// The two products of a projection's adjoint share a launch while four workgroups to a CU hold the tiles of both; the filter gradients
+// share theirs with d_lat, a thread per element, up to twelve to a CU.  Backward pass, fp32, a launch each -> shared, us (E, H_q, H_k, d_h x tokens; number
+// of workgroups of the second kind): 256, 2, 2, 32 x 64 39.1 -> 30.7, x 1000 (413) 77.3 -> 66.7, x 8192 (3134) 749 -> 741; 512, 4, 4, 32 x 4096 (3100)
+// 450 -> 445; beyond it the gradients hold up d_lat: x 8192 (6200) 1337 -> 1346; 256, 4, 2, 64 x 4096 (4200) 707.9 -> 714.0.
+inline bool generic_products_share(long long tiles) { return tiles <= 1024; }
+inline bool generic_gradients_share(long long workgroups) { return workgroups <= 3328; }
+
 // ---- generic prologue: tokens of a workgroup, 32 or 8 ---------------------------------------------------------------------
 // The chain of a workgroup's loads before and after the convolution is four times shorter with 8 tokens, the convolution itself (32
 // columns of a matrix instruction either way) takes as long: the better form while its query and key heads are one round of the grid.

@@ -41,6 +41,8 @@ int r_decode_keys_per_split(long long groups, int len, int dh, int rows_kernel) 
 int r_stream_takes_256(long long rows, int heads, int R, int taps, int adjoint) { return stream_takes_256(rows, heads, R, taps, adjoint); }
 int r_generic_attention_rows(long long BH, int T, int dh, int causal) { return generic_attention_rows(BH, T, dh, causal); }
 int r_generic_product_looks_ahead(long long tiles, long long K) { return generic_product_looks_ahead(tiles, K); }
+int r_generic_products_share(long long tiles) { return generic_products_share(tiles); }
+int r_generic_gradients_share(long long workgroups) { return generic_gradients_share(workgroups); }
 int r_generic_prologue_takes_8(long long B, int T, int heads) { return generic_prologue_takes_8(B, T, heads); }
 int r_generic_attention_bwd_16(long long BHk, int R, int T, int dh, int causal, int bf16) { return generic_attention_bwd_16(BHk, R, T, dh, causal, bf16); }
 int r_grad_splits(long long units, long long rows) { return grad_splits(units, rows); }
@@ -69,7 +71,7 @@ def _lib():
     for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_decode_up_lds=[L, I], r_decode_up_lds_limit=[], r_tile_panel=[I, I, I, I, L], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
                            r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
-                           r_generic_attention_bwd_16=[L, I, I, I, I, I], r_generic_prologue_takes_8=[L, I, I], r_generic_product_looks_ahead=[L, L], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
+                           r_generic_attention_bwd_16=[L, I, I, I, I, I], r_generic_prologue_takes_8=[L, I, I], r_generic_products_share=[L], r_generic_gradients_share=[L], r_generic_product_looks_ahead=[L, L], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
                            r_decode_keys_per_split=[L, I, I, I]).items():
         getattr(lib, name).argtypes = args
     lib.r_tile_panel_us.restype = C.c_double
@@ -146,6 +148,14 @@ def decode_keys_per_split(groups, keys, dh, rows_kernel):
 
 def generic_product_looks_ahead(tiles, K):
     return bool(_lib().r_generic_product_looks_ahead(tiles, K))
+
+
+def generic_products_share(tiles):
+    return bool(_lib().r_generic_products_share(tiles))
+
+
+def generic_gradients_share(workgroups):
+    return bool(_lib().r_generic_gradients_share(workgroups))
 
 
 def generic_prologue_takes_8(B, T, heads):

@@ -182,6 +182,16 @@ def test_generic_cases_reach_both_products():
     assert ahead == {(transposed, four) for transposed in (False, True) for four in (False, True)}
 
 
+def test_generic_cases_share_launches_and_do_not():
+    tiles = lambda m, n: -(-m // 32) * -(-n // 32)
+    products, gradients = set(), set()
+    for c in small.GENERIC_CASES:
+        rows, e_q, n_lat = c["B"] * c["T"], c["Hq"] * c["dh"], (c["Hq"] + 2 * c["Hk"]) * c["dh"]
+        products |= {rules.generic_products_share(tiles(n_in, n_out) + tiles(rows, n_in)) for n_in, n_out in ((e_q, c["E"]), (c["E"], n_lat))}
+        gradients.add(rules.generic_gradients_share(-(-rows * n_lat // 512)))
+    assert products == {True, False} and gradients == {True, False}
+
+
 # T, query and key heads and us of the prologue with 32 tokens a workgroup, with 8
 @pytest.mark.parametrize("T,heads,us32,us8", [(300, 6, 10.5, 8.7), (128, 10, 19.1, 15.8), (64, 32, 10.4, 8.9), (300, 10, 19.2, 21.3), (64, 40, 19.1, 21.9)])
 def test_generic_prologue_form_is_the_faster(T, heads, us32, us8):

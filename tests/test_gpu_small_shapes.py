@@ -522,7 +522,9 @@ GENERIC_CASES = [dict(B=1, T=1, E=48, Hq=2, Hk=1, dh=12, k_seq=2, k_ch=2), dict(
                  dict(B=2, T=161, E=64, Hq=2, Hk=2, dh=32, k_seq=2, k_ch=2), dict(B=3, T=48, E=128, Hq=2, Hk=1, dh=64, k_seq=2, k_ch=2),
                  dict(B=1, T=31, E=256, Hq=1, Hk=1, dh=256, k_seq=2, k_ch=2), dict(B=1, T=1024, E=64, Hq=2, Hk=2, dh=32, k_seq=2, k_ch=2),
                  # more workgroups than one round: the attention's 32-row forms (tests/test_dispatch_rules.py)
-                 dict(B=6, T=65, E=192, Hq=24, Hk=12, dh=8, k_seq=2, k_ch=2), dict(B=13, T=161, E=288, Hq=3, Hk=3, dh=96, k_seq=2, k_ch=2)]
+                 dict(B=6, T=65, E=192, Hq=24, Hk=12, dh=8, k_seq=2, k_ch=2), dict(B=13, T=161, E=288, Hq=3, Hk=3, dh=96, k_seq=2, k_ch=2),
+                 # a projection's adjoints in a launch each
+                 dict(B=5, T=450, E=512, Hq=2, Hk=1, dh=32, k_seq=2, k_ch=2)]
 
 
 @pytest.mark.parametrize("causal", [True, False])
