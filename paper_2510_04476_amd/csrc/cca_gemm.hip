@@ -26,27 +26,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-// Operands of s_waitcnt: vector memory operations that may be outstanding (and any LDS operation); no LDS operation; with &, none of these
-// either.
-constexpr int wait_vm(int n) { return 0x0f70 | (n & 15) | n >> 4 << 14; }
-constexpr int WAIT_LDS = 0xc07f, WAIT_LDS_TOO = 0xf0ff;
-
 constexpr int BM = 256, BK = 64;
 constexpr int A_STAGES = 3, B_STAGES = 2;  // slabs of each operand in the LDS of the 256-row product
 
 // LDS position of the 16-byte chunk c (0..7) of row r in a [rows][64] bf16 tile
 __device__ __forceinline__ int swz(int r, int c) { return r * 8 + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
-
-// Direct load to LDS, 16 bytes a lane: lane i of the wavefront fills chunk i behind `to` (the same for all lanes) from `bytes` bytes
-// at `base` (0 beyond them), `lane_off` + `off` bytes into them.  (A buffer load: while a global load into LDS is outstanding the
-// compiler counts it as an LDS operation that may come back out of order, and every wait for a fragment becomes one for all of them.)
-__device__ __forceinline__ void load_to_lds(const void *base, unsigned bytes, unsigned lane_off, int off, void *to) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef __attribute__((address_space(3))) void lds_void;
-  const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void *)to, 16, lane_off, off, 0, 0);
-#endif
-}
 
 // two floats -> one word of two bf16 (round to nearest even) with the hardware conversion instruction
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {

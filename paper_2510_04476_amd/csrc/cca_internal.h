@@ -35,6 +35,22 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   u += 0x7fffu + ((u >> 16) & 1u);
   return (bf16_t)(u >> 16);
 }
+// Direct load to LDS, 16 bytes a lane: lane i of the wavefront fills chunk i behind `to` (the same for all lanes) from `bytes` bytes
+// at `base` (0 beyond them), `lane_off` + `off` bytes into them.  (A buffer load: while a global load into LDS is outstanding the
+// compiler counts it as an LDS operation that may come back out of order, and every wait for a fragment becomes one for all of them.)
+__device__ __forceinline__ void load_to_lds(const void *base, unsigned bytes, unsigned lane_off, int off, void *to) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef __attribute__((address_space(3))) void lds_void;
+  const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void *)to, 16, lane_off, off, 0, 0);
+#endif
+}
+
+// Operands of s_waitcnt: vector memory operations that may be outstanding (and any LDS operation); no LDS operation; with &, none of these
+// either.
+constexpr int wait_vm(int n) { return 0x0f70 | (n & 15) | n >> 4 << 14; }
+constexpr int WAIT_LDS = 0xc07f, WAIT_LDS_TOO = 0xf0ff;
+
 __device__ __forceinline__ float load_f(const float *p) { return *p; }
 __device__ __forceinline__ float load_f(const bf16_t *p) { return bf16_to_f32(*p); }
 __device__ __forceinline__ void store_f(float *p, float v) { *p = v; }

@@ -438,14 +438,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
 // ---------------------------------------------------------------------------
 // The same prologue for d_h = 256, where one head's folded filter (D x 256 x 256 bf16 = 128 KB per tap) cannot
-// stay in LDS: the filter is STREAMED through a ring of four LDS slabs (16 KB each, three in flight while one is
-// multiplied, requested straight into LDS with one bare barrier per slab), all 4 wavefronts of a workgroup walking
-// the slabs in step.  Workgroup = one head x 128 tokens, wavefront = 32 tokens x all 256 outputs (8 accumulator
-// tiles), one wavefront per SIMD.  The token rows of a wavefront (its 32 and the D - 1 its taps reach) are fetched
-// once, whole, into its own staging rows in LDS and read from there tap by tap, and results leave through the same
-// rows: as fragments straight from memory a load instruction touches 32 rows with 32 bytes each, and the memory
-// pipeline takes about 4.6 cycles per cache line - with 256-token workgroups and two slabs that was what the kernel
-// waited for (6000 tokens, 4 / 1 heads: 50.7 us, now 32.4).  BWD = true is the adjoint, as for the kernel above:
+// stay in LDS: the filter is STREAMED through a ring of four LDS slabs (16 KB each, requested straight into LDS with
+// one bare barrier per slab), all 4 wavefronts of a workgroup walking the slabs in step.  Workgroup = one head x 128
+// tokens, wavefront = 32 tokens x all 256 outputs (8 accumulator tiles), one wavefront per SIMD.  The token rows of a
+// wavefront (its 32 and the D - 1 its taps reach) are fetched once, whole, into its own staging rows in LDS and read
+// from there tap by tap, and results leave through the same rows: as fragments straight from memory a load instruction
+// touches 32 rows with 32 bytes each, and the memory pipeline takes about 4.6 cycles per cache line.
+// With one wavefront per SIMD nothing else covers a wait, so the fragments of one k-step are read between the products
+// of the one before (a slab's barrier stands between its two k-steps, so the next slab's come as early), the rows of the
+// qk-mean's other stream follow the filter through the ring as further slabs, and the rotary table's entries are on
+// their way under the norm.  Read, multiplied and rotated one after the other: 16 workgroups 24.4 us, now 17.6 (adjoint
+// 19.3 and 15.0); 235 (6000 tokens, 4 / 1 heads, one per CU) 32.8 and 27.5 (28.5 and 25.4), where the row traffic,
+// 45 MB that all workgroups ask for at the same times, is the larger part; 3000 tokens, 8 / 2 heads, 32.7 and 27.3.
+// In LDS a slab's reads take 576 cycles, its products 512.
+// BWD = true is the adjoint, as for the kernel above:
 // transposed filter, taps reaching forward in time, the value shift running backwards; the host passes only the
 // qk-mean and value-shift flags, so the norm and RoPE steps are skipped.
 // ---------------------------------------------------------------------------
@@ -695,12 +701,30 @@ struct StreamHead {
   }
 };
 
-// Per token: norm, temperature, RoPE (lane (l32, half): channels 32*nt + 8*rg + 4*half + e)
+// Per token: norm, temperature, RoPE (lane (l32, half): channels 32*nt + 8*rg + 4*half + e).  The table entries of AHEAD of the 16 groups
+// of pairs are on their way at a time, the first ones under the norm: fetched group by group they were 16 latencies one after the other,
+// 6 us of the 128-token kernel (0: they are, where registers are short and the SIMD has another wavefront)
+template <int AHEAD>
 __device__ __forceinline__ void norm_and_rope_256(f32x16 (&acc)[8], const FusedArgs &a, int head, float beta, long long row, int tpos,
                                                   int half, const float2 *__restrict__ ropeA, const float2 *__restrict__ ropeB,
                                                   float *__restrict__ rnorm) {
-  constexpr int DH = 256, NTL = DH / 32;
+  constexpr int DH = 256, NTL = DH / 32, GROUPS = NTL / 2 * 4;
   const int NH = a.Hq + a.Hk;
+  const bool rope = a.flags & CCA_ROPE;
+  f32x4 table[AHEAD ? AHEAD : 1][4];
+  const int thi = tpos >> 7, tlo = tpos & 127;
+  auto fetch = [&](int i) __attribute__((always_inline)) {
+    const int i0 = i * 8 + half * 4;  // 4 consecutive pair indices
+    const f32x4 *pa = reinterpret_cast<const f32x4 *>(ropeA + thi * (DH / 2) + i0);
+    const f32x4 *pb = reinterpret_cast<const f32x4 *>(ropeB + ((i0 >> 2) * 128 + tlo) * 4);
+    f32x4 (&t)[4] = table[AHEAD ? i % AHEAD : 0];
+    t[0] = pa[0], t[1] = pa[1], t[2] = pb[0], t[3] = pb[1];
+    if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+  };
+  if (rope) {
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) fetch(i);
+  }
   if (a.flags & CCA_QK_NORM) {
     float ssq = 0.f;
 #pragma unroll
@@ -717,27 +741,24 @@ __device__ __forceinline__ void norm_and_rope_256(f32x16 (&acc)[8], const FusedA
   } else if (rnorm && half == 0 && row < a.rows) {
     rnorm[row * NH + head] = 1.f;
   }
-  if (a.flags & CCA_ROPE) {
-    const int thi = tpos >> 7, tlo = tpos & 127;
+  if (rope) {
 #pragma unroll
-    for (int nt = 0; nt < NTL / 2; ++nt)
+    for (int i = 0; i < GROUPS; ++i) {
+      const int nt = i / 4, rg = i % 4;
+      if (!AHEAD) fetch(i);
+      const f32x4 (&t)[4] = table[AHEAD ? i % AHEAD : 0];
+      const float ca[4] = {t[0].x, t[0].z, t[1].x, t[1].z}, sa[4] = {t[0].y, t[0].w, t[1].y, t[1].w};
+      const float cb[4] = {t[2].x, t[2].z, t[3].x, t[3].z}, sb[4] = {t[2].y, t[2].w, t[3].y, t[3].w};
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int i0 = nt * 32 + rg * 8 + half * 4;  // 4 consecutive pair indices
-        const f32x4 *pa = reinterpret_cast<const f32x4 *>(ropeA + thi * (DH / 2) + i0);
-        const f32x4 *pb = reinterpret_cast<const f32x4 *>(ropeB + ((i0 >> 2) * 128 + tlo) * 4);
-        const f32x4 a01 = pa[0], a23 = pa[1], b01 = pb[0], b23 = pb[1];
-        const float ca[4] = {a01.x, a01.z, a23.x, a23.z}, sa[4] = {a01.y, a01.w, a23.y, a23.w};
-        const float cb[4] = {b01.x, b01.z, b23.x, b23.z}, sb[4] = {b01.y, b01.w, b23.y, b23.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float cs = ca[e] * cb[e] - sa[e] * sb[e];
-          const float sn = sa[e] * cb[e] + ca[e] * sb[e];
-          const float x1 = acc[nt][rg * 4 + e], x2 = acc[nt + NTL / 2][rg * 4 + e];
-          acc[nt][rg * 4 + e] = x1 * cs - x2 * sn;
-          acc[nt + NTL / 2][rg * 4 + e] = x2 * cs + x1 * sn;
-        }
+      for (int e = 0; e < 4; ++e) {
+        const float cs = ca[e] * cb[e] - sa[e] * sb[e];
+        const float sn = sa[e] * cb[e] + ca[e] * sb[e];
+        const float x1 = acc[nt][rg * 4 + e], x2 = acc[nt + NTL / 2][rg * 4 + e];
+        acc[nt][rg * 4 + e] = x1 * cs - x2 * sn;
+        acc[nt + NTL / 2][rg * 4 + e] = x2 * cs + x1 * sn;
       }
+      if (AHEAD && i + AHEAD < GROUPS) fetch(i + AHEAD);
+    }
   }
 }
 
@@ -751,8 +772,7 @@ __device__ __forceinline__ void prologue_stream_body(
   constexpr int DH = 256, NTL = DH / 32, CPR = DH / 8, ROWB = DH * 2;
   constexpr int QS = DH / SLAB_K, NSLAB = D * QS;              // slabs per tap, slabs
   constexpr int SLAB_INSTR = SLAB_BYTES / 1024 / ST_WAVES;     // load instructions of a wavefront per slab
-  typedef __attribute__((address_space(3))) void lds_void;
-  typedef __attribute__((address_space(1))) void glb_void;
+  static_assert(NSLAB % ST_RING == 0 && ST_RING == 4 && SLAB_INSTR == 4, "a source of the qk-mean is one turn of the ring");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
@@ -770,49 +790,57 @@ __device__ __forceinline__ void prologue_stream_body(
   const int dst_stride = is_q ? a.q_stride : a.k_stride;
 
   // this wavefront's 32 tokens (a wavefront past the end keeps walking the slabs: it loads filter chunks too)
-  const long long trow0 = (long long)hd.bid * (ST_WAVES * 32) + wave * 32;
+  const int first_wave = __builtin_amdgcn_readfirstlane(wave);  // the wavefront, as the scalar that the loads' addresses are made of
+  const long long trow0 = (long long)hd.bid * (ST_WAVES * 32) + first_wave * 32;
   const long long row = trow0 + l32;
   const long long rowc = row < a.rows ? row : a.rows - 1;
   const int tpos = (int)(rowc % a.T);
   const bool any_pad = __any(BWD ? tpos + D - 1 >= a.T : tpos < D - 1) != 0;
 
-  unsigned char *const ring = smem, *const stg = smem + ST_RING * SLAB_BYTES + wave * (stream_rows(D) * ROWB);
-  // 2 rows per load instruction; chunk c of staged row j lies at c ^ (j mod 16); rows outside the tensor repeat an end row
-  // (they lie outside the token's sequence: zeroed or dropped below)
-  auto fetch_rows = [&](unsigned char *to, int col, int first, int n_instr) {
-    for (int i = 0; i < n_instr; ++i) {
-      const int j = 2 * i + (lane >> 5), p = lane & 31;
-      long long r = trow0 + first + j;
-      r = r < 0 ? 0 : (r > a.rows - 1 ? a.rows - 1 : r);
-      __builtin_amdgcn_global_load_lds((glb_void *)(lat + r * a.src_stride + col + (p ^ (j & 15)) * 8), (lds_void *)(to + i * 1024), 16, 0, 0);
-    }
-  };
-  auto row_frag = [&](const unsigned char *from, int j, int kk) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(from + j * ROWB + (((2 * kk + half) ^ (j & 15)) * 16)));
-  };
-  const u32x4 *const wsrc = wc + (long long)hd.head * NSLAB * (SLAB_BYTES / 16) + lane;
-  auto fetch_slab = [&](int s_) {
-#pragma unroll
-    for (int u = 0; u < SLAB_INSTR; ++u) {
-      const int i = wave * SLAB_INSTR + u;
-      __builtin_amdgcn_global_load_lds((glb_void *)(wsrc + (long long)s_ * (SLAB_BYTES / 16) + i * 64),
-                                       (lds_void *)(ring + (s_ % ST_RING) * SLAB_BYTES + i * 1024), 16, 0, 0);
-    }
-  };
-  fetch_rows(stg, ch0, BWD ? 0 : -(D - 1), stream_rows(D) / 2);
-#pragma unroll
-  for (int s_ = 0; s_ < ST_RING - 1; ++s_) fetch_slab(s_);
+  // Rows outside the tensor repeat an end row (they lie outside the token's sequence: zeroed or dropped below).  Rows count from the
+  // wavefront's first token, a load's offset from row_from, the first row that it touches (scalars: 64-bit minima are made in vector
+  // registers)
+  const int row_min = __builtin_amdgcn_readfirstlane((int)max(-trow0, -64ll)), row_max = __builtin_amdgcn_readfirstlane((int)min(a.rows - 1 - trow0, 64ll));
+  auto clamp_row = [&](int r) { return min(max(r, row_min), row_max); };
+  const int row_from = clamp_row(BWD ? 0 : -(D - 1));
+  const bf16_t *const lat_from = lat + (trow0 + row_from) * a.src_stride;
+  auto row_off = [&](int r) { return (unsigned)(clamp_row(r) - row_from) * (unsigned)a.src_stride * 2; };
+  constexpr unsigned NO_BOUND = 0x7fffffff;  // (the rows are clamped)
 
-  // qk-mean weights as identity fragments (see prologue_fused_kernel)
-  const bool mean = a.flags & CCA_QK_MEAN;
-  auto identity_frag = [&](bf16_t wbits, int j) {
-    const bool on = ((l32 >> 4) == j) && (((l32 >> 3) & 1) == half);
-    u32x4 w = {0, 0, 0, 0};
-    const int e = l32 & 7;
-    if (on) w[e >> 1] = (uint32_t)wbits << ((e & 1) * 16);
-    return __builtin_bit_cast(bf16x8, w);
+  unsigned char *const ring = smem, *const stg = smem + ST_RING * SLAB_BYTES + first_wave * (stream_rows(D) * ROWB);
+  // the token rows, 2 per load instruction; chunk c of staged row j lies at c ^ (j mod 16)
+  constexpr int FIRST = BWD ? 0 : -(D - 1);
+#pragma unroll
+  for (int i = 0; i < stream_rows(D) / 2; ++i) {
+    const int j = 2 * i + (lane >> 5), p = lane & 31;
+    load_to_lds(lat_from, NO_BOUND, row_off(FIRST + j) + (p ^ (j & 15)) * 16, ch0 * 2, stg + i * 1024);
+  }
+  auto row_frag = [&](int j, int kk) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(stg + j * ROWB + (((2 * kk + half) ^ (j & 15)) * 16)));
   };
-  const bf16x8 id_half[2] = {identity_frag(f32_to_bf16(0.5f), 0), identity_frag(f32_to_bf16(0.5f), 1)};
+  const bool mean = a.flags & CCA_QK_MEAN;
+  // Ring slab s_ < NSLAB: the filter's.  Slab NSLAB + 4 x + c: of the qk-mean's source x (another head's rows) the workgroup's 128 tokens
+  // x 64 channels from 64 c on, each wavefront its own 32 rows, chunk c of row j at c ^ (j mod 8); beyond the last source, or without
+  // the qk-mean, nothing is read for it.
+  const int n_src = mean ? (is_q ? 1 : a.R) : 0;
+  int src_col = (is_q ? a.e_q + g * DH : g * a.R * DH) * 2, src_bound = mean ? NO_BOUND : 0;
+  asm volatile("" : "+s"(src_col), "+s"(src_bound));  // (settled here: chosen at the loads they would be branches between the products)
+  unsigned src_off[SLAB_INSTR];
+#pragma unroll
+  for (int u = 0; u < SLAB_INSTR; ++u) src_off[u] = row_off(8 * u + (lane >> 3)) + ((lane & 7) ^ (lane >> 3)) * 16;
+  const u32x4 *const wsrc = wc + (long long)hd.head * NSLAB * (SLAB_BYTES / 16);
+  auto fetch_filter = [&](int s_, int u) __attribute__((always_inline)) {
+    const int i = first_wave * SLAB_INSTR + u;
+    load_to_lds(wsrc, NSLAB * SLAB_BYTES, lane * 16, s_ * SLAB_BYTES + i * 1024, ring + (s_ % ST_RING) * SLAB_BYTES + i * 1024);
+  };
+  auto fetch_source = [&](int x, int bound, int c, int u) __attribute__((always_inline)) {
+    load_to_lds(lat_from, bound, src_off[u], src_col + x * (DH * 2) + c * 128, ring + c * SLAB_BYTES + (first_wave * SLAB_INSTR + u) * 1024);
+  };
+  auto fetch = [&](int s_, int u) __attribute__((always_inline)) { s_ < NSLAB ? fetch_filter(s_, u) : fetch_source(0, src_bound, s_ - NSLAB, u); };
+#pragma unroll
+  for (int s_ = 0; s_ < ST_RING; ++s_)
+#pragma unroll
+    for (int u = 0; u < SLAB_INSTR; ++u) fetch(s_, u);
 
   f32x16 acc[NTL];
 #pragma unroll
@@ -824,79 +852,96 @@ __device__ __forceinline__ void prologue_stream_body(
   uint32_t woff[2];
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk) woff[kk] = ((l32 >> 1) * 8 + ((((l32 & 1) << 2) | (2 * kk + half)) ^ ((l32 >> 2) & 3))) * 16;
-#pragma unroll 1
-  for (int d = 0; d < D; ++d) {
-    const int back = D - 1 - d, j = BWD ? l32 + back : l32 + D - 1 - back;
-    const bool outside = any_pad && (BWD ? tpos + back >= a.T : tpos < back);
+  // Two sets of fragments, one per k-step of 16 channels; the other set is read between the products of one
+  bf16x8 uf[2], wf[2][NTL];
+  auto read = [&](int s_, int kk, int i) __attribute__((always_inline)) {
+    const int back = D - 1 - s_ / QS;
+    if (i == 0) uf[kk] = row_frag(BWD ? l32 + back : l32 + D - 1 - back, 2 * (s_ % QS) + kk);
+    else wf[kk][i - 1] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(ring + (s_ % ST_RING) * SLAB_BYTES + woff[kk] + (i - 1) * 2048));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int s_, int kk, int nt) __attribute__((always_inline)) {
+    const int back = D - 1 - s_ / QS;
+    if (nt == 0 && back > 0 && any_pad && (BWD ? tpos + back >= a.T : tpos < back)) uf[kk] = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
+    acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk][nt], uf[kk], acc[nt], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  __builtin_amdgcn_s_waitcnt(wait_vm((ST_RING - 1) * SLAB_INSTR) & WAIT_LDS_TOO);  // the token rows and slab 0
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 #pragma unroll
-    for (int c = 0; c < QS; ++c) {  // compile-time: the channel group picks accumulator tiles of the qk-mean
-      const int s_ = d * QS + c;
-      // slab s_ has landed when only the two after it are in flight; the first wait covers the token rows as well
-      if (s_ + 2 < NSLAB) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * SLAB_INSTR) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      if (s_ + ST_RING - 1 < NSLAB) fetch_slab(s_ + ST_RING - 1);  // its place was read in the step before: free since the barrier
-      const unsigned char *const sw = ring + (s_ % ST_RING) * SLAB_BYTES;
-      bf16x8 uf[2], wf[2][NTL];
+  for (int i = 0; i <= NTL; ++i) read(0, 0, i);
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        uf[kk] = row_frag(stg, j, 2 * c + kk);
+  for (int s_ = 0; s_ < NSLAB; ++s_) {
 #pragma unroll
-        for (int nt = 0; nt < NTL; ++nt) wf[kk][nt] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(sw + woff[kk] + nt * 2048));
-        __builtin_amdgcn_sched_barrier(0);  // the second k-step's fragments are on their way under the first's products
+    for (int nt = 0; nt < NTL; ++nt) {
+      multiply(s_, 0, nt);
+      if (nt == 0) read(s_, 1, 0);
+      read(s_, 1, nt + 1);
+    }
+    // every wavefront holds its last fragments of slab s_, and slab s_ + 1 has landed when only the two behind it are outstanding
+    __builtin_amdgcn_s_waitcnt(wait_vm((ST_RING - 2) * SLAB_INSTR) & WAIT_LDS_TOO);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int nt = 0; nt < NTL; ++nt) {
+      multiply(s_, 1, nt);
+      if (s_ + 1 < NSLAB) {
+        if (nt == 0) read(s_ + 1, 0, 0);
+        read(s_ + 1, 0, nt + 1);
       }
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-        if (outside) uf[kk] = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-        for (int nt = 0; nt < NTL; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk][nt], uf[kk], acc[nt], 0, 0, 0);
-      if (mean && back == 0) {  // own stream of the qk-mean: + 1/2 of the token's own row; channels 32 c .. lie in tile c
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[kk], uf[kk], acc[c], 0, 0, 0);
-      }
+      if (nt % 2 == 1) fetch(s_ + ST_RING, nt / 2);
     }
   }
 
-  // ---- other stream of the qk-mean: each source's rows fetched whole, alternately into this wavefront's quarter of the
-  //      ring and its staging rows, the next source's on the way while one is added
-  __syncthreads();  // the ring is no longer read
   if (mean) {
+    // qk-mean weights as identity fragments (see prologue_fused_kernel)
+    auto identity_frag = [&](bf16_t wbits, int j) {
+      const bool on = ((l32 >> 4) == j) && (((l32 >> 3) & 1) == half);
+      u32x4 w = {0, 0, 0, 0};
+      const int e = l32 & 7;
+      if (on) w[e >> 1] = (uint32_t)wbits << ((e & 1) * 16);
+      return __builtin_bit_cast(bf16x8, w);
+    };
+    // ---- own stream: + 1/2 of the token's own row; channels 32 c .. lie in tile c
+    const bf16x8 id_half[2] = {identity_frag(f32_to_bf16(0.5f), 0), identity_frag(f32_to_bf16(0.5f), 1)};
+    const int own = BWD ? l32 : l32 + D - 1;
+#pragma unroll
+    for (int c = 0; c < QS; ++c)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[kk], row_frag(own, 2 * c + kk), acc[c], 0, 0, 0);
+    // ---- other stream: the sources' slabs, the wavefront's own rows of each
     const float w_other = is_q ? a.mean_q_other : a.mean_k_other;
     const bf16_t w_other_hi = f32_to_bf16(w_other);
     const bf16_t w_other_lo = f32_to_bf16(w_other - bf16_to_f32(w_other_hi));
     const bool grp_lo = (w_other_lo & 0x7fffu) != 0;  // uniform over the workgroup
     const bf16x8 id_hi[2] = {identity_frag(w_other_hi, 0), identity_frag(w_other_hi, 1)};
     const bf16x8 id_lo[2] = {identity_frag(w_other_lo, 0), identity_frag(w_other_lo, 1)};
-    unsigned char *const buf0 = ring + wave * (32 * ROWB);
-    const int nsrc = is_q ? 1 : a.R;
-    auto fetch_src = [&](int x) { fetch_rows(x & 1 ? stg : buf0, is_q ? a.e_q + g * DH : (g * a.R + x) * DH, 0, 16); };
-    fetch_src(0);
-    for (int x = 0; x < nsrc; ++x) {
-      if (x + 1 < nsrc) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        fetch_src(x + 1);
-        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-      } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
-      const unsigned char *const from = x & 1 ? stg : buf0;
+    for (int x = 0; x < n_src; ++x) {
 #pragma unroll
-      for (int c = 0; c < QS; ++c) {
-        const bf16x8 m0 = row_frag(from, l32, 2 * c), m1 = row_frag(from, l32, 2 * c + 1);
-        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_hi[0], m0, acc[c], 0, 0, 0);
-        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_hi[1], m1, acc[c], 0, 0, 0);
-        if (grp_lo) {
-          acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_lo[0], m0, acc[c], 0, 0, 0);
-          acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_lo[1], m1, acc[c], 0, 0, 0);
+      for (int c = 0; c < 4; ++c) {
+        __builtin_amdgcn_s_waitcnt(wait_vm((ST_RING - 1) * SLAB_INSTR));
+        asm volatile("" ::: "memory");
+        bf16x8 m[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          m[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(ring + c * SLAB_BYTES + first_wave * (SLAB_BYTES / ST_WAVES) + l32 * 128 + (((2 * kk + half) ^ (l32 & 7)) * 16)));
+        __builtin_amdgcn_s_waitcnt(WAIT_LDS);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int u = 0; u < SLAB_INSTR; ++u) fetch_source(x + 1, x + 1 < n_src ? NO_BOUND : 0, c, u);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          acc[2 * c + kk / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_hi[kk & 1], m[kk], acc[2 * c + kk / 2], 0, 0, 0);
+          if (grp_lo) acc[2 * c + kk / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_lo[kk & 1], m[kk], acc[2 * c + kk / 2], 0, 0, 0);
         }
       }
     }
   }
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));  // no load into LDS outlives the workgroup
 
-  norm_and_rope_256(acc, a, hd.head, beta, row, tpos, half, ropeA, ropeB, rnorm);
+  norm_and_rope_256<4>(acc, a, hd.head, beta, row, tpos, half, ropeA, ropeB, rnorm);
   // ---- round once to bf16; through this wavefront's staging rows (16-byte chunk c of row r at c ^ r), out as whole rows
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows' last readers are done
 #pragma unroll
@@ -911,11 +956,18 @@ __device__ __forceinline__ void prologue_stream_body(
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // LDS handles a wavefront's accesses in order
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  bf16_t *const to = dst + trow0 * dst_stride;
+  const int rows_left = (int)min(a.rows - trow0, 32ll);
 #pragma unroll
-  for (int it = 0; it < 16; ++it) {
-    const int rr = it * 2 + (lane >> 5), p = lane & 31, c = p ^ rr;
-    const u32x4 val = *reinterpret_cast<const u32x4 *>(stg + rr * ROWB + p * 16);
-    if (trow0 + rr < a.rows) *reinterpret_cast<u32x4 *>(dst + (trow0 + rr) * dst_stride + c * 8) = val;
+  for (int it = 0; it < 16; it += 8) {
+    u32x4 out[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) out[u] = *reinterpret_cast<const u32x4 *>(stg + ((it + u) * 2 + (lane >> 5)) * ROWB + (lane & 31) * 16);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int rr = (it + u) * 2 + (lane >> 5), c = (lane & 31) ^ rr;
+      if (rr < rows_left) *reinterpret_cast<u32x4 *>(to + rr * dst_stride + c * 8) = out[u];
+    }
   }
 }
 
@@ -932,8 +984,8 @@ __global__ __launch_bounds__(ST_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 // The form for grids of several rounds: 256 tokens per workgroup, 8 wavefronts x 32 tokens, two per SIMD.  Each filter byte
 // that comes into LDS serves twice as many tokens, and a wavefront's waits hide under its SIMD's other one; there is no room
 // for staged token rows, so their fragments come straight from the latent rows, and the filter goes through registers into two
-// buffers of two slabs (64 input channels).  Bound by the filter reads from LDS and the waits between barriers: 16384 tokens, 8 / 8
-// heads 225 us against 261 for the kernel above (6000 tokens, 4 / 1 heads: 48 against 29.5; the rule is stream_takes_256).
+// buffers of two slabs (64 input channels).  Bound by the filter reads from LDS and the waits between barriers: 16384 tokens, 8 / 2
+// heads 129 us against 132 for the kernel above (6000 tokens, 4 / 1 heads: 48 against 27.5; the rule is stream_takes_256).
 // ---------------------------------------------------------------------------
 template <int D, bool BWD>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void prologue_stream_long_kernel(
@@ -1065,7 +1117,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
   }
 
-  norm_and_rope_256(acc, a, hd.head, beta, row, tpos, half, ropeA, ropeB, rnorm);
+  norm_and_rope_256<0>(acc, a, hd.head, beta, row, tpos, half, ropeA, ropeB, rnorm);
   if (row < a.rows) {
     bf16_t *const orow = is_q ? q + hd.head * DH + row * a.q_stride : k + hd.g * DH + row * a.k_stride;
 #pragma unroll

@@ -278,17 +278,17 @@ inline bool prologue_is_short(long long rows, int heads, int R, int dh, bool adj
 }
 
 // ---- prologue at d_h = 256: one head x 128 tokens per workgroup (one wavefront per SIMD) or 256 (two) -------------------
-// One workgroup per CU either way.  A lone round of the 128-token form takes half of the other's time (24 against 45 us at two
-// taps each and 6 / 2 heads), a full one 0.6 of it, so it wins while one round is enough (4096 tokens: 31.0 against 46.7) and,
-// by how little a nearly empty last round costs, between 2 and 2.75 of its rounds, where the other begins a second one (9000: 70.5
-// and 79.5; 12288: 85.1 and 81.1); 8192: 57.4 and 50.1, 16384: 113.8 and 92.1, 8 / 8 heads x 32768 520 and 452.  Without a
-// second tap (`taps` = 1) that middle range is not there (16384, 4 / 1 heads: 54.6 and 51.0).  The adjoint with more than two
-// query heads to a group keeps the small form longer: the other fetches all their rows for the key head's mean straight from
-// memory (7000, 6 / 2: 43.6 and 46.0, 12288, 4 / 1: 45.7 and 50.5).
+// One workgroup per CU either way.  A lone round of the 128-token form takes half of the other's time, a full one 0.55 of it, so it
+// wins while one round is enough and, by how little a nearly empty last round costs, between 2 and 2.75 of its rounds, where the
+// other begins a second one (8000, 8 / 2 heads: 63.7 and 82).  Full rounds of both are within 3 % of each other: us with 128 and 256
+// tokens, 3000, 8 / 8: 42.7 and 43.5; 6000, 8 / 8: 86.8 and 88.8 (adjoint 81.5 and 82.7); 8000, 8 / 8: 111 and 113 (108 and 105);
+// 16384, 8 / 2: 132 and 129 (119 and 119).  With many query heads to a group the small form also wins in its second round: the other
+// fetches all their rows for the key head's mean straight from memory (three taps together, 5000, 6 / 1: 39.5 and 57.3; 8000, 4 / 1: 40.3
+// and 51.3; 6000, 8 / 2: 48.5 and 55.5; one tap 36.3 and 43.5; the adjoint, where it did so before as well, 35.0, 36.0 and 46.2).
 inline bool stream_takes_256(long long rows, int heads, int R, int taps, bool adjoint) {
   const long long wgs = (rows + 127) / 128 * heads;
   if (wgs <= 256) return false;
-  if (wgs <= 512) return !(adjoint && R > 2 && (R > 3 || wgs <= 448));
+  if (wgs <= 512) return !(R > 3 || (adjoint && R > 2 && wgs <= 448));
   return wgs > 704 || (taps == 1 && !adjoint);
 }
 

@@ -386,7 +386,8 @@ def transforms(lat, w0, w1, temp, Hq, Hk, dh):
 # d_h = 256, both forms of the prologue and of its adjoint (128 and 256 tokens per workgroup) with 1, 2 and 3 taps: rows that are no
 # multiple of either block or of a wavefront's 32, several sequences in a block, one to four query heads per KV head
 STREAM_CASES = [(3, 45, 1, 1, 1, 1), (2, 131, 4, 1, 2, 2), (1, 1, 2, 2, 2, 1), (1, 257, 4, 2, 3, 1), (5, 421, 8, 8, 2, 2),
-                (1, 2100, 8, 8, 1, 1), (1, 2305, 8, 8, 1, 2), (7, 1801, 4, 1, 3, 1), (2, 7003, 6, 2, 1, 1), (3, 2999, 6, 2, 2, 1)]
+                (1, 2100, 8, 8, 1, 1), (1, 2305, 8, 8, 1, 2), (7, 1801, 4, 1, 3, 1), (2, 7003, 6, 2, 1, 1), (3, 2999, 6, 2, 2, 1),
+                (1, 130, 7, 1, 2, 2)]
 
 
 @pytest.mark.parametrize("B,T,Hq,Hk,k_seq,k_ch", STREAM_CASES)
