@@ -411,6 +411,14 @@ def test_prologue_forms(B, T, Hq, Hk, k_seq, k_ch, dh):
     check_prologue(B, T, Hq, Hk, k_seq, k_ch, dh)
 
 
+# chunks of 512, 1024 and 2048 tokens of the filter gradients: last ones that are short, sequences shorter than a chunk
+@pytest.mark.parametrize("B,T,Hq,Hk,k_seq,k_ch,dh", [(3, 2503, 8, 8, 2, 2, 128), (3, 2611, 8, 8, 2, 2, 128), (131, 61, 8, 8, 2, 1, 128),
+                                                     (1, 19601, 8, 8, 1, 2, 128), (7, 1499, 12, 12, 2, 2, 64)])
+def test_filter_gradient_chunks(B, T, Hq, Hk, k_seq, k_ch, dh):
+    say("filter gradient chunks", B, T, Hq, Hk, k_seq, k_ch, dh)
+    check_prologue(B, T, Hq, Hk, k_seq, k_ch, dh)
+
+
 def check_prologue(B, T, Hq, Hk, k_seq, k_ch, dh):
     """q, k, v and, through autograd, d_lat against the steps in fp64.  The filters are folded and rounded to bf16 (2^-9 of each
     weight), q and k rounded once, the gradient entering the convolutions once: the 1e-2 of the whole-block tests."""
