@@ -751,11 +751,12 @@ __device__ __forceinline__ void norm_and_rope_256(f32x16 (&acc)[8], const FusedA
       const float cb[4] = {t[2].x, t[2].z, t[3].x, t[3].z}, sb[4] = {t[2].y, t[2].w, t[3].y, t[3].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float cs = ca[e] * cb[e] - sa[e] * sb[e];
-        const float sn = sa[e] * cb[e] + ca[e] * sb[e];
+        // (which product is rounded is written out: left to the compiler it differed between groups)
+        const float cs = fmaf(ca[e], cb[e], -(sa[e] * sb[e]));
+        const float sn = fmaf(sa[e], cb[e], ca[e] * sb[e]);
         const float x1 = acc[nt][rg * 4 + e], x2 = acc[nt + NTL / 2][rg * 4 + e];
-        acc[nt][rg * 4 + e] = x1 * cs - x2 * sn;
-        acc[nt + NTL / 2][rg * 4 + e] = x2 * cs + x1 * sn;
+        acc[nt][rg * 4 + e] = fmaf(x1, cs, -(x2 * sn));
+        acc[nt + NTL / 2][rg * 4 + e] = fmaf(x1, sn, x2 * cs);
       }
       if (AHEAD && i + AHEAD < GROUPS) fetch(i + AHEAD);
     }
@@ -866,6 +867,15 @@ __device__ __forceinline__ void prologue_stream_body(
     acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk][nt], uf[kk], acc[nt], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // qk-mean weights as identity fragments (see prologue_fused_kernel)
+  auto identity_frag = [&](bf16_t wbits, int j) {
+    const bool on = ((l32 >> 4) == j) && (((l32 >> 3) & 1) == half);
+    u32x4 w = {0, 0, 0, 0};
+    const int e = l32 & 7;
+    if (on) w[e >> 1] = (uint32_t)wbits << ((e & 1) * 16);
+    return __builtin_bit_cast(bf16x8, w);
+  };
+  const bf16x8 id_half[2] = {identity_frag(f32_to_bf16(0.5f), 0), identity_frag(f32_to_bf16(0.5f), 1)};
   __builtin_amdgcn_s_waitcnt(wait_vm((ST_RING - 1) * SLAB_INSTR) & WAIT_LDS_TOO);  // the token rows and slab 0
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -879,6 +889,7 @@ __device__ __forceinline__ void prologue_stream_body(
       if (nt == 0) read(s_, 1, 0);
       read(s_, 1, nt + 1);
     }
+    const bf16x8 own = uf[0];
     // every wavefront holds its last fragments of slab s_, and slab s_ + 1 has landed when only the two behind it are outstanding
     __builtin_amdgcn_s_waitcnt(wait_vm((ST_RING - 2) * SLAB_INSTR) & WAIT_LDS_TOO);
     __builtin_amdgcn_s_barrier();
@@ -893,25 +904,17 @@ __device__ __forceinline__ void prologue_stream_body(
       }
       if (nt % 2 == 1) fetch(s_ + ST_RING, nt / 2);
     }
+    // own stream of the qk-mean: + 1/2 of the token's own row, whose fragments the last tap holds; channels 32 c .. lie in tile c
+    if (s_ >= NSLAB - QS && mean) {
+      const int c = s_ - (NSLAB - QS);
+      acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[0], own, acc[c], 0, 0, 0);
+      acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[1], uf[1], acc[c], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 
   if (mean) {
-    // qk-mean weights as identity fragments (see prologue_fused_kernel)
-    auto identity_frag = [&](bf16_t wbits, int j) {
-      const bool on = ((l32 >> 4) == j) && (((l32 >> 3) & 1) == half);
-      u32x4 w = {0, 0, 0, 0};
-      const int e = l32 & 7;
-      if (on) w[e >> 1] = (uint32_t)wbits << ((e & 1) * 16);
-      return __builtin_bit_cast(bf16x8, w);
-    };
-    // ---- own stream: + 1/2 of the token's own row; channels 32 c .. lie in tile c
-    const bf16x8 id_half[2] = {identity_frag(f32_to_bf16(0.5f), 0), identity_frag(f32_to_bf16(0.5f), 1)};
-    const int own = BWD ? l32 : l32 + D - 1;
-#pragma unroll
-    for (int c = 0; c < QS; ++c)
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(id_half[kk], row_frag(own, 2 * c + kk), acc[c], 0, 0, 0);
-    // ---- other stream: the sources' slabs, the wavefront's own rows of each
+    // ---- other stream of the qk-mean: the sources' slabs, the wavefront's own rows of each
     const float w_other = is_q ? a.mean_q_other : a.mean_k_other;
     const bf16_t w_other_hi = f32_to_bf16(w_other);
     const bf16_t w_other_lo = f32_to_bf16(w_other - bf16_to_f32(w_other_hi));

@@ -396,6 +396,30 @@ def test_wide_head_prologue(B, T, Hq, Hk, k_seq, k_ch):
     check_prologue(B, T, Hq, Hk, k_seq, k_ch, 256)
 
 
+# tokens of one sequence, and the channel from which a head's own half of the qk-mean joins behind its filter's last products: a slab of 32
+# input channels with 128 tokens a workgroup, one of 64 with 256
+@pytest.mark.parametrize("T,edge", [(130, 224), (16401, 192)])
+def test_own_half_of_the_wide_qk_mean_joins_behind_its_slab(T, edge):
+    """The order of the sums is part of the results, bit for bit.  Every output is 2^30 (first input channel) - 2^30 (last one) + 1/2
+    (own row) + 1/2 (the other stream); the first half is lost in fp32 where it is added before the last channel's product."""
+    say("order of the qk-mean", T)
+    cfg = P.CCAConfig(B=1, T=T, d_model=256, n_q_heads=1, n_kv_heads=1, head_dim=256, k_seq=1, k_ch=1, flags=P.CCA_CAUSAL | P.CCA_CONV_CH | P.CCA_QK_MEAN)
+    assert {rules.stream_takes_256(T, 2, 1, 1, adjoint) for adjoint in (False, True)} == {T > 130}
+    one = lambda *s: torch.ones(s, dtype=torch.bfloat16, device="cuda")
+    pattern = torch.full((256,), 0.5, device="cuda")
+    pattern[edge:] = 1.0
+    w1 = torch.zeros(2, 256, 256, 1, dtype=torch.bfloat16, device="cuda")  # (head, output, input, tap)
+    w1[:, :, 0], w1[:, :, 255] = 2.0 ** 30, -2.0 ** 30
+    w = P.CCAWeights(w_down=None, w_out=None, w_conv_ch=w1)
+    q, k, v, rnorm = one(1, T, 1, 256), one(1, T, 1, 256), one(1, T, 1, 256), torch.ones(1, T, 2, device="cuda")
+    P.cca_prologue(cfg, w, one(1, T, cfg.n_lat), q, k, v, rnorm=rnorm)
+    w = P.CCAWeights(w_down=None, w_out=None, w_conv_ch=w1.transpose(1, 2).contiguous())
+    d_lat, _ = P.cca_prologue_backward(cfg, w, one(1, T, cfg.n_lat), q, k, rnorm, one(*q.shape), one(*k.shape), one(*v.shape))
+    torch.cuda.synchronize()
+    for name, got in (("q", q), ("k", k), ("d_lat", d_lat[..., :512].reshape(1, T, 2, 256))):
+        assert torch.equal(got.float(), pattern.expand(got.shape)), name
+
+
 # d_h = 64 and 128, the short and the long form, forward and adjoint, with 1, 2 and 3 taps: sequences shorter than the taps reach, many
 # of them in a workgroup's 64 tokens, one token more and less than 64, one to five query heads per KV head (their mean's weight
 # exact in bf16 or not, more partner rows than are requested at a time)
