@@ -171,7 +171,9 @@ cca_status cca_forward(const cca_config *cfg, const cca_weights *w, const void *
  * the adjoint of the steps of Sec. 2.2, last step first).  Given d_out =
  * dLoss/d out (B,T,E) and the intermediates `saved` that cca_forward wrote for
  * the SAME cfg, weights and x (every member required except o_lo), computes
- *   d_x (B,T,E)            overwritten; may be NULL (then not computed)
+ *   d_x (B,T,E)            overwritten; may be NULL (then not computed); may lie over x,
+ *                          which is then overwritten last.  No other output may overlap
+ *                          an input
  *   grads->...             see cca_grads; `grads` itself may be NULL.
  * Attention probabilities are recomputed from saved->lse (nothing of size
  * T x T is stored); the convolution inputs are re-read from saved->lat.

@@ -203,15 +203,18 @@ static cca_status weight_grad(const Dims &d, const void *A, const void *Bm, void
   return e == hipSuccess ? CCA_OK : CCA_ERR_LAUNCH;
 }
 
-// The two adjoints of C (rows, n_out) = A (rows, n_in) W (n_in, n_out); d_A or d_W may be NULL (not wanted).
+// The two adjoints of C (rows, n_out) = A (rows, n_in) W (n_in, n_out); d_A or d_W may be NULL (not wanted).  d_A may lie over A: d_W is
+// then complete before it is written.
 static cca_status projection_bwd(const Dims &d, const void *d_C, const void *W, void *d_A, const void *A, void *d_W, int n_in, int n_out,
                                  void *scratch, hipStream_t s) {
-  if (d_A && d_W && d.bf16 && gemm_mfma_supported(d.rows(), n_in, n_out) && tn_mfma(d, n_in, n_out))
+  const size_t a_bytes = (size_t)d.rows() * n_in * d.esize();
+  const bool share = d_A && d_W && !overlap(d_A, a_bytes, A, a_bytes);
+  if (share && d.bf16 && gemm_mfma_supported(d.rows(), n_in, n_out) && tn_mfma(d, n_in, n_out))
     return gemm_adjoint_pair(d_C, W, d_A, A, d_W, d.rows(), n_in, n_out, static_cast<float *>(scratch), s) == hipSuccess
                ? CCA_OK
                : CCA_ERR_LAUNCH;
   const bool a_generic = !(d.bf16 && gemm_mfma_supported(d.rows(), n_in, n_out));  // (as project_t and weight_grad choose)
-  if (d_A && d_W && a_generic && !tn_mfma(d, n_in, n_out) && gemm_generic_pair_supported(d.rows(), n_in, n_out))
+  if (share && a_generic && !tn_mfma(d, n_in, n_out) && gemm_generic_pair_supported(d.rows(), n_in, n_out))
     return gemm_generic_pair(d.bf16, d_C, W, d_A, A, d_W, d.rows(), n_in, n_out, s) == hipSuccess ? CCA_OK : CCA_ERR_LAUNCH;
   cca_status st = CCA_OK;
   if (d_W) st = weight_grad(d, A, d_C, d_W, n_in, n_out, scratch, s);

@@ -721,7 +721,8 @@ static hipError_t prologue_bwd_generic_t(const Dims &d, const cca_weights &w, co
   const GradPlan p = grad_plan(d, want1, want0, want_temp);
   const long long units = (long long)p.n1 * p.s1 + (long long)p.n0 * p.s0 + p.nt;
   const long long n = d.rows() * d.n_lat, blocks = (n + GR_NT - 1) / GR_NT;
-  const bool share = generic_gradients_share(units + blocks);
+  const size_t w0_bytes = (size_t)(d.Hq + d.Hk) * d.dh * d.k_seq * sizeof(T);  // (read for d_lat)
+  const bool share = generic_gradients_share(units + blocks) && !(want0 && overlap(gr->w_conv_seq, w0_bytes, w.w_conv_seq, w0_bytes));
   if (!share || !units)
     pro_bwd_dlat_generic_kernel<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a, (const T *)w.w_conv_seq, d3, d1,
                                                                               (const T *)d_v, (T *)d_lat);

@@ -5,6 +5,7 @@
 
 #include <math.h>
 #include <stddef.h>
+#include <stdint.h>
 
 namespace cca {
 
@@ -154,6 +155,14 @@ inline TnTile tn_tile(int Mo, int No, long long K, double *us = nullptr) {
   if (us) *us = fmin(small, split_us);
   if (small >= split_us) return TN_SPLIT;
   return c64 == small ? TN_64x64 : c64x128 == small ? TN_64x128 : TN_128x128;
+}
+
+// ---- launches that share ------------------------------------------------------------------------------------------------
+// Whether two buffers have bytes in common.  Products that were a launch each ran in stream order, so that one's output could lie over
+// the other's input; where it does they still get a launch each.
+inline bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+  const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+  return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
 }
 
 // ---- the two adjoints of a projection, d_A (rows, n_in) = d_C (rows, n_out) W^T and d_W (n_in, n_out) = A^T d_C -----------------

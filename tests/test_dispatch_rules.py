@@ -192,6 +192,12 @@ def test_generic_cases_share_launches_and_do_not():
     assert products == {True, False} and gradients == {True, False}
 
 
+@pytest.mark.parametrize("a,b,shared", [(4096, 4096, True), (4096, 4096 + 16, True), (4096 + 16, 4096, True), (4096, 4096 + 64, False), (4096 + 64, 4096, False),
+                                        (4096, 4096 + 48, True), (4096 + 48, 4096, True), (0x7F0000000000, 4096, False)])
+def test_overlapping_buffers_are_found(a, b, shared):
+    assert rules.overlap(a, 64, b, 64) == shared
+
+
 # T, query and key heads and us of the prologue with 32 tokens a workgroup, with 8
 @pytest.mark.parametrize("T,heads,us32,us8", [(300, 6, 10.5, 8.7), (128, 10, 19.1, 15.8), (64, 32, 10.4, 8.9), (300, 10, 19.2, 21.3), (64, 40, 19.1, 21.9)])
 def test_generic_prologue_form_is_the_faster(T, heads, us32, us8):

@@ -124,6 +124,49 @@ def test_projection_adjoints_in_one_launch(rows, Hq, Hk, dh, E):
     check_product(g.w_down, x[0].double().t().contiguous() @ d_lat, rows)
 
 
+# d_x over x, and a row further in the same buffer: the weight's gradient still comes from the x that the call was given
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_input_gradient_may_lie_over_the_input(shift, dtype):
+    say("d_x over x", shift, dtype)
+    bf16 = dtype == "bf16"
+    rows, E = 300, 256
+    cfg = P.CCAConfig(B=1, T=rows, d_model=E, n_q_heads=2, n_kv_heads=1, head_dim=64, dtype=P.CCA_BF16 if bf16 else P.CCA_F32, flags=P.CCA_FLAGS_MHA)
+    r = lambda *s, seed, scale=1.0: rnd(*s, seed=seed, scale=scale, dtype=cfg.torch_dtype)
+    w = P.CCAWeights(w_down=r(E, cfg.n_lat, seed=2, scale=0.05), w_out=r(cfg.e_q, E, seed=4, scale=0.05))
+    x, d_out = r(1, rows, E, seed=1), r(1, rows, E, seed=5)
+    saved = P.CCASaved.allocate(cfg, "cuda")
+    P.cca_forward(cfg, w, x, saved=saved)
+    d_x, g = P.cca_backward(cfg, w, x, saved, d_out)
+    both = torch.empty(rows + 1, E, dtype=cfg.torch_dtype, device="cuda")
+    x2, d_x2 = both[None, :rows], both[None, shift:rows + shift]
+    x2.copy_(x)
+    _, g2 = P.cca_backward(cfg, w, x2, saved, d_out, d_x=d_x2)
+    torch.cuda.synchronize()
+    for name, a, b in (("d_x", d_x2, d_x), ("d_w_down", g2.w_down, g.w_down), ("d_w_out", g2.w_out, g.w_out)):
+        say(name)
+        check_product(a, b, rows) if bf16 else torch.testing.assert_close(a, b, rtol=0, atol=0)  # fp32: the same sums in the same order
+
+
+def test_sequence_filter_gradient_may_lie_over_the_filter():
+    """Alone it is written while nothing else reads the filter: d_lat, which does, is complete."""
+    say("d_w_conv_seq over w_conv_seq")
+    B, T, Hq, Hk, dh = 2, 150, 2, 1, 32
+    cfg = P.CCAConfig(B=B, T=T, d_model=64, n_q_heads=Hq, n_kv_heads=Hk, head_dim=dh, dtype=P.CCA_F32)
+    f = lambda *s, seed: rnd(*s, seed=seed, dtype=torch.float32)
+    w = P.CCAWeights(w_down=None, w_out=None, w_conv_seq=f(cfg.e_q + cfg.e_kv, 2, seed=1), w_conv_ch=f(Hq + Hk, dh, dh, 2, seed=2), temp=f(Hk, seed=3))
+    lat, rnorm = f(B, T, cfg.n_lat, seed=4), torch.empty(B, T, Hq + Hk, device="cuda")
+    q, k, v = P.cca_prologue(cfg, w, lat, rnorm=rnorm)
+    call = lambda w0, to: P.cca_prologue_backward(cfg, P.CCAWeights(None, None, w0, w.w_conv_ch, w.temp), lat, q, k, rnorm, f(*q.shape, seed=5), f(*k.shape, seed=6),
+                                                  f(*v.shape, seed=7), grads=P.CCAGrads(w_conv_seq=to))
+    over = w.w_conv_seq.clone()
+    d_lat, g = call(w.w_conv_seq, torch.empty_like(over))
+    d_lat2, _ = call(over, over)
+    torch.cuda.synchronize()
+    assert torch.equal(d_lat, d_lat2) and torch.equal(g.w_conv_seq, over)
+
+
+
 # B, T, Hq, Hk, d_h, causal, normalised: odd lengths, one tile more or less than a pair, rows whose second key group is
 # empty, several query blocks, paired and unpaired grids; scores bounded and not
 SPLIT_CASES = [(1, 300, 2, 1, 128, True, True), (1, 321, 3, 3, 64, True, False), (2, 385, 2, 2, 128, False, True),
