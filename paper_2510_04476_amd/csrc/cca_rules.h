@@ -20,14 +20,14 @@ enum NtTile { NT_256x256, NT_256x192, NT_64x64, NT_64x128, NT_128x128, NT_256x12
 //   128 x 128 (0.528, 3)  64 x 128 (0.354, 3)  64 x 64 (0.232, 2.2)
 // e.g. N = 1536, M = 16384: 384 tiles of 256 (2 rounds, half empty, 102 us) or 512 tiles of 256 x 192 (2 full rounds, 86); N = 2048,
 // K = 1024, M = 6000: 192 tiles of 256 x 256 (29.5) or 256 of 192 x 256 (24.7); N = 1536, K = 2048, M = 6000: 192 tiles of 256 x 192 (38.2)
-// or 256 of 192 x 192 (35.6).  192 x 192 beyond one round only up to K = 2048 (12000 x 1536 x 2048: 76.7 on 256 x 192, 66.3); it reads
-// the most for its products, and longer contractions keep to the wider shapes.
+// or 256 of 192 x 192 (35.6); M = 12000: 376 of 256 x 192 or 504 of 192 x 192, K = 2048 76.1 and 64.4, K = 4096 139.0 and 124.8, K = 8192
+// 264.3 and 230.5.
 inline NtTile nt_tile(long long M, int N, int K, double *us = nullptr) {
   const double slabs = (double)(K / 64);
   const bool halves = K % 128 == 0;  // the shapes that split a slab over two halves of the wavefronts
   const struct { NtTile t; int tm, tn; double per_slab, fixed; bool ok; } shapes[] = {
       {NT_256x192, 256, 192, 0.87, 6.0, true}, {NT_256x256, 256, 256, 1.06, 7.5, true}, {NT_192x256, 192, 256, 0.90, 6.1, true},
-      {NT_192x192, 192, 192, 0.715, 5.1, K <= 2048 || ((M + 191) / 192) * ((N + 191) / 192) <= 256}, {NT_256x128, 256, 128, 0.66, 4.9, true}, {NT_128x128, 128, 128, 0.528, 3.0, true}, {NT_64x128, 64, 128, 0.354, 3.0, halves},
+      {NT_192x192, 192, 192, 0.715, 5.1, true}, {NT_256x128, 256, 128, 0.66, 4.9, true}, {NT_128x128, 128, 128, 0.528, 3.0, true}, {NT_64x128, 64, 128, 0.354, 3.0, halves},
       {NT_64x64, 64, 64, 0.232, 2.2, halves}};
   NtTile best = NT_128x128;
   double least = 1e300;
