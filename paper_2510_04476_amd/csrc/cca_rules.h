@@ -14,7 +14,8 @@ enum NtTile { NT_256x256, NT_256x192, NT_64x64, NT_64x128, NT_128x128, NT_256x12
 
 // A tile shape costs (rounds of the grid over the chip) x (64-wide slabs x time per slab + fill and epilogue).  The two
 // numbers of each large shape (us) are fits (11 % rms) to back-to-back timings of every shape at K = 256 ... 4096,
-// N = 512 ... 6144, M = 1500 ... 16384; over these the choice costs 0.5 % on average against the best shape.  The small shapes' (128 x 128
+// N = 512 ... 6144, M = 1500 ... 16384; over these the choice costs 0.5 % on average against the best shape.  They rank the shapes of one
+// product: the chip's clock falls under a long one, which takes up to 1.3 times the estimate (16384 x 1536 x 2048: 67.7, measured 85).  The small shapes' (128 x 128
 // and below) are fits over M = 64 ... 16384.
 //   256 x 256 (1.06, 7.5)  192 x 256 (0.90, 6.1)  256 x 192 (0.87, 6.0)  192 x 192 (0.715, 5.1)  256 x 128 (0.66, 4.9)
 //   128 x 128 (0.528, 3)  64 x 128 (0.354, 3)  64 x 64 (0.232, 2.2)
@@ -167,43 +168,62 @@ inline bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes
 
 // ---- the two adjoints of a projection, d_A (rows, n_in) = d_C (rows, n_out) W^T and d_W (n_in, n_out) = A^T d_C -----------------
 // One launch on small tiles of both, one workgroup per CU, the product with the longer tiles first, or a launch each in its own best
-// form (4 us more).  The time of the one launch is that of dealing the two kinds of tiles to 256 CUs in that order, each tile at its time from
-// the fits above with all CUs at work.
+// form.  The time of the one launch is that of its busiest CU: workgroups go round the 8 XCDs, there round the 4 groups of 8 CUs, and in a
+// group to the CU that is free first.  Both sides are fits (3 % and 5 % rms) to the same sweep of whole adjoints, all nine pairs of tiles in
+// either order and two launches, 64 ... 8192 rows, 24 products of E = 1024 ... 2048 and 256 ... 6144 columns: a tile takes (slabs x time per
+// slab + fill and epilogue), us, NT 64 x 64 (0.185, 2.0), 64 x 128 (0.275, 2.7), 128 x 128 (0.45, 2.4), TN 0.23, 1.9, 0.32, 2.55 and 0.51, 2.6, the
+// slabs a tenth slower with all CUs at work, the launch 1.4; two launches the sum of what ranks their own tiles, which their
+// length at a falling clock makes 1.05 and 1.15 of it.  Over the sweep the choice costs 0.5 % on average, 9 % at most (E = 2048, 2048 columns, 1400
+// rows: 38.7 and 35.6); with the busiest CU of an even deal over all 256 and the single products' numbers 2.4 % and 38 %.  One launch
+// and two, us: 2100 x 1536 x 640 16.5 and 27.6, 4096 x 768 x 1536 30.3 and 44.7, 4096 x 1536 x 1280 42.5 and 46.8, 8000 x 1536 x 1536 105.9 and 82.4.
 struct PairForm {
   bool one_launch;
   NtTile nt;
   TnTile tn;
   bool nt_first;
 };
+// 8 CUs, n_long tiles and then n_short, each to the CU that is free first
+inline double dealt_to_8(int n_long, double t_long, int n_short, double t_short) {
+  const int more = n_long % 8, others = 8 - more;  // `more` CUs take one long tile more
+  const double low = (double)(n_long / 8) * t_long, high = low + t_long;
+  if (!more) return low + (double)((n_short + 7) / 8) * t_short;
+  const int beside = (int)(t_long / t_short);  // short tiles of another CU beside the last long one
+  if (n_short <= others * beside) return fmax(high, low + (double)((n_short + others - 1) / others) * t_short);
+  const int left = n_short - others * beside, rounds = left / 8, last = left % 8;
+  if (!last) return high + (double)rounds * t_short;
+  return last <= others ? low + (double)(beside + rounds + 1) * t_short : high + (double)(rounds + 1) * t_short;
+}
 inline double dealt(long long n_long, double t_long, long long n_short, double t_short) {
-  const long long full = n_long / 256, more = n_long % 256;  // `more` CUs take one long tile more
-  if (!more) return (double)full * t_long + (double)((n_short + 255) / 256) * t_short;
-  const long long fits = (256 - more) * (long long)(t_long / t_short);  // short tiles beside the last long ones
-  const double low = (double)full * t_long, high = low + t_long;
-  if (n_short > fits) return high + (double)((n_short - fits + 255) / 256) * t_short;
-  return fmax(high, low + (double)((n_short + 255 - more) / (256 - more)) * t_short);
+  const int l = (int)((n_long + 7) / 8), s = (int)((n_short + 7) / 8);  // of an XCD
+  double most = 0.0;
+  for (int g = 0; g < 4; ++g) {
+    const int lg = (l - g + 3) / 4;
+    most = fmax(most, dealt_to_8(lg, t_long, (l + s - g + 3) / 4 - lg, t_short));
+  }
+  return most;
 }
 inline PairForm gemm_pair(long long rows, int n_in, int n_out) {
   PairForm best{false, NT_256x256, TN_SPLIT, true};
   double nt_us, tn_us;
   nt_tile(rows, n_in, n_out, &nt_us);
   tn_tile(n_in, n_out, rows, &tn_us);
-  double least = nt_us + tn_us + 4.0;
+  double least = 1.05 * nt_us + 1.15 * tn_us - 0.5;
   const double s_nt = (double)(n_out / 64), s_tn = (double)((rows + 63) / 64);
   auto tiles = [](long long m, long long n, int tm, int tn) { return ((m + tm - 1) / tm) * ((n + tn - 1) / tn); };
   const bool halves = n_out % 128 == 0;
-  const struct { NtTile t; int tm, tn; double us; bool ok; } nts[3] = {{NT_64x64, 64, 64, s_nt * 0.232 + 2.2, halves},
-                                                                      {NT_64x128, 64, 128, s_nt * 0.354 + 3.0, halves},
-                                                                      {NT_128x128, 128, 128, s_nt * 0.528 + 3.0, true}};
-  const struct { TnTile t; int tm, tn; double us; } tns[3] = {{TN_64x64, 64, 64, s_tn * 0.209 + 3.7},
-                                                              {TN_64x128, 64, 128, s_tn * 0.359 + 3.6},
-                                                              {TN_128x128, 128, 128, s_tn * 0.56 + 4.1}};
+  const struct { NtTile t; int tm, tn; double slab, fixed; bool ok; } nts[3] = {
+      {NT_64x64, 64, 64, 0.185, 2.0, halves}, {NT_64x128, 64, 128, 0.275, 2.7, halves}, {NT_128x128, 128, 128, 0.45, 2.4, true}};
+  const struct { TnTile t; int tm, tn; double slab, fixed; } tns[3] = {
+      {TN_64x64, 64, 64, 0.23, 1.9}, {TN_64x128, 64, 128, 0.32, 2.55}, {TN_128x128, 128, 128, 0.51, 2.6}};
   for (const auto &a : nts)
     for (const auto &b : tns) {
       if (!a.ok) continue;
       const long long na = tiles(rows, n_in, a.tm, a.tn), nb = tiles(n_in, n_out, b.tm, b.tn);
-      const double us = a.us >= b.us ? dealt(na, a.us, nb, b.us) : dealt(nb, b.us, na, a.us);
-      if (us < least) least = us, best = PairForm{true, a.t, b.t, a.us >= b.us};
+      if ((na > nb ? na : nb) > 1 << 24) continue;  // (counted in ints; far from where one launch pays)
+      const double busy = na + nb < 256 ? (double)(na + nb) / 256.0 : 1.0, slower = 1.0 + 0.1 * busy * busy;
+      const double ta = s_nt * a.slab * slower + a.fixed, tb = s_tn * b.slab * slower + b.fixed;
+      const double us = 1.4 + (ta >= tb ? dealt(na, ta, nb, tb) : dealt(nb, tb, na, ta));
+      if (us < least) least = us, best = PairForm{true, a.t, b.t, ta >= tb};
     }
   return best;
 }

@@ -95,7 +95,8 @@ def test_weight_gradient_tiles(rows, Hq, dh, E):
 # rows x (query heads, KV heads, head width, E): the two adjoints of a projection in one launch, every pair of tile forms that the rule
 # chooses, more tiles than CUs, rows short of and past a tile's edge, and products large enough for a launch each
 PAIR_CASES = [(70, 4, 2, 64, 512), (70, 8, 2, 128, 2048), (130, 8, 2, 128, 2048), (400, 8, 2, 128, 2048),
-              (130, 4, 4, 128, 1024), (1000, 8, 2, 128, 2048), (511, 4, 4, 64, 1024), (1025, 8, 8, 64, 1024), (1999, 8, 2, 128, 2048), (300, 12, 12, 64, 1536), (4001, 8, 2, 128, 2048), (2050, 16, 16, 64, 1024)]
+              (130, 4, 4, 128, 1024), (1000, 8, 2, 128, 2048), (511, 4, 4, 64, 1024), (1025, 8, 8, 64, 1024), (1999, 8, 2, 128, 2048), (300, 12, 12, 64, 1536), (4001, 8, 2, 128, 2048), (2050, 16, 16, 64, 1024),
+              (901, 4, 1, 128, 1024), (1301, 2, 2, 64, 1024), (777, 3, 1, 128, 1536)]
 
 
 @pytest.mark.parametrize("rows,Hq,Hk,dh,E", PAIR_CASES)
