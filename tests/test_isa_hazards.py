@@ -93,10 +93,9 @@ def _min_operand_age(ins):
     """Smallest number of issue slots between a vector-ALU instruction that writes a register and an
     inline-assembly MFMA that reads it as an operand.  The compiler pads this distance for the MFMAs it selects
     itself, not for inline assembly.  Seen on the GPU: an MFMA issued one slot after the v_mov_b64 pair that
-    wrote its (zero) operand, and one issued directly behind the v_cvt_pk_bf16_f32 that packed its operand, gave
-    wrong or non-finite results now and then.  Copies out of the accumulation registers (v_accvgpr_read, the
-    compiler's spill reloads) one slot ahead are exempt: the forward kernel has them in its loop and its results
-    are bit-identical from run to run."""
+    wrote its (zero) operand, one issued directly behind the v_cvt_pk_bf16_f32 that packed its operand and, in the
+    forward kernel, one issued directly behind the v_accvgpr_read that copied its operand out of the accumulation
+    registers gave wrong or non-finite results now and then."""
     worst, where = None, None
     for i, (op, toks, in_asm, text) in enumerate(ins):
         if not (in_asm and op.startswith("v_mfma")):
@@ -104,13 +103,20 @@ def _min_operand_age(ins):
         src = set().union(*[_regs(x) for x in toks[1:]])
         dist = 0
         for op2, toks2, _, text2 in reversed(ins[max(0, i - 12):i]):
-            valu = op2.startswith("v_") and not op2.startswith("v_mfma") and not op2.startswith("v_accvgpr_read")
+            valu = op2.startswith("v_") and not op2.startswith("v_mfma")
             if valu and toks2 and _regs(toks2[0]) & src:
                 if worst is None or dist < worst:
                     worst, where = dist, (text2, text)
                 break
             dist += int(toks2[0]) + 1 if op2 == "s_nop" else 1
     return worst, where
+
+
+def _loops(lines):
+    """The instructions from each label to every branch back to it."""
+    label = {m.group(1): i for i, ln in enumerate(lines) if (m := re.match(r"(\.LBB\d+_\d+):", ln))}
+    back = ((label.get(m.group(1)), i) for i, ln in enumerate(lines) if (m := re.match(r"\s+s_(?:cbranch_\w+|branch) (\.LBB\d+_\d+)", ln)))
+    return [_parse(lines[start:i + 1]) for start, i in back if start is not None and start <= i]
 
 
 @pytest.mark.parametrize("source,kernel,count", [("cca_attention.hip", "attn_fwd_wide_kernel", 4),
@@ -126,32 +132,29 @@ def test_inline_mfma_results_are_not_read_too_early(source, kernel, count):
         ins = _parse(body.splitlines())
         n_inline = sum(1 for op, _, a, _ in ins if a and op.startswith("v_mfma"))
         assert n_inline > 0, name
-        loops = [i for i, ln in enumerate(body.splitlines()) if "Inner Loop Header" in ln]
         worst, where = _min_distance(ins)
         assert worst is not None and worst >= NEED, (name, worst, where)
         age, which = _min_operand_age(ins)  # operands written by the vector ALU: at least 4 slots old
         assert age is None or age >= 4, (name, age, which)
-        # the steady-state loop wraps around: scan it twice
-        lines = body.splitlines()
-        for start in loops[:1]:
-            end = next(i for i in range(start, len(lines)) if "s_cbranch_execnz" in lines[i])
-            loop = _parse(lines[start:end + 1])
+        # a loop wraps around: scan it twice
+        loops = [loop for loop in _loops(body.splitlines()) if any(a and op.startswith("v_mfma") for op, _, a, _ in loop)]
+        assert loops, name
+        for loop in loops:
             w2, wh2 = _min_distance(loop + loop)
             assert w2 is None or w2 >= NEED, (name, w2, wh2)
+            age2, which2 = _min_operand_age(loop + loop)
+            assert age2 is None or age2 >= 4, (name, age2, which2)
         checked += 1
     assert checked >= count
 
 
-def test_forward_copies_out_of_the_accumulation_registers_stand_apart():
-    """In the forward kernel operands that live in the accumulation registers are copied out at least four slots ahead as well: right
-    in front of the MFMA they gave wrong scores on the GPU."""
-    text = _isa("cca_attention.hip")
-    bodies = re.findall(r"^_ZN3cca\S*attn_fwd_wide_kernel\S*:.*?s_endpgm", text, flags=re.S | re.M)
-    assert len(bodies) >= 4
-    for body in bodies:
-        ins = [(op.replace("v_accvgpr_read", "v_mov"), *rest) for op, *rest in _parse(body.splitlines())]
-        age, which = _min_operand_age(ins)
-        assert age is not None and age >= 4, which
+def test_operand_age_sees_every_writer_and_the_back_edge():
+    """Each listing has an inline-assembly MFMA one slot behind a writer of its operand, the last one over the loop's back edge."""
+    mfma = [";;#ASMSTART", "v_mfma_f32_32x32x16_bf16 v[0:15], v[20:23], v[24:27], v[0:15]", ";;#ASMEND"]
+    for writer in ("v_accvgpr_read_b32 v21, a3", "v_mov_b64_e32 v[20:21], 0", "v_cvt_pk_bf16_f32 v26, v1, v2"):
+        assert _min_operand_age(_parse([writer, "s_nop 0", *mfma]))[0] == 1
+        loop = _parse([*mfma, writer])
+        assert _min_operand_age(loop)[0] is None and _min_operand_age(loop + loop)[0] == 0
 
 
 @pytest.mark.parametrize("kernel,count", [("attn_bwd_dq_wide_kernel", 2), ("attn_bwd_dkdv_wide_kernel", 4)])
