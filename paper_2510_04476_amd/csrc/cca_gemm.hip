@@ -909,9 +909,7 @@ bool gemm_tn_mfma_supported(int Mo, int No, long long K) {
   return Mo % 8 == 0 && No % 8 == 0 && Mo >= 8 && No >= 8 && Mo < 1 << 23 && No < 1 << 23 && K >= 1;
 }
 
-size_t gemm_tn_scratch_bytes(int Mo, int No, long long K) {
-  return (size_t)tn_splits(Mo, No, K) * ((Mo + 31) / 32) * ((No + 31) / 32) * 1024 * sizeof(float);
-}
+size_t gemm_tn_scratch_bytes(int Mo, int No, long long K) { return (size_t)tn_part_blocks(Mo, No, K) * 1024 * sizeof(float); }
 
 hipError_t gemm_tn_mfma_bf16(const void *A, long long lda, const void *Bm, long long ldb, void *C, int Mo, int No,
                              long long K, float *part, hipStream_t s) {

@@ -158,6 +158,12 @@ inline TnTile tn_tile(int Mo, int No, long long K, double *us = nullptr) {
   return c64 == small ? TN_64x64 : c64x128 == small ? TN_64x128 : TN_128x128;
 }
 
+// 32 x 32 blocks of fp32 partial sums that the product leaves: none where one workgroup walks all of K or one split stores its result
+inline long long tn_part_blocks(int Mo, int No, long long K) {
+  const int splits = tn_splits(Mo, No, K);
+  return tn_tile(Mo, No, K) == TN_SPLIT && splits > 1 ? (long long)splits * ((Mo + 31) / 32) * ((No + 31) / 32) : 0;
+}
+
 // ---- launches that share ------------------------------------------------------------------------------------------------
 // Whether two buffers have bytes in common.  Products that were a launch each ran in stream order, so that one's output could lie over
 // the other's input; where it does they still get a launch each.

@@ -16,6 +16,7 @@ extern "C" {
 int r_nt_tile(long long M, int N, int K) { return nt_tile(M, N, K); }
 int r_tn_tile(int Mo, int No, long long K) { return tn_tile(Mo, No, K); }
 int r_tn_splits(int Mo, int No, long long K) { return tn_splits(Mo, No, K); }
+int r_tn_part_blocks(int Mo, int No, long long K) { return (int)tn_part_blocks(Mo, No, K); }
 int r_prologue_is_short(long long rows, int heads, int R, int dh, int adjoint) { return prologue_is_short(rows, heads, R, dh, adjoint); }
 int r_tile_panel(int tiles_m, int tiles_n, int tm, int tn, long long K) { return tile_panel(tiles_m, tiles_n, tm, tn, K); }
 int r_panel_touches(int tiles_m, int tiles_n, int tm, int tn, int w) { return TilePanel(tiles_m, tiles_n, tm, tn).touched(w); }
@@ -69,7 +70,7 @@ def _lib():
                         os.path.join(ROOT, "paper_2510_04476_amd", "csrc"), src, "-o", so], check=True)
         lib = C.CDLL(so)
     L, I = C.c_longlong, C.c_int
-    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_decode_up_lds=[L, I], r_decode_up_lds_limit=[], r_tile_panel=[I, I, I, I, L], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
+    for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_tn_part_blocks=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_decode_up_lds=[L, I], r_decode_up_lds_limit=[], r_tile_panel=[I, I, I, I, L], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
                            r_overlap=[C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t], r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
                            r_generic_attention_bwd_16=[L, I, I, I, I, I], r_generic_prologue_takes_8=[L, I, I], r_generic_products_share=[L], r_generic_gradients_share=[L], r_generic_product_looks_ahead=[L, L], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
@@ -85,6 +86,10 @@ def nt_tile(M, N, K):
 
 def tn_tile(Mo, No, K):
     return TN_TILES[_lib().r_tn_tile(Mo, No, K)]
+
+
+def tn_part_blocks(Mo, No, K):
+    return _lib().r_tn_part_blocks(Mo, No, K)
 
 
 def tn_splits(Mo, No, K):

@@ -2,6 +2,7 @@
 choose, and at sizes where every form was timed the chosen one is not the slower."""
 import pytest
 
+import paper_2510_04476_amd as P
 import rules
 import test_gpu_small_shapes as small
 
@@ -85,6 +86,19 @@ def test_weight_gradient_cases_reach_every_tile():
     assert set(forms.values()) == set(rules.TN_TILES)
     splits = {rules.tn_splits(Hq * dh, E, r) for (r, Hq, dh, E), f in forms.items() if f == "split"}
     assert len(splits) >= 3 and max(splits) > 16  # few and many parts to add
+
+
+@pytest.mark.parametrize("Mo,No,K,parts", [(1536, 2048, 16384, True), (1024, 2048, 7996, True), (2048, 6144, 4096, False), (1536, 2048, 1024, False)])
+def test_weight_gradients_reserve_the_parts_that_they_write(Mo, No, K, parts):
+    """Sums of several splits; none where one split stores the result, or on small tiles.  The backward's workspace holds them."""
+    blocks = rules.tn_part_blocks(Mo, No, K)
+    assert blocks == (rules.tn_splits(Mo, No, K) * -(-Mo // 32) * -(-No // 32) if parts else 0)
+    cfg = lambda B: P.CCAConfig(B=B, T=K, d_model=No, n_q_heads=Mo // 64, n_kv_heads=1, head_dim=64, flags=P.CCA_FLAGS_MHA)
+    c = cfg(1)
+    taken = max(blocks, rules.tn_part_blocks(No, c.n_lat, K)) * 4096
+    # without the parts, every region grows with the rows alone (each rounded up to 256 bytes)
+    two = [P.cca_backward_workspace_size(cfg(B)) - max(rules.tn_part_blocks(Mo, No, B * K), rules.tn_part_blocks(No, c.n_lat, B * K)) * 4096 for B in (1, 2)]
+    assert P.cca_backward_workspace_size(c) >= taken and abs(two[1] - 2 * two[0]) <= 16 * 256
 
 
 def test_projection_adjoint_cases_reach_every_form():
