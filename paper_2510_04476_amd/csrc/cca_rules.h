@@ -312,6 +312,28 @@ inline bool prologue_is_short(long long rows, int heads, int R, int dh, bool adj
   return blocks <= (adjoint ? 240 : R > 1 ? 512 : 256);
 }
 
+// ---- filter gradients of the prologue's adjoint -------------------------------------------------------------------------------
+// Tokens per chunk of the filter-gradient kernel: the largest of 512..64 (or more, below) that still gives 80 workgroups.  They run beside the
+// adjoint's (at d_h = 256 in a launch of their own), and every chunk's sums (196 KB a head at d_h = 128) are written and read once more: with 256 workgroups and a unit's
+// last few chunks added one after the other the backward pass took (us, then now) 2 x 512 tokens, 8 query and 2 KV heads of 128:
+// 105.7, 99.5; 2 x 2048: 266.0, 251.6; 1 x 2048, 6 + 6 heads: 179.7, 165.3; 1 x 4096, 4 + 1 heads of 256: 638, 631; 40 workgroups:
+// 98.1, 256.6, 165.7, 628.  The prologue's adjoint alone at d_h = 256 (heads, tokens; before this chunk and other changes of its adjoint, and
+// after): 4 + 1, 1024: 70.5, 59.7; 2048: 76.2, 67.0; 6000: 101.0, 85.7; 16384: 197.7, 195.7; 8 + 8, 2048: 110.2, 106.0; 9000: 357.5, 360.3; 2 + 2,
+// 3000: 75.8, 63.6.
+// Beside an adjoint of several rounds a chain of 1024 or 2048 tokens still ends in time, and half or a quarter of the sums are written
+// and read (both launches, us, 512, 1024 and 2048 tokens; heads of 128, then of 64): 11500 tokens, 8 + 2: 63.0, 62.5; 13200: 78.9, 70.0, 71.2;
+// 16384: 86.2, 75.5, 90.0; 32768: 152.0, 138.3, 130.3; 49152: 219.1, 190.2, 176.6; 9000, 8 + 8: 83.6, 71.1, 87.9; 16384, 8 + 8: 143.7,
+// 124.4, 134.5; 16 x 1000, 8 + 2: 88.9, 79.0; but 10000, 8 + 2: 54.8, 58.6; 4 x 6000, 16 + 4: 99.4, 89.7, 99.6; 2 x 16384, 16 + 4:
+// 129.5, 124.6, 120.9; 10000, 16 + 4: 47.2, 50.7.
+// `slices`: workgroups that share a head's output channels.
+inline int filter_gradient_chunk(long long B, int T, int heads, int slices, int dh) {
+  const long long channels = B * T * heads * dh;
+  const int longest = dh == 256 || channels < 16000000 ? 512 : channels < 40000000 ? 1024 : 2048;
+  for (int c = longest; c > 64; c >>= 1)
+    if (B * ((T + c - 1) / c) * heads * slices >= 80) return c;
+  return 64;
+}
+
 // ---- prologue at d_h = 256: one head x 128 tokens per workgroup (one wavefront per SIMD) or 256 (two) -------------------
 // One workgroup per CU either way.  A lone round of the 128-token form takes half of the other's time, a full one 0.55 of it, so it
 // wins while one round is enough and, by how little a nearly empty last round costs, between 2 and 2.75 of its rounds, where the

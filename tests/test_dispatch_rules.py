@@ -82,10 +82,13 @@ def test_order_of_tiles_is_chosen_in_no_time(tiles_m, tiles_n, tm, tn):
 
 
 def test_weight_gradient_cases_reach_every_tile():
-    forms = {(r, Hq, dh, E): rules.tn_tile(Hq * dh, E, r) for r, Hq, dh, E in small.WGRAD_CASES}
-    assert set(forms.values()) == set(rules.TN_TILES)
-    splits = {rules.tn_splits(Hq * dh, E, r) for (r, Hq, dh, E), f in forms.items() if f == "split"}
-    assert len(splits) >= 3 and max(splits) > 16  # few and many parts to add
+    alone = [(E, 3 * Hq * dh, r) for r, Hq, dh, E in small.WGRAD_CASES]  # d W_down: no d_x is wanted
+    # d W_out, where d_o is not on the matrix cores (widths that 64 does not divide) or the rule gives both a launch each
+    alone += [(Hq * dh, E, r) for r, Hq, dh, E in small.WGRAD_CASES if E % 64 or not rules.gemm_pair(r, Hq * dh, E)]
+    assert {rules.tn_tile(*a) for a in alone} == set(rules.TN_TILES)
+    splits = {a: rules.tn_splits(*a) for a in alone if rules.tn_tile(*a) == "split"}
+    assert len(set(splits.values())) >= 3 and max(splits.values()) > 16  # few and many parts to add
+    assert {1, 2, 3} < {-(-a[2] // 64) for a, n in splits.items() if n == 1}  # stored directly: slabs fewer than the kernel's stages, and more
 
 
 @pytest.mark.parametrize("Mo,No,K,parts", [(1536, 2048, 16384, True), (1024, 2048, 7996, True), (2048, 6144, 4096, False), (1536, 2048, 1024, False)])
@@ -241,6 +244,22 @@ def test_overlapping_buffers_are_found(a, b, shared):
     assert rules.overlap(a, 64, b, 64) == shared
 
 
+def test_filter_gradient_cases_reach_every_long_chunk():
+    chunk = lambda B, T, Hq, Hk, k_seq, k_ch, dh: rules.filter_gradient_chunk(B, T, Hq + Hk, 1, dh)
+    got = [(chunk(*c), c[1]) for c in small.FILTER_GRADIENT_CASES]
+    assert {c for c, T in got} == {512, 1024, 2048}
+    assert {c for c, T in got if T % c} == {512, 1024, 2048} and any(T < c for c, T in got)  # short last chunks, sequences shorter than one
+
+
+# sequences, T, heads, d_h and us of the prologue's adjoint with chunks of 512, 1024 and (where timed) 2048 tokens
+@pytest.mark.parametrize("B,T,heads,dh,us", [(1, 10000, 10, 128, (54.8, 58.6)), (1, 13200, 10, 128, (78.9, 70.0, 71.2)), (1, 16384, 10, 128, (86.2, 75.5, 90.0)),
+                                             (1, 32768, 10, 128, (152.0, 138.3, 130.3)), (1, 49152, 10, 128, (219.1, 190.2, 176.6)), (1, 9000, 16, 128, (83.6, 71.1, 87.9)),
+                                             (1, 16384, 16, 128, (143.7, 124.4, 134.5)), (16, 1000, 10, 128, (88.9, 79.0)), (1, 10000, 20, 64, (47.2, 50.7)),
+                                             (4, 6000, 20, 64, (99.4, 89.7, 99.6)), (2, 16384, 20, 64, (129.5, 124.6, 120.9))])
+def test_filter_gradient_chunk_is_the_fastest(B, T, heads, dh, us):
+    assert us[(512, 1024, 2048).index(rules.filter_gradient_chunk(B, T, heads, 1, dh))] == min(us)
+
+
 # T, query and key heads and us of the prologue with 32 tokens a workgroup, with 8
 @pytest.mark.parametrize("T,heads,us32,us8", [(300, 6, 10.5, 8.7), (128, 10, 19.1, 15.8), (64, 32, 10.4, 8.9), (300, 10, 19.2, 21.3), (64, 40, 19.1, 21.9)])
 def test_generic_prologue_form_is_the_faster(T, heads, us32, us8):
@@ -309,9 +328,10 @@ def test_projection_tile_is_the_fastest(M, N, K, us):
 
 
 # Mo, No, tokens and us of the small tiles (in the order of rules.TN_TILES[1:]) and of the best split
-TN_MEASURED = [(2048, 2048, 8000, (168.5, 124.8, 91.7), 83.5), (2048, 2048, 4000, (79.7, 65.7, 46.9), 53.0),
-               (2048, 1536, 8000, (107.3, 120.1, 83.4), 66.7), (1024, 2048, 8000, (80.6, 65.9, 81.3), 51.8), (2048, 6144, 4000, (228.6, 234.3, 145.4), 127.8),
-               (1024, 2048, 1024, (11.4, 11.3, 13.8), 31.3)]
+TN_MEASURED = [(2048, 2048, 8000, (116.7, 105.6, 82.3), 69.8), (2048, 2048, 4000, (58.6, 55.1, 42.5), 46.7), (2048, 1536, 8000, (89.9, 98.4, 72.8), 57.9),
+               (1024, 2048, 8000, (57.3, 52.7, 70.3), 45.1), (2048, 6144, 4000, (173.2, 165.6, 122.2), 90.8), (1024, 2048, 1024, (11.0, 10.2, 12.4), 23.7),
+               (1536, 1280, 4096, (30.2, 27.6, 37.7), 32.2), (768, 1536, 4096, (29.3, 26.3, 37.0), 27.2), (1536, 640, 2100, (12.0, 15.6, 21.4), 23.2),
+               (384, 1536, 2100, (11.7, 15.4, 21.8), 20.1), (2048, 1536, 1024, (15.5, 17.9, 13.0), 24.0), (2048, 1536, 16384, (210.1, 213.2, 149.9), 97.6)]
 
 
 @pytest.mark.parametrize("Mo,No,K,small_us,split_us", TN_MEASURED)

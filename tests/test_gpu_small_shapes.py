@@ -69,14 +69,16 @@ def test_projection_of_few_slabs_on_large_tiles(M, tile, E, slabs):
     check_product(out[0], o[0].double() @ w_out.double(), cfg.e_q)
 
 
-# token rows x (query heads, head width, E): d W_out (e_q, E) = o^T d_out on every tile shape of the weight-gradient GEMM
-# (64 x 64, 64 x 128, 128 x 128, split 256 x 256), with no, one and a few tokens in the last slab of 64; the last three split, on
-# a number of tiles that 8 does not divide and on widths that are no multiple of the 32 x 32 blocks of the partial sums
+# token rows x (query heads, head width, E): d W_out (e_q, E) = o^T d_out, beside d_o or alone as the rules have it, and d W_down (E, 3 e_q) =
+# x^T d_lat, alone, on every tile shape of the weight-gradient GEMM (64 x 64, 64 x 128, 128 x 128, split 256 x 256), with no, one and a few
+# tokens in the last slab of 64; some split on a number of tiles that 8 does not divide and on widths that are no multiple of
+# the 32 x 32 blocks of the partial sums
 WGRAD_CASES = [(1, 1, 64, 64), (63, 3, 64, 256), (1000, 8, 64, 1024), (64, 8, 128, 2048), (129, 8, 128, 2048),
                (1023, 8, 128, 2048), (512, 12, 128, 2048), (2001, 12, 128, 2048), (9001, 8, 128, 2048),
                (9001, 12, 128, 1536), (8003, 25, 40, 1160), (7001, 3, 72, 1032),
                # one split (stored directly), of one, two, three and many slabs
-               (60, 32, 128, 4096), (100, 32, 128, 4096), (190, 49, 80, 4000), (1111, 49, 80, 4000)]
+               (60, 32, 128, 4096), (100, 32, 128, 4096), (190, 49, 80, 4000), (1111, 49, 80, 4000),
+               (60, 8, 128, 2048), (100, 8, 128, 2048), (513, 8, 128, 1024)]
 
 
 @pytest.mark.parametrize("rows,Hq,dh,E", WGRAD_CASES)
@@ -90,6 +92,16 @@ def test_weight_gradient_tiles(rows, Hq, dh, E):
     _, g = P.cca_backward(cfg, w, x, saved, d_out, grads=P.CCAGrads(w_out=torch.full_like(w.w_out, float("nan"))))
     torch.cuda.synchronize()
     check_product(g.w_out, saved.o[0].double().t().contiguous() @ d_out[0].double(), rows)
+    # d_lat stays inside and does not depend on x: with rows of the identity for x, d W_down is d_lat, E rows at a time (sums of one term)
+    down = lambda x_: P.cca_backward(cfg, w, x_, saved, d_out, grads=P.CCAGrads(w_down=torch.full_like(w.w_down, float("nan"))), want_d_x=False)[1].w_down
+    got, d_lat = down(x), []
+    for r0 in range(0, rows, E):
+        n = min(E, rows - r0)
+        one = torch.zeros_like(x)
+        one[0, torch.arange(r0, r0 + n), torch.arange(n)] = 1.0
+        d_lat.append(down(one)[:n])
+    torch.cuda.synchronize()
+    check_product(got, x[0].double().t().contiguous() @ torch.cat(d_lat).double(), rows)
 
 
 # rows x (query heads, KV heads, head width, E): the two adjoints of a projection in one launch, every pair of tile forms that the rule
@@ -480,8 +492,11 @@ def test_prologue_forms(B, T, Hq, Hk, k_seq, k_ch, dh):
 
 
 # chunks of 512, 1024 and 2048 tokens of the filter gradients: last ones that are short, sequences shorter than a chunk
-@pytest.mark.parametrize("B,T,Hq,Hk,k_seq,k_ch,dh", [(3, 2503, 8, 8, 2, 2, 128), (3, 2611, 8, 8, 2, 2, 128), (131, 61, 8, 8, 2, 1, 128),
-                                                     (1, 19601, 8, 8, 1, 2, 128), (7, 1499, 12, 12, 2, 2, 64)])
+FILTER_GRADIENT_CASES = [(3, 2503, 8, 8, 2, 2, 128), (3, 2611, 8, 8, 2, 2, 128), (131, 61, 8, 8, 2, 1, 128), (1, 19601, 8, 8, 1, 2, 128),
+                         (7, 1499, 12, 12, 2, 2, 64)]
+
+
+@pytest.mark.parametrize("B,T,Hq,Hk,k_seq,k_ch,dh", FILTER_GRADIENT_CASES)
 def test_filter_gradient_chunks(B, T, Hq, Hk, k_seq, k_ch, dh):
     say("filter gradient chunks", B, T, Hq, Hk, k_seq, k_ch, dh)
     check_prologue(B, T, Hq, Hk, k_seq, k_ch, dh)
