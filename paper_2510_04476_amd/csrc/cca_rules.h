@@ -179,9 +179,11 @@ inline bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes
 // either order and two launches, 64 ... 8192 rows, 24 products of E = 1024 ... 2048 and 256 ... 6144 columns: a tile takes (slabs x time per
 // slab + fill and epilogue), us, NT 64 x 64 (0.185, 2.0), 64 x 128 (0.275, 2.7), 128 x 128 (0.45, 2.4), TN 0.23, 1.9, 0.32, 2.55 and 0.51, 2.6, the
 // slabs a tenth slower with all CUs at work, the launch 1.4; two launches the sum of what ranks their own tiles, which their
-// length at a falling clock makes 1.05 and 1.15 of it.  Over the sweep the choice costs 0.5 % on average, 9 % at most (E = 2048, 2048 columns, 1400
-// rows: 38.7 and 35.6); with the busiest CU of an even deal over all 256 and the single products' numbers 2.4 % and 38 %.  One launch
-// and two, us: 2100 x 1536 x 640 16.5 and 27.6, 4096 x 768 x 1536 30.3 and 44.7, 4096 x 1536 x 1280 42.5 and 46.8, 8000 x 1536 x 1536 105.9 and 82.4.
+// length at a falling clock makes 1.05 and 1.15 of it.  Beyond 55 us the one launch is held to a tenth more: from there on it takes 3 ... 8 %
+// more than its estimate (8192 x 1024 x 2048: 75.6, measured 82.1, two launches 78.4), where the large tiles of two launches gain.  Over the
+// sweep the choice costs 0.5 % on average, 9 % at most (E = 2048, 2048 columns, 1400 rows: 38.7 and 35.6); with the busiest CU of an even
+// deal over all 256 and the single products' numbers 2.4 % and 38 %.  One launch and two, us: 2100 x 1536 x 640 16.5 and 27.6, 4096 x 768 x
+// 1536 30.3 and 44.7, 4096 x 1536 x 1280 42.5 and 46.8, 8000 x 1536 x 1536 105.9 and 82.4.
 struct PairForm {
   bool one_launch;
   NtTile nt;
@@ -213,7 +215,7 @@ inline PairForm gemm_pair(long long rows, int n_in, int n_out) {
   double nt_us, tn_us;
   nt_tile(rows, n_in, n_out, &nt_us);
   tn_tile(n_in, n_out, rows, &tn_us);
-  double least = 1.05 * nt_us + 1.15 * tn_us - 0.5;
+  double least = 1.05 * nt_us + 1.15 * tn_us;
   const double s_nt = (double)(n_out / 64), s_tn = (double)((rows + 63) / 64);
   auto tiles = [](long long m, long long n, int tm, int tn) { return ((m + tm - 1) / tm) * ((n + tn - 1) / tn); };
   const bool halves = n_out % 128 == 0;
@@ -228,7 +230,8 @@ inline PairForm gemm_pair(long long rows, int n_in, int n_out) {
       if ((na > nb ? na : nb) > 1 << 24) continue;  // (counted in ints; far from where one launch pays)
       const double busy = na + nb < 256 ? (double)(na + nb) / 256.0 : 1.0, slower = 1.0 + 0.1 * busy * busy;
       const double ta = s_nt * a.slab * slower + a.fixed, tb = s_tn * b.slab * slower + b.fixed;
-      const double us = 1.4 + (ta >= tb ? dealt(na, ta, nb, tb) : dealt(nb, tb, na, ta));
+      double us = 1.4 + (ta >= tb ? dealt(na, ta, nb, tb) : dealt(nb, tb, na, ta));
+      if (us > 55.0) us *= 1.1;
       if (us < least) least = us, best = PairForm{true, a.t, b.t, ta >= tb};
     }
   return best;
