@@ -180,7 +180,8 @@ inline bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes
 // slab + fill and epilogue), us, NT 64 x 64 (0.185, 2.0), 64 x 128 (0.275, 2.7), 128 x 128 (0.45, 2.4), TN 0.23, 1.9, 0.32, 2.55 and 0.51, 2.6, the
 // slabs a tenth slower with all CUs at work, the launch 1.4; two launches the sum of what ranks their own tiles, which their
 // length at a falling clock makes 1.05 and 1.15 of it.  Beyond 55 us the one launch is held to a tenth more: from there on it takes 3 ... 8 %
-// more than its estimate (8192 x 1024 x 2048: 75.6, measured 82.1, two launches 78.4), where the large tiles of two launches gain.  Over the
+// more than its estimate (8192 x 1024 x 2048: 75.6, measured 82.1, two launches 78.4), where the large tiles of two launches gain.  Above 10000
+// rows a tile's walk along all of them takes longer than two launches (10974 x 512 x 1024: 46.3 and 43.7; 11810: 49.1 and 44.8).  Over the
 // sweep the choice costs 0.5 % on average, 9 % at most (E = 2048, 2048 columns, 1400 rows: 38.7 and 35.6); with the busiest CU of an even
 // deal over all 256 and the single products' numbers 2.4 % and 38 %.  One launch and two, us: 2100 x 1536 x 640 16.5 and 27.6, 4096 x 768 x
 // 1536 30.3 and 44.7, 4096 x 1536 x 1280 42.5 and 46.8, 8000 x 1536 x 1536 105.9 and 82.4.
@@ -215,6 +216,7 @@ inline PairForm gemm_pair(long long rows, int n_in, int n_out) {
   double nt_us, tn_us;
   nt_tile(rows, n_in, n_out, &nt_us);
   tn_tile(n_in, n_out, rows, &tn_us);
+  if (rows > 10000) return best;
   double least = 1.05 * nt_us + 1.15 * tn_us;
   const double s_nt = (double)(n_out / 64), s_tn = (double)((rows + 63) / 64);
   auto tiles = [](long long m, long long n, int tm, int tn) { return ((m + tm - 1) / tm) * ((n + tn - 1) / tn); };
