@@ -28,6 +28,7 @@ namespace {
 
 constexpr int BM = 256, BK = 64;
 constexpr int A_STAGES = 3, B_STAGES = 2;  // slabs of each operand in the LDS of the 256-row product
+constexpr int PAUSE = 24;  // of 64 clocks each: 0.7 us (start_pauses)
 
 // LDS position of the 16-byte chunk c (0..7) of row r in a [rows][64] bf16 tile
 __device__ __forceinline__ int swz(int r, int c) { return r * 8 + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
@@ -70,9 +71,10 @@ __device__ __forceinline__ void add_wave_parts(f32x16 (&acc)[NI][MI], unsigned c
 }
 
 // Tile (row tm, column tn) of workgroup wg; false: none.  Workgroups are dealt round-robin over the 8 XCDs, each with an L2 of its own, so
-// every XCD gets a contiguous range of tiles; the order runs down panels of `panel` columns of tiles (tile_panel).
+// every XCD gets a contiguous range of tiles; the order runs down panels of `panel` columns of tiles (tile_panel).  `pauses`: slabs behind
+// which a workgroup of the large products pauses (start_pauses).
 struct TileGrid {
-  int tiles_n, tiles, panel;
+  int tiles_n, tiles, panel, pauses;
 };
 __device__ __forceinline__ bool tile_of(const TileGrid &g, int wg, int &tm, int &tn) {
   const int tile = (wg % 8) * ((g.tiles + 7) / 8) + wg / 8;
@@ -84,7 +86,8 @@ __device__ __forceinline__ bool tile_of(const TileGrid &g, int wg, int &tm, int 
 }
 TileGrid tile_grid(long long M, int N, long long K, int tm, int tn) {
   const int tiles_m = (int)((M + tm - 1) / tm), tiles_n = (N + tn - 1) / tn;
-  return TileGrid{tiles_n, tiles_m * tiles_n, tile_panel(tiles_m, tiles_n, tm, tn, K)};
+  const int tiles = tiles_m * tiles_n;
+  return TileGrid{tiles_n, tiles, tile_panel(tiles_m, tiles_n, tm, tn, K), start_pauses(tm * tn, tiles, K / BK)};
 }
 
 // Products of F x F blocks (F = 32 or 16): acc[ni][mi][r] = C[m][n] with m = (wm*MI + mi)*F + lane%F and n = (wn*NI + ni)*F + 8*(r/4) +
@@ -142,6 +145,8 @@ __device__ __forceinline__ void store_tile_bf16(const Acc (&acc)[NI][MI], unsign
 // x 1024 37.1 -> 30.6, 6000 x 1536 x 2048 45.5 -> 35.6, 8192 x 8192 x 8192 955 -> 732.
 // What bounds it: the power the matrix cores draw (8192^3 on all-zero operands: 607 us).  16x16x32 instructions draw less than
 // 32x32x16 ones on the same fragments: 8192^3 877 -> 796 us on random operands, 601 -> 607 on zeros.
+// A large grid's workgroups pause between their first slabs (start_pauses): what all CUs draw at once would cost the kernels around it
+// their clock.
 // Not faster: s_setprio around the MFMAs, any other order of them, the barrier four MFMAs earlier, A's loads closer
 // together or further apart, 4 wavefronts of 128 x 128 (half the fragment reads).  Rows and columns of the tile: what deals the tiles most
 // evenly to 256 CUs (nt_tile).
@@ -270,6 +275,10 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_bf16_nt_kernel(con
     as = as1;
   };
   int kt = 0;
+  for (; kt < grid.pauses && kt + 2 < nk; ++kt) {
+    slab(kt, std::true_type{}, std::true_type{});
+    __builtin_amdgcn_s_sleep(PAUSE);
+  }
   for (; kt + 2 < nk; ++kt) slab(kt, std::true_type{}, std::true_type{});
   if (kt + 1 < nk) slab(kt++, std::false_type{}, std::true_type{});
   slab(kt, std::false_type{}, std::false_type{});

@@ -52,6 +52,7 @@ int r_gemm_pair(long long rows, int n_in, int n_out) {
   return f.one_launch ? 1 + f.nt_first + 2 * f.nt + 32 * f.tn : 0;
 }
 int r_filter_gradient_chunk(long long B, int T, int heads, int slices, int dh) { return filter_gradient_chunk(B, T, heads, slices, dh); }
+int r_start_pauses(int area, long long tiles, long long slabs) { return start_pauses(area, tiles, slabs); }
 int r_overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) { return overlap(a, a_bytes, b, b_bytes); }
 int r_pair_blocks(long long BH, int causal, int blocks) { return pair_blocks(BH, causal, blocks); }
 }
@@ -72,7 +73,7 @@ def _lib():
         lib = C.CDLL(so)
     L, I = C.c_longlong, C.c_int
     for name, args in dict(r_nt_tile=[L, I, I], r_tn_tile=[I, I, L], r_tn_splits=[I, I, L], r_tn_part_blocks=[I, I, L], r_fwd_splits_keys=[L, I, I], r_fwd_takes_64_rows=[L, I, I], r_decode_up_combines=[L, I, I], r_decode_up_lds=[L, I], r_decode_up_lds_limit=[], r_tile_panel=[I, I, I, I, L], r_panel_touches=[I, I, I, I, I], r_tile_panel_us=[I, I, I, I], r_prologue_is_short=[L, I, I, I, I],
-                           r_filter_gradient_chunk=[L, I, I, I, I], r_overlap=[C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t], r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
+                           r_filter_gradient_chunk=[L, I, I, I, I], r_start_pauses=[I, L, L], r_overlap=[C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t], r_dq_splits_keys=[L, I, I], r_dkdv_splits_rows=[L, I, I], r_pair_blocks=[L, I, I],
                            r_stream_takes_256=[L, I, I, I, I], r_generic_attention_rows=[L, I, I, I],
                            r_generic_attention_bwd_16=[L, I, I, I, I, I], r_generic_prologue_takes_8=[L, I, I], r_generic_products_share=[L], r_generic_gradients_share=[L], r_generic_product_looks_ahead=[L, L], r_grad_splits=[L, L], r_gemm_pair=[L, I, I],
                            r_decode_keys_per_split=[L, I, I, I]).items():
@@ -167,6 +168,10 @@ def generic_gradients_share(workgroups):
 
 def filter_gradient_chunk(B, T, heads, slices, dh):
     return _lib().r_filter_gradient_chunk(B, T, heads, slices, dh)
+
+
+def start_pauses(area, tiles, slabs):
+    return _lib().r_start_pauses(area, tiles, slabs)
 
 
 def overlap(a, a_bytes, b, b_bytes):

@@ -327,6 +327,24 @@ def test_projection_tile_is_the_fastest(M, N, K, us):
     assert us[rules.NT_TILES.index(rules.nt_tile(M, N, K))] <= 1.06 * min(us)
 
 
+# M, N, K, tile and us of an attention adjoint with three products behind it, whose workgroups start without a pause, with two, with four
+@pytest.mark.parametrize("M,N,K,tile,us", [(12288, 1536, 1280, "192x192", (1210.9, 1130.3, 1075.1)), (16384, 1536, 2048, "256x192", (1318.6, 1172.6, 1176.9)),
+                                           (6144, 2048, 2048, "192x256", (1109.9, 1059.0, 1060.8)), (10000, 1536, 1280, "192x256", (1129.7, 1080.5, 1085.6))])
+def test_products_start_with_the_pauses_that_keep_the_clock(M, N, K, tile, us):
+    tm, tn = (int(x) for x in tile.split("x"))
+    assert us[(0, 2, 4).index(rules.start_pauses(tm * tn, -(-M // tm) * -(-N // tn), K // 64))] == min(us)
+
+
+def test_projection_cases_start_with_every_number_of_pauses():
+    reached = set()
+    for M, Hq, Hk, dh, E in small.GEMM_CASES:
+        for N, K in (((Hq + 2 * Hk) * dh, E), (E, Hq * dh)):
+            tm, tn = (int(x) for x in rules.nt_tile(M, N, K).split("x"))
+            if tm * tn >= 256 * 128:
+                reached.add(rules.start_pauses(tm * tn, -(-M // tm) * -(-N // tn), K // 64))
+    assert reached == {0, 2, 4}
+
+
 # Mo, No, tokens and us of the small tiles (in the order of rules.TN_TILES[1:]) and of the best split
 TN_MEASURED = [(2048, 2048, 8000, (116.7, 105.6, 82.3), 69.8), (2048, 2048, 4000, (58.6, 55.1, 42.5), 46.7), (2048, 1536, 8000, (89.9, 98.4, 72.8), 57.9),
                (1024, 2048, 8000, (57.3, 52.7, 70.3), 45.1), (2048, 6144, 4000, (173.2, 165.6, 122.2), 90.8), (1024, 2048, 1024, (11.0, 10.2, 12.4), 23.7),
