@@ -155,12 +155,14 @@ struct NewRow {
 
 // ---------------------------------------------------------------------------
 // Transforms of the new token: one workgroup per (sequence, head); heads 0..Hq-1 query, then Hk key, then Hk value.
-// What bounds it is latency, so everything that does not depend on something else is requested or computed first: the
-// filter rows of the first outputs, then (under those loads) the rotary angles, then the rows the taps reach.  LPO = 8 or
-// 16 lanes share an output channel's filter row (128 adjacent bytes per load: the memory pipeline works per cache line)
-// and add their parts on the vector ALU; and no load hides behind a condition (each would be waited for). At B = 32,
+// What bounds it is latency, so every load that does not depend on something else is requested before the first is used:
+// the filter rows of the first outputs, the head's own row and its partners, the rows the taps reach.  The sums of these
+// follow, and behind them the rotary angles (fp64, on d_h / 2 threads), which therefore run under none of the loads.  LPO =
+// 8 or 16 lanes share an output channel's filter row (128 adjacent bytes per load: the memory pipeline works per cache
+// line) and add their parts on the vector ALU; and no load hides behind a condition (each would be waited for). At B = 32,
 // d_h = 128: 14.2 us including the sum of the down-projection's parts, against 12.7 + 4.9 us for one thread per filter row
-// behind a kernel that added them; at B = 1 7.7 against 8.6 + 3.5.  CH = 16- (fp32: 32-) byte chunks of a filter row per lane.
+// behind a kernel that added them; at B = 1 7.7 against 8.6 + 3.5.  CH = 16- (fp32: 32-) byte chunks of a filter row per
+// lane.
 // ---------------------------------------------------------------------------
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float x) {

@@ -49,7 +49,8 @@ inline NtTile nt_tile(long long M, int N, int K, double *us = nullptr) {
 // without pauses, with two, with four: 12288 x 1536 x 1280 on 192 x 192 1070, 990, 936 (46.9, 46.8, 46.3); 16384 x 1536 x 2048 on 256 x 192 1069, 937, 938
 // (83.2, 78.5, 79.5); 6144 x 2048 x 2048 on 192 x 256, one round, 984, 936, 936 (42.0, 41.0, 41.6).  Whole calls: training, 12000 tokens, E =
 // 1536, 12 / 4 heads of 64 1779, 1699, 1630; 16384, 8 / 2 of 128 2851, 2756, 2761; prefill 16384 635.3, 629.1, 631.2; 2 x 3000, 4 / 1 of 256, not
-// causal 181.7, 176.8, 178.0; 4096, plain heads 198.9, 193.5, 200.3; at most 0.6 % longer (6000, 16 / 2 plain heads 244.3, 245.8, 246.9).
+// causal 181.7, 176.8, 178.0; 4096, plain heads 198.9, 193.5, 200.3; 6000, 16 / 2 plain heads 244.3, 245.8, 246.9.  On a machine with power to spare calls take
+// up to 1 % longer with two (4096, plain heads 191.4, 192.7; prefill 16384 629.9, 631.9).
 // So two, and four for several rounds of the smaller ones of these tiles, whose slabs are shorter.  None on less than 7/8 of the CUs, where
 // they cost short calls more than they give (4593 x 1536 x 2048, 216 workgroups: 975 -> 935, 27.7 -> 28.5; 4593 x 2048 x 512 1.5 us of a
 // pass of 75).  Not better: fewer and longer pauses, starts spread over 8 us by CU or XCD (as good behind the product, 2-4
